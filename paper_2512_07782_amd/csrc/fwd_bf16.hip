@@ -534,8 +534,29 @@ static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const 
     return hipGetLastError();
 }
 
+// Which kernel serves a problem.  The persistent one is the better when its rounds of resident workgroups are full of
+// tiles of equal length; what counts is the share of its slots' time that holds work,
+//   (steps of all tiles) / (slots x rounds x steps of the longest tile),
+// a step being a 64-key tile, plus two per tile to fill and drain.  Measured over 24 shapes (N 64 .. 16384, 1 .. 2048
+// tiles, both head dimensions) the split kernel wins below 0.48 (by 1.15 to 2.1) and loses above 0.6 (by up to 1.2).
+// Inside the split kernel: one 32-query block per workgroup while that gives few workgroups (at d = 128 its
+// single-buffered tiles only pay for short bands), 128 queries where the band is long enough to share out.
+static FwdSplit fwd_split_shape(int BH, int N, int d, int w) {
+    const long nq = (N + 127) / 128, cus = device_cu_count(), slots = cus * (d == 64 ? kFwdResident<64> : kFwdResident<128>);
+    const long band = w < N ? w : N, full = (band + 126) / 64 + 2;   // key tiles of a tile whose whole band exists
+    const long ramp = nq < (full - 1) / 2 ? nq : (full - 1) / 2;      // tiles whose band the sequence's start cuts off
+    const long longest = (2 * nq < full ? 2 * nq : full) + 2;
+    const double steps = (double)BH * (double)(ramp * (ramp + 1) + 2 * ramp + (nq - ramp) * longest);
+    const double rounds = (double)((BH * nq + slots - 1) / slots);
+    if (steps >= 0.48 * (double)slots * rounds * (double)longest) return kFwdSplitNone;
+    if ((long)BH * ((N + 31) / 32) <= 5 * cus / 2 && (d == 64 || band <= 1024)) return kFwdSplitNarrow;
+    return band > 1500 ? kFwdSplitWide : kFwdSplitMid;
+}
+
 hipError_t forward_bf16(const void* Q, const void* K, const void* V, const float* c, void* O, float* L,
                         int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s) {
+    if (const FwdSplit shape = fwd_split_shape(B * H, N, d, w))
+        return forward_split_bf16(shape, Q, K, V, c, O, L, B, H, Hkv, N, d, w, scale, s);
     if (d == 128) return launch_fwd<128>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
     return launch_fwd<64>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
 }

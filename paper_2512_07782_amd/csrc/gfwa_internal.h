@@ -25,6 +25,10 @@ hipError_t gate_grad_scan(const float* dc_col, const float* dc_row, float* dalph
 // c, L, dalpha: [B,H,N].
 hipError_t forward_bf16(const void* Q, const void* K, const void* V, const float* c, void* O, float* L,
                         int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
+// The same for few or uneven query tiles, the band of a tile split over groups of waves (fwd_split_bf16.hip).
+enum FwdSplit { kFwdSplitNone = 0, kFwdSplitNarrow, kFwdSplitMid, kFwdSplitWide };  // 32, 64, 128 queries per workgroup
+hipError_t forward_split_bf16(FwdSplit shape, const void* Q, const void* K, const void* V, const float* c, void* O,
+                              float* L, int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
 hipError_t forward_f32(const float* Q, const float* K, const float* V, const float* c, float* O,
                        float* L, int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
 

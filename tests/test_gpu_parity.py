@@ -579,6 +579,21 @@ def test_forward_bf16_partial_last_round(g, oracle, B, H, N, d, w, heads):
     check_bf16_forward(O, L, O_ref, L_ref, tag="partial last round")
 
 
+@pytest.mark.parametrize("B,H,N,d,w,heads", [
+    # few query tiles: 32 queries per workgroup (last block of one row, window inside a block, window past the sequence)
+    (1, 3, 97, 128, 40, [0, 2]), (2, 2, 65, 64, 5000, [0, 3]), (1, 1, 1000, 128, 999, [0]),
+    # 64 queries per workgroup
+    (1, 32, 701, 128, 1024, [0, 31]), (3, 16, 450, 64, 200, [0, 47]),
+    # 128 queries per workgroup: long bands
+    (1, 2, 1801, 128, 1600, [0, 1]), (1, 12, 1930, 64, 1901, [0, 11]),
+])
+def test_forward_bf16_split_band(g, oracle, B, H, N, d, w, heads):
+    note("split band", B, H, N, d, w)
+    wl = gi.custom("split", B, H, N, d, w, "bf16", alpha_mu=-1.5, index=15)
+    O, L, O_ref, L_ref = run_forward(g, oracle, wl, heads=heads)
+    check_bf16_forward(O, L, O_ref, L_ref, tag="split band")
+
+
 # ------------------------------------------------------------------------------------------
 # grouped-query layout
 # ------------------------------------------------------------------------------------------
