@@ -149,9 +149,12 @@ __device__ __forceinline__ void* uniform_ptr(void* p) {
 // must be the same in every lane.  (Scalar base plus a 32-bit offset per lane: one address register instead of two.  In a
 // loop of nothing but MFMAs and such stores this form costs the wave 30 ns per store against 150 ns for the form with
 // a 64-bit address per lane; in the kernels here the two measure the same.)
+// The two wait states behind it are the hardware's: a vector instruction that overwrites the data registers of a store
+// of more than 8 bytes may not follow sooner, and the compiler, which keeps that distance for stores of its own, does
+// not see one in here (without them the d = 64 dK/dV kernel lost elements of dV now and then: up to 2e-2 of its norm).
 template <int IMM = 0>
 __device__ __forceinline__ void stream_store16(void* sbase, unsigned voff, bf16x8 v) {
-    asm volatile("global_store_dwordx4 %0, %1, %2 offset:%3 nt" ::"v"(voff), "v"(v), "s"(sbase), "n"(IMM) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, %2 offset:%3 nt\n\ts_nop 1" ::"v"(voff), "v"(v), "s"(sbase), "n"(IMM) : "memory");
 }
 // s_waitcnt that waits only for vmcnt <= n (gfx9 encoding: expcnt and lgkmcnt fields left at max)
 constexpr int vmcnt_only(int n) { return 0x0f70 | (n & 0xf) | ((n >> 4) << 14); }
