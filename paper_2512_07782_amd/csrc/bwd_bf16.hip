@@ -22,6 +22,8 @@
 // the addend of the single fused multiply-add in front of exp2; the dP accumulator starts from -D.
 // The row sums are analytically zero but are kept: with D formed from the rounded O they carry
 // exactly the error that would otherwise accumulate over the whole suffix in the reverse scan.
+#include <math.h>
+
 #include "gfwa_device.h"
 #include "gfwa_internal.h"
 #include "tile_stage.h"
@@ -909,6 +911,30 @@ size_t backward_bf16_spill_bytes(int B, int H, int N, int d, int w) {
     return (size_t)B * H * nqb * ds_spill_slots(w, nqb) * kSpillBlockBytes;
 }
 
+// Which kernel forms dQ: the split one (FwdSplit shape) for few or uneven tiles, as in the forward.  One 32-query block
+// per workgroup pays while there are few of them (at d = 128, single-buffered tiles, at most one per CU).  With the dS
+// blocks at hand (`spill`) the one-product kernel is the better unless the problem is small (N 2050, 8 heads, d = 128,
+// w = 700: backward 46.3 us split, 48.2 us from blocks, 55.8 us with neither; twice the heads: 61.0, 55.1, 63.3 us).
+static FwdSplit bwd_dq_shape(int BH, int N, int d, int w, bool spill) {
+    const long cus = device_cu_count(), blocks = (long)BH * ((N + 31) / 32);
+    if (query_tile_fill(BH, N, w, 2 * cus) >= 0.48 || (spill && blocks > 5 * cus / 2)) return kFwdSplitNone;
+    return blocks <= (d == 64 ? 5 * cus / 2 : cus) ? kFwdSplitNarrow : kFwdSplitMid;
+}
+// Which kernel forms dK and dV, by estimates of the two in us, fitted to 22 shapes.  The 128-key workgroups walk the
+// 64-query tiles of all G query heads one after another (1.25 us each alone on a CU at d = 64, 2.1 us two on a CU, 1.7 us
+// at d = 128); the 32-key workgroups share the 32-query blocks out over their 8 (4) waves, at 1.1 (1.7) us a block and
+// 5.5 us to start and to sum the partial results, one workgroup per CU at a time.
+static bool bwd_dkv_splits(int BHkv, int G, int N, int d, int w) {
+    if (G > kDkvSplitMaxGroup) return false;
+    const double cus = device_cu_count(), seen = (double)(w < N ? w : N);
+    const double wg0 = (double)BHkv * ((N + 127) / 128), tiles = G * ceil((seen < N - 127 ? seen + 127 : N) / 64.0);
+    const double wg1 = (double)BHkv * ((N + 31) / 32), blocks = G * ceil((seen < N - 31 ? seen + 31 : N) / 32.0);
+    const double per_tile = d == 64 ? (wg0 <= cus ? 1.25 : 2.1 * fmax(1.0, wg0 / (2 * cus))) : 1.7 * fmax(1.0, wg0 / cus);
+    const double whole = 2.0 + tiles * per_tile;
+    const double split = fmax(1.0, wg1 / cus) * (5.5 + ceil(blocks / (d == 64 ? 8 : 4)) * (d == 64 ? 1.1 : 1.7));
+    return split < 0.9 * whole;
+}
+
 template <int D>
 static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO,
                              const float* c, const float* L, void* dQ, void* dK, void* dV, float* dalpha,
@@ -922,15 +948,25 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     double* scan_partial = reinterpret_cast<double*>(ws + 3 * pad);
     const size_t scan_pad = (gate_scan_workspace_bytes(B * H, N) + 255) & ~(size_t)255;
     char* ds_ws = reinterpret_cast<char*>(ws + 3 * pad) + scan_pad;  // only with `spill`
-    constexpr int LPR = D / 8;
-    const unsigned dot_blocks = (unsigned)((rows * LPR + 255) / 256);
-    {
+    const BwdBf16 args = {(const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, c, L, Dv,
+                          (bf16_t*)dQ, (bf16_t*)dK, (bf16_t*)dV, dc_col, dc_row, B, H, Hkv, N, w, scale};
+    const FwdSplit dq_split = bwd_dq_shape(B * H, N, D, w, spill);
+    const bool dkv_split = bwd_dkv_splits(B * Hkv, H / Hkv, N, D, w);
+    if (dq_split || dkv_split) spill = false;  // the dS blocks only travel between the kernels of this file
+    if (dq_split) {
+        if (hipError_t e = bwd_dq_split_bf16(dq_split, args, D, s)) return e;
+    } else {
+        constexpr int LPR = D / 8;
+        const unsigned dot_blocks = (unsigned)((rows * LPR + 255) / 256);
         ProfScope prof(kKernRowDot, s);
         hipLaunchKernelGGL((rowdot_bf16_kernel<D>), dim3(dot_blocks), dim3(256), 0, s, (const bf16_t*)O,
                            (const bf16_t*)dO, Dv, (long)rows);
     }
+    if (dkv_split) {
+        if (hipError_t e = bwd_dkv_split_bf16(args, D, s)) return e;
+    }
     const int nk = (N + 127) / 128;
-    {
+    if (!dkv_split) {
         ProfScope prof(kKernDkv, s);
         if constexpr (D == 128) {  // two waves per SIMD that share a key group (at d = 64 the 4-wave kernel has them already)
             if (spill)
@@ -947,7 +983,7 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
                                (bf16_t*)dK, (bf16_t*)dV, dc_col, N, w, scale, nk, B * Hkv * nk, H, H / Hkv);
     }
     const int nq = (N + 127) / 128;
-    {
+    if (!dq_split) {
         ProfScope prof(kKernDq, s);
         bool launched = false;
         if constexpr (D == 128) {

@@ -534,21 +534,26 @@ static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const 
     return hipGetLastError();
 }
 
-// Which kernel serves a problem.  The persistent one is the better when its rounds of resident workgroups are full of
-// tiles of equal length; what counts is the share of its slots' time that holds work,
-//   (steps of all tiles) / (slots x rounds x steps of the longest tile),
-// a step being a 64-key tile, plus two per tile to fill and drain.  Measured over 24 shapes (N 64 .. 16384, 1 .. 2048
-// tiles, both head dimensions) the split kernel wins below 0.48 (by 1.15 to 2.1) and loses above 0.6 (by up to 1.2).
-// Inside the split kernel: one 32-query block per workgroup while that gives few workgroups (at d = 128 its
-// single-buffered tiles only pay for short bands), 128 queries where the band is long enough to share out.
-static FwdSplit fwd_split_shape(int BH, int N, int d, int w) {
-    const long nq = (N + 127) / 128, cus = device_cu_count(), slots = cus * (d == 64 ? kFwdResident<64> : kFwdResident<128>);
+// The share of `slots` resident workgroups' time that holds work when the 128-query tiles of a problem are taken in
+// rounds:  (steps of all tiles) / (slots x rounds x steps of the longest tile), a step being a 64-key tile, plus
+// two per tile to fill and drain.
+double query_tile_fill(int BH, int N, int w, long slots) {
+    const long nq = (N + 127) / 128;
     const long band = w < N ? w : N, full = (band + 126) / 64 + 2;   // key tiles of a tile whose whole band exists
     const long ramp = nq < (full - 1) / 2 ? nq : (full - 1) / 2;      // tiles whose band the sequence's start cuts off
     const long longest = (2 * nq < full ? 2 * nq : full) + 2;
     const double steps = (double)BH * (double)(ramp * (ramp + 1) + 2 * ramp + (nq - ramp) * longest);
-    const double rounds = (double)((BH * nq + slots - 1) / slots);
-    if (steps >= 0.48 * (double)slots * rounds * (double)longest) return kFwdSplitNone;
+    return steps / ((double)slots * (double)((BH * nq + slots - 1) / slots) * (double)longest);
+}
+
+// Which kernel serves a problem.  The persistent one is the better when its rounds of resident workgroups are full of
+// tiles of equal length.  Measured over 24 shapes (N 64 .. 16384, 1 .. 2048 tiles, both head dimensions) the split
+// kernel wins where they are filled below 0.48 (by 1.15 to 2.1) and loses above 0.6 (by up to 1.2).
+// Inside the split kernel: one 32-query block per workgroup while that gives few workgroups (at d = 128 its
+// single-buffered tiles only pay for short bands), 128 queries where the band is long enough to share out.
+static FwdSplit fwd_split_shape(int BH, int N, int d, int w) {
+    const long cus = device_cu_count(), band = w < N ? w : N;
+    if (query_tile_fill(BH, N, w, cus * (d == 64 ? kFwdResident<64> : kFwdResident<128>)) >= 0.48) return kFwdSplitNone;
     if ((long)BH * ((N + 31) / 32) <= 5 * cus / 2 && (d == 64 || band <= 1024)) return kFwdSplitNarrow;
     return band > 1500 ? kFwdSplitWide : kFwdSplitMid;
 }

@@ -25,12 +25,28 @@ hipError_t gate_grad_scan(const float* dc_col, const float* dc_row, float* dalph
 // c, L, dalpha: [B,H,N].
 hipError_t forward_bf16(const void* Q, const void* K, const void* V, const float* c, void* O, float* L,
                         int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
+double query_tile_fill(int BH, int N, int w, long slots);  // how full rounds of `slots` 128-query tiles are, 0 .. 1
 // The same for few or uneven query tiles, the band of a tile split over groups of waves (fwd_split_bf16.hip).
 enum FwdSplit { kFwdSplitNone = 0, kFwdSplitNarrow, kFwdSplitMid, kFwdSplitWide };  // 32, 64, 128 queries per workgroup
 hipError_t forward_split_bf16(FwdSplit shape, const void* Q, const void* K, const void* V, const float* c, void* O,
                               float* L, int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
 hipError_t forward_f32(const float* Q, const float* K, const float* V, const float* c, float* O,
                        float* L, int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
+
+// Arguments of the bf16 backward kernels (device pointers and sizes as in gfwa_backward_gqa; Dv, dc_col, dc_row: workspace).
+struct BwdBf16 {
+    const __bf16 *Q, *K, *V, *O, *dO;
+    const float *c, *L;
+    float* Dv;
+    __bf16 *dQ, *dK, *dV;
+    float *dc_col, *dc_row;
+    int B, H, Hkv, N, w;
+    float scale;
+};
+constexpr int kDkvSplitMaxGroup = 8;  // query heads per key/value head bwd_dkv_split_bf16 has room for
+// The two passes for few or uneven tiles (bwd_split_bf16.hip).  The dQ pass also forms D_t, so it goes first.
+hipError_t bwd_dq_split_bf16(FwdSplit shape, const BwdBf16& a, int d, hipStream_t s);
+hipError_t bwd_dkv_split_bf16(const BwdBf16& a, int d, hipStream_t s);
 
 // Workspace layout of the backward: three fp32 vectors of B*H*N (each padded to 256 bytes): D, dc_col,
 // dc_row; gate_scan_workspace_bytes(B*H, N) (padded to 256) of segment sums for the gate-gradient scan; with `spill` (bf16, d = 128 only) backward_bf16_spill_bytes() more for the dS blocks.

@@ -666,6 +666,35 @@ def test_gqa_bf16_full_size(g, oracle, ws_variant, name, groups):
     check_grads(got, ref, 1e-2, name)
 
 
+@pytest.mark.parametrize("B,H,Hkv,N,d,w,groups", [
+    # query tiles and key tiles shared out over groups of waves: 32 and 64 queries per workgroup, 32 keys per workgroup
+    (1, 8, 8, 1101, 128, 700, [0, 7]), (3, 16, 16, 450, 64, 200, [0, 47]), (1, 4, 4, 1000, 128, 333, [0, 3]),
+    # groups of 8 query heads (the most the split dK/dV pass has room for) and of 9; a last key block of one key
+    (1, 8, 1, 769, 64, 300, [0]), (1, 9, 1, 257, 64, 100, [0]), (1, 8, 1, 417, 128, 5000, [0]),
+])
+def test_backward_bf16_split(g, oracle, ws_variant, B, H, Hkv, N, d, w, groups):
+    note("backward split", ws_variant, B, H, Hkv, N, d, w)
+    wl = gi.custom("bsplit", B, H, N, d, w, "bf16", alpha_mu=-1.0, index=14, backward=True, kv_heads=Hkv)
+    got, ref = run_gqa(g, oracle, wl, groups=groups)
+    check_bf16_forward(got["O"], got["L"], ref["O"], ref["L"], tag="split")
+    check_grads(got, ref, 1e-2, "split")
+
+
+def test_backward_d64_two_workgroups_per_cu_repeats_bit_exactly(g):
+    # rows leave through inline-assembly stores; with two workgroups of the dK/dV pass on a CU a missing wait state
+    # between a store and the next write of its data registers showed as a few wrong elements of dV
+    B, H, N, d, w = 4, 8, 2050, 64, 700
+    wl = gi.custom("repeat", B, H, N, d, w, "bf16", alpha_mu=-2.0, index=13, backward=True)
+    ins = gi.make_inputs(wl)
+    Q, K, V, dO = (dev(ins[t], "bf16") for t in ("Q", "K", "V", "dO"))
+    c = g.gfwa_gate_prefix(dev(ins["alpha"], "f32"))
+    O, L = g.gfwa_forward(Q, K, V, c, w, wl.scale)
+    first = g.gfwa_backward(Q, K, V, O, dO, c, L, w, wl.scale)
+    for _ in range(4):
+        for a, b in zip(g.gfwa_backward(Q, K, V, O, dO, c, L, w, wl.scale), first):
+            assert torch.equal(a, b)
+
+
 def test_gqa_with_one_head_per_group_is_the_plain_call(g, oracle):
     wl = gi.custom("gqa1", 2, 3, 700, 128, 200, "bf16", alpha_mu=-1.0, index=14, backward=True)
     ins = {t: dev(gi.make_tensor(wl, t), "bf16") for t in ("Q", "K", "V", "dO")}
