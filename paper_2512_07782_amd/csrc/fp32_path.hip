@@ -1,14 +1,21 @@
 // fp32 storage path of GatedFWA on gfx950: forward (paper Alg. 2) and backward (Alg. 3) with all
 // arithmetic in fp32, for problems that need fp32 accuracy; the bf16 MFMA kernels are the throughput path.
-// Two sets of kernels.  The matrix-core set (v_mfma_f32_32x32x2_f32, the structure of the bf16 kernels: a lane
-// owns a query or a key, the second product takes the first one's accumulator registers as its operand) serves
-// everything but tiny problems.  The one-wave-per-row set (plain FMA: lanes first split the keys of a 64-wide
+// Two sets of kernels.  The matrix-core set (bf16 MFMAs on operands split into three pieces, the structure of the bf16
+// kernels: a lane owns a query or a key, the second product takes the first one's accumulator registers as its operand)
+// serves everything but tiny problems.  The one-wave-per-row set (plain FMA: lanes first split the keys of a 64-wide
 // chunk to form the logits, then split the head dimension to accumulate the output row) has a launch's latency
 // and serves those; forward_f32 / backward_f32 choose (f32_use_mfma).
+#include <math.h>
+
+#include <type_traits>
+
 #include "gfwa_device.h"
 #include "gfwa_internal.h"
+#include "split_band.h"
 
 namespace gfwa {
+
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kF32Waves = 4;
 
@@ -82,76 +89,238 @@ __global__ __launch_bounds__(64 * kF32Waves) void fwd_f32_kernel(
 }
 
 // ==========================================================================================
-// fp32 matrix-core kernels.  v_mfma_f32_32x32x2_f32: D[32x32] += A[32x2] * B[2x32], all fp32:
-//   A: lane l holds row (l % 32), k = l / 32        B: lane l holds column (l % 32), k = l / 32
-//   D: as the bf16 instruction: lane l, register v holds column (l % 32), row acc_row(v, l / 32)
-// A contraction over the head dimension takes D / 2 of them; the half h of a wave supplies, in step
-// 4 m + j, the element d = 8 m + 4 h + j of both operands, so a lane's four values of a group m are
-// 16 contiguous bytes of a row.  The second product of each kernel takes an accumulator block as its B
-// operand as it stands (register v of the two halves holds rows acc_row(v, 0) and acc_row(v, 1): the two
-// k of one step) and gathers the matching rows of the other operand from LDS, 4 bytes per lane.
+// fp32 matrix-core kernels.  The part multiplies bf16 sixteen times as fast as fp32, so every product is formed from
+// three bf16 pieces per operand: x = x0 + x1 + x2 holds all 24 bits of an fp32 value (each piece is what the pieces
+// before it leave over, rounded to bf16; values below 2^-110 reach the end of bf16's exponent range), bf16 products are
+// exact in fp32, and
+//   a b = a0 b0 + (a0 b1 + a1 b0) + (a1 b1 + a0 b2 + a2 b0) + what is left out, at most 2^-23 |a b|, 2^-26 typically.
+// Six bf16 MFMAs of 16 terms take 192 cycles where eight fp32 MFMAs of 2 terms take 512, and add to the accumulator
+// less often: against fp64 the outputs are closer than with fp32 MFMAs (B1 H3 N1500 d128 w700, error over norm: O 1.0e-7, was
+// 2.2e-7; dQ 1.7e-7, was 3.4e-7; dK 2.2e-7, was 4.1e-7; dV 1.9e-7, was 3.3e-7; dalpha 1.5e-6, was 1.9e-6).
+// Layouts are those of the bf16 kernels (mfma32): a lane owns a query or a key, the second product of each kernel takes
+// the first one's accumulator registers, split in place, as its B operand.  Operands are split once: resident rows
+// (of Q; Q and dO; K and V) when the workgroup starts, streamed tiles on their way into LDS by the threads that fetched them.
+// Measured, B2 H16 N4096 d128 w1024, with fp32 MFMAs / now: forward 642 / 334 us, dK/dV 1410 / 586 us, dQ 1001 / 470 us.
+// What bounds them: executed bf16 products at 1.1 to 1.3 PFLOP/s, the matrix pipe busy 60 to 65 % of the cycles at 1.85 GHz,
+// the clock the part holds under this load (2.03 GHz with the pipe at 53 %).
 // ==========================================================================================
-__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+
+// two values -> their three bf16 pieces, packed
+struct Split2 {
+    unsigned p[3];
+};
+__device__ __forceinline__ Split2 split2(float x, float y) {
+    auto pack = [](float a, float b) { return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2)); };
+    auto lower = [](unsigned p) { return __uint_as_float(p << 16); };
+    auto upper = [](unsigned p) { return __uint_as_float(p & 0xffff0000u); };
+    Split2 s;
+    s.p[0] = pack(x, y);
+    x -= lower(s.p[0]);
+    y -= upper(s.p[0]);
+    s.p[1] = pack(x, y);
+    s.p[2] = pack(x - lower(s.p[1]), y - upper(s.p[1]));
+    return s;
+}
+// eight values (of a row, or the registers 8 c2 .. 8 c2 + 7 of an accumulator block) -> the pieces of an operand fragment
+template <typename F>
+__device__ __forceinline__ void split_frag(F&& value, bf16x8 (&f)[3]) {
+    u32x4 p[3];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const Split2 t = split2(value(2 * j), value(2 * j + 1));
+#pragma unroll
+        for (int k = 0; k < 3; ++k) p[k][j] = t.p[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) f[k] = __builtin_bit_cast(bf16x8, p[k]);
+}
+__device__ __forceinline__ void split_row(const float* g, bf16x8 (&f)[3]) {
+    const f32x4 x0 = *reinterpret_cast<const f32x4*>(g), x1 = *reinterpret_cast<const f32x4*>(g + 4);
+    split_frag([&](int j) __attribute__((always_inline)) { return j < 4 ? x0[j & 3] : x1[j & 3]; }, f);
+}
+__device__ __forceinline__ void split_acc(const f32x16& s, int c2, bf16x8 (&f)[3]) {
+    split_frag([&](int j) __attribute__((always_inline)) { return s[8 * c2 + j]; }, f);
+}
+// 32 rows of a [N, D] matrix in LDS, as three bf16 planes with the swizzle of tile_off
+template <int D>
+struct SplitTile {
+    static constexpr int kPlane = 32 * D * 2;
+    alignas(256) char p[3][kPlane];
+};
+// piece k of a fragment of such a tile (row_frag, col_frag of split_band.h; `at`: the lane's address in plane 0)
+template <int D>
+__device__ __forceinline__ bf16x8 split_row_frag(unsigned at, int kc, int k) { return row_frag<D>(at, 32 * k, kc); }
+template <int D>
+__device__ __forceinline__ bf16x8 split_col_frag(unsigned at, int r0, int db, int k) { return col_frag<D>(at, 32 * k + r0, db); }
+
+// The product of the 32 rows of a tile with the resident rows b over the head dimension.  All products of smaller pieces
+// come first, over the whole head dimension, then the a0 b0: added in between, the small ones lose bits to an accumulator
+// that is already large (error of O 1.8e-7 of its norm instead of 1.0e-7, of dQ 2.8e-7 instead of 1.7e-7; the second
+// reading of the a0 costs 1 % of the time).
+// QROWS: the tile holds rows of Q or dO, b keys or values; otherwise the other way round.  Either way the same products
+// are added in the same order, so that the dK/dV and the dQ kernel form the same dS, bit by bit, and its row and column
+// sums cancel in the suffix sums of the gate gradient.
+// A fragment is read two chunks ahead, into the registers of the one that has just been used (LDS takes 150 to 300 cycles
+// with eight waves at it, a chunk's products 160).  `beside(kc)` is what else may be placed beside the products, `late` runs
+// in front of the second pass (reads whose results are needed right after it).
+template <int D, bool QROWS, typename F0, typename F1>
+__device__ __forceinline__ f32x16 tile_dot(unsigned at, const bf16x8 (&b)[D / 16][3], F0&& beside, F1&& late) {
+    constexpr int KC = D / 16;
+    f32x16 c;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) c[v] = 0.f;
+    bf16x8 f[2][3];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) f[i][k] = split_row_frag<D>(at, i, k);
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) {
+        bf16x8(&a)[3] = f[kc & 1];
+        // piece k of two chunks further on; of the last two chunks' places the a0 of chunks 0 .. 3 of the second pass take four
+        auto refill = [&](int k) __attribute__((always_inline)) {
+            if (kc + 2 < KC) a[k] = split_row_frag<D>(at, kc + 2, k);
+            else if (k < 2) a[k] = split_row_frag<D>(at, 2 * (kc & 1) + k, 0);
+        };
+        c = QROWS ? mfma32(a[2], b[kc][0], c) : mfma32(a[0], b[kc][2], c);
+        c = QROWS ? mfma32(a[0], b[kc][2], c) : mfma32(a[2], b[kc][0], c);
+        __builtin_amdgcn_sched_barrier(0);
+        refill(2);
+        c = mfma32(a[1], b[kc][1], c);
+        c = QROWS ? mfma32(a[1], b[kc][0], c) : mfma32(a[0], b[kc][1], c);
+        beside(kc);
+        __builtin_amdgcn_sched_barrier(0);
+        if (QROWS) refill(1);
+        c = QROWS ? mfma32(a[0], b[kc][1], c) : mfma32(a[1], b[kc][0], c);
+        __builtin_amdgcn_sched_barrier(0);
+        if (!QROWS) refill(1);
+        refill(0);
+    }
+    late();
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) {
+        bf16x8& a = f[(kc >> 1) & 1][kc & 1];
+        c = mfma32(a, b[kc][0], c);
+        __builtin_amdgcn_sched_barrier(0);
+        if (kc + 4 < KC) a = split_row_frag<D>(at, kc + 4, 0);
+    }
+    return c;
+}
+// The first fragment of a transposed tile (row half C0), to be read before tile_axpy is reached.
+struct ColFrag {
+    bf16x8 a0, a1, a2;
+};
+template <int D, int C0>
+__device__ __forceinline__ ColFrag first_col(unsigned at) {
+    return {split_col_frag<D>(at, 16 * C0, 0, 0), split_col_frag<D>(at, 16 * C0, 0, 1), split_col_frag<D>(at, 16 * C0, 0, 2)};
+}
+// acc[db] += (tile^T, 32-column block db) x over the row halves C0 .. C1 - 1, x an accumulator block as the B operand.  xf: the
+// pieces of the first half; those of the second are formed between the products.  `beside(i)`: as above, (C1 - C0) D / 32
+// times.
+template <int D, int C0, int C1, typename F>
+__device__ __forceinline__ void tile_axpy(unsigned at, const f32x16& x, bf16x8 (&xf)[3], ColFrag f, f32x16 (&acc)[D / 32], F&& beside) {
+    constexpr int DB = D / 32, NF = (C1 - C0) * DB;
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+        const bool more = i + 1 < NF;
+        const int r0 = 16 * (C0 + (i + 1) / DB), db = (i + 1) % DB;
+        f32x16& c = acc[i % DB];
+        c = mfma32(f.a2, xf[0], c);
+        c = mfma32(f.a1, xf[1], c);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) f.a2 = split_col_frag<D>(at, r0, db, 2);
+        c = mfma32(f.a1, xf[0], c);
+        beside(i);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) f.a1 = split_col_frag<D>(at, r0, db, 1);
+        const bf16x8 a0 = f.a0;
+        if (more) f.a0 = split_col_frag<D>(at, r0, db, 0);
+        c = mfma32(a0, xf[2], c);
+        c = mfma32(a0, xf[1], c);
+        c = mfma32(a0, xf[0], c);
+        __builtin_amdgcn_sched_barrier(0);
+        if (C1 - C0 == 2 && i + 1 == DB) split_acc(x, C0 + 1, xf);
+    }
 }
 
-// LDS tile of 32 rows x D floats with a row pitch of D + 4 floats: every address is a per-lane base plus a
-// compile-time offset, the 16-byte reads of 32 rows at one column and the 4-byte gathers of 32 consecutive columns
-// of rows r (half 0) and r + 4 (half 1) conflict at most two ways - beside MFMAs of 64 cycles that is nothing.
-template <int D>
-constexpr int kF32Pitch = D + 4;
-template <int D>
-__device__ __forceinline__ constexpr int f32_tile_off(int row, int col) { return row * kF32Pitch<D> + col; }
-
-constexpr int kF32Threads = 256;  // 4 waves: 32 queries (or keys) each
-
-// One 32-row tile of a [N, D] matrix per workgroup step: 16-byte pieces, a thread takes every 256th.
-template <int D>
-struct F32TileRegs {
-    static constexpr int kPieces = 32 * (D / 4) / kF32Threads;
-    f32x4 r[kPieces];
-    __device__ __forceinline__ void fetch(const float* M, int row0, int N, int tid) {  // rows past N read row N-1
-#pragma unroll
-        for (int i = 0; i < kPieces; ++i) {
-            const int q = tid + kF32Threads * i, row = q / (D / 4), cc = q % (D / 4);
-            r[i] = *reinterpret_cast<const f32x4*>(M + (size_t)min(row0 + row, N - 1) * D + 4 * cc);
-        }
+// 32-row tiles of [N, D] matrices on their way through the registers of a workgroup of T threads: 16-byte pieces, a
+// thread takes every T-th (rows row, row + kStep, ..).
+template <int D, int T>
+struct F32TileMover {
+    static constexpr int kPieces = 32 * (D / 4) / T, kStep = T / (D / 4);
+    static_assert(kStep % 16 == 0 || kStep == 8, "the swizzle has period 16, eight rows further on it differs by chunk bit 1");
+    int row, col, at;  // first row, its column in bytes, LDS address inside a plane
+    __device__ __forceinline__ void init(int tid) {
+        row = tid / (D / 4);
+        col = 16 * (tid % (D / 4));
+        at = tile_off<D>(row, (tid % (D / 4)) >> 1) + 8 * (tid & 1);
     }
-    __device__ __forceinline__ void stash(float* tile, int tid) const {
+    // (`part` of n: those of the pieces that belong there)
+    __device__ __forceinline__ void fetch(f32x4 (&r)[kPieces], const float* M, int row0, int N, int part = 0, int n = 1) const {  // rows past N read row N-1
+        const char* first = reinterpret_cast<const char*>(M + (size_t)row0 * D);
 #pragma unroll
-        for (int i = 0; i < kPieces; ++i) {
-            const int q = tid + kF32Threads * i, row = q / (D / 4), cc = q % (D / 4);
-            *reinterpret_cast<f32x4*>(tile + f32_tile_off<D>(row, 4 * cc)) = r[i];
+        for (int i = part * kPieces / n; i < (part + 1) * kPieces / n; ++i)
+            r[i] = *reinterpret_cast<const f32x4*>(first + (unsigned)(min(row + i * kStep, N - 1 - row0) * (D * 4) + col));
+    }
+    __device__ __forceinline__ void stash(const f32x4 (&r)[kPieces], SplitTile<D>& tile, int part, int n) const {
+#pragma unroll
+        for (int i = part * kPieces / n; i < (part + 1) * kPieces / n; ++i) {
+            char* to = tile.p[0] + (kStep == 8 && (i & 1) ? at ^ 32 : at) + i * kStep * (D * 2);
+            const Split2 a = split2(r[i][0], r[i][1]), b = split2(r[i][2], r[i][3]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x2*>(to + k * SplitTile<D>::kPlane) = u32x2{a.p[k], b.p[k]};
         }
     }
 };
 
-// ---- forward (Alg. 2): a workgroup owns 128 queries, a wave 32 of them, a lane one query (both halves of the
-// wave hold it, with complementary keys).  S^T = K Q^T with the Q fragments in registers, the running maximum
+// ---- forward (Alg. 2): a workgroup of NW waves owns 32 NW queries, a wave 32 of them, a lane one query (both halves of
+// the wave hold it, with complementary keys).  S^T = K Q^T with the Q fragments in registers, the running maximum
 // and sum per lane, O^T += V^T P^T with P^T taken from the S^T accumulator registers.
+// Tiles are double buffered, the next one is split and stored between the PV products, one barrier per block.  With eight
+// waves two share a SIMD, and waves 0 .. 3 have the higher issue priority: they take the matrix pipe first and do their
+// softmax while the others form S, and the others do theirs beside the first ones' PV products.  (Two workgroups of four
+// waves per CU instead, whose waves all come to the softmax at the same time and split every tile twice: 452 us.)
 template <int D>
-__global__ __launch_bounds__(kF32Threads, 2) void fwd_f32_mfma_kernel(
+struct F32FwdSmem {
+    SplitTile<D> k[2], v[2];
+    alignas(16) float c[2][32];
+};
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 ? 1 : 2) void fwd_f32_mfma_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ c, float* __restrict__ O, float* __restrict__ L, int N, int w, float scale,
     int num_qtiles, int total_tiles, int H, int G) {
-    constexpr int NM = D / 8, DB = D / 32;
-    __shared__ __align__(16) float Ks[32 * kF32Pitch<D>];
-    __shared__ __align__(16) float Vs[32 * kF32Pitch<D>];
-    __shared__ float cs[32];
+    constexpr int KC = D / 16, DB = D / 32, BQ = 32 * NW;
+    extern __shared__ __align__(256) char smem_raw[];
+    auto& sm = *reinterpret_cast<F32FwdSmem<D>*>(smem_raw);
     const int tile = xcd_remap(blockIdx.x, total_tiles);
-    const int bh = tile / num_qtiles, q0 = (tile % num_qtiles) * 128;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, h = lane >> 5, lq = lane & 31;
+    const int bh = tile / num_qtiles, q0 = (tile % num_qtiles) * BQ;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lq = lane & 31;
     const int qw0 = q0 + 32 * wv, t = qw0 + lq, tc = min(t, N - 1);
     const size_t ho = (size_t)bh * N * D, kvo = (size_t)kv_head_of(bh, H, G) * N * D;
     const float *Kh = K + kvo, *Vh = V + kvo, *ch = c + (size_t)bh * N;
+    if (NW == 8 && wv < 4) __builtin_amdgcn_s_setprio(1);
 
-    float qf[D / 2];
+    const int jb_lo = max(0, q0 - w + 1) / 32, jb_hi = (min(N, q0 + BQ) - 1) / 32;
+    using Mover = F32TileMover<D, 64 * NW>;
+    Mover mv;
+    mv.init(tid);
+    f32x4 kreg[Mover::kPieces], vreg[Mover::kPieces];
+    float creg = 0.f;
+    auto fetch = [&](int jb, int part = 0, int n = 1) __attribute__((always_inline)) {
+        mv.fetch(kreg, Kh, 32 * jb, N, part, n);
+        mv.fetch(vreg, Vh, 32 * jb, N, part, n);
+        if (part == 0 && tid < 32) creg = ch[min(32 * jb + tid, N - 1)];
+    };
+    auto stash_share = [&](int buf, int i, int n) __attribute__((always_inline)) {
+        mv.stash(kreg, sm.k[buf], i, n);
+        mv.stash(vreg, sm.v[buf], i, n);
+    };
+    fetch(jb_lo);
+    bf16x8 qf[KC][3];
 #pragma unroll
-    for (int m = 0; m < NM; ++m) {
-        const f32x4 q4 = *reinterpret_cast<const f32x4*>(Q + ho + (size_t)tc * D + 8 * m + 4 * h);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) qf[4 * m + j] = q4[j];
-    }
+    for (int kc = 0; kc < KC; ++kc) split_row(Q + ho + (size_t)tc * D + 16 * kc + 8 * h, qf[kc]);
+    __builtin_amdgcn_sched_barrier(0);
     const float ct = ch[tc];
     f32x16 o[DB];
 #pragma unroll
@@ -160,41 +329,47 @@ __global__ __launch_bounds__(kF32Threads, 2) void fwd_f32_mfma_kernel(
         for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
     float mrun = kNegBig, lh = 0.f;  // lh: the sum over this half's keys
 
-    const int jb_lo = max(0, q0 - w + 1) / 32, jb_hi = (min(N, q0 + 128) - 1) / 32;
-    F32TileRegs<D> kreg, vreg;
-    float creg = 0.f;
-    auto fetch = [&](int jb) __attribute__((always_inline)) {
-        kreg.fetch(Kh, 32 * jb, N, tid);
-        vreg.fetch(Vh, 32 * jb, N, tid);
-        if (tid < 32) creg = ch[min(32 * jb + tid, N - 1)];
+    int r_off = row_frag_off<D>(lane), t_off = col_frag_off<D>(lane);
+    stash_share(0, 0, 1);
+    if (tid < 32) sm.c[0][tid] = creg;
+    wg_barrier();
+    auto end_step = [&](int buf) __attribute__((always_inline)) {
+        if (tid < 32) sm.c[buf ^ 1][tid] = creg;
+        wg_barrier();
     };
-    fetch(jb_lo);
-    for (int jb = jb_lo; jb <= jb_hi; ++jb) {
-        __syncthreads();  // the previous block's readers are done
-        kreg.stash(Ks, tid);
-        vreg.stash(Vs, tid);
-        if (tid < 32) cs[tid] = creg;
-        __syncthreads();
-        if (jb < jb_hi) fetch(jb + 1);
-        const int kb0 = 32 * jb;
-        if (!((kb0 <= qw0 + 31) && (kb0 + 31 > qw0 - w) && (qw0 < N))) continue;  // outside this wave's band
-        f32x16 s;
+    auto idle_step = [&](int jb) __attribute__((always_inline)) {  // no block of this wave's band: only its share of the tile
+        const int buf = (jb - jb_lo) & 1;
+        fetch(min(jb + 1, jb_hi));
+        stash_share(buf ^ 1, 0, 1);
+        end_step(buf);
+    };
+    // (three loops: with a branch around the computing step inside one loop the compiler copies the accumulators)
+    const int act_lo = qw0 < N ? max(0, qw0 - w + 1) / 32 : jb_hi + 1, act_hi = min(qw0 / 32, jb_hi);
+    int jb = jb_lo;
+    for (; jb < act_lo; ++jb) idle_step(jb);
+    for (; jb <= act_hi; ++jb) {
+        // (the addresses derived from these are recomputed in every block instead of living in registers across the loop)
+        GFWA_PIN(r_off);
+        GFWA_PIN(t_off);
+        const int kb0 = 32 * jb, buf = (jb - jb_lo) & 1;
+        const unsigned kt = (unsigned)(uintptr_t)sm.k[buf].p[0] + r_off, vt = (unsigned)(uintptr_t)sm.v[buf].p[0] + t_off;
+        f32x16 g;
+        bf16x8 pf[3];
+        f32x16 s = tile_dot<D, false>(
+            kt, qf, [&](int kc) __attribute__((always_inline)) { fetch(min(jb + 1, jb_hi), kc, KC); },
+            [&]() __attribute__((always_inline)) { acc_init_rows(g, sm.c[buf], 0, h); });
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+        for (int v = 0; v < 16; ++v) s[v] = fmaf(scale, s[v], g[v] - ct);
+        if (__builtin_expect(!(kb0 + 31 <= qw0 && kb0 > qw0 + 31 - w), 0)) {
 #pragma unroll
-        for (int m = 0; m < NM; ++m) {
-            const f32x4 k4 = *reinterpret_cast<const f32x4*>(Ks + f32_tile_off<D>(lq, 8 * m + 4 * h));
-#pragma unroll
-            for (int j = 0; j < 4; ++j) s = mfma_f32(k4[j], qf[4 * m + j], s);
+            for (int v = 0; v < 16; ++v) {
+                const int i = kb0 + acc_row(v, h);
+                s[v] = (i <= t && i > t - w) ? s[v] : -INFINITY;
+            }
         }
         float mx = -INFINITY;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int r = acc_row(v, h), i = kb0 + r;
-            const float x = fmaf(scale, s[v], cs[r] - ct);
-            s[v] = (i <= t && i > t - w) ? x : -INFINITY;
-            mx = fmaxf(mx, s[v]);
-        }
+        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[v]);
         // exp through the hardware exp2: the argument's rounding (2^-24 |x| log2 e) only matters for
         // probabilities that are themselves negligible
         const float mnew = fmaxf(mrun, xhalf_max(mx));
@@ -213,12 +388,12 @@ __global__ __launch_bounds__(kF32Threads, 2) void fwd_f32_mfma_kernel(
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o[db][v] *= a;
         }
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[db] = mfma_f32(Vs[f32_tile_off<D>(acc_row(v, h), 32 * db + lq)], s[v], o[db]);
-        }
+        const ColFrag f = first_col<D, 0>(vt);
+        split_acc(s, 0, pf);
+        tile_axpy<D, 0, 2>(vt, s, pf, f, o, [&](int i) __attribute__((always_inline)) { stash_share(buf ^ 1, i, 2 * DB); });
+        end_step(buf);
     }
+    for (; jb <= jb_hi; ++jb) idle_step(jb);
     const float l = xhalf_sum(lh);
     if (t < N) {
         float* orow = O + ho + (size_t)t * D;
@@ -235,239 +410,379 @@ __global__ __launch_bounds__(kF32Threads, 2) void fwd_f32_mfma_kernel(
     }
 }
 
-// ---- dQ and the row sums of dS (Alg. 3, query loop): the forward's layout.  S^T = K Q^T and dP^T = V dO^T with the
-// Q and dO fragments in registers, dS^T = P^T (dP^T - D) in the accumulator registers, dQ^T += K^T dS^T.
+// ---- backward.  The resident rows take 96 registers per matrix at d = 128, so two waves (of one SIMD: waves wv and
+// wv + 4 of eight) share 32 queries or keys.  Wave 0 of a pair holds the rows of the matrix that forms S and turns S into P,
+// wave 1 those that form dP; what they need of each other travels through LDS.  The products with dS are one block behind
+// (the tile they need, K or Q, is kept in a ring of three), so that a step has one barrier and neither wave waits for
+// the other inside it: one's exponentials and splits run beside the other's MFMAs.  (In step, with a second barrier
+// between the first and the second products: dK/dV 606 us, dQ 500 us.)
+constexpr int kF32BwdThreads = 512;
 template <int D>
-__global__ __launch_bounds__(kF32Threads, D == 128 ? 1 : 2) void bwd_dq_f32_mfma_kernel(
+struct F32BwdSmem {
+    SplitTile<D> a[3], b[2];           // dK/dV: Q, dO; dQ: K, V
+    f32x4 x[2][4][4][64];              // per pair, one block behind: P (dK/dV); half of P and half of dP - D (dQ)
+    alignas(16) float v[3][2][32];     // up to three values per row of the tile
+};
+__device__ __forceinline__ int next3(int i) { return i == 2 ? 0 : i + 1; }
+
+// dQ and the row sums of dS (Alg. 3, query loop): the forward's layout.  S^T = K Q^T (wave 0 of a pair) and
+// dP^T = V dO^T (wave 1), then both take half of the block's keys: dS^T = P^T (dP^T - D), dQ^T += K^T dS^T.
+template <int D>
+__global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dq_f32_mfma_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
     const float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dc_row, int N, int w, float scale,
     int num_qtiles, int total_tiles, int H, int G) {
-    constexpr int NM = D / 8, DB = D / 32;
-    __shared__ __align__(16) float Ks[32 * kF32Pitch<D>];
-    __shared__ __align__(16) float Vs[32 * kF32Pitch<D>];
-    __shared__ float cs[32];
+    constexpr int KC = D / 16, DB = D / 32;
+    extern __shared__ __align__(256) char smem_raw[];
+    auto& sm = *reinterpret_cast<F32BwdSmem<D>*>(smem_raw);
     const int tile = xcd_remap(blockIdx.x, total_tiles);
     const int bh = tile / num_qtiles, q0 = (tile % num_qtiles) * 128;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, h = lane >> 5, lq = lane & 31;
-    const int qw0 = q0 + 32 * wv, t = qw0 + lq, tc = min(t, N - 1);
-    const size_t ho = (size_t)bh * N * D, kvo = (size_t)kv_head_of(bh, H, G) * N * D;
-    const float *Kh = K + kvo, *Vh = V + kvo, *ch = c + (size_t)bh * N;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lq = lane & 31;
+    const int qg = wv & 3;
+    auto run = [&](auto role_c) __attribute__((always_inline)) {
+        constexpr int role = decltype(role_c)::value;
+        const int qw0 = q0 + 32 * qg, t = qw0 + lq, tc = min(t, N - 1);
+        const size_t ho = (size_t)bh * N * D, kvo = (size_t)kv_head_of(bh, H, G) * N * D;
+        const float *Kh = K + kvo, *Vh = V + kvo, *ch = c + (size_t)bh * N;
 
-    float qf[D / 2], gf[D / 2];
+        const int jb_lo = max(0, q0 - w + 1) / 32, jb_hi = (min(N, q0 + 128) - 1) / 32;
+        using Mover = F32TileMover<D, kF32BwdThreads>;
+        Mover mv;
+        mv.init(tid);
+        f32x4 kreg[Mover::kPieces], vreg[Mover::kPieces];
+        float creg = 0.f;
+        auto fetch = [&](int jb, int part = 0, int n = 1) __attribute__((always_inline)) {
+            mv.fetch(kreg, Kh, 32 * jb, N, part, n);
+            mv.fetch(vreg, Vh, 32 * jb, N, part, n);
+            if (part == 0 && tid < 32) creg = ch[min(32 * jb + tid, N - 1)];
+        };
+        int buf = 0, a_slot = 0;  // of the current tile
+        auto stash_share = [&](int i, int n) __attribute__((always_inline)) {  // into the next one's
+            mv.stash(kreg, sm.a[next3(a_slot)], i, n);
+            mv.stash(vreg, sm.b[buf ^ 1], i, n);
+        };
+        fetch(jb_lo);
+        bf16x8 rf[KC][3];
 #pragma unroll
-    for (int m = 0; m < NM; ++m) {
-        const f32x4 q4 = *reinterpret_cast<const f32x4*>(Q + ho + (size_t)tc * D + 8 * m + 4 * h);
-        const f32x4 g4 = *reinterpret_cast<const f32x4*>(dO + ho + (size_t)tc * D + 8 * m + 4 * h);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            qf[4 * m + j] = q4[j];
-            gf[4 * m + j] = g4[j];
-        }
-    }
-    const float ct = ch[tc], Lt = L[(size_t)bh * N + tc], Dt = Dv[(size_t)bh * N + tc];
-    f32x16 acc[DB];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[db][v] = 0.f;
-    float rs = 0.f;
-
-    const int jb_lo = max(0, q0 - w + 1) / 32, jb_hi = (min(N, q0 + 128) - 1) / 32;
-    F32TileRegs<D> kreg, vreg;
-    float creg = 0.f;
-    auto fetch = [&](int jb) __attribute__((always_inline)) {
-        kreg.fetch(Kh, 32 * jb, N, tid);
-        vreg.fetch(Vh, 32 * jb, N, tid);
-        if (tid < 32) creg = ch[min(32 * jb + tid, N - 1)];
-    };
-    fetch(jb_lo);
-    for (int jb = jb_lo; jb <= jb_hi; ++jb) {
-        __syncthreads();
-        kreg.stash(Ks, tid);
-        vreg.stash(Vs, tid);
-        if (tid < 32) cs[tid] = creg;
-        __syncthreads();
-        if (jb < jb_hi) fetch(jb + 1);
-        const int kb0 = 32 * jb;
-        if (!((kb0 <= qw0 + 31) && (kb0 + 31 > qw0 - w) && (qw0 < N))) continue;
-        f32x16 s, dp;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) s[v] = dp[v] = 0.f;
-#pragma unroll
-        for (int m = 0; m < NM; ++m) {
-            const f32x4 k4 = *reinterpret_cast<const f32x4*>(Ks + f32_tile_off<D>(lq, 8 * m + 4 * h));
-#pragma unroll
-            for (int j = 0; j < 4; ++j) s = mfma_f32(k4[j], qf[4 * m + j], s);
-        }
-#pragma unroll
-        for (int m = 0; m < NM; ++m) {
-            const f32x4 v4 = *reinterpret_cast<const f32x4*>(Vs + f32_tile_off<D>(lq, 8 * m + 4 * h));
-#pragma unroll
-            for (int j = 0; j < 4; ++j) dp = mfma_f32(v4[j], gf[4 * m + j], dp);
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int r = acc_row(v, h), i = kb0 + r;
-            const float x = fmaf(scale, s[v], cs[r] - ct);
-            const float p = (i <= t && i > t - w) ? fast_exp2((x - Lt) * kLog2e) : 0.f;
-            s[v] = p * (dp[v] - Dt);
-            rs += s[v];
-        }
+        for (int kc = 0; kc < KC; ++kc) split_row((role == 0 ? Q : dO) + ho + (size_t)tc * D + 16 * kc + 8 * h, rf[kc]);
+        __builtin_amdgcn_sched_barrier(0);
+        const float ct = ch[tc], Lt = L[(size_t)bh * N + tc], Dt = Dv[(size_t)bh * N + tc];
+        f32x16 acc[DB];
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[db] = mfma_f32(Ks[f32_tile_off<D>(acc_row(v, h), 32 * db + lq)], s[v], acc[db]);
-    }
-    rs = xhalf_sum(rs);
-    if (t < N) {
-        float* out = dQ + ho + (size_t)t * D;
+            for (int v = 0; v < 16; ++v) acc[db][v] = 0.f;
+        float rs = 0.f;
+        int r_off = row_frag_off<D>(lane), t_off = col_frag_off<D>(lane) + 16 * role * (D * 2);
+        mv.stash(kreg, sm.a[0], 0, 1);
+        mv.stash(vreg, sm.b[0], 0, 1);
+        if (tid < 32) sm.v[0][0][tid] = creg;
+        wg_barrier();
+        auto end_step = [&]() __attribute__((always_inline)) {
+            buf ^= 1;
+            a_slot = next3(a_slot);
+            if (tid < 32) sm.v[0][buf][tid] = creg;
+            wg_barrier();
+        };
+        auto idle_step = [&](int jb) __attribute__((always_inline)) {  // no block of this wave's band: only its share of the tile
+            fetch(min(jb + 1, jb_hi));
+            stash_share(0, 1);
+            end_step();
+        };
+        f32x4 own[2];  // P (wave 0) or dP - D (wave 1) of this wave's half of the block
+        auto first_products = [&](int jb) __attribute__((always_inline)) {
+            const int kb0 = 32 * jb;
+            f32x16 g;
+            const unsigned at = (unsigned)(uintptr_t)(role == 0 ? sm.a[a_slot].p[0] : sm.b[buf].p[0]) + r_off;
+            f32x16 s = tile_dot<D, false>(
+                at, rf, [&](int kc) __attribute__((always_inline)) { stash_share(kc, KC); },
+                [&]() __attribute__((always_inline)) {
+                    if (role == 0) acc_init_rows(g, sm.v[0][buf], 0, h);
+                });
+            if (role == 0) {
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+                for (int v = 0; v < 16; ++v) s[v] = fast_exp2((fmaf(scale, s[v], g[v] - ct) - Lt) * kLog2e);
+                if (__builtin_expect(!(kb0 + 31 <= qw0 && kb0 > qw0 + 31 - w), 0)) {
 #pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4) {
-                f32x4 o4;
+                    for (int v = 0; v < 16; ++v) {
+                        const int i = kb0 + acc_row(v, h);
+                        s[v] = (i <= t && i > t - w) ? s[v] : 0.f;
+                    }
+                }
+            } else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) o4[j] = scale * acc[db][4 * i4 + j];
-                *reinterpret_cast<f32x4*>(out + 32 * db + 8 * i4 + 4 * h) = o4;
+                for (int v = 0; v < 16; ++v) s[v] -= Dt;
             }
-        if (h == 0) dc_row[(size_t)bh * N + t] = rs;
-    }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int mine = 8 * role + 4 * i, other = 8 * (1 - role) + 4 * i;
+                own[i] = f32x4{s[mine], s[mine + 1], s[mine + 2], s[mine + 3]};
+                sm.x[buf][qg][2 * role + i][lane] = f32x4{s[other], s[other + 1], s[other + 2], s[other + 3]};
+            }
+        };
+        auto second_product = [&](int fetched) __attribute__((always_inline)) {  // of the block before the current tile
+            const unsigned at = (unsigned)(uintptr_t)sm.a[a_slot == 0 ? 2 : a_slot - 1].p[0] + t_off;
+            const ColFrag f = first_col<D, 0>(at);
+            float part = 0.f, ds[8];  // (a block's sum by itself first: the suffix sums of the gate gradient add up every rounding)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const f32x4 o = sm.x[buf ^ 1][qg][2 * (1 - role) + i][lane];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    part = fmaf(own[i][j], o[j], part);
+                    ds[4 * i + j] = own[i][j] * o[j];
+                }
+            }
+            rs += part;
+            bf16x8 sf[3];
+            split_frag([&](int j) __attribute__((always_inline)) { return ds[j]; }, sf);
+            tile_axpy<D, 0, 1>(at, acc[0], sf, f, acc, [&](int i) __attribute__((always_inline)) { fetch(fetched, i, DB); });  // (one half: its pieces are in sf)
+        };
+        // (the loop that computes has no branch around the accumulators: with one the compiler copies them)
+        const int act_lo = qw0 < N ? max(0, qw0 - w + 1) / 32 : jb_hi + 1, act_hi = min(qw0 / 32, jb_hi);
+        __builtin_amdgcn_s_setprio(role == 0);  // has the exponentials to do behind its MFMAs
+        int jb = jb_lo;
+        for (; jb < act_lo; ++jb) idle_step(jb);
+        if (jb <= act_hi) {
+            fetch(min(jb + 1, jb_hi));
+            first_products(jb);
+            end_step();
+            for (++jb; jb <= act_hi; ++jb) {
+                // (the addresses derived from these are recomputed in every block instead of living in registers across the loop)
+                GFWA_PIN(r_off);
+                GFWA_PIN(t_off);
+                second_product(min(jb + 1, jb_hi));
+                first_products(jb);
+                end_step();
+            }
+            second_product(min(jb, jb_hi));
+        }
+        for (; jb <= jb_hi; ++jb) idle_step(jb);
+        wg_barrier();
+        // wave 1 of a pair hands its sums over, wave 0 adds and stores (the tiles' space is free)
+        f32x4* xch = reinterpret_cast<f32x4*>(smem_raw) + qg * (4 * DB + 1) * 64;
+        if (role == 1) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4)
+                    xch[(4 * db + i4) * 64 + lane] = f32x4{acc[db][4 * i4], acc[db][4 * i4 + 1], acc[db][4 * i4 + 2], acc[db][4 * i4 + 3]};
+            xch[4 * DB * 64 + lane] = f32x4{rs, 0.f, 0.f, 0.f};
+        }
+        wg_barrier();
+        if (role == 0) {
+            rs = xhalf_sum(rs + xch[4 * DB * 64 + lane][0]);
+            if (t < N) {
+                float* out = dQ + ho + (size_t)t * D;
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4) {
+                        const f32x4 x = xch[(4 * db + i4) * 64 + lane];
+                        f32x4 o4;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) o4[j] = scale * (acc[db][4 * i4 + j] + x[j]);
+                        *reinterpret_cast<f32x4*>(out + 32 * db + 8 * i4 + 4 * h) = o4;
+                    }
+                if (h == 0) dc_row[(size_t)bh * N + t] = rs;
+            }
+        }
+    };
+    if (wv < 4) run(std::integral_constant<int, 0>{});
+    else run(std::integral_constant<int, 1>{});
 }
 
-// ---- dK, dV (summed over the G query heads of a group) and, per query head, the column sums of dS (Alg. 3, key
-// loop): a workgroup owns 128 keys, a wave 32 of them, a lane one key; the K and V fragments are the B operands
-// in registers.  S = Q K^T and dP = dO V^T with 32-query tiles of Q and dO from LDS, then dV^T += dO^T P and
-// dK^T += Q^T dS with P and dS taken from the accumulator registers.
+// dK, dV (summed over the G query heads of a group) and, per query head, the column sums of dS (Alg. 3, key loop): a
+// workgroup owns 128 keys, a pair of waves 32 of them, a lane one key.  S = Q K^T (wave 0) and dP = dO V^T (wave 1) with
+// 32-query tiles of Q and dO from LDS, then dV^T += dO^T P (wave 0) and, a block later, dK^T += Q^T dS (wave 1).
 template <int D>
-__global__ __launch_bounds__(kF32Threads, D == 128 ? 1 : 2) void bwd_dkv_f32_mfma_kernel(
+__global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dkv_f32_mfma_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
     const float* __restrict__ Dv, float* __restrict__ dK, float* __restrict__ dV, float* __restrict__ dc_col,
     int N, int w, float scale, int num_ktiles, int total_tiles, int H, int G) {
-    constexpr int NM = D / 8, DB = D / 32;
-    __shared__ __align__(16) float Qs[32 * kF32Pitch<D>];
-    __shared__ __align__(16) float Gs[32 * kF32Pitch<D>];
-    __shared__ float cqs[32], Lqs[32], Dqs[32];
+    constexpr int KC = D / 16, DB = D / 32;
+    extern __shared__ __align__(256) char smem_raw[];
+    auto& sm = *reinterpret_cast<F32BwdSmem<D>*>(smem_raw);
     const int tile = xcd_remap(blockIdx.x, total_tiles);
     const int bkv = tile / num_ktiles, k0 = (tile % num_ktiles) * 128;  // flat key/value head, first key
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, h = lane >> 5, lk = lane & 31;
-    const int kw0 = k0 + 32 * wv, i = kw0 + lk, ic = min(i, N - 1);
-    const int Hkv = H / G;
-    const int bh0 = (bkv / Hkv) * H + (bkv % Hkv) * G;  // first query head of the group
-    const size_t kvo = (size_t)bkv * N * D;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lk = lane & 31;
+    const int kg = wv & 3;
+    auto run = [&](auto role_c) __attribute__((always_inline)) {
+        constexpr int role = decltype(role_c)::value;
+        const int kw0 = k0 + 32 * kg, i = kw0 + lk, ic = min(i, N - 1);
+        const int Hkv = H / G;
+        const int bh0 = (bkv / Hkv) * H + (bkv % Hkv) * G;  // first query head of the group
+        const size_t kvo = (size_t)bkv * N * D;
 
-    float kf[D / 2], vf[D / 2];
-#pragma unroll
-    for (int m = 0; m < NM; ++m) {
-        const f32x4 k4 = *reinterpret_cast<const f32x4*>(K + kvo + (size_t)ic * D + 8 * m + 4 * h);
-        const f32x4 v4 = *reinterpret_cast<const f32x4*>(V + kvo + (size_t)ic * D + 8 * m + 4 * h);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            kf[4 * m + j] = k4[j];
-            vf[4 * m + j] = v4[j];
-        }
-    }
-    f32x16 dk[DB], dv[DB];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) dk[db][v] = dv[db][v] = 0.f;
-
-    // query blocks that see a key of the tile: rows k0 .. k0 + 127 + w - 1
-    const int qb_lo = k0 / 32;
-    const int qb_hi = (int)(min((long)N - 1, (long)k0 + 127 + w - 1) / 32);
-    const int nblk = qb_hi - qb_lo + 1;
-    F32TileRegs<D> qreg, greg;
-    float creg = 0.f, lreg = 0.f, dreg = 0.f;
-    auto fetch = [&](int it) __attribute__((always_inline)) {
-        const int bh = bh0 + it / nblk, qb0 = 32 * (qb_lo + it % nblk);
-        const size_t ho = (size_t)bh * N * D;
-        qreg.fetch(Q + ho, qb0, N, tid);
-        greg.fetch(dO + ho, qb0, N, tid);
-        if (tid < 32) {
-            const size_t r = (size_t)bh * N + min(qb0 + tid, N - 1);
-            creg = c[r];
-            lreg = L[r];
-            dreg = Dv[r];
-        }
-    };
-    fetch(0);
-    float colsum = 0.f, ci = 0.f;
-    for (int it = 0; it < G * nblk; ++it) {
-        const int g = it / nblk, b = it % nblk, qb0 = 32 * (qb_lo + b);
-        const int bh = bh0 + g;
-        if (b == 0) {
-            colsum = 0.f;
-            ci = c[(size_t)bh * N + ic];
-        }
-        __syncthreads();
-        qreg.stash(Qs, tid);
-        greg.stash(Gs, tid);
-        if (tid < 32) {
-            cqs[tid] = creg;
-            Lqs[tid] = lreg;
-            Dqs[tid] = dreg;
-        }
-        __syncthreads();
-        if (it + 1 < G * nblk) fetch(it + 1);
-        if ((qb0 + 31 >= kw0) && ((long)qb0 <= (long)kw0 + 31 + w - 1) && (kw0 < N)) {
-            f32x16 s, dp;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) s[v] = dp[v] = 0.f;
-#pragma unroll
-            for (int m = 0; m < NM; ++m) {
-                const f32x4 q4 = *reinterpret_cast<const f32x4*>(Qs + f32_tile_off<D>(lk, 8 * m + 4 * h));
-#pragma unroll
-                for (int j = 0; j < 4; ++j) s = mfma_f32(q4[j], kf[4 * m + j], s);
+        // query blocks that see a key of the tile: rows k0 .. k0 + 127 + w - 1, of every query head of the group in turn
+        const int qb_lo = k0 / 32;
+        const int qb_hi = (int)(min((long)N - 1, (long)k0 + 127 + w - 1) / 32);
+        const int nblk = qb_hi - qb_lo + 1;
+        using Mover = F32TileMover<D, kF32BwdThreads>;
+        Mover mv;
+        mv.init(tid);
+        f32x4 qreg[Mover::kPieces], greg[Mover::kPieces];
+        float creg = 0.f, lreg = 0.f, dreg = 0.f;
+        auto fetch = [&](int g, int b, int part, int n) __attribute__((always_inline)) {  // query block b of the group's query head g
+            const int first = 32 * (qb_lo + b);
+            const size_t rows = (size_t)(bh0 + g) * N;
+            mv.fetch(qreg, Q + rows * D, first, N, part, n);
+            mv.fetch(greg, dO + rows * D, first, N, part, n);
+            if (part == 0 && tid < 32) {
+                const unsigned r = (unsigned)min(first + tid, N - 1);
+                creg = (c + rows)[r];
+                lreg = (L + rows)[r];
+                dreg = (Dv + rows)[r];
             }
-#pragma unroll
-            for (int m = 0; m < NM; ++m) {
-                const f32x4 g4 = *reinterpret_cast<const f32x4*>(Gs + f32_tile_off<D>(lk, 8 * m + 4 * h));
-#pragma unroll
-                for (int j = 0; j < 4; ++j) dp = mfma_f32(g4[j], vf[4 * m + j], dp);
+        };
+        auto fetch_next = [&](int g, int b, int part = 0, int n = 1) __attribute__((always_inline)) {  // (behind the last block: that one again)
+            const bool same = b + 1 < nblk;
+            fetch(same ? g : min(g + 1, G - 1), same ? b + 1 : g + 1 < G ? 0 : b, part, n);
+        };
+        int buf = 0, a_slot = 0;  // of the current tile
+        auto stash_share = [&](int p, int n) __attribute__((always_inline)) {  // into the next one's
+            mv.stash(qreg, sm.a[next3(a_slot)], p, n);
+            mv.stash(greg, sm.b[buf ^ 1], p, n);
+        };
+        auto stash_rows = [&]() __attribute__((always_inline)) {
+            if (tid < 32) {
+                sm.v[0][buf][tid] = creg;
+                sm.v[1][buf][tid] = lreg;
+                sm.v[2][buf][tid] = dreg;
             }
+        };
+        fetch(0, 0, 0, 1);
+        bf16x8 rf[KC][3];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = acc_row(v, h), tq = qb0 + r;
-                const float x = fmaf(scale, s[v], ci - cqs[r]);
-                const float p = (i <= tq && i > tq - w && tq < N) ? fast_exp2((x - Lqs[r]) * kLog2e) : 0.f;
-                s[v] = p * (dp[v] - Dqs[r]);
-                dp[v] = p;
-                colsum += s[v];
-            }
-#pragma unroll
-            for (int db = 0; db < DB; ++db) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    dv[db] = mfma_f32(Gs[f32_tile_off<D>(acc_row(v, h), 32 * db + lk)], dp[v], dv[db]);
-                    dk[db] = mfma_f32(Qs[f32_tile_off<D>(acc_row(v, h), 32 * db + lk)], s[v], dk[db]);
-                }
-                __builtin_amdgcn_sched_barrier(0);  // keeps the gathers of one column block from all being hoisted
-            }
-        }
-        if (b == nblk - 1) {  // the query head is finished: its column sums
-            const float cs_all = xhalf_sum(colsum);
-            if (i < N && h == 0) dc_col[(size_t)bh * N + i] = cs_all;
-        }
-    }
-    if (i < N) {
-        float* ok = dK + kvo + (size_t)i * D;
-        float* ov = dV + kvo + (size_t)i * D;
+        for (int kc = 0; kc < KC; ++kc) split_row((role == 0 ? K : V) + kvo + (size_t)ic * D + 16 * kc + 8 * h, rf[kc]);
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16 acc[DB];  // dV of the keys (wave 0), dK (wave 1)
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4) {
-                f32x4 a, b;
+            for (int v = 0; v < 16; ++v) acc[db][v] = 0.f;
+        int r_off = row_frag_off<D>(lane), t_off = col_frag_off<D>(lane);
+        mv.stash(qreg, sm.a[0], 0, 1);
+        mv.stash(greg, sm.b[0], 0, 1);
+        stash_rows();
+        wg_barrier();
+        auto end_step = [&]() __attribute__((always_inline)) {
+            buf ^= 1;
+            a_slot = next3(a_slot);
+            stash_rows();
+            wg_barrier();
+        };
+        auto idle_step = [&](int g, int b) __attribute__((always_inline)) {  // a query block that sees none of this pair's keys
+            fetch_next(g, b);
+            stash_share(0, 1);
+            end_step();
+        };
+        const int b_lo = kw0 < N ? kg : nblk, b_hi = (int)min((long)nblk - 1, ((long)kw0 + 30 + w) / 32 - qb_lo);
+        for (int g = 0; g < G; ++g) {  // query heads
+            int b = 0;
+            for (; b < b_lo; ++b) idle_step(g, b);
+            if constexpr (role == 0) {
+                const float ci = c[(size_t)(bh0 + g) * N + ic];
+                for (; b <= b_hi; ++b) {
+                    // (the addresses derived from these are recomputed in every block instead of living in registers across the loop)
+                    GFWA_PIN(r_off);
+                    GFWA_PIN(t_off);
+                    const int qb0 = 32 * (qb_lo + b);
+                    const unsigned gt = (unsigned)(uintptr_t)sm.b[buf].p[0] + t_off;
+                    f32x16 x, l;
+                    f32x16 s = tile_dot<D, true>(
+                        (unsigned)(uintptr_t)sm.a[a_slot].p[0] + r_off, rf,
+                        [&](int kc) __attribute__((always_inline)) { fetch_next(g, b, kc, KC); },
+                        [&]() __attribute__((always_inline)) { acc_init_rows(x, sm.v[0][buf], 0, h); });
+                    acc_init_rows(l, sm.v[1][buf], 0, h);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    a[j] = scale * dk[db][4 * i4 + j];
-                    b[j] = dv[db][4 * i4 + j];
+                    for (int v = 0; v < 16; ++v) s[v] = fast_exp2((fmaf(scale, s[v], ci - x[v]) - l[v]) * kLog2e);
+                    if (__builtin_expect(!(kw0 + 31 <= qb0 && (long)kw0 > (long)qb0 + 31 - w && qb0 + 31 < N), 0)) {
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            const int tq = qb0 + acc_row(v, h);
+                            s[v] = (i <= tq && i > tq - w && tq < N) ? s[v] : 0.f;
+                        }
+                    }
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4)
+                        sm.x[buf][kg][i4][lane] = f32x4{s[4 * i4], s[4 * i4 + 1], s[4 * i4 + 2], s[4 * i4 + 3]};
+                    const ColFrag f = first_col<D, 0>(gt);
+                    bf16x8 xf[3];
+                    split_acc(s, 0, xf);
+                    tile_axpy<D, 0, 2>(gt, s, xf, f, acc, [&](int p) __attribute__((always_inline)) { stash_share(p, 2 * DB); });
+                    end_step();
                 }
-                *reinterpret_cast<f32x4*>(ok + 32 * db + 8 * i4 + 4 * h) = a;
-                *reinterpret_cast<f32x4*>(ov + 32 * db + 8 * i4 + 4 * h) = b;
+            } else {
+                float colsum = 0.f;
+                f32x16 s;  // dP - D of the block
+                auto first_product = [&]() __attribute__((always_inline)) {
+                    f32x16 x;
+                    s = tile_dot<D, true>(
+                        (unsigned)(uintptr_t)sm.b[buf].p[0] + r_off, rf,
+                        [&](int kc) __attribute__((always_inline)) { stash_share(kc, KC); },
+                        [&]() __attribute__((always_inline)) { acc_init_rows(x, sm.v[2][buf], 0, h); });
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) s[v] -= x[v];
+                };
+                auto second_product = [&](int cur) __attribute__((always_inline)) {  // of the block before the current tile
+                    const unsigned qt = (unsigned)(uintptr_t)sm.a[a_slot == 0 ? 2 : a_slot - 1].p[0] + t_off;
+                    const ColFrag f = first_col<D, 0>(qt);
+                    float part = 0.f;  // (a block's sum by itself first: the suffix sums of the gate gradient add up every rounding)
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4) {
+                        const f32x4 p = sm.x[buf ^ 1][kg][i4][lane];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            part = fmaf(p[j], s[4 * i4 + j], part);
+                            float ds = s[4 * i4 + j] * p[j];
+                            GFWA_PIN(ds);  // formed here, so that P does not stay in registers until the second half is split
+                            s[4 * i4 + j] = ds;
+                        }
+                        GFWA_PIN(part);  // (nor until the sum, which nothing waits for)
+                    }
+                    colsum += part;
+                    __builtin_amdgcn_sched_barrier(0);
+                    bf16x8 xf[3];
+                    split_acc(s, 0, xf);
+                    tile_axpy<D, 0, 2>(qt, s, xf, f, acc, [&](int p) __attribute__((always_inline)) { fetch_next(g, cur, p, 2 * DB); });
+                };
+                if (b <= b_hi) {
+                    fetch_next(g, b);
+                    first_product();
+                    end_step();
+                    for (++b; b <= b_hi; ++b) {
+                        GFWA_PIN(r_off);
+                        GFWA_PIN(t_off);
+                        second_product(b);
+                        first_product();
+                        end_step();
+                    }
+                    second_product(min(b, nblk - 1));  // (its tile and its P are still there in the step that follows, whatever that is)
+                }
+                const float cs_all = xhalf_sum(colsum);
+                if (i < N && h == 0) dc_col[(size_t)(bh0 + g) * N + i] = cs_all;
             }
-    }
+            for (; b < nblk; ++b) idle_step(g, b);
+        }
+        if (i < N) {
+            float* out = (role == 0 ? dV : dK) + kvo + (size_t)i * D;
+            const float f = role == 0 ? 1.0f : scale;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    f32x4 a;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) a[j] = f * acc[db][4 * i4 + j];
+                    *reinterpret_cast<f32x4*>(out + 32 * db + 8 * i4 + 4 * h) = a;
+                }
+        }
+    };
+    if (wv < 4) run(std::integral_constant<int, 0>{});
+    else run(std::integral_constant<int, 1>{});
 }
 
 // ---- D_t = <O_t, dO_t>
@@ -604,32 +919,67 @@ __global__ __launch_bounds__(64 * kF32Waves) void bwd_dkv_f32_kernel(
     }
 }
 
-// Which kernels serve a problem: the matrix-core ones reach half of the fp32 MFMA peak but walk a query (key) tile's
-// band one 32-row block after another, about 3 us each at d = 64; the one-wave-per-row kernels sustain 7 TFLOP/s
-// whatever the shape and finish a tiny problem in one launch latency.  The crossover of the two estimates:
-static bool f32_use_mfma(int B, int H, int N, int d, int w) {
-    const double wc = w < N ? w : N;
-    const double work = (double)B * H * N * wc * d;
-    const double blocks = (wc + 128.0) / 32.0;
-    return work >= blocks * (d / 64.0) * 5.0e6;
+// Which kernels serve a problem, by estimates of the two in us, fitted to 15 shapes (1 to 256 tiles, w 64 .. 2048).  The
+// matrix-core kernels walk a tile's band one 32-row block after another; a row of the one-wave-per-row kernels takes a
+// fixed time per 64 keys while they are few and a rate of 1.7e6 products of the forward per us once they fill the chip.
+// (512 x 512 causal, 4 heads, d = 128: forward 55 and 121 us, backward 119 and 366 us; 256 rows, w = 64, d = 64: 18 and 10,
+// 36 and 27 us.)
+static bool f32_use_mfma(bool backward, int B, int H, int N, int d, int w) {
+    const double wc = w < N ? w : N, wide = d / 64.0, chunks = ceil(wc / 64.0) * wide;
+    const double row = fmax((double)B * H * N * wc * d / (backward ? 0.5e6 : 1.7e6), backward ? 11.0 + 16.0 * chunks : 5.0 + 5.0 * chunks);
+    const double steps = (wc + 127.0) / 32.0 * wide;
+    const double mfma = backward ? 12.0 + 3.3 * steps : 7.0 + 1.6 * steps;
+    return mfma < row;
+}
+
+template <int D, int NW>
+static hipError_t launch_fwd_f32_mfma(const float* Q, const float* K, const float* V, const float* c, float* O, float* L, int B,
+                                      int H, int Hkv, int N, int w, float scale, hipStream_t s) {
+    static DeviceOnce lds_allowed;
+    constexpr size_t lds = sizeof(F32FwdSmem<D>);
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&fwd_f32_mfma_kernel<D, NW>), lds, lds_allowed)) return e;
+    const int nq = (N + 32 * NW - 1) / (32 * NW), total = B * H * nq;
+    hipLaunchKernelGGL((fwd_f32_mfma_kernel<D, NW>), dim3(total), dim3(64 * NW), lds, s, Q, K, V, c, O, L, N, w, scale, nq, total,
+                       H, H / Hkv);
+    return hipGetLastError();
 }
 
 hipError_t forward_f32(const float* Q, const float* K, const float* V, const float* c, float* O, float* L,
                        int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s) {
     ProfScope prof(kKernForward, s);
-    if (f32_use_mfma(B, H, N, d, w)) {
-        const int nq = (N + 127) / 128, total = B * H * nq;
+    if (f32_use_mfma(false, B, H, N, d, w)) {
+        // 256 queries per workgroup (two waves per SIMD) once that gives every CU one
+        const bool wide = B * H * ((N + 255) / 256) >= device_cu_count();
         if (d == 128)
-            hipLaunchKernelGGL((fwd_f32_mfma_kernel<128>), dim3(total), dim3(kF32Threads), 0, s, Q, K, V, c, O, L, N, w,
-                               scale, nq, total, H, H / Hkv);
-        else
-            hipLaunchKernelGGL((fwd_f32_mfma_kernel<64>), dim3(total), dim3(kF32Threads), 0, s, Q, K, V, c, O, L, N, w,
-                               scale, nq, total, H, H / Hkv);
+            return wide ? launch_fwd_f32_mfma<128, 8>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s)
+                        : launch_fwd_f32_mfma<128, 4>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
+        return wide ? launch_fwd_f32_mfma<64, 8>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s)
+                    : launch_fwd_f32_mfma<64, 4>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
     } else {
         const int blocks = B * H * ((N + kF32Waves - 1) / kF32Waves);
         hipLaunchKernelGGL(fwd_f32_kernel, dim3(blocks), dim3(64 * kF32Waves), 0, s, Q, K, V, c, O, L, N, d, w, scale,
                            H, H / Hkv);
     }
+    return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_bwd_f32_mfma(const float* Q, const float* K, const float* V, const float* dO, const float* c,
+                                      const float* L, const float* Dv, float* dQ, float* dK, float* dV, float* dc_col,
+                                      float* dc_row, int B, int H, int Hkv, int N, int w, float scale, hipStream_t s) {
+    static DeviceOnce dkv_lds, dq_lds;
+    constexpr size_t lds = sizeof(F32BwdSmem<D>);
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dkv_f32_mfma_kernel<D>), lds, dkv_lds)) return e;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dq_f32_mfma_kernel<D>), lds, dq_lds)) return e;
+    const int nt = (N + 127) / 128;
+    {
+        ProfScope prof(kKernDkv, s);
+        hipLaunchKernelGGL((bwd_dkv_f32_mfma_kernel<D>), dim3(B * Hkv * nt), dim3(kF32BwdThreads), lds, s, Q, K, V, dO, c, L, Dv,
+                           dK, dV, dc_col, N, w, scale, nt, B * Hkv * nt, H, H / Hkv);
+    }
+    ProfScope prof(kKernDq, s);
+    hipLaunchKernelGGL((bwd_dq_f32_mfma_kernel<D>), dim3(B * H * nt), dim3(kF32BwdThreads), lds, s, Q, K, V, dO, c, L, Dv, dQ,
+                       dc_row, N, w, scale, nt, B * H * nt, H, H / Hkv);
     return hipGetLastError();
 }
 
@@ -647,26 +997,10 @@ hipError_t backward_f32(const float* Q, const float* K, const float* V, const fl
         hipLaunchKernelGGL(rowdot_f32_kernel, dim3((unsigned)((rows + kF32Waves - 1) / kF32Waves)),
                            dim3(64 * kF32Waves), 0, s, O, dO, Dv, (long)rows, d);
     }
-    if (f32_use_mfma(B, H, N, d, w)) {
-        const int nt = (N + 127) / 128;
-        {
-            ProfScope prof(kKernDkv, s);
-            if (d == 128)
-                hipLaunchKernelGGL((bwd_dkv_f32_mfma_kernel<128>), dim3(B * Hkv * nt), dim3(kF32Threads), 0, s, Q, K, V, dO,
-                                   c, L, Dv, dK, dV, dc_col, N, w, scale, nt, B * Hkv * nt, H, H / Hkv);
-            else
-                hipLaunchKernelGGL((bwd_dkv_f32_mfma_kernel<64>), dim3(B * Hkv * nt), dim3(kF32Threads), 0, s, Q, K, V, dO,
-                                   c, L, Dv, dK, dV, dc_col, N, w, scale, nt, B * Hkv * nt, H, H / Hkv);
-        }
-        {
-            ProfScope prof(kKernDq, s);
-            if (d == 128)
-                hipLaunchKernelGGL((bwd_dq_f32_mfma_kernel<128>), dim3(B * H * nt), dim3(kF32Threads), 0, s, Q, K, V, dO, c, L,
-                                   Dv, dQ, dc_row, N, w, scale, nt, B * H * nt, H, H / Hkv);
-            else
-                hipLaunchKernelGGL((bwd_dq_f32_mfma_kernel<64>), dim3(B * H * nt), dim3(kF32Threads), 0, s, Q, K, V, dO, c, L,
-                                   Dv, dQ, dc_row, N, w, scale, nt, B * H * nt, H, H / Hkv);
-        }
+    if (f32_use_mfma(true, B, H, N, d, w)) {
+        const hipError_t e = d == 128 ? launch_bwd_f32_mfma<128>(Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, B, H, Hkv, N, w, scale, s)
+                                      : launch_bwd_f32_mfma<64>(Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, B, H, Hkv, N, w, scale, s);
+        if (e != hipSuccess) return e;
     } else {
         {
             ProfScope prof(kKernDkv, s);

@@ -645,6 +645,21 @@ def test_gqa_f32(g, oracle, B, H, Hkv, N, d, w):
     check_grads(got, ref, 1e-5, "gqa f32")
 
 
+@pytest.mark.parametrize("B,H,Hkv,N,d,w,groups", [
+    # the matrix-core kernels at the edges of their tiles: 128- and 256-query tiles with a last row, a last block and a
+    # full one, windows of one key, inside one block, across one, past the sequence; sampled heads
+    (2, 4, 4, 1025, 64, 97, [0, 7]), (1, 6, 2, 1153, 128, 65, [0, 1]), (2, 32, 32, 1057, 128, 31, [0, 63]),
+    (4, 16, 16, 1281, 64, 33, [0, 63]), (8, 32, 32, 256, 128, 500, [0, 255]), (2, 32, 16, 1120, 64, 129, [0, 31]),
+])
+def test_f32_matrix_core_tiles(g, oracle, B, H, Hkv, N, d, w, groups):
+    note("f32 tiles", B, H, Hkv, N, d, w)
+    wl = gi.custom("f32t", B, H, N, d, w, "f32", alpha_mu=-1.0, index=16, backward=True, kv_heads=Hkv)
+    got, ref = run_gqa(g, oracle, wl, groups=groups)
+    assert rel_inf(got["O"], ref["O"]) <= 1e-5
+    assert (np.abs(got["L"] - ref["L"]) <= 1e-5 * np.abs(ref["L"]).max() + 1e-5).all()
+    check_grads(got, ref, 1e-5, "f32 tiles")
+
+
 GQA_BF16 = [(1, 4, 1, 300, 128, 64), (2, 8, 2, 515, 64, 512), (1, 4, 2, 1536, 128, 1024), (1, 8, 2, 2050, 64, 700),
             (1, 2, 1, 37, 64, 5), (1, 3, 1, 4099, 128, 300)]
 
