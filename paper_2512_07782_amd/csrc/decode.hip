@@ -7,10 +7,10 @@
 //   * rows of the cache are read with 16 lanes x 16 bytes (bf16, d = 128), four rows per wave
 //     instruction, fully coalesced, every byte once;
 //   * the G query heads that read the same key/value head are handled together (4, 2 or 1 per
-//     workgroup), so the cache is read once per group, not once per head;
-//   * the window is split into chunks (256 keys, longer when the batch alone fills the chip), one
-//     workgroup each; the (reference exponent, sum, output) partials are merged across the four waves
-//     through LDS and, when the window has more than one chunk, across chunks by a second small kernel.
+//     workgroup), so the cache is read once per group, not once per head, as long as that leaves enough workgroups;
+//   * the window is shared out over the 4 or 8 waves of a workgroup and, where that does not fill the chip, over
+//     chunks of at least 256 keys, one workgroup each; the (reference exponent, sum, output) partials are merged across
+//     the waves through LDS and, when the window has more than one chunk, across chunks by a second small kernel.
 // With `alpha_t` given the kernel also advances the gate prefix, c[pos] = c[pos-1] + alpha_t, the one
 // step of the scan a decoding step needs.
 #include "gfwa_device.h"
@@ -19,11 +19,8 @@
 
 namespace gfwa {
 
-constexpr int kDecThreads = 256;
-constexpr int kDecWaves = kDecThreads / 64;
-constexpr int kDecChunk = 256;  // keys per workgroup, 64 per wave
+constexpr int kDecChunk = 256;  // a chunk is a multiple of this many keys
 constexpr float kDecNegBig = -1.0e30f;
-constexpr int kDecTargetWorkgroups = 1024;  // workgroups wanted before chunks get longer than 256 keys
 
 __device__ __forceinline__ void load8(const bf16_t* p, float (&x)[8]) {
     const bf16x8 v = *reinterpret_cast<const bf16x8*>(p);
@@ -96,8 +93,19 @@ __device__ __forceinline__ float row_sum(float x) {
     return x;
 }
 
-// One workgroup: GT query heads of one key/value head, one chunk of the window (a multiple of 256
-// keys, a quarter per wave).  A step covers UN rows per lane group (4 UN or 8 UN rows per wave).
+// Sum over the two halves (the four 16-lane rows) of a wave of one value per half (row): x[i] is returned summed in half
+// (row) i alone.  Half the exchanges and additions of summing every value everywhere, and no trip through LDS.
+__device__ __forceinline__ float half_sums(float x0, float x1) {
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float row_pair_sums(float x0, float x1) {  // x0 in even rows of 16 lanes, x1 in odd ones
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// One workgroup of NW waves: GT query heads of one key/value head, one chunk of the window (a multiple of 256
+// keys, 1 / NW of it per wave).  A step covers UN rows per lane group (4 UN or 8 UN rows per wave).
 //   * every lane holds its 16-byte piece of the row and forms the partial dot products of all GT heads
 //     on it; a sum over the lanes of the row (DPP adds on the VALU) leaves every lane with the GT scores;
 //   * all exponentials of a wave are taken against one reference exponent per head, the score of the
@@ -107,8 +115,8 @@ __device__ __forceinline__ float row_sum(float x) {
 //   * the gate prefix of a row is loaded once per head (lane j loads head j % GT) and passed round the
 //     group of GT lanes by DPP;
 //   * the loads of the next step are issued before the current step is computed.
-template <typename T, int D, int GT>
-__global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
+template <typename T, int D, int GT, int NW>
+__global__ __launch_bounds__(64 * NW) void decode_partial_kernel(
     const T* __restrict__ q, const T* __restrict__ Kc, const T* __restrict__ Vc, float* __restrict__ c,
     const float* __restrict__ alpha_t, const int* __restrict__ pos, float* __restrict__ part,
     T* __restrict__ o, float* __restrict__ L, int H, int G, int Tlen, int w, float scale, int S, int chunk) {
@@ -116,8 +124,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
     constexpr int RPI = 64 / LPR;  // rows per wave instruction
     constexpr int UN = 4;          // rows per lane group and step
     constexpr int STEP_ROWS = RPI * UN;
-    __shared__ float sm_acc[kDecWaves][GT][D];
-    __shared__ float sm_m[kDecWaves][GT], sm_l[kDecWaves][GT];
+    __shared__ __align__(16) float sm_acc[NW][GT][D];
+    __shared__ float sm_m[NW][GT], sm_l[NW][GT];
 
     int idx = blockIdx.x;
     const int s = idx % S;
@@ -159,7 +167,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
         for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
     }
 
-    const int per_wave = chunk / kDecWaves;
+    const int per_wave = chunk / NW;
     const int kw0 = k_begin + per_wave * wv;  // first key of this wave
     if (kw0 <= k_end) {                       // uniform over the wave
         const int kw_end = min(k_end, kw0 + per_wave - 1);
@@ -266,39 +274,52 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
                 compute(st + 1, std::integral_constant<int, 1>{});
             }
         }
-        // one reference per head in the whole wave: plain sums over the lane groups (the lanes of a
-        // row all hold the same l)
+    }
+    // One reference per head in the whole wave: plain sums over the lane groups (the lanes of a row all hold the same l).
+    // With four heads head g ends in the g-th row of 16 lanes, with two in the g-th half, a single one in all lanes.
+    float own[8], l_own;
+    {
+        auto across = [&](const float (&x)[GT]) __attribute__((always_inline)) -> float {
+            if constexpr (GT == 4) return row_pair_sums(half_sums(x[0], x[2]), half_sums(x[1], x[3]));
+            const float y = GT == 2 ? half_sums(x[0], x[GT - 1]) : half_sums(x[0], x[0]);
+            return row_pair_sums(y, y);
+        };
 #pragma unroll
-        for (int off = LPR; off < 64; off <<= 1)
+        for (int e = 0; e < 8; ++e) {
+            float x[GT];
 #pragma unroll
-            for (int g = 0; g < GT; ++g) {
-                l[g] += __shfl_xor(l[g], off, 64);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[g][e] += __shfl_xor(acc[g][e], off, 64);
-            }
+            for (int g = 0; g < GT; ++g) x[g] = acc[g][e];
+            own[e] = across(x);
+            if (LPR == 8) own[e] += dpp_mov<0x128>(own[e]);  // the two cache rows of a row of 16 lanes (row_ror:8)
+        }
+        l_own = across(l);
+        if (LPR == 8) l_own += dpp_mov<0x128>(l_own);
     }
     // across the waves through LDS
-    if (r == 0) {
+    {
+        const int g = GT == 4 ? lane >> 4 : GT == 2 ? lane >> 5 : 0;
+        constexpr int kLanesPerHead = GT == 4 ? 16 : GT == 2 ? 32 : 64;
+        if (lane % kLanesPerHead < LPR) {
+            f32x4* to = reinterpret_cast<f32x4*>(&sm_acc[wv][g][8 * j]);
+            to[0] = f32x4{own[0], own[1], own[2], own[3]};
+            to[1] = f32x4{own[4], own[5], own[6], own[7]};
+            if (j == 0) sm_l[wv][g] = l_own;
+        }
+        if (lane == 0) {
 #pragma unroll
-        for (int g = 0; g < GT; ++g) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) sm_acc[wv][g][8 * j + e] = acc[g][e];
-            if (j == 0) {
-                sm_m[wv][g] = mref[g];
-                sm_l[wv][g] = l[g];
-            }
+            for (int k = 0; k < GT; ++k) sm_m[wv][k] = mref[k];
         }
     }
     if (alpha_t != nullptr && s == 0 && tid < GT) c[(size_t)(bh0 + tid) * Tlen + p] = ct_own;  // thread g: head g
     __syncthreads();
-    for (int x = tid; x < GT * D; x += kDecThreads) {
+    for (int x = tid; x < GT * D; x += 64 * NW) {
         const int g = x / D, col = x % D;
         float mm = sm_m[0][g];
 #pragma unroll
-        for (int k = 1; k < kDecWaves; ++k) mm = fmaxf(mm, sm_m[k][g]);
+        for (int k = 1; k < NW; ++k) mm = fmaxf(mm, sm_m[k][g]);
         float ll = 0.f, oo = 0.f;
 #pragma unroll
-        for (int k = 0; k < kDecWaves; ++k) {
+        for (int k = 0; k < NW; ++k) {
             const float f = fast_exp2(sm_m[k][g] - mm);
             ll = fmaf(sm_l[k][g], f, ll);
             oo = fmaf(sm_acc[k][g][col], f, oo);
@@ -323,14 +344,30 @@ __global__ __launch_bounds__(D) void decode_combine_kernel(const float* __restri
                                                            float* __restrict__ L, int S) {
     const int bh = blockIdx.x, col = threadIdx.x;
     const float* rec = part + (size_t)bh * S * dec_record(D);
-    float mm = kDecNegBig;
-    for (int s = 0; s < S; ++s) mm = fmaxf(mm, rec[(size_t)s * dec_record(D) + D]);
-    float ll = 0.f, oo = 0.f;
-    for (int s = 0; s < S; ++s) {
-        const float* rs = rec + (size_t)s * dec_record(D);
-        const float f = fast_exp2(rs[D] - mm);
-        ll = fmaf(rs[D + 1], f, ll);
-        oo = fmaf(rs[col], f, oo);
+    float mm = kDecNegBig, ll = 0.f, oo = 0.f;
+    constexpr int U = 8;  // records whose loads are in flight together
+    for (int s0 = 0; s0 < S; s0 += U) {
+        float m[U], l[U], a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float* rs = rec + (size_t)min(s0 + u, S - 1) * dec_record(D);
+            m[u] = rs[D];
+            l[u] = rs[D + 1];
+            a[u] = rs[col];
+        }
+        float mn = mm;
+#pragma unroll
+        for (int u = 0; u < U; ++u) mn = s0 + u < S ? fmaxf(mn, m[u]) : mn;
+        const float f0 = fast_exp2(mm - mn);
+        ll *= f0;
+        oo *= f0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float f = s0 + u < S ? fast_exp2(m[u] - mn) : 0.f;
+            ll = fmaf(l[u], f, ll);
+            oo = fmaf(a[u], f, oo);
+        }
+        mm = mn;
     }
     o[(size_t)bh * D + col] = (T)(oo / ll);
     if (L != nullptr && col == 0) L[bh] = (mm + log2f(ll)) * kLn2;
@@ -350,28 +387,43 @@ static hipError_t launch_decode(const T* q, const T* Kc, const T* Vc, float* c, 
                                 const int* pos, T* o, float* L, float* part, int B, int H, int Hkv, int Tlen,
                                 int w, float scale, hipStream_t s) {
     const int G = H / Hkv;
-    const int GT = G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1);
+    // How a step is cut up, from a sweep over 12 shapes (1 to 256 sequences, groups of 1 to 4, windows 40 .. 4096):
+    //   * the chip holds 8 waves per CU of the four-head kernel (198 registers), in fp32 half of that pays: one round of
+    //     that many waves is the best size of a launch (B64 H32/8 w1024: 512 workgroups of 4 waves 50.6 us, 1024 61.6 us);
+    //   * a step of a wave costs about as much per head as its loads do (fixed part about one head), so where even
+    //     256-key chunks leave fewer waves than that, fewer heads per workgroup are faster although the cache is then read
+    //     once per head (B1 H32/8 w1024: 8.4 us one head, 9.1 two, 11.9 four);
+    //   * a second chunk brings the merging kernel with it, 2.8 us: worth it from about six steps of one head.
+    constexpr bool kShort = sizeof(T) == 2;
+    const int span = w < Tlen ? w : Tlen, round = (kShort ? 8 : 4) * device_cu_count(), max_splits = decode_splits(Tlen, w);
+    int GT = G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1);
+    while (GT > 1 && (long)B * Hkv * (G / GT) * 8 * max_splits < round) GT /= 2;
     const int items = B * Hkv * (G / GT);
-    // 256-key chunks spread a small batch over the chip; with many (batch, head) items longer chunks
-    // amortise a workgroup's start-up (position, gate prefix, first rows: three dependent trips to memory)
-    const int span = w < Tlen ? w : Tlen;
-    int S = decode_splits(Tlen, w);
-    const int want = (kDecTargetWorkgroups + items - 1) / items;
-    if (want < S) S = want < 1 ? 1 : want;
+    const int NW = kShort && items * 4 < round ? 8 : 4;
+    int S = (round + items * NW - 1) / (items * NW);
+    const int steps = (span + NW * (2048 / D) - 1) / (NW * (2048 / D));  // of a wave, with a single chunk
+    if (steps * (1 + GT) <= 12) S = 1;
+    if (S > max_splits) S = max_splits;
     const int chunk = ((span + S - 1) / S + kDecChunk - 1) / kDecChunk * kDecChunk;
     S = (span + chunk - 1) / chunk;
-    const unsigned grid = (unsigned)(items * S);
     {
         ProfScope prof(kKernDecode, s);
-        if (GT == 4)
-            hipLaunchKernelGGL((decode_partial_kernel<T, D, 4>), dim3(grid), dim3(kDecThreads), 0, s, q, Kc, Vc, c,
-                               alpha_t, pos, part, o, L, H, G, Tlen, w, scale, S, chunk);
-        else if (GT == 2)
-            hipLaunchKernelGGL((decode_partial_kernel<T, D, 2>), dim3(grid), dim3(kDecThreads), 0, s, q, Kc, Vc, c,
-                               alpha_t, pos, part, o, L, H, G, Tlen, w, scale, S, chunk);
-        else
-            hipLaunchKernelGGL((decode_partial_kernel<T, D, 1>), dim3(grid), dim3(kDecThreads), 0, s, q, Kc, Vc, c,
-                               alpha_t, pos, part, o, L, H, G, Tlen, w, scale, S, chunk);
+        auto launch = [&](auto gt, auto nw) {
+            hipLaunchKernelGGL((decode_partial_kernel<T, D, decltype(gt)::value, decltype(nw)::value>), dim3((unsigned)(items * S)),
+                               dim3(64 * decltype(nw)::value), 0, s, q, Kc, Vc, c, alpha_t, pos, part, o, L, H, G, Tlen, w, scale,
+                               S, chunk);
+        };
+        auto with_heads = [&](auto nw) {
+            if (GT == 4) launch(std::integral_constant<int, 4>{}, nw);
+            else if (GT == 2) launch(std::integral_constant<int, 2>{}, nw);
+            else launch(std::integral_constant<int, 1>{}, nw);
+        };
+        if constexpr (kShort) {
+            if (NW == 8) with_heads(std::integral_constant<int, 8>{});
+            else with_heads(std::integral_constant<int, 4>{});
+        } else {
+            with_heads(std::integral_constant<int, 4>{});
+        }
     }
     if (S > 1) {
         ProfScope prof(kKernDecodeCombine, s);

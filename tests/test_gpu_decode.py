@@ -79,6 +79,16 @@ def test_decode_matches_oracle(g, oracle, B, H, Hkv, T, d, w, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,H,Hkv,T,d,w", [
+    # batches large enough for four and for two heads per workgroup: 8 waves and two chunks, 4 waves and one chunk with
+    # waves that have no key, a window of one key more than a chunk
+    (64, 8, 2, 300, 128, 257), (520, 4, 1, 100, 64, 70), (256, 2, 1, 300, 64, 300), (300, 6, 3, 520, 128, 513),
+])
+def test_decode_large_batches(g, oracle, B, H, Hkv, T, d, w, dtype):
+    test_decode_matches_oracle(g, oracle, B, H, Hkv, T, d, w, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("B,H,Hkv,T,d,w", [(2, 8, 2, 700, 128, 512), (2, 4, 2, 900, 64, 300), (1, 4, 4, 640, 128, 640)])
 def test_decode_with_scores_far_apart(g, oracle, B, H, Hkv, T, d, w, dtype):
     # queries and keys of large norm: scores differ by far more than 2^60 inside a wave's 64 keys, so the
