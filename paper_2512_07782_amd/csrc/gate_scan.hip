@@ -1,10 +1,13 @@
 // Gate prefix scans on gfx950 (paper Sec. 3.2 definition of the cumulative gate; Alg. 1, the
 // cumulative-sum / carry steps; Sec. 3.3 for the reverse scan that turns d(prefix) into d(alpha)).
 //
-// One workgroup of 16 waves streams one (b,h) row in chunks of 4096 elements: float4 per thread,
-// in-thread prefix, wavefront scan of the thread totals by lane shuffles, the 16 wave totals
-// through LDS, and a carry kept in fp64 across chunks.  Every element is read once and written
-// once (8 bytes of HBM traffic per element).
+// One workgroup of 4 or 16 waves streams one (b,h) row in chunks of 4096 elements, cut into 16 runs of 256 consecutive ones:
+// float4 per lane, in-lane prefix, scan of the lane totals by DPP moves; the totals of runs and waves are added up in
+// fp64, across the waves through LDS, and a carry is kept in fp64 across chunks.  Every element is read once and written
+// once (8 bytes of HBM traffic per element).  Short rows are bound by latency: the loads of a chunk go out before
+// anything else (before the carry of a segment is formed, before the previous chunk is finished), there is one barrier
+// per chunk and no shuffle through LDS.  (With 16 waves throughout, shuffles and two barriers: 300 rows of 8192 7.6 us, now
+// 5.3; 1024 rows of 65536 114 us, now 105; 100 rows of 262144 with the activation 156 us, now 127.)
 //
 // The same kernel also fuses the gate activation of Alg. 1 in front of the scan: with the
 // pre-activation h and the amplitude beta as inputs it forms
@@ -17,9 +20,8 @@
 
 namespace gfwa {
 
-constexpr int kScanThreads = 1024;
-constexpr int kScanWaves = kScanThreads / 64;
-constexpr int kScanChunk = kScanThreads * 4;
+constexpr int kScanChunk = 4096;  // elements a workgroup takes at a time: 16 runs of 256, shared out over its waves
+constexpr int kScanRuns = kScanChunk / 256;
 constexpr int kScanTargetWorkgroups = 2048;  // scan-then-propagate: segments are cut until about this many exist
 
 // Softplus of z in the overflow-safe form of Alg. 1, nu + log(exp(z - nu) + exp(-nu)) with nu = max(z, 0).
@@ -55,119 +57,156 @@ __device__ __forceinline__ float gate_alpha(float h, float beta, float eps) {
 
 enum ScanInput { kScanPlain = 0, kScanDiff = 1, kScanGate = 2 };
 
-// Logical position p of the scan maps to memory index p (forward) or N-1-p (reverse).
-// MODE kScanDiff: the scanned value is a[idx] - b[idx]; kScanGate: gate_alpha(a[idx], b[idx], eps).
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ float dpp_or_zero(float x) {  // lanes without a source, or in a row that ROWS leaves out, get 0
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROWS, 0xf, false));
+}
+// inclusive scan over the 64 lanes: shifts inside the rows of 16 lanes, then the totals of the rows before
+__device__ __forceinline__ float wave_scan(float x) {
+    x += dpp_or_zero<0x111>(x);
+    x += dpp_or_zero<0x112>(x);
+    x += dpp_or_zero<0x114>(x);
+    x += dpp_or_zero<0x118>(x);
+    x += dpp_or_zero<0x142, 0xa>(x);  // lane 15 (47) to row 1 (3)
+    x += dpp_or_zero<0x143, 0xc>(x);  // lane 31 to rows 2, 3
+    return x;
+}
+__device__ __forceinline__ float lane_value(float x, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
+}
+__device__ __forceinline__ double wave_sum(double x) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
+    return x;
+}
+
+// The four elements at logical positions p .. p + 3 of a row, zero at and beyond `end`.  Position p of the scan is memory index
+// p (forward) or N - 1 - p (reverse).  MODE kScanDiff: the scanned value is a[idx] - b[idx]; kScanGate: gate_alpha(a[idx],
+// b[idx], eps).  vec: float4 accesses, every row starts 16-byte aligned and N is a multiple of 4.  Loading and evaluation
+// are apart so that the loads of a chunk are in flight while something else is computed.
+template <bool REVERSE, int MODE>
+struct ScanQuad {
+    float4 x, y;
+    __device__ __forceinline__ void load(const float* ar, const float* br, int N, int p, int end, bool vec) {
+        constexpr bool TWO = MODE != kScanPlain;
+        x = y = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (vec && p + 3 < end) {
+            const int idx = REVERSE ? N - 4 - p : p;
+            x = *reinterpret_cast<const float4*>(ar + idx);
+            if (TWO) y = *reinterpret_cast<const float4*>(br + idx);
+        } else {
+            float* xs = &x.x;
+            float* ys = &y.x;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (p + e < end) {
+                    const int idx = REVERSE ? N - 1 - (p + e) : p + e, to = REVERSE ? 3 - e : e;
+                    xs[to] = ar[idx];
+                    if (TWO) ys[to] = br[idx];
+                }
+        }
+    }
+    __device__ __forceinline__ void values(float (&v)[4], float eps, int p, int end) const {
+        const float xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int from = REVERSE ? 3 - e : e;
+            v[e] = MODE == kScanPlain ? xs[from] : MODE == kScanDiff ? xs[from] - ys[from] : p + e < end ? gate_alpha(xs[from], ys[from], eps) : 0.f;
+        }
+    }
+};
+// first logical position of run r of this lane's wave in the chunk that starts at `base`
+template <int WAVES>
+__device__ __forceinline__ int run_start(int base, int wv, int r, int lane) { return base + (wv * (kScanRuns / WAVES) + r) * 256 + 4 * lane; }
+
 // With `partial` given (scan-then-propagate) a workgroup takes segment blockIdx.x % P of row blockIdx.x / P,
 // seg_len logical positions long, and starts from the sum of the row's earlier segments.
-template <bool REVERSE, int MODE>
-__global__ __launch_bounds__(kScanThreads) void scan_rows_kernel(const float* __restrict__ a,
+template <bool REVERSE, int MODE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __restrict__ a,
                                                                  const float* __restrict__ b,
                                                                  float* __restrict__ out, int N, float eps,
-                                                                 const double* __restrict__ partial = nullptr,
-                                                                 int seg_len = 0, int P = 1) {
-    constexpr bool DIFF = MODE != kScanPlain;  // a second input row
-    __shared__ float wave_tot[kScanWaves];
-    __shared__ double wave_carry[kScanWaves];
+                                                                 const double* __restrict__ partial,
+                                                                 int seg_len, int P) {
+    constexpr int RUNS = kScanRuns / WAVES;
+    __shared__ double wave_tot[2][WAVES];
     const int seg = partial != nullptr ? (int)(blockIdx.x % P) : 0;
     const size_t row = (size_t)(partial != nullptr ? blockIdx.x / P : blockIdx.x) * N;
     const int begin = partial != nullptr ? seg * seg_len : 0;
     const int end = partial != nullptr ? min(N, begin + seg_len) : N;
     const float* ar = a + row;
-    const float* br = DIFF ? b + row : nullptr;
+    const float* br = MODE != kScanPlain ? b + row : nullptr;
     float* outr = out + row;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    // float4 path only when every row starts 16-byte aligned
-    const uintptr_t bits = (uintptr_t)a | (uintptr_t)out | (DIFF ? (uintptr_t)b : (uintptr_t)0);
+    const uintptr_t bits = (uintptr_t)a | (uintptr_t)out | (MODE != kScanPlain ? (uintptr_t)b : (uintptr_t)0);
     const bool vec = (N % 4 == 0) && ((bits & 15) == 0);
 
+    ScanQuad<REVERSE, MODE> quad[RUNS];
+    auto load = [&](int base) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < RUNS; ++r) quad[r].load(ar, br, N, run_start<WAVES>(base, wv, r, lane), end, vec);
+    };
+    load(begin);
     double carry = 0.0;
-    if (partial != nullptr && seg > 0) {  // sum of the earlier segments of this row, fp64
+    if (partial != nullptr && seg > 0) {  // sum of the earlier segments of this row, fp64, in every wave by itself
         const double* pr = partial + (size_t)(blockIdx.x / P) * P;
         double acc = 0.0;
-        for (int q = tid; q < seg; q += kScanThreads) acc += pr[q];
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
-        if (lane == 0) wave_carry[wv] = acc;
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kScanWaves; ++k) carry += wave_carry[k];
+        for (int q = lane; q < seg; q += 64) acc += pr[q];
+        carry = wave_sum(acc);
     }
-    for (int base = begin; base < end; base += kScanChunk) {
-        const int p0 = base + 4 * tid;
-        float v[4] = {0.f, 0.f, 0.f, 0.f};
-        if (vec && p0 + 3 < end) {
-            const int idx = REVERSE ? N - 4 - p0 : p0;
-            float4 x = *reinterpret_cast<const float4*>(ar + idx);
-            if (MODE == kScanDiff) {
-                const float4 y = *reinterpret_cast<const float4*>(br + idx);
-                x.x -= y.x; x.y -= y.y; x.z -= y.z; x.w -= y.w;
-            } else if (MODE == kScanGate) {
-                const float4 y = *reinterpret_cast<const float4*>(br + idx);
-                x.x = gate_alpha(x.x, y.x, eps); x.y = gate_alpha(x.y, y.y, eps);
-                x.z = gate_alpha(x.z, y.z, eps); x.w = gate_alpha(x.w, y.w, eps);
-            }
-            if (REVERSE) { v[0] = x.w; v[1] = x.z; v[2] = x.y; v[3] = x.x; }
-            else         { v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w; }
-        } else {
+    int buf = 0;
+    for (int base = begin; base < end; base += kScanChunk, buf ^= 1) {
+        float v[RUNS][4], excl[RUNS];  // excl: sum of the lanes before, in the run
+        double before[RUNS], total = 0.0;   // before: sum of the wave's runs before
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int p = p0 + e;
-                if (p < end) {
-                    const int idx = REVERSE ? N - 1 - p : p;
-                    v[e] = MODE == kScanDiff ? ar[idx] - br[idx]
-                         : MODE == kScanGate ? gate_alpha(ar[idx], br[idx], eps) : ar[idx];
-                }
-            }
+        for (int r = 0; r < RUNS; ++r) quad[r].values(v[r], eps, run_start<WAVES>(base, wv, r, lane), end);
+        if (base + kScanChunk < end) load(base + kScanChunk);
+#pragma unroll
+        for (int r = 0; r < RUNS; ++r) {
+            v[r][1] += v[r][0];
+            v[r][2] += v[r][1];
+            v[r][3] += v[r][2];
+            const float incl = wave_scan(v[r][3]);
+            excl[r] = incl - v[r][3];
+            before[r] = total;
+            total += (double)lane_value(incl, 63);
         }
-        v[1] += v[0];
-        v[2] += v[1];
-        v[3] += v[2];
-        // inclusive scan of the per-thread totals across the wavefront
-        float incl = v[3];
+        if (lane == 0) wave_tot[buf][wv] = total;
+        __syncthreads();  // (the totals alternate between two places: the next chunk's writers need no second barrier)
+        double start = carry;
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const float up = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += up;
+        for (int k = 0; k < WAVES; ++k) {
+            const double t = wave_tot[buf][k];
+            if (k < wv) start += t;
+            carry += t;
         }
-        if (lane == 63) wave_tot[wv] = incl;
-        __syncthreads();
-        double before = carry;  // everything that precedes this wave in the row
-        double all = 0.0;
 #pragma unroll
-        for (int k = 0; k < kScanWaves; ++k) {
-            const float tk = wave_tot[k];
-            if (k < wv) before += (double)tk;
-            all += (double)tk;
-        }
-        carry += all;
-        __syncthreads();
-        const double excl = before + (double)(incl - v[3]);
-        float r[4];
+        for (int r = 0; r < RUNS; ++r) {
+            const int p = run_start<WAVES>(base, wv, r, lane);
+            const double from = start + before[r] + (double)excl[r];
+            float y[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = (float)(excl + (double)v[e]);
-        if (vec && p0 + 3 < end) {
-            const int idx = REVERSE ? N - 4 - p0 : p0;
-            const float4 y = REVERSE ? make_float4(r[3], r[2], r[1], r[0]) : make_float4(r[0], r[1], r[2], r[3]);
-            *reinterpret_cast<float4*>(outr + idx) = y;
-        } else {
+            for (int e = 0; e < 4; ++e) y[e] = (float)(from + (double)v[r][e]);
+            if (vec && p + 3 < end) {
+                const int idx = REVERSE ? N - 4 - p : p;
+                *reinterpret_cast<float4*>(outr + idx) = REVERSE ? make_float4(y[3], y[2], y[1], y[0]) : make_float4(y[0], y[1], y[2], y[3]);
+            } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int p = p0 + e;
-                if (p < end) outr[REVERSE ? N - 1 - p : p] = r[e];
+                for (int e = 0; e < 4; ++e)
+                    if (p + e < end) outr[REVERSE ? N - 1 - (p + e) : p + e] = y[e];
             }
         }
     }
 }
 
 // Phase 1 of scan-then-propagate (App. "Preprocessing via Scan-Then-Propagate"): the sum of every
-// segment, the activation recomputed on the fly when the input is (h, beta).  fp32 per thread over
-// its few elements, fp64 across the workgroup.
-template <bool REVERSE, int MODE>
-__global__ __launch_bounds__(kScanThreads) void segment_sum_kernel(const float* __restrict__ a,
+// segment, the activation recomputed on the fly when the input is (h, beta).  fp32 over four elements, fp64 across.
+template <bool REVERSE, int MODE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void segment_sum_kernel(const float* __restrict__ a,
                                                                    const float* __restrict__ b,
                                                                    double* __restrict__ partial, int N, float eps,
                                                                    int seg_len, int P) {
-    __shared__ double wave_sum[kScanWaves];
+    constexpr int RUNS = kScanRuns / WAVES;
+    __shared__ double wave_tot[WAVES];
     const int seg = (int)(blockIdx.x % P);
     const size_t row = (size_t)(blockIdx.x / P) * N;
     const int begin = seg * seg_len, end = min(N, begin + seg_len);
@@ -176,57 +215,61 @@ __global__ __launch_bounds__(kScanThreads) void segment_sum_kernel(const float* 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const uintptr_t bits = (uintptr_t)a | (MODE != kScanPlain ? (uintptr_t)b : (uintptr_t)0);
     const bool vec = (N % 4 == 0) && ((bits & 15) == 0);
-    float acc = 0.f;
-    for (int base = begin; base < end; base += kScanChunk) {  // logical positions, as in scan_rows_kernel
-        const int p0 = base + 4 * tid;
-        if (vec && p0 + 3 < end) {
-            const int idx = REVERSE ? N - 4 - p0 : p0;
-            float4 x = *reinterpret_cast<const float4*>(ar + idx);
-            if (MODE == kScanGate) {
-                const float4 y = *reinterpret_cast<const float4*>(br + idx);
-                x.x = gate_alpha(x.x, y.x, eps); x.y = gate_alpha(x.y, y.y, eps);
-                x.z = gate_alpha(x.z, y.z, eps); x.w = gate_alpha(x.w, y.w, eps);
-            } else if (MODE == kScanDiff) {
-                const float4 y = *reinterpret_cast<const float4*>(br + idx);
-                x.x -= y.x; x.y -= y.y; x.z -= y.z; x.w -= y.w;
-            }
-            acc += (x.x + x.y) + (x.z + x.w);
-        } else {
+    double acc = 0.0;
+    for (int base = begin; base < end; base += kScanChunk) {
+        ScanQuad<REVERSE, MODE> quad[RUNS];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int p = p0 + e;
-                if (p < end) {
-                    const int idx = REVERSE ? N - 1 - p : p;
-                    acc += MODE == kScanGate ? gate_alpha(ar[idx], br[idx], eps) : MODE == kScanDiff ? ar[idx] - br[idx] : ar[idx];
-                }
-            }
+        for (int r = 0; r < RUNS; ++r) quad[r].load(ar, br, N, run_start<WAVES>(base, wv, r, lane), end, vec);
+#pragma unroll
+        for (int r = 0; r < RUNS; ++r) {
+            float v[4];
+            quad[r].values(v, eps, run_start<WAVES>(base, wv, r, lane), end);
+            acc += (double)((v[0] + v[1]) + (v[2] + v[3]));
         }
     }
-    double t = (double)acc;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d, 64);
-    if (lane == 0) wave_sum[wv] = t;
+    acc = wave_sum(acc);
+    if (lane == 0) wave_tot[wv] = acc;
     __syncthreads();
     if (tid == 0) {
         double all = 0.0;
 #pragma unroll
-        for (int k = 0; k < kScanWaves; ++k) all += wave_sum[k];
+        for (int k = 0; k < WAVES; ++k) all += wave_tot[k];
         partial[blockIdx.x] = all;
     }
 }
 
+// Four waves with four runs of a chunk each, or sixteen with one.  Four have less to exchange and four times the loads in
+// flight per wave: better for a workgroup of one or two chunks (300 rows of 8192: 5.3 against 6.6 us).  Longer rows keep a CU
+// busy with one workgroup after another's barrier, and the activation is bound by vector work: sixteen waves cover that
+// (100 rows of 262144 with the activation: 127 against 249 us; sums of 512 segments with it: 7.0 against 8.0 us).
+template <bool REVERSE, int MODE>
+static void launch_scan(const float* a, const float* b, float* out, int rows, int N, float eps, const double* partial, int seg_len,
+                        int P, hipStream_t s) {
+    const unsigned wgs = (unsigned)(rows * P);
+    if ((partial != nullptr ? seg_len : N) <= 2 * kScanChunk)
+        hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 4>), dim3(wgs), dim3(256), 0, s, a, b, out, N, eps, partial, seg_len, P);
+    else
+        hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 16>), dim3(wgs), dim3(1024), 0, s, a, b, out, N, eps, partial, seg_len, P);
+}
+template <bool REVERSE, int MODE>
+static void launch_segment_sum(const float* a, const float* b, double* partial, int rows, int N, float eps, int seg_len, int P, hipStream_t s) {
+    const unsigned wgs = (unsigned)(rows * P);
+    if (MODE != kScanGate && seg_len <= 2 * kScanChunk)
+        hipLaunchKernelGGL((segment_sum_kernel<REVERSE, MODE, 4>), dim3(wgs), dim3(256), 0, s, a, b, partial, N, eps, seg_len, P);
+    else
+        hipLaunchKernelGGL((segment_sum_kernel<REVERSE, MODE, 16>), dim3(wgs), dim3(1024), 0, s, a, b, partial, N, eps, seg_len, P);
+}
+
 hipError_t gate_prefix(const float* alpha, float* c, int rows, int N, hipStream_t s) {
     ProfScope prof(kKernGatePrefix, s);
-    hipLaunchKernelGGL((scan_rows_kernel<false, kScanPlain>), dim3(rows), dim3(kScanThreads), 0, s, alpha,
-                       (const float*)nullptr, c, N, 0.f);
+    launch_scan<false, kScanPlain>(alpha, nullptr, c, rows, N, 0.f, nullptr, 0, 1, s);
     return hipGetLastError();
 }
 
 hipError_t gate_activation_prefix(const float* hpre, const float* beta, float eps, float* c, int rows, int N,
                                   hipStream_t s) {
     ProfScope prof(kKernGateActPrefix, s);
-    hipLaunchKernelGGL((scan_rows_kernel<false, kScanGate>), dim3(rows), dim3(kScanThreads), 0, s, hpre, beta, c,
-                       N, eps);
+    launch_scan<false, kScanGate>(hpre, beta, c, rows, N, eps, nullptr, 0, 1, s);
     return hipGetLastError();
 }
 
@@ -249,22 +292,15 @@ hipError_t gate_prefix_stp(const float* in, const float* beta, float eps, float*
                            int N, hipStream_t s) {
     int seg_len = 0;
     const int P = scan_segments(rows, N, &seg_len);
-    const dim3 grid((unsigned)(rows * P)), block(kScanThreads);
     {
         ProfScope prof(kKernScanSegmentSum, s);
-        if (beta != nullptr)
-            hipLaunchKernelGGL((segment_sum_kernel<false, kScanGate>), grid, block, 0, s, in, beta, partial, N, eps, seg_len, P);
-        else
-            hipLaunchKernelGGL((segment_sum_kernel<false, kScanPlain>), grid, block, 0, s, in, beta, partial, N, eps, seg_len, P);
+        if (beta != nullptr) launch_segment_sum<false, kScanGate>(in, beta, partial, rows, N, eps, seg_len, P, s);
+        else launch_segment_sum<false, kScanPlain>(in, beta, partial, rows, N, eps, seg_len, P, s);
     }
     {
         ProfScope prof(kKernScanPropagate, s);
-        if (beta != nullptr)
-            hipLaunchKernelGGL((scan_rows_kernel<false, kScanGate>), grid, block, 0, s, in, beta, c, N, eps,
-                               (const double*)partial, seg_len, P);
-        else
-            hipLaunchKernelGGL((scan_rows_kernel<false, kScanPlain>), grid, block, 0, s, in, beta, c, N, eps,
-                               (const double*)partial, seg_len, P);
+        if (beta != nullptr) launch_scan<false, kScanGate>(in, beta, c, rows, N, eps, partial, seg_len, P, s);
+        else launch_scan<false, kScanPlain>(in, beta, c, rows, N, eps, partial, seg_len, P, s);
     }
     return hipGetLastError();
 }
@@ -333,20 +369,16 @@ hipError_t gate_grad_scan(const float* dc_col, const float* dc_row, float* dalph
     if (partial != nullptr && gate_grad_scan_wants_segments(rows, N)) {
         int seg_len = 0;
         const int P = scan_segments(rows, N, &seg_len);
-        const dim3 grid((unsigned)(rows * P)), block(kScanThreads);
         {
             ProfScope prof(kKernGateGradSegmentSum, s);
-            hipLaunchKernelGGL((segment_sum_kernel<true, kScanDiff>), grid, block, 0, s, dc_col, dc_row, partial, N, 0.f,
-                               seg_len, P);
+            launch_segment_sum<true, kScanDiff>(dc_col, dc_row, partial, rows, N, 0.f, seg_len, P, s);
         }
         ProfScope prof(kKernGateGrad, s);
-        hipLaunchKernelGGL((scan_rows_kernel<true, kScanDiff>), grid, block, 0, s, dc_col, dc_row, dalpha, N, 0.f,
-                           (const double*)partial, seg_len, P);
+        launch_scan<true, kScanDiff>(dc_col, dc_row, dalpha, rows, N, 0.f, partial, seg_len, P, s);
         return hipGetLastError();
     }
     ProfScope prof(kKernGateGrad, s);
-    hipLaunchKernelGGL((scan_rows_kernel<true, kScanDiff>), dim3(rows), dim3(kScanThreads), 0, s, dc_col,
-                       dc_row, dalpha, N, 0.f);
+    launch_scan<true, kScanDiff>(dc_col, dc_row, dalpha, rows, N, 0.f, nullptr, 0, 1, s);
     return hipGetLastError();
 }
 
