@@ -2,9 +2,7 @@
 // arithmetic in fp32, for problems that need fp32 accuracy; the bf16 MFMA kernels are the throughput path.
 // Two sets of kernels.  The matrix-core set (bf16 MFMAs on operands split into three pieces, the structure of the bf16
 // kernels: a lane owns a query or a key, the second product takes the first one's accumulator registers as its operand)
-// serves everything but tiny problems.  The one-wave-per-row set (plain FMA: lanes first split the keys of a 64-wide
-// chunk to form the logits, then split the head dimension to accumulate the output row) has a launch's latency
-// and serves those; forward_f32 / backward_f32 choose (f32_use_mfma).
+// serves everything but tiny problems.  The one-wave-per-row set (plain FMA) has a launch's latency and serves those; forward_f32 / backward_f32 choose (f32_use_mfma).
 #include <math.h>
 
 #include <type_traits>
@@ -17,38 +15,69 @@ namespace gfwa {
 
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
+// ==========================================================================================
+// One-wave-per-row kernels: a wave owns one query (key) and takes the other side's rows 16 load instructions at a time,
+// D / 4 lanes x 16 bytes per row.  Every lane forms its part of the dot products on the four columns it holds, a sum over the
+// row's lanes by lane moves gives all of them the score, and the same registers then feed the weighted sum of those
+// columns: no transposition, nothing through LDS but per-row values.  Latency bounds them, so all loads of a step go out before
+// anything is waited for.  (Lanes that split the keys for the scores, then the columns, with the rows fetched one load
+// after another: 512 causal rows, 4 heads, d = 128: forward 121 us, now 49; backward 366 us, now 134; prefix and forward of
+// 256 rows, w = 64, d = 64: 11.1 us, now 8.9.)
+// ==========================================================================================
 constexpr int kF32Waves = 4;
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) x = fmaxf(x, __shfl_xor(x, d, 64));
-    return x;
+template <int CTRL>
+__device__ __forceinline__ float dpp_moved(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
 }
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
-    return x;
+__device__ __forceinline__ float row_pair_sum(float x) {  // lane ^ 16
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-__device__ __forceinline__ float dot_row(const float* __restrict__ a_lds, const float* __restrict__ g, int D) {
-    float acc = 0.f;
-    for (int x = 0; x < D; x += 4) {
-        const float4 gv = *reinterpret_cast<const float4*>(g + x);
-        acc = fmaf(a_lds[x], gv.x, acc);
-        acc = fmaf(a_lds[x + 1], gv.y, acc);
-        acc = fmaf(a_lds[x + 2], gv.z, acc);
-        acc = fmaf(a_lds[x + 3], gv.w, acc);
+__device__ __forceinline__ float row_pair_max(float x) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <int D>
+struct RowStep {
+    static constexpr int kLanes = D / 4, kRows = 64 / kLanes;  // lanes per row, rows per load instruction
+    static constexpr int kLoads = 16, kStep = kLoads * kRows;  // rows per step
+    f32x4 x[kLoads];
+    // rows row0 + u kRows + lane / kLanes, u = 0 .. kLoads - 1, of the matrix at M; past `last`: row `last`
+    __device__ __forceinline__ void load(const float* M, int row0, int last, int lane) {
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u)
+            x[u] = *reinterpret_cast<const f32x4*>(M + (size_t)min(row0 + u * kRows + lane / kLanes, last) * D + 4 * (lane % kLanes));
     }
-    return acc;
+    __device__ __forceinline__ float dot(const f32x4& q, int u) const {  // with the row whose columns q holds; in all its lanes
+        float d = q[0] * x[u][0];
+#pragma unroll
+        for (int j = 1; j < 4; ++j) d = fmaf(q[j], x[u][j], d);
+        d += dpp_moved<0x128>(d);  // row_ror:8, 4, 2, 1
+        d += dpp_moved<0x124>(d);
+        d += dpp_moved<0x122>(d);
+        d += dpp_moved<0x121>(d);
+        return D == 128 ? row_pair_sum(d) : d;
+    }
+    // sum over the row groups of a wave
+    static __device__ __forceinline__ float group_sum(float v) { return xhalf_sum(D == 128 ? v : row_pair_sum(v)); }
+    static __device__ __forceinline__ float group_max(float v) { return xhalf_max(D == 128 ? v : row_pair_max(v)); }
+    static __device__ __forceinline__ f32x4 group_sum(const f32x4& v) {
+        return {group_sum(v[0]), group_sum(v[1]), group_sum(v[2]), group_sum(v[3])};
+    }
+};
+__device__ __forceinline__ f32x4 fma4(float a, const f32x4& x, const f32x4& c) {
+    return {fmaf(a, x[0], c[0]), fmaf(a, x[1], c[1]), fmaf(a, x[2], c[2]), fmaf(a, x[3], c[3])};
 }
 
-// ---- forward: online softmax over 64-key chunks of the window of row t
+// ---- forward: online softmax over the steps of the window of row t
+template <int D>
 __global__ __launch_bounds__(64 * kF32Waves) void fwd_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-    const float* __restrict__ c, float* __restrict__ O, float* __restrict__ L, int N, int D, int w,
+    const float* __restrict__ c, float* __restrict__ O, float* __restrict__ L, int N, int w,
     float scale, int H, int G) {
-    __shared__ float qs[kF32Waves][128];
-    __shared__ float ps[kF32Waves][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    using Step = RowStep<D>;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rows_per_head = (N + kF32Waves - 1) / kF32Waves;
     const int bh = blockIdx.x / rows_per_head;
     const int t = (blockIdx.x % rows_per_head) * kF32Waves + wv;
@@ -58,34 +87,152 @@ __global__ __launch_bounds__(64 * kF32Waves) void fwd_f32_kernel(
     const float* Kh = K + kvo;
     const float* Vh = V + kvo;
     const float* ch = c + (size_t)bh * N;
-    for (int x = lane; x < D; x += 64) qs[wv][x] = Q[ho + (size_t)t * D + x];
-    const float ct = ch[t];
+    const int r = lane / Step::kLanes, col = 4 * (lane % Step::kLanes);
     const int lo = max(0, t - w + 1);
-    float m = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f;
-    for (int i0 = lo; i0 <= t; i0 += 64) {
-        const int i = i0 + lane;
-        float s = -INFINITY;
-        if (i <= t) s = fmaf(scale, dot_row(qs[wv], Kh + (size_t)i * D, D), ch[i] - ct);
-        const float mnew = fmaxf(m, wave_max(s));  // finite: the chunk always holds a valid key
+    Step k, v;
+    float ci[Step::kLoads];
+    const f32x4 q = *reinterpret_cast<const f32x4*>(Q + ho + (size_t)t * D + col);
+    const float ct = ch[t];
+    float m = -INFINITY, l = 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    for (int i0 = lo; i0 <= t; i0 += Step::kStep) {
+        k.load(Kh, i0, t, lane);
+#pragma unroll
+        for (int u = 0; u < Step::kLoads; ++u) ci[u] = ch[min(i0 + u * Step::kRows + r, t)];
+        v.load(Vh, i0, t, lane);
+        float s[Step::kLoads], mx = m;
+#pragma unroll
+        for (int u = 0; u < Step::kLoads; ++u) {
+            s[u] = fmaf(scale, k.dot(q, u), ci[u] - ct);
+            s[u] = i0 + u * Step::kRows + r <= t ? s[u] : -INFINITY;
+            mx = fmaxf(mx, s[u]);
+        }
+        const float mnew = Step::group_max(mx);  // finite: the step always holds a valid key
         const float a = expf(m - mnew);
-        const float p = expf(s - mnew);
-        l = fmaf(l, a, wave_sum(p));
+        l *= a;
+        o *= a;
         m = mnew;
-        ps[wv][lane] = p;
-        o0 *= a;
-        o1 *= a;
-        const int n = min(64, t - i0 + 1);
-        for (int j = 0; j < n; ++j) {
-            const float pj = ps[wv][j];
-            const float* vr = Vh + (size_t)(i0 + j) * D;
-            o0 = fmaf(pj, vr[lane], o0);
-            if (D > 64) o1 = fmaf(pj, vr[lane + 64], o1);
+#pragma unroll
+        for (int u = 0; u < Step::kLoads; ++u) {
+            const float p = expf(s[u] - mnew);
+            l += p;
+            o = fma4(p, v.x[u], o);
         }
     }
-    float* orow = O + ho + (size_t)t * D;
-    orow[lane] = o0 / l;
-    if (D > 64) orow[lane + 64] = o1 / l;
+    l = Step::group_sum(l);
+    o = Step::group_sum(o);
+    if (r == 0) *reinterpret_cast<f32x4*>(O + ho + (size_t)t * D + col) = f32x4{o[0] / l, o[1] / l, o[2] / l, o[3] / l};
     if (lane == 0) L[(size_t)bh * N + t] = m + logf(l);
+}
+
+// ---- D_t = <O_t, dO_t>, dQ_t and the row sum of dS
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves) void bwd_dq_f32_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ O,
+    const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
+    float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dc_row, int N,
+    int w, float scale, int H, int G) {
+    using Step = RowStep<D>;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rows_per_head = (N + kF32Waves - 1) / kF32Waves;
+    const int bh = blockIdx.x / rows_per_head;
+    const int t = (blockIdx.x % rows_per_head) * kF32Waves + wv;
+    if (t >= N) return;
+    const size_t ho = (size_t)bh * N * D;
+    const size_t kvo = (size_t)kv_head_of(bh, H, G) * N * D;
+    const float* Kh = K + kvo;
+    const float* Vh = V + kvo;
+    const float* ch = c + (size_t)bh * N;
+    const int r = lane / Step::kLanes, col = 4 * (lane % Step::kLanes);
+    const int lo = max(0, t - w + 1);
+    Step k, v;
+    float ci[Step::kLoads];
+    const size_t at = ho + (size_t)t * D + col;
+    const f32x4 q = *reinterpret_cast<const f32x4*>(Q + at), g = *reinterpret_cast<const f32x4*>(dO + at);
+    const float ct = ch[t], Lt = L[(size_t)bh * N + t];
+    float Dt = 0.f, rs = 0.f;
+    f32x4 dq = {0.f, 0.f, 0.f, 0.f};
+    for (int i0 = lo; i0 <= t; i0 += Step::kStep) {
+        k.load(Kh, i0, t, lane);
+#pragma unroll
+        for (int u = 0; u < Step::kLoads; ++u) ci[u] = ch[min(i0 + u * Step::kRows + r, t)];
+        v.load(Vh, i0, t, lane);
+        if (i0 == lo) {
+            RowStep<D> one;
+            one.x[0] = *reinterpret_cast<const f32x4*>(O + at);
+            Dt = one.dot(g, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < Step::kLoads; ++u) {
+            const float s = fmaf(scale, k.dot(q, u), ci[u] - ct);
+            const float ds = i0 + u * Step::kRows + r <= t ? expf(s - Lt) * (v.dot(g, u) - Dt) : 0.f;
+            rs += ds;
+            dq = fma4(ds, k.x[u], dq);
+        }
+    }
+    rs = Step::group_sum(rs);
+    dq = Step::group_sum(dq);
+    if (r == 0) *reinterpret_cast<f32x4*>(dQ + at) = dq * scale;
+    if (lane == 0) {
+        Dv[(size_t)bh * N + t] = Dt;
+        dc_row[(size_t)bh * N + t] = rs;
+    }
+}
+
+// ---- dK_i, dV_i (summed over the G query heads that read this key/value head) and, per query
+// head, the column sum of dS
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves) void bwd_dkv_f32_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+    const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
+    const float* __restrict__ Dv, float* __restrict__ dK, float* __restrict__ dV,
+    float* __restrict__ dc_col, int N, int w, float scale, int H, int G) {
+    using Step = RowStep<D>;
+    __shared__ f32x4 rows_s[kF32Waves][64];  // c, L, D of a step's queries
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rows_per_head = (N + kF32Waves - 1) / kF32Waves;
+    const int bkv = blockIdx.x / rows_per_head;  // flat key/value head
+    const int i = (blockIdx.x % rows_per_head) * kF32Waves + wv;
+    if (i >= N) return;
+    const int Hkv = H / G;
+    const int bh0 = (bkv / Hkv) * H + (bkv % Hkv) * G;  // first query head of the group
+    const int r = lane / Step::kLanes, col = 4 * (lane % Step::kLanes);
+    const size_t at = (size_t)bkv * N * D + (size_t)i * D + col;
+    const f32x4 k = *reinterpret_cast<const f32x4*>(K + at), v = *reinterpret_cast<const f32x4*>(V + at);
+    const int t_hi = (int)min((long)N - 1, (long)i + w - 1);  // key i is seen by rows i .. i+w-1
+    f32x4 dk = {0.f, 0.f, 0.f, 0.f}, dv = dk;
+    Step q, d;
+    for (int g = 0; g < G; ++g) {
+        const size_t rows = (size_t)(bh0 + g) * N;
+        const float ci = c[rows + i];
+        float cs = 0.f;
+        for (int t0 = i; t0 <= t_hi; t0 += Step::kStep) {
+            const int tl = min(t0 + lane, t_hi);
+            const f32x4 row = {c[rows + tl], L[rows + tl], Dv[rows + tl], 0.f};
+            q.load(Q + rows * D, t0, t_hi, lane);
+            d.load(dO + rows * D, t0, t_hi, lane);
+            rows_s[wv][lane] = row;
+#pragma unroll
+            for (int u = 0; u < Step::kLoads; ++u) {
+                const int n = u * Step::kRows + r;
+                const f32x4 x = rows_s[wv][n];
+                const float s = fmaf(scale, q.dot(k, u), ci - x[0]);
+                const float p = t0 + n <= t_hi ? expf(s - x[1]) : 0.f;
+                const float ds = p * (d.dot(v, u) - x[2]);
+                cs += ds;
+                dv = fma4(p, d.x[u], dv);
+                dk = fma4(ds, q.x[u], dk);
+            }
+        }
+        cs = Step::group_sum(cs);
+        if (lane == 0) dc_col[rows + i] = cs;
+    }
+    dk = Step::group_sum(dk);
+    dv = Step::group_sum(dv);
+    if (r == 0) {
+        *reinterpret_cast<f32x4*>(dK + at) = dk * scale;
+        *reinterpret_cast<f32x4*>(dV + at) = dv;
+    }
 }
 
 // ==========================================================================================
@@ -786,149 +933,32 @@ __global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dkv_f32_mfma_kernel(
 }
 
 // ---- D_t = <O_t, dO_t>
-__global__ __launch_bounds__(64 * kF32Waves) void rowdot_f32_kernel(const float* __restrict__ O,
-                                                                    const float* __restrict__ dO,
-                                                                    float* __restrict__ Dv, long rows, int D) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const long r = (long)blockIdx.x * kF32Waves + wv;
-    if (r >= rows) return;
-    float acc = 0.f;
-    for (int x = lane; x < D; x += 64) acc = fmaf(O[r * D + x], dO[r * D + x], acc);
-    acc = wave_sum(acc);
-    if (lane == 0) Dv[r] = acc;
+template <int D>
+__global__ __launch_bounds__(256) void rowdot_f32_kernel(const float* __restrict__ O, const float* __restrict__ dO,
+                                                         float* __restrict__ Dv, long rows) {
+    using Step = RowStep<D>;
+    const int lane = threadIdx.x & 63;
+    const long row = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * Step::kRows + lane / Step::kLanes;
+    if (row - lane / Step::kLanes >= rows) return;  // the whole wave
+    const size_t at = (size_t)min(row, rows - 1) * D + 4 * (lane % Step::kLanes);
+    Step o;
+    o.x[0] = *reinterpret_cast<const f32x4*>(O + at);
+    const float d = o.dot(*reinterpret_cast<const f32x4*>(dO + at), 0);
+    if (row < rows && lane % Step::kLanes == 0) Dv[row] = d;
 }
 
-// ---- dQ_t and the row sum of dS
-__global__ __launch_bounds__(64 * kF32Waves) void bwd_dq_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-    const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
-    const float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dc_row, int N, int D,
-    int w, float scale, int H, int G) {
-    __shared__ float qs[kF32Waves][128];
-    __shared__ float gs[kF32Waves][128];
-    __shared__ float ds_s[kF32Waves][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int rows_per_head = (N + kF32Waves - 1) / kF32Waves;
-    const int bh = blockIdx.x / rows_per_head;
-    const int t = (blockIdx.x % rows_per_head) * kF32Waves + wv;
-    if (t >= N) return;
-    const size_t ho = (size_t)bh * N * D;
-    const size_t kvo = (size_t)kv_head_of(bh, H, G) * N * D;
-    const float* Kh = K + kvo;
-    const float* Vh = V + kvo;
-    const float* ch = c + (size_t)bh * N;
-    for (int x = lane; x < D; x += 64) {
-        qs[wv][x] = Q[ho + (size_t)t * D + x];
-        gs[wv][x] = dO[ho + (size_t)t * D + x];
-    }
-    const float ct = ch[t], Lt = L[(size_t)bh * N + t], Dt = Dv[(size_t)bh * N + t];
-    const int lo = max(0, t - w + 1);
-    float rs = 0.f, g0 = 0.f, g1 = 0.f;
-    for (int i0 = lo; i0 <= t; i0 += 64) {
-        const int i = i0 + lane;
-        float ds = 0.f;
-        if (i <= t) {
-            const float s = fmaf(scale, dot_row(qs[wv], Kh + (size_t)i * D, D), ch[i] - ct);
-            const float p = expf(s - Lt);
-            ds = p * (dot_row(gs[wv], Vh + (size_t)i * D, D) - Dt);
-        }
-        rs += ds;
-        ds_s[wv][lane] = ds;
-        const int n = min(64, t - i0 + 1);
-        for (int j = 0; j < n; ++j) {
-            const float dj = ds_s[wv][j];
-            const float* kr = Kh + (size_t)(i0 + j) * D;
-            g0 = fmaf(dj, kr[lane], g0);
-            if (D > 64) g1 = fmaf(dj, kr[lane + 64], g1);
-        }
-    }
-    rs = wave_sum(rs);
-    float* out = dQ + ho + (size_t)t * D;
-    out[lane] = scale * g0;
-    if (D > 64) out[lane + 64] = scale * g1;
-    if (lane == 0) dc_row[(size_t)bh * N + t] = rs;
-}
-
-// ---- dK_i, dV_i (summed over the G query heads that read this key/value head) and, per query
-// head, the column sum of dS
-__global__ __launch_bounds__(64 * kF32Waves) void bwd_dkv_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-    const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
-    const float* __restrict__ Dv, float* __restrict__ dK, float* __restrict__ dV,
-    float* __restrict__ dc_col, int N, int D, int w, float scale, int H, int G) {
-    __shared__ float ks[kF32Waves][128];
-    __shared__ float vs[kF32Waves][128];
-    __shared__ float p_s[kF32Waves][64];
-    __shared__ float ds_s[kF32Waves][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int rows_per_head = (N + kF32Waves - 1) / kF32Waves;
-    const int bkv = blockIdx.x / rows_per_head;  // flat key/value head
-    const int i = (blockIdx.x % rows_per_head) * kF32Waves + wv;
-    if (i >= N) return;
-    const int Hkv = H / G;
-    const int bh0 = (bkv / Hkv) * H + (bkv % Hkv) * G;  // first query head of the group
-    const size_t kvo = (size_t)bkv * N * D;
-    for (int x = lane; x < D; x += 64) {
-        ks[wv][x] = K[kvo + (size_t)i * D + x];
-        vs[wv][x] = V[kvo + (size_t)i * D + x];
-    }
-    const long t_hi = min((long)N - 1, (long)i + w - 1);  // key i is seen by rows i .. i+w-1
-    float k0 = 0.f, k1 = 0.f, v0 = 0.f, v1 = 0.f;
-    for (int g = 0; g < G; ++g) {
-        const int bh = bh0 + g;
-        const size_t ho = (size_t)bh * N * D;
-        const float* Qh = Q + ho;
-        const float* Gh = dO + ho;
-        const float* ch = c + (size_t)bh * N;
-        const float* Lh = L + (size_t)bh * N;
-        const float* Dh = Dv + (size_t)bh * N;
-        const float ci = ch[i];
-        float cs = 0.f;
-        for (long t0 = i; t0 <= t_hi; t0 += 64) {
-            const long t = t0 + lane;
-            float p = 0.f, ds = 0.f;
-            if (t <= t_hi) {
-                const float s = fmaf(scale, dot_row(ks[wv], Qh + (size_t)t * D, D), ci - ch[t]);
-                p = expf(s - Lh[t]);
-                ds = p * (dot_row(vs[wv], Gh + (size_t)t * D, D) - Dh[t]);
-            }
-            cs += ds;
-            p_s[wv][lane] = p;
-            ds_s[wv][lane] = ds;
-            const int n = (int)min(64L, t_hi - t0 + 1);
-            for (int j = 0; j < n; ++j) {
-                const float pj = p_s[wv][j], dj = ds_s[wv][j];
-                const float* gr = Gh + (size_t)(t0 + j) * D;
-                const float* qr = Qh + (size_t)(t0 + j) * D;
-                v0 = fmaf(pj, gr[lane], v0);
-                k0 = fmaf(dj, qr[lane], k0);
-                if (D > 64) {
-                    v1 = fmaf(pj, gr[lane + 64], v1);
-                    k1 = fmaf(dj, qr[lane + 64], k1);
-                }
-            }
-        }
-        cs = wave_sum(cs);
-        if (lane == 0) dc_col[(size_t)bh * N + i] = cs;
-    }
-    dK[kvo + (size_t)i * D + lane] = scale * k0;
-    dV[kvo + (size_t)i * D + lane] = v0;
-    if (D > 64) {
-        dK[kvo + (size_t)i * D + lane + 64] = scale * k1;
-        dV[kvo + (size_t)i * D + lane + 64] = v1;
-    }
-}
-
-// Which kernels serve a problem, by estimates of the two in us, fitted to 15 shapes (1 to 256 tiles, w 64 .. 2048).  The
-// matrix-core kernels walk a tile's band one 32-row block after another; a row of the one-wave-per-row kernels takes a
-// fixed time per 64 keys while they are few and a rate of 1.7e6 products of the forward per us once they fill the chip.
-// (512 x 512 causal, 4 heads, d = 128: forward 55 and 121 us, backward 119 and 366 us; 256 rows, w = 64, d = 64: 18 and 10,
-// 36 and 27 us.)
-static bool f32_use_mfma(bool backward, int B, int H, int N, int d, int w) {
-    const double wc = w < N ? w : N, wide = d / 64.0, chunks = ceil(wc / 64.0) * wide;
-    const double row = fmax((double)B * H * N * wc * d / (backward ? 0.5e6 : 1.7e6), backward ? 11.0 + 16.0 * chunks : 5.0 + 5.0 * chunks);
-    const double steps = (wc + 127.0) / 32.0 * wide;
-    const double mfma = backward ? 12.0 + 3.3 * steps : 7.0 + 1.6 * steps;
+// Which kernels serve a problem, by estimates of the two in us, fitted to 16 shapes (1 to 256 tiles, w 64 .. 700).  The
+// matrix-core kernels walk a tile's band one 32-row block after another.  A row of the one-wave-per-row kernels takes a
+// fixed time per step of 64 (d = 64) or 32 keys while they are few, and they sustain 2.3e6 products of the forward per us
+// once they fill the chip.  In the backward both walk the G query heads of a key one after another.
+// (One-wave-per-row / matrix cores: 256 rows, w = 64, d = 64: forward 2 / 13 us, backward 7 / 28 us; 512 causal rows, 4 heads,
+// d = 128: 49 / 53, 134 / 119; 1024 rows, w = 128, 8 heads, d = 128: 52 / 36, 140 / 73; events included, about 5 us each.)
+static bool f32_use_mfma(bool backward, int B, int H, int Hkv, int N, int d, int w) {
+    const double wc = w < N ? w : N, wide = d / 64.0, G = H / Hkv;
+    const double products = (double)B * H * (N * wc - wc * (wc - 1.0) / 2.0) * d;
+    const double steps = ceil(wc / 64.0 * wide), blocks = fmin((double)N, wc + 127.0) / 32.0 * wide;
+    const double row = backward ? 10.0 + fmax(products / 0.95e6, (2.5 + 3.0 * G) * steps) : 4.0 + fmax(products / 2.3e6, 2.5 * steps);
+    const double mfma = backward ? 15.0 + (1.7 + 2.0 * G) * blocks : 7.0 + 1.65 * blocks;
     return mfma < row;
 }
 
@@ -947,7 +977,7 @@ static hipError_t launch_fwd_f32_mfma(const float* Q, const float* K, const floa
 hipError_t forward_f32(const float* Q, const float* K, const float* V, const float* c, float* O, float* L,
                        int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s) {
     ProfScope prof(kKernForward, s);
-    if (f32_use_mfma(false, B, H, N, d, w)) {
+    if (f32_use_mfma(false, B, H, Hkv, N, d, w)) {
         // 256 queries per workgroup (two waves per SIMD) once that gives every CU one
         const bool wide = B * H * ((N + 255) / 256) >= device_cu_count();
         if (d == 128)
@@ -957,29 +987,49 @@ hipError_t forward_f32(const float* Q, const float* K, const float* V, const flo
                     : launch_fwd_f32_mfma<64, 4>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
     } else {
         const int blocks = B * H * ((N + kF32Waves - 1) / kF32Waves);
-        hipLaunchKernelGGL(fwd_f32_kernel, dim3(blocks), dim3(64 * kF32Waves), 0, s, Q, K, V, c, O, L, N, d, w, scale,
-                           H, H / Hkv);
+        if (d == 128)
+            hipLaunchKernelGGL((fwd_f32_kernel<128>), dim3(blocks), dim3(64 * kF32Waves), 0, s, Q, K, V, c, O, L, N, w, scale, H, H / Hkv);
+        else
+            hipLaunchKernelGGL((fwd_f32_kernel<64>), dim3(blocks), dim3(64 * kF32Waves), 0, s, Q, K, V, c, O, L, N, w, scale, H, H / Hkv);
     }
     return hipGetLastError();
 }
 
 template <int D>
-static hipError_t launch_bwd_f32_mfma(const float* Q, const float* K, const float* V, const float* dO, const float* c,
-                                      const float* L, const float* Dv, float* dQ, float* dK, float* dV, float* dc_col,
-                                      float* dc_row, int B, int H, int Hkv, int N, int w, float scale, hipStream_t s) {
+static hipError_t launch_bwd_f32(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,
+                                 const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, int B,
+                                 int H, int Hkv, int N, int w, float scale, hipStream_t s) {
+    const int G = H / Hkv;
+    if (!f32_use_mfma(true, B, H, Hkv, N, D, w)) {
+        const int per_head = (N + kF32Waves - 1) / kF32Waves;
+        {   // forms D as well, so it goes first
+            ProfScope prof(kKernDq, s);
+            hipLaunchKernelGGL((bwd_dq_f32_kernel<D>), dim3(B * H * per_head), dim3(64 * kF32Waves), 0, s, Q, K, V, O, dO, c, L, Dv,
+                               dQ, dc_row, N, w, scale, H, G);
+        }
+        ProfScope prof(kKernDkv, s);
+        hipLaunchKernelGGL((bwd_dkv_f32_kernel<D>), dim3(B * Hkv * per_head), dim3(64 * kF32Waves), 0, s, Q, K, V, dO, c, L, Dv, dK,
+                           dV, dc_col, N, w, scale, H, G);
+        return hipGetLastError();
+    }
     static DeviceOnce dkv_lds, dq_lds;
     constexpr size_t lds = sizeof(F32BwdSmem<D>);
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dkv_f32_mfma_kernel<D>), lds, dkv_lds)) return e;
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dq_f32_mfma_kernel<D>), lds, dq_lds)) return e;
-    const int nt = (N + 127) / 128;
+    const long rows = (long)B * H * N;
+    const int nt = (N + 127) / 128, dot_rows = 4 * RowStep<D>::kRows;
+    {
+        ProfScope prof(kKernRowDot, s);
+        hipLaunchKernelGGL((rowdot_f32_kernel<D>), dim3((unsigned)((rows + dot_rows - 1) / dot_rows)), dim3(256), 0, s, O, dO, Dv, rows);
+    }
     {
         ProfScope prof(kKernDkv, s);
         hipLaunchKernelGGL((bwd_dkv_f32_mfma_kernel<D>), dim3(B * Hkv * nt), dim3(kF32BwdThreads), lds, s, Q, K, V, dO, c, L, Dv,
-                           dK, dV, dc_col, N, w, scale, nt, B * Hkv * nt, H, H / Hkv);
+                           dK, dV, dc_col, N, w, scale, nt, B * Hkv * nt, H, G);
     }
     ProfScope prof(kKernDq, s);
     hipLaunchKernelGGL((bwd_dq_f32_mfma_kernel<D>), dim3(B * H * nt), dim3(kF32BwdThreads), lds, s, Q, K, V, dO, c, L, Dv, dQ,
-                       dc_row, N, w, scale, nt, B * H * nt, H, H / Hkv);
+                       dc_row, N, w, scale, nt, B * H * nt, H, G);
     return hipGetLastError();
 }
 
@@ -990,30 +1040,8 @@ hipError_t backward_f32(const float* Q, const float* K, const float* V, const fl
     float* Dv = ws;
     float* dc_col = ws + rows;
     float* dc_row = ws + 2 * rows;
-    const int per_head = (N + kF32Waves - 1) / kF32Waves;
-    const int blocks = B * H * per_head;
-    {
-        ProfScope prof(kKernRowDot, s);
-        hipLaunchKernelGGL(rowdot_f32_kernel, dim3((unsigned)((rows + kF32Waves - 1) / kF32Waves)),
-                           dim3(64 * kF32Waves), 0, s, O, dO, Dv, (long)rows, d);
-    }
-    if (f32_use_mfma(true, B, H, N, d, w)) {
-        const hipError_t e = d == 128 ? launch_bwd_f32_mfma<128>(Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, B, H, Hkv, N, w, scale, s)
-                                      : launch_bwd_f32_mfma<64>(Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, B, H, Hkv, N, w, scale, s);
-        if (e != hipSuccess) return e;
-    } else {
-        {
-            ProfScope prof(kKernDkv, s);
-            hipLaunchKernelGGL(bwd_dkv_f32_kernel, dim3(B * Hkv * per_head), dim3(64 * kF32Waves), 0, s, Q, K, V, dO,
-                               c, L, Dv, dK, dV, dc_col, N, d, w, scale, H, H / Hkv);
-        }
-        {
-            ProfScope prof(kKernDq, s);
-            hipLaunchKernelGGL(bwd_dq_f32_kernel, dim3(blocks), dim3(64 * kF32Waves), 0, s, Q, K, V, dO, c, L,
-                               Dv, dQ, dc_row, N, d, w, scale, H, H / Hkv);
-        }
-    }
-    hipError_t e = hipGetLastError();
+    const hipError_t e = d == 128 ? launch_bwd_f32<128>(Q, K, V, O, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, B, H, Hkv, N, w, scale, s)
+                                  : launch_bwd_f32<64>(Q, K, V, O, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, B, H, Hkv, N, w, scale, s);
     if (e != hipSuccess) return e;
     // behind the three vectors as the workspace query sizes them (each padded to 256 bytes)
     const size_t one = ((rows * sizeof(float)) + 255) & ~(size_t)255;
