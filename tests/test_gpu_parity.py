@@ -152,6 +152,30 @@ def test_gate_prefix_scan_then_propagate(g, oracle, B, H, N, act):
     assert np.abs(c - one_pass).max() <= tol
 
 
+@pytest.mark.parametrize("B,H,N", [
+    # up to two chunks of 4096 a row or segment takes four waves, beyond that sixteen: both sides, with and without a remainder
+    (3, 1, 8191), (1, 2, 8192), (2, 1, 8193), (1, 2, 12288), (1, 1, 12290),
+    # scan-then-propagate: segments of two and of three chunks
+    (2, 150, 49157), (4, 128, 32772)])
+@pytest.mark.parametrize("act", [False, True])
+def test_gate_scan_wave_counts(g, oracle, B, H, N, act):
+    note("gate scan", B, H, N, "activation" if act else "plain")
+    wl = gi.custom("gscan", B, H, N, 64, 8, alpha_mu=-1.0, index=17)
+    if act:
+        h, beta = gi.make_gate_inputs(wl)
+        args = (dev(h, "f32"), dev(beta, "f32"), GATE_EPS)
+        ref = oracle.gate_prefix(oracle.gate_activation(h, beta, GATE_EPS))
+        one_pass = g.gfwa_gate_activation_prefix(*args)
+    else:
+        alpha = gi.make_tensor(wl, "alpha")
+        args = (dev(alpha, "f32"),)
+        ref = oracle.gate_prefix(alpha)
+        one_pass = g.gfwa_gate_prefix(*args)
+    tol = 8 * np.finfo(np.float32).eps * ref.max()  # as above
+    for c in (one_pass, g.gfwa_gate_prefix_stp(*args)):
+        assert np.abs(host(c) - ref).max() <= tol
+
+
 def test_gate_activation_elementwise(g, oracle):
     # rows of length 1: c is alpha itself, so the activation is checked element by element, over
     # pre-activations from deeply negative (alpha ~ e^z, where the rounding of 1 + e^z would show) to large
@@ -643,6 +667,18 @@ def test_gqa_f32(g, oracle, B, H, Hkv, N, d, w):
     assert rel_inf(got["O"], ref["O"]) <= 1e-5
     assert (np.abs(got["L"] - ref["L"]) <= 1e-5 * np.abs(ref["L"]).max() + 1e-5).all()
     check_grads(got, ref, 1e-5, "gqa f32")
+
+
+# the one-wave-per-row kernels at the edges of their steps of 64 (d = 64) and 32 keys: one full step, one key more, several
+@pytest.mark.parametrize("B,H,Hkv,N,d,w", [(1, 8, 1, 66, 64, 64), (1, 4, 1, 97, 64, 65), (1, 2, 2, 131, 64, 129),
+                                           (2, 2, 2, 33, 128, 32), (1, 2, 1, 70, 128, 33)])
+def test_f32_row_steps(g, oracle, B, H, Hkv, N, d, w):
+    note("f32 row steps", B, H, Hkv, N, d, w)
+    wl = gi.custom("f32s", B, H, N, d, w, "f32", alpha_mu=-1.0, index=18, backward=True, kv_heads=Hkv)
+    got, ref = run_gqa(g, oracle, wl)
+    assert rel_inf(got["O"], ref["O"]) <= 1e-5
+    assert (np.abs(got["L"] - ref["L"]) <= 1e-5 * np.abs(ref["L"]).max() + 1e-5).all()
+    check_grads(got, ref, 1e-5, "f32 row steps")
 
 
 @pytest.mark.parametrize("B,H,Hkv,N,d,w,groups", [
