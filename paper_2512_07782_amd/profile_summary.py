@@ -52,6 +52,8 @@ LIB = {
     "bwd_dq_bf16_kernel<64>": "bwd_dq",
     "bwd_dkv8_bf16_kernel<128, false>": "bwd_dkv",
     "bwd_dq_bf16_kernel<128>": "bwd_dq",
+    # few or uneven tiles
+    "fwd_split_bf16_kernel": "forward", "bwd_dkv_split_bf16_kernel": "bwd_dkv", "bwd_dq_split_bf16_kernel": "bwd_dq",
     # fp32 storage
     "fwd_f32_mfma_kernel<128>": "forward", "fwd_f32_mfma_kernel<64>": "forward", "fwd_f32_kernel": "forward",
     "rowdot_f32_kernel": "bwd_rowdot",
@@ -61,6 +63,15 @@ LIB = {
 # the long_bwd workload of bench.py
 B, H, N, D, W = 1, 32, 16384, 128, 1024
 CAL = "plain f32 copy (calibration)"
+
+
+def lib_name(kernel: str):
+    """The library's name of a kernel, or None; the waves per workgroup of the scans and of the fp32 forward and the
+    sizes of the split and of the one-wave-per-row kernels do not matter."""
+    for k in (kernel, re.sub(r", \d+>$", ">", kernel), re.sub(r"<.*", "", kernel)):
+        if k in LIB:
+            return LIB[k]
+    return None
 
 
 def short(name: str) -> str:
@@ -116,7 +127,7 @@ def kernel_trace(kt_dir: str, log: str, bench_args: str = "--no-cpu-baseline --p
     ]
     for r in csv.DictReader(open(stats)):
         s = short(r["Name"])
-        b = bj["kernels"].get(LIB.get(s, ""), {}).get("avg_ms")
+        b = bj["kernels"].get(lib_name(s) or "", {}).get("avg_ms")
         out.append(f"{s:36.36s} {r['Calls']:>5s} {float(r['AverageNs']) / 1e3:9.1f} {float(r['MinNs']) / 1e3:9.1f} "
                    f"{float(r['MaxNs']) / 1e3:9.1f} {float(r['Percentage']):7.2f} "
                    f"{('%16.1f' % (b * 1e3)) if b else ' ' * 16}")
@@ -174,8 +185,9 @@ def hbm_traffic(fetch_dir: str, write_dir: str) -> str:
         f"{'algo wr MB':>10s} {'fetch/algo':>10s} {'write/algo':>10s}",
     ]
     rows, tot = [], [0.0, 0.0]
-    for s, name in LIB.items():
-        if s not in fe:
+    for s in fe:
+        name = lib_name(s)
+        if name not in algo:
             continue
         fb, wb = fe[s] * ff * 1024, wr[s] * wf * 1024
         ar, aw = algo[name]
