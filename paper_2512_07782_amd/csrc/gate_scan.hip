@@ -1,7 +1,7 @@
 // Gate prefix scans on gfx950 (paper Sec. 3.2 definition of the cumulative gate; Alg. 1, the
 // cumulative-sum / carry steps; Sec. 3.3 for the reverse scan that turns d(prefix) into d(alpha)).
 //
-// One workgroup of 4 or 16 waves streams one (b,h) row in chunks of 4096 elements, cut into 16 runs of 256 consecutive ones:
+// One workgroup of 4 or 16 waves (scan_four_waves) streams one (b,h) row in chunks of 4096 elements, cut into 16 runs of 256 consecutive ones:
 // float4 per lane, in-lane prefix, scan of the lane totals by DPP moves; the totals of runs and waves are added up in
 // fp64, across the waves through LDS, and a carry is kept in fp64 across chunks.  Every element is read once and written
 // once (8 bytes of HBM traffic per element).  Short rows are bound by latency: the loads of a chunk go out before
@@ -238,15 +238,24 @@ __global__ __launch_bounds__(64 * WAVES) void segment_sum_kernel(const float* __
     }
 }
 
-// Four waves with four runs of a chunk each, or sixteen with one.  Four have less to exchange and four times the loads in
-// flight per wave: better for a workgroup of one or two chunks (300 rows of 8192: 5.3 against 6.6 us).  Longer rows keep a CU
-// busy with one workgroup after another's barrier, and the activation is bound by vector work: sixteen waves cover that
-// (100 rows of 262144 with the activation: 127 against 249 us; sums of 512 segments with it: 7.0 against 8.0 us).
+// Four waves with four runs of a chunk each, or sixteen with one.  Four have less to exchange and more loads in flight per
+// wave: better for rows of one or two chunks once CUs have several (320 rows of 4096: 3.4 against 4.3 us; 1024 rows of 515:
+// 4.3 against 6.5; 300 rows of 8192: 5.3 against 6.6), and for segments (scan and sums of 8 rows of 32768: 5.8 against 6.2).
+// A workgroup alone on its CU has no other to hide its vector work and its scattered accesses behind, and sixteen waves
+// share them out: up to one per CU, sixteen are better with the activation (64 rows of 4096: 3.4 against 3.8 us, of 8192:
+// 4.9 against 6.3) and for whole rows of one chunk (64 rows of 515: 2.9 against 3.4; of 4096, in front of a forward that
+// displaces the inputs: the pair 67.7 against 68.8).
+// Longer rows keep a CU busy with one workgroup after another's barrier, and the activation is bound by vector work: sixteen
+// waves cover that (100 rows of 262144 with the activation: 127 against 249 us; sums of 512 segments with it: 7.0 against 8.0).
+static bool scan_four_waves(bool activation, bool segment, long workgroups, int len) {
+    if (workgroups <= device_cu_count() && (activation || (!segment && len <= kScanChunk))) return false;
+    return len <= 2 * kScanChunk;
+}
 template <bool REVERSE, int MODE>
 static void launch_scan(const float* a, const float* b, float* out, int rows, int N, float eps, const double* partial, int seg_len,
                         int P, hipStream_t s) {
     const unsigned wgs = (unsigned)(rows * P);
-    if ((partial != nullptr ? seg_len : N) <= 2 * kScanChunk)
+    if (scan_four_waves(MODE == kScanGate, partial != nullptr, wgs, partial != nullptr ? seg_len : N))
         hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 4>), dim3(wgs), dim3(256), 0, s, a, b, out, N, eps, partial, seg_len, P);
     else
         hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 16>), dim3(wgs), dim3(1024), 0, s, a, b, out, N, eps, partial, seg_len, P);

@@ -153,8 +153,11 @@ def test_gate_prefix_scan_then_propagate(g, oracle, B, H, N, act):
 
 
 @pytest.mark.parametrize("B,H,N", [
-    # up to two chunks of 4096 a row or segment takes four waves, beyond that sixteen: both sides, with and without a remainder
+    # two chunks of 4096 of a row take four waves (sixteen with the activation and few rows), longer rows sixteen: both
+    # sides, with and without a remainder
     (3, 1, 8191), (1, 2, 8192), (2, 1, 8193), (1, 2, 12288), (1, 1, 12290),
+    # rows of one chunk: sixteen waves up to one row per CU, four beyond
+    (2, 128, 515), (1, 257, 515), (8, 64, 4096),
     # scan-then-propagate: segments of two and of three chunks
     (2, 150, 49157), (4, 128, 32772)])
 @pytest.mark.parametrize("act", [False, True])
