@@ -49,6 +49,13 @@ struct RowStep {
         for (int u = 0; u < kLoads; ++u)
             x[u] = *reinterpret_cast<const f32x4*>(M + (size_t)min(row0 + u * kRows + lane / kLanes, last) * D + 4 * (lane % kLanes));
     }
+    // the rows past `last` become zero: they have weight zero, and zero times an infinity is NaN
+    __device__ __forceinline__ void clear_past(int row0, int last, int lane) {
+        if (row0 + kStep - 1 <= last) return;  // (the same in all lanes)
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u)
+            if (row0 + u * kRows + lane / kLanes > last) x[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     __device__ __forceinline__ float dot(const f32x4& q, int u) const {  // with the row whose columns q holds; in all its lanes
         float d = q[0] * x[u][0];
 #pragma unroll
@@ -107,6 +114,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void fwd_f32_kernel(
             s[u] = i0 + u * Step::kRows + r <= t ? s[u] : -INFINITY;
             mx = fmaxf(mx, s[u]);
         }
+        v.clear_past(i0, t, lane);
         const float mnew = Step::group_max(mx);  // finite: the step always holds a valid key
         const float a = expf(m - mnew);
         l *= a;
@@ -162,6 +170,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void bwd_dq_f32_kernel(
             one.x[0] = *reinterpret_cast<const f32x4*>(O + at);
             Dt = one.dot(g, 0);
         }
+        k.clear_past(i0, t, lane);
 #pragma unroll
         for (int u = 0; u < Step::kLoads; ++u) {
             const float s = fmaf(scale, k.dot(q, u), ci[u] - ct);
@@ -212,13 +221,16 @@ __global__ __launch_bounds__(64 * kF32Waves) void bwd_dkv_f32_kernel(
             q.load(Q + rows * D, t0, t_hi, lane);
             d.load(dO + rows * D, t0, t_hi, lane);
             rows_s[wv][lane] = row;
+            q.clear_past(t0, t_hi, lane);
+            d.clear_past(t0, t_hi, lane);
 #pragma unroll
             for (int u = 0; u < Step::kLoads; ++u) {
                 const int n = u * Step::kRows + r;
                 const f32x4 x = rows_s[wv][n];
                 const float s = fmaf(scale, q.dot(k, u), ci - x[0]);
-                const float p = t0 + n <= t_hi ? expf(s - x[1]) : 0.f;
-                const float ds = p * (d.dot(v, u) - x[2]);
+                const bool seen = t0 + n <= t_hi;
+                const float p = seen ? expf(s - x[1]) : 0.f;
+                const float ds = seen ? p * (d.dot(v, u) - x[2]) : 0.f;
                 cs += ds;
                 dv = fma4(p, d.x[u], dv);
                 dk = fma4(ds, q.x[u], dk);

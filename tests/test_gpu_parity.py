@@ -684,6 +684,38 @@ def test_f32_row_steps(g, oracle, B, H, Hkv, N, d, w):
     check_grads(got, ref, 1e-5, "f32 row steps")
 
 
+# (the one-wave-per-row kernels: steps of 64 keys at d = 64, of 32 at d = 128, the last ones of a row partly filled)
+@pytest.mark.parametrize("B,H,Hkv,N,d,w", [(1, 2, 1, 77, 64, 30), (1, 2, 2, 50, 128, 33)])
+def test_f32_rows_with_infinities(g, oracle, B, H, Hkv, N, d, w):
+    note("f32 rows with infinities", B, H, Hkv, N, d, w)
+    wl = gi.custom("f32i", B, H, N, d, w, "f32", alpha_mu=-1.0, index=19, backward=True, kv_heads=Hkv)
+    ins = {t: gi.make_tensor(wl, t) for t in ("Q", "K", "V", "alpha", "dO")}
+    c = dev(oracle.gate_prefix(ins["alpha"]).astype(np.float32), "f32")
+    Q, K, V, dO = (dev(ins[t], "f32") for t in ("Q", "K", "V", "dO"))
+    O, L = g.gfwa_forward_gqa(Q, K, V, c, w, wl.scale)
+    want = [O, *g.gfwa_backward_gqa(Q, K, V, O, dO, c, L, w, wl.scale)]
+    # one value column of one key: plus infinity in that column of the rows that see the key, all else as without it
+    key, col = N // 2, 5
+    Vi = V.clone()
+    Vi[:, :, key, col] = float("inf")
+    Oi, _ = g.gfwa_forward_gqa(Q, K, Vi, c, w, wl.scale)
+    hit = torch.zeros_like(O, dtype=torch.bool)
+    hit[:, :, key:key + w, col] = True
+    assert (Oi[hit] == float("inf")).all() and torch.equal(Oi[~hit], O[~hit])
+    # one gradient entry of one row: what does not depend on the row is as without it
+    row = N // 3
+    dOi = dO.clone()
+    dOi[:, :, row, col] = float("inf")
+    dQ, dK, dV, _ = g.gfwa_backward_gqa(Q, K, V, O, dOi, c, L, w, wl.scale)
+    keys = torch.arange(N, device=DEV)
+    free = (keys < row - w + 1) | (keys > row)
+    assert torch.equal(dQ[:, :, keys != row], want[1][:, :, keys != row])
+    assert torch.equal(dK[:, :, free], want[2][:, :, free]) and torch.equal(dV[:, :, free], want[3][:, :, free])
+    others = torch.arange(d, device=DEV) != col
+    assert torch.equal(dV[..., others], want[3][..., others])
+    assert (dV[:, :, ~free, col] == float("inf")).all()
+
+
 @pytest.mark.parametrize("B,H,Hkv,N,d,w,groups", [
     # the matrix-core kernels at the edges of their tiles: 128- and 256-query tiles with a last row, a last block and a
     # full one, windows of one key, inside one block, across one, past the sequence; sampled heads
