@@ -25,6 +25,7 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 // 256 rows, w = 64, d = 64: 11.1 us, now 8.9.)
 // ==========================================================================================
 constexpr int kF32Waves = 4;
+constexpr int kRowLoads = 16;  // load instructions per matrix and step
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_moved(float x) {
@@ -38,10 +39,10 @@ __device__ __forceinline__ float row_pair_max(float x) {
     auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-template <int D>
+template <int D, int LOADS>
 struct RowStep {
     static constexpr int kLanes = D / 4, kRows = 64 / kLanes;  // lanes per row, rows per load instruction
-    static constexpr int kLoads = 16, kStep = kLoads * kRows;  // rows per step
+    static constexpr int kLoads = LOADS, kStep = kLoads * kRows;  // rows per step
     f32x4 x[kLoads];
     // rows row0 + u kRows + lane / kLanes, u = 0 .. kLoads - 1, of the matrix at M; past `last`: row `last`
     __device__ __forceinline__ void load(const float* M, int row0, int last, int lane) {
@@ -77,28 +78,16 @@ __device__ __forceinline__ f32x4 fma4(float a, const f32x4& x, const f32x4& c) {
     return {fmaf(a, x[0], c[0]), fmaf(a, x[1], c[1]), fmaf(a, x[2], c[2]), fmaf(a, x[3], c[3])};
 }
 
-// ---- forward: online softmax over the steps of the window of row t
-template <int D>
-__global__ __launch_bounds__(64 * kF32Waves) void fwd_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-    const float* __restrict__ c, float* __restrict__ O, float* __restrict__ L, int N, int w,
-    float scale, int H, int G) {
-    using Step = RowStep<D>;
-    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int rows_per_head = (N + kF32Waves - 1) / kF32Waves;
-    const int bh = blockIdx.x / rows_per_head;
-    const int t = (blockIdx.x % rows_per_head) * kF32Waves + wv;
-    if (t >= N) return;  // whole wave leaves; no workgroup barriers are used below
-    const size_t ho = (size_t)bh * N * D;
-    const size_t kvo = (size_t)kv_head_of(bh, H, G) * N * D;
-    const float* Kh = K + kvo;
-    const float* Vh = V + kvo;
-    const float* ch = c + (size_t)bh * N;
+// ---- forward: online softmax over the steps of the window of row t.  Pointers are the head's.
+template <int D, int LOADS>
+__device__ __forceinline__ void fwd_row(const float* Qh, const float* Kh, const float* Vh, const float* ch, float* Oh, float* Lh, int t,
+                                        int w, float scale, int lane) {
+    using Step = RowStep<D, LOADS>;
     const int r = lane / Step::kLanes, col = 4 * (lane % Step::kLanes);
     const int lo = max(0, t - w + 1);
     Step k, v;
     float ci[Step::kLoads];
-    const f32x4 q = *reinterpret_cast<const f32x4*>(Q + ho + (size_t)t * D + col);
+    const f32x4 q = *reinterpret_cast<const f32x4*>(Qh + (size_t)t * D + col);
     const float ct = ch[t];
     float m = -INFINITY, l = 0.f;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
@@ -115,59 +104,60 @@ __global__ __launch_bounds__(64 * kF32Waves) void fwd_f32_kernel(
             mx = fmaxf(mx, s[u]);
         }
         v.clear_past(i0, t, lane);
-        const float mnew = Step::group_max(mx);  // finite: the step always holds a valid key
-        const float a = expf(m - mnew);
+        const float mnew = Step::group_max(mx);
+        const float ref = mnew == -INFINITY ? 0.f : mnew;  // (every score so far is minus infinity: weight zero)
+        const float a = expf(m - ref);
         l *= a;
         o *= a;
         m = mnew;
 #pragma unroll
         for (int u = 0; u < Step::kLoads; ++u) {
-            const float p = expf(s[u] - mnew);
+            const float p = expf(s[u] - ref);
             l += p;
             o = fma4(p, v.x[u], o);
         }
     }
     l = Step::group_sum(l);
     o = Step::group_sum(o);
-    if (r == 0) *reinterpret_cast<f32x4*>(O + ho + (size_t)t * D + col) = f32x4{o[0] / l, o[1] / l, o[2] / l, o[3] / l};
-    if (lane == 0) L[(size_t)bh * N + t] = m + logf(l);
+    if (r == 0) *reinterpret_cast<f32x4*>(Oh + (size_t)t * D + col) = f32x4{o[0] / l, o[1] / l, o[2] / l, o[3] / l};
+    if (lane == 0) Lh[t] = m + logf(l);
 }
-
-// ---- D_t = <O_t, dO_t>, dQ_t and the row sum of dS
 template <int D>
-__global__ __launch_bounds__(64 * kF32Waves) void bwd_dq_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ O,
-    const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
-    float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dc_row, int N,
-    int w, float scale, int H, int G) {
-    using Step = RowStep<D>;
+__global__ __launch_bounds__(64 * kF32Waves) void fwd_f32_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+    const float* __restrict__ c, float* __restrict__ O, float* __restrict__ L, int N, int w,
+    float scale, int H, int G) {
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rows_per_head = (N + kF32Waves - 1) / kF32Waves;
     const int bh = blockIdx.x / rows_per_head;
     const int t = (blockIdx.x % rows_per_head) * kF32Waves + wv;
-    if (t >= N) return;
-    const size_t ho = (size_t)bh * N * D;
-    const size_t kvo = (size_t)kv_head_of(bh, H, G) * N * D;
-    const float* Kh = K + kvo;
-    const float* Vh = V + kvo;
-    const float* ch = c + (size_t)bh * N;
+    if (t >= N) return;  // whole wave leaves; no workgroup barriers are used below
+    const size_t ho = (size_t)bh * N * D, kvo = (size_t)kv_head_of(bh, H, G) * N * D, rows = (size_t)bh * N;
+    fwd_row<D, kRowLoads>(Q + ho, K + kvo, V + kvo, c + rows, O + ho, L + rows, t, w, scale, lane);
+}
+
+// ---- dQ_t and the row sum of dS.  Where Oh is given D_t = <O_t, dO_t> is formed and stored, else it is read.
+template <int D, int LOADS>
+__device__ __forceinline__ void dq_row(const float* Qh, const float* Kh, const float* Vh, const float* Oh, const float* dOh, const float* ch,
+                                       const float* Lh, float* Dh, float* dQh, float* dc_rowh, int t, int w, float scale, int lane) {
+    using Step = RowStep<D, LOADS>;
     const int r = lane / Step::kLanes, col = 4 * (lane % Step::kLanes);
     const int lo = max(0, t - w + 1);
     Step k, v;
     float ci[Step::kLoads];
-    const size_t at = ho + (size_t)t * D + col;
-    const f32x4 q = *reinterpret_cast<const f32x4*>(Q + at), g = *reinterpret_cast<const f32x4*>(dO + at);
-    const float ct = ch[t], Lt = L[(size_t)bh * N + t];
-    float Dt = 0.f, rs = 0.f;
+    const size_t at = (size_t)t * D + col;
+    const f32x4 q = *reinterpret_cast<const f32x4*>(Qh + at), g = *reinterpret_cast<const f32x4*>(dOh + at);
+    const float ct = ch[t], Lt = Lh[t];
+    float Dt = Oh == nullptr ? Dh[t] : 0.f, rs = 0.f;
     f32x4 dq = {0.f, 0.f, 0.f, 0.f};
     for (int i0 = lo; i0 <= t; i0 += Step::kStep) {
         k.load(Kh, i0, t, lane);
 #pragma unroll
         for (int u = 0; u < Step::kLoads; ++u) ci[u] = ch[min(i0 + u * Step::kRows + r, t)];
         v.load(Vh, i0, t, lane);
-        if (i0 == lo) {
-            RowStep<D> one;
-            one.x[0] = *reinterpret_cast<const f32x4*>(O + at);
+        if (Oh != nullptr && i0 == lo) {
+            RowStep<D, 1> one;
+            one.x[0] = *reinterpret_cast<const f32x4*>(Oh + at);
             Dt = one.dot(g, 0);
         }
         k.clear_past(i0, t, lane);
@@ -181,33 +171,37 @@ __global__ __launch_bounds__(64 * kF32Waves) void bwd_dq_f32_kernel(
     }
     rs = Step::group_sum(rs);
     dq = Step::group_sum(dq);
-    if (r == 0) *reinterpret_cast<f32x4*>(dQ + at) = dq * scale;
+    if (r == 0) *reinterpret_cast<f32x4*>(dQh + at) = dq * scale;
     if (lane == 0) {
-        Dv[(size_t)bh * N + t] = Dt;
-        dc_row[(size_t)bh * N + t] = rs;
+        if (Oh != nullptr) Dh[t] = Dt;
+        dc_rowh[t] = rs;
     }
 }
-
-// ---- dK_i, dV_i (summed over the G query heads that read this key/value head) and, per query
-// head, the column sum of dS
 template <int D>
-__global__ __launch_bounds__(64 * kF32Waves) void bwd_dkv_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+__global__ __launch_bounds__(64 * kF32Waves) void bwd_dq_f32_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ O,
     const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
-    const float* __restrict__ Dv, float* __restrict__ dK, float* __restrict__ dV,
-    float* __restrict__ dc_col, int N, int w, float scale, int H, int G) {
-    using Step = RowStep<D>;
-    __shared__ f32x4 rows_s[kF32Waves][64];  // c, L, D of a step's queries
+    float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dc_row, int N,
+    int w, float scale, int H, int G) {
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rows_per_head = (N + kF32Waves - 1) / kF32Waves;
-    const int bkv = blockIdx.x / rows_per_head;  // flat key/value head
-    const int i = (blockIdx.x % rows_per_head) * kF32Waves + wv;
-    if (i >= N) return;
-    const int Hkv = H / G;
-    const int bh0 = (bkv / Hkv) * H + (bkv % Hkv) * G;  // first query head of the group
+    const int bh = blockIdx.x / rows_per_head;
+    const int t = (blockIdx.x % rows_per_head) * kF32Waves + wv;
+    if (t >= N) return;
+    const size_t ho = (size_t)bh * N * D, kvo = (size_t)kv_head_of(bh, H, G) * N * D, rows = (size_t)bh * N;
+    dq_row<D, kRowLoads>(Q + ho, K + kvo, V + kvo, O + ho, dO + ho, c + rows, L + rows, Dv + rows, dQ + ho, dc_row + rows, t, w, scale, lane);
+}
+
+// ---- dK_i, dV_i (summed over the G query heads that read this key/value head, bh0 the first) and, per query head, the
+// column sum of dS.  rows_s: 64 places of LDS of the wave's own, for c, L, D of a step's queries.
+template <int D, int LOADS>
+__device__ __forceinline__ void dkv_row(const float* Q, const float* Kh, const float* Vh, const float* dO, const float* c, const float* L,
+                                        const float* Dv, float* dKh, float* dVh, float* dc_col, f32x4* rows_s, int bh0, int G, int i, int N,
+                                        int w, float scale, int lane) {
+    using Step = RowStep<D, LOADS>;
     const int r = lane / Step::kLanes, col = 4 * (lane % Step::kLanes);
-    const size_t at = (size_t)bkv * N * D + (size_t)i * D + col;
-    const f32x4 k = *reinterpret_cast<const f32x4*>(K + at), v = *reinterpret_cast<const f32x4*>(V + at);
+    const size_t at = (size_t)i * D + col;
+    const f32x4 k = *reinterpret_cast<const f32x4*>(Kh + at), v = *reinterpret_cast<const f32x4*>(Vh + at);
     const int t_hi = (int)min((long)N - 1, (long)i + w - 1);  // key i is seen by rows i .. i+w-1
     f32x4 dk = {0.f, 0.f, 0.f, 0.f}, dv = dk;
     Step q, d;
@@ -220,13 +214,13 @@ __global__ __launch_bounds__(64 * kF32Waves) void bwd_dkv_f32_kernel(
             const f32x4 row = {c[rows + tl], L[rows + tl], Dv[rows + tl], 0.f};
             q.load(Q + rows * D, t0, t_hi, lane);
             d.load(dO + rows * D, t0, t_hi, lane);
-            rows_s[wv][lane] = row;
+            rows_s[lane] = row;
             q.clear_past(t0, t_hi, lane);
             d.clear_past(t0, t_hi, lane);
 #pragma unroll
             for (int u = 0; u < Step::kLoads; ++u) {
                 const int n = u * Step::kRows + r;
-                const f32x4 x = rows_s[wv][n];
+                const f32x4 x = rows_s[n];
                 const float s = fmaf(scale, q.dot(k, u), ci - x[0]);
                 const bool seen = t0 + n <= t_hi;
                 const float p = seen ? expf(s - x[1]) : 0.f;
@@ -242,9 +236,26 @@ __global__ __launch_bounds__(64 * kF32Waves) void bwd_dkv_f32_kernel(
     dk = Step::group_sum(dk);
     dv = Step::group_sum(dv);
     if (r == 0) {
-        *reinterpret_cast<f32x4*>(dK + at) = dk * scale;
-        *reinterpret_cast<f32x4*>(dV + at) = dv;
+        *reinterpret_cast<f32x4*>(dKh + at) = dk * scale;
+        *reinterpret_cast<f32x4*>(dVh + at) = dv;
     }
+}
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves) void bwd_dkv_f32_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+    const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
+    const float* __restrict__ Dv, float* __restrict__ dK, float* __restrict__ dV,
+    float* __restrict__ dc_col, int N, int w, float scale, int H, int G) {
+    __shared__ f32x4 rows_s[kF32Waves][64];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rows_per_head = (N + kF32Waves - 1) / kF32Waves;
+    const int bkv = blockIdx.x / rows_per_head;  // flat key/value head
+    const int i = (blockIdx.x % rows_per_head) * kF32Waves + wv;
+    if (i >= N) return;
+    const int Hkv = H / G;
+    const size_t kvo = (size_t)bkv * N * D;
+    dkv_row<D, kRowLoads>(Q, K + kvo, V + kvo, dO, c, L, Dv, dK + kvo, dV + kvo, dc_col, rows_s[wv], (bkv / Hkv) * H + (bkv % Hkv) * G, G, i, N, w,
+               scale, lane);
 }
 
 // ==========================================================================================
@@ -300,6 +311,24 @@ __device__ __forceinline__ void split_row(const float* g, bf16x8 (&f)[3]) {
 __device__ __forceinline__ void split_acc(const f32x16& s, int c2, bf16x8 (&f)[3]) {
     split_frag([&](int j) __attribute__((always_inline)) { return s[8 * c2 + j]; }, f);
 }
+// Whether the rows a wave has finished have to be formed once more by the one-wave-per-row code above, which is plain fp32
+// throughout.  The pieces hold every fp32 value but the infinities and those from 2^128 - 2^119 on, whose first piece is infinite and
+// whose second is NaN, and products of pieces can overflow with either sign where the whole product is one infinity.  Any
+// of it leaves NaN or an infinity in each result that it is part of, so the results are looked at, once, when they are done.
+constexpr int kAgainLoads = 4;  // (few registers: that code must not cost the kernels that contain it any)
+struct RangeCheck {
+    bool finite = true;
+    __device__ __forceinline__ void add(float x) { finite = finite && fabsf(x) <= 3.402823466e38f; }
+    template <int DB>
+    __device__ __forceinline__ void add(const f32x16 (&x)[DB]) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) add(x[db][v]);
+    }
+    // (the same in all lanes; valid: this lane's row exists)
+    __device__ __forceinline__ bool failed(bool valid) const { return __builtin_amdgcn_ballot_w64(valid && !finite) != 0; }
+};
 // 32 rows of a [N, D] matrix in LDS, as three bf16 planes with the swizzle of tile_off
 template <int D>
 struct SplitTile {
@@ -554,7 +583,14 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 ? 1 : 2) void fwd_f32_
     }
     for (; jb <= jb_hi; ++jb) idle_step(jb);
     const float l = xhalf_sum(lh);
-    if (t < N) {
+    RangeCheck check;
+    check.add(o);
+    check.add(l);
+    check.add(1.0f / l);  // (no score of the row above the first reference)
+    if (__builtin_expect(check.failed(t < N), 0)) {
+#pragma unroll 1
+        for (int row = qw0; row < min(N, qw0 + 32); ++row) fwd_row<D, kAgainLoads>(Q + ho, Kh, Vh, ch, O + ho, L + (size_t)bh * N, row, w, scale, lane);
+    } else if (t < N) {
         float* orow = O + ho + (size_t)t * D;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -732,18 +768,31 @@ __global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dq_f32_mfma_kernel(
         wg_barrier();
         if (role == 0) {
             rs = xhalf_sum(rs + xch[4 * DB * 64 + lane][0]);
-            if (t < N) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    const f32x4 x = xch[(4 * db + i4) * 64 + lane];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[db][4 * i4 + j] = scale * (acc[db][4 * i4 + j] + x[j]);
+                }
+            RangeCheck check;
+            check.add(acc);
+            check.add(rs);
+            if (__builtin_expect(check.failed(t < N), 0)) {
+                const size_t rows = (size_t)bh * N;
+#pragma unroll 1
+                for (int row = qw0; row < min(N, qw0 + 32); ++row)
+                    dq_row<D, kAgainLoads>(Q + ho, Kh, Vh, nullptr, dO + ho, ch, L + rows, const_cast<float*>(Dv + rows), dQ + ho, dc_row + rows, row, w,
+                              scale, lane);
+            } else if (t < N) {
                 float* out = dQ + ho + (size_t)t * D;
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
 #pragma unroll
-                    for (int i4 = 0; i4 < 4; ++i4) {
-                        const f32x4 x = xch[(4 * db + i4) * 64 + lane];
-                        f32x4 o4;
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) o4[j] = scale * (acc[db][4 * i4 + j] + x[j]);
-                        *reinterpret_cast<f32x4*>(out + 32 * db + 8 * i4 + 4 * h) = o4;
-                    }
+                    for (int i4 = 0; i4 < 4; ++i4)
+                        *reinterpret_cast<f32x4*>(out + 32 * db + 8 * i4 + 4 * h) =
+                            f32x4{acc[db][4 * i4], acc[db][4 * i4 + 1], acc[db][4 * i4 + 2], acc[db][4 * i4 + 3]};
                 if (h == 0) dc_row[(size_t)bh * N + t] = rs;
             }
         }
@@ -838,6 +887,7 @@ __global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dkv_f32_mfma_kernel(
             stash_share(0, 1);
             end_step();
         };
+        RangeCheck check;
         const int b_lo = kw0 < N ? kg : nblk, b_hi = (int)min((long)nblk - 1, ((long)kw0 + 30 + w) / 32 - qb_lo);
         for (int g = 0; g < G; ++g) {  // query heads
             int b = 0;
@@ -922,22 +972,37 @@ __global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dkv_f32_mfma_kernel(
                     second_product(min(b, nblk - 1));  // (its tile and its P are still there in the step that follows, whatever that is)
                 }
                 const float cs_all = xhalf_sum(colsum);
+                check.add(cs_all);
                 if (i < N && h == 0) dc_col[(size_t)(bh0 + g) * N + i] = cs_all;
             }
             for (; b < nblk; ++b) idle_step(g, b);
         }
-        if (i < N) {
-            float* out = (role == 0 ? dV : dK) + kvo + (size_t)i * D;
-            const float f = role == 0 ? 1.0f : scale;
+        if (role == 1)
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    f32x4 a;
+                for (int v = 0; v < 16; ++v) acc[db][v] *= scale;
+        check.add(acc);
+        const bool failed = check.failed(i < N);
+        wg_barrier();  // the tiles and the exchange are read, their space is free
+        int* verdict = reinterpret_cast<int*>(smem_raw);  // [pair][role]
+        if (lane == 0) verdict[2 * kg + role] = failed;
+        wg_barrier();
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane(verdict[2 * kg] | verdict[2 * kg + 1]), 0)) {
+            // both results of the pair's keys, by the wave that has already stored column sums of them
+            f32x4* rows_s = reinterpret_cast<f32x4*>(smem_raw + 1024) + 64 * kg;
+            if (role == 1)
+#pragma unroll 1
+                for (int key = kw0; key < min(N, kw0 + 32); ++key)
+                    dkv_row<D, kAgainLoads>(Q, K + kvo, V + kvo, dO, c, L, Dv, dK + kvo, dV + kvo, dc_col, rows_s, bh0, G, key, N, w, scale, lane);
+        } else if (i < N) {
+            float* out = (role == 0 ? dV : dK) + kvo + (size_t)i * D;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) a[j] = f * acc[db][4 * i4 + j];
-                    *reinterpret_cast<f32x4*>(out + 32 * db + 8 * i4 + 4 * h) = a;
-                }
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4)
+                    *reinterpret_cast<f32x4*>(out + 32 * db + 8 * i4 + 4 * h) =
+                        f32x4{acc[db][4 * i4], acc[db][4 * i4 + 1], acc[db][4 * i4 + 2], acc[db][4 * i4 + 3]};
         }
     };
     if (wv < 4) run(std::integral_constant<int, 0>{});
@@ -948,7 +1013,7 @@ __global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dkv_f32_mfma_kernel(
 template <int D>
 __global__ __launch_bounds__(256) void rowdot_f32_kernel(const float* __restrict__ O, const float* __restrict__ dO,
                                                          float* __restrict__ Dv, long rows) {
-    using Step = RowStep<D>;
+    using Step = RowStep<D, 1>;
     const int lane = threadIdx.x & 63;
     const long row = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * Step::kRows + lane / Step::kLanes;
     if (row - lane / Step::kLanes >= rows) return;  // the whole wave
@@ -1029,7 +1094,7 @@ static hipError_t launch_bwd_f32(const float* Q, const float* K, const float* V,
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dkv_f32_mfma_kernel<D>), lds, dkv_lds)) return e;
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dq_f32_mfma_kernel<D>), lds, dq_lds)) return e;
     const long rows = (long)B * H * N;
-    const int nt = (N + 127) / 128, dot_rows = 4 * RowStep<D>::kRows;
+    const int nt = (N + 127) / 128, dot_rows = 4 * RowStep<D, 1>::kRows;
     {
         ProfScope prof(kKernRowDot, s);
         hipLaunchKernelGGL((rowdot_f32_kernel<D>), dim3((unsigned)((rows + dot_rows - 1) / dot_rows)), dim3(256), 0, s, O, dO, Dv, rows);

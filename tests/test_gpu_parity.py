@@ -716,6 +716,68 @@ def test_f32_rows_with_infinities(g, oracle, B, H, Hkv, N, d, w):
     assert (dV[:, :, ~free, col] == float("inf")).all()
 
 
+# fp32 storage takes every finite value, and infinities where plain fp32 arithmetic gives a meaning to them, at any size
+@pytest.mark.parametrize("H,Hkv,N,d,w", [(4, 2, 1100, 128, 400), (4, 4, 1300, 64, 300)])
+def test_f32_matrix_core_range(g, oracle, H, Hkv, N, d, w):
+    note("f32 range", H, Hkv, N, d, w)
+    wl = gi.custom("f32x", 1, H, N, d, w, "f32", alpha_mu=-2.0, index=20, backward=True, kv_heads=Hkv)
+    ins = {t: gi.make_tensor(wl, t).astype(np.float32) for t in ("Q", "K", "V", "alpha", "dO")}
+    ins["Q"][..., 0] = 1.0 + np.abs(ins["Q"][..., 0])
+    c_host = oracle.gate_prefix(ins["alpha"]).astype(np.float32)
+    c = dev(c_host, "f32")
+    big, key, col = np.finfo(np.float32).max, N // 2, 5
+    forward = lambda Q, K, V: g.gfwa_forward_gqa(dev(Q, "f32"), dev(K, "f32"), dev(V, "f32"), c, w, wl.scale)
+    clean = [host(x) for x in forward(ins["Q"], ins["K"], ins["V"])]
+    hit = np.zeros(clean[0].shape, dtype=bool)
+    hit[:, :, key:key + w, col] = True
+
+    def near(got, want, tag):
+        note("  ", tag, rel_inf(got, want))
+        assert np.isfinite(got).all() and rel_inf(got, want) <= 1e-5, tag
+
+    # an infinite and the largest finite value in one column of V
+    for x in (np.inf, big):
+        V = ins["V"].copy()
+        V[:, :, key, col] = x
+        O, L = (host(y) for y in forward(ins["Q"], ins["K"], V))
+        near(O[~hit], clean[0][~hit], f"V {x}: other elements")
+        near(L, clean[1], "L")
+        if np.isinf(x):
+            assert (O[hit] == np.inf).all()
+        else:
+            O_ref, _ = oracle.forward_gqa_from_c(ins["Q"], ins["K"], V, c_host, w, wl.scale)
+            near(O[hit], O_ref[hit], "V max")
+    # a key nobody may see: the scores are minus infinity, the type's lowest value, or overflow
+    K = ins["K"].copy()
+    K[:, :, key, 0] = -1e5
+    want = [host(x) for x in forward(ins["Q"], K, ins["V"])]
+    for x in (-np.inf, -big):
+        K[:, :, key, 0] = x
+        for got, ref in zip(forward(ins["Q"], K, ins["V"]), want):
+            near(host(got), ref, f"K {x}")
+    Q, K = ins["Q"].copy(), ins["K"].copy()
+    K[..., 0] = 0.0
+    want = [host(x) for x in forward(Q, np.where(np.arange(N)[:, None] == key, np.eye(1, d) * -1e5, K).astype(np.float32), ins["V"])]
+    Q[..., 0] *= 1e25
+    K[:, :, key, 0] = -1.2345678e20
+    for got, ref in zip(forward(Q, K, ins["V"]), want):
+        near(host(got), ref, "overflowing product")
+    # backward: the type's lowest value in K, its largest in V, in dO (scaled so that the results are finite)
+    for name, x, shrink in (("K", -big, ()), ("V", big, ("dO",)), ("dO", big, ("V", "dO"))):
+        t = {k: ins[k].copy() for k in ("Q", "K", "V", "dO")}
+        for k in shrink:
+            t[k] = (t[k] * np.float32(2.0 ** -30)).astype(np.float32)
+        t[name][:, :, key, 0 if name == "K" else col] = x
+        O_ref, L_ref = oracle.forward_gqa_from_c(t["Q"], t["K"], t["V"], c_host, w, wl.scale)
+        ref = oracle.backward_gqa_from_c(t["Q"], t["K"], t["V"], c_host, t["dO"], w, wl.scale)
+        got = g.gfwa_backward_gqa(*(dev(t[k], "f32") for k in ("Q", "K", "V")), dev(O_ref.astype(np.float32), "f32"), dev(t["dO"], "f32"),
+                                  c, dev(L_ref.astype(np.float32), "f32"), w, wl.scale)
+        for k, y in zip(("dQ", "dK", "dV", "dalpha"), got):
+            r = rel_l2(host(y), ref[k].reshape(y.shape))
+            note("  backward", name, x, k, r)
+            assert r <= 1e-5, (name, k)
+
+
 @pytest.mark.parametrize("B,H,Hkv,N,d,w,groups", [
     # the matrix-core kernels at the edges of their tiles: 128- and 256-query tiles with a last row, a last block and a
     # full one, windows of one key, inside one block, across one, past the sequence; sampled heads
