@@ -34,7 +34,10 @@ typedef struct ihipStream_t *gfwa_stream_t;
 typedef int gfwa_dtype_t;
 enum {
     GFWA_BF16 = 0, /* Q,K,V,O,dO,dQ,dK,dV stored as bfloat16; products on bf16 MFMA, fp32 accumulate */
-    GFWA_F32 = 1   /* stored as float; all arithmetic fp32 */
+    GFWA_F32 = 1   /* stored as float, any finite value.  Large problems form a product of two floats from three bf16
+                      pieces of each, accurate to 2^-22 of it, accumulated in fp32; a piece of an element below 2^-110 in
+                      magnitude is only kept to 2^-134, and where a whole block of results is so small that this would show
+                      (all below 2^-80), or one is not finite, the block is formed again in plain fp32 arithmetic. */
 };
 
 typedef enum {

@@ -1,5 +1,5 @@
-// fp32 storage path of GatedFWA on gfx950: forward (paper Alg. 2) and backward (Alg. 3) with all
-// arithmetic in fp32, for problems that need fp32 accuracy; the bf16 MFMA kernels are the throughput path.
+// fp32 storage path of GatedFWA on gfx950: forward (paper Alg. 2) and backward (Alg. 3) to fp32 accuracy, for problems that
+// need it; the bf16 MFMA kernels are the throughput path.
 // Two sets of kernels.  The matrix-core set (bf16 MFMAs on operands split into three pieces, the structure of the bf16
 // kernels: a lane owns a query or a key, the second product takes the first one's accumulator registers as its operand)
 // serves everything but tiny problems.  The one-wave-per-row set (plain FMA) has a launch's latency and serves those; forward_f32 / backward_f32 choose (f32_use_mfma).
@@ -312,22 +312,33 @@ __device__ __forceinline__ void split_acc(const f32x16& s, int c2, bf16x8 (&f)[3
     split_frag([&](int j) __attribute__((always_inline)) { return s[8 * c2 + j]; }, f);
 }
 // Whether the rows a wave has finished have to be formed once more by the one-wave-per-row code above, which is plain fp32
-// throughout.  The pieces hold every fp32 value but the infinities and those from 2^128 - 2^119 on, whose first piece is infinite and
+// throughout.  Two reasons.  The pieces hold every fp32 value but the infinities and those from 2^128 - 2^119 on, whose first piece is infinite and
 // whose second is NaN, and products of pieces can overflow with either sign where the whole product is one infinity.  Any
 // of it leaves NaN or an infinity in each result that it is part of, so the results are looked at, once, when they are done.
+// And pieces end at 2^-133: a value below 2^-110 loses its low bits, of 2^-122 all but 11.  Beside values that are 2^24 times as
+// large that is nothing, but a whole matrix may be that small (an unscaled gradient, say).  Then all results are, since
+// each of O, dQ, dK, dV is a sum over the rows of one matrix with weights that another has made: rows that are not zero but
+// below 2^-80 throughout a wave's 32 are formed again as well.
 constexpr int kAgainLoads = 4;  // (few registers: that code must not cost the kernels that contain it any)
 struct RangeCheck {
     bool finite = true;
+    float largest = 0.f;
     __device__ __forceinline__ void add(float x) { finite = finite && fabsf(x) <= 3.402823466e38f; }
     template <int DB>
     __device__ __forceinline__ void add(const f32x16 (&x)[DB]) {
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) add(x[db][v]);
+            for (int v = 0; v < 16; ++v) {
+                add(x[db][v]);
+                largest = fmaxf(largest, fabsf(x[db][v]));
+            }
     }
     // (the same in all lanes; valid: this lane's row exists)
-    __device__ __forceinline__ bool failed(bool valid) const { return __builtin_amdgcn_ballot_w64(valid && !finite) != 0; }
+    __device__ __forceinline__ bool failed(bool valid) const {
+        return __builtin_amdgcn_ballot_w64(valid && !finite) != 0 ||
+               (__builtin_amdgcn_ballot_w64(valid && largest >= 8.27180613e-25f) == 0 && __builtin_amdgcn_ballot_w64(valid && largest > 0.f) != 0);
+    }
 };
 // 32 rows of a [N, D] matrix in LDS, as three bf16 planes with the swizzle of tile_off
 template <int D>
@@ -584,9 +595,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 ? 1 : 2) void fwd_f32_
     for (; jb <= jb_hi; ++jb) idle_step(jb);
     const float l = xhalf_sum(lh);
     RangeCheck check;
-    check.add(o);
+    check.add(o);  // (before the division by l, which is between 1 and the number of keys unless the next two say otherwise)
     check.add(l);
-    check.add(1.0f / l);  // (no score of the row above the first reference)
+    check.add(1.0f / l);
     if (__builtin_expect(check.failed(t < N), 0)) {
 #pragma unroll 1
         for (int row = qw0; row < min(N, qw0 + 32); ++row) fwd_row<D, kAgainLoads>(Q + ho, Kh, Vh, ch, O + ho, L + (size_t)bh * N, row, w, scale, lane);

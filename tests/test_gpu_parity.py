@@ -778,6 +778,38 @@ def test_f32_matrix_core_range(g, oracle, H, Hkv, N, d, w):
             assert r <= 1e-5, (name, k)
 
 
+@pytest.mark.parametrize("H,Hkv,N,d,w", [(4, 2, 1100, 128, 400), (4, 4, 1300, 64, 300)])
+def test_f32_matrix_core_small_values(g, oracle, H, Hkv, N, d, w):
+    # matrices of values of 2^-118, exactly the scaled ones: every result that is linear in the matrix is the scaled one too,
+    # to the fp32 bar (2^-149, the spacing of the smallest fp32 values, is 2^-31 of 2^-118)
+    note("f32 small values", H, Hkv, N, d, w)
+    wl = gi.custom("f32z", 1, H, N, d, w, "f32", alpha_mu=-2.0, index=21, backward=True, kv_heads=Hkv)
+    Q, K, V, dO = (dev(gi.make_tensor(wl, t), "f32") for t in ("Q", "K", "V", "dO"))
+    c = dev(oracle.gate_prefix(gi.make_tensor(wl, "alpha")).astype(np.float32), "f32")
+    tiny = 2.0 ** -118
+
+    def step(Q, K, V, dO, scale=wl.scale):
+        O, L = g.gfwa_forward_gqa(Q, K, V, c, w, scale)
+        return dict(zip(("O", "dQ", "dK", "dV", "dalpha"), (O, *g.gfwa_backward_gqa(Q, K, V, O, dO, c, L, w, scale))))
+
+    clean = step(Q, K, V, dO)
+    ref = {k: host(v) for k, v in clean.items()}
+    for name, got, scaled in (("dO", step(Q, K, V, dO * tiny), ("dQ", "dK", "dV", "dalpha")),
+                              ("V", step(Q, K, V * tiny, dO), ("O", "dQ", "dK", "dalpha"))):
+        for k in ref:
+            r = rel_l2(host(got[k]) / (tiny if k in scaled else 1.0), ref[k])
+            note("  small", name, k, r)
+            assert r <= 1e-5, (name, k)
+    # a key (query) matrix that small leaves the gate alone to decide; it is the same matrix in dQ (dK)
+    zero = step(Q, torch.zeros_like(K), V, dO)
+    assert float(zero["dQ"].abs().max()) == 0.0
+    like = step(Q, K, V, dO, scale=2.0 ** -60)  # scores of 2^-60: nothing beside the gate
+    for name, got, k in (("K", step(Q, K * tiny, V, dO), "dQ"), ("Q", step(Q * tiny, K, V, dO), "dK")):
+        r = rel_l2(host(got[k]) / (tiny * wl.scale), host(like[k]) / 2.0 ** -60)
+        note("  small", name, k, r)
+        assert r <= 1e-5, (name, k)
+
+
 @pytest.mark.parametrize("B,H,Hkv,N,d,w,groups", [
     # the matrix-core kernels at the edges of their tiles: 128- and 256-query tiles with a last row, a last block and a
     # full one, windows of one key, inside one block, across one, past the sequence; sampled heads
