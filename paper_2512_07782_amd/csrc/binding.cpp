@@ -42,6 +42,14 @@ PyObject* raise_status = nullptr;  // binding._check: turns a negative status in
 
 struct PyError {};  // a Python exception is set
 
+// A scope without the interpreter lock, taken again however the scope is left (looking up the stream may throw).
+struct Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked&) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 [[noreturn]] void fail(PyObject* type, const std::string& text) {
     PyErr_SetString(type, text.c_str());
     throw PyError{};
@@ -167,9 +175,10 @@ gfwa_stream_t stream() { return c10::hip::getCurrentHIPStream().stream(); }
 template <typename F>
 void call(F&& f) {
     int status;
-    Py_BEGIN_ALLOW_THREADS
-    status = f();
-    Py_END_ALLOW_THREADS
+    {
+        Unlocked other_threads_may_run;
+        status = f();
+    }
     if (status != 0) {
         PyObject* r = PyObject_CallFunction(raise_status, "i", status);
         Py_XDECREF(r);
