@@ -82,7 +82,9 @@ const void* input(PyObject* o, at::IntArrayRef shape, at::ScalarType dtype, cons
     return t.const_data_ptr();
 }
 
+// without the interpreter lock, as torch.empty does it: an allocation may wait for the driver
 at::Tensor fresh(at::IntArrayRef shape, at::ScalarType dtype, at::Device device) {
+    Unlocked other_threads_may_run;
     return at::Tensor(at::detail::empty_cuda(shape, dtype, device, std::nullopt));
 }
 

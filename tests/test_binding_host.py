@@ -38,3 +38,22 @@ for _ in range(3):
         print("raised:", e)
 """)
     assert out.count("raised:") == 3, out
+
+
+def test_outputs_are_allocated_without_the_lock(tmp_path):
+    # an allocation may wait for the driver.  The allocation the binding calls is put in front of torch's, asks for the
+    # lock's state and ends the process
+    call_lib = os.path.join(ROOT, "paper_2512_07782_amd", "_gfwa_call.so")
+    names = subprocess.run(["nm", "-D", "--undefined-only", call_lib], stdout=subprocess.PIPE, text=True, check=True).stdout.split()
+    (name,) = [n for n in names if "empty_cuda" in n]
+    (tmp_path / "seen.c").write_text(f"""
+        #include <stdio.h>
+        #include <unistd.h>
+        int PyGILState_Check(void);
+        void allocation(void) __asm__("{name}");
+        void allocation(void) {{ printf("lock held: %d\\n", PyGILState_Check()); fflush(stdout); _exit(0); }}
+    """)
+    lib = str(tmp_path / "seen.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", lib, str(tmp_path / "seen.c")], check=True)
+    first = "import ctypes, sys\nctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)\n"
+    assert "lock held: 0" in child(first + SETUP + "g.gfwa_gate_prefix(alpha)\n", lib)
