@@ -950,9 +950,11 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     char* ds_ws = reinterpret_cast<char*>(ws + 3 * pad) + scan_pad;  // only with `spill`
     const BwdBf16 args = {(const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, c, L, Dv,
                           (bf16_t*)dQ, (bf16_t*)dK, (bf16_t*)dV, dc_col, dc_row, B, H, Hkv, N, w, scale};
-    const FwdSplit dq_split = bwd_dq_shape(B * H, N, D, w, spill);
+    // the dS blocks only travel between the kernels of this file: dK/dV is chosen first, dQ by whether there are blocks then
     const bool dkv_split = bwd_dkv_splits(B * Hkv, H / Hkv, N, D, w);
-    if (dq_split || dkv_split) spill = false;  // the dS blocks only travel between the kernels of this file
+    if (dkv_split) spill = false;
+    const FwdSplit dq_split = bwd_dq_shape(B * H, N, D, w, spill);
+    if (dq_split) spill = false;
     if (dq_split) {
         if (hipError_t e = bwd_dq_split_bf16(dq_split, args, D, s)) return e;
     } else {

@@ -860,6 +860,36 @@ def test_backward_bf16_split(g, oracle, ws_variant, B, H, Hkv, N, d, w, groups):
     check_grads(got, ref, 1e-2, "split")
 
 
+def launched(g, call):
+    """Names of the kernels that `call` launches."""
+    g.gfwa_profile_enable(True)
+    call()
+    torch.cuda.synchronize()
+    g.gfwa_profile_enable(False)
+    return {name for name, (_, count) in g.gfwa_profile_read().items() if count}
+
+
+@pytest.mark.parametrize("B,H,Hkv,N,w", [(1, 32, 8, 700, 1024), (1, 16, 8, 1577, 1416)])
+def test_large_workspace_does_not_change_the_route_where_dkv_is_split(g, B, H, Hkv, N, w):
+    # the split dK/dV pass stores no dS blocks, so the dQ pass is the one that serves the minimum workspace (which
+    # forms D itself, without the row-dot launch), not the one that would have read them
+    note("large workspace", B, H, Hkv, N, w)
+    wl = gi.custom("lws", B, H, N, 128, w, "bf16", alpha_mu=-1.0, index=22, backward=True, kv_heads=Hkv)
+    ins = gi.make_inputs(wl)
+    Q, K, V, dO = (dev(ins[t], "bf16") for t in ("Q", "K", "V", "dO"))
+    c = g.gfwa_gate_prefix(dev(ins["alpha"], "f32"))
+    O, L = g.gfwa_forward_gqa(Q, K, V, c, w, wl.scale)
+    sizes = [f(torch.bfloat16, B, H, N, 128, w) for f in (g.gfwa_backward_workspace_bytes, g.gfwa_backward_fast_workspace_bytes)]
+    assert sizes[1] > sizes[0]  # (with one query head per key/value head the blocks are used)
+    results = []
+    for n in sizes:
+        ws = torch.empty(n, dtype=torch.uint8, device=DEV)
+        assert launched(g, lambda: results.append(g.gfwa_backward_gqa(Q, K, V, O, dO, c, L, w, wl.scale, workspace=ws))) == {
+            "bwd_dq", "bwd_dkv", "gate_grad_scan"}
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+
+
 def test_backward_d64_two_workgroups_per_cu_repeats_bit_exactly(g):
     # rows leave through inline-assembly stores; with two workgroups of the dK/dV pass on a CU a missing wait state
     # between a store and the next write of its data registers showed as a few wrong elements of dV
