@@ -123,6 +123,8 @@ size_t gfwa_backward_workspace_bytes(gfwa_dtype_t dt, int B, int H, int N, int d
  * gfwa_backward_workspace_bytes where there is no such variant: fp32, d = 64).  The variant keeps the dS
  * blocks of App. E.2 the dK/dV pass forms (bf16, about 2 (w + 48) bytes per token and head) for the dQ pass
  * instead of forming S and dP twice; same outputs to the rounding of dS, which both passes apply anyway.
+ * The size follows from the arguments alone.  Problems with few or uneven tiles run kernels that keep no
+ * blocks, whatever the workspace; the bytes beyond the minimum then go unused.
  */
 size_t gfwa_backward_fast_workspace_bytes(gfwa_dtype_t dt, int B, int H, int N, int d, int w);
 
