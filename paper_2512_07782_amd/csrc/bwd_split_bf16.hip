@@ -87,7 +87,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void bwd_dq_sp
             auto requests = [&](int i0, int i1) __attribute__((always_inline)) {  // of the loads of a later step
                 if (RING > 1)
 #pragma unroll
-                    for (int i = i0; i < i1; ++i) band.issue_piece(s_next, s + RING - 1, i);
+                    for (int i = i0; i < i1; ++i) band.issue_piece(s_next, s + 1, i);
             };
             constexpr int P = 2 * Band::kLoads;
 #pragma unroll
@@ -359,7 +359,7 @@ hipError_t bwd_dq_split_bf16(FwdSplit shape, const BwdBf16& a, int d, hipStream_
         if (shape == kFwdSplitMid) return launch_dq_split<128, 4, 2, 1, 2>(a, s);
         return launch_dq_split<128, 4, 1, 1, 1>(a, s);
     }
-    if (shape == kFwdSplitMid) return launch_dq_split<64, 4, 2, 1, 3>(a, s);
+    if (shape == kFwdSplitMid) return launch_dq_split<64, 4, 2, 1, 2>(a, s);
     return launch_dq_split<64, 4, 1, 1, 2>(a, s);
 }
 

@@ -94,7 +94,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_split
                     constexpr int P = 2 * Band::kLoads;
 #pragma unroll
                     for (int i = P * (KC * b + kc) / (KC * KB); i < P * (KC * b + kc + 1) / (KC * KB); ++i)
-                        band.issue_piece(s_next, s + RING - 1, i);
+                        band.issue_piece(s_next, s + 1, i);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -191,7 +191,7 @@ hipError_t forward_split_bf16(FwdSplit shape, const void* Q, const void* K, cons
         return launch_split<128, 4, 1, 1, 1>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
     }
     if (shape == kFwdSplitWide) return launch_split<64, 8, 4, 2, 2>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
-    if (shape == kFwdSplitMid) return launch_split<64, 4, 2, 1, 3>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
+    if (shape == kFwdSplitMid) return launch_split<64, 4, 2, 1, 2>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
     return launch_split<64, 4, 1, 1, 2>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
 }
 

@@ -64,7 +64,7 @@ struct SplitBandSmem {
 
 template <int D, int NW, int QW, int KB, int RING>
 struct SplitBand {
-    static_assert(RING > 1 || QW == 1, "a slot that other waves read is refilled behind a barrier");
+    static_assert(RING == 2 || (RING == 1 && QW == 1), "a slot that other waves read is refilled behind a barrier");
     static constexpr int KW = NW / QW, kKeys = 32 * KB, KC = D / 16, DB = D / 32;
     static constexpr int kLoads = kKeys / PieceLoader<D>::kRows / QW;  // per wave and matrix
     using Smem = SplitBandSmem<D, NW, QW, KB, RING>;
@@ -105,9 +105,7 @@ struct SplitBand {
             s_end = n_last >= kg ? min(mine, (n_last - kg) / KW + 1) : 0;
         }
         c_next = mine > 0 ? gate_of(0) : 0.f;
-#pragma unroll
-        for (int s = 0; s < (RING > 1 ? RING - 1 : 1); ++s)
-            if (s < mine) issue(s);
+        if (mine > 0) issue(0);
         cbase = ch[q0];
     }
     __device__ __forceinline__ int first_key(int s) const { return (kt_hi - (s * KW + kg)) * kKeys; }
@@ -124,22 +122,19 @@ struct SplitBand {
     // start of a step: the group's tile of step s has landed, the readers of the slot that is filled next are done
     __device__ __forceinline__ void open_step(int s) {
         if (s < mine) sm.g[wv][s & 1][KB == 1 ? lane & 31 : lane] = (c_next - cbase) * inv_scale;
-        if (RING > 2 && s + 2 < mine) {  // the loads of later steps stay in flight
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 2) * 2 * kLoads) : "memory");
-        } else {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        }
+        // (The next step's gate value is a load that the compiler waits for by itself, with vmcnt(0): a tile requested two
+        // steps ahead, into a third slot, would be waited for as well.)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (QW > 1) wg_barrier();
         if (s + 1 < mine) c_next = gate_of(s + 1);
     }
     // a step with no block of this wave's band: only its share of the loads
     __device__ __forceinline__ void idle_step(int s) {
         open_step(s);
-        const int s_next = s + (RING > 1 ? RING - 1 : 1);
-        if (s_next < mine) issue(s_next);
+        if (s + 1 < mine) issue(s + 1);
     }
     // the step whose tile is requested during step s; past the end the last one again, into a slot that nothing reads any more
-    __device__ __forceinline__ int requested(int s) const { return min(s + RING - 1, mine - 1); }
+    __device__ __forceinline__ int requested(int s) const { return min(s + 1, mine - 1); }
     // RING == 1: the slot's reads by this wave (its only reader) are done, refill it
     __device__ __forceinline__ void close_step(int s) const {
         if (RING == 1 && s + 1 < mine) {
