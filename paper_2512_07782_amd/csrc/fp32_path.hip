@@ -16,7 +16,7 @@ namespace gfwa {
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 // ==========================================================================================
-// One-wave-per-row kernels: a wave owns one query (key) and takes the other side's rows 16 load instructions at a time,
+// One-wave-per-row kernels: a wave owns one query (key) and takes the other side's rows 4 or 16 load instructions at a time,
 // D / 4 lanes x 16 bytes per row.  Every lane forms its part of the dot products on the four columns it holds, a sum over the
 // row's lanes by lane moves gives all of them the score, and the same registers then feed the weighted sum of those
 // columns: no transposition, nothing through LDS but per-row values.  Latency bounds them, so all loads of a step go out before
@@ -25,7 +25,12 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 // 256 rows, w = 64, d = 64: 11.1 us, now 8.9.)
 // ==========================================================================================
 constexpr int kF32Waves = 4;
-constexpr int kRowLoads = 16;  // load instructions per matrix and step
+// Load instructions per matrix and step.  Four keep a wave at 63 to 84 registers, so that up to eight share a SIMD and hide
+// each other's latency, and a short window is not rounded up to a long step.  A forward of so few rows that a wave has the
+// SIMD to itself is the one place where more loads in flight win (one head, d = 64, 512 causal rows: 16.4 us with 16 loads,
+// 18.6 with 4; 8192 rows, w = 16, d = 128: 19.1 and 11.0; 65536 rows of 4096 sequences, d = 64: 118 and 34, backward 290
+// and 82).
+constexpr int kRowLoads = 4, kRowLoadsAlone = 16;
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_moved(float x) {
@@ -122,7 +127,7 @@ __device__ __forceinline__ void fwd_row(const float* Qh, const float* Kh, const 
     if (r == 0) *reinterpret_cast<f32x4*>(Oh + (size_t)t * D + col) = f32x4{o[0] / l, o[1] / l, o[2] / l, o[3] / l};
     if (lane == 0) Lh[t] = m + logf(l);
 }
-template <int D>
+template <int D, int LOADS>
 __global__ __launch_bounds__(64 * kF32Waves) void fwd_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ c, float* __restrict__ O, float* __restrict__ L, int N, int w,
@@ -133,7 +138,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void fwd_f32_kernel(
     const int t = (blockIdx.x % rows_per_head) * kF32Waves + wv;
     if (t >= N) return;  // whole wave leaves; no workgroup barriers are used below
     const size_t ho = (size_t)bh * N * D, kvo = (size_t)kv_head_of(bh, H, G) * N * D, rows = (size_t)bh * N;
-    fwd_row<D, kRowLoads>(Q + ho, K + kvo, V + kvo, c + rows, O + ho, L + rows, t, w, scale, lane);
+    fwd_row<D, LOADS>(Q + ho, K + kvo, V + kvo, c + rows, O + ho, L + rows, t, w, scale, lane);
 }
 
 // ---- dQ_t and the row sum of dS.  Where Oh is given D_t = <O_t, dO_t> is formed and stored, else it is read.
@@ -319,7 +324,6 @@ __device__ __forceinline__ void split_acc(const f32x16& s, int c2, bf16x8 (&f)[3
 // large that is nothing, but a whole matrix may be that small (an unscaled gradient, say).  Then all results are, since
 // each of O, dQ, dK, dV is a sum over the rows of one matrix with weights that another has made: rows that are not zero but
 // below 2^-80 throughout a wave's 32 are formed again as well.
-constexpr int kAgainLoads = 4;  // (few registers: that code must not cost the kernels that contain it any)
 struct RangeCheck {
     bool finite = true;
     float largest = 0.f;
@@ -447,7 +451,7 @@ __device__ __forceinline__ void tile_axpy(unsigned at, const f32x16& x, bf16x8 (
 template <int D, int T>
 struct F32TileMover {
     static constexpr int kPieces = 32 * (D / 4) / T, kStep = T / (D / 4);
-    static_assert(kStep % 16 == 0 || kStep == 8, "the swizzle has period 16, eight rows further on it differs by chunk bit 1");
+    static_assert(kStep % 16 == 0 || kStep == 8, "the swizzle has period 16, eight rows further on it differs by one chunk bit (as in col_frag)");
     int row, col, at;  // first row, its column in bytes, LDS address inside a plane
     __device__ __forceinline__ void init(int tid) {
         row = tid / (D / 4);
@@ -464,7 +468,7 @@ struct F32TileMover {
     __device__ __forceinline__ void stash(const f32x4 (&r)[kPieces], SplitTile<D>& tile, int part, int n) const {
 #pragma unroll
         for (int i = part * kPieces / n; i < (part + 1) * kPieces / n; ++i) {
-            char* to = tile.p[0] + (kStep == 8 && (i & 1) ? at ^ 32 : at) + i * kStep * (D * 2);
+            char* to = tile.p[0] + (kStep == 8 && (i & 1) ? at ^ (D == 128 ? 32 : 16) : at) + i * kStep * (D * 2);
             const Split2 a = split2(r[i][0], r[i][1]), b = split2(r[i][2], r[i][3]);
 #pragma unroll
             for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x2*>(to + k * SplitTile<D>::kPlane) = u32x2{a.p[k], b.p[k]};
@@ -479,19 +483,21 @@ struct F32TileMover {
 // waves two share a SIMD, and waves 0 .. 3 have the higher issue priority: they take the matrix pipe first and do their
 // softmax while the others form S, and the others do theirs beside the first ones' PV products.  (Two workgroups of four
 // waves per CU instead, whose waves all come to the softmax at the same time and split every tile twice: 452 us.)
-template <int D>
+// S = 1, for short bands: one buffer, refilled between two barriers, and the LDS it saves holds further workgroups that run
+// meanwhile.
+template <int D, int S>
 struct F32FwdSmem {
-    SplitTile<D> k[2], v[2];
-    alignas(16) float c[2][32];
+    SplitTile<D> k[S], v[S];
+    alignas(16) float c[S][32];
 };
-template <int D, int NW>
-__global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 ? 1 : 2) void fwd_f32_mfma_kernel(
+template <int D, int NW, int S>
+__global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) void fwd_f32_mfma_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ c, float* __restrict__ O, float* __restrict__ L, int N, int w, float scale,
     int num_qtiles, int total_tiles, int H, int G) {
     constexpr int KC = D / 16, DB = D / 32, BQ = 32 * NW;
     extern __shared__ __align__(256) char smem_raw[];
-    auto& sm = *reinterpret_cast<F32FwdSmem<D>*>(smem_raw);
+    auto& sm = *reinterpret_cast<F32FwdSmem<D, S>*>(smem_raw);
     const int tile = xcd_remap(blockIdx.x, total_tiles);
     const int bh = tile / num_qtiles, q0 = (tile % num_qtiles) * BQ;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lq = lane & 31;
@@ -532,15 +538,19 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 ? 1 : 2) void fwd_f32_
     stash_share(0, 0, 1);
     if (tid < 32) sm.c[0][tid] = creg;
     wg_barrier();
-    auto end_step = [&](int buf) __attribute__((always_inline)) {
-        if (tid < 32) sm.c[buf ^ 1][tid] = creg;
+    auto end_step = [&](int jb) __attribute__((always_inline)) {
+        if (S == 1) {
+            if (jb == jb_hi) return;
+            wg_barrier();  // the tile is read by all
+            stash_share(0, 0, 1);
+        }
+        if (tid < 32) sm.c[S == 2 ? (jb - jb_lo + 1) & 1 : 0][tid] = creg;
         wg_barrier();
     };
     auto idle_step = [&](int jb) __attribute__((always_inline)) {  // no block of this wave's band: only its share of the tile
-        const int buf = (jb - jb_lo) & 1;
         fetch(min(jb + 1, jb_hi));
-        stash_share(buf ^ 1, 0, 1);
-        end_step(buf);
+        if (S == 2) stash_share((jb - jb_lo + 1) & 1, 0, 1);
+        end_step(jb);
     };
     // (three loops: with a branch around the computing step inside one loop the compiler copies the accumulators)
     const int act_lo = qw0 < N ? max(0, qw0 - w + 1) / 32 : jb_hi + 1, act_hi = min(qw0 / 32, jb_hi);
@@ -550,7 +560,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 ? 1 : 2) void fwd_f32_
         // (the addresses derived from these are recomputed in every block instead of living in registers across the loop)
         GFWA_PIN(r_off);
         GFWA_PIN(t_off);
-        const int kb0 = 32 * jb, buf = (jb - jb_lo) & 1;
+        const int kb0 = 32 * jb, buf = S == 2 ? (jb - jb_lo) & 1 : 0;
         const unsigned kt = (unsigned)(uintptr_t)sm.k[buf].p[0] + r_off, vt = (unsigned)(uintptr_t)sm.v[buf].p[0] + t_off;
         f32x16 g;
         bf16x8 pf[3];
@@ -589,8 +599,10 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 ? 1 : 2) void fwd_f32_
         }
         const ColFrag f = first_col<D, 0>(vt);
         split_acc(s, 0, pf);
-        tile_axpy<D, 0, 2>(vt, s, pf, f, o, [&](int i) __attribute__((always_inline)) { stash_share(buf ^ 1, i, 2 * DB); });
-        end_step(buf);
+        tile_axpy<D, 0, 2>(vt, s, pf, f, o, [&](int i) __attribute__((always_inline)) {
+            if (S == 2) stash_share(buf ^ 1, i, 2 * DB);
+        });
+        end_step(jb);
     }
     for (; jb <= jb_hi; ++jb) idle_step(jb);
     const float l = xhalf_sum(lh);
@@ -600,7 +612,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 ? 1 : 2) void fwd_f32_
     check.add(1.0f / l);
     if (__builtin_expect(check.failed(t < N), 0)) {
 #pragma unroll 1
-        for (int row = qw0; row < min(N, qw0 + 32); ++row) fwd_row<D, kAgainLoads>(Q + ho, Kh, Vh, ch, O + ho, L + (size_t)bh * N, row, w, scale, lane);
+        for (int row = qw0; row < min(N, qw0 + 32); ++row) fwd_row<D, kRowLoads>(Q + ho, Kh, Vh, ch, O + ho, L + (size_t)bh * N, row, w, scale, lane);
     } else if (t < N) {
         float* orow = O + ho + (size_t)t * D;
 #pragma unroll
@@ -616,44 +628,43 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 ? 1 : 2) void fwd_f32_
     }
 }
 
-// ---- backward.  The resident rows take 96 registers per matrix at d = 128, so two waves (of one SIMD: waves wv and
-// wv + 4 of eight) share 32 queries or keys.  Wave 0 of a pair holds the rows of the matrix that forms S and turns S into P,
+// ---- backward.  The resident rows take 96 registers per matrix at d = 128, so two waves (of eight: wv and
+// wv + 4, of one SIMD) share 32 queries or keys.  Wave 0 of a pair holds the rows of the matrix that forms S and turns S into P,
 // wave 1 those that form dP; what they need of each other travels through LDS.  The products with dS are one block behind
 // (the tile they need, K or Q, is kept in a ring of three), so that a step has one barrier and neither wave waits for
 // the other inside it: one's exponentials and splits run beside the other's MFMAs.  (In step, with a second barrier
-// between the first and the second products: dK/dV 606 us, dQ 500 us.)
-constexpr int kF32BwdThreads = 512;
-template <int D>
+// between the first and the second products: dK/dV 606 us, dQ 500 us.)  NP: pairs of a workgroup, four, or two for short bands.
+template <int D, int NP>
 struct F32BwdSmem {
     SplitTile<D> a[3], b[2];           // dK/dV: Q, dO; dQ: K, V
-    f32x4 x[2][4][4][64];              // per pair, one block behind: P (dK/dV); half of P and half of dP - D (dQ)
+    f32x4 x[2][NP][4][64];              // per pair, one block behind: P (dK/dV); half of P and half of dP - D (dQ)
     alignas(16) float v[3][2][32];     // up to three values per row of the tile
 };
 __device__ __forceinline__ int next3(int i) { return i == 2 ? 0 : i + 1; }
 
 // dQ and the row sums of dS (Alg. 3, query loop): the forward's layout.  S^T = K Q^T (wave 0 of a pair) and
 // dP^T = V dO^T (wave 1), then both take half of the block's keys: dS^T = P^T (dP^T - D), dQ^T += K^T dS^T.
-template <int D>
-__global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dq_f32_mfma_kernel(
+template <int D, int NP>
+__global__ __launch_bounds__(128 * NP, NP == 4 ? 1 : 2) void bwd_dq_f32_mfma_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
     const float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dc_row, int N, int w, float scale,
     int num_qtiles, int total_tiles, int H, int G) {
     constexpr int KC = D / 16, DB = D / 32;
     extern __shared__ __align__(256) char smem_raw[];
-    auto& sm = *reinterpret_cast<F32BwdSmem<D>*>(smem_raw);
+    auto& sm = *reinterpret_cast<F32BwdSmem<D, NP>*>(smem_raw);
     const int tile = xcd_remap(blockIdx.x, total_tiles);
-    const int bh = tile / num_qtiles, q0 = (tile % num_qtiles) * 128;
+    const int bh = tile / num_qtiles, q0 = (tile % num_qtiles) * 32 * NP;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lq = lane & 31;
-    const int qg = wv & 3;
+    const int qg = wv % NP;
     auto run = [&](auto role_c) __attribute__((always_inline)) {
         constexpr int role = decltype(role_c)::value;
         const int qw0 = q0 + 32 * qg, t = qw0 + lq, tc = min(t, N - 1);
         const size_t ho = (size_t)bh * N * D, kvo = (size_t)kv_head_of(bh, H, G) * N * D;
         const float *Kh = K + kvo, *Vh = V + kvo, *ch = c + (size_t)bh * N;
 
-        const int jb_lo = max(0, q0 - w + 1) / 32, jb_hi = (min(N, q0 + 128) - 1) / 32;
-        using Mover = F32TileMover<D, kF32BwdThreads>;
+        const int jb_lo = max(0, q0 - w + 1) / 32, jb_hi = (min(N, q0 + 32 * NP) - 1) / 32;
+        using Mover = F32TileMover<D, 128 * NP>;
         Mover mv;
         mv.init(tid);
         f32x4 kreg[Mover::kPieces], vreg[Mover::kPieces];
@@ -794,7 +805,7 @@ __global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dq_f32_mfma_kernel(
                 const size_t rows = (size_t)bh * N;
 #pragma unroll 1
                 for (int row = qw0; row < min(N, qw0 + 32); ++row)
-                    dq_row<D, kAgainLoads>(Q + ho, Kh, Vh, nullptr, dO + ho, ch, L + rows, const_cast<float*>(Dv + rows), dQ + ho, dc_row + rows, row, w,
+                    dq_row<D, kRowLoads>(Q + ho, Kh, Vh, nullptr, dO + ho, ch, L + rows, const_cast<float*>(Dv + rows), dQ + ho, dc_row + rows, row, w,
                               scale, lane);
             } else if (t < N) {
                 float* out = dQ + ho + (size_t)t * D;
@@ -808,26 +819,26 @@ __global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dq_f32_mfma_kernel(
             }
         }
     };
-    if (wv < 4) run(std::integral_constant<int, 0>{});
+    if (wv < NP) run(std::integral_constant<int, 0>{});
     else run(std::integral_constant<int, 1>{});
 }
 
 // dK, dV (summed over the G query heads of a group) and, per query head, the column sums of dS (Alg. 3, key loop): a
-// workgroup owns 128 keys, a pair of waves 32 of them, a lane one key.  S = Q K^T (wave 0) and dP = dO V^T (wave 1) with
+// workgroup owns 32 NP keys, a pair of waves 32 of them, a lane one key.  S = Q K^T (wave 0) and dP = dO V^T (wave 1) with
 // 32-query tiles of Q and dO from LDS, then dV^T += dO^T P (wave 0) and, a block later, dK^T += Q^T dS (wave 1).
-template <int D>
-__global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dkv_f32_mfma_kernel(
+template <int D, int NP>
+__global__ __launch_bounds__(128 * NP, NP == 4 ? 1 : 2) void bwd_dkv_f32_mfma_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
     const float* __restrict__ Dv, float* __restrict__ dK, float* __restrict__ dV, float* __restrict__ dc_col,
     int N, int w, float scale, int num_ktiles, int total_tiles, int H, int G) {
     constexpr int KC = D / 16, DB = D / 32;
     extern __shared__ __align__(256) char smem_raw[];
-    auto& sm = *reinterpret_cast<F32BwdSmem<D>*>(smem_raw);
+    auto& sm = *reinterpret_cast<F32BwdSmem<D, NP>*>(smem_raw);
     const int tile = xcd_remap(blockIdx.x, total_tiles);
-    const int bkv = tile / num_ktiles, k0 = (tile % num_ktiles) * 128;  // flat key/value head, first key
+    const int bkv = tile / num_ktiles, k0 = (tile % num_ktiles) * 32 * NP;  // flat key/value head, first key
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lk = lane & 31;
-    const int kg = wv & 3;
+    const int kg = wv % NP;
     auto run = [&](auto role_c) __attribute__((always_inline)) {
         constexpr int role = decltype(role_c)::value;
         const int kw0 = k0 + 32 * kg, i = kw0 + lk, ic = min(i, N - 1);
@@ -835,11 +846,11 @@ __global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dkv_f32_mfma_kernel(
         const int bh0 = (bkv / Hkv) * H + (bkv % Hkv) * G;  // first query head of the group
         const size_t kvo = (size_t)bkv * N * D;
 
-        // query blocks that see a key of the tile: rows k0 .. k0 + 127 + w - 1, of every query head of the group in turn
+        // query blocks that see a key of the tile: rows k0 .. k0 + 32 NP - 1 + w - 1, of every query head of the group in turn
         const int qb_lo = k0 / 32;
-        const int qb_hi = (int)(min((long)N - 1, (long)k0 + 127 + w - 1) / 32);
+        const int qb_hi = (int)(min((long)N - 1, (long)k0 + 32 * NP - 1 + w - 1) / 32);
         const int nblk = qb_hi - qb_lo + 1;
-        using Mover = F32TileMover<D, kF32BwdThreads>;
+        using Mover = F32TileMover<D, 128 * NP>;
         Mover mv;
         mv.init(tid);
         f32x4 qreg[Mover::kPieces], greg[Mover::kPieces];
@@ -1005,7 +1016,7 @@ __global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dkv_f32_mfma_kernel(
             if (role == 1)
 #pragma unroll 1
                 for (int key = kw0; key < min(N, kw0 + 32); ++key)
-                    dkv_row<D, kAgainLoads>(Q, K + kvo, V + kvo, dO, c, L, Dv, dK + kvo, dV + kvo, dc_col, rows_s, bh0, G, key, N, w, scale, lane);
+                    dkv_row<D, kRowLoads>(Q, K + kvo, V + kvo, dO, c, L, Dv, dK + kvo, dV + kvo, dc_col, rows_s, bh0, G, key, N, w, scale, lane);
         } else if (i < N) {
             float* out = (role == 0 ? dV : dK) + kvo + (size_t)i * D;
 #pragma unroll
@@ -1016,7 +1027,7 @@ __global__ __launch_bounds__(kF32BwdThreads, 1) void bwd_dkv_f32_mfma_kernel(
                         f32x4{acc[db][4 * i4], acc[db][4 * i4 + 1], acc[db][4 * i4 + 2], acc[db][4 * i4 + 3]};
         }
     };
-    if (wv < 4) run(std::integral_constant<int, 0>{});
+    if (wv < NP) run(std::integral_constant<int, 0>{});
     else run(std::integral_constant<int, 1>{});
 }
 
@@ -1035,51 +1046,133 @@ __global__ __launch_bounds__(256) void rowdot_f32_kernel(const float* __restrict
     if (row < rows && lane % Step::kLanes == 0) Dv[row] = d;
 }
 
-// Which kernels serve a problem, by estimates of the two in us, fitted to 16 shapes (1 to 256 tiles, w 64 .. 700).  The
-// matrix-core kernels walk a tile's band one 32-row block after another.  A row of the one-wave-per-row kernels takes a
-// fixed time per step of 64 (d = 64) or 32 keys while they are few, and they sustain 2.3e6 products of the forward per us
-// once they fill the chip.  In the backward both walk the G query heads of a key one after another.
-// (One-wave-per-row / matrix cores: 256 rows, w = 64, d = 64: forward 2 / 13 us, backward 7 / 28 us; 512 causal rows, 4 heads,
-// d = 128: 49 / 53, 134 / 119; 1024 rows, w = 128, 8 heads, d = 128: 52 / 36, 140 / 73; events included, about 5 us each.)
-static bool f32_use_mfma(bool backward, int B, int H, int Hkv, int N, int d, int w) {
-    const double wc = w < N ? w : N, wide = d / 64.0, G = H / Hkv;
-    const double products = (double)B * H * (N * wc - wc * (wc - 1.0) / 2.0) * d;
-    const double steps = ceil(wc / 64.0 * wide), blocks = fmin((double)N, wc + 127.0) / 32.0 * wide;
-    const double row = backward ? 10.0 + fmax(products / 0.95e6, (2.5 + 3.0 * G) * steps) : 4.0 + fmax(products / 2.3e6, 2.5 * steps);
-    const double mfma = backward ? 15.0 + (1.7 + 2.0 * G) * blocks : 7.0 + 1.65 * blocks;
-    return mfma < row;
+// Bands that workgroups of 64 queries (keys) serve better than larger ones: d = 64, at most 128 long.  A workgroup walks
+// band + rows - 1 keys, of which a wave needs band + 31, and the LDS of the small one lets four (backward: two) share a CU.
+// (64- / 128- / 256-query workgroups, B1 H64 N4096 w8: forward 64 / 73 / 103 us, backward with 64 / 128: 231 / 294; B4 H16 N2000
+// w128: 56 / 57 / 65, 167 / 191; w256: 77 / 78 / 83, 233 / 251; B2 H16 N2000 w512: 63 / 60 / 58, 194 / 187.)
+static bool f32_short_band(int N, int d, int w) { return d == 64 && (w < N ? w : N) <= 128; }
+
+// How the matrix-core forward is cut up: 256 queries per workgroup (two waves per SIMD) once that gives every CU one, 128
+// before and where a sequence ends within them.  More such sequences than CUs give up the second tile buffer at d = 128, for a
+// second workgroup on the CU (512 sequences of 32: 11.8 us, 17.0 with 256-query workgroups; 2048 of 64: 81, 98; 256 of 64: 14.5,
+// 13.1).  Between 65 and 128 long bands of d = 64 are one workgroup's (512 sequences of 128: 20.2 us with 64 queries, 19.7).
+enum F32Fwd { kF32Fwd64, kF32Fwd128, kF32Fwd128Double, kF32Fwd256Double };  // queries per workgroup, tile buffers
+static F32Fwd f32_fwd_shape(long BH, int N, int d, int w) {
+    if (f32_short_band(N, d, w) && (w <= 64 || N <= 64 || N > 128)) return kF32Fwd64;
+    if (N <= 128) return d == 128 && BH > device_cu_count() ? kF32Fwd128 : kF32Fwd128Double;
+    return BH * ((N + 255) / 256) >= device_cu_count() ? kF32Fwd256Double : kF32Fwd128Double;
 }
 
-template <int D, int NW>
+// Which kernels serve a problem, by estimates of the two in us, fitted to 166 shapes (1 to 4096 sequences of 1 to 5001, w 1 .. 2000;
+// where the choice costs more than 8 % it costs at most 7 us forward, 10 backward).  A row of the one-wave-per-row kernels takes 0.25 ns and 0.3
+// ns per step of 16 (d = 64) or 8 keys, and the longest row's steps follow one another; the backward takes about twice that.
+// The matrix-core kernels walk a tile's band one 32-row block after another, in rounds of as many workgroups as the chip holds.
+// In the backward the key side of both walks the G query heads one after another.  (One-wave-per-row / matrix cores: 256 rows,
+// w = 64, d = 64: forward 4.5 / 12 us, backward 14 / 28; 512 causal rows, 4 heads, d = 128: 48 / 51, 130 / 122; 1100 rows, w = 400, 4 heads,
+// d = 128: 68 / 57, 177 / 129; 4096 sequences of 16, d = 64: 34 / 25, 82 / 105; 2048 of 8, d = 128: 10 / 33, 35 / 140; 2048 of 64, d = 128: 299 / 81,
+// 769 / 290.)
+static bool f32_use_mfma(bool backward, int B, int H, int Hkv, int N, int d, int w) {
+    const double cus = device_cu_count(), BH = (double)B * H, wc = w < N ? w : N, G = H / Hkv, wide = d / 64.0;
+    const double step = kRowLoads * 256.0 / d, longest = ceil(wc / step), rows = BH * N * 1e-3;
+    const double steps = (wc - wc * (wc - 1.0) / (2.0 * N)) / step;  // of a row, on average, before they are rounded up
+    if (!backward) {
+        const F32Fwd shape = f32_fwd_shape((long)B * H, N, d, w);
+        const int q = shape == kF32Fwd64 ? 64 : shape == kF32Fwd256Double ? 256 : 128;
+        const double blocks = ceil(fmin((double)N, wc + q - 1.0) / 32.0);
+        double per_cu = BH * ((N + q - 1) / q) / cus;
+        if (q == 256) per_cu = ceil(per_cu);  // one workgroup on a CU at a time
+        return 2.5 + 2.0 * wide + blocks * fmax(d == 128 ? 2.75 : 1.5, (d == 128 ? 4.5 : q == 64 ? 1.3 : q == 128 ? 1.8 : 2.5) * per_cu) <
+               3.0 + rows * (0.25 + 0.3 * fmax(1.0, steps + 0.5)) + 0.36 * longest;
+    }
+    const int k = f32_short_band(N, d, w) ? 64 : 128;
+    const double tiles = (N + k - 1) / k, slots = cus * (k == 64 ? 2 : 1), blocks = ceil(fmin((double)N, wc + k - 1.0) / 32.0);
+    const double fixed = 4.0 * wide, block = d == 128 ? 1.6 : 1.0;
+    return 7.0 + ceil(BH * tiles / slots) * (fixed + 1.7 * block * blocks) + ceil(BH / G * tiles / slots) * (fixed + 2.0 * G * block * blocks) <
+           8.0 + rows * (0.5 + 0.66 * fmin(longest, steps + 1.0)) + (0.35 + 0.5 * G) * (d == 128 ? 1.3 : 1.0) * longest;
+}
+
+template <int D, int NW, int S>
 static hipError_t launch_fwd_f32_mfma(const float* Q, const float* K, const float* V, const float* c, float* O, float* L, int B,
                                       int H, int Hkv, int N, int w, float scale, hipStream_t s) {
     static DeviceOnce lds_allowed;
-    constexpr size_t lds = sizeof(F32FwdSmem<D>);
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&fwd_f32_mfma_kernel<D, NW>), lds, lds_allowed)) return e;
+    constexpr size_t lds = sizeof(F32FwdSmem<D, S>);
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&fwd_f32_mfma_kernel<D, NW, S>), lds, lds_allowed)) return e;
     const int nq = (N + 32 * NW - 1) / (32 * NW), total = B * H * nq;
-    hipLaunchKernelGGL((fwd_f32_mfma_kernel<D, NW>), dim3(total), dim3(64 * NW), lds, s, Q, K, V, c, O, L, N, w, scale, nq, total,
+    hipLaunchKernelGGL((fwd_f32_mfma_kernel<D, NW, S>), dim3(total), dim3(64 * NW), lds, s, Q, K, V, c, O, L, N, w, scale, nq, total,
                        H, H / Hkv);
     return hipGetLastError();
+}
+
+template <int D, int LOADS>
+static void launch_fwd_f32_rows(const float* Q, const float* K, const float* V, const float* c, float* O, float* L, int B, int H, int Hkv,
+                                int N, int w, float scale, hipStream_t s) {
+    hipLaunchKernelGGL((fwd_f32_kernel<D, LOADS>), dim3(B * H * ((N + kF32Waves - 1) / kF32Waves)), dim3(64 * kF32Waves), 0, s, Q, K, V, c, O,
+                       L, N, w, scale, H, H / Hkv);
+}
+
+template <int D>
+static hipError_t launch_fwd_f32(const float* Q, const float* K, const float* V, const float* c, float* O, float* L, int B, int H, int Hkv,
+                                 int N, int w, float scale, hipStream_t s) {
+    if (!f32_use_mfma(false, B, H, Hkv, N, D, w)) {
+        if ((long)B * H * N <= 4L * device_cu_count()) launch_fwd_f32_rows<D, kRowLoadsAlone>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
+        else launch_fwd_f32_rows<D, kRowLoads>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
+        return hipGetLastError();
+    }
+    switch (f32_fwd_shape(B * H, N, D, w)) {
+        case kF32Fwd64:
+            if constexpr (D == 64) return launch_fwd_f32_mfma<D, 2, 1>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
+            [[fallthrough]];
+        case kF32Fwd128: return launch_fwd_f32_mfma<D, 4, 1>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
+        case kF32Fwd128Double: return launch_fwd_f32_mfma<D, 4, 2>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
+        default: return launch_fwd_f32_mfma<D, 8, 2>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
+    }
 }
 
 hipError_t forward_f32(const float* Q, const float* K, const float* V, const float* c, float* O, float* L,
                        int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s) {
     ProfScope prof(kKernForward, s);
-    if (f32_use_mfma(false, B, H, Hkv, N, d, w)) {
-        // 256 queries per workgroup (two waves per SIMD) once that gives every CU one
-        const bool wide = B * H * ((N + 255) / 256) >= device_cu_count();
-        if (d == 128)
-            return wide ? launch_fwd_f32_mfma<128, 8>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s)
-                        : launch_fwd_f32_mfma<128, 4>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
-        return wide ? launch_fwd_f32_mfma<64, 8>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s)
-                    : launch_fwd_f32_mfma<64, 4>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
-    } else {
-        const int blocks = B * H * ((N + kF32Waves - 1) / kF32Waves);
-        if (d == 128)
-            hipLaunchKernelGGL((fwd_f32_kernel<128>), dim3(blocks), dim3(64 * kF32Waves), 0, s, Q, K, V, c, O, L, N, w, scale, H, H / Hkv);
-        else
-            hipLaunchKernelGGL((fwd_f32_kernel<64>), dim3(blocks), dim3(64 * kF32Waves), 0, s, Q, K, V, c, O, L, N, w, scale, H, H / Hkv);
+    return d == 128 ? launch_fwd_f32<128>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s)
+                    : launch_fwd_f32<64>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
+}
+
+template <int D>
+static hipError_t launch_bwd_f32_rows(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,
+                                      const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, int B,
+                                      int H, int Hkv, int N, int w, float scale, hipStream_t s) {
+    const int per_head = (N + kF32Waves - 1) / kF32Waves;
+    {   // forms D as well, so it goes first
+        ProfScope prof(kKernDq, s);
+        hipLaunchKernelGGL((bwd_dq_f32_kernel<D>), dim3(B * H * per_head), dim3(64 * kF32Waves), 0, s, Q, K, V, O, dO, c, L, Dv,
+                           dQ, dc_row, N, w, scale, H, H / Hkv);
     }
+    ProfScope prof(kKernDkv, s);
+    hipLaunchKernelGGL((bwd_dkv_f32_kernel<D>), dim3(B * Hkv * per_head), dim3(64 * kF32Waves), 0, s, Q, K, V, dO, c, L, Dv, dK,
+                       dV, dc_col, N, w, scale, H, H / Hkv);
+    return hipGetLastError();
+}
+
+template <int D, int NP>
+static hipError_t launch_bwd_f32_mfma(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,
+                                      const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, int B,
+                                      int H, int Hkv, int N, int w, float scale, hipStream_t s) {
+    static DeviceOnce dkv_lds, dq_lds;
+    constexpr size_t lds = sizeof(F32BwdSmem<D, NP>);
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dkv_f32_mfma_kernel<D, NP>), lds, dkv_lds)) return e;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dq_f32_mfma_kernel<D, NP>), lds, dq_lds)) return e;
+    const long rows = (long)B * H * N;
+    const int nt = (N + 32 * NP - 1) / (32 * NP), dot_rows = 4 * RowStep<D, 1>::kRows;
+    {
+        ProfScope prof(kKernRowDot, s);
+        hipLaunchKernelGGL((rowdot_f32_kernel<D>), dim3((unsigned)((rows + dot_rows - 1) / dot_rows)), dim3(256), 0, s, O, dO, Dv, rows);
+    }
+    {
+        ProfScope prof(kKernDkv, s);
+        hipLaunchKernelGGL((bwd_dkv_f32_mfma_kernel<D, NP>), dim3(B * Hkv * nt), dim3(128 * NP), lds, s, Q, K, V, dO, c, L, Dv, dK,
+                           dV, dc_col, N, w, scale, nt, B * Hkv * nt, H, H / Hkv);
+    }
+    ProfScope prof(kKernDq, s);
+    hipLaunchKernelGGL((bwd_dq_f32_mfma_kernel<D, NP>), dim3(B * H * nt), dim3(128 * NP), lds, s, Q, K, V, dO, c, L, Dv, dQ,
+                       dc_row, N, w, scale, nt, B * H * nt, H, H / Hkv);
     return hipGetLastError();
 }
 
@@ -1087,38 +1180,12 @@ template <int D>
 static hipError_t launch_bwd_f32(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,
                                  const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, int B,
                                  int H, int Hkv, int N, int w, float scale, hipStream_t s) {
-    const int G = H / Hkv;
-    if (!f32_use_mfma(true, B, H, Hkv, N, D, w)) {
-        const int per_head = (N + kF32Waves - 1) / kF32Waves;
-        {   // forms D as well, so it goes first
-            ProfScope prof(kKernDq, s);
-            hipLaunchKernelGGL((bwd_dq_f32_kernel<D>), dim3(B * H * per_head), dim3(64 * kF32Waves), 0, s, Q, K, V, O, dO, c, L, Dv,
-                               dQ, dc_row, N, w, scale, H, G);
-        }
-        ProfScope prof(kKernDkv, s);
-        hipLaunchKernelGGL((bwd_dkv_f32_kernel<D>), dim3(B * Hkv * per_head), dim3(64 * kF32Waves), 0, s, Q, K, V, dO, c, L, Dv, dK,
-                           dV, dc_col, N, w, scale, H, G);
-        return hipGetLastError();
-    }
-    static DeviceOnce dkv_lds, dq_lds;
-    constexpr size_t lds = sizeof(F32BwdSmem<D>);
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dkv_f32_mfma_kernel<D>), lds, dkv_lds)) return e;
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dq_f32_mfma_kernel<D>), lds, dq_lds)) return e;
-    const long rows = (long)B * H * N;
-    const int nt = (N + 127) / 128, dot_rows = 4 * RowStep<D, 1>::kRows;
-    {
-        ProfScope prof(kKernRowDot, s);
-        hipLaunchKernelGGL((rowdot_f32_kernel<D>), dim3((unsigned)((rows + dot_rows - 1) / dot_rows)), dim3(256), 0, s, O, dO, Dv, rows);
-    }
-    {
-        ProfScope prof(kKernDkv, s);
-        hipLaunchKernelGGL((bwd_dkv_f32_mfma_kernel<D>), dim3(B * Hkv * nt), dim3(kF32BwdThreads), lds, s, Q, K, V, dO, c, L, Dv,
-                           dK, dV, dc_col, N, w, scale, nt, B * Hkv * nt, H, G);
-    }
-    ProfScope prof(kKernDq, s);
-    hipLaunchKernelGGL((bwd_dq_f32_mfma_kernel<D>), dim3(B * H * nt), dim3(kF32BwdThreads), lds, s, Q, K, V, dO, c, L, Dv, dQ,
-                       dc_row, N, w, scale, nt, B * H * nt, H, G);
-    return hipGetLastError();
+    auto with = [&](auto launch) { return launch(Q, K, V, O, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, B, H, Hkv, N, w, scale, s); };
+    if (!f32_use_mfma(true, B, H, Hkv, N, D, w))
+        return with(launch_bwd_f32_rows<D>);
+    if constexpr (D == 64)
+        if (f32_short_band(N, D, w)) return with(launch_bwd_f32_mfma<D, 2>);
+    return with(launch_bwd_f32_mfma<D, 4>);
 }
 
 hipError_t backward_f32(const float* Q, const float* K, const float* V, const float* O, const float* dO,

@@ -350,8 +350,8 @@ def test_forward_tiny_f32(g, oracle):
     assert rel_inf(L, L_ref) <= 1e-5
 
 
-# (the first three are served by the one-wave-per-row kernels, the others by the fp32 matrix-core kernels: the library
-# chooses by the size of the problem)
+# (the first three are served by the one-wave-per-row kernels, the next three by the fp32 matrix-core kernels; of windows of one
+# key and just over a block many rows, and long ones, go to the matrix cores too)
 @pytest.mark.parametrize("B,H,N,d,w", [(1, 2, 77, 64, 9), (2, 1, 130, 128, 500), (1, 1, 65, 128, 1),
                                        (2, 3, 1500, 128, 700), (1, 4, 2100, 64, 300), (1, 4, 1237, 128, 5000),
                                        (4, 16, 5001, 64, 1), (1, 8, 2049, 128, 33)])
@@ -672,9 +672,11 @@ def test_gqa_f32(g, oracle, B, H, Hkv, N, d, w):
     check_grads(got, ref, 1e-5, "gqa f32")
 
 
-# the one-wave-per-row kernels at the edges of their steps of 64 (d = 64) and 32 keys: one full step, one key more, several
+# the one-wave-per-row kernels at the edges of their steps: one full step, one key more, several.  A forward of up to 1024 rows takes
+# 64 (d = 64) or 32 keys a step, of more rows 16 or 8, as every backward does
 @pytest.mark.parametrize("B,H,Hkv,N,d,w", [(1, 8, 1, 66, 64, 64), (1, 4, 1, 97, 64, 65), (1, 2, 2, 131, 64, 129),
-                                           (2, 2, 2, 33, 128, 32), (1, 2, 1, 70, 128, 33)])
+                                           (2, 2, 2, 33, 128, 32), (1, 2, 1, 70, 128, 33),
+                                           (2, 8, 8, 130, 64, 16), (1, 12, 4, 97, 64, 17), (1, 9, 3, 131, 128, 8), (2, 5, 5, 129, 128, 9)])
 def test_f32_row_steps(g, oracle, B, H, Hkv, N, d, w):
     note("f32 row steps", B, H, Hkv, N, d, w)
     wl = gi.custom("f32s", B, H, N, d, w, "f32", alpha_mu=-1.0, index=18, backward=True, kv_heads=Hkv)
@@ -684,8 +686,8 @@ def test_f32_row_steps(g, oracle, B, H, Hkv, N, d, w):
     check_grads(got, ref, 1e-5, "f32 row steps")
 
 
-# (the one-wave-per-row kernels: steps of 64 keys at d = 64, of 32 at d = 128, the last ones of a row partly filled)
-@pytest.mark.parametrize("B,H,Hkv,N,d,w", [(1, 2, 1, 77, 64, 30), (1, 2, 2, 50, 128, 33)])
+# (the one-wave-per-row kernels, the last steps of a row partly filled; the last two: more than 1024 rows, the forward's short steps)
+@pytest.mark.parametrize("B,H,Hkv,N,d,w", [(1, 2, 1, 77, 64, 30), (1, 2, 2, 50, 128, 33), (1, 16, 8, 77, 64, 30), (1, 24, 24, 50, 128, 11)])
 def test_f32_rows_with_infinities(g, oracle, B, H, Hkv, N, d, w):
     note("f32 rows with infinities", B, H, Hkv, N, d, w)
     wl = gi.custom("f32i", B, H, N, d, w, "f32", alpha_mu=-1.0, index=19, backward=True, kv_heads=Hkv)
@@ -811,15 +813,22 @@ def test_f32_matrix_core_small_values(g, oracle, H, Hkv, N, d, w):
 
 
 @pytest.mark.parametrize("B,H,Hkv,N,d,w,groups", [
-    # the matrix-core kernels at the edges of their tiles: 128- and 256-query tiles with a last row, a last block and a
+    # the matrix-core kernels at the edges of their tiles: 64-, 128- and 256-query tiles with a last row, a last block and a
     # full one, windows of one key, inside one block, across one, past the sequence; sampled heads
-    (2, 4, 4, 1025, 64, 97, [0, 7]), (1, 6, 2, 1153, 128, 65, [0, 1]), (2, 32, 32, 1057, 128, 31, [0, 63]),
+    (2, 4, 4, 1025, 64, 97, [0, 7]), (1, 6, 2, 1153, 128, 165, [0, 1]), (2, 32, 32, 1057, 128, 31, [0, 63]),
     (4, 16, 16, 1281, 64, 33, [0, 63]), (8, 32, 32, 256, 128, 500, [0, 255]), (2, 32, 16, 1120, 64, 129, [0, 31]),
+    # d = 64, short bands: 64 queries and keys per workgroup
+    (6, 64, 64, 129, 64, 1, [0, 383]), (3, 100, 25, 65, 64, 50, [0, 74]), (4, 80, 80, 33, 64, 31, [0, 319]),
+    (2, 150, 150, 100, 64, 90, [0, 299]),  # (the forward with 128)
+    # d = 128, more sequences that end within 128 than CUs: one tile buffer
+    (5, 60, 60, 97, 128, 33, [0, 299]), (1, 260, 130, 128, 128, 128, [0, 129]),
 ])
 def test_f32_matrix_core_tiles(g, oracle, B, H, Hkv, N, d, w, groups):
     note("f32 tiles", B, H, Hkv, N, d, w)
     wl = gi.custom("f32t", B, H, N, d, w, "f32", alpha_mu=-1.0, index=16, backward=True, kv_heads=Hkv)
-    got, ref = run_gqa(g, oracle, wl, groups=groups)
+    results = []
+    assert "bwd_rowdot" in launched(g, lambda: results.extend(run_gqa(g, oracle, wl, groups=groups)))  # (not the one-wave-per-row kernels)
+    got, ref = results
     assert rel_inf(got["O"], ref["O"]) <= 1e-5
     assert (np.abs(got["L"] - ref["L"]) <= 1e-5 * np.abs(ref["L"]).max() + 1e-5).all()
     check_grads(got, ref, 1e-5, "f32 tiles")
