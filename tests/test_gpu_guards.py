@@ -49,8 +49,17 @@ def dev(x, dtype):
 
 SHAPES = [  # B, H, Hkv, N, d, w: ragged in every tile size the kernels use
     (1, 2, 2, 333, 128, 50), (2, 4, 2, 77, 64, 200), (1, 1, 1, 1, 128, 1), (1, 3, 1, 1027, 128, 1024),
-    (1, 2, 1, 259, 64, 64), (2, 4, 2, 1301, 64, 300),   # (the last and the fourth: large enough for the fp32 matrix-core kernels)
+    (1, 2, 1, 259, 64, 64), (2, 4, 2, 1301, 64, 300),   # (this and the fourth: large enough for the fp32 matrix-core kernels)
+    # short sequences, many of them: the fp32 matrix-core kernels with one tile buffer
+    (5, 60, 60, 97, 128, 33), (2, 150, 75, 65, 64, 50),
+    # bf16: the band split over groups of waves, 64 and 128 queries per workgroup
+    (1, 32, 8, 701, 128, 1024), (1, 8, 8, 5003, 128, 2999),
+    # bf16: the persistent forward and the dQ kernel of whole 128-query tiles
+    (1, 20, 20, 4099, 128, 301), (1, 48, 12, 2049, 128, 333), (1, 25, 25, 4099, 64, 301),
 ]
+# The shapes with a row-dot launch in their backward.  bf16: those that take the whole-tile dQ kernel; with the large workspace
+# one more, and at d = 128 it works from stored dS blocks then.  fp32: those that take the matrix-core kernels.
+ROW_DOT = {("bf16", False): SHAPES[6:8] + SHAPES[10:], ("bf16", True): SHAPES[6:8] + SHAPES[9:], ("f32", False): SHAPES[3:4] + SHAPES[5:]}
 
 
 @pytest.mark.parametrize("fast", [False, True])
@@ -74,9 +83,16 @@ def test_forward_backward_stay_inside_their_buffers(g, B, H, Hkv, N, d, w, dtype
         ws = Guarded((size(tdt, B, H, N, d, w),), torch.uint8)
         g.gfwa_gate_prefix(alpha, c.t)
         g.gfwa_forward_gqa(Q, K, V, c.t, w, wl.scale, O=O.t, L=L.t)
+        g.gfwa_profile_enable(True)
         g.gfwa_backward_gqa(Q, K, V, O.t, dO, c.t, L.t, w, wl.scale, workspace=ws.t, dQ=dQ.t, dK=dK.t, dV=dV.t,
                             dalpha=dal.t)
         torch.cuda.synchronize()
+        g.gfwa_profile_enable(False)
+        row_dot = (B, H, Hkv, N, d, w) in ROW_DOT[dtype, fast]
+        assert (g.gfwa_profile_read()["bwd_rowdot"][1] > 0) == row_dot, "other kernels than the shape is here for"
+        if fast:
+            blocks = ws.t[g.gfwa_backward_workspace_bytes(tdt, B, H, N, d, w):]
+            assert bool((blocks != POISON).any()) == row_dot, "dS blocks"
         for name, gd in (("c", c), ("O", O), ("L", L), ("dQ", dQ), ("dK", dK), ("dV", dV), ("dalpha", dal),
                          ("workspace", ws)):
             assert gd.intact(), f"{name}: bytes outside the buffer were written"

@@ -899,6 +899,24 @@ def test_large_workspace_does_not_change_the_route_where_dkv_is_split(g, B, H, H
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("B,H,Hkv,N,d,w,groups", [
+    # the persistent forward and the backward kernels of whole 128-row tiles, where they have a ragged end: last tiles of 3 rows
+    # to one row, odd windows, windows past the sequence, grouped heads; sampled heads
+    (1, 20, 20, 4099, 128, 301, [0, 19]), (1, 48, 12, 2049, 128, 333, [0, 11]), (2, 100, 100, 513, 128, 1000, [0, 199]),
+    (1, 25, 25, 4099, 64, 301, [0, 24]), (1, 40, 10, 3001, 64, 333, [0, 9]), (1, 250, 250, 641, 64, 5000, [0, 249]),
+    (1, 8, 8, 5003, 128, 2999, [3]),  # (these, the dQ pass from dS blocks, with the large workspace only)
+])
+def test_bf16_whole_tiles_ragged(g, oracle, ws_variant, B, H, Hkv, N, d, w, groups):
+    note("whole tiles", ws_variant, B, H, Hkv, N, d, w)
+    wl = gi.custom("whole", B, H, N, d, w, "bf16", alpha_mu=-1.5, index=23, backward=True, kv_heads=Hkv)
+    results = []
+    names = launched(g, lambda: results.extend(run_gqa(g, oracle, wl, groups=groups)))
+    assert ("bwd_rowdot" in names) == (H > 8 or VARIANT["fast"])  # the launch in front of the whole-tile dQ kernel
+    got, ref = results
+    check_bf16_forward(got["O"], got["L"], ref["O"], ref["L"], tag="whole tiles")
+    check_grads(got, ref, 1e-2, "whole tiles")
+
+
 def test_backward_d64_two_workgroups_per_cu_repeats_bit_exactly(g):
     # rows leave through inline-assembly stores; with two workgroups of the dK/dV pass on a CU a missing wait state
     # between a store and the next write of its data registers showed as a few wrong elements of dV
