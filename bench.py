@@ -22,8 +22,8 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0    # MI355X dense bf16 MFMA, published
 PEAK_F32_TFLOPS = 157.3      # MI355X fp32 MFMA (and fp32 vector), published
-# what the fp32 kernels can reach: they form an fp32 product from six bf16 ones, so the roofline fraction of a kernel
-# against the published fp32 peak may exceed one
+# what the fp32 kernels can reach: they form an fp32 product from six bf16 ones, so `frac` of a kernel, which is of the
+# published fp32 peak, may exceed one; `frac_split_bf16_peak` beside it is of this
 PEAK_F32_SPLIT_TFLOPS = PEAK_BF16_TFLOPS / 6
 PEAK_HBM_GBS = 8000.0
 
@@ -448,6 +448,8 @@ def main() -> int:
             ach, peak, unit = work / (avg_ms * 1e-3) / 1e9, PEAK_HBM_GBS, "GB/s"
         kernels[name] = {"avg_ms": round(avg_ms, 5), "launches": cnt, "bound": bound, "achieved": round(ach, 2),
                          "peak": peak, "unit": unit, "frac": round(ach / peak, 4)}
+        if bound == "mfma" and not bf:
+            kernels[name]["frac_split_bf16_peak"] = round(ach / reach_tf, 4)
     dominant = max(kernels, key=lambda k: kernels[k]["avg_ms"])
     # measured HBM bytes per launch (fetch + write) of the dominant kernel, from the counter runs
     traffic = None
@@ -476,7 +478,7 @@ def main() -> int:
                        "bwd_ms_min": call_ms["backward"]["min"], "bwd_tflops_nominal": round(f_bwd / bwd_ms / 1e9, 2),
                        f"bwd_frac_{peak_name}_peak": round(f_bwd / bwd_ms / 1e9 / reach_tf, 4)})
     if not bf:
-        detail["f32_peak_tflops"] = round(PEAK_F32_SPLIT_TFLOPS, 1)   # what the two fractions above are of
+        detail["split_bf16_peak_tflops"] = round(PEAK_F32_SPLIT_TFLOPS, 1)   # what fwd_frac_f32_peak and bwd_frac_f32_peak are of
     detail["step_ms_median"] = call_ms["step"]["median"]
     detail["step_ms_min"] = call_ms["step"]["min"]
     detail["gate_prefix_ms"] = call_ms["gate_prefix"]["avg"]
