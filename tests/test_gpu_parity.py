@@ -686,6 +686,21 @@ def test_f32_row_steps(g, oracle, B, H, Hkv, N, d, w):
     check_grads(got, ref, 1e-5, "f32 row steps")
 
 
+@pytest.mark.parametrize("B,H,Hkv,N,d,w", [(2, 6, 6, 300, 128, 77), (2, 8, 2, 130, 64, 100), (4, 1, 1, 700, 64, 700), (1, 1, 1, 256, 64, 64)])
+def test_f32_rows_gate_gradient_cancels(g, oracle, B, H, Hkv, N, d, w):
+    # d(alpha)[..., 0] is the sum of every dS as a column minus the sum of every dS as a row: zero.  The two kernels form the same
+    # dS bit by bit and add it up in fp64, so what is left is the rounding of the 2 N stored sums, at most 2^-24 of each and
+    # independent (four deviations of 2^-24 / sqrt(3) each), and that of the scan, some additions of 2^-24 of a suffix sum
+    note("f32 rows, gate gradient", B, H, Hkv, N, d, w)
+    wl = gi.custom("f32g", B, H, N, d, w, "f32", alpha_mu=-1.0, index=24, backward=True, kv_heads=Hkv)
+    got, ref = run_gqa(g, oracle, wl)
+    dc = ref["dalpha"] - np.concatenate([ref["dalpha"][..., 1:], np.zeros_like(ref["dalpha"][..., :1])], axis=-1)
+    bound = 2.0 ** -24 * (4 / np.sqrt(3) * np.sqrt((dc ** 2).sum(axis=-1)) + np.abs(ref["dalpha"]).max(axis=-1))
+    ratio = (np.abs(got["dalpha"][..., 0]) / bound).max()
+    note("  |d(alpha)[..., 0]| over its bound", ratio)
+    assert ratio <= 1
+
+
 # (the one-wave-per-row kernels, the last steps of a row partly filled; the last two: more than 1024 rows, the forward's short steps)
 @pytest.mark.parametrize("B,H,Hkv,N,d,w", [(1, 2, 1, 77, 64, 30), (1, 2, 2, 50, 128, 33), (1, 16, 8, 77, 64, 30), (1, 24, 24, 50, 128, 11)])
 def test_f32_rows_with_infinities(g, oracle, B, H, Hkv, N, d, w):
