@@ -548,7 +548,9 @@ double query_tile_fill(int BH, int N, int w, long slots) {
 
 // Which kernel serves a problem.  The persistent one is the better when its rounds of resident workgroups are full of
 // tiles of equal length.  Measured over 24 shapes (N 64 .. 16384, 1 .. 2048 tiles, both head dimensions) the split
-// kernel wins where they are filled below 0.48 (by 1.15 to 2.1) and loses above 0.6 (by up to 1.2).
+// kernel wins where they are filled below 0.48 (by 1.15 to 2.1).  The line is on the safe side: over 18 shapes filled to 0.49 .. 0.63
+// the 64-query shape is between 1.33 times as fast and 1.06 times as slow (B2 H32 N1973 d64 w196: 21.5 against 28.6 us; B1 H12 N3425
+// d128 w698: 31.5 against 29.6; median 1.12 times as fast); above that the 24 have it lose by up to 1.2.
 // Inside the split kernel: one 32-query block per workgroup while that gives few workgroups (at d = 128 its
 // single-buffered tiles only pay for short bands), 128 queries where the band is long enough to share out.
 static FwdSplit fwd_split_shape(int BH, int N, int d, int w) {

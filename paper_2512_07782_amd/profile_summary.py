@@ -55,10 +55,9 @@ LIB = {
     # few or uneven tiles
     "fwd_split_bf16_kernel": "forward", "bwd_dkv_split_bf16_kernel": "bwd_dkv", "bwd_dq_split_bf16_kernel": "bwd_dq",
     # fp32 storage
-    "fwd_f32_mfma_kernel<128>": "forward", "fwd_f32_mfma_kernel<64>": "forward", "fwd_f32_kernel": "forward",
-    "rowdot_f32_kernel": "bwd_rowdot",
-    "bwd_dkv_f32_mfma_kernel<128>": "bwd_dkv", "bwd_dkv_f32_mfma_kernel<64>": "bwd_dkv", "bwd_dkv_f32_kernel": "bwd_dkv",
-    "bwd_dq_f32_mfma_kernel<128>": "bwd_dq", "bwd_dq_f32_mfma_kernel<64>": "bwd_dq", "bwd_dq_f32_kernel": "bwd_dq",
+    "fwd_f32_mfma_kernel": "forward", "fwd_f32_kernel": "forward", "rowdot_f32_kernel": "bwd_rowdot",
+    "bwd_dkv_f32_mfma_kernel": "bwd_dkv", "bwd_dkv_f32_kernel": "bwd_dkv",
+    "bwd_dq_f32_mfma_kernel": "bwd_dq", "bwd_dq_f32_kernel": "bwd_dq",
 }
 # the long_bwd workload of bench.py
 B, H, N, D, W = 1, 32, 16384, 128, 1024
@@ -66,8 +65,8 @@ CAL = "plain f32 copy (calibration)"
 
 
 def lib_name(kernel: str):
-    """The library's name of a kernel, or None; the waves per workgroup of the scans and of the fp32 forward and the
-    sizes of the split and of the one-wave-per-row kernels do not matter."""
+    """The library's name of a kernel, or None; the waves per workgroup of the scans and the sizes of the split and of the
+    fp32 kernels do not matter."""
     for k in (kernel, re.sub(r", \d+>$", ">", kernel), re.sub(r"<.*", "", kernel)):
         if k in LIB:
             return LIB[k]
