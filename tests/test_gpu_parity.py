@@ -733,8 +733,13 @@ def test_f32_rows_with_infinities(g, oracle, B, H, Hkv, N, d, w):
     assert (dV[:, :, ~free, col] == float("inf")).all()
 
 
+# (128 queries per workgroup; 64; 128 with one tile buffer.  One query head per key/value head where the largest value of one
+# query would else add up to infinity)
+F32_MATRIX_CORE = [(4, 2, 1100, 128, 400), (4, 4, 1300, 64, 300), (64, 64, 193, 64, 65), (300, 300, 97, 128, 40)]
+
+
 # fp32 storage takes every finite value, and infinities where plain fp32 arithmetic gives a meaning to them, at any size
-@pytest.mark.parametrize("H,Hkv,N,d,w", [(4, 2, 1100, 128, 400), (4, 4, 1300, 64, 300)])
+@pytest.mark.parametrize("H,Hkv,N,d,w", F32_MATRIX_CORE)
 def test_f32_matrix_core_range(g, oracle, H, Hkv, N, d, w):
     note("f32 range", H, Hkv, N, d, w)
     wl = gi.custom("f32x", 1, H, N, d, w, "f32", alpha_mu=-2.0, index=20, backward=True, kv_heads=Hkv)
@@ -795,7 +800,7 @@ def test_f32_matrix_core_range(g, oracle, H, Hkv, N, d, w):
             assert r <= 1e-5, (name, k)
 
 
-@pytest.mark.parametrize("H,Hkv,N,d,w", [(4, 2, 1100, 128, 400), (4, 4, 1300, 64, 300)])
+@pytest.mark.parametrize("H,Hkv,N,d,w", F32_MATRIX_CORE)
 def test_f32_matrix_core_small_values(g, oracle, H, Hkv, N, d, w):
     # matrices of values of 2^-118, exactly the scaled ones: every result that is linear in the matrix is the scaled one too,
     # to the fp32 bar (2^-149, the spacing of the smallest fp32 values, is 2^-31 of 2^-118)
