@@ -221,6 +221,8 @@ __global__ __launch_bounds__(64 * NW) void decode_partial_kernel(
             Raw8<T> k1;
             k1.load(Kh + (size_t)kw_end * D);
             scores(k1, (alpha_t != nullptr && kw_end == p) ? ct_own : c_own[kw_end], mref);
+#pragma unroll
+            for (int g = 0; g < GT; ++g) mref[g] = fmaxf(mref[g], kDecNegBig);  // that key may be masked: a score of minus infinity
         }
 
         auto compute = [&](int st, auto bufc) __attribute__((always_inline)) {

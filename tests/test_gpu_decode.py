@@ -89,6 +89,35 @@ def test_decode_large_batches(g, oracle, B, H, Hkv, T, d, w, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,H,Hkv,T,d,w", [
+    # one head per workgroup of 8 (fp32: 4) waves, one chunk and several; two heads; four heads
+    (1, 8, 2, 900, 128, 300), (1, 4, 4, 1500, 64, 1500), (256, 2, 1, 300, 64, 300), (64, 8, 2, 300, 128, 257),
+])
+def test_decode_with_masked_keys(g, oracle, B, H, Hkv, T, d, w, dtype):
+    # a key that holds the type's lowest value where the query is positive scores minus infinity and has no weight, wherever it
+    # stands: at the end of a wave's share of the window (the waves start from the score there), in all of it, last of all
+    wl = gi.custom("decmask", B, H, T, d, w, dtype, alpha_mu=-2.0, index=26, kv_heads=Hkv)
+    Kc, Vc, alpha = (gi.make_tensor(wl, t) for t in ("K", "V", "alpha"))
+    q = np.ascontiguousarray(gi.make_tensor(wl, "Q")[:, :, 0, :])
+    q[..., 0] = 12.0
+    pos = np.full(B, T - 1, dtype=np.int32)
+    c32 = oracle.gate_prefix(alpha).astype(np.float32)
+    back = T - 1 - np.arange(T)
+    for name, masked in (("two of three", back % 3 != 1), ("every eighth", back % 8 == 0), ("a run", (back >= 5) & (back < w // 2 + 40)),
+                         ("all but two", (back != 3) & (back != w - 2))):
+        Kc[:, :, masked, 0] = -1e5
+        o_ref, L_ref = oracle.decode_from_c(q, Kc, Vc, c32, pos, w, wl.scale)
+        Kd = dev(Kc, dtype)
+        Kd[:, :, torch.from_numpy(masked).to(DEV), 0] = torch.finfo(Kd.dtype).min
+        o, L = g.gfwa_decode(dev(q, dtype), Kd, dev(Vc, dtype), dev(c32, "f32"), dev(pos, "i32"), w, wl.scale)
+        Kc[:, :, masked, 0] = 0.0
+        err, lerr = np.abs(host(o) - o_ref), np.abs(host(L) - L_ref)
+        print("  masked:", name, err.max(), lerr.max(), flush=True)
+        assert err.max() <= (2e-2 if dtype == "bf16" else 1e-5 * np.abs(o_ref).max())
+        assert (lerr <= 1e-4 + 1e-5 * np.abs(L_ref) + 2.0 ** -21 * window_span(c32, w)).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("B,H,Hkv,T,d,w", [(2, 8, 2, 700, 128, 512), (2, 4, 2, 900, 64, 300), (1, 4, 4, 640, 128, 640)])
 def test_decode_with_scores_far_apart(g, oracle, B, H, Hkv, T, d, w, dtype):
     # queries and keys of large norm: scores differ by far more than 2^60 inside a wave's 64 keys, so the
