@@ -503,6 +503,12 @@ __global__ __launch_bounds__(kFwdThreads, kFwdResident<D>) void fwd_bf16_kernel(
         store_acc_rows<DB>(o[qb], inv, sm.v[kStageQ ? 1 : 0] + 4096 * wv, O + head_done + (size_t)row0 * D, N - row0, lane);
     }
     if (!more) break;
+    // The first iteration of the next tile multiplies what lies there by zero probabilities, and rows past N that see no
+    // key, or rows whose keys are all masked, have left NaN (0 / 0): it is made finite again, 64 16-byte words at a time.
+    static_assert(kQB == 1 && kFwdThreads == 256, "the four waves' 4 KB are the V slot (d = 64: both) that is read");
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<f32x4*>(sm.v[kStageQ ? 1 : 0] + 4096 * wv + 1024 * i + 16 * lane) = f32x4{0.f, 0.f, 0.f, 0.f};
     // the Q fragments, after the stores (they would otherwise be live beside the accumulators): from the rings if the
     // drain step has fetched them (rows 32 wv .. of the 128: waves 0, 1 from K slot 1, waves 2, 3 from V slot 0)
     if (kStageQ && stage_T >= 0) {

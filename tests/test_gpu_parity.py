@@ -606,6 +606,16 @@ def test_forward_bf16_partial_last_round(g, oracle, B, H, N, d, w, heads):
     check_bf16_forward(O, L, O_ref, L_ref, tag="partial last round")
 
 
+@pytest.mark.parametrize("H,N,d,w", [(40, 2049, 128, 16), (60, 2049, 64, 16), (36, 2070, 128, 1)])
+def test_forward_bf16_after_rows_past_the_end(g, oracle, H, N, d, w):
+    # the last query tile of a head has waves without a query, whose made-up rows see no key at all (N + 32 .. with short
+    # windows): what they leave in LDS must not reach the tile of another head that the same workgroup takes next
+    note("after rows past the end", H, N, d, w)
+    wl = gi.custom("past", 1, H, N, d, w, "bf16", alpha_mu=-1.5, index=27)
+    O, L, O_ref, L_ref = run_forward(g, oracle, wl)
+    check_bf16_forward(O, L, O_ref, L_ref, tag="past the end")
+
+
 @pytest.mark.parametrize("B,H,N,d,w,heads", [
     # few query tiles: 32 queries per workgroup (last block of one row, window inside a block, window past the sequence)
     (1, 3, 97, 128, 40, [0, 2]), (2, 2, 65, 64, 5000, [0, 3]), (1, 1, 1000, 128, 999, [0]),
