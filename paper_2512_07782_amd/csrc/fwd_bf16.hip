@@ -1,4 +1,5 @@
-// GatedFWA fused forward for bf16 storage on gfx950 (paper Alg. 2, re-designed for CDNA4).
+// GatedFWA fused forward for bf16 storage on gfx950, 128-wide heads (paper Alg. 2, re-designed for CDNA4;
+// 64-wide heads: fwd_d64_bf16.hip).
 //
 // Workgroups of 4 waves, two resident per CU (two waves per SIMD, 256 registers each), persistent: a
 // workgroup takes one tile of 128 consecutive queries of one (b,h) after another, and a wave owns one block of
@@ -17,7 +18,7 @@
 //
 // Software pipeline inside the wave.  With blocks of 32 keys numbered n in visiting order, iteration n
 // issues, as one straight-line instruction stream,
-//   matrix pipe:  S(n) = g + K Q^T      and      O += V^T P(n-2)          (16 MFMAs at d = 128)
+//   matrix pipe:  S(n) = g + K Q^T      and      O += V^T P(n-2)          (16 MFMAs)
 //   vector unit:  P(n-1) = exp2(S(n-1) * sl - m * sl), row sums
 //   LDS:          the fragments of the MFMAs four steps ahead
 //   load unit:    in the first block of a tile, this wave's share of the keys of tile T+1 and of the values of
@@ -30,7 +31,7 @@
 // T+1 (by the PV products, which lag two blocks), the K tile of step T+1 is requested in step T.
 // When a tile is finished the first key tile of the next one is requested before O is stored, and O
 // leaves as whole 128-byte lines through the idle V ring.  The next tile's queries arrive through the rings as
-// well when the tile count is even (d = 128): the last step's loads, which no product reads, fetch them.
+// well when the tile count is even: the last step's loads, which no product reads, fetch them.
 //
 // The gate bias rides in the MFMA accumulator: S is initialised with g_i = (c_i - c_base) / scale
 // straight from LDS before the K Q^T chain, so S = q.k + g_i and the probability is one fused
@@ -56,35 +57,25 @@ namespace gfwa {
 
 constexpr int kFwdWaves = 4;
 constexpr int kFwdThreads = 64 * kFwdWaves;
-// 32-query blocks per wave.  One: at d = 128 that is the register budget of two waves per SIMD; at d = 64 two blocks
-// fit (254 registers, every K and V fragment read from LDS then feeds two MFMAs) but measured slower, 84 us against
-// 74 us on the LM-scale workload: the 256-query tile staggers the waves' bands further and the waves run out of
-// independent work to cover each other.
-template <int D>
-constexpr int kQueryBlocks = 1;
-template <int D>
-constexpr int kFwdBR = 32 * kQueryBlocks<D> * kFwdWaves;  // queries per workgroup
+constexpr int kQueryBlocks = 1;  // 32-query blocks per wave: the register budget of two waves per SIMD
+constexpr int kFwdBR = 32 * kQueryBlocks * kFwdWaves;  // queries per workgroup
 constexpr int kRing = 2;                         // K and V tile slots each: one being read, one in flight
-// Resident workgroups per CU: two at d = 128 (256 registers per wave); three at d = 64, where the accumulators are
-// half as large (the kernel fits 168 registers) and a workgroup's rings take 33 KB of LDS.
-template <int D>
-constexpr int kFwdResident = D == 64 ? 3 : 2;
+constexpr int kFwdResident = 2;  // workgroups per CU (256 registers per wave)
+constexpr int D = 128;
 
-template <int D>
 using FwdSmem = KvRingSmem<D, kRing>;
 
-template <int D>
-__global__ __launch_bounds__(kFwdThreads, kFwdResident<D>) void fwd_bf16_kernel(
+__global__ __launch_bounds__(kFwdThreads, kFwdResident) void fwd_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w,
     float scale_log2, int num_qtiles, int total_tiles, int H, int G) {
-    constexpr int kQB = kQueryBlocks<D>;
-    constexpr int BR = kFwdBR<D>;
+    constexpr int kQB = kQueryBlocks;
+    constexpr int BR = kFwdBR;
     constexpr int KC = D / 16;  // MFMA k-chunks along the head dimension
     constexpr int DB = D / 32;  // 32-wide blocks of the head dimension
     using Loader = TilePairLoader<D, kFwdWaves>;
     extern __shared__ __align__(16) char smem_raw[];
-    FwdSmem<D>& sm = *reinterpret_cast<FwdSmem<D>*>(smem_raw);
+    FwdSmem& sm = *reinterpret_cast<FwdSmem*>(smem_raw);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -140,9 +131,8 @@ __global__ __launch_bounds__(kFwdThreads, kFwdResident<D>) void fwd_bf16_kernel(
     // those land in K slot 1 and V slot 0, both idle by then, and the first key tile of the next query tile goes to
     // K slot 0.  So in that step the two loads fetch the next tile's 128 queries instead (first 64 into the K slot,
     // last 64 into the V slot, swizzled like any tile), and the waves pick their Q fragments up from LDS when the tile
-    // starts instead of waiting for a round trip to memory.  (d = 128 only: at d = 64 the output staging needs both
-    // V slots.  Odd tile counts keep the loads from global memory.)
-    constexpr bool kStageQ = D == 128 && kQB == 1;
+    // starts instead of waiting for a round trip to memory.  (Odd tile counts keep the loads from global memory.)
+    constexpr bool kStageQ = kQB == 1;
     int stage_T = -1000;      // the step whose spare loads fetch the next tile's queries, if any
     const char* Qn = nullptr; // Q of the next tile's head
     int qn0 = 0;              // first query of the next tile
@@ -171,7 +161,7 @@ __global__ __launch_bounds__(kFwdThreads, kFwdResident<D>) void fwd_bf16_kernel(
     load_query_gates();
     // ring slots that were never loaded are read by the first and last iterations of a band (as operands
     // of products with zero probabilities, or into scores that the mask overrides): make them finite once
-    for (int o16 = tid * 16; o16 < (int)(offsetof(FwdSmem<D>, craw)); o16 += kFwdThreads * 16)
+    for (int o16 = tid * 16; o16 < (int)(offsetof(FwdSmem, craw)); o16 += kFwdThreads * 16)
         *reinterpret_cast<f32x4*>(smem_raw + o16) = f32x4{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
 
@@ -182,9 +172,9 @@ __global__ __launch_bounds__(kFwdThreads, kFwdResident<D>) void fwd_bf16_kernel(
     // a tile index below 0 reads tile 0 (the loads of the two steps after a band's last tile, which nothing reads).
     constexpr int kRowsPerLoad = Loader::kRowsPerLoad, kLoadsPerWave = Loader::kLoadsPerWave;
     constexpr int kRowsPerWave = Loader::kRowsPerWave, kChunksPerRow = Loader::kChunksPerRow;
-    static_assert(kRowsPerLoad == 4 || kRowsPerLoad == 8, "1 KB loads of 256- or 128-byte rows");
+    static_assert(kRowsPerLoad == 4, "1 KB loads of 256-byte rows");
     // load g fetches row ld_row0 + kRowsPerLoad g of the tile; the swizzle of that row differs from load 0's only
-    // in chunk bits that g alone sets (d = 128: bits 0-1 = (row >> 2) & 3 = g; d = 64: bit 0 = (row >> 3) & 1 = g & 1)
+    // in chunk bits that g alone sets (bits 0-1 = (row >> 2) & 3 = g)
     const int ld_row0 = kRowsPerWave * wv + lane / kChunksPerRow;
     const unsigned ld_chunk0 = (unsigned)(swz_chunk<D>(ld_row0, lane % kChunksPerRow) * 16);
     // load g of tile T (position in visiting order: tile j_hi - T) of the matrix at Mh into its ring slot
@@ -236,16 +226,16 @@ __global__ __launch_bounds__(kFwdThreads, kFwdResident<D>) void fwd_bf16_kernel(
         lds_ptr base = (lds_ptr)smem_raw;
 #pragma unroll
         for (int kc = 0; kc < KC; ++kc)
-            kaddr[kc] = base + offsetof(FwdSmem<D>, k) + tile_off<D>(lane & 31, 2 * kc + h);
+            kaddr[kc] = base + offsetof(FwdSmem, k) + tile_off<D>(lane & 31, 2 * kc + h);
         const int i16 = lane & 15;
         const int row = 4 * h + (i16 >> 2);
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             const int col = 32 * db + 16 * ((lane & 31) >> 4) + 4 * (i16 & 3);
-            vaddr[db][0] = base + offsetof(FwdSmem<D>, v) + tile_off<D>(row, col >> 3) + (col & 7) * 2;
-            vaddr[db][1] = base + offsetof(FwdSmem<D>, v) + tile_off<D>(row + 8, col >> 3) + (col & 7) * 2;
+            vaddr[db][0] = base + offsetof(FwdSmem, v) + tile_off<D>(row, col >> 3) + (col & 7) * 2;
+            vaddr[db][1] = base + offsetof(FwdSmem, v) + tile_off<D>(row + 8, col >> 3) + (col & 7) * 2;
         }
-        gaddr = base + offsetof(FwdSmem<D>, g) + 16 * h;
+        gaddr = base + offsetof(FwdSmem, g) + 16 * h;
     }
     constexpr int kTileBytes = kTileRows * D * 2;
     auto read_k = [&](int kc, int disp) __attribute__((always_inline)) -> bf16x8 {
@@ -505,7 +495,7 @@ __global__ __launch_bounds__(kFwdThreads, kFwdResident<D>) void fwd_bf16_kernel(
     if (!more) break;
     // The first iteration of the next tile multiplies what lies there by zero probabilities, and rows past N that see no
     // key, or rows whose keys are all masked, have left NaN (0 / 0): it is made finite again, 64 16-byte words at a time.
-    static_assert(kQB == 1 && kFwdThreads == 256, "the four waves' 4 KB are the V slot (d = 64: both) that is read");
+    static_assert(kQB == 1 && kFwdThreads == 256, "the four waves' 4 KB are the V slot that is read");
 #pragma unroll
     for (int i = 0; i < 4; ++i)
         *reinterpret_cast<f32x4*>(sm.v[kStageQ ? 1 : 0] + 4096 * wv + 1024 * i + 16 * lane) = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -522,56 +512,72 @@ __global__ __launch_bounds__(kFwdThreads, kFwdResident<D>) void fwd_bf16_kernel(
     }
 }
 
-template <int D>
 static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const float* c, void* O,
                              float* L, int B, int H, int Hkv, int N, int w, float scale, hipStream_t s) {
-    const int num_qtiles = (N + kFwdBR<D> - 1) / kFwdBR<D>;
+    const int num_qtiles = (N + kFwdBR - 1) / kFwdBR;
     const int total = B * H * num_qtiles;
     static DeviceOnce lds_allowed;
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&fwd_bf16_kernel<D>), sizeof(FwdSmem<D>),
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&fwd_bf16_kernel), sizeof(FwdSmem),
                                          lds_allowed))
         return e;
     const int num_cu = device_cu_count();
-    const int grid = total < kFwdResident<D> * num_cu ? total : kFwdResident<D> * num_cu;  // every workgroup resident
+    const int grid = total < kFwdResident * num_cu ? total : kFwdResident * num_cu;  // every workgroup resident
     ProfScope prof(kKernForward, s);
-    hipLaunchKernelGGL((fwd_bf16_kernel<D>), dim3(grid), dim3(kFwdThreads), sizeof(FwdSmem<D>), s,
+    hipLaunchKernelGGL(fwd_bf16_kernel, dim3(grid), dim3(kFwdThreads), sizeof(FwdSmem), s,
                        (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, c, (bf16_t*)O, L, N, w,
                        scale * kLog2e, num_qtiles, total, H, H / Hkv);
     return hipGetLastError();
 }
 
-// The share of `slots` resident workgroups' time that holds work when the 128-query tiles of a problem are taken in
-// rounds:  (steps of all tiles) / (slots x rounds x steps of the longest tile), a step being a 64-key tile, plus
-// two per tile to fill and drain.
-double query_tile_fill(int BH, int N, int w, long slots) {
+// Steps (64-key tiles, plus two per tile to fill and drain) of all 128-query tiles of a problem, and of the longest.
+static double query_tile_steps(int BH, int N, int w, long& longest) {
     const long nq = (N + 127) / 128;
     const long band = w < N ? w : N, full = (band + 126) / 64 + 2;   // key tiles of a tile whose whole band exists
     const long ramp = nq < (full - 1) / 2 ? nq : (full - 1) / 2;      // tiles whose band the sequence's start cuts off
-    const long longest = (2 * nq < full ? 2 * nq : full) + 2;
-    const double steps = (double)BH * (double)(ramp * (ramp + 1) + 2 * ramp + (nq - ramp) * longest);
+    longest = (2 * nq < full ? 2 * nq : full) + 2;
+    return (double)BH * (double)(ramp * (ramp + 1) + 2 * ramp + (nq - ramp) * longest);
+}
+// The share of `slots` resident workgroups' time that holds work when the tiles are taken in rounds:
+// (steps of all tiles) / (slots x rounds x steps of the longest tile).
+double query_tile_fill(int BH, int N, int w, long slots) {
+    long longest;
+    const double steps = query_tile_steps(BH, N, w, longest);
+    const long nq = (N + 127) / 128;
     return steps / ((double)slots * (double)((BH * nq + slots - 1) / slots) * (double)longest);
 }
 
-// Which kernel serves a problem.  The persistent one is the better when its rounds of resident workgroups are full of
-// tiles of equal length.  Measured over 24 shapes (N 64 .. 16384, 1 .. 2048 tiles, both head dimensions) the split
-// kernel wins where they are filled below 0.48 (by 1.15 to 2.1).  The line is on the safe side: over 18 shapes filled to 0.49 .. 0.63
-// the 64-query shape is between 1.33 times as fast and 1.06 times as slow (B2 H32 N1973 d64 w196: 21.5 against 28.6 us; B1 H12 N3425
-// d128 w698: 31.5 against 29.6; median 1.12 times as fast); above that the 24 have it lose by up to 1.2.
+// Which kernel serves a problem.
+// d = 128: the persistent one is the better when its rounds of resident workgroups are full of tiles of equal length.
+// Measured over 24 shapes (N 64 .. 16384, 1 .. 2048 tiles, both head dimensions) the split kernel wins where they are
+// filled below 0.48 (by 1.15 to 2.1).  The line is on the safe side: over 18 shapes filled to 0.49 .. 0.63 the 64-query
+// shape is between 1.33 times as fast and 1.06 times as slow (B1 H12 N3425 w698: 31.5 against 29.6 us; median 1.12 times
+// as fast); above that the 24 have it lose by up to 1.2.
+// d = 64: the kernel of four workgroups on a CU wins once a CU has 1.3 times the steps of the longest tile to do.  Over 37
+// shapes (N 100 .. 16384) the best split shape is 1.04 to 1.8 times as fast below that (one exception, 0.98), and above it
+// between 1.27 times as slow and equal (one exception, H24 N2100 w300: 12.5 against 14.5 us).  Sequences shorter than a
+// key tile, which that kernel does not take, are served better by 64 queries than by 32 (512 x 4 heads of 50: 13.7, 28.0).
 // Inside the split kernel: one 32-query block per workgroup while that gives few workgroups (at d = 128 its
-// single-buffered tiles only pay for short bands), 128 queries where the band is long enough to share out.
+// single-buffered tiles only pay for short bands), 128 queries where the band is long enough to share out (at d = 64,
+// H12 N4000 w2000: 38.6 against 31.4 us with 64, H15 N4000 causal: 48.5 against 71.7).
 static FwdSplit fwd_split_shape(int BH, int N, int d, int w) {
     const long cus = device_cu_count(), band = w < N ? w : N;
-    if (query_tile_fill(BH, N, w, cus * (d == 64 ? kFwdResident<64> : kFwdResident<128>)) >= 0.48) return kFwdSplitNone;
+    if (d == 64) {
+        long longest;
+        const double steps = query_tile_steps(BH, N, w, longest);
+        if (N >= 64 && steps >= 1.3 * (double)cus * (double)longest) return kFwdSplitNone;
+    } else if (query_tile_fill(BH, N, w, cus * kFwdResident) >= 0.48) {
+        return kFwdSplitNone;
+    }
     if ((long)BH * ((N + 31) / 32) <= 5 * cus / 2 && (d == 64 || band <= 1024)) return kFwdSplitNarrow;
-    return band > 1500 ? kFwdSplitWide : kFwdSplitMid;
+    return band > (d == 64 ? 2560 : 1500) ? kFwdSplitWide : kFwdSplitMid;
 }
 
 hipError_t forward_bf16(const void* Q, const void* K, const void* V, const float* c, void* O, float* L,
                         int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s) {
     if (const FwdSplit shape = fwd_split_shape(B * H, N, d, w))
         return forward_split_bf16(shape, Q, K, V, c, O, L, B, H, Hkv, N, d, w, scale, s);
-    if (d == 128) return launch_fwd<128>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
-    return launch_fwd<64>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
+    if (d == 64) return forward_d64_bf16(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
+    return launch_fwd(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
 }
 
 }  // namespace gfwa
