@@ -20,6 +20,9 @@
 // In both kernels the row- (dkv) or key- (dq) dependent part of the exponent rides in the MFMA
 // accumulator (it is initialised from an LDS vector before the product), the lane-constant part is
 // the addend of the single fused multiply-add in front of exp2; the dP accumulator starts from -D.
+// Workgroups are dealt out from the longest band to the shortest over all heads of an XCD (tile_of_block); one head after
+// another, launches whose bands differ ended half empty: whole backward B2 H32 N2048 causal 309 -> 260 us at d = 128 and
+// 181 -> 145 at d = 64, B4 H16 N4096 d64 w2000 414 -> 368, B1 H32 N16384 d128 w1024 (blocks kept) 947 -> 930.
 // The row sums are analytically zero but are kept: with D formed from the rounded O they carry
 // exactly the error that would otherwise accumulate over the whole suffix in the reverse scan.
 #include <math.h>
@@ -75,9 +78,10 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkv_bf16_kernel(
     constexpr int KC = D / 16, DB = D / 32;
     __shared__ DkvSmem<D> sm;
 
-    const int tile = xcd_remap(blockIdx.x, total_tiles);
-    const int bkv = tile / num_ktiles;  // flat key/value head; its G query heads are visited in turn
-    const int k0 = (tile % num_ktiles) * BK;
+    int bkv, kt;  // flat key/value head, whose G query heads are visited in turn; the sequence's end, which few queries see, last
+    const int heads = total_tiles / num_ktiles;
+    tile_of_block(heads, num_ktiles, heads % 8 == 0 || w >= N, bkv, kt);
+    const int k0 = kt * BK;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, lk = lane & 31;
@@ -306,9 +310,10 @@ __global__ __launch_bounds__(2 * kThreads, 1) void bwd_dkv8_bf16_kernel(
     __shared__ Dkv8Smem<D> sm8;
     auto& sm = sm8.t;
 
-    const int tile = xcd_remap(blockIdx.x, total_tiles);
-    const int bkv = tile / num_ktiles;  // flat key/value head; its G query heads are visited in turn
-    const int k0 = (tile % num_ktiles) * BK;
+    int bkv, kt;  // flat key/value head, whose G query heads are visited in turn; the sequence's end, which few queries see, last
+    const int heads = total_tiles / num_ktiles;
+    tile_of_block(heads, num_ktiles, heads % 8 == 0 || w >= N, bkv, kt);
+    const int k0 = kt * BK;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     // 32-key group kg and 32-query block `half` of every tile.  The two waves of a key group sit on different
@@ -624,9 +629,12 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_bf16_kernel(
     constexpr int KC = D / 16, DB = D / 32;
     __shared__ DqSmem<D> sm;
 
-    const int tile = xcd_remap(blockIdx.x, total_tiles);
-    const int bh = tile / num_qtiles;
-    const int q0 = (tile % num_qtiles) * BR;
+    // (at d = 128 K and V tiles of many heads at a time are more than an L2 holds: whole backward of B4 H16 N8192
+    // w1024 1025 us so, 1005 one head after another; with bands of half the sequence, B4 H16 N4096 w2048, 700 and 708)
+    const int heads = total_tiles / num_qtiles;
+    int bh, qt;
+    tile_of_block(heads, num_qtiles, (heads % 8 == 0 && (D == 64 || 4L * w >= N)) || w >= N, bh, qt);
+    const int q0 = (num_qtiles - 1 - qt) * BR;  // longest bands first
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, lq = lane & 31;
@@ -797,9 +805,10 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_spill_bf16_kernel(
     extern __shared__ __align__(16) char smem_raw[];
     DqSpillSmem<D>& sm = *reinterpret_cast<DqSpillSmem<D>*>(smem_raw);
 
-    const int tile = xcd_remap(blockIdx.x, total_tiles);
-    const int bh = tile / num_qtiles;
-    const int q0 = (tile % num_qtiles) * BR;
+    const int heads = total_tiles / num_qtiles;
+    int bh, qt;
+    tile_of_block(heads, num_qtiles, heads % 8 == 0 || w >= N, bh, qt);
+    const int q0 = (num_qtiles - 1 - qt) * BR;  // longest bands first
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, lq = lane & 31;

@@ -47,19 +47,11 @@ __global__ __launch_bounds__(64 * kWaves, 4) void fwd_d64_bf16_kernel(
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = lane >> 5, lq = lane & 31;
     const float sl = scale_log2, inv_scale = kLog2e / scale_log2;
-    // Longest bands (the end of the sequence) first over all heads; the heads of a group, which share keys, stay on one
-    // XCD.  Where the heads do not divide by the XCDs, contiguous ranges of tiles keep an XCD to few heads (B1 H12 N8192
-    // w1024: 35.5 against 37.6 us), unless the bands grow with the whole sequence (B3 H11 N4096 causal: 105 against 107 us).
-    const int BH = total / num_qtiles, b = (int)blockIdx.x;
+    // Longest bands (the end of the sequence) first.  Heads that do not divide by the XCDs: B1 H12 N8192 w1024 37.6 us tile
+    // after tile, 35.5 in contiguous ranges; B3 H11 N4096 causal 105 and 107 us.
+    const int heads = total / num_qtiles;
     int bh, qt;
-    if (BH % 8 == 0 || w >= N) {
-        bh = BH % 8 == 0 ? (b % 8) * (BH / 8) + b % BH / 8 : b % BH;
-        qt = b / BH;
-    } else {
-        const int id = xcd_remap(b, total);
-        bh = id / num_qtiles;
-        qt = id % num_qtiles;
-    }
+    tile_of_block(heads, num_qtiles, heads % 8 == 0 || w >= N, bh, qt);
     const int q0 = (num_qtiles - 1 - qt) * 128;
     const size_t head_off = (size_t)bh * N * D, kv_off = (size_t)kv_head_of(bh, H, G) * N * D;
     const char* Kh = reinterpret_cast<const char*>(K + kv_off);
