@@ -30,9 +30,6 @@ double query_tile_fill(int BH, int N, int w, long slots);  // how full rounds of
 enum FwdSplit { kFwdSplitNone = 0, kFwdSplitNarrow, kFwdSplitMid, kFwdSplitWide };  // 32, 64, 128 queries per workgroup
 hipError_t forward_split_bf16(FwdSplit shape, const void* Q, const void* K, const void* V, const float* c, void* O,
                               float* L, int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
-// The same for d = 64, N >= 64 (fwd_d64_bf16.hip).
-hipError_t forward_d64_bf16(const void* Q, const void* K, const void* V, const float* c, void* O, float* L, int B, int H,
-                             int Hkv, int N, int w, float scale, hipStream_t s);
 hipError_t forward_f32(const float* Q, const float* K, const float* V, const float* c, float* O,
                        float* L, int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
 

@@ -631,18 +631,21 @@ def test_forward_bf16_split_band(g, oracle, B, H, N, d, w, heads):
     check_bf16_forward(O, L, O_ref, L_ref, tag="split band")
 
 
-@pytest.mark.parametrize("B,H,N,w,heads", [
-    # 64-wide heads, more than 1.3 longest tiles of work per CU: sequences of one key tile, one row on either side of a key
-    # and of a query tile, windows of one key, inside a tile, at its edge and past the sequence; head counts that divide
-    # by the XCDs and that do not; last: shorter than a key tile, which the split kernel takes
-    (48, 8, 64, 64, [0, 383]), (5, 67, 65, 9, [0, 334]), (48, 8, 127, 1, [0, 200]), (5, 67, 128, 5000, [0, 334]),
-    (24, 16, 129, 64, [0, 383]), (7, 31, 193, 65, [0, 216]), (10, 20, 321, 128, [0, 199]), (128, 4, 63, 64, [0, 511]),
+@pytest.mark.parametrize("B,H,N,d,w,heads", [
+    # enough work per CU for the kernel of many workgroups on a CU: sequences of one key tile (64 keys at d = 64, 32 at
+    # d = 128), one row on either side of a key and of a query tile, windows of one key, inside a tile, at its edge and past the
+    # sequence; head counts that divide by the XCDs and that do not; shorter than a key tile, which the split kernel takes;
+    # last: a launch that puts two workgroups on a CU instead of three
+    (48, 8, 64, 64, 64, [0, 383]), (5, 67, 65, 64, 9, [0, 334]), (48, 8, 127, 64, 1, [0, 200]), (5, 67, 128, 64, 5000, [0, 334]),
+    (24, 16, 129, 64, 64, [0, 383]), (7, 31, 193, 64, 65, [0, 216]), (10, 20, 321, 64, 128, [0, 199]), (128, 4, 63, 64, 64, [0, 511]),
+    (48, 8, 32, 128, 32, [0, 383]), (5, 67, 33, 128, 9, [0, 334]), (48, 8, 127, 128, 1, [0, 200]), (5, 67, 128, 128, 5000, [0, 334]),
+    (24, 16, 161, 128, 32, [0, 383]), (7, 31, 193, 128, 65, [0, 216]), (128, 4, 31, 128, 64, [0, 511]), (7, 32, 450, 128, 128, [0, 223]),
 ])
-def test_forward_bf16_d64_tiles(g, oracle, B, H, N, w, heads):
-    note("d = 64 tiles", B, H, N, w)
-    wl = gi.custom("d64", B, H, N, 64, w, "bf16", alpha_mu=-1.5, index=15)
+def test_forward_bf16_many_workgroups(g, oracle, B, H, N, d, w, heads):
+    note("many workgroups", B, H, N, d, w)
+    wl = gi.custom("many", B, H, N, d, w, "bf16", alpha_mu=-1.5, index=15)
     O, L, O_ref, L_ref = run_forward(g, oracle, wl, heads=heads)
-    check_bf16_forward(O, L, O_ref, L_ref, tag="d64 tiles")
+    check_bf16_forward(O, L, O_ref, L_ref, tag="many workgroups")
 
 
 # ------------------------------------------------------------------------------------------
