@@ -80,38 +80,39 @@ __device__ __forceinline__ double wave_sum(double x) {
     return x;
 }
 
+// Four floats in one access at any multiple of 4 bytes: rows of odd length start anywhere.  (Element by element, rows of
+// such a length took four times the load and store instructions: 8 rows of 5003 5.75 -> 4.18 us, 1024 of 515 4.80 -> 4.05,
+// 300 of 999 with the activation 5.33 -> 4.57, 3 of 100001 with it in segments 9.75 -> 7.46.)
+typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // The four elements at logical positions p .. p + 3 of a row, zero at and beyond `end`.  Position p of the scan is memory index
 // p (forward) or N - 1 - p (reverse).  MODE kScanDiff: the scanned value is a[idx] - b[idx]; kScanGate: gate_alpha(a[idx],
-// b[idx], eps).  vec: float4 accesses, every row starts 16-byte aligned and N is a multiple of 4.  Loading and evaluation
-// are apart so that the loads of a chunk are in flight while something else is computed.
+// b[idx], eps).  Loading and evaluation are apart so that the loads of a chunk are in flight while something else is computed.
 template <bool REVERSE, int MODE>
 struct ScanQuad {
-    float4 x, y;
-    __device__ __forceinline__ void load(const float* ar, const float* br, int N, int p, int end, bool vec) {
+    f32x4 x, y;
+    __device__ __forceinline__ void load(const float* ar, const float* br, int N, int p, int end) {
         constexpr bool TWO = MODE != kScanPlain;
-        x = y = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (vec && p + 3 < end) {
+        x = y = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (p + 3 < end) {
             const int idx = REVERSE ? N - 4 - p : p;
-            x = *reinterpret_cast<const float4*>(ar + idx);
-            if (TWO) y = *reinterpret_cast<const float4*>(br + idx);
+            x = *reinterpret_cast<const float4_any*>(ar + idx);
+            if (TWO) y = *reinterpret_cast<const float4_any*>(br + idx);
         } else {
-            float* xs = &x.x;
-            float* ys = &y.x;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (p + e < end) {
                     const int idx = REVERSE ? N - 1 - (p + e) : p + e, to = REVERSE ? 3 - e : e;
-                    xs[to] = ar[idx];
-                    if (TWO) ys[to] = br[idx];
+                    x[to] = ar[idx];
+                    if (TWO) y[to] = br[idx];
                 }
         }
     }
     __device__ __forceinline__ void values(float (&v)[4], float eps, int p, int end) const {
-        const float xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int from = REVERSE ? 3 - e : e;
-            v[e] = MODE == kScanPlain ? xs[from] : MODE == kScanDiff ? xs[from] - ys[from] : p + e < end ? gate_alpha(xs[from], ys[from], eps) : 0.f;
+            v[e] = MODE == kScanPlain ? x[from] : MODE == kScanDiff ? x[from] - y[from] : p + e < end ? gate_alpha(x[from], y[from], eps) : 0.f;
         }
     }
 };
@@ -137,13 +138,11 @@ __global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __re
     const float* br = MODE != kScanPlain ? b + row : nullptr;
     float* outr = out + row;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const uintptr_t bits = (uintptr_t)a | (uintptr_t)out | (MODE != kScanPlain ? (uintptr_t)b : (uintptr_t)0);
-    const bool vec = (N % 4 == 0) && ((bits & 15) == 0);
 
     ScanQuad<REVERSE, MODE> quad[RUNS];
     auto load = [&](int base) __attribute__((always_inline)) {
 #pragma unroll
-        for (int r = 0; r < RUNS; ++r) quad[r].load(ar, br, N, run_start<WAVES>(base, wv, r, lane), end, vec);
+        for (int r = 0; r < RUNS; ++r) quad[r].load(ar, br, N, run_start<WAVES>(base, wv, r, lane), end);
     };
     load(begin);
     double carry = 0.0;
@@ -186,9 +185,9 @@ __global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __re
             float y[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) y[e] = (float)(from + (double)v[r][e]);
-            if (vec && p + 3 < end) {
+            if (p + 3 < end) {
                 const int idx = REVERSE ? N - 4 - p : p;
-                *reinterpret_cast<float4*>(outr + idx) = REVERSE ? make_float4(y[3], y[2], y[1], y[0]) : make_float4(y[0], y[1], y[2], y[3]);
+                *reinterpret_cast<float4_any*>(outr + idx) = REVERSE ? f32x4{y[3], y[2], y[1], y[0]} : f32x4{y[0], y[1], y[2], y[3]};
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -213,13 +212,11 @@ __global__ __launch_bounds__(64 * WAVES) void segment_sum_kernel(const float* __
     const float* ar = a + row;
     const float* br = MODE != kScanPlain ? b + row : nullptr;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const uintptr_t bits = (uintptr_t)a | (MODE != kScanPlain ? (uintptr_t)b : (uintptr_t)0);
-    const bool vec = (N % 4 == 0) && ((bits & 15) == 0);
     double acc = 0.0;
     for (int base = begin; base < end; base += kScanChunk) {
         ScanQuad<REVERSE, MODE> quad[RUNS];
 #pragma unroll
-        for (int r = 0; r < RUNS; ++r) quad[r].load(ar, br, N, run_start<WAVES>(base, wv, r, lane), end, vec);
+        for (int r = 0; r < RUNS; ++r) quad[r].load(ar, br, N, run_start<WAVES>(base, wv, r, lane), end);
 #pragma unroll
         for (int r = 0; r < RUNS; ++r) {
             float v[4];
@@ -248,7 +245,7 @@ __global__ __launch_bounds__(64 * WAVES) void segment_sum_kernel(const float* __
 // Longer rows keep a CU busy with one workgroup after another's barrier, and the activation is bound by vector work: sixteen
 // waves cover that (100 rows of 262144 with the activation: 127 against 249 us; sums of 512 segments with it: 7.0 against 8.0).
 static bool scan_four_waves(bool activation, bool segment, long workgroups, int len) {
-    if (workgroups <= device_cu_count() && (activation || (!segment && len <= kScanChunk))) return false;
+    if (workgroups <= device_cu_count() && (activation || !segment)) return false;
     return len <= 2 * kScanChunk;
 }
 template <bool REVERSE, int MODE>
