@@ -944,6 +944,19 @@ static bool bwd_dkv_splits(int BHkv, int G, int N, int d, int w) {
     return split < 0.9 * whole;
 }
 
+// Whether both passes go in one launch of split workgroups (32 keys of a key/value head, or 64 queries).  Measured over 41
+// small shapes (1 .. 128 heads of 64 .. 8000 tokens): with a workgroup for every CU at most it is between equal and 1.7 times
+// as fast as the best pair of launches (B1 H4 N300 d64 18.9 -> 11.2 us, H1 N64 12.5 -> 9.4), and so it is up to about twice as
+// many where the bands are at least half the sequence (H8 N1000 causal, d = 64 22.6 -> 21.0, d = 128 36.9 -> 33.1; H2 N4000
+// w1000 it would be 23.8 -> 27.8 and 41 -> 51).  At d = 128 a long chain of query blocks, each of which now brings its rows
+// of O along, is the exception (8 query heads on one key/value head, N500: 68 us in two launches, 76 in one).
+static bool bwd_in_one_launch(int BH, int BHkv, int N, int d, int w) {
+    const long cus = device_cu_count(), seen = w < N ? w : N, G = BH / BHkv;
+    const long blocks = (long)BHkv * ((N + 31) / 32) + (long)BH * ((N + 63) / 64);
+    if (G > kDkvSplitMaxGroup || (d == 128 && G * ((seen + 31) / 32) > 4 * 24)) return false;
+    return blocks <= cus || (2 * seen >= N && 10 * blocks <= (d == 64 ? 21 : 20) * cus);
+}
+
 template <int D>
 static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO,
                              const float* c, const float* L, void* dQ, void* dK, void* dV, float* dalpha,
@@ -959,6 +972,10 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     char* ds_ws = reinterpret_cast<char*>(ws + 3 * pad) + scan_pad;  // only with `spill`
     const BwdBf16 args = {(const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, c, L, Dv,
                           (bf16_t*)dQ, (bf16_t*)dK, (bf16_t*)dV, dc_col, dc_row, B, H, Hkv, N, w, scale};
+    if (bwd_in_one_launch(B * H, B * Hkv, N, D, w)) {
+        if (hipError_t e = bwd_both_split_bf16(args, D, s)) return e;
+        return gate_grad_scan(dc_col, dc_row, dalpha, scan_partial, B * H, N, s);
+    }
     // the dS blocks only travel between the kernels of this file: dK/dV is chosen first, dQ by whether there are blocks then
     const bool dkv_split = bwd_dkv_splits(B * Hkv, H / Hkv, N, D, w);
     if (dkv_split) spill = false;

@@ -6,7 +6,9 @@
 //        all query heads of the group - through LDS of its own, without a barrier, and the NW partial dK, dV are
 //        summed through LDS at the end
 // Latency bounds these sizes (first loads, first pass through the code, about 1 us per step of a wave), not a rate.
-// Whole backward, us, with the 128-row kernels / with the kernels here:
+// Where all workgroups of the two passes fit the chip together they go in one launch, D_t formed by both (bwd_in_one_launch in
+// bwd_bf16.hip has the line and more figures).
+// Whole backward, us, with the 128-row kernels / with the kernels here, one launch each (B2 H8/2 N515 d64 in one: 22.2):
 //   B2 H8/2 N515 d64 w512   63.4 / 26.6      B2 H8/2 N515 d128 w512   80.7 / 47.9     B1 H4 N1000 d128 w333    39.9 / 24.9
 //   B1 H8 N700 d128 w1024   46.9 / 31.7      B1 H4 N5003 d64 w3000   117.6 / 74.2     B1 H16/4 N5003 d64 w3000  323 / 223 (dKV only)
 #include "gfwa_device.h"
@@ -17,20 +19,22 @@ namespace gfwa {
 
 constexpr float kPosBig = 1.0e30f;
 
-// ---- D_t = <O_t, dO_t>, dQ, row sums of dS
+// ---- D_t = <O_t, dO_t>, dQ, row sums of dS.  Workgroup `block` of the pass.
 template <int D, int NW, int QW, int KB, int RING>
-__global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void bwd_dq_split_bf16_kernel(
-    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V, const bf16_t* __restrict__ O,
-    const bf16_t* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L, float* __restrict__ Dv,
-    bf16_t* __restrict__ dQ, float* __restrict__ dc_row, int N, int w, float scale, int num_qtiles, int BH, int H, int G) {
+__device__ __forceinline__ void dq_split(const BwdBf16& a, int num_qtiles, int block) {
     using Band = SplitBand<D, NW, QW, KB, RING>;
     constexpr int KC = D / 16, DB = D / 32, KW = Band::KW;
     extern __shared__ __align__(256) char smem_raw[];
     auto& sm = *reinterpret_cast<typename Band::Smem*>(smem_raw);
 
-    const float sl = scale * kLog2e;
-    const int bh = (int)(blockIdx.x % BH);  // longest bands first
-    const int q0 = (num_qtiles - 1 - (int)(blockIdx.x / BH)) * 32 * QW;
+    const bf16_t *__restrict__ Q = a.Q, *__restrict__ K = a.K, *__restrict__ V = a.V, *__restrict__ O = a.O, *__restrict__ dO = a.dO;
+    const float *__restrict__ c = a.c, *__restrict__ L = a.L;
+    float *__restrict__ Dv = a.Dv, *__restrict__ dc_row = a.dc_row;
+    bf16_t* __restrict__ dQ = a.dQ;
+    const int N = a.N, w = a.w, BH = a.B * a.H, H = a.H, G = a.H / a.Hkv;
+    const float scale = a.scale, sl = scale * kLog2e;
+    const int bh = block % BH;  // longest bands first
+    const int q0 = (num_qtiles - 1 - block / BH) * 32 * QW;
     const size_t head_off = (size_t)bh * N * D, kv_off = (size_t)kv_head_of(bh, H, G) * N * D;
     Band band(sm);
     band.open(K + kv_off, V + kv_off, c + (size_t)bh * N, N, w, q0, 1.0f / scale);
@@ -152,7 +156,13 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void bwd_dq_sp
         dQ + head_off + (size_t)q0 * D, N - q0);
 }
 
-// ---- dK, dV (summed over the query heads of a group), column sums of dS per query head
+template <int D, int NW, int QW, int KB, int RING>
+__global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void bwd_dq_split_bf16_kernel(BwdBf16 a, int num_qtiles) {
+    dq_split<D, NW, QW, KB, RING>(a, num_qtiles, (int)blockIdx.x);
+}
+
+// ---- dK, dV (summed over the query heads of a group), column sums of dS per query head.  OWN_D: D_t is formed here too, from
+// the rows of O, in the order of additions of dq_split, instead of read.
 template <int D, int NW>
 struct DkvSplitSmem {
     union {
@@ -168,20 +178,21 @@ struct DkvSplitSmem {
     float col[NW][kDkvSplitMaxGroup][32];
 };
 
-template <int D, int NW>
-__global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void bwd_dkv_split_bf16_kernel(
-    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-    const bf16_t* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
-    const float* __restrict__ Dv, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, float* __restrict__ dc_col, int N,
-    int w, float scale, int BHkv, int H, int G) {
+template <int D, int NW, bool OWN_D>
+__device__ __forceinline__ void dkv_split(const BwdBf16& a, int block) {
     constexpr int KC = D / 16, DB = D / 32;
     extern __shared__ __align__(256) char smem_raw[];
     auto& sm = *reinterpret_cast<DkvSplitSmem<D, NW>*>(smem_raw);
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = lane >> 5, lk = lane & 31;
-    const float sl = scale * kLog2e, inv_scale = 1.0f / scale;
+    const bf16_t *__restrict__ Q = a.Q, *__restrict__ K = a.K, *__restrict__ V = a.V, *__restrict__ O = a.O, *__restrict__ dO = a.dO;
+    const float *__restrict__ c = a.c, *__restrict__ L = a.L, *__restrict__ Dv = a.Dv;
+    bf16_t *__restrict__ dK = a.dK, *__restrict__ dV = a.dV;
+    float* __restrict__ dc_col = a.dc_col;
+    const int N = a.N, w = a.w, BHkv = a.B * a.Hkv, H = a.H, G = a.H / a.Hkv;
+    const float scale = a.scale, sl = scale * kLog2e, inv_scale = 1.0f / scale;
 
-    const int bkv = (int)(blockIdx.x % BHkv), k0 = (int)(blockIdx.x / BHkv) * 32;  // whole bands first, the sequence's end last
+    const int bkv = block % BHkv, k0 = block / BHkv * 32;  // whole bands first, the sequence's end last
     const int Hkv = H / G, bh0 = (bkv / Hkv) * H + (bkv % Hkv) * G;
     const size_t kv_off = (size_t)bkv * N * D;
     const int key = k0 + lk, keyc = min(key, N - 1);
@@ -192,6 +203,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void bwd_dkv_split_bf16_k
     PieceLoader<D> loader;
     loader.init(lane);
     float l_next = 0.f, c_next = 0.f, d_next = 0.f, ck_next = 0.f;
+    bf16x8 o_next[OWN_D ? KC : 1];  // OWN_D: this lane's half row of O, the elements that row_frag has of dO
     auto issue = [&](int s, int slot) __attribute__((always_inline)) {
         const int it = wv + s * NW, bh = bh0 + it / nblk, t0 = (qb_lo + it % nblk) * 32;
         const size_t rows = (size_t)bh * N;
@@ -200,7 +212,13 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void bwd_dkv_split_bf16_k
         const int tc = min(t0 + lk, N - 1);
         l_next = L[rows + tc];
         c_next = c[rows + tc];
-        d_next = Dv[rows + tc];
+        if constexpr (OWN_D) {
+            const bf16_t* orow = O + (rows + tc) * D + 8 * h;
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc) o_next[kc] = *reinterpret_cast<const bf16x8*>(orow + 16 * kc);
+        } else {
+            d_next = Dv[rows + tc];
+        }
         ck_next = c[rows + keyc];
 #pragma unroll
         for (int j = 0; j < 32 / PieceLoader<D>::kRows; ++j) {
@@ -237,8 +255,19 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void bwd_dkv_split_bf16_k
         const int it = wv + s * NW, g = it / nblk, t0 = (qb_lo + it % nblk) * 32;
         const float cbase = __shfl(ck_next, 0, 64), ckl = (ck_next - cbase) * kLog2e;  // c_base: the head's c at the first key
         sm.nl[wv][s & 1][lk] = t0 + lk < N ? -(l_next + (c_next - cbase)) * inv_scale : -kPosBig;
-        sm.dvec[wv][s & 1][lk] = -d_next;
+        if (!OWN_D) sm.dvec[wv][s & 1][lk] = -d_next;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if constexpr (OWN_D) {
+            const unsigned gt = (unsigned)(uintptr_t)sm.t.g[wv][s & 1];
+            float dsum = 0.f;
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc) {
+                const bf16x8 ga = row_frag<D>(gt + row_frag_off<D>(lane), 0, kc);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) dsum = fmaf((float)o_next[kc][e], (float)ga[e], dsum);
+            }
+            sm.dvec[wv][s & 1][lk] = -xhalf_sum(dsum);
+        }
         issue(min(s + 1, mine - 1), s + 1);  // (the last block once more at the end, into a slot nothing reads)
         const unsigned qt = (unsigned)(uintptr_t)sm.t.q[wv][s & 1], gt = (unsigned)(uintptr_t)sm.t.g[wv][s & 1];
         f32x16 sc, dp;
@@ -340,6 +369,19 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void bwd_dkv_split_bf16_k
     }
 }
 
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void bwd_dkv_split_bf16_kernel(BwdBf16 a) {
+    dkv_split<D, NW, false>(a, (int)blockIdx.x);
+}
+
+// Both passes in one launch, for problems whose workgroups all fit the chip at once: one after the other each leaves most
+// of it idle and pays for its own launch.  The first dkv_blocks workgroups, the longer chains, are the dK/dV pass.
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void bwd_both_split_bf16_kernel(BwdBf16 a, int dkv_blocks, int num_qtiles) {
+    if ((int)blockIdx.x < dkv_blocks) dkv_split<D, NW, true>(a, (int)blockIdx.x);
+    else dq_split<D, NW, 2, 1, 2>(a, num_qtiles, (int)blockIdx.x - dkv_blocks);
+}
+
 template <int D, int NW, int QW, int KB, int RING>
 static hipError_t launch_dq_split(const BwdBf16& a, hipStream_t s) {
     using Smem = SplitBandSmem<D, NW, QW, KB, RING>;
@@ -349,8 +391,7 @@ static hipError_t launch_dq_split(const BwdBf16& a, hipStream_t s) {
         return e;
     const int nq = (a.N + 32 * QW - 1) / (32 * QW), BH = a.B * a.H;
     ProfScope prof(kKernDq, s);
-    hipLaunchKernelGGL((bwd_dq_split_bf16_kernel<D, NW, QW, KB, RING>), dim3((unsigned)BH * nq), dim3(64 * NW), sizeof(Smem), s,
-                       a.Q, a.K, a.V, a.O, a.dO, a.c, a.L, a.Dv, a.dQ, a.dc_row, a.N, a.w, a.scale, nq, BH, a.H, a.H / a.Hkv);
+    hipLaunchKernelGGL((bwd_dq_split_bf16_kernel<D, NW, QW, KB, RING>), dim3((unsigned)BH * nq), dim3(64 * NW), sizeof(Smem), s, a, nq);
     return hipGetLastError();
 }
 
@@ -371,13 +412,29 @@ static hipError_t launch_dkv_split(const BwdBf16& a, hipStream_t s) {
         return e;
     ProfScope prof(kKernDkv, s);
     hipLaunchKernelGGL((bwd_dkv_split_bf16_kernel<D, NW>), dim3((unsigned)(a.B * a.Hkv) * ((a.N + 31) / 32)), dim3(64 * NW),
-                       sizeof(Smem), s, a.Q, a.K, a.V, a.dO, a.c, a.L, a.Dv, a.dK, a.dV, a.dc_col, a.N, a.w, a.scale,
-                       a.B * a.Hkv, a.H, a.H / a.Hkv);
+                       sizeof(Smem), s, a);
     return hipGetLastError();
 }
 
 hipError_t bwd_dkv_split_bf16(const BwdBf16& a, int d, hipStream_t s) {
     return d == 128 ? launch_dkv_split<128, 4>(a, s) : launch_dkv_split<64, 8>(a, s);
+}
+
+template <int D, int NW>
+static hipError_t launch_both_split(const BwdBf16& a, hipStream_t s) {
+    using DkvSmem = DkvSplitSmem<D, NW>;
+    using DqSmem = SplitBandSmem<D, NW, 2, 1, 2>;
+    constexpr size_t lds = sizeof(DkvSmem) > sizeof(DqSmem) ? sizeof(DkvSmem) : sizeof(DqSmem);
+    static DeviceOnce lds_allowed;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_both_split_bf16_kernel<D, NW>), lds, lds_allowed)) return e;
+    const int nq = (a.N + 63) / 64, nk = a.B * a.Hkv * ((a.N + 31) / 32);
+    ProfScope prof(kKernDkv, s);
+    hipLaunchKernelGGL((bwd_both_split_bf16_kernel<D, NW>), dim3((unsigned)(nk + a.B * a.H * nq)), dim3(64 * NW), lds, s, a, nk, nq);
+    return hipGetLastError();
+}
+
+hipError_t bwd_both_split_bf16(const BwdBf16& a, int d, hipStream_t s) {
+    return d == 128 ? launch_both_split<128, 4>(a, s) : launch_both_split<64, 8>(a, s);
 }
 
 }  // namespace gfwa

@@ -47,6 +47,7 @@ constexpr int kDkvSplitMaxGroup = 8;  // query heads per key/value head bwd_dkv_
 // The two passes for few or uneven tiles (bwd_split_bf16.hip).  The dQ pass also forms D_t, so it goes first.
 hipError_t bwd_dq_split_bf16(FwdSplit shape, const BwdBf16& a, int d, hipStream_t s);
 hipError_t bwd_dkv_split_bf16(const BwdBf16& a, int d, hipStream_t s);
+hipError_t bwd_both_split_bf16(const BwdBf16& a, int d, hipStream_t s);  // in one launch
 
 // Workspace layout of the backward: three fp32 vectors of B*H*N (each padded to 256 bytes): D, dc_col,
 // dc_row; gate_scan_workspace_bytes(B*H, N) (padded to 256) of segment sums for the gate-gradient scan; with `spill` (bf16, d = 128 only) backward_bf16_spill_bytes() more for the dS blocks.

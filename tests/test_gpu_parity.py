@@ -925,6 +925,24 @@ def launched(g, call):
     return {name for name, (_, count) in g.gfwa_profile_read().items() if count}
 
 
+@pytest.mark.parametrize("B,H,Hkv,N,d,w,one", [
+    # both passes in one launch: a workgroup each of a single row, either side of a 32-key and a 64-query block, eight query
+    # heads on a key/value head, exactly a workgroup for every CU, more than that with bands of half the sequence
+    (1, 1, 1, 1, 64, 4, True), (1, 2, 1, 33, 128, 7, True), (2, 3, 3, 65, 64, 64, True), (1, 8, 1, 97, 64, 1000, True),
+    (1, 8, 1, 161, 128, 33, True), (4, 16, 16, 70, 64, 35, True), (2, 6, 2, 449, 128, 225, True),
+    # and just not: one head more with a shorter band; a chain of more than 96 blocks at d = 128
+    (1, 65, 65, 70, 64, 34, False), (1, 8, 1, 417, 128, 500, False),
+])
+def test_backward_bf16_one_launch(g, oracle, ws_variant, B, H, Hkv, N, d, w, one):
+    note("one launch", ws_variant, B, H, Hkv, N, d, w)
+    wl = gi.custom("one", B, H, N, d, w, "bf16", alpha_mu=-1.5, index=23, backward=True, kv_heads=Hkv)
+    results = []
+    names = launched(g, lambda: results.extend(run_gqa(g, oracle, wl)))
+    assert ("bwd_dq" not in names) == one
+    got, ref = results
+    check_grads(got, ref, 1e-2, "one launch", tiny=N <= 33)
+
+
 @pytest.mark.parametrize("B,H,Hkv,N,w", [(1, 32, 8, 700, 1024), (1, 16, 8, 1577, 1416)])
 def test_large_workspace_does_not_change_the_route_where_dkv_is_split(g, B, H, Hkv, N, w):
     # the split dK/dV pass stores no dS blocks, so the dQ pass is the one that serves the minimum workspace (which
