@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkv_bf16_kernel(
 
     int bkv, kt;  // flat key/value head, whose G query heads are visited in turn; the sequence's end, which few queries see, last
     const int heads = total_tiles / num_ktiles;
-    tile_of_block(heads, num_ktiles, heads % 8 == 0 || w >= N, bkv, kt);
+    tile_of_block((int)blockIdx.x, heads, num_ktiles, heads % 8 == 0 || w >= N, bkv, kt);
     const int k0 = kt * BK;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(2 * kThreads, 1) void bwd_dkv8_bf16_kernel(
 
     int bkv, kt;  // flat key/value head, whose G query heads are visited in turn; the sequence's end, which few queries see, last
     const int heads = total_tiles / num_ktiles;
-    tile_of_block(heads, num_ktiles, heads % 8 == 0 || w >= N, bkv, kt);
+    tile_of_block((int)blockIdx.x, heads, num_ktiles, heads % 8 == 0 || w >= N, bkv, kt);
     const int k0 = kt * BK;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -633,7 +633,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_bf16_kernel(
     // w1024 1025 us so, 1005 one head after another; with bands of half the sequence, B4 H16 N4096 w2048, 700 and 708)
     const int heads = total_tiles / num_qtiles;
     int bh, qt;
-    tile_of_block(heads, num_qtiles, (heads % 8 == 0 && (D == 64 || 4L * w >= N)) || w >= N, bh, qt);
+    tile_of_block((int)blockIdx.x, heads, num_qtiles, (heads % 8 == 0 && (D == 64 || 4L * w >= N)) || w >= N, bh, qt);
     const int q0 = (num_qtiles - 1 - qt) * BR;  // longest bands first
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -807,7 +807,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_spill_bf16_kernel(
 
     const int heads = total_tiles / num_qtiles;
     int bh, qt;
-    tile_of_block(heads, num_qtiles, heads % 8 == 0 || w >= N, bh, qt);
+    tile_of_block((int)blockIdx.x, heads, num_qtiles, heads % 8 == 0 || w >= N, bh, qt);
     const int q0 = (num_qtiles - 1 - qt) * BR;  // longest bands first
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -189,20 +189,6 @@ __device__ __forceinline__ void dq_row(const float* Qh, const float* Kh, const f
         dc_rowh[t] = (float)rs;
     }
 }
-template <int D>
-__global__ __launch_bounds__(64 * kF32Waves) void bwd_dq_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ O,
-    const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
-    float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dc_row, int N,
-    int w, float scale, int H, int G) {
-    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int rows_per_head = (N + kF32Waves - 1) / kF32Waves;
-    const int bh = blockIdx.x / rows_per_head;
-    const int t = (blockIdx.x % rows_per_head) * kF32Waves + wv;
-    if (t >= N) return;
-    const size_t ho = (size_t)bh * N * D, kvo = (size_t)kv_head_of(bh, H, G) * N * D, rows = (size_t)bh * N;
-    dq_row<D, kRowLoads>(Q + ho, K + kvo, V + kvo, O + ho, dO + ho, c + rows, L + rows, Dv + rows, dQ + ho, dc_row + rows, t, w, scale, lane);
-}
 
 // ---- dK_i, dV_i (summed over the G query heads that read this key/value head, bh0 the first) and, per query head, the
 // column sum of dS.  rows_s: 64 places of LDS of the wave's own, for c, L, D of a step's queries.
@@ -252,22 +238,29 @@ __device__ __forceinline__ void dkv_row(const float* Q, const float* Kh, const f
         *reinterpret_cast<f32x4*>(dVh + at) = dv;
     }
 }
+// Both: the first workgroups take keys (the longer rows), the others queries.  D_t has been formed (rowdot_f32_kernel).  In two
+// launches, D formed by the first, neither pass of a small problem filled the chip (B1 H4 N300 d64: 35.5 us, 24.5 in one; B4 H8 N200
+// w100 35.0 / 22.8; 256 rows, w = 64 14.0 / 11.8).
 template <int D>
-__global__ __launch_bounds__(64 * kF32Waves) void bwd_dkv_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-    const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
-    const float* __restrict__ Dv, float* __restrict__ dK, float* __restrict__ dV,
-    float* __restrict__ dc_col, int N, int w, float scale, int H, int G) {
+__global__ __launch_bounds__(64 * kF32Waves) void bwd_f32_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO,
+    const float* __restrict__ c, const float* __restrict__ L, float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dK,
+    float* __restrict__ dV, float* __restrict__ dc_col, float* __restrict__ dc_row, int N, int w, float scale, int key_blocks, int H, int G) {
     __shared__ f32x4 rows_s[kF32Waves][64];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rows_per_head = (N + kF32Waves - 1) / kF32Waves;
-    const int bkv = blockIdx.x / rows_per_head;  // flat key/value head
-    const int i = (blockIdx.x % rows_per_head) * kF32Waves + wv;
-    if (i >= N) return;
-    const int Hkv = H / G;
-    const size_t kvo = (size_t)bkv * N * D;
-    dkv_row<D, kRowLoads>(Q, K + kvo, V + kvo, dO, c, L, Dv, dK + kvo, dV + kvo, dc_col, rows_s[wv], (bkv / Hkv) * H + (bkv % Hkv) * G, G, i, N, w,
-               scale, lane);
+    const bool keys = (int)blockIdx.x < key_blocks;
+    const int block = (int)blockIdx.x - (keys ? 0 : key_blocks), head = block / rows_per_head, row = block % rows_per_head * kF32Waves + wv;
+    if (row >= N) return;  // whole wave leaves; no workgroup barriers are used
+    if (keys) {
+        const int Hkv = H / G;
+        const size_t kvo = (size_t)head * N * D;
+        dkv_row<D, kRowLoads>(Q, K + kvo, V + kvo, dO, c, L, Dv, dK + kvo, dV + kvo, dc_col, rows_s[wv], (head / Hkv) * H + (head % Hkv) * G, G,
+                              row, N, w, scale, lane);
+    } else {
+        const size_t ho = (size_t)head * N * D, kvo = (size_t)kv_head_of(head, H, G) * N * D, rows = (size_t)head * N;
+        dq_row<D, kRowLoads>(Q + ho, K + kvo, V + kvo, nullptr, dO + ho, c + rows, L + rows, Dv + rows, dQ + ho, dc_row + rows, row, w, scale, lane);
+    }
 }
 
 // ==========================================================================================
@@ -512,7 +505,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) voi
     auto& sm = *reinterpret_cast<F32FwdSmem<D, S>*>(smem_raw);
     const int heads = total_tiles / num_qtiles;
     int bh, qt;
-    tile_of_block(heads, num_qtiles, f32_by_length(heads, N, w), bh, qt);
+    tile_of_block((int)blockIdx.x, heads, num_qtiles, f32_by_length(heads, N, w), bh, qt);
     const int q0 = (num_qtiles - 1 - qt) * BQ;  // longest bands first
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lq = lane & 31;
     const int qw0 = q0 + 32 * wv, t = qw0 + lq, tc = min(t, N - 1);
@@ -659,17 +652,13 @@ __device__ __forceinline__ int next3(int i) { return i == 2 ? 0 : i + 1; }
 // dQ and the row sums of dS (Alg. 3, query loop): the forward's layout.  S^T = K Q^T (wave 0 of a pair) and
 // dP^T = V dO^T (wave 1), then both take half of the block's keys: dS^T = P^T (dP^T - D), dQ^T += K^T dS^T.
 template <int D, int NP>
-__global__ __launch_bounds__(128 * NP, NP == 4 ? 1 : 2) void bwd_dq_f32_mfma_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-    const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
-    const float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dc_row, int N, int w, float scale,
-    int num_qtiles, int total_tiles, int H, int G) {
+__device__ __forceinline__ void dq_f32_mfma(int block, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dc_row, int N, int w, float scale, int num_qtiles, int total_tiles, int H, int G) {
     constexpr int KC = D / 16, DB = D / 32;
     extern __shared__ __align__(256) char smem_raw[];
     auto& sm = *reinterpret_cast<F32BwdSmem<D, NP>*>(smem_raw);
     const int heads = total_tiles / num_qtiles;
     int bh, qt;
-    tile_of_block(heads, num_qtiles, f32_by_length(heads, N, w), bh, qt);
+    tile_of_block(block, heads, num_qtiles, f32_by_length(heads, N, w), bh, qt);
     const int q0 = (num_qtiles - 1 - qt) * 32 * NP;  // longest bands first
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lq = lane & 31;
     const int qg = wv % NP;
@@ -843,17 +832,13 @@ __global__ __launch_bounds__(128 * NP, NP == 4 ? 1 : 2) void bwd_dq_f32_mfma_ker
 // workgroup owns 32 NP keys, a pair of waves 32 of them, a lane one key.  S = Q K^T (wave 0) and dP = dO V^T (wave 1) with
 // 32-query tiles of Q and dO from LDS, then dV^T += dO^T P (wave 0) and, a block later, dK^T += Q^T dS (wave 1).
 template <int D, int NP>
-__global__ __launch_bounds__(128 * NP, NP == 4 ? 1 : 2) void bwd_dkv_f32_mfma_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-    const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
-    const float* __restrict__ Dv, float* __restrict__ dK, float* __restrict__ dV, float* __restrict__ dc_col,
-    int N, int w, float scale, int num_ktiles, int total_tiles, int H, int G) {
+__device__ __forceinline__ void dkv_f32_mfma(int block, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dK, float* __restrict__ dV, float* __restrict__ dc_col, int N, int w, float scale, int num_ktiles, int total_tiles, int H, int G) {
     constexpr int KC = D / 16, DB = D / 32;
     extern __shared__ __align__(256) char smem_raw[];
     auto& sm = *reinterpret_cast<F32BwdSmem<D, NP>*>(smem_raw);
     const int heads = total_tiles / num_ktiles;
     int bkv, kt;  // flat key/value head; the sequence's end, which few queries see, last
-    tile_of_block(heads, num_ktiles, f32_by_length(heads, N, w), bkv, kt);
+    tile_of_block(block, heads, num_ktiles, f32_by_length(heads, N, w), bkv, kt);
     const int k0 = kt * 32 * NP;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lk = lane & 31;
     const int kg = wv % NP;
@@ -1049,6 +1034,21 @@ __global__ __launch_bounds__(128 * NP, NP == 4 ? 1 : 2) void bwd_dkv_f32_mfma_ke
     else run(std::integral_constant<int, 1>{});
 }
 
+// Both passes in one launch, the first dkv_tiles workgroups the dK/dV pass, whose chains are the longer ones with grouped heads:
+// the dQ pass fills the CUs that those leave idle, at the end of a large problem or beside all of a small one.  Two launches /
+// one, whole backward: B1 H8 N1000 d128 w500 149 / 87 us, B1 H2 N2000 d64 causal 240 / 139, B1 H4 N4000 d128 w1000 250 / 155,
+// B2 H8/2 N515 d64 181 / 150, B2 H16 N1000 d128 causal 236 / 176, B2 H16 N4096 d128 w1024 1108 / 1065.
+template <int D, int NP>
+__global__ __launch_bounds__(128 * NP, NP == 4 ? 1 : 2) void bwd_f32_mfma_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO,
+    const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dK,
+    float* __restrict__ dV, float* __restrict__ dc_col, float* __restrict__ dc_row, int N, int w, float scale, int tiles_per_head, int dkv_tiles,
+    int dq_tiles, int H, int G) {
+    const int b = (int)blockIdx.x;
+    if (b < dkv_tiles) dkv_f32_mfma<D, NP>(b, Q, K, V, dO, c, L, Dv, dK, dV, dc_col, N, w, scale, tiles_per_head, dkv_tiles, H, G);
+    else dq_f32_mfma<D, NP>(b - dkv_tiles, Q, K, V, dO, c, L, Dv, dQ, dc_row, N, w, scale, tiles_per_head, dq_tiles, H, G);
+}
+
 // ---- D_t = <O_t, dO_t>
 template <int D>
 __global__ __launch_bounds__(256) void rowdot_f32_kernel(const float* __restrict__ O, const float* __restrict__ dO,
@@ -1154,18 +1154,20 @@ hipError_t forward_f32(const float* Q, const float* K, const float* V, const flo
 }
 
 template <int D>
+static void launch_rowdot_f32(const float* O, const float* dO, float* Dv, long rows, hipStream_t s) {
+    constexpr int kRows = 4 * RowStep<D, 1>::kRows;
+    hipLaunchKernelGGL((rowdot_f32_kernel<D>), dim3((unsigned)((rows + kRows - 1) / kRows)), dim3(256), 0, s, O, dO, Dv, rows);
+}
+
+template <int D>
 static hipError_t launch_bwd_f32_rows(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,
                                       const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, int B,
                                       int H, int Hkv, int N, int w, float scale, hipStream_t s) {
     const int per_head = (N + kF32Waves - 1) / kF32Waves;
-    {   // forms D as well, so it goes first
-        ProfScope prof(kKernDq, s);
-        hipLaunchKernelGGL((bwd_dq_f32_kernel<D>), dim3(B * H * per_head), dim3(64 * kF32Waves), 0, s, Q, K, V, O, dO, c, L, Dv,
-                           dQ, dc_row, N, w, scale, H, H / Hkv);
-    }
-    ProfScope prof(kKernDkv, s);
-    hipLaunchKernelGGL((bwd_dkv_f32_kernel<D>), dim3(B * Hkv * per_head), dim3(64 * kF32Waves), 0, s, Q, K, V, dO, c, L, Dv, dK,
-                       dV, dc_col, N, w, scale, H, H / Hkv);
+    ProfScope prof(kKernDkv, s);  // one record for the two launches
+    launch_rowdot_f32<D>(O, dO, Dv, (long)B * H * N, s);
+    hipLaunchKernelGGL((bwd_f32_kernel<D>), dim3(B * (Hkv + H) * per_head), dim3(64 * kF32Waves), 0, s, Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col,
+                       dc_row, N, w, scale, B * Hkv * per_head, H, H / Hkv);
     return hipGetLastError();
 }
 
@@ -1173,24 +1175,17 @@ template <int D, int NP>
 static hipError_t launch_bwd_f32_mfma(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,
                                       const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, int B,
                                       int H, int Hkv, int N, int w, float scale, hipStream_t s) {
-    static DeviceOnce dkv_lds, dq_lds;
+    static DeviceOnce lds_allowed;
     constexpr size_t lds = sizeof(F32BwdSmem<D, NP>);
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dkv_f32_mfma_kernel<D, NP>), lds, dkv_lds)) return e;
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dq_f32_mfma_kernel<D, NP>), lds, dq_lds)) return e;
-    const long rows = (long)B * H * N;
-    const int nt = (N + 32 * NP - 1) / (32 * NP), dot_rows = 4 * RowStep<D, 1>::kRows;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_f32_mfma_kernel<D, NP>), lds, lds_allowed)) return e;
+    const int nt = (N + 32 * NP - 1) / (32 * NP);
     {
         ProfScope prof(kKernRowDot, s);
-        hipLaunchKernelGGL((rowdot_f32_kernel<D>), dim3((unsigned)((rows + dot_rows - 1) / dot_rows)), dim3(256), 0, s, O, dO, Dv, rows);
+        launch_rowdot_f32<D>(O, dO, Dv, (long)B * H * N, s);
     }
-    {
-        ProfScope prof(kKernDkv, s);
-        hipLaunchKernelGGL((bwd_dkv_f32_mfma_kernel<D, NP>), dim3(B * Hkv * nt), dim3(128 * NP), lds, s, Q, K, V, dO, c, L, Dv, dK,
-                           dV, dc_col, N, w, scale, nt, B * Hkv * nt, H, H / Hkv);
-    }
-    ProfScope prof(kKernDq, s);
-    hipLaunchKernelGGL((bwd_dq_f32_mfma_kernel<D, NP>), dim3(B * H * nt), dim3(128 * NP), lds, s, Q, K, V, dO, c, L, Dv, dQ,
-                       dc_row, N, w, scale, nt, B * H * nt, H, H / Hkv);
+    ProfScope prof(kKernDkv, s);
+    hipLaunchKernelGGL((bwd_f32_mfma_kernel<D, NP>), dim3(B * (Hkv + H) * nt), dim3(128 * NP), lds, s, Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col,
+                       dc_row, N, w, scale, nt, B * Hkv * nt, B * H * nt, H, H / Hkv);
     return hipGetLastError();
 }
 

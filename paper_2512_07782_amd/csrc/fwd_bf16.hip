@@ -88,7 +88,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, FwdTile<D>::kResident) void fwd_bf1
     // after tile, 35.5 in contiguous ranges; B3 H11 N4096 causal 105 and 107 us.
     const int heads = total / num_qtiles;
     int bh, qt;
-    tile_of_block(heads, num_qtiles, heads % 8 == 0 || w >= N, bh, qt);
+    tile_of_block((int)blockIdx.x, heads, num_qtiles, heads % 8 == 0 || w >= N, bh, qt);
     const int q0 = (num_qtiles - 1 - qt) * 128;
     const size_t head_off = (size_t)bh * N * D, kv_off = (size_t)kv_head_of(bh, H, G) * N * D;
     const char* Kh = reinterpret_cast<const char*>(K + kv_off);

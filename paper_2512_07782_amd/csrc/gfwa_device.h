@@ -173,13 +173,12 @@ __device__ __forceinline__ int xcd_remap(int pid, int total) {
     return x * base + (x < rem ? x : rem) + idx;
 }
 
-// Order in which the workgroups of a launch take the tiles (heads x tiles of a head).  by_length: tile after tile over all
+// Order in which the workgroups b of a launch take the tiles (heads x tiles of a head).  by_length: tile after tile over all
 // heads, so that a launch that numbers its tiles from the longest band to the shortest ends with short ones; the heads
 // of a group, which share keys, stay on one XCD if the heads divide by the XCDs.  Otherwise one head after another, every
 // XCD a contiguous range, which keeps an XCD to few heads.
-__device__ __forceinline__ void tile_of_block(int heads, int tiles, bool by_length, int& head, int& tile) {
+__device__ __forceinline__ void tile_of_block(int b, int heads, int tiles, bool by_length, int& head, int& tile) {
     constexpr int kXcd = 8;
-    const int b = (int)blockIdx.x;
     if (by_length) {
         head = heads % kXcd == 0 ? (b % kXcd) * (heads / kXcd) + b % heads / kXcd : b % heads;
         tile = b / heads;

@@ -56,8 +56,8 @@ LIB = {
     "fwd_split_bf16_kernel": "forward", "bwd_dkv_split_bf16_kernel": "bwd_dkv", "bwd_dq_split_bf16_kernel": "bwd_dq",
     # fp32 storage
     "fwd_f32_mfma_kernel": "forward", "fwd_f32_kernel": "forward", "rowdot_f32_kernel": "bwd_rowdot",
-    "bwd_dkv_f32_mfma_kernel": "bwd_dkv", "bwd_dkv_f32_kernel": "bwd_dkv",
-    "bwd_dq_f32_mfma_kernel": "bwd_dq", "bwd_dq_f32_kernel": "bwd_dq",
+    "bwd_both_split_bf16_kernel": "bwd_dkv",  # one launch for both passes here and below
+    "bwd_f32_mfma_kernel": "bwd_dkv", "bwd_f32_kernel": "bwd_dkv",
 }
 # the long_bwd workload of bench.py
 B, H, N, D, W = 1, 32, 16384, 128, 1024
