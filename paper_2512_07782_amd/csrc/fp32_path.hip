@@ -1159,6 +1159,15 @@ static void launch_rowdot_f32(const float* O, const float* dO, float* Dv, long r
     hipLaunchKernelGGL((rowdot_f32_kernel<D>), dim3((unsigned)((rows + kRows - 1) / kRows)), dim3(256), 0, s, O, dO, Dv, rows);
 }
 
+// One launch(key_blocks, blocks) for both passes of the backward, or one for each where a grid with all blocks would hold the 2^32
+// work items at which a launch is refused (MHA, 2^23 sequences of up to four tokens).
+template <class Launch>
+static void launch_passes(long key_blocks, long query_blocks, int threads, Launch launch) {
+    if ((key_blocks + query_blocks) * threads < 1L << 32) return launch((int)key_blocks, (int)(key_blocks + query_blocks));
+    launch((int)key_blocks, (int)key_blocks);
+    launch(0, (int)query_blocks);
+}
+
 template <int D>
 static hipError_t launch_bwd_f32_rows(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,
                                       const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, int B,
@@ -1166,8 +1175,10 @@ static hipError_t launch_bwd_f32_rows(const float* Q, const float* K, const floa
     const int per_head = (N + kF32Waves - 1) / kF32Waves;
     ProfScope prof(kKernDkv, s);  // one record for the two launches
     launch_rowdot_f32<D>(O, dO, Dv, (long)B * H * N, s);
-    hipLaunchKernelGGL((bwd_f32_kernel<D>), dim3(B * (Hkv + H) * per_head), dim3(64 * kF32Waves), 0, s, Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col,
-                       dc_row, N, w, scale, B * Hkv * per_head, H, H / Hkv);
+    launch_passes((long)B * Hkv * per_head, (long)B * H * per_head, 64 * kF32Waves, [&](int key_blocks, int blocks) {
+        hipLaunchKernelGGL((bwd_f32_kernel<D>), dim3(blocks), dim3(64 * kF32Waves), 0, s, Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, N, w,
+                           scale, key_blocks, H, H / Hkv);
+    });
     return hipGetLastError();
 }
 
@@ -1184,8 +1195,10 @@ static hipError_t launch_bwd_f32_mfma(const float* Q, const float* K, const floa
         launch_rowdot_f32<D>(O, dO, Dv, (long)B * H * N, s);
     }
     ProfScope prof(kKernDkv, s);
-    hipLaunchKernelGGL((bwd_f32_mfma_kernel<D, NP>), dim3(B * (Hkv + H) * nt), dim3(128 * NP), lds, s, Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col,
-                       dc_row, N, w, scale, nt, B * Hkv * nt, B * H * nt, H, H / Hkv);
+    launch_passes((long)B * Hkv * nt, (long)B * H * nt, 128 * NP, [&](int dkv_tiles, int blocks) {
+        hipLaunchKernelGGL((bwd_f32_mfma_kernel<D, NP>), dim3(blocks), dim3(128 * NP), lds, s, Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row,
+                           N, w, scale, nt, dkv_tiles, blocks - dkv_tiles, H, H / Hkv);
+    });
     return hipGetLastError();
 }
 

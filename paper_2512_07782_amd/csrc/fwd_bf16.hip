@@ -339,6 +339,16 @@ static FwdSplit fwd_split_shape(int BH, int N, int d, int w) {
 
 hipError_t forward_bf16(const void* Q, const void* K, const void* V, const float* c, void* O, float* L,
                         int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s) {
+    // A grid of 2^32 work items is refused; the densest here has 256 for 64 queries.  Half of the key/value heads at a time
+    // then, or of the query heads of the only one.
+    if ((long)B * H * ((N + 63) / 64) >= 1L << 24) {
+        const int kv = B * Hkv, G = H / Hkv, kv0 = kv > 1 ? kv / 2 : 1, g0 = kv > 1 ? G : G / 2;
+        const size_t rows = (size_t)N * kv0 * g0, keys = kv > 1 ? (size_t)N * kv0 : 0;
+        auto from = [&](const void* p, size_t row) { return (const char*)p + row * d * sizeof(bf16_t); };
+        if (hipError_t e = forward_bf16(Q, K, V, c, O, L, kv0, g0, 1, N, d, w, scale, s)) return e;
+        return forward_bf16(from(Q, rows), from(K, keys), from(V, keys), c + rows, (char*)O + rows * d * sizeof(bf16_t), L + rows,
+                            kv > 1 ? kv - kv0 : 1, kv > 1 ? G : G - g0, 1, N, d, w, scale, s);
+    }
     if (const FwdSplit shape = fwd_split_shape(B * H, N, d, w))
         return forward_split_bf16(shape, Q, K, V, c, O, L, B, H, Hkv, N, d, w, scale, s);
     if (d == 64) return launch_fwd<64>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);

@@ -965,7 +965,7 @@ def test_large_workspace_does_not_change_the_route_where_dkv_is_split(g, B, H, H
 
 
 @pytest.mark.parametrize("B,H,Hkv,N,d,w,groups", [
-    # the persistent forward and the backward kernels of whole 128-row tiles, where they have a ragged end: last tiles of 3 rows
+    # the forward and the backward kernels of whole 128-row tiles, where they have a ragged end: last tiles of 3 rows
     # to one row, odd windows, windows past the sequence, grouped heads; sampled heads
     (1, 20, 20, 4099, 128, 301, [0, 19]), (1, 48, 12, 2049, 128, 333, [0, 11]), (2, 100, 100, 513, 128, 1000, [0, 199]),
     (1, 25, 25, 4099, 64, 301, [0, 24]), (1, 40, 10, 3001, 64, 333, [0, 9]), (1, 250, 250, 641, 64, 5000, [0, 249]),
@@ -1131,6 +1131,46 @@ def _random_shapes(n, seed):
         w = int(rng.choice([1, rng.integers(2, 70), rng.integers(70, 600), N, N + 17, 4 * N + 1]))
         out.append((int(rng.integers(1, 3)), Hkv * G, Hkv, N, d, max(1, w)))
     return out
+
+
+# more workgroups than one launch takes (2^32 work items): the forward goes in several, by key/value heads or by the query
+# heads of the only one, and the fp32 backward in one launch for each pass
+@pytest.mark.parametrize("B,H,Hkv", [(3, (1 << 24) // 3, (1 << 24) // 3), (4, 1 << 22, 1 << 22), (2, 1 << 23, 1 << 21), (1, 1 << 24, 1)])
+def test_forward_bf16_at_the_most_heads(g, B, H, Hkv):
+    note("most heads", B, H, Hkv)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    normal = lambda *shape, dtype=torch.bfloat16: torch.randn(shape, generator=gen, device="cuda", dtype=dtype)
+    Q, K, V = normal(B, H, 1, 64), normal(B, Hkv, 1, 64), normal(B, Hkv, 1, 64)
+    c = normal(B, H, 1, dtype=torch.float32)
+    O, L = (g.gfwa_forward if H == Hkv else g.gfwa_forward_gqa)(Q, K, V, c, 4, 0.125)
+    G = H // Hkv
+    for lo in range(0, H, 1 << 20):
+        part = torch.arange(lo, min(H, lo + (1 << 20)), device="cuda")
+        assert (O[:, part] == V[:, part // G]).all()  # one key: its value, and its score
+        # 64 additions of 2^-24 of sums that stay below 64, times 0.125
+        score = 0.125 * (Q[:, part].double() * K[:, part // G].double()).sum(-1)
+        assert (L[:, part].double() - score).abs().max() <= 3e-5
+
+
+def test_backward_f32_with_more_blocks_than_one_launch_takes(g, oracle):
+    B, H, N, d, scale = 2, 1 << 22, 2, 64, 0.125
+    note("most blocks", B, H, N, d)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    normal = lambda *shape: torch.randn(shape, generator=gen, device="cuda")
+    Q, K, V, dO = (normal(B, H, N, d) for _ in range(4))
+    alpha = normal(B, H, N).exp_()
+    c = g.gfwa_gate_prefix(alpha)
+    O, L = g.gfwa_forward(Q, K, V, c, N, scale)
+    dQ, dK, dV, dalpha = g.gfwa_backward(Q, K, V, O, dO, c, L, N, scale)
+    torch.cuda.synchronize()
+    for bh in [(0, 0), (0, H // 2), (0, H - 1), (1, 0), (1, 1), (1, H - 1)]:
+        one = lambda x: host(x[bh]).astype(np.float32)[None, None]
+        ref = oracle.backward(one(Q), one(K), one(V), one(alpha), one(dO), N, scale)
+        for name, got in (("dQ", dQ), ("dK", dK), ("dV", dV), ("dalpha", dalpha)):
+            assert np.abs(host(got[bh]) - ref[name][0, 0]).max() <= 1e-5 * max(1.0, np.abs(ref[name]).max()), (bh, name)
+    for got in (dQ, dK, dV, dalpha):
+        assert torch.isfinite(got).all()
+
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
