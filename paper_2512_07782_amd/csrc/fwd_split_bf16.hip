@@ -1,13 +1,14 @@
 // GatedFWA fused forward for bf16 storage, for problems with too few query tiles to fill the chip (paper Alg. 2).
 //
-// The persistent kernel of fwd_bf16.hip gives 128 queries to a workgroup of 4 waves and walks their band one key
+// The kernel of fwd_bf16.hip gives 128 queries to a workgroup of 4 waves and walks their band one key
 // tile after another: with few query tiles, or tiles of very different bands, most SIMDs hold one wave or none and the
 // launch lasts as long as its longest chain of tiles.  Here a workgroup of NW waves owns QW blocks of 32 queries, and
 // KW = NW / QW groups of QW waves take every KW-th key tile (KB blocks of 32 keys) of the band each; the partial
 // (reference exponent, sum, output) of the groups are merged through LDS at the end.  The band then takes 1 / KW
 // of the steps, at the price of K and V travelling to LDS once per 32 QW queries and of the merge (about 1.5 us).
 // What bounds it at these sizes is latency: launch, first loads, the first pass through the code (instruction
-// cache), then about 0.8 us per step.  Three shapes (which one: fwd_split_shape in fwd_bf16.hip), forward alone, us:
+// cache), then about 0.8 us per step.  Three shapes (which one: fwd_split_shape in fwd_bf16.hip), forward alone, us,
+// and beside them a persistent kernel of 128-query tiles, the predecessor of the one in fwd_bf16.hip:
 //                                       persistent   wide (8 waves, 4x2)   mid (4 waves, 2x2)   narrow (4 waves, 1x4)
 //   B1 H32/8 N700  d128 w1024              17.5            16.1                 14.4                 16.8
 //   B1 H4    N1000 d128 w333               16.1            14.2                 10.4                  7.5
@@ -17,8 +18,7 @@
 //   B1 H4    N16384 d128 w1024             42.2            52.6                 52.0                 66.9
 //
 // Products, layouts, gate and softmax are those of fwd_bf16.hip (a lane owns one query, S^T = K Q^T starts from the
-// gate, O^T += V^T P^T takes the S accumulators as its operand, deferred running maximum), without the
-// software pipeline inside the wave.  Steps outside a wave's own band only load, so that the loop that computes has no
+// gate, O^T += V^T P^T takes the S accumulators as its operand, deferred running maximum).  Steps outside a wave's own band only load, so that the loop that computes has no
 // branch around the accumulators (with one the compiler copies all of them twice per step).
 #include "gfwa_device.h"
 #include "gfwa_internal.h"

@@ -233,7 +233,8 @@ def sq_counters(a_dir: str, b_dir: str, kt_dir: str) -> str:
         "matrix pipe of its SIMD for 32 cycles, so 'matrix pipe busy' = 32 x SQ_INSTS_MFMA / (4 x SQ_WAVE_CYCLES / 2) is the",
         "share of a SIMD's cycles in which its matrix pipe works, whatever the clock was, and 'implied clock' =",
         "4 x SQ_WAVE_CYCLES / 2048 / duration is the core clock the kernel ran at (durations: kernel-trace averages of the",
-        "same command; the part lowers its clock under load, see the probe_* rows of the kernel trace).",
+        "same command; the part lowers its clock under load, see the probe_* rows of the kernel trace).  The forward keeps three",
+        "waves on a SIMD: its two busy shares times 1.5 and its clock times 2 / 3, as in the last three rows.",
         "",
         f"{'':38s}" + "".join(f"{c[1]:>14s}" for c in cols),
     ]
@@ -258,6 +259,11 @@ def sq_counters(a_dir: str, b_dir: str, kt_dir: str) -> str:
     row("wave time waiting to issue", lambda t, d: t["SQ_WAIT_INST_ANY"] / t["SQ_WAVE_CYCLES"])
     row("wave time waiting for LDS issue", lambda t, d: t["SQ_WAIT_INST_LDS"] / t["SQ_WAVE_CYCLES"])
     row("LDS bank conflict / LDS active", lambda t, d: t["SQ_LDS_BANK_CONFLICT"] / max(t["SQ_LDS_IDX_ACTIVE"], 1.0))
+    o.append("")
+    waves = lambda t: 1.5 if t is tab["fwd_bf16_kernel<128>"] else 1.0
+    row("with its waves: matrix pipe busy", lambda t, d: waves(t) * 16.0 * t["SQ_INSTS_MFMA"] / t["SQ_WAVE_CYCLES"])
+    row("                clock, GHz", lambda t, d: 4.0 * t["SQ_WAVE_CYCLES"] / 2048.0 / d / 1e9 / waves(t))
+    row("                LDS address pipe busy", lambda t, d: waves(t) * t["SQ_LDS_IDX_ACTIVE"] / (4.0 * t["SQ_WAVE_CYCLES"] / 8.0))
     return "\n".join(o) + "\n"
 
 

@@ -54,7 +54,7 @@ SHAPES = [  # B, H, Hkv, N, d, w: ragged in every tile size the kernels use
     (5, 60, 60, 97, 128, 33), (2, 150, 75, 65, 64, 50),
     # bf16: the band split over groups of waves, 64 and 128 queries per workgroup
     (1, 32, 8, 701, 128, 1024), (1, 8, 8, 5003, 128, 2999),
-    # bf16: the persistent forward and the dQ kernel of whole 128-query tiles
+    # bf16: the forward and the dQ kernel of whole 128-query tiles
     (1, 20, 20, 4099, 128, 301), (1, 48, 12, 2049, 128, 333), (1, 25, 25, 4099, 64, 301),
 ]
 # The shapes with a row-dot launch in their backward.  bf16: those that take the whole-tile dQ kernel; with the large workspace
