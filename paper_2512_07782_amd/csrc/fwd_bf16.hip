@@ -289,9 +289,10 @@ template <int D>
 static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const float* c, void* O,
                              float* L, int B, int H, int Hkv, int N, int w, float scale, hipStream_t s) {
     const int nq = (N + 127) / 128, total = B * H * nq, cus = device_cu_count();
-    // Three workgroups on a CU leave a short second round of one a CU where there are just more than fit at once: two on a
-    // CU then, by asking for more LDS (H28 N4096 w256: 43.0 -> 39.5 us, H32 41.0 -> 39.7; H24 and H40 lose 6 us by it).
-    const size_t lds = D == 128 && total > 3 * cus && total <= 4 * cus ? (size_t)56 << 10 : sizeof(FwdSmem<D>);
+    // Three workgroups on a CU leave a second round of less than one a CU where up to four a CU are to be done: two on a CU
+    // then, by asking for more LDS, if two rounds of that are nearly full and most bands equal (H28 N4096 w256: 43.0 -> 39.5 us, H30
+    // w1000 86.7 -> 78.5, w1800 127.6 -> 117.4; H26 w1800, at 3.25 a CU, would be 92.4 -> 105.2, H32 causal 129.7 -> 140.4).
+    const size_t lds = D == 128 && 2 * total >= 7 * cus && total <= 4 * cus && 9L * w <= 4L * N ? (size_t)56 << 10 : sizeof(FwdSmem<D>);
     static_assert(sizeof(FwdSmem<D>) <= (56 << 10), "two workgroups of 56 KB fit a CU, three do not");
     ProfScope prof(kKernForward, s);
     hipLaunchKernelGGL((fwd_bf16_kernel<D>), dim3(total), dim3(64 * kFwdWaves), lds, s, (const bf16_t*)Q,
@@ -308,7 +309,7 @@ static double query_tile_steps(int BH, int N, int w, long& longest) {
     return (double)BH * (double)(ramp * (ramp + 1) + 2 * ramp + (nq - ramp) * longest);
 }
 // The share of `slots` resident workgroups' time that holds work when the tiles are taken in rounds:
-// (steps of all tiles) / (slots x rounds x steps of the longest tile).  (The dQ pass asks.)
+// (steps of all tiles) / (slots x rounds x steps of the longest tile).  (The dQ pass asks too.)
 double query_tile_fill(int BH, int N, int w, long slots) {
     long longest;
     const double steps = query_tile_steps(BH, N, w, longest);
@@ -320,8 +321,12 @@ double query_tile_fill(int BH, int N, int w, long slots) {
 // do (`ratio`), the split one below.
 // d = 64, 1.3: over 37 shapes (N 100 .. 16384) the best split shape is 1.04 to 1.8 times as fast below (one exception,
 // 0.98), and above between 1.27 times as slow and equal (one exception, H24 N2100 w300: 12.5 against 14.5 us).
-// d = 128, 1.0, or 1.5 for bands that 128 queries share out well: over 29 shapes 1.03 to 2.2 times as fast below, 1.45 times
-// as slow to equal above (H20 N4096 causal, at 1.33: 102 against 111 us; B20 H4 N600, at 1.04: 22.1 against 18.5).
+// d = 128, 1.0: over 29 shapes 1.03 to 2.2 times as fast below, 1.45 times as slow to equal above (B20 H4 N600, at 1.04: 22.1
+// against 18.5).  For bands that 128 queries share out well 1.5, for longer ones 1.95 (H20 N4096 causal, at 1.33: 102 against 111
+// us; H13 N5003 w2500, at 1.53: 92 against 98; H20/5 N5003 w4000, at 1.91: 147 against 153; H32 N4096 causal, at 2.12: 145
+// against 130), or less where the tiles fill two places on every CU: the split kernel, one on a CU, takes whole rounds (H7 N8192
+// w3000, filled to 0.71: 107 against 92, H10 N5003 w2000, 0.63: 72 against 64; H12 N4096 w1800, 0.58: 58 against 59, H9 N5003
+// w3000, 0.50: 69 against 89).
 // Sequences shorter than a step's tile are the split kernel's, and there 64 queries are the better than 32 (d = 64, 512 x 4
 // heads of 50: 13.7, 28.0 us).
 // Inside the split kernel: one 32-query block per workgroup while that gives few workgroups (at d = 128 its
@@ -331,8 +336,9 @@ static FwdSplit fwd_split_shape(int BH, int N, int d, int w) {
     const long cus = device_cu_count(), band = w < N ? w : N;
     long longest;
     const double ratio = query_tile_steps(BH, N, w, longest) / ((double)cus * (double)longest);
-    if (N >= (d == 64 ? FwdTile<64>::kKeys : FwdTile<128>::kKeys) && ratio >= (d == 64 ? 1.3 : band > 1500 ? 1.5 : 1.0))
-        return kFwdSplitNone;
+    const bool filled = ratio >= (d == 64 ? 1.3 : band > 2048 ? 1.95 : band > 1500 ? 1.5 : 1.0) ||
+                        (d == 128 && band > 1500 && query_tile_fill(BH, N, w, 2 * cus) >= 0.61);
+    if (N >= (d == 64 ? FwdTile<64>::kKeys : FwdTile<128>::kKeys) && filled) return kFwdSplitNone;
     if ((long)BH * ((N + 31) / 32) <= 5 * cus / 2 && (d == 64 || band <= 1024)) return kFwdSplitNarrow;
     return band > (d == 64 ? 2560 : 1500) ? kFwdSplitWide : kFwdSplitMid;
 }
