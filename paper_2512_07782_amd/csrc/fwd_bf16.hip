@@ -1,8 +1,8 @@
 // GatedFWA fused forward for bf16 storage on gfx950 (paper Alg. 2, re-designed for CDNA4), and the choice of the kernel
 // that serves a problem.
 //
-// A workgroup of 4 waves owns 128 consecutive queries of one head, a wave 32 of them.  Key/value tiles of 64 (d = 64) or
-// 32 keys travel global -> LDS by direct loads (no staging registers, no LDS stores) into two ring slots each; only the
+// A workgroup of 4 waves owns 128 consecutive queries of one head, a wave 32 of them.  Key/value tiles of 64 (d = 64, or few
+// workgroups) or 32 keys travel global -> LDS by direct loads (no staging registers, no LDS stores) into two ring slots each; only the
 // tiles that intersect the band [q0-w+1, q0+127] are visited, from the diagonal backwards, one per step.  A wave computes
 // only in the steps that hold blocks of its own band (in the others it just issues its share of the loads) and masks only
 // where the band edge or the diagonal cuts.
@@ -19,7 +19,7 @@
 // issuing nothing else).  That is approached by many waves in different phases, not by a pipeline inside one wave: four
 // (three) workgroups on a CU, 128 (168) registers, nothing carried from step to step but O, m and l.  A step is
 //   d = 64    S(upper 32 keys)  ->  S(lower) beside exp(upper)  ->  O += V P(upper) beside exp(lower)  ->  O += V P(lower)
-//   d = 128   S  ->  exp  ->  O += V P
+//   d = 128   S  ->  exp  ->  O += V P; with few workgroups on a CU the step of d = 64, two on a CU with 188 registers
 // A step takes 420 cycles per block and SIMD at d = 64.  The kernel this one took over from, persistent, two (three) waves
 // on a SIMD and three blocks in flight inside each, took 600: the branches for the mask and for the reference exponent cut
 // its iterations into pieces shorter than an MFMA chain's latency.  Without effect here (1 % and less): tile loads earlier
@@ -33,6 +33,8 @@
 //            B4 H16/4  N4096 w512   62.3 / 48.3     B2 H16 N8000 w200   45.0 / 36.3   B1 H32   N16384 w1024  196 / 163
 //   d = 128  B1 H32 N16384 w1024    315 / 294       B4 H16 N8192 w1024  309 / 283     B16 H16  N1000 w200   65.2 / 55.1
 //            B1 H32/8 N8192 w4096   435 / 355       B2 H32 N2048 causal 101 / 73
+//   and with two blocks a step
+//            B1 H4  N16384 w4096    124 / 127       B1 H14 N7817  w1160  86 / 85      B1 H38  N1287 w1057 37.2 / 37.2
 //
 // The gate bias rides in the MFMA accumulator: S is initialised with g_i = (c_i - c_base) / scale
 // straight from LDS before the K Q^T chain, so S = q.k + g_i and the probability is one fused
@@ -58,28 +60,26 @@ namespace gfwa {
 
 constexpr int kFwdWaves = 4;
 template <int D>
-struct FwdTile {
-    static constexpr int kBlocks = D == 64 ? 2 : 1, kKeys = 32 * kBlocks;  // of a step
-    static constexpr int kResident = D == 64 ? 4 : 3;                      // workgroups on a CU
-    static constexpr int kRowBytes = D * 2, kTileBytes = kKeys * kRowBytes;
-};
-template <int D>
+constexpr int kFwdBlocks = D == 64 ? 2 : 1;  // blocks of 32 keys in a step where nothing else is said
+template <int D, int NB>
 struct FwdSmem {
-    alignas(256) char k[2][FwdTile<D>::kTileBytes];
-    alignas(256) char v[2][FwdTile<D>::kTileBytes];
-    alignas(16) float g[2][FwdTile<D>::kKeys];  // (c - c_base) / scale of the tile's keys
+    static constexpr int kKeys = 32 * NB, kTileBytes = kKeys * D * 2;
+    alignas(256) char k[2][kTileBytes];
+    alignas(256) char v[2][kTileBytes];
+    alignas(16) float g[2][kKeys];  // (c - c_base) / scale of the tile's keys
 };
 
-template <int D>
-__global__ __launch_bounds__(64 * kFwdWaves, FwdTile<D>::kResident) void fwd_bf16_kernel(
+template <int D, int NB>
+__device__ __forceinline__ void fwd_tile(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w, float scale_log2,
     int num_qtiles, int total, int H, int G) {
-    constexpr int KC = D / 16, DB = D / 32, NV = 2 * DB, NB = FwdTile<D>::kBlocks, kKeys = FwdTile<D>::kKeys;
-    constexpr int kRowBytes = FwdTile<D>::kRowBytes, kTileBytes = FwdTile<D>::kTileBytes;
+    constexpr int KC = D / 16, DB = D / 32, NV = 2 * DB;
+    using Smem = FwdSmem<D, NB>;
+    constexpr int kKeys = Smem::kKeys, kRowBytes = D * 2, kTileBytes = Smem::kTileBytes;
     constexpr int kChunks = kRowBytes / 16, kPieceRows = 1024 / kRowBytes, kPieces = kKeys / kFwdWaves / kPieceRows;  // per wave and matrix
     extern __shared__ __align__(256) char smem_raw[];
-    auto& sm = *reinterpret_cast<FwdSmem<D>*>(smem_raw);
+    auto& sm = *reinterpret_cast<Smem*>(smem_raw);
 
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = lane >> 5, lq = lane & 31;
@@ -137,12 +137,12 @@ __global__ __launch_bounds__(64 * kFwdWaves, FwdTile<D>::kResident) void fwd_bf1
     unsigned ka, va, ga;  // LDS addresses of the lane's first fragments in the current slot
     {
         const unsigned base = (unsigned)(uintptr_t)smem_raw;  // 0: the kernel has no other LDS, so a slot is one address bit
-        ka = base + offsetof(FwdSmem<D>, k) + row_frag_off<D>(lane);
-        va = base + offsetof(FwdSmem<D>, v) + col_frag_off<D>(lane);
-        ga = base + offsetof(FwdSmem<D>, g) + 16 * h;
+        ka = base + offsetof(Smem, k) + row_frag_off<D>(lane);
+        va = base + offsetof(Smem, v) + col_frag_off<D>(lane);
+        ga = base + offsetof(Smem, g) + 16 * h;
     }
-    static_assert(offsetof(FwdSmem<D>, k) % (2 * kTileBytes) == 0 && offsetof(FwdSmem<D>, v) % (2 * kTileBytes) == 0 &&
-                      offsetof(FwdSmem<D>, g) % (8 * kKeys) == 0, "the two slots of a ring differ in one address bit");
+    static_assert(offsetof(Smem, k) % (2 * kTileBytes) == 0 && offsetof(Smem, v) % (2 * kTileBytes) == 0 &&
+                      offsetof(Smem, g) % (8 * kKeys) == 0, "the two slots of a ring differ in one address bit");
     auto flip = [&]() __attribute__((always_inline)) {  // to the other ring slot
         ka ^= kTileBytes;
         va ^= kTileBytes;
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, FwdTile<D>::kResident) void fwd_bf1
             bf16x8 kf[KC];
 #pragma unroll
             for (int kc = 0; kc < KC; ++kc) kf[kc] = row_frag<D>(ka, 32 * b, kc);
-            if (NB == 1) __builtin_amdgcn_sched_barrier(0);  // all reads ahead of the products (d = 128: 2 %)
+            if (D == 128) __builtin_amdgcn_sched_barrier(0);  // all reads ahead of the products (2 %)
 #pragma unroll
             for (int kc = 0; kc < KC; ++kc) {
                 s[b] = mfma32(kf[kc], qf[kc], s[b]);
@@ -286,18 +286,19 @@ __global__ __launch_bounds__(64 * kFwdWaves, FwdTile<D>::kResident) void fwd_bf1
 }
 
 template <int D>
-static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const float* c, void* O,
-                             float* L, int B, int H, int Hkv, int N, int w, float scale, hipStream_t s) {
-    const int nq = (N + 127) / 128, total = B * H * nq, cus = device_cu_count();
-    // Three workgroups on a CU leave a second round of less than one a CU where up to four a CU are to be done: two on a CU
-    // then, by asking for more LDS, if two rounds of that are nearly full and most bands equal (H28 N4096 w256: 43.0 -> 39.5 us, H30
-    // w1000 86.7 -> 78.5, w1800 127.6 -> 117.4; H26 w1800, at 3.25 a CU, would be 92.4 -> 105.2, H32 causal 129.7 -> 140.4).
-    const size_t lds = D == 128 && 2 * total >= 7 * cus && total <= 4 * cus && 9L * w <= 4L * N ? (size_t)56 << 10 : sizeof(FwdSmem<D>);
-    static_assert(sizeof(FwdSmem<D>) <= (56 << 10), "two workgroups of 56 KB fit a CU, three do not");
-    ProfScope prof(kKernForward, s);
-    hipLaunchKernelGGL((fwd_bf16_kernel<D>), dim3(total), dim3(64 * kFwdWaves), lds, s, (const bf16_t*)Q,
-                       (const bf16_t*)K, (const bf16_t*)V, c, (bf16_t*)O, L, N, w, scale * kLog2e, nq, total, H, H / Hkv);
-    return hipGetLastError();
+__global__ __launch_bounds__(64 * kFwdWaves, D == 64 ? 4 : 3) void fwd_bf16_kernel(
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+    const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w, float scale_log2,
+    int num_qtiles, int total, int H, int G) {
+    fwd_tile<D, kFwdBlocks<D>>(Q, K, V, c, O, L, N, w, scale_log2, num_qtiles, total, H, G);
+}
+// d = 128 with the step of d = 64, for launches that put few workgroups on a CU (fwd_two_blocks has the line and figures): with two
+// waves on a SIMD the exponentials of a block have to run beside the products of the same wave's other block.
+__global__ __launch_bounds__(64 * kFwdWaves, 2) void fwd_two_blocks_bf16_kernel(
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+    const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w, float scale_log2,
+    int num_qtiles, int total, int H, int G) {
+    fwd_tile<128, 2>(Q, K, V, c, O, L, N, w, scale_log2, num_qtiles, total, H, G);
 }
 
 // Steps (64-key tiles, plus two per tile to fill and drain) of all 128-query tiles of a problem, and of the longest.
@@ -317,16 +318,58 @@ double query_tile_fill(int BH, int N, int w, long slots) {
     return steps / ((double)slots * (double)((BH * nq + slots - 1) / slots) * (double)longest);
 }
 
+// Whether the d = 128 forward takes steps of two blocks, two workgroups on a CU, instead of one and three.  Lines from 712 shapes
+// (N 64 .. 20000, 0.3 .. 31 tiles a CU); two blocks / one, us:
+//   all tiles on the CUs at once, bands not short       H4 N16384 w4096 127 / 135, H7 N8192 w3000 89 / 94 (H73 N861 w213 19.9 / 19.1)
+//   two nearly full rounds of two, not one of three     H14 N7817 w1160 85 / 94, H7 N16106 w907 73 / 82 (H10 N7269 w557, at 2.2 tiles
+//   and a rest, bands equal and not short               a CU, 48 / 39; H32 N4096 causal 146 / 138)
+//   long bands that are mostly equal, from three a CU   H8 N16384 w4096 235 / 252, H9 N18120 w2021 178 / 182
+// Elsewhere three waves on a SIMD are the better (B4 H16 N8192 w1024 302 / 283, B1 H32 N16384 w1024 318 / 297, B1 H124/31 N2246 w27
+// 51 / 42).
+// (No band here is shorter than 128, so that no sequence is shorter than a 64-key tile.)
+static bool fwd_two_blocks(int BH, int N, int w) {
+    const long total = (long)BH * ((N + 127) / 128), cus = device_cu_count(), band = w < N ? w : N;
+    if (total <= 2 * cus) return band >= (total <= cus ? 128 : 256);
+    long longest;
+    const double even = query_tile_steps(BH, N, w, longest) / ((double)total * (double)longest);
+    if (even < 0.75) return false;
+    return (band >= 2048 && total > 3 * cus) || (band >= 250 && (even >= 0.9 ? 3 * total >= 10 * cus : 2 * total >= 7 * cus) && total <= 4 * cus);
+}
+
+template <int D>
+static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const float* c, void* O,
+                             float* L, int B, int H, int Hkv, int N, int w, float scale, hipStream_t s) {
+    const int nq = (N + 127) / 128, total = B * H * nq, cus = device_cu_count();
+    auto kernel = fwd_bf16_kernel<D>;
+    // Bands too short for two blocks a step: two workgroups on a CU by asking for more LDS, where two rounds of that are nearly
+    // full and three on a CU leave a second round of less than one a CU (H25 N4803 w106 33.9 -> 32.9 us, H27 N4611 w58 30.3 -> 29.2).
+    const bool two_rounds = D == 128 && 2 * total >= 7 * cus && total <= 4 * cus && 9L * w <= 4L * N;
+    size_t lds = two_rounds ? (size_t)56 << 10 : sizeof(FwdSmem<D, kFwdBlocks<D>>);
+    static_assert(sizeof(FwdSmem<D, kFwdBlocks<D>>) <= (56 << 10), "two workgroups of 56 KB fit a CU, three do not");
+    if constexpr (D == 128) {
+        if (fwd_two_blocks(B * H, N, w)) {
+            kernel = fwd_two_blocks_bf16_kernel;
+            lds = sizeof(FwdSmem<D, 2>);
+            static DeviceOnce lds_allowed;
+            if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, lds_allowed)) return e;
+        }
+    }
+    ProfScope prof(kKernForward, s);
+    hipLaunchKernelGGL(kernel, dim3(total), dim3(64 * kFwdWaves), lds, s, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, c,
+                       (bf16_t*)O, L, N, w, scale * kLog2e, nq, total, H, H / Hkv);
+    return hipGetLastError();
+}
+
 // Which kernel serves a problem.  The one of this file wins once a CU has so many times the steps of the longest tile to
 // do (`ratio`), the split one below.
 // d = 64, 1.3: over 37 shapes (N 100 .. 16384) the best split shape is 1.04 to 1.8 times as fast below (one exception,
 // 0.98), and above between 1.27 times as slow and equal (one exception, H24 N2100 w300: 12.5 against 14.5 us).
-// d = 128, 1.0: over 29 shapes 1.03 to 2.2 times as fast below, 1.45 times as slow to equal above (B20 H4 N600, at 1.04: 22.1
-// against 18.5).  For bands that 128 queries share out well 1.5, for longer ones 1.95 (H20 N4096 causal, at 1.33: 102 against 111
-// us; H13 N5003 w2500, at 1.53: 92 against 98; H20/5 N5003 w4000, at 1.91: 147 against 153; H32 N4096 causal, at 2.12: 145
-// against 130), or less where the tiles fill two places on every CU: the split kernel, one on a CU, takes whole rounds (H7 N8192
-// w3000, filled to 0.71: 107 against 92, H10 N5003 w2000, 0.63: 72 against 64; H12 N4096 w1800, 0.58: 58 against 59, H9 N5003
-// w3000, 0.50: 69 against 89).
+// d = 128, over 712 shapes: 1.0, or 0.85 where every tile has a CU to itself or the band is longer than 1024 (H3 N10679 w361, at
+// 0.97: 23.0 against 16.4 us split, H2 N15792 w1194, 0.93: 50.9 against 29.9; with several short bands on few of the CUs, B2 H6 N2776
+// w392, 0.95, 18.7 against 21.7).  Bands that 128 queries share out well 1.05 (B2 H4/2 N5746 w1976, 1.17: 65 against 51; B2 H14
+// N2021 w1786, 1.0: 44 against 55), above 2048 1.95 (H20/5 N5003 w4000, 1.91: 139 against 153; H32 N4096 causal, 2.12: 145 against
+// 130), or less where the tiles fill two places on every CU: the split kernel, one on a CU, takes whole rounds (H6 N7814 w3225,
+// filled to 0.58: 99 against 91; H4 N11226 w6064, 0.50: 116 against 156).
 // Sequences shorter than a step's tile are the split kernel's, and there 64 queries are the better than 32 (d = 64, 512 x 4
 // heads of 50: 13.7, 28.0 us).
 // Inside the split kernel: one 32-query block per workgroup while that gives few workgroups (at d = 128 its
@@ -336,9 +379,10 @@ static FwdSplit fwd_split_shape(int BH, int N, int d, int w) {
     const long cus = device_cu_count(), band = w < N ? w : N;
     long longest;
     const double ratio = query_tile_steps(BH, N, w, longest) / ((double)cus * (double)longest);
-    const bool filled = ratio >= (d == 64 ? 1.3 : band > 2048 ? 1.95 : band > 1500 ? 1.5 : 1.0) ||
-                        (d == 128 && band > 1500 && query_tile_fill(BH, N, w, 2 * cus) >= 0.61);
-    if (N >= (d == 64 ? FwdTile<64>::kKeys : FwdTile<128>::kKeys) && filled) return kFwdSplitNone;
+    bool filled = ratio >= (d == 64 ? 1.3 : band > 2048 ? 1.95 : band > 1500 ? 1.05 : band > 1024 ? 0.85 : 1.0);
+    if (d == 128 && band > 1500) filled |= query_tile_fill(BH, N, w, 2 * cus) >= 0.57;
+    if (d == 128 && band <= 1024 && band >= 128) filled |= ratio >= 0.85 && (long)BH * ((N + 127) / 128) <= cus;
+    if (N >= 32 * (d == 64 ? kFwdBlocks<64> : kFwdBlocks<128>) && filled) return kFwdSplitNone;
     if ((long)BH * ((N + 31) / 32) <= 5 * cus / 2 && (d == 64 || band <= 1024)) return kFwdSplitNarrow;
     return band > (d == 64 ? 2560 : 1500) ? kFwdSplitWide : kFwdSplitMid;
 }

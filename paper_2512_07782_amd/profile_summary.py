@@ -52,6 +52,7 @@ LIB = {
     "bwd_dq_bf16_kernel<64>": "bwd_dq",
     "bwd_dkv8_bf16_kernel<128, false>": "bwd_dkv",
     "bwd_dq_bf16_kernel<128>": "bwd_dq",
+    "fwd_two_blocks_bf16_kernel": "forward",  # d = 128, few workgroups on a CU
     # few or uneven tiles
     "fwd_split_bf16_kernel": "forward", "bwd_dkv_split_bf16_kernel": "bwd_dkv", "bwd_dq_split_bf16_kernel": "bwd_dq",
     # fp32 storage

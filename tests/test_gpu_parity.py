@@ -28,6 +28,8 @@ The forward entry point is compared with the oracle on the same fp32 prefix c (t
 prefix rounded to fp32); the prefix entry point is compared separately; one chained test runs
 alpha -> c -> O entirely on the GPU against the oracle's definition from alpha.
 """
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -631,20 +633,43 @@ def test_forward_bf16_split_band(g, oracle, B, H, N, d, w, heads):
     check_bf16_forward(O, L, O_ref, L_ref, tag="split band")
 
 
-@pytest.mark.parametrize("B,H,N,d,w,heads", [
+def kernels(call):
+    """Names (with template arguments) of the library's kernels that `call` runs, as the profiler sees them."""
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    found = (re.search(r"gfwa::(\w+(<[^>]*>)?)", e.key) for e in prof.key_averages())
+    return {m.group(1) for m in found if m}
+
+
+MANY64, MANY128, TWO_BLOCKS, SPLIT = "fwd_bf16_kernel<64>", "fwd_bf16_kernel<128>", "fwd_two_blocks_bf16_kernel", "fwd_split_bf16_kernel"
+
+
+@pytest.mark.parametrize("B,H,N,d,w,heads,kernel", [
     # enough work per CU for the kernel of many workgroups on a CU: sequences of one key tile (64 keys at d = 64, 32 at
     # d = 128), one row on either side of a key and of a query tile, windows of one key, inside a tile, at its edge and past the
     # sequence; head counts that divide by the XCDs and that do not; shorter than a key tile, which the split kernel takes;
     # last: a launch that puts two workgroups on a CU instead of three
-    (48, 8, 64, 64, 64, [0, 383]), (5, 67, 65, 64, 9, [0, 334]), (48, 8, 127, 64, 1, [0, 200]), (5, 67, 128, 64, 5000, [0, 334]),
-    (24, 16, 129, 64, 64, [0, 383]), (7, 31, 193, 64, 65, [0, 216]), (10, 20, 321, 64, 128, [0, 199]), (128, 4, 63, 64, 64, [0, 511]),
-    (48, 8, 32, 128, 32, [0, 383]), (5, 67, 33, 128, 9, [0, 334]), (48, 8, 127, 128, 1, [0, 200]), (5, 67, 128, 128, 5000, [0, 334]),
-    (24, 16, 161, 128, 32, [0, 383]), (7, 31, 193, 128, 65, [0, 216]), (128, 4, 31, 128, 64, [0, 511]), (7, 32, 450, 128, 128, [0, 223]),
+    (48, 8, 64, 64, 64, [0, 383], MANY64), (5, 71, 65, 64, 9, [0, 354], MANY64), (48, 8, 127, 64, 1, [0, 200], MANY64),
+    (5, 71, 128, 64, 5000, [0, 354], MANY64), (24, 16, 129, 64, 64, [0, 383], MANY64), (7, 31, 193, 64, 65, [0, 216], MANY64),
+    (10, 20, 321, 64, 128, [0, 199], MANY64), (128, 4, 63, 64, 64, [0, 511], SPLIT),
+    (48, 8, 32, 128, 32, [0, 383], MANY128), (5, 71, 33, 128, 9, [0, 354], MANY128), (48, 8, 127, 128, 1, [0, 200], MANY128),
+    (5, 71, 128, 128, 5000, [0, 354], MANY128), (24, 16, 161, 128, 32, [0, 383], MANY128), (7, 31, 193, 128, 65, [0, 216], MANY128),
+    (128, 4, 31, 128, 64, [0, 511], SPLIT), (8, 31, 450, 128, 128, [0, 247], MANY128),
+    # few workgroups on a CU, d = 128 in steps of 64 keys: sequences of two key tiles, the last tile of one row, of all but one
+    # and of three, windows at a tile's edge, one past it and past the sequence; one, two and four workgroups on a CU
+    (30, 8, 128, 128, 128, [0, 239], TWO_BLOCKS), (32, 8, 128, 128, 5000, [0, 255], TWO_BLOCKS), (1, 14, 2049, 128, 129, [0, 13], TWO_BLOCKS),
+    (1, 15, 2047, 128, 192, [0, 14], TWO_BLOCKS), (2, 58, 450, 128, 300, [0, 115], TWO_BLOCKS), (7, 16, 449, 128, 257, [0, 111], TWO_BLOCKS),
+    (1, 14, 7817, 128, 300, [0, 13], TWO_BLOCKS),
 ])
-def test_forward_bf16_many_workgroups(g, oracle, B, H, N, d, w, heads):
+def test_forward_bf16_many_workgroups(g, oracle, B, H, N, d, w, heads, kernel):
     note("many workgroups", B, H, N, d, w)
     wl = gi.custom("many", B, H, N, d, w, "bf16", alpha_mu=-1.5, index=15)
-    O, L, O_ref, L_ref = run_forward(g, oracle, wl, heads=heads)
+    got = []
+    names = kernels(lambda: got.extend(run_forward(g, oracle, wl, heads=heads)))
+    assert any(n.startswith(kernel) for n in names), names
+    O, L, O_ref, L_ref = got
     check_bf16_forward(O, L, O_ref, L_ref, tag="many workgroups")
 
 
