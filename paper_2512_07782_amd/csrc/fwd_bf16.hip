@@ -84,11 +84,14 @@ __device__ __forceinline__ void fwd_tile(
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = lane >> 5, lq = lane & 31;
     const float sl = scale_log2, inv_scale = kLog2e / scale_log2;
-    // Longest bands (the end of the sequence) first.  Heads that do not divide by the XCDs: B1 H12 N8192 w1024 37.6 us tile
-    // after tile, 35.5 in contiguous ranges; B3 H11 N4096 causal 105 and 107 us.
+    // Longest bands (the end of the sequence) first.  Heads that do not divide by the XCDs go in contiguous ranges while bands are
+    // short against the sequence (B1 H12 N8192 w1024 37.6 us tile after tile, 35.5 so); with longer ones a range holds long or short
+    // bands only, and the XCDs finish apart.  d = 64, over 200 shapes: from 0.4 N on 1.0 to 1.5 times as fast tile after tile (B2 H9
+    // N3795 w2727 70.0 -> 46.3 us, H30 N3284 w1803 56.0 -> 49.4; B4 H113 N162 w146 would be 11.1 -> 12.7, hence 256).
     const int heads = total / num_qtiles;
     int bh, qt;
-    tile_of_block((int)blockIdx.x, heads, num_qtiles, heads % 8 == 0 || w >= N, bh, qt);
+    const bool uneven = w >= N || (D == 64 && N > 256 && 5L * w >= 2L * N);
+    tile_of_block((int)blockIdx.x, heads, num_qtiles, heads % 8 == 0 || uneven, bh, qt);
     const int q0 = (num_qtiles - 1 - qt) * 128;
     const size_t head_off = (size_t)bh * N * D, kv_off = (size_t)kv_head_of(bh, H, G) * N * D;
     const char* Kh = reinterpret_cast<const char*>(K + kv_off);

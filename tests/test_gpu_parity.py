@@ -654,6 +654,8 @@ MANY64, MANY128, TWO_BLOCKS, SPLIT = "fwd_bf16_kernel<64>", "fwd_bf16_kernel<128
     (48, 8, 64, 64, 64, [0, 383], MANY64), (5, 71, 65, 64, 9, [0, 354], MANY64), (48, 8, 127, 64, 1, [0, 200], MANY64),
     (5, 71, 128, 64, 5000, [0, 354], MANY64), (24, 16, 129, 64, 64, [0, 383], MANY64), (7, 31, 193, 64, 65, [0, 216], MANY64),
     (10, 20, 321, 64, 128, [0, 199], MANY64), (128, 4, 63, 64, 64, [0, 511], SPLIT),
+    # (the two sides of the order of tiles for heads that do not divide by the XCDs, windows of 0.4 N)
+    (5, 43, 321, 64, 129, [0, 1, 43, 214], MANY64), (5, 43, 321, 64, 128, [0, 1, 43, 214], MANY64),
     (48, 8, 32, 128, 32, [0, 383], MANY128), (5, 71, 33, 128, 9, [0, 354], MANY128), (48, 8, 127, 128, 1, [0, 200], MANY128),
     (5, 71, 128, 128, 5000, [0, 354], MANY128), (24, 16, 161, 128, 32, [0, 383], MANY128), (7, 31, 193, 128, 65, [0, 216], MANY128),
     (128, 4, 31, 128, 64, [0, 511], SPLIT), (8, 31, 450, 128, 128, [0, 247], MANY128),
