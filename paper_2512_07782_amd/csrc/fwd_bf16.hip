@@ -69,6 +69,22 @@ struct FwdSmem {
     alignas(16) float g[2][kKeys];  // (c - c_base) / scale of the tile's keys
 };
 
+// Longest bands (the end of the sequence) first.  Heads that do not divide by the XCDs go in contiguous ranges while bands are
+// short against the sequence (B1 H12 N8192 w1024 37.6 us tile after tile, 35.5 so); with longer ones a range holds long or short
+// bands only, and the XCDs finish apart.  d = 64, over 200 shapes: from 0.4 N on 1.0 to 1.5 times as fast tile after tile (B2 H9
+// N3795 w2727 70.0 -> 46.3 us, H30 N3284 w1803 56.0 -> 49.4; B4 H113 N162 w146 would be 11.1 -> 12.7, hence 256).  At d = 128
+// the keys of all heads at once outgrow an XCD's L2 (tile after tile B2 H9 N5458 w2294 114 -> 134 us, B3 H22/11 N1219 w1138 42.4
+// -> 45.3), so only causal ones, nearly causal ones with two blocks a step, and few tiles, up to 2.5 a CU, with bands of 0.3 N
+// (H36/9 N2155 w1379 63.9 -> 48.8, B3 H12/3 N1845 w920 46.7 -> 37.3) or where a few tiles, not the shortest, begin another round
+// (H11 N3193 w492, 275 tiles on 256 CUs, 29.6 -> 21.7, B2 H3 N5525 w364 25.1 -> 18.1; w63 13.0 -> 14.3, as other short bands).
+template <int D, int NB>
+__host__ __device__ __forceinline__ bool fwd_by_length(int heads, long tiles, int N, int w) {
+    if (heads % 8 == 0 || w >= N) return true;
+    if (D == 64) return N > 256 && 5L * w >= 2L * N;
+    if (NB == 2 && N >= 1000 && 4L * w >= 3L * N) return true;
+    return N > 256 && tiles > 256 && tiles <= 640 && (10L * w >= 3L * N || (w >= 192 && tiles % 256 <= 64));
+}
+
 template <int D, int NB>
 __device__ __forceinline__ void fwd_tile(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
@@ -84,14 +100,9 @@ __device__ __forceinline__ void fwd_tile(
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = lane >> 5, lq = lane & 31;
     const float sl = scale_log2, inv_scale = kLog2e / scale_log2;
-    // Longest bands (the end of the sequence) first.  Heads that do not divide by the XCDs go in contiguous ranges while bands are
-    // short against the sequence (B1 H12 N8192 w1024 37.6 us tile after tile, 35.5 so); with longer ones a range holds long or short
-    // bands only, and the XCDs finish apart.  d = 64, over 200 shapes: from 0.4 N on 1.0 to 1.5 times as fast tile after tile (B2 H9
-    // N3795 w2727 70.0 -> 46.3 us, H30 N3284 w1803 56.0 -> 49.4; B4 H113 N162 w146 would be 11.1 -> 12.7, hence 256).
     const int heads = total / num_qtiles;
     int bh, qt;
-    const bool uneven = w >= N || (D == 64 && N > 256 && 5L * w >= 2L * N);
-    tile_of_block((int)blockIdx.x, heads, num_qtiles, heads % 8 == 0 || uneven, bh, qt);
+    tile_of_block((int)blockIdx.x, heads, num_qtiles, fwd_by_length<D, NB>(heads, total, N, w), bh, qt);
     const int q0 = (num_qtiles - 1 - qt) * 128;
     const size_t head_off = (size_t)bh * N * D, kv_off = (size_t)kv_head_of(bh, H, G) * N * D;
     const char* Kh = reinterpret_cast<const char*>(K + kv_off);
@@ -304,7 +315,8 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void fwd_two_blocks_bf16_kernel(
     fwd_tile<128, 2>(Q, K, V, c, O, L, N, w, scale_log2, num_qtiles, total, H, G);
 }
 
-// Steps (64-key tiles, plus two per tile to fill and drain) of all 128-query tiles of a problem, and of the longest.
+// What all 128-query tiles of a problem cost and what the longest does, counted in 64-key tiles plus two for each query tile's start
+// and end, whatever the kernel's own step is: the lines below were measured against this count.
 static double query_tile_steps(int BH, int N, int w, long& longest) {
     const long nq = (N + 127) / 128;
     const long band = w < N ? w : N, full = (band + 126) / 64 + 2;   // key tiles of a tile whose whole band exists
@@ -323,16 +335,22 @@ double query_tile_fill(int BH, int N, int w, long slots) {
 
 // Whether the d = 128 forward takes steps of two blocks, two workgroups on a CU, instead of one and three.  Lines from 712 shapes
 // (N 64 .. 20000, 0.3 .. 31 tiles a CU); two blocks / one, us:
-//   all tiles on the CUs at once, bands not short       H4 N16384 w4096 127 / 135, H7 N8192 w3000 89 / 94 (H73 N861 w213 19.9 / 19.1)
+//   all tiles on the CUs at once, bands not short       H4 N16384 w4096 127 / 135, H7 N8192 w3000 89 / 94 (H73 N861 w213 19.9 / 19.1;
+//                                                       long sequences from 64 on: H2 N16382 w89 11.6 / 11.9, split 13.6)
 //   two nearly full rounds of two, not one of three     H14 N7817 w1160 85 / 94, H7 N16106 w907 73 / 82 (H10 N7269 w557, at 2.2 tiles
 //   and a rest, bands equal and not short               a CU, 48 / 39; H32 N4096 causal 146 / 138)
 //   long bands that are mostly equal, from three a CU   H8 N16384 w4096 235 / 252, H9 N18120 w2021 178 / 182
+//   nearly causal, heads that do not divide by the XCDs, B3 H6 N11097 574 / 624, H12 N11676 400 / 428, H36 N4466 177 / 203,
+//   not many, so that every XCD streams the keys of all  H28 N6200 261 / 300 (B6 H30/15 N1407 125 / 117, H108 N801 36 / 34)
+//   from 128 on where tiles go by length, N > 192        H168 N226 11.2 / 12.0, H120 N387 w200 14.8 / 15.2
 // Elsewhere three waves on a SIMD are the better (B4 H16 N8192 w1024 302 / 283, B1 H32 N16384 w1024 318 / 297, B1 H124/31 N2246 w27
 // 51 / 42).
-// (No band here is shorter than 128, so that no sequence is shorter than a 64-key tile.)
+// (No band here is shorter than 64, so that no sequence is shorter than a 64-key tile.)
 static bool fwd_two_blocks(int BH, int N, int w) {
     const long total = (long)BH * ((N + 127) / 128), cus = device_cu_count(), band = w < N ? w : N;
-    if (total <= 2 * cus) return band >= (total <= cus ? 128 : 256);
+    const bool by_length = fwd_by_length<128, 2>(BH, total, N, w);
+    if (total <= 2 * cus) return band >= (total <= cus ? (N >= 4096 ? 64 : 128) : by_length && N > 192 ? 128 : 256);
+    if (BH % 8 != 0 && BH <= 64 && 4L * w >= 3L * N && N >= 1000 && total <= 8 * cus) return true;
     long longest;
     const double even = query_tile_steps(BH, N, w, longest) / ((double)total * (double)longest);
     if (even < 0.75) return false;
@@ -365,9 +383,13 @@ static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const 
 
 // Which kernel serves a problem.  The one of this file wins once a CU has so many times the steps of the longest tile to
 // do (`ratio`), the split one below.
-// d = 64, 1.3: over 37 shapes (N 100 .. 16384) the best split shape is 1.04 to 1.8 times as fast below (one exception,
-// 0.98), and above between 1.27 times as slow and equal (one exception, H24 N2100 w300: 12.5 against 14.5 us).
-// d = 128, over 712 shapes: 1.0, or 0.85 where every tile has a CU to itself or the band is longer than 1024 (H3 N10679 w361, at
+// d = 64, 1.3: over 1182 shapes the best split shape is 1.0 to 1.8 times as fast below (a mean of 1.1 at 1.2), and above between 1.3
+// times as slow and equal, but where a CU has one tile or two: up to two a CU for heads that divide by the XCDs (H16/4 N3367 w1048, 1.7 a
+// CU: 27.6 against 24.6 us split; B8 H3 N3313 w335 1.14 of the time, from 2.0 on 0.95 to 1.0), one and a half for others (B4 H13 N939
+// w311 14.9, 12.9; at 1.6 to 2 between 0.77 and 1.13, 0.94 on average).
+// d = 128, over 1766 shapes: 1.0, or 0.85 where every tile has a CU to itself or, with heads that divide by the XCDs, the band is longer
+// than 1024 (B5 H4 N1921 w1282, that do not: 43.3 against 30.2 split), 0.9 for tiles by length up to two a CU (B7 H13 N437 causal 15.9
+// against 20.6 split, H11 N3193 w492 21.7, 29.6; B4 H7 N1179 w381, in ranges, 20.7, 16.8) (H3 N10679 w361, at
 // 0.97: 23.0 against 16.4 us split, H2 N15792 w1194, 0.93: 50.9 against 29.9; with several short bands on few of the CUs, B2 H6 N2776
 // w392, 0.95, 18.7 against 21.7).  Bands that 128 queries share out well 1.05 (B2 H4/2 N5746 w1976, 1.17: 65 against 51; B2 H14
 // N2021 w1786, 1.0: 44 against 55), above 2048 1.95 (H20/5 N5003 w4000, 1.91: 139 against 153; H32 N4096 causal, 2.12: 145 against
@@ -376,18 +398,26 @@ static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const 
 // Sequences shorter than a step's tile are the split kernel's, and there 64 queries are the better than 32 (d = 64, 512 x 4
 // heads of 50: 13.7, 28.0 us).
 // Inside the split kernel: one 32-query block per workgroup while that gives few workgroups (at d = 128 its
-// single-buffered tiles only pay for short bands), 128 queries where the band is long enough to share out (at d = 64,
-// H12 N4000 w2000: 38.6 against 31.4 us with 64, H15 N4000 causal: 48.5 against 71.7).
+// single-buffered tiles only pay for short bands), 128 queries where the band is long enough to share out: at d = 64 from 2560 on
+// (H15 N4000 causal: 48.5 against 71.7 us with 64; H12 N4000 w2000 38.6 against 31.4), and from 1500 on, near one tile a CU and with
+// uneven bands, for heads that are no multiple of four, above all odd ones: consecutive workgroups are consecutive heads, so that every XCD
+// reads the keys of all of them, half as often with 128 queries (B3 H9 N1855 causal 27.2 against 33.4, B7 H3 N2175 27.1, 36.3, H11 N3968
+// w2459 35.4, 46.6; B2 H16/4 N1806 30.0, 25.6; B2 H18/9 N1517 24.8, 21.9; H6/3 N7231 w2373 52.4, 40.7; H7 N6799 w1618 45.3, 37.2).
 static FwdSplit fwd_split_shape(int BH, int N, int d, int w) {
     const long cus = device_cu_count(), band = w < N ? w : N;
     long longest;
     const double ratio = query_tile_steps(BH, N, w, longest) / ((double)cus * (double)longest);
-    bool filled = ratio >= (d == 64 ? 1.3 : band > 2048 ? 1.95 : band > 1500 ? 1.05 : band > 1024 ? 0.85 : 1.0);
+    const long tiles = (long)BH * ((N + 127) / 128);
+    bool filled = ratio >= (d == 64 ? 1.3 : band > 2048 ? 1.95 : band > 1500 ? 1.05 : band > 1024 && BH % 8 == 0 ? 0.85 : 1.0);
+    if (d == 64) filled &= 2 * tiles > (BH % 8 == 0 ? 4 : 3) * cus;
     if (d == 128 && band > 1500) filled |= query_tile_fill(BH, N, w, 2 * cus) >= 0.57;
-    if (d == 128 && band <= 1024 && band >= 128) filled |= ratio >= 0.85 && (long)BH * ((N + 127) / 128) <= cus;
+    if (d == 128 && band <= 1024 && band >= (N >= 4096 ? 64 : 128)) filled |= ratio >= 0.85 && tiles <= cus;
+    if (d == 128 && band <= 1024 && band >= 128 && N > 192 && fwd_by_length<128, 2>(BH, tiles, N, w)) filled |= ratio >= 0.9 && tiles <= 2 * cus;
     if (N >= 32 * (d == 64 ? kFwdBlocks<64> : kFwdBlocks<128>) && filled) return kFwdSplitNone;
     if ((long)BH * ((N + 31) / 32) <= 5 * cus / 2 && (d == 64 || band <= 1024)) return kFwdSplitNarrow;
-    return band > (d == 64 ? 2560 : 1500) ? kFwdSplitWide : kFwdSplitMid;
+    const bool uneven = BH % 2 != 0 ? 5L * w >= 2L * N : BH % 4 != 0 && 4L * w >= 3L * N;
+    const bool wide = d == 128 || (uneven && ratio >= 0.6 && ratio <= 1.25);
+    return band > (wide ? 1500 : 2560) ? kFwdSplitWide : kFwdSplitMid;
 }
 
 hipError_t forward_bf16(const void* Q, const void* K, const void* V, const float* c, void* O, float* L,

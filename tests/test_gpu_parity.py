@@ -651,8 +651,8 @@ MANY64, MANY128, TWO_BLOCKS, SPLIT = "fwd_bf16_kernel<64>", "fwd_bf16_kernel<128
     # d = 128), one row on either side of a key and of a query tile, windows of one key, inside a tile, at its edge and past the
     # sequence; head counts that divide by the XCDs and that do not; shorter than a key tile, which the split kernel takes;
     # last: a launch that puts two workgroups on a CU instead of three
-    (48, 8, 64, 64, 64, [0, 383], MANY64), (5, 71, 65, 64, 9, [0, 354], MANY64), (48, 8, 127, 64, 1, [0, 200], MANY64),
-    (5, 71, 128, 64, 5000, [0, 354], MANY64), (24, 16, 129, 64, 64, [0, 383], MANY64), (7, 31, 193, 64, 65, [0, 216], MANY64),
+    (66, 8, 64, 64, 64, [0, 527], MANY64), (5, 81, 65, 64, 9, [0, 404], MANY64), (66, 8, 127, 64, 1, [0, 200], MANY64),
+    (5, 81, 128, 64, 5000, [0, 404], MANY64), (24, 16, 129, 64, 64, [0, 383], MANY64), (7, 31, 193, 64, 65, [0, 216], MANY64),
     (10, 20, 321, 64, 128, [0, 199], MANY64), (128, 4, 63, 64, 64, [0, 511], SPLIT),
     # (the two sides of the order of tiles for heads that do not divide by the XCDs, windows of 0.4 N)
     (5, 43, 321, 64, 129, [0, 1, 43, 214], MANY64), (5, 43, 321, 64, 128, [0, 1, 43, 214], MANY64),
@@ -664,6 +664,14 @@ MANY64, MANY128, TWO_BLOCKS, SPLIT = "fwd_bf16_kernel<64>", "fwd_bf16_kernel<128
     (30, 8, 128, 128, 128, [0, 239], TWO_BLOCKS), (32, 8, 128, 128, 5000, [0, 255], TWO_BLOCKS), (1, 14, 2049, 128, 129, [0, 13], TWO_BLOCKS),
     (1, 15, 2047, 128, 192, [0, 14], TWO_BLOCKS), (2, 58, 450, 128, 300, [0, 115], TWO_BLOCKS), (7, 16, 449, 128, 257, [0, 111], TWO_BLOCKS),
     (1, 14, 7817, 128, 300, [0, 13], TWO_BLOCKS),
+    # the lines between the kernels.  d = 64: up to two tiles a CU for heads that divide by the XCDs, one and a half for others; wide
+    # split tiles.  d = 128: a tile a CU of short bands, long sequences only; two a CU by length, N > 192; heads in ranges, bands of more
+    # than 1024; nearly causal bands; few tiles of another round, in ranges and by length
+    (1, 16, 1667, 64, 1048, [0, 15], SPLIT), (4, 13, 939, 64, 311, [0, 51], MANY64), (3, 9, 1855, 64, 1855, [26], SPLIT),
+    (1, 7, 4097, 128, 65, [0, 6], TWO_BLOCKS), (1, 7, 4095, 128, 65, [0, 6], SPLIT), (19, 8, 226, 128, 226, [0, 151], TWO_BLOCKS),
+    (19, 8, 192, 128, 192, [0, 151], SPLIT), (5, 4, 1921, 128, 1282, [0, 19], SPLIT),
+    (7, 9, 1100, 128, 825, [0, 62], TWO_BLOCKS), (7, 9, 1100, 128, 824, [0, 62], MANY128),
+    (1, 11, 3193, 128, 492, [0, 10], TWO_BLOCKS), (1, 11, 3193, 128, 191, [0, 10], MANY128),
 ])
 def test_forward_bf16_many_workgroups(g, oracle, B, H, N, d, w, heads, kernel):
     note("many workgroups", B, H, N, d, w)
