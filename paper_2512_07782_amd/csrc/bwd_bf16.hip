@@ -944,17 +944,26 @@ static bool bwd_dkv_splits(int BHkv, int G, int N, int d, int w) {
     return split < 0.9 * whole;
 }
 
-// Whether both passes go in one launch of split workgroups (32 keys of a key/value head, or 64 queries).  Measured over 41
-// small shapes (1 .. 128 heads of 64 .. 8000 tokens): with a workgroup for every CU at most it is between equal and 1.7 times
-// as fast as the best pair of launches (B1 H4 N300 d64 18.9 -> 11.2 us, H1 N64 12.5 -> 9.4), and so it is up to about twice as
-// many where the bands are at least half the sequence (H8 N1000 causal, d = 64 22.6 -> 21.0, d = 128 36.9 -> 33.1; H2 N4000
-// w1000 it would be 23.8 -> 27.8 and 41 -> 51).  At d = 128 a long chain of query blocks, each of which now brings its rows
-// of O along, is the exception (8 query heads on one key/value head, N500: 68 us in two launches, 76 in one).
+// Whether both passes go in one launch of split workgroups (32 keys of a key/value head, or 64 queries; the LDS of either is that of
+// the larger, one workgroup a CU).  Over 2813 shapes of 1 .. 128 heads, one launch / the best pair:
+//   a workgroup for every CU at most    between equal and 1.7 times as fast (B1 H4 N300 d64 18.9 -> 11.2 us, H1 N64 12.5 -> 9.4), but at
+//                                       d = 128 for long chains of query blocks, each of which now brings its rows of O along (8 query
+//                                       heads on one key/value head, N500: 68 -> 76; in groups of 4, N650: 52.8 -> 55.5)
+//   up to twice as many, in two rounds  where the bands are at least half the sequence (H8 N1000 causal, d = 64 22.6 -> 21.0, d = 128 36.9
+//                                       -> 33.1, B4 H1 N1680 causal 28.2 -> 21.6; H2 N4000 w1000 would be 23.8 -> 27.8 and 41 -> 51), but at
+//                                       d = 128 above 1.75 for chains of more than 40 blocks of one head (B3 H1 N3498 w2526, 82 -> 104; B1 H36/9
+//                                       N544 54 -> 47), and at d = 64 for short sequences whose keys take four fifths of the first round to
+//                                       all of it, so that the queries wait for the second (B5 H15 N91 14.8 -> 15.8); d = 64 to 2.1 for
+//                                       others (H32/8 N673 34 -> 28; B4 H44/11 N124 20.4 -> 23.0)
 static bool bwd_in_one_launch(int BH, int BHkv, int N, int d, int w) {
     const long cus = device_cu_count(), seen = w < N ? w : N, G = BH / BHkv;
-    const long blocks = (long)BHkv * ((N + 31) / 32) + (long)BH * ((N + 63) / 64);
-    if (G > kDkvSplitMaxGroup || (d == 128 && G * ((seen + 31) / 32) > 4 * 24)) return false;
-    return blocks <= cus || (2 * seen >= N && 10 * blocks <= (d == 64 ? 21 : 20) * cus);
+    const long keys = (long)BHkv * ((N + 31) / 32), blocks = keys + (long)BH * ((N + 63) / 64);
+    const long chain = G * ((seen + 31) / 32);
+    if (G > kDkvSplitMaxGroup || (d == 128 && chain > 96)) return false;
+    if (blocks <= cus) return true;
+    if (2 * seen < N) return false;
+    if (d == 64) return N > 128 ? 10 * blocks <= 21 * cus : blocks <= 2 * cus && (5 * keys <= 4 * cus || keys > cus);
+    return blocks <= 2 * cus && (G > 1 || chain <= 40 || 4 * blocks <= 7 * cus);
 }
 
 template <int D>

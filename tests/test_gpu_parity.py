@@ -967,6 +967,10 @@ def launched(g, call):
     (1, 8, 1, 161, 128, 33, True), (4, 16, 16, 70, 64, 35, True), (2, 6, 2, 449, 128, 225, True),
     # and just not: one head more with a shorter band; a chain of more than 96 blocks at d = 128
     (1, 65, 65, 70, 64, 34, False), (1, 8, 1, 417, 128, 500, False),
+    # two rounds: short sequences whose keys fill just the first, less of it and more; longer ones up to 2.1; at d = 128 a long chain of
+    # one head and of two
+    (5, 15, 15, 91, 64, 91, False), (5, 13, 13, 91, 64, 91, True), (6, 15, 15, 91, 64, 91, True), (1, 32, 8, 673, 64, 673, True),
+    (1, 7, 7, 1400, 128, 1400, False), (1, 10, 5, 1441, 128, 1441, True),
 ])
 def test_backward_bf16_one_launch(g, oracle, ws_variant, B, H, Hkv, N, d, w, one):
     note("one launch", ws_variant, B, H, Hkv, N, d, w)
