@@ -145,10 +145,11 @@ __global__ __launch_bounds__(64 * kF32Waves) void fwd_f32_kernel(
     fwd_row<D, LOADS>(Q + ho, K + kvo, V + kvo, c + rows, O + ho, L + rows, t, w, scale, lane);
 }
 
-// ---- dQ_t and the row sum of dS.  Where Oh is given D_t = <O_t, dO_t> is formed and stored, else it is read.
-template <int D, int LOADS>
+// ---- dQ_t and the row sum of dS.  OWN_D: D_t = <O_t, dO_t> is formed and stored; else it is read and Oh is not.
+template <int D, int LOADS, bool OWN_D>
 __device__ __forceinline__ void dq_row(const float* Qh, const float* Kh, const float* Vh, const float* Oh, const float* dOh, const float* ch,
-                                       const float* Lh, float* Dh, float* dQh, float* dc_rowh, int t, int w, float scale, int lane) {
+                                       const float* Lh, std::conditional_t<OWN_D, float, const float>* Dh, float* dQh, float* dc_rowh,
+                                       int t, int w, float scale, int lane) {
     using Step = RowStep<D, LOADS>;
     const int r = lane / Step::kLanes, col = 4 * (lane % Step::kLanes);
     const int lo = max(0, t - w + 1);
@@ -157,7 +158,7 @@ __device__ __forceinline__ void dq_row(const float* Qh, const float* Kh, const f
     const size_t at = (size_t)t * D + col;
     const f32x4 q = *reinterpret_cast<const f32x4*>(Qh + at), g = *reinterpret_cast<const f32x4*>(dOh + at);
     const float ct = ch[t], Lt = Lh[t];
-    float Dt = Oh == nullptr ? Dh[t] : 0.f;
+    float Dt = OWN_D ? 0.f : Dh[t];
     // fp64: the suffix sums of the gate gradient add up what this sum and the column sums of dkv_row round (with running fp32
     // sums d(alpha) of 12 heads of 300 rows, d = 128, w = 77 was off by 1.4e-6 of its norm instead of 1.0e-6)
     double rs = 0.0;
@@ -167,11 +168,12 @@ __device__ __forceinline__ void dq_row(const float* Qh, const float* Kh, const f
 #pragma unroll
         for (int u = 0; u < Step::kLoads; ++u) ci[u] = ch[min(i0 + u * Step::kRows + r, t)];
         v.load(Vh, i0, t, lane);
-        if (Oh != nullptr && i0 == lo) {
-            RowStep<D, 1> one;
-            one.x[0] = *reinterpret_cast<const f32x4*>(Oh + at);
-            Dt = one.dot(g, 0);
-        }
+        if constexpr (OWN_D)
+            if (i0 == lo) {
+                RowStep<D, 1> one;
+                one.x[0] = *reinterpret_cast<const f32x4*>(Oh + at);
+                Dt = one.dot(g, 0);
+            }
         k.clear_past(i0, t, lane);
 #pragma unroll
         for (int u = 0; u < Step::kLoads; ++u) {
@@ -185,7 +187,7 @@ __device__ __forceinline__ void dq_row(const float* Qh, const float* Kh, const f
     dq = Step::group_sum(dq);
     if (r == 0) *reinterpret_cast<f32x4*>(dQh + at) = dq * scale;
     if (lane == 0) {
-        if (Oh != nullptr) Dh[t] = Dt;
+        if constexpr (OWN_D) Dh[t] = Dt;
         dc_rowh[t] = (float)rs;
     }
 }
@@ -238,28 +240,32 @@ __device__ __forceinline__ void dkv_row(const float* Q, const float* Kh, const f
         *reinterpret_cast<f32x4*>(dVh + at) = dv;
     }
 }
-// Both: the first workgroups take keys (the longer rows), the others queries.  D_t has been formed (rowdot_f32_kernel).  In two
-// launches, D formed by the first, neither pass of a small problem filled the chip (B1 H4 N300 d64: 35.5 us, 24.5 in one; B4 H8 N200
-// w100 35.0 / 22.8; 256 rows, w = 64 14.0 / 11.8).
-template <int D>
+// Both in one launch (the first workgroups take keys, the longer rows; D_t has been formed by rowdot_f32_kernel), or one of them (the
+// queries, which then form D_t, first).  In two launches neither pass of a small problem fills the chip (B1 H4 N300 d64: 35.5 us,
+// 24.5 in one; B4 H8 N200 w100 35.0 / 22.8; 256 rows, w = 64 14.0 / 11.8).  f32_rows_in_one_launch has the line.
+enum F32Pass { kF32Both, kF32Queries, kF32Keys };
+template <int D, F32Pass PASS>
 __global__ __launch_bounds__(64 * kF32Waves) void bwd_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO,
-    const float* __restrict__ c, const float* __restrict__ L, float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dK,
-    float* __restrict__ dV, float* __restrict__ dc_col, float* __restrict__ dc_row, int N, int w, float scale, int key_blocks, int H, int G) {
-    __shared__ f32x4 rows_s[kF32Waves][64];
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ O,
+    const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L, float* __restrict__ Dv, float* __restrict__ dQ,
+    float* __restrict__ dK, float* __restrict__ dV, float* __restrict__ dc_col, float* __restrict__ dc_row, int N, int w, float scale,
+    int key_blocks, int H, int G) {
+    __shared__ f32x4 rows_s[PASS == kF32Queries ? 1 : kF32Waves][64];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rows_per_head = (N + kF32Waves - 1) / kF32Waves;
-    const bool keys = (int)blockIdx.x < key_blocks;
-    const int block = (int)blockIdx.x - (keys ? 0 : key_blocks), head = block / rows_per_head, row = block % rows_per_head * kF32Waves + wv;
+    const bool keys = PASS == kF32Both ? (int)blockIdx.x < key_blocks : PASS == kF32Keys;
+    const int block = (int)blockIdx.x - (PASS == kF32Both && !keys ? key_blocks : 0);
+    const int head = block / rows_per_head, row = block % rows_per_head * kF32Waves + wv;
     if (row >= N) return;  // whole wave leaves; no workgroup barriers are used
     if (keys) {
         const int Hkv = H / G;
         const size_t kvo = (size_t)head * N * D;
-        dkv_row<D, kRowLoads>(Q, K + kvo, V + kvo, dO, c, L, Dv, dK + kvo, dV + kvo, dc_col, rows_s[wv], (head / Hkv) * H + (head % Hkv) * G, G,
-                              row, N, w, scale, lane);
+        dkv_row<D, kRowLoads>(Q, K + kvo, V + kvo, dO, c, L, Dv, dK + kvo, dV + kvo, dc_col, rows_s[PASS == kF32Queries ? 0 : wv],
+                              (head / Hkv) * H + (head % Hkv) * G, G, row, N, w, scale, lane);
     } else {
         const size_t ho = (size_t)head * N * D, kvo = (size_t)kv_head_of(head, H, G) * N * D, rows = (size_t)head * N;
-        dq_row<D, kRowLoads>(Q + ho, K + kvo, V + kvo, nullptr, dO + ho, c + rows, L + rows, Dv + rows, dQ + ho, dc_row + rows, row, w, scale, lane);
+        dq_row<D, kRowLoads, PASS == kF32Queries>(Q + ho, K + kvo, V + kvo, O + ho, dO + ho, c + rows, L + rows, Dv + rows, dQ + ho,
+                                                  dc_row + rows, row, w, scale, lane);
     }
 }
 
@@ -810,8 +816,8 @@ __device__ __forceinline__ void dq_f32_mfma(int block, const float* __restrict__
                 const size_t rows = (size_t)bh * N;
 #pragma unroll 1
                 for (int row = qw0; row < min(N, qw0 + 32); ++row)
-                    dq_row<D, kRowLoads>(Q + ho, Kh, Vh, nullptr, dO + ho, ch, L + rows, const_cast<float*>(Dv + rows), dQ + ho, dc_row + rows, row, w,
-                              scale, lane);
+                    dq_row<D, kRowLoads, false>(Q + ho, Kh, Vh, nullptr, dO + ho, ch, L + rows, Dv + rows, dQ + ho, dc_row + rows, row, w, scale,
+                                                lane);
             } else if (t < N) {
                 float* out = dQ + ho + (size_t)t * D;
 #pragma unroll
@@ -1168,17 +1174,34 @@ static void launch_passes(long key_blocks, long query_blocks, int threads, Launc
     launch(0, (int)query_blocks);
 }
 
+// One launch for both passes of the row kernels, unless the chip is full anyway and a row is one step (d = 128, 8 keys): then the
+// row-dot launch's second reading of dO and the registers of the longer pass, which the query rows take too, are all that is left of
+// it.  Two launches / one, us: B48 H24/6 N695 w5 912 / 1030, B57 H6 N1480 w7 758 / 848, B15 H6 N739 w4 92 / 98; 8192 rows of w <= 8
+// equal; with windows of 9 to 32 one launch is up to 1.2 times as fast at every size, at d = 64 always.
+static bool f32_rows_in_one_launch(long rows, int N, int d, int w) { return d == 64 || (w < N ? w : N) > 8 || rows <= 8192; }
+
 template <int D>
 static hipError_t launch_bwd_f32_rows(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,
                                       const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, int B,
                                       int H, int Hkv, int N, int w, float scale, hipStream_t s) {
     const int per_head = (N + kF32Waves - 1) / kF32Waves;
+    auto launch = [&](auto kernel, int key_blocks, int blocks) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * kF32Waves), 0, s, Q, K, V, O, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, N, w, scale,
+                           key_blocks, H, H / Hkv);
+    };
+    if (!f32_rows_in_one_launch((long)B * H * N, N, D, w)) {
+        {
+            ProfScope prof(kKernDq, s);
+            launch(bwd_f32_kernel<D, kF32Queries>, 0, B * H * per_head);
+        }
+        ProfScope prof(kKernDkv, s);
+        launch(bwd_f32_kernel<D, kF32Keys>, 0, B * Hkv * per_head);
+        return hipGetLastError();
+    }
     ProfScope prof(kKernDkv, s);  // one record for the two launches
     launch_rowdot_f32<D>(O, dO, Dv, (long)B * H * N, s);
-    launch_passes((long)B * Hkv * per_head, (long)B * H * per_head, 64 * kF32Waves, [&](int key_blocks, int blocks) {
-        hipLaunchKernelGGL((bwd_f32_kernel<D>), dim3(blocks), dim3(64 * kF32Waves), 0, s, Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, N, w,
-                           scale, key_blocks, H, H / Hkv);
-    });
+    launch_passes((long)B * Hkv * per_head, (long)B * H * per_head, 64 * kF32Waves,
+                  [&](int key_blocks, int blocks) { launch(bwd_f32_kernel<D, kF32Both>, key_blocks, blocks); });
     return hipGetLastError();
 }
 

@@ -129,15 +129,6 @@ __device__ __forceinline__ void dma16_stream(const void* sbase, unsigned voff, c
         : "s"(lds_addr), "v"(voff), "s"(sbase)
         : "memory");
 }
-__device__ __forceinline__ void dma4(const void* sbase, unsigned voff, const void* lds_base) {
-    const unsigned lds_addr = (unsigned)(uintptr_t)lds_base;
-    unsigned saved;
-    asm volatile(
-        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, %3\n\ts_mov_b32 m0, %0"
-        : "=&s"(saved)
-        : "s"(lds_addr), "v"(voff), "s"(sbase)
-        : "memory");
-}
 // A pointer that is the same in every lane, moved into scalar registers (the first lane's value).
 __device__ __forceinline__ void* uniform_ptr(void* p) {
     const uint64_t a = reinterpret_cast<uint64_t>(p);

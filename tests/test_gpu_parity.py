@@ -748,6 +748,21 @@ def test_f32_row_steps(g, oracle, B, H, Hkv, N, d, w):
     check_grads(got, ref, 1e-5, "f32 row steps")
 
 
+@pytest.mark.parametrize("B,H,Hkv,N,d,w,two", [
+    # rows of one step, 8 keys at d = 128, and more of them than 8192: a launch for each pass, the first forms D; just not
+    (3, 12, 4, 229, 128, 8, True), (2, 9, 9, 517, 128, 1, True), (61, 135, 135, 1, 128, 8, True),
+    (3, 12, 4, 227, 128, 8, False), (3, 12, 4, 229, 128, 9, False), (3, 12, 4, 229, 64, 8, False),
+])
+def test_backward_f32_rows_in_two_launches(g, oracle, B, H, Hkv, N, d, w, two):
+    note("f32 rows, two launches", B, H, Hkv, N, d, w)
+    wl = gi.custom("f32two", B, H, N, d, w, "f32", alpha_mu=-1.0, index=30, backward=True, kv_heads=Hkv)
+    results = []
+    names = launched(g, lambda: results.extend(run_gqa(g, oracle, wl)))
+    assert ("bwd_dq" in names) == two and "bwd_rowdot" not in names
+    got, ref = results
+    check_grads(got, ref, 1e-5, "f32 rows, two launches", tiny=N == 1)
+
+
 @pytest.mark.parametrize("B,H,Hkv,N,d,w", [(2, 6, 6, 300, 128, 77), (2, 8, 2, 130, 64, 100), (4, 1, 1, 700, 64, 700), (1, 1, 1, 256, 64, 64)])
 def test_f32_rows_gate_gradient_cancels(g, oracle, B, H, Hkv, N, d, w):
     # d(alpha)[..., 0] is the sum of every dS as a column minus the sum of every dS as a row: zero.  The two kernels form the same
