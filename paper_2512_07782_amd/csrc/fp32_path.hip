@@ -497,9 +497,18 @@ struct F32FwdSmem {
     SplitTile<D> k[S], v[S];
     alignas(16) float c[S][32];
 };
-// Tiles dealt out by the length of their bands (tile_of_block) where these differ enough to pay for the keys of more heads
-// at a time: backward B1 H32 N2048 d128 causal 786 -> 576 us, B16 H16 N300 140 -> 127, B2 H16 N4096 w1024 1120 -> 1132.
-__device__ __forceinline__ bool f32_by_length(int heads, int N, int w) { return w >= N || (heads % 8 == 0 && 2L * w >= N); }
+// Order of the forward's tiles.  From the longest band to the shortest over all heads (tile_of_block), over 3418 shapes 0.95 of the
+// time of one head after another (B1 H12/6 N6219 d64 w2854 374 -> 261 us, B1 H10/5 N6600 d128 w918 290 -> 189), except
+//   heads that do not divide by the XCDs and are one tile each: the heads of a group on one XCD (B41 H12/3 N49 d128 21.8 -> 18.9)
+//   short bands, less than a tenth of the sequence, whose lengths hardly differ: d = 64 such heads one after another too (B11 H4/2
+//   N1091 w15 18.1 -> 16.0), d = 128 all heads from the sequence's start to its end (B3 H24/12 N4505 w228 397 -> 373)
+template <int D>
+__device__ __forceinline__ int f32_fwd_tile(int block, int heads, int tiles, int N, int w, int& head) {
+    const bool short_band = 10L * w < N, by_length = heads % 8 == 0 || (tiles > 1 && (D == 128 || !short_band));
+    int tile;
+    tile_of_block(block, heads, tiles, by_length, head, tile);
+    return by_length && (D == 64 || !short_band) ? tiles - 1 - tile : tile;
+}
 
 template <int D, int NW, int S>
 __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) void fwd_f32_mfma_kernel(
@@ -510,9 +519,8 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) voi
     extern __shared__ __align__(256) char smem_raw[];
     auto& sm = *reinterpret_cast<F32FwdSmem<D, S>*>(smem_raw);
     const int heads = total_tiles / num_qtiles;
-    int bh, qt;
-    tile_of_block((int)blockIdx.x, heads, num_qtiles, f32_by_length(heads, N, w), bh, qt);
-    const int q0 = (num_qtiles - 1 - qt) * BQ;  // longest bands first
+    int bh;
+    const int q0 = f32_fwd_tile<D>((int)blockIdx.x, heads, num_qtiles, N, w, bh) * BQ;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lq = lane & 31;
     const int qw0 = q0 + 32 * wv, t = qw0 + lq, tc = min(t, N - 1);
     const size_t ho = (size_t)bh * N * D, kvo = (size_t)kv_head_of(bh, H, G) * N * D;
@@ -664,7 +672,7 @@ __device__ __forceinline__ void dq_f32_mfma(int block, const float* __restrict__
     auto& sm = *reinterpret_cast<F32BwdSmem<D, NP>*>(smem_raw);
     const int heads = total_tiles / num_qtiles;
     int bh, qt;
-    tile_of_block(block, heads, num_qtiles, f32_by_length(heads, N, w), bh, qt);
+    tile_of_block(block, heads, num_qtiles, true, bh, qt);
     const int q0 = (num_qtiles - 1 - qt) * 32 * NP;  // longest bands first
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lq = lane & 31;
     const int qg = wv % NP;
@@ -844,7 +852,7 @@ __device__ __forceinline__ void dkv_f32_mfma(int block, const float* __restrict_
     auto& sm = *reinterpret_cast<F32BwdSmem<D, NP>*>(smem_raw);
     const int heads = total_tiles / num_ktiles;
     int bkv, kt;  // flat key/value head; the sequence's end, which few queries see, last
-    tile_of_block(block, heads, num_ktiles, f32_by_length(heads, N, w), bkv, kt);
+    tile_of_block(block, heads, num_ktiles, true, bkv, kt);
     const int k0 = kt * 32 * NP;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lk = lane & 31;
     const int kg = wv % NP;
@@ -1044,6 +1052,8 @@ __device__ __forceinline__ void dkv_f32_mfma(int block, const float* __restrict_
 // the dQ pass fills the CUs that those leave idle, at the end of a large problem or beside all of a small one.  Two launches /
 // one, whole backward: B1 H8 N1000 d128 w500 149 / 87 us, B1 H2 N2000 d64 causal 240 / 139, B1 H4 N4000 d128 w1000 250 / 155,
 // B2 H8/2 N515 d64 181 / 150, B2 H16 N1000 d128 causal 236 / 176, B2 H16 N4096 d128 w1024 1108 / 1065.
+// Both passes deal out their tiles by length, whatever the shape: over 1557 shapes 1.00 to 1.02 of the time of the best order in every
+// class of them, one head after another 1.0 to 1.19 (B1 H2 N10498 d128 w1236 326 -> 308).
 template <int D, int NP>
 __global__ __launch_bounds__(128 * NP, NP == 4 ? 1 : 2) void bwd_f32_mfma_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO,

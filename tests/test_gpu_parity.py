@@ -683,6 +683,23 @@ def test_forward_bf16_many_workgroups(g, oracle, B, H, N, d, w, heads, kernel):
     check_bf16_forward(O, L, O_ref, L_ref, tag="many workgroups")
 
 
+@pytest.mark.parametrize("B,H,N,d,w,heads", [
+    # the orders of the tiles: heads that do not divide by the XCDs and are one tile each, two tiles, bands just shorter than a tenth of
+    # the sequence and a tenth, d = 64 and 128; heads that divide, with a short band; the last tile of one row
+    (5, 60, 97, 128, 40, [0, 299]), (3, 100, 65, 64, 50, [0, 299]), (1, 9, 2049, 64, 204, [0, 8]), (1, 9, 2049, 64, 205, [0, 8]),
+    (1, 25, 1537, 128, 153, [0, 1, 24]), (1, 25, 1537, 128, 154, [0, 24]), (2, 32, 1025, 128, 70, [0, 1, 63]), (3, 7, 1025, 64, 600, [0, 20]),
+])
+def test_forward_f32_order_of_tiles(g, oracle, B, H, N, d, w, heads):
+    note("f32 order of tiles", B, H, N, d, w)
+    wl = gi.custom("order", B, H, N, d, w, "f32", alpha_mu=-1.5, index=29)
+    got = []
+    names = kernels(lambda: got.extend(run_forward(g, oracle, wl, heads=heads)))
+    assert any(n.startswith("fwd_f32_mfma_kernel") for n in names), names
+    O, L, O_ref, L_ref = got
+    assert rel_inf(O, O_ref) <= 1e-5
+    assert (np.abs(L - L_ref) <= 1e-5 * np.abs(L_ref).max() + 1e-5).all()
+
+
 # ------------------------------------------------------------------------------------------
 # grouped-query layout
 # ------------------------------------------------------------------------------------------
