@@ -426,7 +426,8 @@ def main() -> int:
         "gate_prefix_scan": ("hbm", 8.0 * bhn),
         "forward": ("mfma", f_fwd),
         "bwd_rowdot": ("hbm", bhn * (4.0 * d + 4.0)),
-        "bwd_dkv": ("mfma", (8.0 if bf else 10.0) * bhn * w * d),  # S, dP, dV, dK products (fp32: and dQ, the passes share a launch)
+        # S, dP, dV, dK products; and dQ where the two passes share a launch, which then has no record of its own
+        "bwd_dkv": ("mfma", (8.0 if prof.get("bwd_dq", (0, 0))[1] else 10.0) * bhn * w * d),
         "bwd_dq": ("mfma", 2.0 * bhn * w * d),      # the dQ product; its S and dP are recomputation (bf16: also forms D)
         "gate_grad_scan": ("hbm", 12.0 * bhn),
         "gate_activation_prefix_scan": ("hbm", 12.0 * bhn),   # h, beta in; c out

@@ -220,7 +220,9 @@ int gfwa_version(void);
  * 5 gate-gradient reverse scan, 6 gate activation + prefix scan, 7 gate activation backward,
  * 8 decoding step (per-chunk partials), 9 decoding step (merge of the chunks), 10 and 11 the two
  * launches of gfwa_gate_prefix_stp (segment sums, scan of the segments), 12 the segment sums of the
- * gate-gradient scan when the backward cuts few long rows into segments (its scan is then id 5);
+ * gate-gradient scan when the backward cuts few long rows into segments (its scan is then id 5).
+ * Where both passes of the backward go in one launch (fp32, and small bf16 problems) id 3 is that launch and
+ * id 4 stays empty; the row dots of small fp32 problems, and of small bf16 ones, are part of the same record.
  * gfwa_profile_kernel_name gives the same as text.
  * An event pair costs a few microseconds on the stream: kernels of about ten microseconds read
  * correspondingly longer than in a trace.  The three calls may come from any host thread (the records

@@ -6,8 +6,8 @@
 //        all query heads of the group - through LDS of its own, without a barrier, and the NW partial dK, dV are
 //        summed through LDS at the end
 // Latency bounds these sizes (first loads, first pass through the code, about 1 us per step of a wave), not a rate.
-// Where all workgroups of the two passes fit the chip together they go in one launch, D_t formed by both (bwd_in_one_launch in
-// bwd_bf16.hip has the line and more figures).
+// Where the workgroups of the two passes together are one a CU, or up to about two of long bands, they go in one launch, D_t formed by
+// both (bwd_in_one_launch in bwd_bf16.hip has the line and more figures).
 // Whole backward, us, with the 128-row kernels / with the kernels here, one launch each (B2 H8/2 N515 d64 in one: 22.2):
 //   B2 H8/2 N515 d64 w512   63.4 / 26.6      B2 H8/2 N515 d128 w512   80.7 / 47.9     B1 H4 N1000 d128 w333    39.9 / 24.9
 //   B1 H8 N700 d128 w1024   46.9 / 31.7      B1 H4 N5003 d64 w3000   117.6 / 74.2     B1 H16/4 N5003 d64 w3000  323 / 223 (dKV only)
@@ -374,8 +374,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void bwd_dkv_split_bf16_k
     dkv_split<D, NW, false>(a, (int)blockIdx.x);
 }
 
-// Both passes in one launch, for problems whose workgroups all fit the chip at once: one after the other each leaves most
-// of it idle and pays for its own launch.  The first dkv_blocks workgroups, the longer chains, are the dK/dV pass.
+// Both passes in one launch, for problems of few workgroups: one after the other each leaves most of the chip idle and pays for its own
+// launch.  The first dkv_blocks workgroups, the longer chains, are the dK/dV pass.  Every workgroup asks for the LDS of the larger half, about
+// 140 KB, so one is resident on a CU, and a second round starts behind the shortest of the first.
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void bwd_both_split_bf16_kernel(BwdBf16 a, int dkv_blocks, int num_qtiles) {
     if ((int)blockIdx.x < dkv_blocks) dkv_split<D, NW, true>(a, (int)blockIdx.x);

@@ -666,7 +666,10 @@ __device__ __forceinline__ int next3(int i) { return i == 2 ? 0 : i + 1; }
 // dQ and the row sums of dS (Alg. 3, query loop): the forward's layout.  S^T = K Q^T (wave 0 of a pair) and
 // dP^T = V dO^T (wave 1), then both take half of the block's keys: dS^T = P^T (dP^T - D), dQ^T += K^T dS^T.
 template <int D, int NP>
-__device__ __forceinline__ void dq_f32_mfma(int block, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dc_row, int N, int w, float scale, int num_qtiles, int total_tiles, int H, int G) {
+__device__ __forceinline__ void dq_f32_mfma(
+    int block, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO,
+    const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dQ,
+    float* __restrict__ dc_row, int N, int w, float scale, int num_qtiles, int total_tiles, int H, int G) {
     constexpr int KC = D / 16, DB = D / 32;
     extern __shared__ __align__(256) char smem_raw[];
     auto& sm = *reinterpret_cast<F32BwdSmem<D, NP>*>(smem_raw);
@@ -846,7 +849,10 @@ __device__ __forceinline__ void dq_f32_mfma(int block, const float* __restrict__
 // workgroup owns 32 NP keys, a pair of waves 32 of them, a lane one key.  S = Q K^T (wave 0) and dP = dO V^T (wave 1) with
 // 32-query tiles of Q and dO from LDS, then dV^T += dO^T P (wave 0) and, a block later, dK^T += Q^T dS (wave 1).
 template <int D, int NP>
-__device__ __forceinline__ void dkv_f32_mfma(int block, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dK, float* __restrict__ dV, float* __restrict__ dc_col, int N, int w, float scale, int num_ktiles, int total_tiles, int H, int G) {
+__device__ __forceinline__ void dkv_f32_mfma(
+    int block, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO,
+    const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dK,
+    float* __restrict__ dV, float* __restrict__ dc_col, int N, int w, float scale, int num_ktiles, int total_tiles, int H, int G) {
     constexpr int KC = D / 16, DB = D / 32;
     extern __shared__ __align__(256) char smem_raw[];
     auto& sm = *reinterpret_cast<F32BwdSmem<D, NP>*>(smem_raw);
@@ -1097,14 +1103,19 @@ static F32Fwd f32_fwd_shape(long BH, int N, int d, int w) {
     return BH * ((N + 255) / 256) >= device_cu_count() ? kF32Fwd256Double : kF32Fwd128Double;
 }
 
-// Which kernels serve a problem, by estimates of the two in us, fitted to 166 shapes (1 to 4096 sequences of 1 to 5001, w 1 .. 2000;
-// where the choice costs more than 8 % it costs at most 7 us forward, 10 backward).  A row of the one-wave-per-row kernels takes 0.25 ns and 0.3
-// ns per step of 16 (d = 64) or 8 keys, and the longest row's steps follow one another; the backward takes about twice that.
-// The matrix-core kernels walk a tile's band one 32-row block after another, in rounds of as many workgroups as the chip holds.
-// In the backward the key side of both walks the G query heads one after another.  (One-wave-per-row / matrix cores: 256 rows,
-// w = 64, d = 64: forward 4.5 / 12 us, backward 14 / 28; 512 causal rows, 4 heads, d = 128: 48 / 51, 130 / 122; 1100 rows, w = 400, 4 heads,
-// d = 128: 68 / 57, 177 / 129; 4096 sequences of 16, d = 64: 34 / 25, 82 / 105; 2048 of 8, d = 128: 10 / 33, 35 / 140; 2048 of 64, d = 128: 299 / 81,
-// 769 / 290.)
+// Which kernels serve a problem.  Forward, by estimates of the two in us, fitted to 166 shapes (1 to 4096 sequences of 1 to 5001, w 1 ..
+// 2000; where the choice costs more than 8 % it costs at most 7 us).  A row of the one-wave-per-row kernels takes 0.25 ns and 0.3 ns per step
+// of 16 (d = 64) or 8 keys, and the longest row's steps follow one another.  The matrix-core kernels walk a tile's band one 32-row block
+// after another, in rounds of as many workgroups as the chip holds.  (Row / matrix-core kernels: 256 rows, w = 64, d = 64: 4.5 / 12 us; 512
+// causal rows, 4 heads, d = 128: 48 / 51; 1100 rows, w = 400, 4 heads, d = 128: 68 / 57; 4096 sequences of 16, d = 64: 34 / 25; 2048 of 8, d = 128:
+// 10 / 33; 2048 of 64, d = 128: 299 / 81.)
+// Backward, a line on the safe side of the row kernels, whose gate gradient is the more exact one: they form the same dS in both passes
+// and add it up in fp64 (against fp64, error over norm, 26 shapes of 60 to 1100 rows: dQ, dK, dV 1.3e-7 to 3.2e-7 with either, d(alpha) 2.7e-7
+// to 1.9e-6 and 4.2e-7 to 2.5e-6, 1.1 to 3.9 times as much with the matrix cores at 25 of them).  The terms are those of the two passes one
+// after another, the key side walking the G query heads in turn.  Over 10315 shapes (1 to 64 sequences of 1 to 16384, 1 to 8 query heads on a
+// key/value head), one launch for both passes, the row kernels serve 6344, and are slower by more than a tenth at 185 of those (up to
+// 1.56: B3 H1 N885 d64 97 / 69 us, B3 H14 N89 d128 36 / 26); of the others the matrix-core kernels are slower by more than 8 % at 52 (up to 1.28:
+// B9 H18/3 N134 d64 w36 49 / 62).
 static bool f32_use_mfma(bool backward, int B, int H, int Hkv, int N, int d, int w) {
     const double cus = device_cu_count(), BH = (double)B * H, wc = w < N ? w : N, G = H / Hkv, wide = d / 64.0;
     const double step = kRowLoads * 256.0 / d, longest = ceil(wc / step), rows = BH * N * 1e-3;
@@ -1186,7 +1197,7 @@ static void launch_passes(long key_blocks, long query_blocks, int threads, Launc
 
 // One launch for both passes of the row kernels, unless the chip is full anyway and a row is one step (d = 128, 8 keys): then the
 // row-dot launch's second reading of dO and the registers of the longer pass, which the query rows take too, are all that is left of
-// it.  Two launches / one, us: B48 H24/6 N695 w5 912 / 1030, B57 H6 N1480 w7 758 / 848, B15 H6 N739 w4 92 / 98; 8192 rows of w <= 8
+// it.  Two launches / one, us: B48 H24/6 N695 w5 939 / 1051, B57 H6 N1480 w7 796 / 853, B15 H6 N739 w4 91 / 95; 8192 rows of w <= 8
 // equal; with windows of 9 to 32 one launch is up to 1.2 times as fast at every size, at d = 64 always.
 static bool f32_rows_in_one_launch(long rows, int N, int d, int w) { return d == 64 || (w < N ? w : N) > 8 || rows <= 8192; }
 

@@ -240,8 +240,8 @@ __global__ __launch_bounds__(64 * WAVES) void segment_sum_kernel(const float* __
 // 4.3 against 6.5; 300 rows of 8192: 5.3 against 6.6), and for segments (scan and sums of 8 rows of 32768: 5.8 against 6.2).
 // A workgroup alone on its CU has no other to hide its vector work and its scattered accesses behind, and sixteen waves
 // share them out: up to one per CU, sixteen are better with the activation (64 rows of 4096: 3.4 against 3.8 us, of 8192:
-// 4.9 against 6.3) and for whole rows of one chunk (64 rows of 515: 2.9 against 3.4; of 4096, in front of a forward that
-// displaces the inputs: the pair 67.7 against 68.8).
+// 4.9 against 6.3) and for whole rows (64 rows of 515: 2.9 against 3.2; of 4096, in front of a forward that displaces the inputs: the
+// pair 67.7 against 68.8; of 6000, two chunks: 4.0 against 4.2, of exactly two 3.96 against 3.86).
 // Longer rows keep a CU busy with one workgroup after another's barrier, and the activation is bound by vector work: sixteen
 // waves cover that (100 rows of 262144 with the activation: 127 against 249 us; sums of 512 segments with it: 7.0 against 8.0).
 static bool scan_four_waves(bool activation, bool segment, long workgroups, int len) {

@@ -1263,7 +1263,7 @@ def test_random_shapes_forward_backward(g, oracle, ws_variant, dtype):
 
 
 def test_gate_kernels_with_pointers_off_the_16_byte_grid(g, oracle):
-    # 4-byte aligned but not 16-byte aligned buffers take the element-wise path of the scan kernels
+    # buffers that are 4-byte but not 16-byte aligned: the scan kernels' accesses of four elements at any address, one by one at a row's end
     B, H, N = 2, 3, 1000
     wl = gi.custom("unal", B, H, N, 64, 8, alpha_mu=-1.0, index=5)
     h, beta = gi.make_gate_inputs(wl)
