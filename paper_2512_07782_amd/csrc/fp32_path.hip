@@ -242,7 +242,7 @@ __device__ __forceinline__ void dkv_row(const float* Q, const float* Kh, const f
 }
 // Both in one launch (the first workgroups take keys, the longer rows; D_t has been formed by rowdot_f32_kernel), or one of them (the
 // queries, which then form D_t, first).  In two launches neither pass of a small problem fills the chip (B1 H4 N300 d64: 35.5 us,
-// 24.5 in one; B4 H8 N200 w100 35.0 / 22.8; 256 rows, w = 64 14.0 / 11.8).  f32_rows_in_one_launch has the line.
+// 24.5 in one; B4 H8 N200 w100 35.0 / 22.8; 256 rows, w = 64 14.0 / 11.8).  f32_rows_in_two_launches has the line.
 enum F32Pass { kF32Both, kF32Queries, kF32Keys };
 template <int D, F32Pass PASS>
 __global__ __launch_bounds__(64 * kF32Waves) void bwd_f32_kernel(
@@ -1199,7 +1199,7 @@ static void launch_passes(long key_blocks, long query_blocks, int threads, Launc
 // row-dot launch's second reading of dO and the registers of the longer pass, which the query rows take too, are all that is left of
 // it.  Two launches / one, us: B48 H24/6 N695 w5 939 / 1051, B57 H6 N1480 w7 796 / 853, B15 H6 N739 w4 91 / 95; 8192 rows of w <= 8
 // equal; with windows of 9 to 32 one launch is up to 1.2 times as fast at every size, at d = 64 always.
-static bool f32_rows_in_one_launch(long rows, int N, int d, int w) { return d == 64 || (w < N ? w : N) > 8 || rows <= 8192; }
+static bool f32_rows_in_two_launches(long rows, int N, int w) { return (w < N ? w : N) <= 8 && rows > 8192; }
 
 template <int D>
 static hipError_t launch_bwd_f32_rows(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,
@@ -1210,15 +1210,16 @@ static hipError_t launch_bwd_f32_rows(const float* Q, const float* K, const floa
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * kF32Waves), 0, s, Q, K, V, O, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, N, w, scale,
                            key_blocks, H, H / Hkv);
     };
-    if (!f32_rows_in_one_launch((long)B * H * N, N, D, w)) {
-        {
-            ProfScope prof(kKernDq, s);
-            launch(bwd_f32_kernel<D, kF32Queries>, 0, B * H * per_head);
+    if constexpr (D == 128)
+        if (f32_rows_in_two_launches((long)B * H * N, N, w)) {
+            {
+                ProfScope prof(kKernDq, s);
+                launch(bwd_f32_kernel<D, kF32Queries>, 0, B * H * per_head);
+            }
+            ProfScope prof(kKernDkv, s);
+            launch(bwd_f32_kernel<D, kF32Keys>, 0, B * Hkv * per_head);
+            return hipGetLastError();
         }
-        ProfScope prof(kKernDkv, s);
-        launch(bwd_f32_kernel<D, kF32Keys>, 0, B * Hkv * per_head);
-        return hipGetLastError();
-    }
     ProfScope prof(kKernDkv, s);  // one record for the two launches
     launch_rowdot_f32<D>(O, dO, Dv, (long)B * H * N, s);
     launch_passes((long)B * Hkv * per_head, (long)B * H * per_head, 64 * kF32Waves,

@@ -58,7 +58,7 @@ LIB = {
     # fp32 storage
     "fwd_f32_mfma_kernel": "forward", "fwd_f32_kernel": "forward", "rowdot_f32_kernel": "bwd_rowdot",
     "bwd_both_split_bf16_kernel": "bwd_dkv",  # one launch for both passes here and below
-    "bwd_f32_mfma_kernel": "bwd_dkv", "bwd_f32_kernel": "bwd_dkv",
+    "bwd_f32_mfma_kernel": "bwd_dkv", "bwd_f32_kernel": "bwd_dkv", "bwd_f32_kernel<128, (gfwa::F32Pass)1>": "bwd_dq",
 }
 # the long_bwd workload of bench.py
 B, H, N, D, W = 1, 32, 16384, 128, 1024
