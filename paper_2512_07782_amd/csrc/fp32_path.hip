@@ -1197,9 +1197,9 @@ static void launch_passes(long key_blocks, long query_blocks, int threads, Launc
 
 // One launch for both passes of the row kernels, unless the chip is full anyway and a row is one step (d = 128, 8 keys): then the
 // row-dot launch's second reading of dO and the registers of the longer pass, which the query rows take too, are all that is left of
-// it.  Two launches / one, us: B48 H24/6 N695 w5 939 / 1051, B57 H6 N1480 w7 796 / 853, B15 H6 N739 w4 91 / 95; 8192 rows of w <= 8
-// equal; with windows of 9 to 32 one launch is up to 1.2 times as fast at every size, at d = 64 always.
-static bool f32_rows_in_two_launches(long rows, int N, int w) { return (w < N ? w : N) <= 8 && rows > 8192; }
+// it.  Two launches / one, us: B48 H24/6 N695 w5 939 / 1051, B57 H6 N1480 w7 796 / 853, B15 H6 N739 w4 91 / 95; 16384 rows of
+// w <= 8 equal, of grouped heads 1.02 (H32/8 N686 w7 38 / 35); with windows of 9 to 32 one launch is up to 1.2 times as fast at every size, at d = 64 always.
+static bool f32_rows_in_two_launches(long rows, int N, int w) { return (w < N ? w : N) <= 8 && rows > 32768; }
 
 template <int D>
 static hipError_t launch_bwd_f32_rows(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,

@@ -766,9 +766,9 @@ def test_f32_row_steps(g, oracle, B, H, Hkv, N, d, w):
 
 
 @pytest.mark.parametrize("B,H,Hkv,N,d,w,two", [
-    # rows of one step, 8 keys at d = 128, and more of them than 8192: a launch for each pass, the first forms D; just not
-    (3, 12, 4, 229, 128, 8, True), (2, 9, 9, 517, 128, 1, True), (61, 135, 135, 1, 128, 8, True),
-    (3, 12, 4, 227, 128, 8, False), (3, 12, 4, 229, 128, 9, False), (3, 12, 4, 229, 64, 8, False),
+    # rows of one step, 8 keys at d = 128, and more of them than 32768: a launch for each pass, the first forms D; just not
+    (12, 12, 4, 229, 128, 8, True), (8, 9, 9, 517, 128, 1, True), (9, 61, 61, 61, 128, 8, True),
+    (12, 12, 4, 227, 128, 8, False), (12, 12, 4, 229, 128, 9, False), (3, 12, 4, 229, 64, 8, False),
 ])
 def test_backward_f32_rows_in_two_launches(g, oracle, B, H, Hkv, N, d, w, two):
     note("f32 rows, two launches", B, H, Hkv, N, d, w)
