@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgfwa.so")
 CALL_LIB = os.path.join(HERE, "_gfwa_call.so")  # the native half of the Python binding (host code only)
-SOURCES = ["api.hip", "gate_scan.hip", "fp32_path.hip", "fwd_bf16.hip", "fwd_split_bf16.hip", "bwd_bf16.hip", "bwd_split_bf16.hip", "decode.hip", "probe.hip"]
+SOURCES = ["api.hip", "gate_scan.hip", "fp32_path.hip", "fwd_bf16.hip", "fwd_split_bf16.hip", "key_reach.hip", "bwd_bf16.hip", "bwd_split_bf16.hip", "decode.hip", "probe.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
     # packed fp32 VALU ops are kept off on the test machines

@@ -1,0 +1,214 @@
+// How far the band of a tile reaches before the gate has erased it.
+//
+// exp2 returns zero for every argument below -126 (the smallest normal number; measured over -120 .. -151).  A key so far behind a
+// query that its score lies more than that below the query's reference has a probability of exactly zero, and then every
+// product it enters is zero: leaving it out changes no bit of O, L or a gradient.  The gate's decay grows along the band and
+// soon outweighs what a score can add, which the norms bound: scale |q.k| <= scale |q| |k|.  (Gates of softplus(N(-2, 1))
+// decay by 190 over 1024 keys, unit-variance rows of d = 128 have |q| |k| / sqrt(d) of 11 to 15: the far 480 keys are erased.)
+//
+// So a pass over the rows in front of the kernels takes the largest norm of every block of them, and a workgroup shortens its band, in front
+// of its first step, by the blocks at the far end that are erased for all rows of its tile.  The pass costs one reading of a
+// matrix or two, the band of a step as many readings from the L2 as there are tiles in a window; workgroups that look at the rows of their
+// band by themselves read as much as the steps they save (forward B4 H16 N8192 d128 w1024, gates as above: 288 us without, 284 so).
+// Blocks whose gate decays too little read nothing (reach_pays).  A row that is not finite keeps its block, and a kept
+// block all that lie in front of it: zero times infinity is NaN, here as in the kernels without this.
+//
+// The blocks' values travel in the rows of an output that is not written yet (O in front of the forward, dalpha in front of the
+// backward), so that no call needs more memory for them.
+//
+// Measured, us, whole bands / shortened, the pass for the norms included; gates of softplus(N(mu, 1)):
+//                                        mu        -3           -2           -1
+//   forward   B4 H16   N8192 d128 w1024        322 / 327    301 / 266    293 / 201
+//             B1 H32/8 N8192 d128 w4096        378 / 220    372 / 131    373 / 100
+//             B4 H16   N4096 d64  causal       154 / 118    150 /  79    153 /  59
+//   backward  B4 H16   N8192 d128 w1024       1197 /1195   1061 / 835   1043 / 619
+//             B1 H32/8 N8192 d128 w4096       1427 / 670   1399 / 386   1390 / 269
+//             B4 H16/4 N4096 d64  causal       575 / 347    555 / 200    552 / 133
+//   fp32, whole step  B2 H16 N4096 d128 w1024              1430 /1082   1430 / 745
+#pragma once
+#include <type_traits>
+
+#include "tile_stage.h"
+
+namespace gfwa {
+
+// Base-2 exponent below which a probability counts as zero: 126, and 1 for the roundings of scores and references.
+constexpr float kErased = 127.f;
+// Whether it can pay to read norms: `decay` over the `len` rows that see a block (that it sees).  Scores of unit-variance rows add about
+// 14 to the 88 of kErased (in units of the gate); the pass reads for every row as much as 20 to 60 rows of a band take from the L2.  (Two
+// products compared, so that two kernels which ask the same always agree: there is nothing the compiler could fuse in one of them.)
+constexpr float kTypicalReach = 104.f;
+constexpr int kFewRows = 128;
+__device__ __forceinline__ bool reach_pays(float decay, int len) {
+    return decay > kTypicalReach && decay * (float)(len - kFewRows) > kTypicalReach * (float)len;
+}
+
+// Integers in the order of the floats (its own inverse); NaN, which must not let anything be erased, as the lowest or the highest.
+__device__ __forceinline__ int int_order(int bits) { return bits ^ ((bits >> 31) & 0x7fffffff); }
+__device__ __forceinline__ int lowest_order(float x) { return x == x ? int_order(__float_as_int(x)) : (int)0x80000000; }
+__device__ __forceinline__ int highest_order(float x) { return x == x ? int_order(__float_as_int(x)) : 0x7fffffff; }
+__device__ __forceinline__ float from_order(int o) { return __int_as_float(int_order(o)); }
+__device__ __forceinline__ bool finite(float x) { return fabsf(x) <= 3.402823466e38f; }
+
+// op over LANES (32 or 64) lanes of a wave, result in all of them: within four, eight and sixteen lanes by moves, then between
+// the rows of sixteen.
+template <int LANES, typename Op>
+__device__ __forceinline__ int over_lanes(int x, Op&& op) {
+    x = op(x, __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true));   // quad_perm 1 0 3 2
+    x = op(x, __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true));   // quad_perm 2 3 0 1
+    x = op(x, __builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true));  // row_half_mirror
+    x = op(x, __builtin_amdgcn_mov_dpp(x, 0x140, 0xF, 0xF, true));  // row_mirror
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = op((int)r[0], (int)r[1]);
+    if (LANES == 64) {
+        const auto q = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        x = op((int)q[0], (int)q[1]);
+    }
+    return x;
+}
+template <int LANES = 64>
+__device__ __forceinline__ int lanes_max(int x) {
+    return over_lanes<LANES>(x, [](int a, int b) { return max(a, b); });
+}
+template <int LANES = 64>
+__device__ __forceinline__ int lanes_min(int x) {
+    return over_lanes<LANES>(x, [](int a, int b) { return min(a, b); });
+}
+// Sum over the 8 or 16 lanes of a row, in all of them.
+template <int LANES>
+__device__ __forceinline__ float row_sum(float x) {
+    auto moved = [](float v, auto ctrl) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), decltype(ctrl)::value, 0xF, 0xF, true));
+    };
+    x += moved(x, std::integral_constant<int, 0xB1>{});
+    x += moved(x, std::integral_constant<int, 0x4E>{});
+    x += moved(x, std::integral_constant<int, 0x141>{});
+    if (LANES == 16) x += moved(x, std::integral_constant<int, 0x140>{});
+    return x;
+}
+// Sums of products of eight values; of squares as bits in the order of the floats (NaN above infinity).
+__device__ __forceinline__ float dot8(const bf16x8& a, const bf16x8& b, float x) {
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) x = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{a[e], a[e + 1]}, bf16x2{b[e], b[e + 1]}, x, false);
+    return x;
+}
+__device__ __forceinline__ int norm_bits(float n2) { return __float_as_int(n2) & 0x7fffffff; }
+
+// What a wave (or workgroup) knows of its own rows: the largest squared norm, times (scale log2 e)^2 and a thousandth for the
+// roundings of norms and products.
+__device__ __forceinline__ float reach2_of(int norm, float sl) { return __int_as_float(norm) * (sl * sl * 1.004f); }
+// room: what a score would have to exceed, in base-2 exponents, for a weight
+__device__ __forceinline__ bool is_erased(float n2, float reach2, float room) { return room > 0.f && n2 * reach2 < room * room; }
+
+// ---- keys in front of a query tile (forward).  A tile of queries from q0 finds in its own rows of O, as entry e, the largest squared norm
+// and the highest gate of the block of `block` keys that is e + 1 blocks before the one that holds q0 (key_reach.hip).
+struct KeyBlock {
+    float n2, c;
+};
+// Entries that `rows` rows of O have room for, T the storage type.  (A last tile of one to three rows may lack some: its band stays whole.)
+template <int D, typename T>
+__host__ __device__ __forceinline__ constexpr int key_blocks_in(int rows) { return rows * (D * (int)sizeof(T) / (int)sizeof(KeyBlock)); }
+// Entry `lane` of the tile whose first row of O is at `first`.
+template <int D, typename T>
+__device__ __forceinline__ KeyBlock key_block(const T* first, int rows, int lane) {
+    const bool there = lane < key_blocks_in<D, T>(rows);
+    const KeyBlock kb = reinterpret_cast<const KeyBlock*>(first)[there ? lane : 0];
+    return {there ? kb.n2 : INFINITY, kb.c};
+}
+// First key that the 32 queries of a wave need.  reach2 and `lowest` of the wave (lowest: the lowest exponent, relative to gate cbase,
+// that a weight of a row is measured against, less kErased).
+__device__ __forceinline__ int first_needed_key(const KeyBlock& kb, int q0, int k_lo, int block, float reach2, float lowest, float cbase, int lane) {
+    const int hi = q0 / block - 1, n = hi - k_lo / block + 1;  // (n <= 64, reach_of_forward sees to that)
+    const bool kept = lane < n && !is_erased(kb.n2, reach2, lowest - (kb.c - cbase) * kLog2e);
+    const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
+    const int farthest = mask ? 63 - __builtin_clzll(mask) : -1;
+    return max(k_lo, (hi - farthest) * block);
+}
+// The lowest (highest) of the waves' values, in all of them; for uniform control flow, at[WAVES] of LDS.
+template <int WAVES, bool LOWEST>
+__device__ __forceinline__ int over_waves(int x, int* at, int wv, int lane) {
+    if (lane == 0) at[wv] = x;
+    wg_barrier();
+    int r = at[0];
+#pragma unroll
+    for (int k = 1; k < WAVES; ++k) r = LOWEST ? min(r, at[k]) : max(r, at[k]);
+    return __builtin_amdgcn_readfirstlane(r);
+}
+
+// The forward's side of a query tile of bf16 rows: first key that the workgroup needs.  q: the lane's fragments of row tc (halves of a
+// wave: complementary columns), kd: the key of the same row.
+template <int D, int WAVES>
+__device__ __forceinline__ int forward_reach(const bf16x8 (&q)[D / 16], const bf16_t* kd, const KeyBlock& kb, float cq, int q0, int k_lo,
+                                             int block, float cbase, float sl, int* at, int wv, int lane) {
+    float q2 = 0.f, k2 = 0.f, own = 0.f;
+#pragma unroll
+    for (int kc = 0; kc < D / 16; ++kc) {
+        const bf16x8 k = *reinterpret_cast<const bf16x8*>(kd + 16 * kc);
+        q2 = dot8(q[kc], q[kc], q2);
+        k2 = dot8(k, k, k2);
+        own = dot8(q[kc], k, own);
+    }
+    q2 = xhalf_sum(q2);
+    // the reference is at least the score of the query's own key, which its wave meets first
+    const float edge = cq * kLog2e + sl * (xhalf_sum(own) - 1e-4f * sqrtf(q2 * xhalf_sum(k2)));
+    const float reach2 = reach2_of(lanes_max<32>(norm_bits(q2)), sl), lowest = from_order(lanes_min<32>(lowest_order(edge))) - kErased;
+    return over_waves<WAVES, true>(first_needed_key(kb, q0, k_lo, block, reach2, lowest, cbase, lane), at, wv, lane);
+}
+
+// ---- queries behind a key tile (backward).  The first rows of every 64-query block of dalpha hold the block's largest squared norm and
+// the lowest (c - c of the block's first row) + L of its rows (reach_of_queries, called beside the row dots), and the third one of every
+// 128-key tile, from the dK/dV kernel on, the last 64-query block that needs one of its keys.
+// With fp32 storage, where one launch holds both passes, they hold the block's keys instead: squared norm and highest gate.
+constexpr int kReachRows = 64, kReachNorm = 0, kReachEdge = 1, kReachLast = 2, kReachKeyNorm = 2, kReachKeyHigh = 3;
+// Last 64-query block from i_hi down to i_min + 1 that needs a key of a wave's, else i_min.  at: of the head.
+__device__ __forceinline__ int last_needing_block(const float* at, const float* ch, int i_min, int i_hi, int N, float reach2, float highest,
+                                                  float cbase, int lane) {
+    for (int top = i_hi; top > i_min; top -= 64) {
+        const int i = top - lane;
+        bool kept = i > i_min;
+        if (kept && 64 * i + kReachEdge < N) {
+            const float n2 = at[64 * i + kReachNorm], y = (ch[64 * i] - cbase) + at[64 * i + kReachEdge];
+            kept = !is_erased(n2, reach2, y * kLog2e - highest);
+        }
+        const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
+        if (mask) return top - __builtin_ctzll(mask);
+    }
+    return i_min;
+}
+
+// fp32: what the table says of the own rows of a tile, blocks i0 .. i1 of queries (of keys).
+struct OwnRows {
+    float reach2, edge;  // edge: relative to gate cbase, in base-2 exponents; the lowest of the queries, the highest of the keys
+};
+__device__ __forceinline__ OwnRows own_queries(const float* at, const float* ch, int i0, int i1, int N, float cbase, float sl) {
+    int norm = 0, edge = 0x7fffffff;
+    for (int i = i0; i <= i1; ++i) {
+        const bool there = 64 * i + kReachEdge < N;
+        norm = max(norm, there ? norm_bits(at[64 * i + kReachNorm]) : 0x7f800000);
+        if (there) edge = min(edge, lowest_order((ch[64 * i] - cbase) + at[64 * i + kReachEdge]));
+    }
+    return {reach2_of(norm, sl), from_order(edge) * kLog2e};
+}
+__device__ __forceinline__ OwnRows own_keys(const float* at, int i0, int i1, int N, float cbase, float sl) {
+    int norm = 0, edge = (int)0x80000000;
+    for (int i = i0; i <= i1; ++i) {
+        const bool there = 64 * i + kReachKeyHigh < N;
+        norm = max(norm, there ? norm_bits(at[64 * i + kReachKeyNorm]) : 0x7f800000);
+        if (there) edge = max(edge, highest_order(at[64 * i + kReachKeyHigh] - cbase));
+    }
+    return {reach2_of(norm, sl), from_order(edge) * kLog2e};
+}
+// First 64-key block from i_lo on that is needed, i_max if none before it is.
+__device__ __forceinline__ int first_needed_block(const float* at, int i_lo, int i_max, int N, float reach2, float lowest, float cbase, int lane) {
+    for (int base = i_lo; base < i_max; base += 64) {
+        const int i = base + lane;
+        bool kept = i < i_max;
+        if (kept && 64 * i + kReachKeyHigh < N)
+            kept = !is_erased(at[64 * i + kReachKeyNorm], reach2, lowest - (at[64 * i + kReachKeyHigh] - cbase) * kLog2e);
+        const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
+        if (mask) return base + __builtin_ctzll(mask);
+    }
+    return i_max;
+}
+
+}  // namespace gfwa

@@ -44,6 +44,8 @@
 // unrounded probabilities with plain adds (the packed dot-product instructions run on the matrix pipe
 // and would queue behind the MFMAs).
 //
+// Keys that the gate has erased for a whole tile are left out at the far end of its band (band_reach.h); the step knows nothing of it.
+//
 // Deferred running max.  exp2 is taken against the reference exponent m left by earlier blocks
 // without first looking for the block's own maximum; fp32 and bf16 share their exponent range, so a
 // probability may grow to 2^60 with no loss of precision.  Only when a lane's block sum exceeds that
@@ -52,6 +54,7 @@
 // visited from the diagonal backwards, where the gate bias is largest, so this is rare.
 #include <stddef.h>
 
+#include "band_reach.h"
 #include "gfwa_device.h"
 #include "gfwa_internal.h"
 #include "split_band.h"
@@ -67,6 +70,7 @@ struct FwdSmem {
     alignas(256) char k[2][kTileBytes];
     alignas(256) char v[2][kTileBytes];
     alignas(16) float g[2][kKeys];  // (c - c_base) / scale of the tile's keys
+    int needed[kFwdWaves];           // over_waves
 };
 
 // Longest bands (the end of the sequence) first.  Heads that do not divide by the XCDs go in contiguous ranges while bands are
@@ -89,7 +93,7 @@ template <int D, int NB>
 __device__ __forceinline__ void fwd_tile(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w, float scale_log2,
-    int num_qtiles, int total, int H, int G) {
+    int num_qtiles, int total, int H, int G, int reach_block) {
     constexpr int KC = D / 16, DB = D / 32, NV = 2 * DB;
     using Smem = FwdSmem<D, NB>;
     constexpr int kKeys = Smem::kKeys, kRowBytes = D * 2, kTileBytes = Smem::kTileBytes;
@@ -108,7 +112,8 @@ __device__ __forceinline__ void fwd_tile(
     const char* Kh = reinterpret_cast<const char*>(K + kv_off);
     const char* Vh = reinterpret_cast<const char*>(V + kv_off);
     const float* ch = c + (size_t)bh * N;
-    const int j_lo = max(0, q0 - w + 1) / kKeys, j_hi = (min(N, q0 + 128) - 1) / kKeys, ntiles = j_hi - j_lo + 1;
+    const int k_lo = max(0, q0 - w + 1), j_hi = (min(N, q0 + 128) - 1) / kKeys;
+    int ntiles = j_hi - k_lo / kKeys + 1;
     const int qw0 = q0 + 32 * wv;
     int T_first = ntiles, T_end = ntiles;  // the steps this wave computes in
     if (qw0 < N) {
@@ -147,6 +152,14 @@ __device__ __forceinline__ void fwd_tile(
         const bf16_t* qp = Q + head_off + (size_t)tc * D + 8 * h;
 #pragma unroll
         for (int kc = 0; kc < KC; ++kc) qf[kc] = *reinterpret_cast<const bf16x8*>(qp + 16 * kc);
+    }
+    if (reach_block != 0 && reach_pays(cbase - ch[k_lo], q0 - k_lo)) {  // the keys that the gate has erased for all 128 queries stay out
+        const int first = forward_reach<D, kFwdWaves>(qf, K + kv_off + (size_t)min(t, N - 1) * D + 8 * h,
+                                                      key_block<D>(O + head_off + (size_t)q0 * D, min(128, N - q0), lane), cq, q0, k_lo, reach_block,
+                                                      cbase, sl, sm.needed, wv, lane);
+        ntiles = j_hi - first / kKeys + 1;
+        T_first = min(T_first, ntiles);
+        T_end = min(T_end, ntiles);
     }
     unsigned ka, va, ga;  // LDS addresses of the lane's first fragments in the current slot
     {
@@ -303,16 +316,16 @@ template <int D>
 __global__ __launch_bounds__(64 * kFwdWaves, D == 64 ? 4 : 3) void fwd_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w, float scale_log2,
-    int num_qtiles, int total, int H, int G) {
-    fwd_tile<D, kFwdBlocks<D>>(Q, K, V, c, O, L, N, w, scale_log2, num_qtiles, total, H, G);
+    int num_qtiles, int total, int H, int G, int reach_block) {
+    fwd_tile<D, kFwdBlocks<D>>(Q, K, V, c, O, L, N, w, scale_log2, num_qtiles, total, H, G, reach_block);
 }
 // d = 128 with the step of d = 64, for launches that put few workgroups on a CU (fwd_two_blocks has the line and figures): with two
 // waves on a SIMD the exponentials of a block have to run beside the products of the same wave's other block.
 __global__ __launch_bounds__(64 * kFwdWaves, 2) void fwd_two_blocks_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w, float scale_log2,
-    int num_qtiles, int total, int H, int G) {
-    fwd_tile<128, 2>(Q, K, V, c, O, L, N, w, scale_log2, num_qtiles, total, H, G);
+    int num_qtiles, int total, int H, int G, int reach_block) {
+    fwd_tile<128, 2>(Q, K, V, c, O, L, N, w, scale_log2, num_qtiles, total, H, G, reach_block);
 }
 
 // What all 128-query tiles of a problem cost and what the longest does, counted in 64-key tiles plus two for each query tile's start
@@ -376,8 +389,10 @@ static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const 
         }
     }
     ProfScope prof(kKernForward, s);
+    const KeyReach reach = scale > 0.f ? reach_of_forward(B * H, N, D, w, 128, true) : KeyReach{0, 128};
+    if (hipError_t e = key_reach(reach, true, K, V, c, O, B, H, Hkv, N, D, w, s)) return e;
     hipLaunchKernelGGL(kernel, dim3(total), dim3(64 * kFwdWaves), lds, s, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, c,
-                       (bf16_t*)O, L, N, w, scale * kLog2e, nq, total, H, H / Hkv);
+                       (bf16_t*)O, L, N, w, scale * kLog2e, nq, total, H, H / Hkv, reach.block);
     return hipGetLastError();
 }
 

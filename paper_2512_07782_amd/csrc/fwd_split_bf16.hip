@@ -20,6 +20,7 @@
 // Products, layouts, gate and softmax are those of fwd_bf16.hip (a lane owns one query, S^T = K Q^T starts from the
 // gate, O^T += V^T P^T takes the S accumulators as its operand, deferred running maximum).  Steps outside a wave's own band only load, so that the loop that computes has no
 // branch around the accumulators (with one the compiler copies all of them twice per step).
+#include "band_reach.h"
 #include "gfwa_device.h"
 #include "gfwa_internal.h"
 #include "split_band.h"
@@ -30,7 +31,7 @@ template <int D, int NW, int QW, int KB, int RING>
 __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_split_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w, float scale_log2,
-    int num_qtiles, int BH, int H, int G) {
+    int num_qtiles, int BH, int H, int G, int reach_block) {
     using Band = SplitBand<D, NW, QW, KB, RING>;
     constexpr int KC = D / 16, DB = D / 32, KW = Band::KW;
     extern __shared__ __align__(256) char smem_raw[];
@@ -54,6 +55,11 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_split
     // used up here, so that the compiler does not wait for these loads (and every later one) inside the loop
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) GFWA_PIN(qf[kc]);
+    const int k_lo = max(0, q0 - w + 1);
+    if (reach_block != 0 && reach_pays(band.cbase - band.ch[k_lo], q0 - k_lo))  // what the gate has erased for all queries stays out
+        band.from(forward_reach<D, NW>(qf, K + kv_off + (size_t)tc * D + 8 * h, key_block<D>(O + head_off + (size_t)q0 * D, min(32 * QW, N - q0), lane), cq,
+                                       q0, k_lo, reach_block, band.cbase, sl, sm.needed, band.wv, lane),
+                  q0, w);
 
     f32x16 o[DB];
 #pragma unroll
@@ -177,9 +183,11 @@ static hipError_t launch_split(const void* Q, const void* K, const void* V, cons
         return e;
     const int nq = (N + 32 * QW - 1) / (32 * QW);
     ProfScope prof(kKernForward, s);
+    const KeyReach reach = scale > 0.f ? reach_of_forward(B * H, N, D, w, 32 * QW, true) : KeyReach{0, 32 * QW};
+    if (hipError_t e = key_reach(reach, true, K, V, c, O, B, H, Hkv, N, D, w, s)) return e;
     hipLaunchKernelGGL((fwd_split_bf16_kernel<D, NW, QW, KB, RING>), dim3((unsigned)(B * H) * nq), dim3((64 * NW)), sizeof(Smem),
                        s, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, c, (bf16_t*)O, L, N, w, scale * kLog2e, nq,
-                       B * H, H, H / Hkv);
+                       B * H, H, H / Hkv, reach.block);
     return hipGetLastError();
 }
 

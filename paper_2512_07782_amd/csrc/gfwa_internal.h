@@ -27,6 +27,13 @@ hipError_t forward_bf16(const void* Q, const void* K, const void* V, const float
                         int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
 double query_tile_fill(int BH, int N, int w, long slots);  // how full rounds of `slots` 128-query tiles are, 0 .. 1
 // The same for few or uneven query tiles, the band of a tile split over groups of waves (fwd_split_bf16.hip).
+// Values of the key blocks in front of the forward's query tiles (band_reach.h), in O: block keys each, 0 for none, for tiles of `tile` queries.
+struct KeyReach {
+    int block, tile;
+};
+KeyReach reach_of_forward(int BH, int N, int d, int w, int tile, bool bf16);
+hipError_t key_reach(const KeyReach& r, bool bf16, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv,
+                     int N, int d, int w, hipStream_t s);
 enum FwdSplit { kFwdSplitNone = 0, kFwdSplitNarrow, kFwdSplitMid, kFwdSplitWide };  // 32, 64, 128 queries per workgroup
 hipError_t forward_split_bf16(FwdSplit shape, const void* Q, const void* K, const void* V, const float* c, void* O,
                               float* L, int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);

@@ -60,6 +60,7 @@ struct SplitBandSmem {
     };
     float m[NW][64], l[NW][64];
     alignas(16) float g[NW][2][32 * KB];  // (c - c_base) / scale of the keys of a wave's tile
+    int needed[NW];                       // over_waves
 };
 
 template <int D, int NW, int QW, int KB, int RING>
@@ -93,20 +94,24 @@ struct SplitBand {
         qi = wv % QW;
         kg = wv / QW;
         loader.init(lane);
-        const int kt_lo = max(0, q0 - w + 1) / kKeys, qw0 = q0 + 32 * qi;
         kt_hi = (min(N, q0 + 32 * QW) - 1) / kKeys;
-        const int ntile = kt_hi - kt_lo + 1;
+        from(max(0, q0 - w + 1), q0, w);
+        c_next = mine > 0 ? gate_of(0) : 0.f;
+        if (mine > 0) issue(0);
+        cbase = ch[q0];
+    }
+    // The steps of a band that starts at key k_lo, in the window or behind what the gate has erased (at q0 at most).  Called again before
+    // the first step: tiles past the new start may have been requested then, and are waited for in merge.
+    __device__ __forceinline__ void from(int k_lo, int q0, int w) {
+        const int kt_lo = k_lo / kKeys, qw0 = q0 + 32 * qi, ntile = kt_hi - kt_lo + 1;
         mine = ntile > kg ? (ntile - kg + KW - 1) / KW : 0;
         steps = (ntile + KW - 1) / KW;
         s_first = s_end = 0;
         if (qw0 < N) {
-            const int n_first = kt_hi - (qw0 + 31) / kKeys, n_last = kt_hi - max(0, qw0 - w + 1) / kKeys;
+            const int n_first = kt_hi - (qw0 + 31) / kKeys, n_last = kt_hi - max(k_lo, qw0 - w + 1) / kKeys;
             s_first = n_first > kg ? min((n_first - kg + KW - 1) / KW, steps) : 0;
             s_end = n_last >= kg ? min(mine, (n_last - kg) / KW + 1) : 0;
         }
-        c_next = mine > 0 ? gate_of(0) : 0.f;
-        if (mine > 0) issue(0);
-        cbase = ch[q0];
     }
     __device__ __forceinline__ int first_key(int s) const { return (kt_hi - (s * KW + kg)) * kKeys; }
     __device__ __forceinline__ float gate_of(int s) const { return ch[min(first_key(s) + (KB == 1 ? lane & 31 : lane), N - 1)]; }
