@@ -1,7 +1,8 @@
 // GatedFWA backward for bf16 storage on gfx950 (paper App. E.2 / Alg. 3, re-designed for CDNA4).
 //
 // Four launches, no atomics, deterministic:
-//   1. rowdot:   D_t = <O_t, dO_t>                                   (HBM-bound)
+//   1. rowdot:   D_t = <O_t, dO_t>                                   (HBM-bound), norms of Q where the gate may have erased keys:
+//                launch 2 then leaves out the queries that see none of its keys, and launch 3 those keys (band_reach.h)
 //   2. dkv:      key-stationary.  A wave works on 32 keys, whose K and V are MFMA B operands (in
 //                registers at d = 64, staged in LDS at d = 128, see the two kernels), and streams
 //                64-query tiles of Q and dO through LDS (direct global->LDS loads):
@@ -27,6 +28,7 @@
 // exactly the error that would otherwise accumulate over the whole suffix in the reverse scan.
 #include <math.h>
 
+#include "band_reach.h"
 #include "gfwa_device.h"
 #include "gfwa_internal.h"
 #include "tile_stage.h"
@@ -36,26 +38,65 @@ namespace gfwa {
 constexpr float kPosBig = 1.0e30f;
 
 // ------------------------------------------------------------------------------------------
-// 1. D_t = <O_t, dO_t>
+// 1. D_t = <O_t, dO_t>, and what the dK/dV kernel asks of a block of queries (band_reach.h)
 // ------------------------------------------------------------------------------------------
+// A workgroup takes 64 rows of a head, 16 bytes of each matrix a lane and all of them in flight.  Q is read only where the gate decays
+// enough over the window that keys may be erased for these rows.  reach: dalpha, or nullptr.
 template <int D>
-__global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restrict__ O,
-                                                          const bf16_t* __restrict__ dO,
-                                                          float* __restrict__ Dv, long rows) {
+__global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO,
+                                                          const bf16_t* __restrict__ Q, const float* __restrict__ c,
+                                                          const float* __restrict__ L, float* __restrict__ Dv, float* __restrict__ reach, int N,
+                                                          int w, int blocks) {
     constexpr int LPR = D / 8;  // lanes per row, 16 bytes each
-    const long gid = (long)blockIdx.x * 256 + threadIdx.x;
-    const long r = gid / LPR;
-    const int part = (int)(gid % LPR);
-    float acc = 0.f;
-    if (r < rows) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8*>(O + r * D + part * 8);
-        const bf16x8 b = *reinterpret_cast<const bf16x8*>(dO + r * D + part * 8);
+    constexpr int kRows = 256 / LPR, kPasses = kReachRows / kRows;
+    __shared__ int norm_s, edge_s;
+    const int bh = (int)blockIdx.x / blocks, t0 = (int)blockIdx.x % blocks * kReachRows;
+    const size_t head = (size_t)bh * N;
+    const int part = threadIdx.x % LPR, r0 = t0 + threadIdx.x / LPR;
+    bf16x8 a[kPasses], b[kPasses];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc = fmaf((float)a[e], (float)b[e], acc);
+    for (int p = 0; p < kPasses; ++p) {
+        const size_t at = (head + min(r0 + p * kRows, N - 1)) * D + 8 * part;
+        a[p] = *reinterpret_cast<const bf16x8*>(O + at);
+        b[p] = *reinterpret_cast<const bf16x8*>(dO + at);
     }
+    const float c0 = c[head + t0];
+    const int far = max(0, t0 - w + 1);
+    const bool look = reach != nullptr && reach_pays(c0 - c[head + far], t0 - far);
+    if (look && threadIdx.x == 0) norm_s = 0, edge_s = 0x7fffffff;
+    float dot[kPasses];
 #pragma unroll
-    for (int d = LPR / 2; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
-    if (r < rows && part == 0) Dv[r] = acc;
+    for (int p = 0; p < kPasses; ++p) {
+        dot[p] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dot[p] = fmaf((float)a[p][e], (float)b[p][e], dot[p]);
+#pragma unroll
+        for (int d = LPR / 2; d >= 1; d >>= 1) dot[p] += __shfl_xor(dot[p], d, 64);
+        if (part == 0 && r0 + p * kRows < N) Dv[head + r0 + p * kRows] = dot[p];
+    }
+    if (look) {
+        int norm = 0, edge = 0x7fffffff;
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) {
+            const size_t row = head + min(r0 + p * kRows, N - 1);
+            const bf16x8 q = *reinterpret_cast<const bf16x8*>(Q + row * D + 8 * part);
+            // (D is not finite if a value of dO is not)
+            norm = max(norm, finite(dot[p]) ? norm_bits(row_sum<LPR>(dot8(q, q, 0.f))) : 0x7fffffff);
+            edge = min(edge, lowest_order((c[row] - c0) + L[row]));
+        }
+        norm = lanes_max(norm);
+        edge = lanes_min(edge);
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) {
+            atomicMax(&norm_s, norm);
+            atomicMin(&edge_s, edge);
+        }
+        __syncthreads();
+    }
+    if (reach != nullptr && threadIdx.x == 0) {
+        reach[head + t0 + kReachNorm] = look ? __int_as_float(norm_s) : INFINITY;
+        if (t0 + kReachEdge < N) reach[head + t0 + kReachEdge] = look ? from_order(edge_s) : 0.f;
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -64,16 +105,55 @@ __global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restri
 template <int D>
 struct DkvSmem {
     TilePairSmem<D> qg;                    // a = Q tile, b = dO tile
+    int needed[8];                         // over_waves
     alignas(16) float nl[2][kTileRows];    // -(L_t + c_t - c_base) / scale; -big for rows >= N
     alignas(16) float dvec[2][kTileRows];  // -D_t
 };
+
+// The last query tile (of 64) that a workgroup's 128 keys are streamed against: that of t_hi, or where the gate has erased all of them
+// before.  The waves' own 32 keys come as fragments or as matrices.  at: of the head (nullptr: t_hi's), needed: over_waves.  `key` is the lane's.
+template <int D>
+struct KeyFragments {
+    const bf16x8 (&k)[D / 16], (&v)[D / 16];
+    __device__ __forceinline__ void get(int kc, bf16x8& x, bf16x8& y) const { x = k[kc], y = v[kc]; }
+};
+struct KeyRows {
+    const bf16_t *k, *v;  // the lane's half row
+    __device__ __forceinline__ void get(int kc, bf16x8& x, bf16x8& y) const {
+        x = *reinterpret_cast<const bf16x8*>(k + 16 * kc), y = *reinterpret_cast<const bf16x8*>(v + 16 * kc);
+    }
+};
+template <int D, int WAVES, typename Keys>
+__device__ __forceinline__ int last_query_tile(const Keys& keys, const float* ch, float* at, int k0, int t_hi, int N, int key, float cbase, float sl,
+                                               int* needed, int wv, int lane) {
+    const int i_hi = t_hi / kTileRows, k1 = min(k0 + 128, N) - 1, i_min = k1 / kTileRows;
+    int last = i_hi;
+    if (at == nullptr) return last;
+    if (i_hi > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1)) {
+        float k2 = 0.f, v2 = 0.f;
+#pragma unroll
+        for (int kc = 0; kc < D / 16; ++kc) {
+            bf16x8 k, v;
+            keys.get(kc, k, v);
+            k2 = dot8(k, k, k2);
+            v2 = dot8(v, v, v2);
+        }
+        // (a value row that is not finite keeps everything: its dP is not either)
+        const int norm = lanes_max(finite(xhalf_sum(v2)) ? norm_bits(xhalf_sum(k2)) : 0x7fffffff);
+        const float highest = from_order(lanes_max(highest_order(ch[min(key, N - 1)] - cbase))) * kLog2e + kErased;
+        const int own = last_needing_block(at, ch, i_min, i_hi, N, reach2_of(norm, sl), highest, cbase, lane);
+        last = over_waves<WAVES, false>(own, needed, wv, lane);
+    }
+    if (threadIdx.x == 0 && k0 + kReachLast < N) reinterpret_cast<int*>(at)[k0 + kReachLast] = last;
+    return last;
+}
 
 template <int D>
 __global__ __launch_bounds__(kThreads, 1) void bwd_dkv_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
     const float* __restrict__ Dv, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV,
-    float* __restrict__ dc_col, int N, int w, float scale, int num_ktiles, int total_tiles, int H, int G) {
+    float* __restrict__ dc_col, float* reach, int N, int w, float scale, int num_ktiles, int total_tiles, int H, int G) {
     constexpr int BK = 128;  // keys per workgroup, 32 per wave
     constexpr int KC = D / 16, DB = D / 32;
     __shared__ DkvSmem<D> sm;
@@ -117,7 +197,7 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkv_bf16_kernel(
 
     // queries that can see a key of this tile: k0 <= t <= min(N-1, k0+BK-1+w-1)
     const int t_hi = (int)min((long)N - 1, (long)k0 + BK - 1 + (long)w - 1);
-    const int i_lo = k0 / kTileRows, i_hi = t_hi / kTileRows;
+    const int i_lo = k0 / kTileRows;
     const int ifull = N / kTileRows;
 
     TilePairLoader<D> loader;
@@ -159,6 +239,8 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkv_bf16_kernel(
         };
         loader.load(Qh, Gh, i_lo, ifull, N, sm.qg.a[0], sm.qg.b[0]);
         load_vec(i_lo);
+        const int i_hi = last_query_tile<D, 4>(KeyFragments<D>{kf, vf}, ch, reach == nullptr ? nullptr : reach + (size_t)bh * N, k0, t_hi, N, key,
+                                                 cbase, sl, sm.needed, wv, lane);
         store_vec(0);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -303,7 +385,7 @@ __global__ __launch_bounds__(2 * kThreads, 1) void bwd_dkv8_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
     const float* __restrict__ Dv, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV,
-    float* __restrict__ dc_col, char* __restrict__ ds_ws, int N, int w, float scale, int num_ktiles,
+    float* __restrict__ dc_col, float* reach, char* __restrict__ ds_ws, int N, int w, float scale, int num_ktiles,
     int total_tiles, int H, int G) {
     constexpr int BK = 128;  // keys per workgroup, 32 per wave
     constexpr int KC = D / 16, DB = D / 32;
@@ -333,6 +415,7 @@ __global__ __launch_bounds__(2 * kThreads, 1) void bwd_dkv8_bf16_kernel(
     const int key = kw0 + lk;
 
     // K^T and V^T fragments (B operands: column = key, k = head dimension) come from the staged tiles
+    const size_t own_row = head_off + (size_t)min(key, N - 1) * D + 8 * h;
     const char* ktile = sm8.kv.a[kg >> 1];
     const char* vtile = sm8.kv.b[kg >> 1];
     const int krow0 = 32 * (kg & 1);
@@ -348,7 +431,7 @@ __global__ __launch_bounds__(2 * kThreads, 1) void bwd_dkv8_bf16_kernel(
 
     // queries that can see a key of this tile: k0 <= t <= min(N-1, k0+BK-1+w-1)
     const int t_hi = (int)min((long)N - 1, (long)k0 + BK - 1 + (long)w - 1);
-    const int i_lo = k0 / kTileRows, i_hi = t_hi / kTileRows;
+    const int i_lo = k0 / kTileRows;
     const int ifull = N / kTileRows;
 
     // dS spill: 32-query blocks per head, slots per query block, this lane's 16-byte slot in the two pieces
@@ -405,6 +488,8 @@ __global__ __launch_bounds__(2 * kThreads, 1) void bwd_dkv8_bf16_kernel(
         };
         loader.load(Qh, Gh, i_lo, ifull, N, sm.qg.a[0], sm.qg.b[0]);
         load_vec(i_lo);
+        const int i_hi = last_query_tile<D, 8>(KeyRows{K + own_row, V + own_row}, ch, reach == nullptr ? nullptr : reach + (size_t)bh * N, k0, t_hi,
+                                                 N, key, cbase, sl, sm.needed, wv, lane);
         store_vec(0);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -613,6 +698,30 @@ __global__ __launch_bounds__(2 * kThreads, 1) void bwd_dkv8_bf16_kernel(
 // ------------------------------------------------------------------------------------------
 // 3. dQ, row sums: query-stationary
 // ------------------------------------------------------------------------------------------
+// Key tiles of 128 that the dK/dV pass has streamed against the queries of a dQ workgroup (kReachLast), 64 tiles at a time from `from` on.
+// The limits are requested when this is set up and waited for in `look`: the loads of the first key tile go out in between.
+struct SeenKeys {
+    const float* at;  // of the head, or nullptr: all
+    int from, hi, N, lane, last;
+    __device__ __forceinline__ SeenKeys(const float* reach, size_t head, int kt_lo, int kt_hi, int N_, int lane_)
+        : at(reach == nullptr ? nullptr : reach + head), from(kt_lo), hi(kt_hi), N(N_), lane(lane_) { request(); }
+    __device__ __forceinline__ void request() {
+        const int row = min(from + lane, hi) * 128 + kReachLast;  // (a tile of one or two keys has no room for it; it is the last, which all see)
+        last = at != nullptr && row < N ? reinterpret_cast<const int*>(at)[row] : 0x7fffffff;
+    }
+    __device__ __forceinline__ unsigned long long look(int i) const {  // tile from + bit: streamed against query tile i (of 64)
+        return __builtin_amdgcn_ballot_w64(last >= i || from + lane >= hi);
+    }
+    __device__ __forceinline__ int first(int i) {  // first such tile; `from` is at most 63 before it
+        unsigned long long mask;
+        while ((mask = look(i)) == 0) {
+            from += 64;
+            request();
+        }
+        return min(hi, from + (int)__builtin_ctzll(mask));
+    }
+};
+
 template <int D>
 struct DqSmem {
     TilePairSmem<D> kv;                // a = K tile, b = V tile
@@ -623,7 +732,7 @@ template <int D>
 __global__ __launch_bounds__(kThreads, 2) void bwd_dq_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ dO, const float* __restrict__ c, const float* __restrict__ L,
-    const float* __restrict__ Dv, bf16_t* __restrict__ dQ, float* __restrict__ dc_row, int N, int w,
+    const float* __restrict__ Dv, bf16_t* __restrict__ dQ, float* __restrict__ dc_row, const float* __restrict__ reach, int N, int w,
     float scale, int num_qtiles, int total_tiles, int H, int G) {
     constexpr int BR = 128;
     constexpr int KC = D / 16, DB = D / 32;
@@ -677,7 +786,9 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_bf16_kernel(
 
     const int k_lo = max(0, q0 - w + 1);
     const int k_hi = min(N, q0 + BR) - 1;
-    const int j_lo = k_lo / kTileRows, j_hi = k_hi / kTileRows;
+    SeenKeys seen(reach, (size_t)bh * N, k_lo / 128, k_hi / 128, N, lane);
+    int j_lo = k_lo / kTileRows;
+    const int j_hi = k_hi / kTileRows;
     const int jfull = N / kTileRows;
 
     TilePairLoader<D> loader;
@@ -687,6 +798,12 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_bf16_kernel(
         return ch[key];
     };
     loader.load(Kh, Vh, j_lo, jfull, N, sm.kv.a[0], sm.kv.b[0]);
+    const int j_seen = 2 * seen.first(q0 / kTileRows);
+    if (j_seen > j_lo) {  // the gate has erased the tiles before
+        j_lo = j_seen;
+        __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+        loader.load(Kh, Vh, j_lo, jfull, N, sm.kv.a[0], sm.kv.b[0]);
+    }
     if (tid < kTileRows) sm.g[0][tid] = (gate_of(j_lo) - cbase) * inv_scale;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -799,7 +916,8 @@ struct DqSpillSmem {
 template <int D>
 __global__ __launch_bounds__(kThreads, 2) void bwd_dq_spill_bf16_kernel(
     const bf16_t* __restrict__ K, const char* __restrict__ ds_ws, bf16_t* __restrict__ dQ,
-    float* __restrict__ dc_row, int N, int w, float scale, int num_qtiles, int total_tiles, int H, int G) {
+    float* __restrict__ dc_row, const float* __restrict__ reach, int N, int w, float scale, int num_qtiles, int total_tiles, int H,
+    int G) {
     constexpr int BR = 128;
     constexpr int DB = D / 32;
     extern __shared__ __align__(16) char smem_raw[];
@@ -852,18 +970,28 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_spill_bf16_kernel(
 
     const int k_lo = max(0, q0 - w + 1);
     const int k_hi = min(N, q0 + BR) - 1;
-    const int j_lo = k_lo / kTileRows, j_hi = k_hi / kTileRows;
+    SeenKeys seen(reach, (size_t)bh * N, k_lo / 128, k_hi / 128, N, lane);
+    int j_lo = k_lo / kTileRows;
+    const int j_hi = k_hi / kTileRows;
     const int jfull = N / kTileRows;
+    unsigned long long stored = ~0ull;  // key tiles seen.from + bit: the blocks of this wave's queries have been stored
     auto in_band = [&](int kb0) { return (kb0 <= qw0 + 31) && (kb0 + 31 > qw0 - w) && (qw0 < N); };
+    bool there = false;  // whether the tile that is computed next has blocks
 
     TilePairLoader<D> loader;
     loader.init(wv, lane);
     auto issue = [&](int j, int buf) {
         loader.load_one(Kh, j, jfull, N, sm.k[buf]);
+        if ((j >> 1) >= seen.from + 64) {
+            seen.from += 64;
+            seen.request();
+            stored = seen.look(qw0 / kTileRows);
+        }
+        there = (stored >> ((j >> 1) - seen.from)) & 1;
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb) {
             const int kb0 = j * kTileRows + 32 * sb;
-            if (in_band(kb0)) {
+            if (there && in_band(kb0)) {
                 const char* src = blk0 + (size_t)((kb0 >> 5) - qb + nslot - 1) * kSpillBlockBytes;
                 dma16_stream(src, gather0, sm.ds[buf][wv][sb]);
                 dma16_stream(src, gather1, sm.ds[buf][wv][sb] + 1024);
@@ -871,16 +999,25 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_spill_bf16_kernel(
         }
     };
     issue(j_lo, 0);
+    const int j_seen = 2 * seen.first(q0 / kTileRows);
+    stored = seen.look(qw0 / kTileRows);
+    if (j_seen > j_lo) {  // the gate has erased the tiles before
+        j_lo = j_seen;
+        __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+        issue(j_lo, 0);
+    }
+    there = (stored >> ((j_lo >> 1) - seen.from)) & 1;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
     for (int j = j_lo; j <= j_hi; ++j) {
         const int buf = (j - j_lo) & 1;
+        const bool now = there;
         if (j < j_hi) issue(j + 1, buf ^ 1);
         const char* kt = sm.k[buf];
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb) {
-            if (!in_band(j * kTileRows + 32 * sb)) continue;
+            if (!now || !in_band(j * kTileRows + 32 * sb)) continue;
             const char* blk = sm.ds[buf][wv][sb];
             bf16x8 dsf[2];
 #pragma unroll
@@ -990,14 +1127,16 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     if (dkv_split) spill = false;
     const FwdSplit dq_split = bwd_dq_shape(B * H, N, D, w, spill);
     if (dq_split) spill = false;
+    // Where all passes are whole-tile ones they leave out what the gate has erased; the blocks' values travel in dalpha, which the scan
+    // behind them writes.
+    float* reach = !dkv_split && !dq_split && scale > 0.f ? dalpha : nullptr;
     if (dq_split) {
         if (hipError_t e = bwd_dq_split_bf16(dq_split, args, D, s)) return e;
     } else {
-        constexpr int LPR = D / 8;
-        const unsigned dot_blocks = (unsigned)((rows * LPR + 255) / 256);
+        const int blocks = (N + kReachRows - 1) / kReachRows;
         ProfScope prof(kKernRowDot, s);
-        hipLaunchKernelGGL((rowdot_bf16_kernel<D>), dim3(dot_blocks), dim3(256), 0, s, (const bf16_t*)O,
-                           (const bf16_t*)dO, Dv, (long)rows);
+        hipLaunchKernelGGL((rowdot_bf16_kernel<D>), dim3((unsigned)(B * H) * blocks), dim3(256), 0, s, (const bf16_t*)O, (const bf16_t*)dO,
+                           (const bf16_t*)Q, c, L, Dv, reach, N, w, blocks);
     }
     if (dkv_split) {
         if (hipError_t e = bwd_dkv_split_bf16(args, D, s)) return e;
@@ -1009,15 +1148,15 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
             if (spill)
                 hipLaunchKernelGGL((bwd_dkv8_bf16_kernel<D, true>), dim3(B * Hkv * nk), dim3(2 * kThreads), 0, s,
                                    (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, c, L, Dv,
-                                   (bf16_t*)dK, (bf16_t*)dV, dc_col, ds_ws, N, w, scale, nk, B * Hkv * nk, H, H / Hkv);
+                                   (bf16_t*)dK, (bf16_t*)dV, dc_col, reach, ds_ws, N, w, scale, nk, B * Hkv * nk, H, H / Hkv);
             else
                 hipLaunchKernelGGL((bwd_dkv8_bf16_kernel<D, false>), dim3(B * Hkv * nk), dim3(2 * kThreads), 0, s,
                                    (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, c, L, Dv,
-                                   (bf16_t*)dK, (bf16_t*)dV, dc_col, ds_ws, N, w, scale, nk, B * Hkv * nk, H, H / Hkv);
+                                   (bf16_t*)dK, (bf16_t*)dV, dc_col, reach, ds_ws, N, w, scale, nk, B * Hkv * nk, H, H / Hkv);
         } else
             hipLaunchKernelGGL((bwd_dkv_bf16_kernel<D>), dim3(B * Hkv * nk), dim3(kThreads), 0, s,
                                (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, c, L, Dv,
-                               (bf16_t*)dK, (bf16_t*)dV, dc_col, N, w, scale, nk, B * Hkv * nk, H, H / Hkv);
+                               (bf16_t*)dK, (bf16_t*)dV, dc_col, reach, N, w, scale, nk, B * Hkv * nk, H, H / Hkv);
     }
     const int nq = (N + 127) / 128;
     if (!dq_split) {
@@ -1030,7 +1169,7 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
                                                      sizeof(DqSpillSmem<D>), lds_allowed))
                     return e;
                 hipLaunchKernelGGL((bwd_dq_spill_bf16_kernel<D>), dim3(B * H * nq), dim3(kThreads),
-                                   sizeof(DqSpillSmem<D>), s, (const bf16_t*)K, ds_ws, (bf16_t*)dQ, dc_row, N, w,
+                                   sizeof(DqSpillSmem<D>), s, (const bf16_t*)K, ds_ws, (bf16_t*)dQ, dc_row, reach, N, w,
                                    scale, nq, B * H * nq, H, H / Hkv);
                 launched = true;
             }
@@ -1038,7 +1177,7 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
         if (!launched)
             hipLaunchKernelGGL((bwd_dq_bf16_kernel<D>), dim3(B * H * nq), dim3(kThreads), 0, s,
                                (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, c, L, Dv,
-                               (bf16_t*)dQ, dc_row, N, w, scale, nq, B * H * nq, H, H / Hkv);
+                               (bf16_t*)dQ, dc_row, reach, N, w, scale, nq, B * H * nq, H, H / Hkv);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
