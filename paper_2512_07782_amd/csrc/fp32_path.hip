@@ -7,6 +7,7 @@
 
 #include <type_traits>
 
+#include "band_reach.h"
 #include "gfwa_device.h"
 #include "gfwa_internal.h"
 #include "split_band.h"
@@ -496,6 +497,7 @@ template <int D, int S>
 struct F32FwdSmem {
     SplitTile<D> k[S], v[S];
     alignas(16) float c[S][32];
+    int needed[8];  // over_waves
 };
 // Order of the forward's tiles.  From the longest band to the shortest over all heads (tile_of_block), over 3418 shapes 0.95 of the
 // time of one head after another (B1 H12/6 N6219 d64 w2854 374 -> 261 us, B1 H10/5 N6600 d128 w918 290 -> 189), except
@@ -514,7 +516,7 @@ template <int D, int NW, int S>
 __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) void fwd_f32_mfma_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ c, float* __restrict__ O, float* __restrict__ L, int N, int w, float scale,
-    int num_qtiles, int total_tiles, int H, int G) {
+    int num_qtiles, int total_tiles, int H, int G, int reach_block) {
     constexpr int KC = D / 16, DB = D / 32, BQ = 32 * NW;
     extern __shared__ __align__(256) char smem_raw[];
     auto& sm = *reinterpret_cast<F32FwdSmem<D, S>*>(smem_raw);
@@ -527,7 +529,26 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) voi
     const float *Kh = K + kvo, *Vh = V + kvo, *ch = c + (size_t)bh * N;
     if (NW == 8 && wv < 4) __builtin_amdgcn_s_setprio(1);
 
-    const int jb_lo = max(0, q0 - w + 1) / 32, jb_hi = (min(N, q0 + BQ) - 1) / 32;
+    const int k_lo = max(0, q0 - w + 1), jb_hi = (min(N, q0 + BQ) - 1) / 32;
+    int first_key = k_lo;
+    if (reach_block != 0 && reach_pays(ch[q0] - ch[k_lo], q0 - k_lo)) {  // the keys that the gate has erased for all queries stay out
+        float q2 = 0.f, k2 = 0.f, own = 0.f;
+        const float *qr = Q + ho + (size_t)tc * D + 4 * h, *kr = Kh + (size_t)tc * D + 4 * h;  // (the halves take every other four columns)
+#pragma unroll 4
+        for (int i = 0; i < D / 8; ++i) {
+            const f32x4 q = *reinterpret_cast<const f32x4*>(qr + 8 * i), k = *reinterpret_cast<const f32x4*>(kr + 8 * i);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) q2 = fmaf(q[j], q[j], q2), k2 = fmaf(k[j], k[j], k2), own = fmaf(q[j], k[j], own);
+        }
+        q2 = xhalf_sum(q2);
+        // the row's maximum is at least the score of the query's own key
+        const float edge = (ch[tc] - ch[q0]) * kLog2e + scale * kLog2e * (xhalf_sum(own) - 1e-4f * sqrtf(q2 * xhalf_sum(k2)));
+        const float reach2 = reach2_of(lanes_max<32>(norm_bits(q2)), scale * kLog2e), lowest = from_order(lanes_min<32>(lowest_order(edge))) - kErased;
+        first_key = over_waves<NW, true>(first_needed_key(key_block<D>(O + ho + (size_t)q0 * D, min(BQ, N - q0), lane), q0, k_lo, reach_block, reach2,
+                                                          lowest, ch[q0], lane),
+                                         sm.needed, wv, lane);
+    }
+    const int jb_lo = first_key / 32;
     using Mover = F32TileMover<D, 64 * NW>;
     Mover mv;
     mv.init(tid);
@@ -574,7 +595,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) voi
         end_step(jb);
     };
     // (three loops: with a branch around the computing step inside one loop the compiler copies the accumulators)
-    const int act_lo = qw0 < N ? max(0, qw0 - w + 1) / 32 : jb_hi + 1, act_hi = min(qw0 / 32, jb_hi);
+    const int act_lo = qw0 < N ? max(first_key, qw0 - w + 1) / 32 : jb_hi + 1, act_hi = min(qw0 / 32, jb_hi);
     int jb = jb_lo;
     for (; jb < act_lo; ++jb) idle_step(jb);
     for (; jb <= act_hi; ++jb) {
@@ -669,7 +690,7 @@ template <int D, int NP>
 __device__ __forceinline__ void dq_f32_mfma(
     int block, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO,
     const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dQ,
-    float* __restrict__ dc_row, int N, int w, float scale, int num_qtiles, int total_tiles, int H, int G) {
+    float* __restrict__ dc_row, const float* __restrict__ reach, int N, int w, float scale, int num_qtiles, int total_tiles, int H, int G) {
     constexpr int KC = D / 16, DB = D / 32;
     extern __shared__ __align__(256) char smem_raw[];
     auto& sm = *reinterpret_cast<F32BwdSmem<D, NP>*>(smem_raw);
@@ -685,7 +706,13 @@ __device__ __forceinline__ void dq_f32_mfma(
         const size_t ho = (size_t)bh * N * D, kvo = (size_t)kv_head_of(bh, H, G) * N * D;
         const float *Kh = K + kvo, *Vh = V + kvo, *ch = c + (size_t)bh * N;
 
-        const int jb_lo = max(0, q0 - w + 1) / 32, jb_hi = (min(N, q0 + 32 * NP) - 1) / 32;
+        int first_key = max(0, q0 - w + 1);
+        if (reach != nullptr && reach_pays(ch[q0] - ch[first_key], q0 - first_key)) {  // the keys that the gate has erased for all queries stay out
+            const float* at = reach + (size_t)bh * N;
+            const OwnRows own = own_queries(at, ch, q0 / 64, (min(N, q0 + 32 * NP) - 1) / 64, N, ch[q0], scale * kLog2e);
+            first_key = max(first_key, 64 * first_needed_block(at, first_key / 64, q0 / 64, N, own.reach2, own.edge - kErased, ch[q0], lane));
+        }
+        const int jb_lo = first_key / 32, jb_hi = (min(N, q0 + 32 * NP) - 1) / 32;
         using Mover = F32TileMover<D, 128 * NP>;
         Mover mv;
         mv.init(tid);
@@ -779,7 +806,7 @@ __device__ __forceinline__ void dq_f32_mfma(
             tile_axpy<D, 0, 1>(at, acc[0], sf, f, acc, [&](int i) __attribute__((always_inline)) { fetch(fetched, i, DB); });  // (one half: its pieces are in sf)
         };
         // (the loop that computes has no branch around the accumulators: with one the compiler copies them)
-        const int act_lo = qw0 < N ? max(0, qw0 - w + 1) / 32 : jb_hi + 1, act_hi = min(qw0 / 32, jb_hi);
+        const int act_lo = qw0 < N ? max(first_key, qw0 - w + 1) / 32 : jb_hi + 1, act_hi = min(qw0 / 32, jb_hi);
         __builtin_amdgcn_s_setprio(role == 0);  // has the exponentials to do behind its MFMAs
         int jb = jb_lo;
         for (; jb < act_lo; ++jb) idle_step(jb);
@@ -852,7 +879,8 @@ template <int D, int NP>
 __device__ __forceinline__ void dkv_f32_mfma(
     int block, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO,
     const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dK,
-    float* __restrict__ dV, float* __restrict__ dc_col, int N, int w, float scale, int num_ktiles, int total_tiles, int H, int G) {
+    float* __restrict__ dV, float* __restrict__ dc_col, const float* __restrict__ reach, int N, int w, float scale, int num_ktiles, int total_tiles,
+    int H, int G) {
     constexpr int KC = D / 16, DB = D / 32;
     extern __shared__ __align__(256) char smem_raw[];
     auto& sm = *reinterpret_cast<F32BwdSmem<D, NP>*>(smem_raw);
@@ -871,8 +899,19 @@ __device__ __forceinline__ void dkv_f32_mfma(
 
         // query blocks that see a key of the tile: rows k0 .. k0 + 32 NP - 1 + w - 1, of every query head of the group in turn
         const int qb_lo = k0 / 32;
-        const int qb_hi = (int)(min((long)N - 1, (long)k0 + 32 * NP - 1 + w - 1) / 32);
-        const int nblk = qb_hi - qb_lo + 1;
+        const int t_hi = (int)min((long)N - 1, (long)k0 + 32 * NP - 1 + w - 1);
+        auto blocks_of = [&](int g) __attribute__((always_inline)) {  // of query head g, without those that the gate has erased all keys for
+            int qb_hi = t_hi / 32;
+            const size_t rows = (size_t)(bh0 + g) * N;
+            const float* ch = c + rows;
+            const int k1 = min(k0 + 32 * NP, N) - 1, i_min = k1 / 64;
+            if (reach != nullptr && t_hi / 64 > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1)) {
+                const OwnRows own = own_keys(reach + rows, k0 / 64, k1 / 64, N, ch[k0], scale * kLog2e);
+                qb_hi = min(qb_hi, 2 * last_needing_block(reach + rows, ch, i_min, t_hi / 64, N, own.reach2, own.edge + kErased, ch[k0], lane) + 1);
+            }
+            return __builtin_amdgcn_readfirstlane(qb_hi) - qb_lo + 1;
+        };
+        int nblk = blocks_of(0);  // of the query head at hand
         using Mover = F32TileMover<D, 128 * NP>;
         Mover mv;
         mv.init(tid);
@@ -933,8 +972,9 @@ __device__ __forceinline__ void dkv_f32_mfma(
             end_step();
         };
         RangeCheck check;
-        const int b_lo = kw0 < N ? kg : nblk, b_hi = (int)min((long)nblk - 1, ((long)kw0 + 30 + w) / 32 - qb_lo);
         for (int g = 0; g < G; ++g) {  // query heads
+            if (g > 0) nblk = blocks_of(g);
+            const int b_lo = kw0 < N ? kg : nblk, b_hi = (int)min((long)nblk - 1, ((long)kw0 + 30 + w) / 32 - qb_lo);
             int b = 0;
             for (; b < b_lo; ++b) idle_step(g, b);
             if constexpr (role == 0) {
@@ -1064,11 +1104,11 @@ template <int D, int NP>
 __global__ __launch_bounds__(128 * NP, NP == 4 ? 1 : 2) void bwd_f32_mfma_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO,
     const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dK,
-    float* __restrict__ dV, float* __restrict__ dc_col, float* __restrict__ dc_row, int N, int w, float scale, int tiles_per_head, int dkv_tiles,
-    int dq_tiles, int H, int G) {
+    float* __restrict__ dV, float* __restrict__ dc_col, float* __restrict__ dc_row, const float* __restrict__ reach, int N, int w, float scale,
+    int tiles_per_head, int dkv_tiles, int dq_tiles, int H, int G) {
     const int b = (int)blockIdx.x;
-    if (b < dkv_tiles) dkv_f32_mfma<D, NP>(b, Q, K, V, dO, c, L, Dv, dK, dV, dc_col, N, w, scale, tiles_per_head, dkv_tiles, H, G);
-    else dq_f32_mfma<D, NP>(b - dkv_tiles, Q, K, V, dO, c, L, Dv, dQ, dc_row, N, w, scale, tiles_per_head, dq_tiles, H, G);
+    if (b < dkv_tiles) dkv_f32_mfma<D, NP>(b, Q, K, V, dO, c, L, Dv, dK, dV, dc_col, reach, N, w, scale, tiles_per_head, dkv_tiles, H, G);
+    else dq_f32_mfma<D, NP>(b - dkv_tiles, Q, K, V, dO, c, L, Dv, dQ, dc_row, reach, N, w, scale, tiles_per_head, dq_tiles, H, G);
 }
 
 // ---- D_t = <O_t, dO_t>
@@ -1084,6 +1124,68 @@ __global__ __launch_bounds__(256) void rowdot_f32_kernel(const float* __restrict
     o.x[0] = *reinterpret_cast<const f32x4*>(O + at);
     const float d = o.dot(*reinterpret_cast<const f32x4*>(dO + at), 0);
     if (row < rows && lane % Step::kLanes == 0) Dv[row] = d;
+}
+
+// The same in front of the matrix-core kernels, with what these ask of a block of 64 rows (band_reach.h): squared norms of Q and K, the lowest
+// edge of the queries and the highest gate of the keys, where the gate decays enough that they are asked for.  A value row or a D that
+// is not finite keeps its block.  reach: dalpha.
+template <int D>
+__global__ __launch_bounds__(256) void rowdot_reach_f32_kernel(const float* __restrict__ O, const float* __restrict__ dO,
+                                                               const float* __restrict__ Q, const float* __restrict__ K,
+                                                               const float* __restrict__ V, const float* __restrict__ c,
+                                                               const float* __restrict__ L, float* __restrict__ Dv, float* __restrict__ reach,
+                                                               int N, int w, int blocks, int H, int G) {
+    using Step = RowStep<D, 1>;
+    constexpr int kLanes = Step::kLanes, kRows = 4 * Step::kRows, kPasses = kReachRows / kRows;
+    __shared__ int norm_s, edge_s, key_norm_s, high_s;
+    const int lane = threadIdx.x & 63, bh = (int)blockIdx.x / blocks, t0 = (int)blockIdx.x % blocks * kReachRows;
+    const size_t head = (size_t)bh * N, kv = (size_t)kv_head_of(bh, H, G) * N;
+    const int r0 = t0 + threadIdx.x / kLanes, col = 4 * (lane % kLanes);
+    auto row_of = [&](int p) { return min(r0 + p * kRows, N - 1); };
+    float d[kPasses];
+#pragma unroll
+    for (int p = 0; p < kPasses; ++p) {
+        Step o;
+        o.x[0] = *reinterpret_cast<const f32x4*>(O + (head + row_of(p)) * D + col);
+        d[p] = o.dot(*reinterpret_cast<const f32x4*>(dO + (head + row_of(p)) * D + col), 0);
+        if (r0 + p * kRows < N && lane % kLanes == 0) Dv[head + row_of(p)] = d[p];
+    }
+    const float* ch = c + head;
+    const int far = max(0, t0 - w + 1), t1 = min(t0 + kReachRows, N) - 1, end = (int)min((long)N - 1, (long)t1 + w - 1);
+    const bool queries = reach_pays(ch[t0] - ch[far], t0 - far), keys = reach_pays(ch[end] - ch[t0], end - t0);
+    if (queries || keys) {
+        if (threadIdx.x == 0) norm_s = key_norm_s = 0, edge_s = 0x7fffffff, high_s = (int)0x80000000;
+        __syncthreads();
+        auto norm_of = [&](const float* row) {
+            Step x;
+            x.x[0] = *reinterpret_cast<const f32x4*>(row + col);
+            return x.dot(x.x[0], 0);
+        };
+        int norm = 0, edge = 0x7fffffff, key_norm = 0, high = (int)0x80000000;
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) {
+            const int row = row_of(p);
+            norm = max(norm, finite(d[p]) ? norm_bits(norm_of(Q + (head + row) * D)) : 0x7fffffff);
+            edge = min(edge, lowest_order((ch[row] - ch[t0]) + L[head + row]));
+            key_norm = max(key_norm, finite(norm_of(V + (kv + row) * D)) ? norm_bits(norm_of(K + (kv + row) * D)) : 0x7fffffff);
+            high = max(high, highest_order(ch[row]));
+        }
+        norm = lanes_max(norm), edge = lanes_min(edge), key_norm = lanes_max(key_norm), high = lanes_max(high);
+        if (lane == 0) {
+            atomicMax(&norm_s, norm);
+            atomicMin(&edge_s, edge);
+            atomicMax(&key_norm_s, key_norm);
+            atomicMax(&high_s, high);
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x < 4 && t0 + (int)threadIdx.x < N) {
+        const bool look = queries || keys;
+        const int i = threadIdx.x;
+        float x = i == kReachNorm || i == kReachKeyNorm ? INFINITY : 0.f;
+        if (look) x = i == kReachNorm ? __int_as_float(norm_s) : i == kReachEdge ? from_order(edge_s) : i == kReachKeyNorm ? __int_as_float(key_norm_s) : from_order(high_s);
+        reach[head + t0 + i] = x;
+    }
 }
 
 // Bands that workgroups of 64 queries (keys) serve better than larger ones: d = 64, at most 128 long.  A workgroup walks
@@ -1143,8 +1245,10 @@ static hipError_t launch_fwd_f32_mfma(const float* Q, const float* K, const floa
     constexpr size_t lds = sizeof(F32FwdSmem<D, S>);
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&fwd_f32_mfma_kernel<D, NW, S>), lds, lds_allowed)) return e;
     const int nq = (N + 32 * NW - 1) / (32 * NW), total = B * H * nq;
+    const KeyReach reach = scale > 0.f ? reach_of_forward(B * H, N, D, w, 32 * NW, false) : KeyReach{0, 32 * NW};
+    if (hipError_t e = key_reach(reach, false, K, V, c, O, B, H, Hkv, N, D, w, s)) return e;
     hipLaunchKernelGGL((fwd_f32_mfma_kernel<D, NW, S>), dim3(total), dim3(64 * NW), lds, s, Q, K, V, c, O, L, N, w, scale, nq, total,
-                       H, H / Hkv);
+                       H, H / Hkv, reach.block);
     return hipGetLastError();
 }
 
@@ -1229,31 +1333,36 @@ static hipError_t launch_bwd_f32_rows(const float* Q, const float* K, const floa
 
 template <int D, int NP>
 static hipError_t launch_bwd_f32_mfma(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,
-                                      const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, int B,
-                                      int H, int Hkv, int N, int w, float scale, hipStream_t s) {
+                                      const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, float* reach,
+                                      int B, int H, int Hkv, int N, int w, float scale, hipStream_t s) {
     static DeviceOnce lds_allowed;
     constexpr size_t lds = sizeof(F32BwdSmem<D, NP>);
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_f32_mfma_kernel<D, NP>), lds, lds_allowed)) return e;
     const int nt = (N + 32 * NP - 1) / (32 * NP);
+    if (NP == 2 || !(scale > 0.f)) reach = nullptr;  // (bands of up to 128)
     {
         ProfScope prof(kKernRowDot, s);
-        launch_rowdot_f32<D>(O, dO, Dv, (long)B * H * N, s);
+        const int blocks = (N + kReachRows - 1) / kReachRows;
+        if (reach == nullptr) launch_rowdot_f32<D>(O, dO, Dv, (long)B * H * N, s);
+        else
+            hipLaunchKernelGGL((rowdot_reach_f32_kernel<D>), dim3((unsigned)(B * H) * blocks), dim3(256), 0, s, O, dO, Q, K, V, c, L, Dv, reach, N, w,
+                               blocks, H, H / Hkv);
     }
     ProfScope prof(kKernDkv, s);
     launch_passes((long)B * Hkv * nt, (long)B * H * nt, 128 * NP, [&](int dkv_tiles, int blocks) {
         hipLaunchKernelGGL((bwd_f32_mfma_kernel<D, NP>), dim3(blocks), dim3(128 * NP), lds, s, Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row,
-                           N, w, scale, nt, dkv_tiles, blocks - dkv_tiles, H, H / Hkv);
+                           reach, N, w, scale, nt, dkv_tiles, blocks - dkv_tiles, H, H / Hkv);
     });
     return hipGetLastError();
 }
 
 template <int D>
 static hipError_t launch_bwd_f32(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,
-                                 const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, int B,
+                                 const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, float* reach, int B,
                                  int H, int Hkv, int N, int w, float scale, hipStream_t s) {
-    auto with = [&](auto launch) { return launch(Q, K, V, O, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, B, H, Hkv, N, w, scale, s); };
     if (!f32_use_mfma(true, B, H, Hkv, N, D, w))
-        return with(launch_bwd_f32_rows<D>);
+        return launch_bwd_f32_rows<D>(Q, K, V, O, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, B, H, Hkv, N, w, scale, s);
+    auto with = [&](auto launch) { return launch(Q, K, V, O, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, reach, B, H, Hkv, N, w, scale, s); };
     if constexpr (D == 64)
         if (f32_short_band(N, D, w)) return with(launch_bwd_f32_mfma<D, 2>);
     return with(launch_bwd_f32_mfma<D, 4>);
@@ -1266,8 +1375,8 @@ hipError_t backward_f32(const float* Q, const float* K, const float* V, const fl
     float* Dv = ws;
     float* dc_col = ws + rows;
     float* dc_row = ws + 2 * rows;
-    const hipError_t e = d == 128 ? launch_bwd_f32<128>(Q, K, V, O, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, B, H, Hkv, N, w, scale, s)
-                                  : launch_bwd_f32<64>(Q, K, V, O, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, B, H, Hkv, N, w, scale, s);
+    const hipError_t e = d == 128 ? launch_bwd_f32<128>(Q, K, V, O, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, dalpha, B, H, Hkv, N, w, scale, s)
+                                  : launch_bwd_f32<64>(Q, K, V, O, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, dalpha, B, H, Hkv, N, w, scale, s);
     if (e != hipSuccess) return e;
     // behind the three vectors as the workspace query sizes them (each padded to 256 bytes)
     const size_t one = ((rows * sizeof(float)) + 255) & ~(size_t)255;
