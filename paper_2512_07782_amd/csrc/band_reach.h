@@ -38,7 +38,7 @@ constexpr float kErased = 127.f;
 // 14 to the 88 of kErased (in units of the gate); the pass reads for every row as much as 20 to 60 rows of a band take from the L2.  (Two
 // products compared, so that two kernels which ask the same always agree: there is nothing the compiler could fuse in one of them.)
 constexpr float kTypicalReach = 104.f;
-constexpr int kFewRows = 128;
+constexpr int kFewRows = 256;
 __device__ __forceinline__ bool reach_pays(float decay, int len) {
     return decay > kTypicalReach && decay * (float)(len - kFewRows) > kTypicalReach * (float)len;
 }
@@ -155,20 +155,23 @@ __device__ __forceinline__ int forward_reach(const bf16x8 (&q)[D / 16], const bf
     return over_waves<WAVES, true>(first_needed_key(kb, q0, k_lo, block, reach2, lowest, cbase, lane), at, wv, lane);
 }
 
-// ---- queries behind a key tile (backward).  The first rows of every 64-query block of dalpha hold the block's largest squared norm and
-// the lowest (c - c of the block's first row) + L of its rows (reach_of_queries, called beside the row dots), and the third one of every
-// 128-key tile, from the dK/dV kernel on, the last 64-query block that needs one of its keys.
-// With fp32 storage, where one launch holds both passes, they hold the block's keys instead: squared norm and highest gate.
-constexpr int kReachRows = 64, kReachNorm = 0, kReachEdge = 1, kReachLast = 2, kReachKeyNorm = 2, kReachKeyHigh = 3;
+// ---- both sides of the backward.  The first rows of every 64-row block of dalpha hold the block's largest squared norm of Q and the lowest
+// (c - c of the block's first row) + L of its queries and, where a pass cannot look at its keys by itself (split kernels, fp32), the
+// largest squared norm of K and the highest gate of its keys: the row-dot kernels write them.  The whole-tile dK/dV kernel leaves as the fifth
+// value of the first block of each of its 128-key tiles the last 64-query block that needs one of the keys, for the dQ pass behind it.
+constexpr int kReachRows = 64, kReachNorm = 0, kReachEdge = 1, kReachKeyNorm = 2, kReachKeyHigh = 3, kReachLast = 4;
+constexpr int kReachShortest = 256;  // bands up to this long never pay (kFewRows)
+// Row of dalpha from which on block i has its five values: its first, or for a last block of less than five rows the ninth of the one before.
+__device__ __forceinline__ int reach_row(int i, int N) { return kReachRows * i + 5 <= N ? kReachRows * i : kReachRows * (i - 1) + 8; }
 // Last 64-query block from i_hi down to i_min + 1 that needs a key of a wave's, else i_min.  at: of the head.
 __device__ __forceinline__ int last_needing_block(const float* at, const float* ch, int i_min, int i_hi, int N, float reach2, float highest,
                                                   float cbase, int lane) {
     for (int top = i_hi; top > i_min; top -= 64) {
         const int i = top - lane;
         bool kept = i > i_min;
-        if (kept && 64 * i + kReachEdge < N) {
-            const float n2 = at[64 * i + kReachNorm], y = (ch[64 * i] - cbase) + at[64 * i + kReachEdge];
-            kept = !is_erased(n2, reach2, y * kLog2e - highest);
+        if (kept) {
+            const float* r = at + reach_row(i, N);
+            kept = !is_erased(r[kReachNorm], reach2, ((ch[64 * i] - cbase) + r[kReachEdge]) * kLog2e - highest);
         }
         const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
         if (mask) return top - __builtin_ctzll(mask);
@@ -176,25 +179,25 @@ __device__ __forceinline__ int last_needing_block(const float* at, const float* 
     return i_min;
 }
 
-// fp32: what the table says of the own rows of a tile, blocks i0 .. i1 of queries (of keys).
+// What the table says of the own rows of a tile, blocks i0 .. i1 of queries (of keys).
 struct OwnRows {
     float reach2, edge;  // edge: relative to gate cbase, in base-2 exponents; the lowest of the queries, the highest of the keys
 };
 __device__ __forceinline__ OwnRows own_queries(const float* at, const float* ch, int i0, int i1, int N, float cbase, float sl) {
     int norm = 0, edge = 0x7fffffff;
     for (int i = i0; i <= i1; ++i) {
-        const bool there = 64 * i + kReachEdge < N;
-        norm = max(norm, there ? norm_bits(at[64 * i + kReachNorm]) : 0x7f800000);
-        if (there) edge = min(edge, lowest_order((ch[64 * i] - cbase) + at[64 * i + kReachEdge]));
+        const float* r = at + reach_row(i, N);
+        norm = max(norm, norm_bits(r[kReachNorm]));
+        edge = min(edge, lowest_order((ch[64 * i] - cbase) + r[kReachEdge]));
     }
     return {reach2_of(norm, sl), from_order(edge) * kLog2e};
 }
 __device__ __forceinline__ OwnRows own_keys(const float* at, int i0, int i1, int N, float cbase, float sl) {
     int norm = 0, edge = (int)0x80000000;
     for (int i = i0; i <= i1; ++i) {
-        const bool there = 64 * i + kReachKeyHigh < N;
-        norm = max(norm, there ? norm_bits(at[64 * i + kReachKeyNorm]) : 0x7f800000);
-        if (there) edge = max(edge, highest_order(at[64 * i + kReachKeyHigh] - cbase));
+        const float* r = at + reach_row(i, N);
+        norm = max(norm, norm_bits(r[kReachKeyNorm]));
+        edge = max(edge, highest_order(r[kReachKeyHigh] - cbase));
     }
     return {reach2_of(norm, sl), from_order(edge) * kLog2e};
 }
@@ -203,8 +206,10 @@ __device__ __forceinline__ int first_needed_block(const float* at, int i_lo, int
     for (int base = i_lo; base < i_max; base += 64) {
         const int i = base + lane;
         bool kept = i < i_max;
-        if (kept && 64 * i + kReachKeyHigh < N)
-            kept = !is_erased(at[64 * i + kReachKeyNorm], reach2, lowest - (at[64 * i + kReachKeyHigh] - cbase) * kLog2e);
+        if (kept) {
+            const float* r = at + reach_row(i, N);
+            kept = !is_erased(r[kReachKeyNorm], reach2, lowest - (r[kReachKeyHigh] - cbase) * kLog2e);
+        }
         const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
         if (mask) return base + __builtin_ctzll(mask);
     }

@@ -41,15 +41,17 @@ constexpr float kPosBig = 1.0e30f;
 // 1. D_t = <O_t, dO_t>, and what the dK/dV kernel asks of a block of queries (band_reach.h)
 // ------------------------------------------------------------------------------------------
 // A workgroup takes 64 rows of a head, 16 bytes of each matrix a lane and all of them in flight.  Q is read only where the gate decays
-// enough over the window that keys may be erased for these rows.  reach: dalpha, or nullptr.
-template <int D>
+// enough over the window that keys may be erased for these rows.  KEYS, in front of the split kernels, which hold too few rows to look at the
+// other side for themselves: K and V as well.  reach: dalpha, or nullptr.
+template <int D, bool KEYS>
 __global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO,
-                                                          const bf16_t* __restrict__ Q, const float* __restrict__ c,
+                                                          const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
+                                                          const bf16_t* __restrict__ V, const float* __restrict__ c,
                                                           const float* __restrict__ L, float* __restrict__ Dv, float* __restrict__ reach, int N,
-                                                          int w, int blocks) {
+                                                          int w, int blocks, int H, int G) {
     constexpr int LPR = D / 8;  // lanes per row, 16 bytes each
     constexpr int kRows = 256 / LPR, kPasses = kReachRows / kRows;
-    __shared__ int norm_s, edge_s;
+    __shared__ int norm_s, edge_s, key_norm_s, high_s;
     const int bh = (int)blockIdx.x / blocks, t0 = (int)blockIdx.x % blocks * kReachRows;
     const size_t head = (size_t)bh * N;
     const int part = threadIdx.x % LPR, r0 = t0 + threadIdx.x / LPR;
@@ -62,8 +64,12 @@ __global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restri
     }
     const float c0 = c[head + t0];
     const int far = max(0, t0 - w + 1);
-    const bool look = reach != nullptr && reach_pays(c0 - c[head + far], t0 - far);
-    if (look && threadIdx.x == 0) norm_s = 0, edge_s = 0x7fffffff;
+    bool look = reach != nullptr && reach_pays(c0 - c[head + far], t0 - far);
+    if (KEYS && reach != nullptr) {
+        const int end = (int)min((long)N - 1, (long)t0 + kReachRows - 2 + w);
+        look |= reach_pays(c[head + end] - c0, end - t0);
+    }
+    if (look && threadIdx.x == 0) norm_s = key_norm_s = 0, edge_s = 0x7fffffff, high_s = (int)0x80000000;
     float dot[kPasses];
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
@@ -75,27 +81,43 @@ __global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restri
         if (part == 0 && r0 + p * kRows < N) Dv[head + r0 + p * kRows] = dot[p];
     }
     if (look) {
-        int norm = 0, edge = 0x7fffffff;
+        const size_t kv = KEYS ? (size_t)kv_head_of(bh, H, G) * N : 0;
+        int norm = 0, edge = 0x7fffffff, key_norm = 0, high = (int)0x80000000;
 #pragma unroll
         for (int p = 0; p < kPasses; ++p) {
-            const size_t row = head + min(r0 + p * kRows, N - 1);
-            const bf16x8 q = *reinterpret_cast<const bf16x8*>(Q + row * D + 8 * part);
+            const int r = min(r0 + p * kRows, N - 1);
+            const size_t row = head + r;
+            auto norm_of = [&](const bf16_t* x) {
+                const bf16x8 v = *reinterpret_cast<const bf16x8*>(x + 8 * part);
+                return row_sum<LPR>(dot8(v, v, 0.f));
+            };
             // (D is not finite if a value of dO is not)
-            norm = max(norm, finite(dot[p]) ? norm_bits(row_sum<LPR>(dot8(q, q, 0.f))) : 0x7fffffff);
+            norm = max(norm, finite(dot[p]) ? norm_bits(norm_of(Q + row * D)) : 0x7fffffff);
             edge = min(edge, lowest_order((c[row] - c0) + L[row]));
+            if (KEYS) {
+                key_norm = max(key_norm, finite(norm_of(V + (kv + r) * D)) ? norm_bits(norm_of(K + (kv + r) * D)) : 0x7fffffff);
+                high = max(high, highest_order(c[row]));
+            }
         }
         norm = lanes_max(norm);
         edge = lanes_min(edge);
+        if (KEYS) key_norm = lanes_max(key_norm), high = lanes_max(high);
         __syncthreads();
         if ((threadIdx.x & 63) == 0) {
             atomicMax(&norm_s, norm);
             atomicMin(&edge_s, edge);
+            if (KEYS) atomicMax(&key_norm_s, key_norm), atomicMax(&high_s, high);
         }
         __syncthreads();
     }
     if (reach != nullptr && threadIdx.x == 0) {
-        reach[head + t0 + kReachNorm] = look ? __int_as_float(norm_s) : INFINITY;
-        if (t0 + kReachEdge < N) reach[head + t0 + kReachEdge] = look ? from_order(edge_s) : 0.f;
+        float* at = reach + head + reach_row(t0 / kReachRows, N);
+        at[kReachNorm] = look ? __int_as_float(norm_s) : INFINITY;
+        at[kReachEdge] = look ? from_order(edge_s) : 0.f;
+        if (KEYS) {
+            at[kReachKeyNorm] = look ? __int_as_float(key_norm_s) : INFINITY;
+            at[kReachKeyHigh] = look ? from_order(high_s) : 0.f;
+        }
     }
 }
 
@@ -144,7 +166,7 @@ __device__ __forceinline__ int last_query_tile(const Keys& keys, const float* ch
         const int own = last_needing_block(at, ch, i_min, i_hi, N, reach2_of(norm, sl), highest, cbase, lane);
         last = over_waves<WAVES, false>(own, needed, wv, lane);
     }
-    if (threadIdx.x == 0 && k0 + kReachLast < N) reinterpret_cast<int*>(at)[k0 + kReachLast] = last;
+    if (threadIdx.x == 0) reinterpret_cast<int*>(at)[reach_row(k0 / kReachRows, N) + kReachLast] = last;
     return last;
 }
 
@@ -706,8 +728,7 @@ struct SeenKeys {
     __device__ __forceinline__ SeenKeys(const float* reach, size_t head, int kt_lo, int kt_hi, int N_, int lane_)
         : at(reach == nullptr ? nullptr : reach + head), from(kt_lo), hi(kt_hi), N(N_), lane(lane_) { request(); }
     __device__ __forceinline__ void request() {
-        const int row = min(from + lane, hi) * 128 + kReachLast;  // (a tile of one or two keys has no room for it; it is the last, which all see)
-        last = at != nullptr && row < N ? reinterpret_cast<const int*>(at)[row] : 0x7fffffff;
+        last = at != nullptr ? reinterpret_cast<const int*>(at)[reach_row(2 * min(from + lane, hi), N) + kReachLast] : 0x7fffffff;
     }
     __device__ __forceinline__ unsigned long long look(int i) const {  // tile from + bit: streamed against query tile i (of 64)
         return __builtin_amdgcn_ballot_w64(last >= i || from + lane >= hi);
@@ -1103,6 +1124,13 @@ static bool bwd_in_one_launch(int BH, int BHkv, int N, int d, int w) {
     return blocks <= 2 * cus && (G > 1 || chain <= 40 || 4 * blocks <= 7 * cus);
 }
 
+// Whether the split kernels look at the norms, which a row-dot launch of 4 us then takes for them: for bands that all but the slowest gates
+// erase in part.  Whole step, us, without / with, gates of mu = -6 (nothing erased), -3, -2:
+//   H1 N2000 d64 causal    36 /  38    35 /  39    35 /  33      H8 N2000 d128 causal   120 / 125   120 / 122   120 /  91
+//   H4 N8192 d64 w4096    192 / 198   189 / 106   189 /  73      H1 N16384 d128 w4096   246 / 251   247 / 138   246 /  96
+//   H4 N3000 d64 w1600     50 /  55    50 /  57    50 /  51  (this one does not take it)
+static bool bwd_split_looks(int N, int w) { return (w < N ? w : N) >= 1900; }
+
 template <int D>
 static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO,
                              const float* c, const float* L, void* dQ, void* dK, void* dV, float* dalpha,
@@ -1116,27 +1144,38 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     double* scan_partial = reinterpret_cast<double*>(ws + 3 * pad);
     const size_t scan_pad = (gate_scan_workspace_bytes(B * H, N) + 255) & ~(size_t)255;
     char* ds_ws = reinterpret_cast<char*>(ws + 3 * pad) + scan_pad;  // only with `spill`
-    const BwdBf16 args = {(const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, c, L, Dv,
-                          (bf16_t*)dQ, (bf16_t*)dK, (bf16_t*)dV, dc_col, dc_row, B, H, Hkv, N, w, scale};
-    if (bwd_in_one_launch(B * H, B * Hkv, N, D, w)) {
+    BwdBf16 args = {(const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, c, L, Dv,
+                    (bf16_t*)dQ, (bf16_t*)dK, (bf16_t*)dV, dc_col, dc_row, nullptr, B, H, Hkv, N, w, scale};
+    auto rowdot = [&](auto keys, float* reach) {
+        const int blocks = (N + kReachRows - 1) / kReachRows;
+        ProfScope prof(kKernRowDot, s);
+        hipLaunchKernelGGL((rowdot_bf16_kernel<D, decltype(keys)::value>), dim3((unsigned)(B * H) * blocks), dim3(256), 0, s, args.O, args.dO, args.Q,
+                           args.K, args.V, c, L, Dv, reach, N, w, blocks, H, H / Hkv);
+    };
+    const bool one_launch = bwd_in_one_launch(B * H, B * Hkv, N, D, w);
+    // the dS blocks only travel between the kernels of this file: dK/dV is chosen first, dQ by whether there are blocks then
+    const bool dkv_split = one_launch || bwd_dkv_splits(B * Hkv, H / Hkv, N, D, w);
+    if (dkv_split) spill = false;
+    const FwdSplit dq_split = one_launch ? kFwdSplitMid : bwd_dq_shape(B * H, N, D, w, spill);
+    if (dq_split) spill = false;
+    // What the gate has erased is left out; the blocks' values travel in dalpha, which the scan behind the passes writes.  The split kernels
+    // form D by themselves, so the row-dot launch is one more where they look at the norms.  (A split dK/dV pass leaves no limits for the
+    // whole-tile dQ kernels.)
+    const bool some_split = dkv_split || dq_split;
+    float* reach = scale > 0.f && (w < N ? w : N) > kReachShortest && (!some_split || bwd_split_looks(N, w)) ? dalpha : nullptr;
+    const float* seen = dkv_split ? nullptr : reach;
+    if (some_split && reach != nullptr) {
+        rowdot(std::true_type{}, reach);
+        args.reach = reach;
+    }
+    if (one_launch) {
         if (hipError_t e = bwd_both_split_bf16(args, D, s)) return e;
         return gate_grad_scan(dc_col, dc_row, dalpha, scan_partial, B * H, N, s);
     }
-    // the dS blocks only travel between the kernels of this file: dK/dV is chosen first, dQ by whether there are blocks then
-    const bool dkv_split = bwd_dkv_splits(B * Hkv, H / Hkv, N, D, w);
-    if (dkv_split) spill = false;
-    const FwdSplit dq_split = bwd_dq_shape(B * H, N, D, w, spill);
-    if (dq_split) spill = false;
-    // Where all passes are whole-tile ones they leave out what the gate has erased; the blocks' values travel in dalpha, which the scan
-    // behind them writes.
-    float* reach = !dkv_split && !dq_split && scale > 0.f ? dalpha : nullptr;
     if (dq_split) {
         if (hipError_t e = bwd_dq_split_bf16(dq_split, args, D, s)) return e;
-    } else {
-        const int blocks = (N + kReachRows - 1) / kReachRows;
-        ProfScope prof(kKernRowDot, s);
-        hipLaunchKernelGGL((rowdot_bf16_kernel<D>), dim3((unsigned)(B * H) * blocks), dim3(256), 0, s, (const bf16_t*)O, (const bf16_t*)dO,
-                           (const bf16_t*)Q, c, L, Dv, reach, N, w, blocks);
+    } else if (!some_split || reach == nullptr) {
+        rowdot(std::false_type{}, reach);
     }
     if (dkv_split) {
         if (hipError_t e = bwd_dkv_split_bf16(args, D, s)) return e;
@@ -1169,7 +1208,7 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
                                                      sizeof(DqSpillSmem<D>), lds_allowed))
                     return e;
                 hipLaunchKernelGGL((bwd_dq_spill_bf16_kernel<D>), dim3(B * H * nq), dim3(kThreads),
-                                   sizeof(DqSpillSmem<D>), s, (const bf16_t*)K, ds_ws, (bf16_t*)dQ, dc_row, reach, N, w,
+                                   sizeof(DqSpillSmem<D>), s, (const bf16_t*)K, ds_ws, (bf16_t*)dQ, dc_row, seen, N, w,
                                    scale, nq, B * H * nq, H, H / Hkv);
                 launched = true;
             }
@@ -1177,7 +1216,7 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
         if (!launched)
             hipLaunchKernelGGL((bwd_dq_bf16_kernel<D>), dim3(B * H * nq), dim3(kThreads), 0, s,
                                (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, c, L, Dv,
-                               (bf16_t*)dQ, dc_row, reach, N, w, scale, nq, B * H * nq, H, H / Hkv);
+                               (bf16_t*)dQ, dc_row, seen, N, w, scale, nq, B * H * nq, H, H / Hkv);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -11,6 +11,7 @@
 // Whole backward, us, with the 128-row kernels / with the kernels here, one launch each (B2 H8/2 N515 d64 in one: 22.2):
 //   B2 H8/2 N515 d64 w512   63.4 / 26.6      B2 H8/2 N515 d128 w512   80.7 / 47.9     B1 H4 N1000 d128 w333    39.9 / 24.9
 //   B1 H8 N700 d128 w1024   46.9 / 31.7      B1 H4 N5003 d64 w3000   117.6 / 74.2     B1 H16/4 N5003 d64 w3000  323 / 223 (dKV only)
+#include "band_reach.h"
 #include "gfwa_device.h"
 #include "gfwa_internal.h"
 #include "split_band.h"
@@ -58,6 +59,13 @@ __device__ __forceinline__ void dq_split(const BwdBf16& a, int num_qtiles, int b
     }
     const float dt = xhalf_sum(dsum);
     if (band.kg == 0 && h == 0 && t < N) Dv[(size_t)bh * N + t] = dt;
+    int first = max(0, q0 - w + 1);
+    if (a.reach != nullptr && reach_pays(band.cbase - band.ch[first], q0 - first)) {  // the keys that the gate has erased for all queries stay out
+        const float* at = a.reach + (size_t)bh * N;
+        const OwnRows own = own_queries(at, band.ch, q0 / 64, (min(N, q0 + 32 * QW) - 1) / 64, N, band.cbase, sl);
+        first = max(first, 64 * first_needed_block(at, first / 64, q0 / 64, N, own.reach2, own.edge - kErased, band.cbase, lane));
+        band.from(__builtin_amdgcn_readfirstlane(first), q0, w);
+    }
     // rows past N get an exponent of -big, i.e. p = 0
     const float nlsub = t < N ? -(L[(size_t)bh * N + tc] + (band.ch[tc] - band.cbase)) * kLog2e : -kPosBig;
     const int k_off = row_frag_off<D>(lane), v_off = col_frag_off<D>(lane);
@@ -198,7 +206,23 @@ __device__ __forceinline__ void dkv_split(const BwdBf16& a, int block) {
     const int key = k0 + lk, keyc = min(key, N - 1);
 
     // 32-query blocks that see one of the keys, of every query head of the group in turn; wave wv takes every NW-th
-    const int qb_lo = k0 >> 5, nblk = (int)(min((long)N - 1, (long)k0 + 31 + w - 1) >> 5) - qb_lo + 1;
+    const int qb_lo = k0 >> 5, t_hi = (int)min((long)N - 1, (long)k0 + 31 + w - 1);
+    int nblk = (t_hi >> 5) - qb_lo + 1;
+    if (a.reach != nullptr) {  // up to the last that one of the heads needs: the gate has erased the keys for those behind it
+        const int k1 = min(k0 + 32, N) - 1, i_min = k1 / 64;
+        int last = i_min;
+        for (int g = 0; g < G && last < t_hi / 64; ++g) {
+            const size_t rows = (size_t)(bh0 + g) * N;
+            const float* ch = c + rows;
+            if (reach_pays(ch[t_hi] - ch[k1], t_hi - k1)) {
+                const OwnRows own = own_keys(a.reach + rows, k0 / 64, k0 / 64, N, ch[k0], sl);
+                last = max(last, last_needing_block(a.reach + rows, ch, i_min, t_hi / 64, N, own.reach2, own.edge + kErased, ch[k0], lane));
+            } else {
+                last = t_hi / 64;
+            }
+        }
+        nblk = __builtin_amdgcn_readfirstlane(min(t_hi >> 5, 2 * last + 1)) - qb_lo + 1;
+    }
     const int items = G * nblk, mine = items > wv ? (items - wv + NW - 1) / NW : 0;
     PieceLoader<D> loader;
     loader.init(lane);

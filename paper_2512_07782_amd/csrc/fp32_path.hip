@@ -1179,12 +1179,12 @@ __global__ __launch_bounds__(256) void rowdot_reach_f32_kernel(const float* __re
         }
         __syncthreads();
     }
-    if (threadIdx.x < 4 && t0 + (int)threadIdx.x < N) {
+    if (threadIdx.x < 4) {
         const bool look = queries || keys;
         const int i = threadIdx.x;
         float x = i == kReachNorm || i == kReachKeyNorm ? INFINITY : 0.f;
         if (look) x = i == kReachNorm ? __int_as_float(norm_s) : i == kReachEdge ? from_order(edge_s) : i == kReachKeyNorm ? __int_as_float(key_norm_s) : from_order(high_s);
-        reach[head + t0 + i] = x;
+        reach[head + reach_row(t0 / kReachRows, N) + i] = x;
     }
 }
 
@@ -1339,7 +1339,7 @@ static hipError_t launch_bwd_f32_mfma(const float* Q, const float* K, const floa
     constexpr size_t lds = sizeof(F32BwdSmem<D, NP>);
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_f32_mfma_kernel<D, NP>), lds, lds_allowed)) return e;
     const int nt = (N + 32 * NP - 1) / (32 * NP);
-    if (NP == 2 || !(scale > 0.f)) reach = nullptr;  // (bands of up to 128)
+    if (!(scale > 0.f) || (w < N ? w : N) <= kReachShortest) reach = nullptr;
     {
         ProfScope prof(kKernRowDot, s);
         const int blocks = (N + kReachRows - 1) / kReachRows;

@@ -47,6 +47,7 @@ struct BwdBf16 {
     float* Dv;
     __bf16 *dQ, *dK, *dV;
     float *dc_col, *dc_row;
+    const float* reach;  // norms of the row blocks (band_reach.h), or nullptr
     int B, H, Hkv, N, w;
     float scale;
 };

@@ -72,12 +72,13 @@ __global__ __launch_bounds__(64) void key_reach_kernel(const T* __restrict__ K, 
 }
 
 // Whether a forward looks at the reach of its keys, and by what blocks.  Where the gate then decays too little the launch is in vain, 2 to 3 us:
-// 1 % of the shortest forward that takes it for a window that only gates of more than 0.1 a key erase in part, 10 % for windows that all but the
-// slowest do, and there a forward of 25 us is 12 us with mu = -2 (the estimate is the rate of long forwards).  Below 600 keys hardly any gate does.
+// 2 to 3 % of the shortest forwards that take it for a window that only gates of more than 0.1 a key erase in part, and up to 10 % for
+// windows that all but the slowest do, where a forward of 30 us is one of 15 with mu = -2.  (us: at the rate of long forwards, which short
+// ones do not reach.)  Below 600 keys hardly any gate does.
 KeyReach reach_of_forward(int BH, int N, int d, int w, int tile, bool bf16) {
     const long band = w < N ? w : N;
     const double us = 4e-6 * BH * (double)N * band * d / (bf16 ? d == 128 ? 900.0 : 700.0 : 150.0) / (2 * band > N ? 2.0 : 1.0);
-    if (band < 600 || us < (band < 1500 ? 150.0 : 25.0)) return {0, tile};
+    if (band < 600 || us < (band < 1500 ? 100.0 : band < 1900 ? 50.0 : 20.0)) return {0, tile};
     long block = 64;
     while ((band + block) / block + 1 > 64) block *= 2;  // (an entry for each lane of a wave)
     return {(int)block, tile};
