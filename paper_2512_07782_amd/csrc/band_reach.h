@@ -1,10 +1,15 @@
 // How far the band of a tile reaches before the gate has erased it.
 //
-// exp2 returns zero for every argument below -126 (the smallest normal number; measured over -120 .. -151).  A key so far behind a
-// query that its score lies more than that below the query's reference has a probability of exactly zero, and then every
-// product it enters is zero: leaving it out changes no bit of O, L or a gradient.  The gate's decay grows along the band and
-// soon outweighs what a score can add, which the norms bound: scale |q.k| <= scale |q| |k|.  (Gates of softplus(N(-2, 1))
-// decay by 190 over 1024 keys, unit-variance rows of d = 128 have |q| |k| / sqrt(d) of 11 to 15: the far 480 keys are erased.)
+// The gate's decay grows along the band and soon outweighs what a score can add, which the norms bound: scale |q.k| <= scale |q| |k|.
+// A key whose score then lies below the reference of a row by more than the binary orders that an fp32 sum resolves has no part in it:
+//   kErased = 127  exp2 returns zero for every argument below -126 (the smallest normal number; measured over -120 .. -151), so the
+//                  probability is exactly zero and every product it enters is zero, whatever the values are
+//   kFaint = 64    the weights left out add up to less than 2^-52 of the row's (4096 keys); the values they would have multiplied are at most 2^16
+//                  times as large as those of rows close by (kOutweighs), so a sum misses less than 2^-36 of the values it is made of,
+//                  2^-12 of a rounding of fp32.  Where a block's rows outweigh that, the line is kErased.
+// Against the same kernels with whole bands O, L and gradients are the same bit for bit over 500 drawn steps, 13 of them with a changed order
+// of additions apart (split dK/dV kernel, grouped heads).  (softplus(N(-2, 1)) decays by 190 over 1024 keys, unit-variance rows of d = 128 have
+// |q| |k| / sqrt(d) of 11 to 15: the far 700 keys are left out.)
 //
 // So a pass over the rows in front of the kernels takes the largest norm of every block of them, and a workgroup shortens its band, in front
 // of its first step, by the blocks at the far end that are erased for all rows of its tile.  The pass costs one reading of a
@@ -32,15 +37,17 @@
 
 namespace gfwa {
 
-// Base-2 exponent below which a probability counts as zero: 126, and 1 for the roundings of scores and references.
-constexpr float kErased = 127.f;
+// Base-2 exponents below which a weight counts for nothing, with 1 for the roundings of scores and references, and the ratio of squared norms up
+// to which a block's rows count as no heavier than others.
+constexpr float kErased = 127.f, kFaint = 65.f, kOutweighs = 4294967296.f;
 // Whether it can pay to read norms: `decay` over the `len` rows that see a block (that it sees).  Scores of unit-variance rows add about
-// 14 to the 88 of kErased (in units of the gate); the pass reads for every row as much as 20 to 60 rows of a band take from the L2.  (Two
-// products compared, so that two kernels which ask the same always agree: there is nothing the compiler could fuse in one of them.)
-constexpr float kTypicalReach = 104.f;
-constexpr int kFewRows = 256;
-__device__ __forceinline__ bool reach_pays(float decay, int len) {
-    return decay > kTypicalReach && decay * (float)(len - kFewRows) > kTypicalReach * (float)len;
+// 15 to the 45 of kFaint (in units of the gate); `few` rows fewer have to be worth the reading, one matrix of three in front of the backward,
+// two in front of the forward, which are half of what it has to move at all.  (Two products compared, so that two kernels which ask the same
+// always agree: there is nothing the compiler could fuse in one of them.)
+constexpr float kTypicalReach = 61.f;
+constexpr int kFewForward = 384, kFewBackward = 128;
+__device__ __forceinline__ bool reach_pays(float decay, int len, int few) {
+    return decay > kTypicalReach && decay * (float)(len - few) > kTypicalReach * (float)len;
 }
 
 // Integers in the order of the floats (its own inverse); NaN, which must not let anything be erased, as the lowest or the highest.
@@ -97,14 +104,26 @@ __device__ __forceinline__ int norm_bits(float n2) { return __float_as_int(n2) &
 // What a wave (or workgroup) knows of its own rows: the largest squared norm, times (scale log2 e)^2 and a thousandth for the
 // roundings of norms and products.
 __device__ __forceinline__ float reach2_of(int norm, float sl) { return __int_as_float(norm) * (sl * sl * 1.004f); }
-// room: what a score would have to exceed, in base-2 exponents, for a weight
-__device__ __forceinline__ bool is_erased(float n2, float reach2, float room) { return room > 0.f && n2 * reach2 < room * room; }
+// room: what a score would have to exceed, in base-2 exponents, for a weight of 2^-kErased; light: kFaint will do
+__device__ __forceinline__ bool is_erased(float n2, float reach2, float room, bool light) {
+    if (light) room += kErased - kFaint;
+    return room > 0.f && n2 * reach2 < room * room;
+}
 
-// ---- keys in front of a query tile (forward).  A tile of queries from q0 finds in its own rows of O, as entry e, the largest squared norm
-// and the highest gate of the block of `block` keys that is e + 1 blocks before the one that holds q0 (key_reach.hip).
+// ---- keys in front of a query tile (forward).  A tile of queries from q0 finds in its own rows of O, as entry e, what there is to know of the
+// block of `block` keys that is e + 1 blocks before the one that holds q0 (key_reach.hip): the largest squared norms of its key and of its
+// value rows, each rounded up to bf16, and its highest gate.
 struct KeyBlock {
-    float n2, c;
+    unsigned norms;  // value rows in the upper half
+    float c;
+    __device__ __forceinline__ float k2() const { return __uint_as_float(norms << 16); }
+    __device__ __forceinline__ float v2() const { return __uint_as_float(norms & 0xffff0000u); }
 };
+constexpr int kInfBits = 0x7f800000;
+__device__ __forceinline__ unsigned pack_norms(int k2, int v2) {  // (NaN becomes infinite)
+    const unsigned k = (unsigned)min(k2, kInfBits) + 0xffffu, v = (unsigned)min(v2, kInfBits) + 0xffffu;
+    return (k >> 16) | (v & 0xffff0000u);
+}
 // Entries that `rows` rows of O have room for, T the storage type.  (A last tile of one to three rows may lack some: its band stays whole.)
 template <int D, typename T>
 __host__ __device__ __forceinline__ constexpr int key_blocks_in(int rows) { return rows * (D * (int)sizeof(T) / (int)sizeof(KeyBlock)); }
@@ -113,13 +132,15 @@ template <int D, typename T>
 __device__ __forceinline__ KeyBlock key_block(const T* first, int rows, int lane) {
     const bool there = lane < key_blocks_in<D, T>(rows);
     const KeyBlock kb = reinterpret_cast<const KeyBlock*>(first)[there ? lane : 0];
-    return {there ? kb.n2 : INFINITY, kb.c};
+    return {there ? kb.norms : pack_norms(kInfBits, kInfBits), kb.c};
 }
 // First key that the 32 queries of a wave need.  reach2 and `lowest` of the wave (lowest: the lowest exponent, relative to gate cbase,
-// that a weight of a row is measured against, less kErased).
+// that a weight of a row is measured against, less kErased).  Values close by are those of entry 0.
 __device__ __forceinline__ int first_needed_key(const KeyBlock& kb, int q0, int k_lo, int block, float reach2, float lowest, float cbase, int lane) {
     const int hi = q0 / block - 1, n = hi - k_lo / block + 1;  // (n <= 64, reach_of_forward sees to that)
-    const bool kept = lane < n && !is_erased(kb.n2, reach2, lowest - (kb.c - cbase) * kLog2e);
+    const float near_v2 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(kb.v2())));
+    const bool light = kb.v2() <= kOutweighs * near_v2;
+    const bool kept = lane < n && !is_erased(kb.k2(), reach2, lowest - (kb.c - cbase) * kLog2e, light);
     const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
     const int farthest = mask ? 63 - __builtin_clzll(mask) : -1;
     return max(k_lo, (hi - farthest) * block);
@@ -155,43 +176,56 @@ __device__ __forceinline__ int forward_reach(const bf16x8 (&q)[D / 16], const bf
     return over_waves<WAVES, true>(first_needed_key(kb, q0, k_lo, block, reach2, lowest, cbase, lane), at, wv, lane);
 }
 
-// ---- both sides of the backward.  The first rows of every 64-row block of dalpha hold the block's largest squared norm of Q and the lowest
-// (c - c of the block's first row) + L of its queries and, where a pass cannot look at its keys by itself (split kernels, fp32), the
-// largest squared norm of K and the highest gate of its keys: the row-dot kernels write them.  The whole-tile dK/dV kernel leaves as the fifth
-// value of the first block of each of its 128-key tiles the last 64-query block that needs one of the keys, for the dQ pass behind it.
-constexpr int kReachRows = 64, kReachNorm = 0, kReachEdge = 1, kReachKeyNorm = 2, kReachKeyHigh = 3, kReachLast = 4;
-constexpr int kReachShortest = 256;  // bands up to this long never pay (kFewRows)
-// Row of dalpha from which on block i has its five values: its first, or for a last block of less than five rows the ninth of the one before.
-__device__ __forceinline__ int reach_row(int i, int N) { return kReachRows * i + 5 <= N ? kReachRows * i : kReachRows * (i - 1) + 8; }
-// Last 64-query block from i_hi down to i_min + 1 that needs a key of a wave's, else i_min.  at: of the head.
-__device__ __forceinline__ int last_needing_block(const float* at, const float* ch, int i_min, int i_hi, int N, float reach2, float highest,
-                                                  float cbase, int lane) {
-    for (int top = i_hi; top > i_min; top -= 64) {
-        const int i = top - lane;
-        bool kept = i > i_min;
-        if (kept) {
-            const float* r = at + reach_row(i, N);
-            kept = !is_erased(r[kReachNorm], reach2, ((ch[64 * i] - cbase) + r[kReachEdge]) * kLog2e - highest);
-        }
-        const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
-        if (mask) return top - __builtin_ctzll(mask);
-    }
-    return i_min;
-}
-
-// What the table says of the own rows of a tile, blocks i0 .. i1 of queries (of keys).
-struct OwnRows {
-    float reach2, edge;  // edge: relative to gate cbase, in base-2 exponents; the lowest of the queries, the highest of the keys
+// ---- both sides of the backward.  Every 64-row block has values in its first rows of dalpha, which the row-dot kernels write:
+constexpr int kReachRows = 64;
+enum : int {
+    kReachNorm,      // largest squared norm of its query rows (infinite: the block is kept), ..
+    kReachEdge,      // .. lowest (c - c of the first row) + L,
+    kReachG, kReachD,       // .. largest squared norm of dO and square of D,
+    kReachOneK, kReachOneV,  // .. squared norms of its first key and value row: what such rows weigh here;
+    kReachKeyNorm,   // and, for passes that cannot look at their keys by themselves (split kernels, fp32), the largest squared norm of its
+    kReachKeyHigh,   // .. key rows, their highest gate
+    kReachValue,     // .. and the largest squared norm of its value rows.
+    kReachLast,      // From the whole-tile dK/dV kernel on, in the first block of its 128-key tiles: the last block of queries that needs a key.
+    kReachValues
 };
+constexpr int kReachShortest = kFewBackward;  // bands up to this long never pay
+// Row of dalpha from which on block i has its values: its first, or for a last block of too few rows the 17th of the one before.
+__device__ __forceinline__ int reach_row(int i, int N) { return kReachRows * i + kReachValues <= N ? kReachRows * i : kReachRows * (i - 1) + 16; }
+
+// What the own rows of a tile are: (scale log2 e |row|)^2 of the largest, their edge relative to gate cbase in base-2 exponents (the lowest of
+// queries, the highest of keys), and what rows weigh here.
+struct OwnRows {
+    float reach2, edge;
+    float q2, g2, d2;  // (of a key tile: those of the queries at the diagonal)
+    float k2, v2;      // (of a key tile: its own, 0 where the dQ pass looks by itself)
+};
+// Blocks i0 .. i1 of queries.
 __device__ __forceinline__ OwnRows own_queries(const float* at, const float* ch, int i0, int i1, int N, float cbase, float sl) {
     int norm = 0, edge = 0x7fffffff;
+    OwnRows own = {};
     for (int i = i0; i <= i1; ++i) {
         const float* r = at + reach_row(i, N);
         norm = max(norm, norm_bits(r[kReachNorm]));
         edge = min(edge, lowest_order((ch[64 * i] - cbase) + r[kReachEdge]));
+        own.k2 = fmaxf(own.k2, r[kReachOneK]);
+        own.v2 = fmaxf(own.v2, r[kReachOneV]);
     }
-    return {reach2_of(norm, sl), from_order(edge) * kLog2e};
+    own.reach2 = reach2_of(norm, sl);
+    own.edge = from_order(edge) * kLog2e;
+    return own;
 }
+// Blocks i0 .. i1 of queries at the diagonal of a key tile.
+__device__ __forceinline__ void own_weights(OwnRows& own, const float* at, int i0, int i1, int N) {
+    own.q2 = own.g2 = own.d2 = 0.f;
+    for (int i = i0; i <= i1; ++i) {
+        const float* r = at + reach_row(i, N);
+        own.q2 = fmaxf(own.q2, r[kReachNorm]);
+        own.g2 = fmaxf(own.g2, r[kReachG]);
+        own.d2 = fmaxf(own.d2, r[kReachD]);
+    }
+}
+// Blocks i0 .. i1 of keys.
 __device__ __forceinline__ OwnRows own_keys(const float* at, int i0, int i1, int N, float cbase, float sl) {
     int norm = 0, edge = (int)0x80000000;
     for (int i = i0; i <= i1; ++i) {
@@ -199,21 +233,78 @@ __device__ __forceinline__ OwnRows own_keys(const float* at, int i0, int i1, int
         norm = max(norm, norm_bits(r[kReachKeyNorm]));
         edge = max(edge, highest_order(r[kReachKeyHigh] - cbase));
     }
-    return {reach2_of(norm, sl), from_order(edge) * kLog2e};
+    OwnRows own = {};
+    own.reach2 = reach2_of(norm, sl);
+    own.edge = from_order(edge) * kLog2e;
+    own_weights(own, at, i0, i1, N);
+    return own;
 }
-// First 64-key block from i_lo on that is needed, i_max if none before it is.
-__device__ __forceinline__ int first_needed_block(const float* at, int i_lo, int i_max, int N, float reach2, float lowest, float cbase, int lane) {
+// Last block of queries from i_hi down to i_min + 1 that needs one of the keys, else i_min.  at: of the head.
+__device__ __forceinline__ int last_needing_block(const float* at, const float* ch, int i_min, int i_hi, int N, const OwnRows& own, float cbase, int lane) {
+    for (int top = i_hi; top > i_min; top -= 64) {
+        const int i = top - lane;
+        bool kept = i > i_min;
+        if (kept) {
+            const float* r = at + reach_row(i, N);
+            const bool light = r[kReachNorm] <= kOutweighs * own.q2 && r[kReachG] <= kOutweighs * own.g2 && r[kReachD] <= kOutweighs * own.d2 &&
+                               own.k2 <= kOutweighs * r[kReachOneK] && own.v2 <= kOutweighs * r[kReachOneV];
+            kept = !is_erased(r[kReachNorm], own.reach2, ((ch[64 * i] - cbase) + r[kReachEdge]) * kLog2e - own.edge - kErased, light);
+        }
+        const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
+        if (mask) return top - __builtin_ctzll(mask);
+    }
+    return i_min;
+}
+// First block of keys from i_lo on that is needed, i_max if none before it is.
+__device__ __forceinline__ int first_needed_block(const float* at, int i_lo, int i_max, int N, const OwnRows& own, float cbase, int lane) {
     for (int base = i_lo; base < i_max; base += 64) {
         const int i = base + lane;
         bool kept = i < i_max;
         if (kept) {
             const float* r = at + reach_row(i, N);
-            kept = !is_erased(r[kReachKeyNorm], reach2, lowest - (r[kReachKeyHigh] - cbase) * kLog2e);
+            const bool light = r[kReachKeyNorm] <= kOutweighs * own.k2 && r[kReachValue] <= kOutweighs * own.v2;
+            kept = !is_erased(r[kReachKeyNorm], own.reach2, own.edge - kErased - (r[kReachKeyHigh] - cbase) * kLog2e, light);
         }
         const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
         if (mask) return base + __builtin_ctzll(mask);
     }
     return i_max;
+}
+// What a row-dot workgroup has gathered of a block, `row` its place (one thread).  looked: whether it has; else the block is kept.
+struct BlockValues {
+    int norm, edge, g, d, one_k, one_v, key_norm, high, value;
+};
+__device__ __forceinline__ void write_block(float* row, const BlockValues& b, bool looked, bool keys) {
+    row[kReachNorm] = looked ? __int_as_float(b.norm) : INFINITY;
+    row[kReachEdge] = looked ? from_order(b.edge) : 0.f;
+    row[kReachG] = looked ? __int_as_float(b.g) : 0.f;
+    row[kReachD] = looked ? __int_as_float(b.d) : 0.f;
+    row[kReachOneK] = looked ? __int_as_float(b.one_k) : 0.f;
+    row[kReachOneV] = looked ? __int_as_float(b.one_v) : 0.f;
+    if (!keys) return;
+    row[kReachKeyNorm] = looked ? __int_as_float(b.key_norm) : INFINITY;
+    row[kReachKeyHigh] = looked ? from_order(b.high) : 0.f;
+    row[kReachValue] = looked ? __int_as_float(b.value) : 0.f;
+}
+// Over the workgroup, from all waves' lanes; at: of LDS.
+template <bool KEYS>
+__device__ __forceinline__ void gather_block(BlockValues* at, BlockValues b) {
+    if (threadIdx.x == 0) *at = {0, 0x7fffffff, 0, 0, b.one_k, b.one_v, 0, (int)0x80000000, 0};
+    b.norm = lanes_max(b.norm), b.edge = lanes_min(b.edge), b.g = lanes_max(b.g), b.d = lanes_max(b.d);
+    if (KEYS) b.key_norm = lanes_max(b.key_norm), b.high = lanes_max(b.high), b.value = lanes_max(b.value);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        atomicMax(&at->norm, b.norm);
+        atomicMin(&at->edge, b.edge);
+        atomicMax(&at->g, b.g);
+        atomicMax(&at->d, b.d);
+        if (KEYS) {
+            atomicMax(&at->key_norm, b.key_norm);
+            atomicMax(&at->high, b.high);
+            atomicMax(&at->value, b.value);
+        }
+    }
+    __syncthreads();
 }
 
 }  // namespace gfwa

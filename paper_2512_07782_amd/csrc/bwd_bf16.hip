@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restri
                                                           int w, int blocks, int H, int G) {
     constexpr int LPR = D / 8;  // lanes per row, 16 bytes each
     constexpr int kRows = 256 / LPR, kPasses = kReachRows / kRows;
-    __shared__ int norm_s, edge_s, key_norm_s, high_s;
+    __shared__ BlockValues values;
     const int bh = (int)blockIdx.x / blocks, t0 = (int)blockIdx.x % blocks * kReachRows;
     const size_t head = (size_t)bh * N;
     const int part = threadIdx.x % LPR, r0 = t0 + threadIdx.x / LPR;
@@ -63,13 +63,8 @@ __global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restri
         b[p] = *reinterpret_cast<const bf16x8*>(dO + at);
     }
     const float c0 = c[head + t0];
-    const int far = max(0, t0 - w + 1);
-    bool look = reach != nullptr && reach_pays(c0 - c[head + far], t0 - far);
-    if (KEYS && reach != nullptr) {
-        const int end = (int)min((long)N - 1, (long)t0 + kReachRows - 2 + w);
-        look |= reach_pays(c[head + end] - c0, end - t0);
-    }
-    if (look && threadIdx.x == 0) norm_s = key_norm_s = 0, edge_s = 0x7fffffff, high_s = (int)0x80000000;
+    const int far = max(0, t0 - w + 1), end = (int)min((long)N - 1, (long)t0 + kReachRows - 2 + w);
+    const bool look = reach != nullptr && (reach_pays(c0 - c[head + far], t0 - far, kFewBackward) || reach_pays(c[head + end] - c0, end - t0, kFewBackward));
     float dot[kPasses];
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
@@ -81,44 +76,31 @@ __global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restri
         if (part == 0 && r0 + p * kRows < N) Dv[head + r0 + p * kRows] = dot[p];
     }
     if (look) {
-        const size_t kv = KEYS ? (size_t)kv_head_of(bh, H, G) * N : 0;
-        int norm = 0, edge = 0x7fffffff, key_norm = 0, high = (int)0x80000000;
+        const size_t kv = (size_t)kv_head_of(bh, H, G) * N;
+        auto norm_of = [&](const bf16_t* x) {
+            const bf16x8 v = *reinterpret_cast<const bf16x8*>(x + 8 * part);
+            return row_sum<LPR>(dot8(v, v, 0.f));
+        };
+        BlockValues mine = {0, 0x7fffffff, 0, 0, norm_bits(norm_of(K + (kv + t0) * D)), norm_bits(norm_of(V + (kv + t0) * D)), 0, (int)0x80000000, 0};
 #pragma unroll
         for (int p = 0; p < kPasses; ++p) {
             const int r = min(r0 + p * kRows, N - 1);
             const size_t row = head + r;
-            auto norm_of = [&](const bf16_t* x) {
-                const bf16x8 v = *reinterpret_cast<const bf16x8*>(x + 8 * part);
-                return row_sum<LPR>(dot8(v, v, 0.f));
-            };
             // (D is not finite if a value of dO is not)
-            norm = max(norm, finite(dot[p]) ? norm_bits(norm_of(Q + row * D)) : 0x7fffffff);
-            edge = min(edge, lowest_order((c[row] - c0) + L[row]));
+            mine.norm = max(mine.norm, finite(dot[p]) ? norm_bits(norm_of(Q + row * D)) : kInfBits);
+            mine.edge = min(mine.edge, lowest_order((c[row] - c0) + L[row]));
+            mine.g = max(mine.g, norm_bits(row_sum<LPR>(dot8(b[p], b[p], 0.f))));
+            mine.d = max(mine.d, norm_bits(dot[p] * dot[p]));
             if (KEYS) {
-                key_norm = max(key_norm, finite(norm_of(V + (kv + r) * D)) ? norm_bits(norm_of(K + (kv + r) * D)) : 0x7fffffff);
-                high = max(high, highest_order(c[row]));
+                const float v2 = norm_of(V + (kv + r) * D);
+                mine.key_norm = max(mine.key_norm, finite(v2) ? norm_bits(norm_of(K + (kv + r) * D)) : kInfBits);
+                mine.high = max(mine.high, highest_order(c[row]));
+                mine.value = max(mine.value, norm_bits(v2));
             }
         }
-        norm = lanes_max(norm);
-        edge = lanes_min(edge);
-        if (KEYS) key_norm = lanes_max(key_norm), high = lanes_max(high);
-        __syncthreads();
-        if ((threadIdx.x & 63) == 0) {
-            atomicMax(&norm_s, norm);
-            atomicMin(&edge_s, edge);
-            if (KEYS) atomicMax(&key_norm_s, key_norm), atomicMax(&high_s, high);
-        }
-        __syncthreads();
+        gather_block<KEYS>(&values, mine);
     }
-    if (reach != nullptr && threadIdx.x == 0) {
-        float* at = reach + head + reach_row(t0 / kReachRows, N);
-        at[kReachNorm] = look ? __int_as_float(norm_s) : INFINITY;
-        at[kReachEdge] = look ? from_order(edge_s) : 0.f;
-        if (KEYS) {
-            at[kReachKeyNorm] = look ? __int_as_float(key_norm_s) : INFINITY;
-            at[kReachKeyHigh] = look ? from_order(high_s) : 0.f;
-        }
-    }
+    if (reach != nullptr && threadIdx.x == 0) write_block(reach + head + reach_row(t0 / kReachRows, N), values, look, KEYS);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -151,7 +133,7 @@ __device__ __forceinline__ int last_query_tile(const Keys& keys, const float* ch
     const int i_hi = t_hi / kTileRows, k1 = min(k0 + 128, N) - 1, i_min = k1 / kTileRows;
     int last = i_hi;
     if (at == nullptr) return last;
-    if (i_hi > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1)) {
+    if (i_hi > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1, kFewBackward)) {
         float k2 = 0.f, v2 = 0.f;
 #pragma unroll
         for (int kc = 0; kc < D / 16; ++kc) {
@@ -160,11 +142,18 @@ __device__ __forceinline__ int last_query_tile(const Keys& keys, const float* ch
             k2 = dot8(k, k, k2);
             v2 = dot8(v, v, v2);
         }
+        v2 = xhalf_sum(v2);
+        k2 = xhalf_sum(k2);
         // (a value row that is not finite keeps everything: its dP is not either)
-        const int norm = lanes_max(finite(xhalf_sum(v2)) ? norm_bits(xhalf_sum(k2)) : 0x7fffffff);
-        const float highest = from_order(lanes_max(highest_order(ch[min(key, N - 1)] - cbase))) * kLog2e + kErased;
-        const int own = last_needing_block(at, ch, i_min, i_hi, N, reach2_of(norm, sl), highest, cbase, lane);
-        last = over_waves<WAVES, false>(own, needed, wv, lane);
+        const int norm = lanes_max(finite(v2) ? norm_bits(k2) : kInfBits);
+        OwnRows own = {};
+        own.reach2 = reach2_of(norm, sl);
+        own.edge = from_order(lanes_max(highest_order(ch[min(key, N - 1)] - cbase))) * kLog2e;
+        own.k2 = __int_as_float(norm);
+        own.v2 = __int_as_float(lanes_max(norm_bits(v2)));
+        own_weights(own, at, k0 / kReachRows, i_min, N);
+        const int needing = last_needing_block(at, ch, i_min, i_hi, N, own, cbase, lane);
+        last = over_waves<WAVES, false>(needing, needed, wv, lane);
     }
     if (threadIdx.x == 0) reinterpret_cast<int*>(at)[reach_row(k0 / kReachRows, N) + kReachLast] = last;
     return last;
@@ -1129,7 +1118,7 @@ static bool bwd_in_one_launch(int BH, int BHkv, int N, int d, int w) {
 //   H1 N2000 d64 causal    36 /  38    35 /  39    35 /  33      H8 N2000 d128 causal   120 / 125   120 / 122   120 /  91
 //   H4 N8192 d64 w4096    192 / 198   189 / 106   189 /  73      H1 N16384 d128 w4096   246 / 251   247 / 138   246 /  96
 //   H4 N3000 d64 w1600     50 /  55    50 /  57    50 /  51  (this one does not take it)
-static bool bwd_split_looks(int N, int w) { return (w < N ? w : N) >= 1900; }
+static bool bwd_split_looks(int N, int w) { return (w < N ? w : N) >= 1500; }
 
 template <int D>
 static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO,

@@ -531,7 +531,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) voi
 
     const int k_lo = max(0, q0 - w + 1), jb_hi = (min(N, q0 + BQ) - 1) / 32;
     int first_key = k_lo;
-    if (reach_block != 0 && reach_pays(ch[q0] - ch[k_lo], q0 - k_lo)) {  // the keys that the gate has erased for all queries stay out
+    if (reach_block != 0 && reach_pays(ch[q0] - ch[k_lo], q0 - k_lo, kFewForward)) {  // the keys that the gate has erased for all queries stay out
         float q2 = 0.f, k2 = 0.f, own = 0.f;
         const float *qr = Q + ho + (size_t)tc * D + 4 * h, *kr = Kh + (size_t)tc * D + 4 * h;  // (the halves take every other four columns)
 #pragma unroll 4
@@ -707,10 +707,10 @@ __device__ __forceinline__ void dq_f32_mfma(
         const float *Kh = K + kvo, *Vh = V + kvo, *ch = c + (size_t)bh * N;
 
         int first_key = max(0, q0 - w + 1);
-        if (reach != nullptr && reach_pays(ch[q0] - ch[first_key], q0 - first_key)) {  // the keys that the gate has erased for all queries stay out
+        if (reach != nullptr && reach_pays(ch[q0] - ch[first_key], q0 - first_key, kFewBackward)) {  // the keys that the gate has erased for all queries stay out
             const float* at = reach + (size_t)bh * N;
             const OwnRows own = own_queries(at, ch, q0 / 64, (min(N, q0 + 32 * NP) - 1) / 64, N, ch[q0], scale * kLog2e);
-            first_key = max(first_key, 64 * first_needed_block(at, first_key / 64, q0 / 64, N, own.reach2, own.edge - kErased, ch[q0], lane));
+            first_key = max(first_key, 64 * first_needed_block(at, first_key / 64, q0 / 64, N, own, ch[q0], lane));
         }
         const int jb_lo = first_key / 32, jb_hi = (min(N, q0 + 32 * NP) - 1) / 32;
         using Mover = F32TileMover<D, 128 * NP>;
@@ -905,9 +905,9 @@ __device__ __forceinline__ void dkv_f32_mfma(
             const size_t rows = (size_t)(bh0 + g) * N;
             const float* ch = c + rows;
             const int k1 = min(k0 + 32 * NP, N) - 1, i_min = k1 / 64;
-            if (reach != nullptr && t_hi / 64 > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1)) {
+            if (reach != nullptr && t_hi / 64 > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1, kFewBackward)) {
                 const OwnRows own = own_keys(reach + rows, k0 / 64, k1 / 64, N, ch[k0], scale * kLog2e);
-                qb_hi = min(qb_hi, 2 * last_needing_block(reach + rows, ch, i_min, t_hi / 64, N, own.reach2, own.edge + kErased, ch[k0], lane) + 1);
+                qb_hi = min(qb_hi, 2 * last_needing_block(reach + rows, ch, i_min, t_hi / 64, N, own, ch[k0], lane) + 1);
             }
             return __builtin_amdgcn_readfirstlane(qb_hi) - qb_lo + 1;
         };
@@ -1137,55 +1137,46 @@ __global__ __launch_bounds__(256) void rowdot_reach_f32_kernel(const float* __re
                                                                int N, int w, int blocks, int H, int G) {
     using Step = RowStep<D, 1>;
     constexpr int kLanes = Step::kLanes, kRows = 4 * Step::kRows, kPasses = kReachRows / kRows;
-    __shared__ int norm_s, edge_s, key_norm_s, high_s;
+    __shared__ BlockValues values;
     const int lane = threadIdx.x & 63, bh = (int)blockIdx.x / blocks, t0 = (int)blockIdx.x % blocks * kReachRows;
     const size_t head = (size_t)bh * N, kv = (size_t)kv_head_of(bh, H, G) * N;
     const int r0 = t0 + threadIdx.x / kLanes, col = 4 * (lane % kLanes);
     auto row_of = [&](int p) { return min(r0 + p * kRows, N - 1); };
-    float d[kPasses];
+    float d[kPasses], g2[kPasses];
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
-        Step o;
+        Step o, go;
         o.x[0] = *reinterpret_cast<const f32x4*>(O + (head + row_of(p)) * D + col);
-        d[p] = o.dot(*reinterpret_cast<const f32x4*>(dO + (head + row_of(p)) * D + col), 0);
+        go.x[0] = *reinterpret_cast<const f32x4*>(dO + (head + row_of(p)) * D + col);
+        d[p] = o.dot(go.x[0], 0);
+        g2[p] = go.dot(go.x[0], 0);
         if (r0 + p * kRows < N && lane % kLanes == 0) Dv[head + row_of(p)] = d[p];
     }
     const float* ch = c + head;
-    const int far = max(0, t0 - w + 1), t1 = min(t0 + kReachRows, N) - 1, end = (int)min((long)N - 1, (long)t1 + w - 1);
-    const bool queries = reach_pays(ch[t0] - ch[far], t0 - far), keys = reach_pays(ch[end] - ch[t0], end - t0);
-    if (queries || keys) {
-        if (threadIdx.x == 0) norm_s = key_norm_s = 0, edge_s = 0x7fffffff, high_s = (int)0x80000000;
-        __syncthreads();
+    const int far = max(0, t0 - w + 1), end = (int)min((long)N - 1, (long)t0 + kReachRows - 2 + w);
+    const bool look = reach_pays(ch[t0] - ch[far], t0 - far, kFewBackward) || reach_pays(ch[end] - ch[t0], end - t0, kFewBackward);
+    if (look) {
         auto norm_of = [&](const float* row) {
             Step x;
             x.x[0] = *reinterpret_cast<const f32x4*>(row + col);
             return x.dot(x.x[0], 0);
         };
-        int norm = 0, edge = 0x7fffffff, key_norm = 0, high = (int)0x80000000;
+        BlockValues mine = {0, 0x7fffffff, 0, 0, norm_bits(norm_of(K + (kv + t0) * D)), norm_bits(norm_of(V + (kv + t0) * D)), 0, (int)0x80000000, 0};
 #pragma unroll
         for (int p = 0; p < kPasses; ++p) {
             const int row = row_of(p);
-            norm = max(norm, finite(d[p]) ? norm_bits(norm_of(Q + (head + row) * D)) : 0x7fffffff);
-            edge = min(edge, lowest_order((ch[row] - ch[t0]) + L[head + row]));
-            key_norm = max(key_norm, finite(norm_of(V + (kv + row) * D)) ? norm_bits(norm_of(K + (kv + row) * D)) : 0x7fffffff);
-            high = max(high, highest_order(ch[row]));
+            const float v2 = norm_of(V + (kv + row) * D);
+            mine.norm = max(mine.norm, finite(d[p]) ? norm_bits(norm_of(Q + (head + row) * D)) : kInfBits);
+            mine.edge = min(mine.edge, lowest_order((ch[row] - ch[t0]) + L[head + row]));
+            mine.g = max(mine.g, norm_bits(g2[p]));
+            mine.d = max(mine.d, norm_bits(d[p] * d[p]));
+            mine.key_norm = max(mine.key_norm, finite(v2) ? norm_bits(norm_of(K + (kv + row) * D)) : kInfBits);
+            mine.high = max(mine.high, highest_order(ch[row]));
+            mine.value = max(mine.value, norm_bits(v2));
         }
-        norm = lanes_max(norm), edge = lanes_min(edge), key_norm = lanes_max(key_norm), high = lanes_max(high);
-        if (lane == 0) {
-            atomicMax(&norm_s, norm);
-            atomicMin(&edge_s, edge);
-            atomicMax(&key_norm_s, key_norm);
-            atomicMax(&high_s, high);
-        }
-        __syncthreads();
+        gather_block<true>(&values, mine);
     }
-    if (threadIdx.x < 4) {
-        const bool look = queries || keys;
-        const int i = threadIdx.x;
-        float x = i == kReachNorm || i == kReachKeyNorm ? INFINITY : 0.f;
-        if (look) x = i == kReachNorm ? __int_as_float(norm_s) : i == kReachEdge ? from_order(edge_s) : i == kReachKeyNorm ? __int_as_float(key_norm_s) : from_order(high_s);
-        reach[head + reach_row(t0 / kReachRows, N) + i] = x;
-    }
+    if (threadIdx.x == 0) write_block(reach + head + reach_row(t0 / kReachRows, N), values, look, true);
 }
 
 // Bands that workgroups of 64 queries (keys) serve better than larger ones: d = 64, at most 128 long.  A workgroup walks

@@ -153,7 +153,7 @@ __device__ __forceinline__ void fwd_tile(
 #pragma unroll
         for (int kc = 0; kc < KC; ++kc) qf[kc] = *reinterpret_cast<const bf16x8*>(qp + 16 * kc);
     }
-    if (reach_block != 0 && reach_pays(cbase - ch[k_lo], q0 - k_lo)) {  // the keys that the gate has erased for all 128 queries stay out
+    if (reach_block != 0 && reach_pays(cbase - ch[k_lo], q0 - k_lo, kFewForward)) {  // the keys that the gate has erased for all 128 queries stay out
         const int first = forward_reach<D, kFwdWaves>(qf, K + kv_off + (size_t)min(t, N - 1) * D + 8 * h,
                                                       key_block<D>(O + head_off + (size_t)q0 * D, min(128, N - q0), lane), cq, q0, k_lo, reach_block,
                                                       cbase, sl, sm.needed, wv, lane);

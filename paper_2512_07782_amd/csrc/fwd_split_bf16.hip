@@ -56,7 +56,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_split
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) GFWA_PIN(qf[kc]);
     const int k_lo = max(0, q0 - w + 1);
-    if (reach_block != 0 && reach_pays(band.cbase - band.ch[k_lo], q0 - k_lo))  // what the gate has erased for all queries stays out
+    if (reach_block != 0 && reach_pays(band.cbase - band.ch[k_lo], q0 - k_lo, kFewForward))  // what the gate has erased for all queries stays out
         band.from(forward_reach<D, NW>(qf, K + kv_off + (size_t)tc * D + 8 * h, key_block<D>(O + head_off + (size_t)q0 * D, min(32 * QW, N - q0), lane), cq,
                                        q0, k_lo, reach_block, band.cbase, sl, sm.needed, band.wv, lane),
                   q0, w);

@@ -1,4 +1,4 @@
-// Norms and gates of the key blocks in front of the query tiles of a forward (band_reach.h): largest squared norm and highest gate of
+// Norms and gates of the key blocks in front of the query tiles of a forward (band_reach.h): largest squared norms and highest gate of
 // every block of keys, written into the rows of O of the tiles that see it.
 //
 // Memory bounds it where it reads (K and V once: B4 H16 N8192 d128, 268 MB, 43 us, 6.2 TB/s), the launch where no tile asks.
@@ -38,13 +38,13 @@ __global__ __launch_bounds__(64) void key_reach_kernel(const T* __restrict__ K, 
     auto asks = [&](int g, int t) __attribute__((always_inline)) {
         const float* ch = c + (size_t)(bh0 + g) * N;
         const int q0 = (t_lo + t) * tile, k_lo = max(0, q0 - w + 1);
-        return reach_pays(ch[q0] - ch[k_lo], q0 - k_lo);
+        return reach_pays(ch[q0] - ch[k_lo], q0 - k_lo, kFewForward);
     };
     bool any = false;
     for (int g = 0; g < G; ++g)
         for (int t = lane; t < nt; t += 64) any |= asks(g, t);
     if (__builtin_amdgcn_ballot_w64(any) == 0) return;
-    int norm = 0;
+    int norm = 0, value = 0;
     const size_t at = (size_t)bkv * N * D + 8 * (lane % kLanes);
     for (int r0 = k0 + lane / kLanes; r0 - lane / kLanes < k1; r0 += U * kRows) {
         float nk[U], nv[U];
@@ -55,9 +55,13 @@ __global__ __launch_bounds__(64) void key_reach_kernel(const T* __restrict__ K, 
             nv[u] = square8(V + row, 0.f);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) norm = max(norm, finite(nv[u]) ? norm_bits(row_sum<kLanes>(nk[u])) : 0x7fffffff);
+        for (int u = 0; u < U; ++u) {
+            const float v2 = row_sum<kLanes>(nv[u]);
+            norm = max(norm, finite(v2) ? norm_bits(row_sum<kLanes>(nk[u])) : kInfBits);  // (a value row that is not finite keeps its block)
+            value = max(value, norm_bits(v2));
+        }
     }
-    norm = lanes_max(norm);
+    const unsigned norms = pack_norms(lanes_max(norm), lanes_max(value));
     for (int g = 0; g < G; ++g) {
         const float* ch = c + (size_t)(bh0 + g) * N;
         int high = (int)0x80000000;
@@ -66,7 +70,7 @@ __global__ __launch_bounds__(64) void key_reach_kernel(const T* __restrict__ K, 
         for (int t = lane; t < nt; t += 64) {
             const int q0 = (t_lo + t) * tile, e = q0 / block - 1 - kb;
             if (asks(g, t) && e < key_blocks_in<D, T>(min(tile, N - q0)))
-                reinterpret_cast<KeyBlock*>(O + ((size_t)(bh0 + g) * N + q0) * D)[e] = {__int_as_float(norm), from_order(high)};
+                reinterpret_cast<KeyBlock*>(O + ((size_t)(bh0 + g) * N + q0) * D)[e] = {norms, from_order(high)};
         }
     }
 }
@@ -78,7 +82,7 @@ __global__ __launch_bounds__(64) void key_reach_kernel(const T* __restrict__ K, 
 KeyReach reach_of_forward(int BH, int N, int d, int w, int tile, bool bf16) {
     const long band = w < N ? w : N;
     const double us = 4e-6 * BH * (double)N * band * d / (bf16 ? d == 128 ? 900.0 : 700.0 : 150.0) / (2 * band > N ? 2.0 : 1.0);
-    if (band < 600 || us < (band < 1500 ? 100.0 : band < 1900 ? 50.0 : 20.0)) return {0, tile};
+    if (band < 600 || us < (band < 900 ? 100.0 : band < 1300 ? 50.0 : 20.0)) return {0, tile};
     long block = 64;
     while ((band + block) / block + 1 > 64) block *= 2;  // (an entry for each lane of a wave)
     return {(int)block, tile};
