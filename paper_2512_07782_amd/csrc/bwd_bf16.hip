@@ -807,14 +807,18 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_bf16_kernel(
         const int key = min(j * kTileRows + tid, N - 1);
         return ch[key];
     };
+    float g_first = tid < kTileRows ? gate_of(j_lo) : 0.f;
     loader.load(Kh, Vh, j_lo, jfull, N, sm.kv.a[0], sm.kv.b[0]);
-    const int j_seen = 2 * seen.first(q0 / kTileRows);
-    if (j_seen > j_lo) {  // the gate has erased the tiles before
-        j_lo = j_seen;
-        __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
-        loader.load(Kh, Vh, j_lo, jfull, N, sm.kv.a[0], sm.kv.b[0]);
+    if (reach != nullptr) {
+        const int j_seen = 2 * seen.first(q0 / kTileRows);
+        if (j_seen > j_lo) {  // the gate has erased the tiles before
+            j_lo = j_seen;
+            __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+            if (tid < kTileRows) g_first = gate_of(j_lo);
+            loader.load(Kh, Vh, j_lo, jfull, N, sm.kv.a[0], sm.kv.b[0]);
+        }
     }
-    if (tid < kTileRows) sm.g[0][tid] = (gate_of(j_lo) - cbase) * inv_scale;
+    if (tid < kTileRows) sm.g[0][tid] = (g_first - cbase) * inv_scale;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
@@ -1009,14 +1013,16 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_spill_bf16_kernel(
         }
     };
     issue(j_lo, 0);
-    const int j_seen = 2 * seen.first(q0 / kTileRows);
-    stored = seen.look(qw0 / kTileRows);
-    if (j_seen > j_lo) {  // the gate has erased the tiles before
-        j_lo = j_seen;
-        __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
-        issue(j_lo, 0);
+    if (reach != nullptr) {
+        const int j_seen = 2 * seen.first(q0 / kTileRows);
+        stored = seen.look(qw0 / kTileRows);
+        if (j_seen > j_lo) {  // the gate has erased the tiles before
+            j_lo = j_seen;
+            __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+            issue(j_lo, 0);
+        }
+        there = (stored >> ((j_lo >> 1) - seen.from)) & 1;
     }
-    there = (stored >> ((j_lo >> 1) - seen.from)) & 1;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
