@@ -31,8 +31,10 @@
 //             B4 H16/4 N4096 d64  causal       575 / 347    555 / 200    552 / 133
 //   fp32, whole step  B2 H16 N4096 d128 w1024              1430 /1082   1430 / 745
 #pragma once
+#include <initializer_list>
 #include <type_traits>
 
+#include "gfwa_internal.h"
 #include "tile_stage.h"
 
 namespace gfwa {
@@ -192,6 +194,17 @@ enum : int {
 constexpr int kReachShortest = kFewBackward;  // bands up to this long never pay
 // Row of dalpha from which on block i has its values: its first, or for a last block of too few rows the 17th of the one before.
 __device__ __forceinline__ int reach_row(int i, int N) { return kReachRows * i + kReachValues <= N ? kReachRows * i : kReachRows * (i - 1) + 16; }
+
+// dalpha, if the passes of a backward may leave rows out and may use it as scratch, else nullptr.
+inline float* backward_reach(float* dalpha, const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* c, const float* L,
+                             size_t size, int B, int H, int Hkv, int N, int d, int w, float scale) {
+    const size_t rows = (size_t)B * H * N, gate = rows * sizeof(float), q = rows * d * size, kv = (size_t)B * Hkv * N * d * size;
+    bool free = scale > 0.f && (w < N ? w : N) > kReachShortest;
+    for (const void* m : {Q, O, dO}) free = free && !overlap(dalpha, gate, m, q);
+    for (const void* m : {K, V}) free = free && !overlap(dalpha, gate, m, kv);
+    for (const float* v : {c, L}) free = free && !overlap(dalpha, gate, v, gate);
+    return free ? dalpha : nullptr;
+}
 
 // What the own rows of a tile are: (scale log2 e |row|)^2 of the largest, their edge relative to gate cbase in base-2 exponents (the lowest of
 // queries, the highest of keys), and what rows weigh here.

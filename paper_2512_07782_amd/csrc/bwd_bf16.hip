@@ -1157,7 +1157,8 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     // form D by themselves, so the row-dot launch is one more where they look at the norms.  (A split dK/dV pass leaves no limits for the
     // whole-tile dQ kernels.)
     const bool some_split = dkv_split || dq_split;
-    float* reach = scale > 0.f && (w < N ? w : N) > kReachShortest && (!some_split || bwd_split_looks(N, w)) ? dalpha : nullptr;
+    float* reach = backward_reach(dalpha, Q, K, V, O, dO, c, L, sizeof(bf16_t), B, H, Hkv, N, D, w, scale);
+    if (some_split && !bwd_split_looks(N, w)) reach = nullptr;
     const float* seen = dkv_split ? nullptr : reach;
     if (some_split && reach != nullptr) {
         rowdot(std::true_type{}, reach);

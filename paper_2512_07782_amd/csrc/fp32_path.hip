@@ -1236,10 +1236,10 @@ static hipError_t launch_fwd_f32_mfma(const float* Q, const float* K, const floa
     constexpr size_t lds = sizeof(F32FwdSmem<D, S>);
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&fwd_f32_mfma_kernel<D, NW, S>), lds, lds_allowed)) return e;
     const int nq = (N + 32 * NW - 1) / (32 * NW), total = B * H * nq;
-    const KeyReach reach = scale > 0.f ? reach_of_forward(B * H, N, D, w, 32 * NW, false) : KeyReach{0, 32 * NW};
-    if (hipError_t e = key_reach(reach, false, K, V, c, O, B, H, Hkv, N, D, w, s)) return e;
+    int reach_block = 0;
+    if (hipError_t e = key_reach(reach_block, 32 * NW, false, Q, K, V, c, O, B, H, Hkv, N, D, w, scale, s)) return e;
     hipLaunchKernelGGL((fwd_f32_mfma_kernel<D, NW, S>), dim3(total), dim3(64 * NW), lds, s, Q, K, V, c, O, L, N, w, scale, nq, total,
-                       H, H / Hkv, reach.block);
+                       H, H / Hkv, reach_block);
     return hipGetLastError();
 }
 
@@ -1330,7 +1330,7 @@ static hipError_t launch_bwd_f32_mfma(const float* Q, const float* K, const floa
     constexpr size_t lds = sizeof(F32BwdSmem<D, NP>);
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_f32_mfma_kernel<D, NP>), lds, lds_allowed)) return e;
     const int nt = (N + 32 * NP - 1) / (32 * NP);
-    if (!(scale > 0.f) || (w < N ? w : N) <= kReachShortest) reach = nullptr;
+    reach = backward_reach(reach, Q, K, V, O, dO, c, L, sizeof(float), B, H, Hkv, N, D, w, scale);
     {
         ProfScope prof(kKernRowDot, s);
         const int blocks = (N + kReachRows - 1) / kReachRows;

@@ -389,10 +389,10 @@ static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const 
         }
     }
     ProfScope prof(kKernForward, s);
-    const KeyReach reach = scale > 0.f ? reach_of_forward(B * H, N, D, w, 128, true) : KeyReach{0, 128};
-    if (hipError_t e = key_reach(reach, true, K, V, c, O, B, H, Hkv, N, D, w, s)) return e;
+    int reach_block = 0;
+    if (hipError_t e = key_reach(reach_block, 128, true, Q, K, V, c, O, B, H, Hkv, N, D, w, scale, s)) return e;
     hipLaunchKernelGGL(kernel, dim3(total), dim3(64 * kFwdWaves), lds, s, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, c,
-                       (bf16_t*)O, L, N, w, scale * kLog2e, nq, total, H, H / Hkv, reach.block);
+                       (bf16_t*)O, L, N, w, scale * kLog2e, nq, total, H, H / Hkv, reach_block);
     return hipGetLastError();
 }
 

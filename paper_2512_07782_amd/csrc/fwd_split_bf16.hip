@@ -183,11 +183,11 @@ static hipError_t launch_split(const void* Q, const void* K, const void* V, cons
         return e;
     const int nq = (N + 32 * QW - 1) / (32 * QW);
     ProfScope prof(kKernForward, s);
-    const KeyReach reach = scale > 0.f ? reach_of_forward(B * H, N, D, w, 32 * QW, true) : KeyReach{0, 32 * QW};
-    if (hipError_t e = key_reach(reach, true, K, V, c, O, B, H, Hkv, N, D, w, s)) return e;
+    int reach_block = 0;
+    if (hipError_t e = key_reach(reach_block, 32 * QW, true, Q, K, V, c, O, B, H, Hkv, N, D, w, scale, s)) return e;
     hipLaunchKernelGGL((fwd_split_bf16_kernel<D, NW, QW, KB, RING>), dim3((unsigned)(B * H) * nq), dim3((64 * NW)), sizeof(Smem),
                        s, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, c, (bf16_t*)O, L, N, w, scale * kLog2e, nq,
-                       B * H, H, H / Hkv, reach.block);
+                       B * H, H, H / Hkv, reach_block);
     return hipGetLastError();
 }
 

@@ -120,8 +120,8 @@ struct ScanQuad {
 template <int WAVES>
 __device__ __forceinline__ int run_start(int base, int wv, int r, int lane) { return base + (wv * (kScanRuns / WAVES) + r) * 256 + 4 * lane; }
 
-// With `partial` given (scan-then-propagate) a workgroup takes segment blockIdx.x % P of row blockIdx.x / P,
-// seg_len logical positions long, and starts from the sum of the row's earlier segments.
+// A workgroup takes segment blockIdx.x % P of row blockIdx.x / P, seg_len logical positions long, and starts from the sum of the
+// row's earlier segments: from `partial` (scan-then-propagate), or, where that is nullptr, from the row itself (scan_rows_alone).
 template <bool REVERSE, int MODE, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __restrict__ a,
                                                                  const float* __restrict__ b,
@@ -130,10 +130,9 @@ __global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __re
                                                                  int seg_len, int P) {
     constexpr int RUNS = kScanRuns / WAVES;
     __shared__ double wave_tot[2][WAVES];
-    const int seg = partial != nullptr ? (int)(blockIdx.x % P) : 0;
-    const size_t row = (size_t)(partial != nullptr ? blockIdx.x / P : blockIdx.x) * N;
-    const int begin = partial != nullptr ? seg * seg_len : 0;
-    const int end = partial != nullptr ? min(N, begin + seg_len) : N;
+    const int seg = (int)(blockIdx.x % P);
+    const size_t row = (size_t)(blockIdx.x / P) * N;
+    const int begin = seg * seg_len, end = min(N, begin + seg_len);
     const float* ar = a + row;
     const float* br = MODE != kScanPlain ? b + row : nullptr;
     float* outr = out + row;
@@ -151,6 +150,29 @@ __global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __re
         double acc = 0.0;
         for (int q = lane; q < seg; q += 64) acc += pr[q];
         carry = wave_sum(acc);
+    } else if (seg > 0) {  // of its elements, fp32 over four, fp64 across (as segment_sum_kernel)
+        double acc = 0.0;
+        constexpr int U = 4 / RUNS > 1 ? 4 / RUNS : 1;  // chunks in flight
+        for (int base = 0; base < begin; base += U * kScanChunk) {
+            ScanQuad<REVERSE, MODE> q[U][RUNS];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < RUNS; ++r) q[u][r].load(ar, br, N, run_start<WAVES>(base + u * kScanChunk, wv, r, lane), begin);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < RUNS; ++r) {
+                    float v[4];
+                    q[u][r].values(v, eps, run_start<WAVES>(base + u * kScanChunk, wv, r, lane), begin);
+                    acc += (double)((v[0] + v[1]) + (v[2] + v[3]));
+                }
+        }
+        acc = wave_sum(acc);
+        if (lane == 0) wave_tot[1][wv] = acc;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) carry += wave_tot[1][k];  // (the first chunk's totals go to the other place)
     }
     int buf = 0;
     for (int base = begin; base < end; base += kScanChunk, buf ^= 1) {
@@ -248,11 +270,34 @@ static bool scan_four_waves(bool activation, bool segment, long workgroups, int 
     if (workgroups <= device_cu_count() && (activation || !segment)) return false;
     return len <= 2 * kScanChunk;
 }
+// Few rows of three chunks or more go in segments of one chunk that each add up the row before them by themselves: one launch, no scratch,
+// the row read (P + 1) / 2 times out of the L2.  Up to a workgroup a CU, with the activation, which is formed again as often, three on four, and
+// 16 segments.  Scan-then-propagate, a launch more, pays against one workgroup a row from 7 chunks on (5 with the activation), against
+// this from 9 (5).  us, one workgroup a row / scan-then-propagate / this:
+//               1 row of 12000    16384            32768            65536             32 rows of 12000   16384            24576            32768
+//   plain       4.5 / 8.1 / 4.1   5.4 / 8.0 / 4.3  9.3 / 8.1 / 6.1  17.1 / 8.1 / 9.9   5.0 / 8.4 / 4.3   5.9 / 8.4 / 4.6   7.9 / 8.5 / 5.8  10.0 / 8.6 /  8.2
+//   activation  5.8 / 8.1 / 5.7   7.2 / 8.1 / 6.2 12.7 / 8.1 / 9.6  23.7 / 8.2 / 15.9  6.3 / 8.4 / 6.2   7.7 / 8.5 / 6.8  10.5 / 8.6 / 9.6  13.5 / 8.8 / 14.9
+// (96 rows of 16384, 384 segments: 6.5 / 8.9 / 6.8, 8.3 / 10.5 / 13.4.)
+static bool scan_rows_alone(bool activation, int rows, int N) {
+    const int P = (N + kScanChunk - 1) / kScanChunk;
+    return P >= 3 && P <= 16 && (activation ? 4 : 3) * (long)rows * P <= 3L * device_cu_count();
+}
+static bool scan_in_two_launches(bool activation, int rows, int N) {
+    const int P = (N + kScanChunk - 1) / kScanChunk;
+    return P > (activation ? 4 : scan_rows_alone(false, rows, N) ? 8 : 6);
+}
 template <bool REVERSE, int MODE>
 static void launch_scan(const float* a, const float* b, float* out, int rows, int N, float eps, const double* partial, int seg_len,
                         int P, hipStream_t s) {
+    if (partial == nullptr) {
+        // (out over an input: the segments behind still need what the ones in front overwrite)
+        const size_t bytes = (size_t)rows * N * sizeof(float);
+        const bool alone = scan_rows_alone(MODE == kScanGate, rows, N) && !overlap(out, bytes, a, bytes) && !(b != nullptr && overlap(out, bytes, b, bytes));
+        seg_len = alone ? kScanChunk : N;
+        P = alone ? (N + kScanChunk - 1) / kScanChunk : 1;
+    }
     const unsigned wgs = (unsigned)(rows * P);
-    if (scan_four_waves(MODE == kScanGate, partial != nullptr, wgs, partial != nullptr ? seg_len : N))
+    if (scan_four_waves(MODE == kScanGate, P > 1, wgs, seg_len))
         hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 4>), dim3(wgs), dim3(256), 0, s, a, b, out, N, eps, partial, seg_len, P);
     else
         hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 16>), dim3(wgs), dim3(1024), 0, s, a, b, out, N, eps, partial, seg_len, P);
@@ -296,6 +341,8 @@ size_t gate_scan_workspace_bytes(int rows, int N) {
 
 hipError_t gate_prefix_stp(const float* in, const float* beta, float eps, float* c, double* partial, int rows,
                            int N, hipStream_t s) {
+    if (!scan_in_two_launches(beta != nullptr, rows, N))
+        return beta != nullptr ? gate_activation_prefix(in, beta, eps, c, rows, N, s) : gate_prefix(in, c, rows, N, s);
     int seg_len = 0;
     const int P = scan_segments(rows, N, &seg_len);
     {
@@ -367,7 +414,7 @@ hipError_t gate_activation_backward(const float* hpre, const float* beta, float 
 // Few long rows leave most of the chip idle with one workgroup per row: then the rows are cut into segments
 // (scan-then-propagate, as gate_prefix_stp does for the forward prefix), which needs `partial`.
 bool gate_grad_scan_wants_segments(int rows, int N) {
-    return rows < device_cu_count() && N >= 2 * kScanChunk;
+    return rows < device_cu_count() && scan_in_two_launches(false, rows, N);
 }
 
 hipError_t gate_grad_scan(const float* dc_col, const float* dc_row, float* dalpha, double* partial, int rows, int N,

@@ -5,6 +5,11 @@
 
 namespace gfwa {
 
+// Whether two ranges of bytes share one: outputs that a caller puts over inputs do not serve as scratch before these are read.
+inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+    return (const char*)a < (const char*)b + b_bytes && (const char*)b < (const char*)a + a_bytes;
+}
+
 // c = inclusive prefix sum of alpha along N, one row per (b,h).
 hipError_t gate_prefix(const float* alpha, float* c, int rows, int N, hipStream_t s);
 hipError_t gate_activation_prefix(const float* hpre, const float* beta, float eps, float* c, int rows, int N,
@@ -27,13 +32,10 @@ hipError_t forward_bf16(const void* Q, const void* K, const void* V, const float
                         int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
 double query_tile_fill(int BH, int N, int w, long slots);  // how full rounds of `slots` 128-query tiles are, 0 .. 1
 // The same for few or uneven query tiles, the band of a tile split over groups of waves (fwd_split_bf16.hip).
-// Values of the key blocks in front of the forward's query tiles (band_reach.h), in O: block keys each, 0 for none, for tiles of `tile` queries.
-struct KeyReach {
-    int block, tile;
-};
-KeyReach reach_of_forward(int BH, int N, int d, int w, int tile, bool bf16);
-hipError_t key_reach(const KeyReach& r, bool bf16, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv,
-                     int N, int d, int w, hipStream_t s);
+// Values of the key blocks in front of the forward's query tiles (band_reach.h), in O.
+// key_reach: launches the pass for tiles of `tile` queries if it pays, and says by what blocks (0: it does not).
+hipError_t key_reach(int& block, int tile, bool bf16, const void* Q, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv,
+                     int N, int d, int w, float scale, hipStream_t s);
 enum FwdSplit { kFwdSplitNone = 0, kFwdSplitNarrow, kFwdSplitMid, kFwdSplitWide };  // 32, 64, 128 queries per workgroup
 hipError_t forward_split_bf16(FwdSplit shape, const void* Q, const void* K, const void* V, const float* c, void* O,
                               float* L, int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);

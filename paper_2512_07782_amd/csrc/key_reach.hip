@@ -79,26 +79,30 @@ __global__ __launch_bounds__(64) void key_reach_kernel(const T* __restrict__ K, 
 // 2 to 3 % of the shortest forwards that take it for a window that only gates of more than 0.1 a key erase in part, and up to 10 % for
 // windows that all but the slowest do, where a forward of 30 us is one of 15 with mu = -2.  (us: at the rate of long forwards, which short
 // ones do not reach.)  Below 600 keys hardly any gate does.
-KeyReach reach_of_forward(int BH, int N, int d, int w, int tile, bool bf16) {
+static int reach_block_of(int BH, int N, int d, int w, bool bf16) {
     const long band = w < N ? w : N;
     const double us = 4e-6 * BH * (double)N * band * d / (bf16 ? d == 128 ? 900.0 : 700.0 : 150.0) / (2 * band > N ? 2.0 : 1.0);
-    if (band < 600 || us < (band < 900 ? 100.0 : band < 1300 ? 50.0 : 20.0)) return {0, tile};
+    if (band < 600 || us < (band < 900 ? 100.0 : band < 1300 ? 50.0 : 20.0)) return 0;
     long block = 64;
     while ((band + block) / block + 1 > 64) block *= 2;  // (an entry for each lane of a wave)
-    return {(int)block, tile};
+    return (int)block;
 }
 
 template <int D, typename T>
-static void launch(const KeyReach& r, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv, int N, int w, hipStream_t s) {
-    const int blocks = (N + r.block - 1) / r.block;
+static void launch(int block, int tile, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv, int N, int w, hipStream_t s) {
+    const int blocks = (N + block - 1) / block;
     hipLaunchKernelGGL((key_reach_kernel<D, T>), dim3((unsigned)(B * Hkv) * blocks), dim3(64), 0, s, (const T*)K, (const T*)V, c, (T*)O, N, w, blocks,
-                       r.block, r.tile, H, H / Hkv);
+                       block, tile, H, H / Hkv);
 }
-hipError_t key_reach(const KeyReach& r, bool bf16, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv, int N, int d,
-                     int w, hipStream_t s) {
-    if (r.block == 0) return hipSuccess;
-    if (bf16) d == 128 ? launch<128, bf16_t>(r, K, V, c, O, B, H, Hkv, N, w, s) : launch<64, bf16_t>(r, K, V, c, O, B, H, Hkv, N, w, s);
-    else d == 128 ? launch<128, float>(r, K, V, c, O, B, H, Hkv, N, w, s) : launch<64, float>(r, K, V, c, O, B, H, Hkv, N, w, s);
+hipError_t key_reach(int& block, int tile, bool bf16, const void* Q, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv,
+                     int N, int d, int w, float scale, hipStream_t s) {
+    const size_t row = (size_t)d * (bf16 ? 2 : 4), out = (size_t)B * H * N * row, keys = (size_t)B * Hkv * N * row;
+    block = scale > 0.f ? reach_block_of(B * H, N, d, w, bf16) : 0;
+    if (overlap(O, out, Q, out) || overlap(O, out, K, keys) || overlap(O, out, V, keys) || overlap(O, out, c, (size_t)B * H * N * sizeof(float)))
+        block = 0;
+    if (block == 0) return hipSuccess;
+    if (bf16) d == 128 ? launch<128, bf16_t>(block, tile, K, V, c, O, B, H, Hkv, N, w, s) : launch<64, bf16_t>(block, tile, K, V, c, O, B, H, Hkv, N, w, s);
+    else d == 128 ? launch<128, float>(block, tile, K, V, c, O, B, H, Hkv, N, w, s) : launch<64, float>(block, tile, K, V, c, O, B, H, Hkv, N, w, s);
     return hipGetLastError();
 }
 

@@ -102,3 +102,23 @@ def test_far_rows_that_are_not_finite(g, oracle, B, H, Hkv, N, d, w, dtype, mu, 
         assert bad("O", later) and bad("dQ", later)
     else:
         assert bad("dK", earlier) and (which == "Q" or bad("dV", earlier))
+
+
+@pytest.mark.parametrize("B,H,N,d,w,dtype", [(2, 24, 2048, 128, 1400, "bf16"), (1, 4, 6146, 64, 4001, "bf16"), (1, 8, 2177, 128, 1600, "f32")])
+def test_outputs_over_inputs(g, oracle, B, H, N, d, w, dtype):
+    # outputs serve as scratch in front of the kernels, unless they lie over an input that is still read
+    note("outputs over inputs", B, H, N, d, w, dtype)
+    wl, ins = inputs(B, H, H, N, d, w, dtype, -1.0)
+    c = g.gfwa_gate_prefix(dev(ins["alpha"], "f32"))
+    want = step(g, wl, ins, c, False)
+    t = {k: dev(ins[k], dtype) for k in ("Q", "K", "V", "dO")}
+    over = t["Q"].clone()
+    O, L = g.gfwa_forward(over, t["K"], t["V"], c, w, wl.scale, O=over)
+    assert torch.equal(O, want["O"]) and torch.equal(L, want["L"])
+    for name in ("c", "L"):
+        x = {"c": c.clone(), "L": L.clone()}
+        grads = g.gfwa_backward(t["Q"], t["K"], t["V"], O, t["dO"], x["c"], x["L"], w, wl.scale, dalpha=x[name])
+        for k, got in zip(("dQ", "dK", "dV", "dalpha"), grads):
+            # the column sums of the last block of a band may be contracted differently, half an ulp each (2^-24 of 16 here), and
+            # dalpha adds up thousands of them: a random walk of 1e-4 at most, of values up to 15
+            assert rel_inf(host(got), host(want[k])) <= (2e-5 if k == "dalpha" else 1e-6), (name, k)
