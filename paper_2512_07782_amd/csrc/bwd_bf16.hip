@@ -1141,9 +1141,9 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     char* ds_ws = reinterpret_cast<char*>(ws + 3 * pad) + scan_pad;  // only with `spill`
     BwdBf16 args = {(const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, c, L, Dv,
                     (bf16_t*)dQ, (bf16_t*)dK, (bf16_t*)dV, dc_col, dc_row, nullptr, B, H, Hkv, N, w, scale};
-    auto rowdot = [&](auto keys, float* reach) {
+    auto rowdot = [&](auto keys, float* reach, KernelId as) {
         const int blocks = (N + kReachRows - 1) / kReachRows;
-        ProfScope prof(kKernRowDot, s);
+        ProfScope prof(as, s);
         hipLaunchKernelGGL((rowdot_bf16_kernel<D, decltype(keys)::value>), dim3((unsigned)(B * H) * blocks), dim3(256), 0, s, args.O, args.dO, args.Q,
                            args.K, args.V, c, L, Dv, reach, N, w, blocks, H, H / Hkv);
     };
@@ -1161,7 +1161,7 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     if (some_split && !bwd_split_looks(N, w)) reach = nullptr;
     const float* seen = dkv_split ? nullptr : reach;
     if (some_split && reach != nullptr) {
-        rowdot(std::true_type{}, reach);
+        rowdot(std::true_type{}, reach, dq_split && !one_launch ? kKernDq : kKernDkv);  // (recorded with the pass that it is for)
         args.reach = reach;
     }
     if (one_launch) {
@@ -1171,7 +1171,7 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     if (dq_split) {
         if (hipError_t e = bwd_dq_split_bf16(dq_split, args, D, s)) return e;
     } else if (!some_split || reach == nullptr) {
-        rowdot(std::false_type{}, reach);
+        rowdot(std::false_type{}, reach, kKernRowDot);
     }
     if (dkv_split) {
         if (hipError_t e = bwd_dkv_split_bf16(args, D, s)) return e;
