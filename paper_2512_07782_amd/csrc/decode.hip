@@ -39,12 +39,21 @@ __host__ __device__ constexpr int dec_record(int D) { return D + 2; }
 
 // Eight consecutive cache elements as they arrive from memory, converted to fp32 only when used (so
 // that the loads of the next step can be in flight, in few registers, while the current one is computed).
+// ONCE: no other workgroup reads them, so bf16 loads are non-temporal.  A cache that holds nothing of the window yet is then read faster (us,
+// three states in turn: B64 H32/8 N16384 d128 w1024 63 -> 57, H32/32 213 -> 174, B16 H32/8 w4096 57 -> 52, B4 H32/8 w1024 12.4 -> 12.4), one that
+// the memory-side cache still holds in full more slowly (the first 52 -> 56): a program reads its other layers in between.  fp32 gains nothing
+// (B16 H32/32 w1024 99 -> 101) and loads as before.
 template <typename T>
 struct Raw8;
 template <>
 struct Raw8<bf16_t> {
     bf16x8 v;
-    __device__ __forceinline__ void load(const bf16_t* p) { v = *reinterpret_cast<const bf16x8*>(p); }
+    template <bool ONCE>
+    __device__ __forceinline__ void load(const bf16_t* p) {
+        const bf16x8* from = reinterpret_cast<const bf16x8*>(p);
+        if constexpr (ONCE) v = __builtin_nontemporal_load(from);
+        else v = *from;
+    }
     __device__ __forceinline__ void get(float (&x)[8]) const {
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[e] = (float)v[e];
@@ -53,6 +62,7 @@ struct Raw8<bf16_t> {
 template <>
 struct Raw8<float> {
     float4 a, b;
+    template <bool ONCE>
     __device__ __forceinline__ void load(const float* p) {
         a = reinterpret_cast<const float4*>(p)[0];
         b = reinterpret_cast<const float4*>(p)[1];
@@ -115,7 +125,7 @@ __device__ __forceinline__ float row_pair_sums(float x0, float x1) {  // x0 in e
 //   * the gate prefix of a row is loaded once per head (lane j loads head j % GT) and passed round the
 //     group of GT lanes by DPP;
 //   * the loads of the next step are issued before the current step is computed.
-template <typename T, int D, int GT, int NW>
+template <typename T, int D, int GT, int NW, bool ONCE>
 __global__ __launch_bounds__(64 * NW) void decode_partial_kernel(
     const T* __restrict__ q, const T* __restrict__ Kc, const T* __restrict__ Vc, float* __restrict__ c,
     const float* __restrict__ alpha_t, const int* __restrict__ pos, float* __restrict__ part,
@@ -210,8 +220,8 @@ __global__ __launch_bounds__(64 * NW) void decode_partial_kernel(
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
                 const int kk = min(kw0 + st * STEP_ROWS + u * RPI + r, kw_end);  // past the range: its last row, masked
-                kr[buf][u].load(Kh + (size_t)kk * D);
-                vr[buf][u].load(Vh + (size_t)kk * D);
+                kr[buf][u].template load<ONCE>(Kh + (size_t)kk * D);
+                vr[buf][u].template load<ONCE>(Vh + (size_t)kk * D);
                 cvr[buf][u] = (alpha_t != nullptr && kk == p) ? ct_own : c_own[kk];
             }
         };
@@ -219,7 +229,7 @@ __global__ __launch_bounds__(64 * NW) void decode_partial_kernel(
 
         {  // reference exponents: the scores of the wave's newest key
             Raw8<T> k1;
-            k1.load(Kh + (size_t)kw_end * D);
+            k1.template load<ONCE>(Kh + (size_t)kw_end * D);
             scores(k1, (alpha_t != nullptr && kw_end == p) ? ct_own : c_own[kw_end], mref);
 #pragma unroll
             for (int g = 0; g < GT; ++g) mref[g] = fmaxf(mref[g], kDecNegBig);  // that key may be masked: a score of minus infinity
@@ -411,9 +421,13 @@ static hipError_t launch_decode(const T* q, const T* Kc, const T* Vc, float* c, 
     {
         ProfScope prof(kKernDecode, s);
         auto launch = [&](auto gt, auto nw) {
-            hipLaunchKernelGGL((decode_partial_kernel<T, D, decltype(gt)::value, decltype(nw)::value>), dim3((unsigned)(items * S)),
-                               dim3(64 * decltype(nw)::value), 0, s, q, Kc, Vc, c, alpha_t, pos, part, o, L, H, G, Tlen, w, scale,
-                               S, chunk);
+            auto as = [&](auto once) {
+                hipLaunchKernelGGL((decode_partial_kernel<T, D, decltype(gt)::value, decltype(nw)::value, decltype(once)::value>),
+                                   dim3((unsigned)(items * S)), dim3(64 * decltype(nw)::value), 0, s, q, Kc, Vc, c, alpha_t, pos, part,
+                                   o, L, H, G, Tlen, w, scale, S, chunk);
+            };
+            if (kShort && G == GT) as(std::integral_constant<bool, kShort>{});
+            else as(std::integral_constant<bool, false>{});
         };
         auto with_heads = [&](auto nw) {
             if (GT == 4) launch(std::integral_constant<int, 4>{}, nw);
