@@ -4,12 +4,11 @@
 // A key whose score then lies below the reference of a row by more than the binary orders that an fp32 sum resolves has no part in it:
 //   kErased = 127  exp2 returns zero for every argument below -126 (the smallest normal number; measured over -120 .. -151), so the
 //                  probability is exactly zero and every product it enters is zero, whatever the values are
-//   kFaint = 64    the weights left out add up to less than 2^-52 of the row's (4096 keys); the values they would have multiplied are at most 2^16
-//                  times as large as those of rows close by (kOutweighs), so a sum misses less than 2^-36 of the values it is made of,
-//                  2^-12 of a rounding of fp32.  Where a block's rows outweigh that, the line is kErased.
-// Against the same kernels with whole bands O, L and gradients are the same bit for bit over 500 drawn steps, 13 of them with a changed order
-// of additions apart (split dK/dV kernel, grouped heads).  (softplus(N(-2, 1)) decays by 190 over 1024 keys, unit-variance rows of d = 128 have
-// |q| |k| / sqrt(d) of 11 to 15: the far 700 keys are left out.)
+//   kFaint = 48    and one more for every doubling by which the values that the weight would multiply outweigh those of rows close by
+//                  (outweighs): the weights left out add up to less than 2^-36 of the row's (4096 keys) in these terms, so a sum misses
+//                  less than 2^-36 of the values it is made of, 2^-12 of a rounding of fp32.
+// (softplus(N(-2, 1)) decays by 190 over 1024 keys, unit-variance rows of d = 128 have |q| |k| / sqrt(d) of 11 to 15: the far 750 keys are
+// left out.)
 //
 // So a pass over the rows in front of the kernels takes the largest norm of every block of them, and a workgroup shortens its band, in front
 // of its first step, by the blocks at the far end that are erased for all rows of its tile.  The pass costs one reading of a
@@ -39,14 +38,15 @@
 
 namespace gfwa {
 
-// Base-2 exponents below which a weight counts for nothing, with 1 for the roundings of scores and references, and the ratio of squared norms up
-// to which a block's rows count as no heavier than others.
-constexpr float kErased = 127.f, kFaint = 65.f, kOutweighs = 4294967296.f;
+// Base-2 exponents below which a weight counts for nothing, with 1 for the roundings of scores and references.
+constexpr float kErased = 127.f, kFaint = 49.f;
+// Doublings by which rows of squared norm `far` outweigh rows of `near` (at least 0; NaN or infinite: no line but kErased holds).
+__device__ __forceinline__ float outweighs(float far, float near) { return far <= near ? 0.f : 0.5f * (fast_log2(far) - fast_log2(near)); }
 // Whether it can pay to read norms: `decay` over the `len` rows that see a block (that it sees).  Scores of unit-variance rows add about
-// 15 to the 45 of kFaint (in units of the gate); `few` rows fewer have to be worth the reading, one matrix of three in front of the backward,
+// 15 to the 34 of kFaint (in units of the gate); `few` rows fewer have to be worth the reading, one matrix of three in front of the backward,
 // two in front of the forward, which are half of what it has to move at all.  (Two products compared, so that two kernels which ask the same
 // always agree: there is nothing the compiler could fuse in one of them.)
-constexpr float kTypicalReach = 61.f;
+constexpr float kTypicalReach = 49.f;
 constexpr int kFewForward = 384, kFewBackward = 128;
 __device__ __forceinline__ bool reach_pays(float decay, int len, int few) {
     return decay > kTypicalReach && decay * (float)(len - few) > kTypicalReach * (float)len;
@@ -106,9 +106,10 @@ __device__ __forceinline__ int norm_bits(float n2) { return __float_as_int(n2) &
 // What a wave (or workgroup) knows of its own rows: the largest squared norm, times (scale log2 e)^2 and a thousandth for the
 // roundings of norms and products.
 __device__ __forceinline__ float reach2_of(int norm, float sl) { return __int_as_float(norm) * (sl * sl * 1.004f); }
-// room: what a score would have to exceed, in base-2 exponents, for a weight of 2^-kErased; light: kFaint will do
-__device__ __forceinline__ bool is_erased(float n2, float reach2, float room, bool light) {
-    if (light) room += kErased - kFaint;
+// room: what a score would have to exceed, in base-2 exponents, for a weight of 2^-kErased; heavier: doublings by which the values of the
+// block outweigh others (fminf: kErased for NaN)
+__device__ __forceinline__ bool is_erased(float n2, float reach2, float room, float heavier) {
+    room += kErased - fminf(kFaint + heavier, kErased);
     return room > 0.f && n2 * reach2 < room * room;
 }
 
@@ -141,8 +142,7 @@ __device__ __forceinline__ KeyBlock key_block(const T* first, int rows, int lane
 __device__ __forceinline__ int first_needed_key(const KeyBlock& kb, int q0, int k_lo, int block, float reach2, float lowest, float cbase, int lane) {
     const int hi = q0 / block - 1, n = hi - k_lo / block + 1;  // (n <= 64, reach_of_forward sees to that)
     const float near_v2 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(kb.v2())));
-    const bool light = kb.v2() <= kOutweighs * near_v2;
-    const bool kept = lane < n && !is_erased(kb.k2(), reach2, lowest - (kb.c - cbase) * kLog2e, light);
+    const bool kept = lane < n && !is_erased(kb.k2(), reach2, lowest - (kb.c - cbase) * kLog2e, outweighs(kb.v2(), near_v2));
     const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
     const int farthest = mask ? 63 - __builtin_clzll(mask) : -1;
     return max(k_lo, (hi - farthest) * block);
@@ -259,9 +259,10 @@ __device__ __forceinline__ int last_needing_block(const float* at, const float* 
         bool kept = i > i_min;
         if (kept) {
             const float* r = at + reach_row(i, N);
-            const bool light = r[kReachNorm] <= kOutweighs * own.q2 && r[kReachG] <= kOutweighs * own.g2 && r[kReachD] <= kOutweighs * own.d2 &&
-                               own.k2 <= kOutweighs * r[kReachOneK] && own.v2 <= kOutweighs * r[kReachOneV];
-            kept = !is_erased(r[kReachNorm], own.reach2, ((ch[64 * i] - cbase) + r[kReachEdge]) * kLog2e - own.edge - kErased, light);
+            // dO in dV, dS of dO and D times Q in dK; and in these queries' dQ dS of V times K
+            const float here = fmaxf(outweighs(r[kReachG], own.g2), outweighs(r[kReachD], own.d2)) + outweighs(r[kReachNorm], own.q2);
+            const float there = outweighs(own.v2, r[kReachOneV]) + outweighs(own.k2, r[kReachOneK]);
+            kept = !is_erased(r[kReachNorm], own.reach2, ((ch[64 * i] - cbase) + r[kReachEdge]) * kLog2e - own.edge - kErased, fmaxf(here, there));
         }
         const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
         if (mask) return top - __builtin_ctzll(mask);
@@ -275,8 +276,8 @@ __device__ __forceinline__ int first_needed_block(const float* at, int i_lo, int
         bool kept = i < i_max;
         if (kept) {
             const float* r = at + reach_row(i, N);
-            const bool light = r[kReachKeyNorm] <= kOutweighs * own.k2 && r[kReachValue] <= kOutweighs * own.v2;
-            kept = !is_erased(r[kReachKeyNorm], own.reach2, own.edge - kErased - (r[kReachKeyHigh] - cbase) * kLog2e, light);
+            const float heavier = outweighs(r[kReachKeyNorm], own.k2) + outweighs(r[kReachValue], own.v2);
+            kept = !is_erased(r[kReachKeyNorm], own.reach2, own.edge - kErased - (r[kReachKeyHigh] - cbase) * kLog2e, heavier);
         }
         const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
         if (mask) return base + __builtin_ctzll(mask);
