@@ -43,11 +43,11 @@ constexpr float kErased = 127.f, kFaint = 49.f;
 // Doublings by which rows of squared norm `far` outweigh rows of `near` (at least 0; NaN or infinite: no line but kErased holds).
 __device__ __forceinline__ float outweighs(float far, float near) { return far <= near ? 0.f : 0.5f * (fast_log2(far) - fast_log2(near)); }
 // Whether it can pay to read norms: `decay` over the `len` rows that see a block (that it sees).  Scores of unit-variance rows add about
-// 15 to the 34 of kFaint (in units of the gate); `few` rows fewer have to be worth the reading, one matrix of three in front of the backward,
-// two in front of the forward, which are half of what it has to move at all.  (Two products compared, so that two kernels which ask the same
+// 15 to the 34 of kFaint (in units of the gate); `few` rows fewer have to be worth the reading: of one matrix of three in front of the backward,
+// of two in a launch of their own in front of the forward (key_reach.hip).  (Two products compared, so that two kernels which ask the same
 // always agree: there is nothing the compiler could fuse in one of them.)
 constexpr float kTypicalReach = 49.f;
-constexpr int kFewForward = 384, kFewBackward = 128;
+constexpr int kFewBackward = 128;
 __device__ __forceinline__ bool reach_pays(float decay, int len, int few) {
     return decay > kTypicalReach && decay * (float)(len - few) > kTypicalReach * (float)len;
 }

@@ -516,7 +516,7 @@ template <int D, int NW, int S>
 __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) void fwd_f32_mfma_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ c, float* __restrict__ O, float* __restrict__ L, int N, int w, float scale,
-    int num_qtiles, int total_tiles, int H, int G, int reach_block) {
+    int num_qtiles, int total_tiles, int H, int G, KeyReach reach) {
     constexpr int KC = D / 16, DB = D / 32, BQ = 32 * NW;
     extern __shared__ __align__(256) char smem_raw[];
     auto& sm = *reinterpret_cast<F32FwdSmem<D, S>*>(smem_raw);
@@ -531,7 +531,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) voi
 
     const int k_lo = max(0, q0 - w + 1), jb_hi = (min(N, q0 + BQ) - 1) / 32;
     int first_key = k_lo;
-    if (reach_block != 0 && reach_pays(ch[q0] - ch[k_lo], q0 - k_lo, kFewForward)) {  // the keys that the gate has erased for all queries stay out
+    if (reach.block != 0 && reach_pays(ch[q0] - ch[k_lo], q0 - k_lo, reach.few)) {  // the keys that the gate has erased for all queries stay out
         float q2 = 0.f, k2 = 0.f, own = 0.f;
         const float *qr = Q + ho + (size_t)tc * D + 4 * h, *kr = Kh + (size_t)tc * D + 4 * h;  // (the halves take every other four columns)
 #pragma unroll 4
@@ -544,7 +544,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) voi
         // the row's maximum is at least the score of the query's own key
         const float edge = (ch[tc] - ch[q0]) * kLog2e + scale * kLog2e * (xhalf_sum(own) - 1e-4f * sqrtf(q2 * xhalf_sum(k2)));
         const float reach2 = reach2_of(lanes_max<32>(norm_bits(q2)), scale * kLog2e), lowest = from_order(lanes_min<32>(lowest_order(edge))) - kErased;
-        first_key = over_waves<NW, true>(first_needed_key(key_block<D>(O + ho + (size_t)q0 * D, min(BQ, N - q0), lane), q0, k_lo, reach_block, reach2,
+        first_key = over_waves<NW, true>(first_needed_key(key_block<D>(O + ho + (size_t)q0 * D, min(BQ, N - q0), lane), q0, k_lo, reach.block, reach2,
                                                           lowest, ch[q0], lane),
                                          sm.needed, wv, lane);
     }
@@ -1236,10 +1236,10 @@ static hipError_t launch_fwd_f32_mfma(const float* Q, const float* K, const floa
     constexpr size_t lds = sizeof(F32FwdSmem<D, S>);
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&fwd_f32_mfma_kernel<D, NW, S>), lds, lds_allowed)) return e;
     const int nq = (N + 32 * NW - 1) / (32 * NW), total = B * H * nq;
-    int reach_block = 0;
-    if (hipError_t e = key_reach(reach_block, 32 * NW, false, Q, K, V, c, O, B, H, Hkv, N, D, w, scale, s)) return e;
+    KeyReach reach;
+    if (hipError_t e = key_reach(reach, 32 * NW, false, Q, K, V, c, O, B, H, Hkv, N, D, w, scale, s)) return e;
     hipLaunchKernelGGL((fwd_f32_mfma_kernel<D, NW, S>), dim3(total), dim3(64 * NW), lds, s, Q, K, V, c, O, L, N, w, scale, nq, total,
-                       H, H / Hkv, reach_block);
+                       H, H / Hkv, reach);
     return hipGetLastError();
 }
 

@@ -93,7 +93,7 @@ template <int D, int NB>
 __device__ __forceinline__ void fwd_tile(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w, float scale_log2,
-    int num_qtiles, int total, int H, int G, int reach_block) {
+    int num_qtiles, int total, int H, int G, KeyReach reach) {
     constexpr int KC = D / 16, DB = D / 32, NV = 2 * DB;
     using Smem = FwdSmem<D, NB>;
     constexpr int kKeys = Smem::kKeys, kRowBytes = D * 2, kTileBytes = Smem::kTileBytes;
@@ -153,9 +153,9 @@ __device__ __forceinline__ void fwd_tile(
 #pragma unroll
         for (int kc = 0; kc < KC; ++kc) qf[kc] = *reinterpret_cast<const bf16x8*>(qp + 16 * kc);
     }
-    if (reach_block != 0 && reach_pays(cbase - ch[k_lo], q0 - k_lo, kFewForward)) {  // the keys that the gate has erased for all 128 queries stay out
+    if (reach.block != 0 && reach_pays(cbase - ch[k_lo], q0 - k_lo, reach.few)) {  // the keys that the gate has erased for all 128 queries stay out
         const int first = forward_reach<D, kFwdWaves>(qf, K + kv_off + (size_t)min(t, N - 1) * D + 8 * h,
-                                                      key_block<D>(O + head_off + (size_t)q0 * D, min(128, N - q0), lane), cq, q0, k_lo, reach_block,
+                                                      key_block<D>(O + head_off + (size_t)q0 * D, min(128, N - q0), lane), cq, q0, k_lo, reach.block,
                                                       cbase, sl, sm.needed, wv, lane);
         ntiles = j_hi - first / kKeys + 1;
         T_first = min(T_first, ntiles);
@@ -316,16 +316,16 @@ template <int D>
 __global__ __launch_bounds__(64 * kFwdWaves, D == 64 ? 4 : 3) void fwd_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w, float scale_log2,
-    int num_qtiles, int total, int H, int G, int reach_block) {
-    fwd_tile<D, kFwdBlocks<D>>(Q, K, V, c, O, L, N, w, scale_log2, num_qtiles, total, H, G, reach_block);
+    int num_qtiles, int total, int H, int G, KeyReach reach) {
+    fwd_tile<D, kFwdBlocks<D>>(Q, K, V, c, O, L, N, w, scale_log2, num_qtiles, total, H, G, reach);
 }
 // d = 128 with the step of d = 64, for launches that put few workgroups on a CU (fwd_two_blocks has the line and figures): with two
 // waves on a SIMD the exponentials of a block have to run beside the products of the same wave's other block.
 __global__ __launch_bounds__(64 * kFwdWaves, 2) void fwd_two_blocks_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w, float scale_log2,
-    int num_qtiles, int total, int H, int G, int reach_block) {
-    fwd_tile<128, 2>(Q, K, V, c, O, L, N, w, scale_log2, num_qtiles, total, H, G, reach_block);
+    int num_qtiles, int total, int H, int G, KeyReach reach) {
+    fwd_tile<128, 2>(Q, K, V, c, O, L, N, w, scale_log2, num_qtiles, total, H, G, reach);
 }
 
 // What all 128-query tiles of a problem cost and what the longest does, counted in 64-key tiles plus two for each query tile's start
@@ -389,10 +389,10 @@ static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const 
         }
     }
     ProfScope prof(kKernForward, s);
-    int reach_block = 0;
-    if (hipError_t e = key_reach(reach_block, 128, true, Q, K, V, c, O, B, H, Hkv, N, D, w, scale, s)) return e;
+    KeyReach reach;
+    if (hipError_t e = key_reach(reach, 128, true, Q, K, V, c, O, B, H, Hkv, N, D, w, scale, s)) return e;
     hipLaunchKernelGGL(kernel, dim3(total), dim3(64 * kFwdWaves), lds, s, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, c,
-                       (bf16_t*)O, L, N, w, scale * kLog2e, nq, total, H, H / Hkv, reach_block);
+                       (bf16_t*)O, L, N, w, scale * kLog2e, nq, total, H, H / Hkv, reach);
     return hipGetLastError();
 }
 

@@ -31,7 +31,7 @@ template <int D, int NW, int QW, int KB, int RING>
 __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_split_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w, float scale_log2,
-    int num_qtiles, int BH, int H, int G, int reach_block) {
+    int num_qtiles, int BH, int H, int G, KeyReach reach) {
     using Band = SplitBand<D, NW, QW, KB, RING>;
     constexpr int KC = D / 16, DB = D / 32, KW = Band::KW;
     extern __shared__ __align__(256) char smem_raw[];
@@ -56,9 +56,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_split
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) GFWA_PIN(qf[kc]);
     const int k_lo = max(0, q0 - w + 1);
-    if (reach_block != 0 && reach_pays(band.cbase - band.ch[k_lo], q0 - k_lo, kFewForward))  // what the gate has erased for all queries stays out
+    if (reach.block != 0 && reach_pays(band.cbase - band.ch[k_lo], q0 - k_lo, reach.few))  // what the gate has erased for all queries stays out
         band.from(forward_reach<D, NW>(qf, K + kv_off + (size_t)tc * D + 8 * h, key_block<D>(O + head_off + (size_t)q0 * D, min(32 * QW, N - q0), lane), cq,
-                                       q0, k_lo, reach_block, band.cbase, sl, sm.needed, band.wv, lane),
+                                       q0, k_lo, reach.block, band.cbase, sl, sm.needed, band.wv, lane),
                   q0, w);
 
     f32x16 o[DB];
@@ -183,11 +183,11 @@ static hipError_t launch_split(const void* Q, const void* K, const void* V, cons
         return e;
     const int nq = (N + 32 * QW - 1) / (32 * QW);
     ProfScope prof(kKernForward, s);
-    int reach_block = 0;
-    if (hipError_t e = key_reach(reach_block, 32 * QW, true, Q, K, V, c, O, B, H, Hkv, N, D, w, scale, s)) return e;
+    KeyReach reach;
+    if (hipError_t e = key_reach(reach, 32 * QW, true, Q, K, V, c, O, B, H, Hkv, N, D, w, scale, s)) return e;
     hipLaunchKernelGGL((fwd_split_bf16_kernel<D, NW, QW, KB, RING>), dim3((unsigned)(B * H) * nq), dim3((64 * NW)), sizeof(Smem),
                        s, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, c, (bf16_t*)O, L, N, w, scale * kLog2e, nq,
-                       B * H, H, H / Hkv, reach_block);
+                       B * H, H, H / Hkv, reach);
     return hipGetLastError();
 }
 

@@ -33,8 +33,12 @@ hipError_t forward_bf16(const void* Q, const void* K, const void* V, const float
 double query_tile_fill(int BH, int N, int w, long slots);  // how full rounds of `slots` 128-query tiles are, 0 .. 1
 // The same for few or uneven query tiles, the band of a tile split over groups of waves (fwd_split_bf16.hip).
 // Values of the key blocks in front of the forward's query tiles (band_reach.h), in O.
-// key_reach: launches the pass for tiles of `tile` queries if it pays, and says by what blocks (0: it does not).
-hipError_t key_reach(int& block, int tile, bool bf16, const void* Q, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv,
+// key_reach: launches the pass for tiles of `tile` queries if it pays, and says by what blocks (0: it does not) and how many keys have to be
+// erased for reading their norms to pay.
+struct KeyReach {
+    int block, few;
+};
+hipError_t key_reach(KeyReach& reach, int tile, bool bf16, const void* Q, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv,
                      int N, int d, int w, float scale, hipStream_t s);
 enum FwdSplit { kFwdSplitNone = 0, kFwdSplitNarrow, kFwdSplitMid, kFwdSplitWide };  // 32, 64, 128 queries per workgroup
 hipError_t forward_split_bf16(FwdSplit shape, const void* Q, const void* K, const void* V, const float* c, void* O,

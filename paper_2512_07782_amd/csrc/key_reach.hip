@@ -25,7 +25,7 @@ __device__ __forceinline__ float square8(const float* p, float x) {
 // are resident at once, and where nothing is read the launch is over after two dependent loads; 4096 workgroups of four waves 9 us.)
 template <int D, typename T>
 __global__ __launch_bounds__(64) void key_reach_kernel(const T* __restrict__ K, const T* __restrict__ V, const float* __restrict__ c,
-                                                       T* __restrict__ O, int N, int w, int blocks, int block, int tile, int H, int G) {
+                                                       T* __restrict__ O, int N, int w, int blocks, int block, int few, int tile, int H, int G) {
     constexpr int kLanes = D / 8, kRows = 64 / kLanes, U = 16 / sizeof(T);  // lanes of a row, rows at a time, times in flight
     const int lane = threadIdx.x;
     const int bkv = (int)blockIdx.x / blocks, kb = (int)blockIdx.x % blocks, k0 = kb * block, k1 = min(N, k0 + block);
@@ -38,11 +38,10 @@ __global__ __launch_bounds__(64) void key_reach_kernel(const T* __restrict__ K, 
     auto asks = [&](int g, int t) __attribute__((always_inline)) {
         const float* ch = c + (size_t)(bh0 + g) * N;
         const int q0 = (t_lo + t) * tile, k_lo = max(0, q0 - w + 1);
-        return reach_pays(ch[q0] - ch[k_lo], q0 - k_lo, kFewForward);
+        return reach_pays(ch[q0] - ch[k_lo], q0 - k_lo, few);
     };
     bool any = false;
-    for (int g = 0; g < G; ++g)
-        for (int t = lane; t < nt; t += 64) any |= asks(g, t);
+    for (int i = lane; i < G * nt; i += 64) any |= asks(i / nt, i % nt);
     if (__builtin_amdgcn_ballot_w64(any) == 0) return;
     int norm = 0, value = 0;
     const size_t at = (size_t)bkv * N * D + 8 * (lane % kLanes);
@@ -62,47 +61,64 @@ __global__ __launch_bounds__(64) void key_reach_kernel(const T* __restrict__ K, 
         }
     }
     const unsigned norms = pack_norms(lanes_max(norm), lanes_max(value));
-    for (int g = 0; g < G; ++g) {
-        const float* ch = c + (size_t)(bh0 + g) * N;
-        int high = (int)0x80000000;
-        for (int i = k0 + lane; i < k1; i += 64) high = max(high, highest_order(ch[i]));
-        high = lanes_max(high);
-        for (int t = lane; t < nt; t += 64) {
-            const int q0 = (t_lo + t) * tile, e = q0 / block - 1 - kb;
-            if (asks(g, t) && e < key_blocks_in<D, T>(min(tile, N - q0)))
-                reinterpret_cast<KeyBlock*>(O + ((size_t)(bh0 + g) * N + q0) * D)[e] = {norms, from_order(high)};
+    for (int g0 = 0; g0 < G; g0 += 4) {  // four heads' gates at once, and their tiles over the lanes
+        int high[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) high[j] = (int)0x80000000;
+        for (int i = k0 + lane; i < k1; i += 64)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) high[j] = max(high[j], highest_order(c[(size_t)(bh0 + min(g0 + j, G - 1)) * N + i]));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) high[j] = lanes_max(high[j]);
+        for (int i = lane; i < min(4, G - g0) * nt; i += 64) {
+            const int j = i / nt, t = i % nt, q0 = (t_lo + t) * tile, e = q0 / block - 1 - kb;
+            const int top = j < 2 ? (j == 0 ? high[0] : high[1]) : (j == 2 ? high[2] : high[3]);
+            if (asks(g0 + j, t) && e < key_blocks_in<D, T>(min(tile, N - q0)))
+                reinterpret_cast<KeyBlock*>(O + ((size_t)(bh0 + g0 + j) * N + q0) * D)[e] = {norms, from_order(top)};
         }
     }
 }
 
-// Whether a forward looks at the reach of its keys, and by what blocks.  Where the gate then decays too little the launch is in vain, 2 to 3 us:
-// 2 to 3 % of the shortest forwards that take it for a window that only gates of more than 0.1 a key erase in part, and up to 10 % for
-// windows that all but the slowest do, where a forward of 30 us is one of 15 with mu = -2.  (us: at the rate of long forwards, which short
-// ones do not reach.)  Below 600 keys hardly any gate does.
-static int reach_block_of(int BH, int N, int d, int w, bool bf16) {
-    const long band = w < N ? w : N;
-    const double us = 4e-6 * BH * (double)N * band * d / (bf16 ? d == 128 ? 900.0 : 700.0 : 150.0) / (2 * band > N ? 2.0 : 1.0);
-    if (band < 600 || us < (band < 900 ? 100.0 : band < 1300 ? 50.0 : 20.0)) return 0;
+// Whether a forward looks at the reach of its keys, by what blocks, and what they have to save.
+// few: the keys a tile's band has to lose to be as fast as without: 100 that tiles and blocks do not divide (steps of 32 or 64 keys, 64-key blocks,
+// the tile's own queries), and those that the forward streams while the pass reads K and V, with 7 us for its launch and its trips to memory one
+// behind the other.  Both at the rates of large problems, the forward's never below half of the chip.
+// A launch in which no tile asks costs 2 to 3 us, so there is one only where a gate of softplus(N(-2, 1)), 0.19 a key, would save 6 us.
+// Whole bands / with the launch, us, gates of softplus(N(mu, 1)):                mu    -3          -2          -1         0.5
+//   taken      B4 H16   N4096 d64  w700                                             61 / 65     61 / 56     59 / 48    58 / 46
+//              B4 H16/4 N8192 d64  w512                                            101 / 106   101 / 89     98 / 70    97 / 62
+//              B1 H32/8 N2048 d128 w1024                                            36 / 40     35 / 29     34 / 24    34 / 23
+//              B2 H16   N4096 d128 w700 fp32                                       278 / 278   279 / 217   277 / 176  282 / 150
+//   not taken  B4 H16   N4096 d64  w512                                             54 / 57     54 / 55     52 / 47    53 / 44
+//              B1 H32   N2048 d64  w1024                                            25 / 27     24 / 23     24 / 21    24 / 19
+//              B1 H8    N2048 d128 w1024                                            18 / 23     17 / 18     17 / 17    17 / 16
+static KeyReach reach_of(int B, int H, int Hkv, int N, int d, int w, bool bf16) {
+    const double band = w < N ? w : N, mean = band - band * band / (2.0 * N), rows = (double)B * H * N;
+    const double fill = rows / 128 < 256 ? rows / (128 * 256) : 1.0, rate = bf16 ? d == 128 ? 900e6 : 700e6 : 150e6;  // FLOP/us
+    const double per_key = 4 * rows * d / rate / (fill < 0.5 ? 0.5 : fill);  // us for a key of the band
+    const double pass = 7 + 2.0 * B * Hkv * N * d * (bf16 ? 2 : 4) / 6.2e6;
+    const double few = 100 + pass / per_key, typical = 49 / 0.19;
+    if (per_key * (mean - few - typical) < 6) return {0, 0};
     long block = 64;
-    while ((band + block) / block + 1 > 64) block *= 2;  // (an entry for each lane of a wave)
-    return (int)block;
+    while (((long)band + block) / block + 1 > 64) block *= 2;  // (an entry for each lane of a wave)
+    return {(int)block, (int)few};
 }
 
 template <int D, typename T>
-static void launch(int block, int tile, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv, int N, int w, hipStream_t s) {
-    const int blocks = (N + block - 1) / block;
+static void launch(KeyReach reach, int tile, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv, int N, int w, hipStream_t s) {
+    const int blocks = (N + reach.block - 1) / reach.block;
     hipLaunchKernelGGL((key_reach_kernel<D, T>), dim3((unsigned)(B * Hkv) * blocks), dim3(64), 0, s, (const T*)K, (const T*)V, c, (T*)O, N, w, blocks,
-                       block, tile, H, H / Hkv);
+                       reach.block, reach.few, tile, H, H / Hkv);
 }
-hipError_t key_reach(int& block, int tile, bool bf16, const void* Q, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv,
+hipError_t key_reach(KeyReach& reach, int tile, bool bf16, const void* Q, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv,
                      int N, int d, int w, float scale, hipStream_t s) {
     const size_t row = (size_t)d * (bf16 ? 2 : 4), out = (size_t)B * H * N * row, keys = (size_t)B * Hkv * N * row;
-    block = scale > 0.f ? reach_block_of(B * H, N, d, w, bf16) : 0;
+    reach = scale > 0.f ? reach_of(B, H, Hkv, N, d, w, bf16) : KeyReach{0, 0};
     if (overlap(O, out, Q, out) || overlap(O, out, K, keys) || overlap(O, out, V, keys) || overlap(O, out, c, (size_t)B * H * N * sizeof(float)))
-        block = 0;
-    if (block == 0) return hipSuccess;
-    if (bf16) d == 128 ? launch<128, bf16_t>(block, tile, K, V, c, O, B, H, Hkv, N, w, s) : launch<64, bf16_t>(block, tile, K, V, c, O, B, H, Hkv, N, w, s);
-    else d == 128 ? launch<128, float>(block, tile, K, V, c, O, B, H, Hkv, N, w, s) : launch<64, float>(block, tile, K, V, c, O, B, H, Hkv, N, w, s);
+        reach.block = 0;
+    if (reach.block == 0) return hipSuccess;
+    if (bf16) d == 128 ? launch<128, bf16_t>(reach, tile, K, V, c, O, B, H, Hkv, N, w, s) : launch<64, bf16_t>(reach, tile, K, V, c, O, B, H, Hkv, N, w, s);
+    else d == 128 ? launch<128, float>(reach, tile, K, V, c, O, B, H, Hkv, N, w, s) : launch<64, float>(reach, tile, K, V, c, O, B, H, Hkv, N, w, s);
     return hipGetLastError();
 }
 
