@@ -48,6 +48,9 @@ __device__ __forceinline__ float outweighs(float far, float near) { return far <
 // always agree: there is nothing the compiler could fuse in one of them.)
 constexpr float kTypicalReach = 49.f;
 constexpr int kFewBackward = 128;
+// The whole-tile kernels of bf16 at d = 128 run one workgroup a CU, whose look nothing overlaps: whole bands / shortened, us, B4 H16 N4096 w256, where
+// mu = -1 (0.5) erases 130 (210) keys: 239 / 250 (237 / 234), at d = 64 117 / 115 (115 / 106).
+__device__ constexpr int few_backward(int d) { return d == 128 ? 192 : kFewBackward; }
 __device__ __forceinline__ bool reach_pays(float decay, int len, int few) {
     return decay > kTypicalReach && decay * (float)(len - few) > kTypicalReach * (float)len;
 }
@@ -83,7 +86,7 @@ template <int LANES = 64>
 __device__ __forceinline__ int lanes_min(int x) {
     return over_lanes<LANES>(x, [](int a, int b) { return min(a, b); });
 }
-// Sum over the 8 or 16 lanes of a row, in all of them.
+// Sum over the 4, 8 or 16 lanes of a row, in all of them.
 template <int LANES>
 __device__ __forceinline__ float row_sum(float x) {
     auto moved = [](float v, auto ctrl) {
@@ -91,7 +94,7 @@ __device__ __forceinline__ float row_sum(float x) {
     };
     x += moved(x, std::integral_constant<int, 0xB1>{});
     x += moved(x, std::integral_constant<int, 0x4E>{});
-    x += moved(x, std::integral_constant<int, 0x141>{});
+    if (LANES >= 8) x += moved(x, std::integral_constant<int, 0x141>{});
     if (LANES == 16) x += moved(x, std::integral_constant<int, 0x140>{});
     return x;
 }
@@ -213,76 +216,87 @@ struct OwnRows {
     float q2, g2, d2;  // (of a key tile: those of the queries at the diagonal)
     float k2, v2;      // (of a key tile: its own, 0 where the dQ pass looks by itself)
 };
-// Blocks i0 .. i1 of queries.
+// Blocks i0 and i1 (the same, or next to each other) of queries.
 __device__ __forceinline__ OwnRows own_queries(const float* at, const float* ch, int i0, int i1, int N, float cbase, float sl) {
-    int norm = 0, edge = 0x7fffffff;
+    const float *r0 = at + reach_row(i0, N), *r1 = at + reach_row(i1, N);
+    const int norm = max(norm_bits(r0[kReachNorm]), norm_bits(r1[kReachNorm]));
+    const int edge = min(lowest_order((ch[64 * i0] - cbase) + r0[kReachEdge]), lowest_order((ch[64 * i1] - cbase) + r1[kReachEdge]));
     OwnRows own = {};
-    for (int i = i0; i <= i1; ++i) {
-        const float* r = at + reach_row(i, N);
-        norm = max(norm, norm_bits(r[kReachNorm]));
-        edge = min(edge, lowest_order((ch[64 * i] - cbase) + r[kReachEdge]));
-        own.k2 = fmaxf(own.k2, r[kReachOneK]);
-        own.v2 = fmaxf(own.v2, r[kReachOneV]);
-    }
+    own.k2 = fmaxf(r0[kReachOneK], r1[kReachOneK]);
+    own.v2 = fmaxf(r0[kReachOneV], r1[kReachOneV]);
     own.reach2 = reach2_of(norm, sl);
     own.edge = from_order(edge) * kLog2e;
     return own;
 }
-// Blocks i0 .. i1 of queries at the diagonal of a key tile.
-__device__ __forceinline__ void own_weights(OwnRows& own, const float* at, int i0, int i1, int N) {
-    own.q2 = own.g2 = own.d2 = 0.f;
-    for (int i = i0; i <= i1; ++i) {
-        const float* r = at + reach_row(i, N);
-        own.q2 = fmaxf(own.q2, r[kReachNorm]);
-        own.g2 = fmaxf(own.g2, r[kReachG]);
-        own.d2 = fmaxf(own.d2, r[kReachD]);
-    }
-}
-// Blocks i0 .. i1 of keys.
+// Blocks i0 and i1 of keys, and of queries at their diagonal.
 __device__ __forceinline__ OwnRows own_keys(const float* at, int i0, int i1, int N, float cbase, float sl) {
-    int norm = 0, edge = (int)0x80000000;
-    for (int i = i0; i <= i1; ++i) {
-        const float* r = at + reach_row(i, N);
-        norm = max(norm, norm_bits(r[kReachKeyNorm]));
-        edge = max(edge, highest_order(r[kReachKeyHigh] - cbase));
-    }
+    const float *r0 = at + reach_row(i0, N), *r1 = at + reach_row(i1, N);
+    const int norm = max(norm_bits(r0[kReachKeyNorm]), norm_bits(r1[kReachKeyNorm]));
+    const int edge = max(highest_order(r0[kReachKeyHigh] - cbase), highest_order(r1[kReachKeyHigh] - cbase));
     OwnRows own = {};
     own.reach2 = reach2_of(norm, sl);
     own.edge = from_order(edge) * kLog2e;
-    own_weights(own, at, i0, i1, N);
+    own.q2 = fmaxf(r0[kReachNorm], r1[kReachNorm]);
+    own.g2 = fmaxf(r0[kReachG], r1[kReachG]);
+    own.d2 = fmaxf(r0[kReachD], r1[kReachD]);
     return own;
 }
-// Last block of queries from i_hi down to i_min + 1 that needs one of the keys, else i_min.  at: of the head.
-__device__ __forceinline__ int last_needing_block(const float* at, const float* ch, int i_min, int i_hi, int N, const OwnRows& own, float cbase, int lane) {
+// What block i of queries has to say to a key tile.
+struct QueryBlock {
+    float norm, edge, g, d, one_k, one_v, c;
+};
+__device__ __forceinline__ QueryBlock query_block(const float* at, const float* ch, int i, int N) {
+    const float* r = at + reach_row(i, N);
+    return {r[kReachNorm], r[kReachEdge], r[kReachG], r[kReachD], r[kReachOneK], r[kReachOneV], ch[64 * i]};
+}
+__device__ __forceinline__ bool needs_keys(const QueryBlock& b, const OwnRows& own, float cbase) {
+    // dO in dV, dS of dO and D times Q in dK; and in these queries' dQ dS of V times K
+    const float here = fmaxf(outweighs(b.g, own.g2), outweighs(b.d, own.d2)) + outweighs(b.norm, own.q2);
+    const float there = outweighs(own.v2, b.one_v) + outweighs(own.k2, b.one_k);
+    return !is_erased(b.norm, own.reach2, ((b.c - cbase) + b.edge) * kLog2e - own.edge - kErased, fmaxf(here, there));
+}
+// Last block of queries from i_hi down to i_min + 1 that needs one of the keys, else i_min.  at: of the head; first: block i_hi - lane, if
+// there is one.
+__device__ __forceinline__ int last_needing_block(const float* at, const float* ch, int i_min, int i_hi, int N, const OwnRows& own, float cbase, int lane,
+                                                  QueryBlock first) {
     for (int top = i_hi; top > i_min; top -= 64) {
         const int i = top - lane;
-        bool kept = i > i_min;
-        if (kept) {
-            const float* r = at + reach_row(i, N);
-            // dO in dV, dS of dO and D times Q in dK; and in these queries' dQ dS of V times K
-            const float here = fmaxf(outweighs(r[kReachG], own.g2), outweighs(r[kReachD], own.d2)) + outweighs(r[kReachNorm], own.q2);
-            const float there = outweighs(own.v2, r[kReachOneV]) + outweighs(own.k2, r[kReachOneK]);
-            kept = !is_erased(r[kReachNorm], own.reach2, ((ch[64 * i] - cbase) + r[kReachEdge]) * kLog2e - own.edge - kErased, fmaxf(here, there));
-        }
-        const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
+        if (top != i_hi) first = query_block(at, ch, max(i, i_min), N);
+        const unsigned long long mask = __builtin_amdgcn_ballot_w64(i > i_min && needs_keys(first, own, cbase));
         if (mask) return top - __builtin_ctzll(mask);
     }
     return i_min;
 }
-// First block of keys from i_lo on that is needed, i_max if none before it is.
-__device__ __forceinline__ int first_needed_block(const float* at, int i_lo, int i_max, int N, const OwnRows& own, float cbase, int lane) {
+// What block i of keys has to say to a query tile.
+struct KeyValues {
+    float norm, high, value;
+};
+__device__ __forceinline__ KeyValues key_values(const float* at, int i, int N) {
+    const float* r = at + reach_row(i, N);
+    return {r[kReachKeyNorm], r[kReachKeyHigh], r[kReachValue]};
+}
+// First block of keys from i_lo on that is needed, i_max if none before it is.  first: block i_lo + lane, if there is one.
+__device__ __forceinline__ int first_needed_block(const float* at, int i_lo, int i_max, int N, const OwnRows& own, float cbase, int lane, KeyValues first) {
     for (int base = i_lo; base < i_max; base += 64) {
         const int i = base + lane;
-        bool kept = i < i_max;
-        if (kept) {
-            const float* r = at + reach_row(i, N);
-            const float heavier = outweighs(r[kReachKeyNorm], own.k2) + outweighs(r[kReachValue], own.v2);
-            kept = !is_erased(r[kReachKeyNorm], own.reach2, own.edge - kErased - (r[kReachKeyHigh] - cbase) * kLog2e, heavier);
-        }
+        if (base != i_lo) first = key_values(at, min(i, i_max), N);
+        const float heavier = outweighs(first.norm, own.k2) + outweighs(first.value, own.v2);
+        const bool kept = i < i_max && !is_erased(first.norm, own.reach2, own.edge - kErased - (first.high - cbase) * kLog2e, heavier);
         const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
         if (mask) return base + __builtin_ctzll(mask);
     }
     return i_max;
+}
+// The two for a tile that has nothing requested yet: its own blocks and the first 64 of the other side in one trip to memory.
+__device__ __forceinline__ int first_needed_block(const float* at, const float* ch, int i_lo, int i0, int i1, int N, float cbase, float sl, int lane) {
+    const KeyValues first = key_values(at, min(i_lo + lane, i0), N);
+    asm volatile("" ::: "memory");
+    return first_needed_block(at, i_lo, i0, N, own_queries(at, ch, i0, i1, N, cbase, sl), cbase, lane, first);
+}
+__device__ __forceinline__ int last_needing_block(const float* at, const float* ch, int i0, int i1, int i_hi, int N, float cbase, float sl, int lane) {
+    const QueryBlock first = query_block(at, ch, max(i_hi - lane, i1), N);
+    asm volatile("" ::: "memory");
+    return last_needing_block(at, ch, i1, i_hi, N, own_keys(at, i0, i1, N, cbase, sl), cbase, lane, first);
 }
 // What a row-dot workgroup has gathered of a block, `row` its place (one thread).  looked: whether it has; else the block is kept.
 struct BlockValues {

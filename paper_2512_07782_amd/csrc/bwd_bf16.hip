@@ -64,7 +64,8 @@ __global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restri
     }
     const float c0 = c[head + t0];
     const int far = max(0, t0 - w + 1), end = (int)min((long)N - 1, (long)t0 + kReachRows - 2 + w);
-    const bool look = reach != nullptr && (reach_pays(c0 - c[head + far], t0 - far, kFewBackward) || reach_pays(c[head + end] - c0, end - t0, kFewBackward));
+    constexpr int few = KEYS ? kFewBackward : few_backward(D);
+    const bool look = reach != nullptr && (reach_pays(c0 - c[head + far], t0 - far, few) || reach_pays(c[head + end] - c0, end - t0, few));
     float dot[kPasses];
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
@@ -115,44 +116,81 @@ struct DkvSmem {
 };
 
 // The last query tile (of 64) that a workgroup's 128 keys are streamed against: that of t_hi, or where the gate has erased all of them
-// before.  The waves' own 32 keys come as fragments or as matrices.  at: of the head (nullptr: t_hi's), needed: over_waves.  `key` is the lane's.
+// before.  at: of the head (nullptr: t_hi's), needed: over_waves, keys: the wave's (or 16 of the 32 that two waves have in common).
+// Norms and gates of keys: the largest squared norm (infinite where a value row is not finite: its dP is not either), that of a value row, the
+// highest gate.
+struct KeyNorms {
+    int norm;
+    float v2, high;
+};
 template <int D>
-struct KeyFragments {
+struct KeyFragments {  // already there, a key's row in two lanes
     const bf16x8 (&k)[D / 16], (&v)[D / 16];
-    __device__ __forceinline__ void get(int kc, bf16x8& x, bf16x8& y) const { x = k[kc], y = v[kc]; }
-};
-struct KeyRows {
-    const bf16_t *k, *v;  // the lane's half row
-    __device__ __forceinline__ void get(int kc, bf16x8& x, bf16x8& y) const {
-        x = *reinterpret_cast<const bf16x8*>(k + 16 * kc), y = *reinterpret_cast<const bf16x8*>(v + 16 * kc);
-    }
-};
-template <int D, int WAVES, typename Keys>
-__device__ __forceinline__ int last_query_tile(const Keys& keys, const float* ch, float* at, int k0, int t_hi, int N, int key, float cbase, float sl,
-                                               int* needed, int wv, int lane) {
-    const int i_hi = t_hi / kTileRows, k1 = min(k0 + 128, N) - 1, i_min = k1 / kTileRows;
-    int last = i_hi;
-    if (at == nullptr) return last;
-    if (i_hi > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1, kFewBackward)) {
+    const float* gate;
+    float g;
+    __device__ __forceinline__ void request() { g = *gate; }
+    __device__ __forceinline__ KeyNorms norms() const {
         float k2 = 0.f, v2 = 0.f;
 #pragma unroll
         for (int kc = 0; kc < D / 16; ++kc) {
-            bf16x8 k, v;
-            keys.get(kc, k, v);
-            k2 = dot8(k, k, k2);
-            v2 = dot8(v, v, v2);
+            k2 = dot8(k[kc], k[kc], k2);
+            v2 = dot8(v[kc], v[kc], v2);
         }
         v2 = xhalf_sum(v2);
         k2 = xhalf_sum(k2);
-        // (a value row that is not finite keeps everything: its dP is not either)
-        const int norm = lanes_max(finite(v2) ? norm_bits(k2) : kInfBits);
+        return {lanes_max(finite(v2) ? norm_bits(k2) : kInfBits), __int_as_float(lanes_max(norm_bits(v2))), g};
+    }
+};
+template <int D>
+struct KeyRows {  // a row in four lanes
+    const bf16_t *K, *V;  // the lane's quarter
+    const float* gate;
+    bf16x8 k[D / 32], v[D / 32];
+    float g;
+    __device__ __forceinline__ void request() {
+        g = *gate;
+#pragma unroll
+        for (int i = 0; i < D / 32; ++i) {
+            k[i] = *reinterpret_cast<const bf16x8*>(K + 8 * i);
+            v[i] = *reinterpret_cast<const bf16x8*>(V + 8 * i);
+        }
+    }
+    __device__ __forceinline__ KeyNorms norms() const {
+        float k2 = 0.f, v2 = 0.f;
+#pragma unroll
+        for (int i = 0; i < D / 32; ++i) {
+            k2 = dot8(k[i], k[i], k2);
+            v2 = dot8(v[i], v[i], v2);
+        }
+        v2 = row_sum<4>(v2);
+        k2 = row_sum<4>(k2);
+        return {lanes_max(finite(v2) ? norm_bits(k2) : kInfBits), __int_as_float(lanes_max(norm_bits(v2))), g};
+    }
+};
+template <int D, int WAVES, typename Keys>
+__device__ __forceinline__ int last_query_tile(Keys keys, const float* ch, float* at, int k0, int t_hi, int N, float cbase, float sl, int* needed,
+                                               int wv, int lane) {
+    const int i_hi = t_hi / kTileRows, k1 = min(k0 + 128, N) - 1, i_min = k1 / kTileRows;
+    int last = i_hi;
+    if (at == nullptr) return last;
+    if (i_hi > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1, few_backward(D))) {
+        // All that the answer takes is requested at once, behind the first tiles: four trips to memory one behind the other in front of the first
+        // product otherwise.  (Backward, us, one by one / at once: B4 H16 N8192 d128 w1024 mu -2 643 / 609, mu -1 542 / 508, H16/4 N4096 277 / 259.
+        // In front of the branch, too, they would be for nothing where it is not taken: w256 mu -3 494 / 522.)
+        keys.request();
+        const QueryBlock block = query_block(at, ch, max(i_hi - lane, i_min), N), here = query_block(at, ch, i_min, N),
+                         front = query_block(at, ch, k0 / kReachRows, N);
+        asm volatile("" ::: "memory");
+        const KeyNorms n = keys.norms();
         OwnRows own = {};
-        own.reach2 = reach2_of(norm, sl);
-        own.edge = from_order(lanes_max(highest_order(ch[min(key, N - 1)] - cbase))) * kLog2e;
-        own.k2 = __int_as_float(norm);
-        own.v2 = __int_as_float(lanes_max(norm_bits(v2)));
-        own_weights(own, at, k0 / kReachRows, i_min, N);
-        const int needing = last_needing_block(at, ch, i_min, i_hi, N, own, cbase, lane);
+        own.reach2 = reach2_of(n.norm, sl);
+        own.edge = from_order(lanes_max(highest_order(n.high - cbase))) * kLog2e;
+        own.k2 = __int_as_float(n.norm);
+        own.v2 = n.v2;
+        own.q2 = fmaxf(front.norm, here.norm);
+        own.g2 = fmaxf(front.g, here.g);
+        own.d2 = fmaxf(front.d, here.d);
+        const int needing = last_needing_block(at, ch, i_min, i_hi, N, own, cbase, lane, block);
         last = over_waves<WAVES, false>(needing, needed, wv, lane);
     }
     if (threadIdx.x == 0) reinterpret_cast<int*>(at)[reach_row(k0 / kReachRows, N) + kReachLast] = last;
@@ -250,8 +288,8 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkv_bf16_kernel(
         };
         loader.load(Qh, Gh, i_lo, ifull, N, sm.qg.a[0], sm.qg.b[0]);
         load_vec(i_lo);
-        const int i_hi = last_query_tile<D, 4>(KeyFragments<D>{kf, vf}, ch, reach == nullptr ? nullptr : reach + (size_t)bh * N, k0, t_hi, N, key,
-                                                 cbase, sl, sm.needed, wv, lane);
+        const int i_hi = last_query_tile<D, 4>(KeyFragments<D>{kf, vf, ch + min(key, N - 1), 0.f}, ch, reach == nullptr ? nullptr : reach + (size_t)bh * N,
+                                                k0, t_hi, N, cbase, sl, sm.needed, wv, lane);
         store_vec(0);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -426,7 +464,8 @@ __global__ __launch_bounds__(2 * kThreads, 1) void bwd_dkv8_bf16_kernel(
     const int key = kw0 + lk;
 
     // K^T and V^T fragments (B operands: column = key, k = head dimension) come from the staged tiles
-    const size_t own_row = head_off + (size_t)min(key, N - 1) * D + 8 * h;
+    const int norm_key = min(kw0 + 16 * half + lane / 4, N - 1);  // (last_query_tile)
+    const size_t norm_row = head_off + (size_t)norm_key * D + D / 4 * (lane % 4);
     const char* ktile = sm8.kv.a[kg >> 1];
     const char* vtile = sm8.kv.b[kg >> 1];
     const int krow0 = 32 * (kg & 1);
@@ -499,8 +538,8 @@ __global__ __launch_bounds__(2 * kThreads, 1) void bwd_dkv8_bf16_kernel(
         };
         loader.load(Qh, Gh, i_lo, ifull, N, sm.qg.a[0], sm.qg.b[0]);
         load_vec(i_lo);
-        const int i_hi = last_query_tile<D, 8>(KeyRows{K + own_row, V + own_row}, ch, reach == nullptr ? nullptr : reach + (size_t)bh * N, k0, t_hi,
-                                                 N, key, cbase, sl, sm.needed, wv, lane);
+        const int i_hi = last_query_tile<D, 8>(KeyRows<D>{K + norm_row, V + norm_row, ch + norm_key}, ch,
+                                                reach == nullptr ? nullptr : reach + (size_t)bh * N, k0, t_hi, N, cbase, sl, sm.needed, wv, lane);
         store_vec(0);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -1123,8 +1162,10 @@ static bool bwd_in_one_launch(int BH, int BHkv, int N, int d, int w) {
 // erase in part.  Whole step, us, without / with, gates of mu = -6 (nothing erased), -3, -2:
 //   H1 N2000 d64 causal    36 /  38    35 /  39    35 /  33      H8 N2000 d128 causal   120 / 125   120 / 122   120 /  91
 //   H4 N8192 d64 w4096    192 / 198   189 / 106   189 /  73      H1 N16384 d128 w4096   246 / 251   247 / 138   246 /  96
-//   H4 N3000 d64 w1600     50 /  55    50 /  57    50 /  51  (this one does not take it)
-static bool bwd_split_looks(int N, int w) { return (w < N ? w : N) >= 1500; }
+// Backward alone, gates of mu = -3, -2, -1:
+//   H8 N2048 d128 w1024    57 /  58    57 /  45    57 /  39      H8/2 N2048 d64 w1024    36 /  38    36 /  30    36 /  26
+//   H8 N2048 d128 w700     46 /  59    46 /  46    46 /  41      H8 N2048 d64 w1024      36 /  39    35 /  34    35 /  33  (these do not take it)
+static bool bwd_split_looks(int G, int N, int d, int w) { return (w < N ? w : N) >= (d == 128 || G > 1 ? 1000 : 1500); }
 
 template <int D>
 static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO,
@@ -1158,7 +1199,7 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     // whole-tile dQ kernels.)
     const bool some_split = dkv_split || dq_split;
     float* reach = backward_reach(dalpha, Q, K, V, O, dO, c, L, sizeof(bf16_t), B, H, Hkv, N, D, w, scale);
-    if (some_split && !bwd_split_looks(N, w)) reach = nullptr;
+    if (some_split && !bwd_split_looks(H / Hkv, N, D, w)) reach = nullptr;
     const float* seen = dkv_split ? nullptr : reach;
     if (some_split && reach != nullptr) {
         rowdot(std::true_type{}, reach, dq_split && !one_launch ? kKernDq : kKernDkv);  // (recorded with the pass that it is for)

@@ -62,8 +62,7 @@ __device__ __forceinline__ void dq_split(const BwdBf16& a, int num_qtiles, int b
     int first = max(0, q0 - w + 1);
     if (a.reach != nullptr && reach_pays(band.cbase - band.ch[first], q0 - first, kFewBackward)) {  // the keys that the gate has erased for all queries stay out
         const float* at = a.reach + (size_t)bh * N;
-        const OwnRows own = own_queries(at, band.ch, q0 / 64, (min(N, q0 + 32 * QW) - 1) / 64, N, band.cbase, sl);
-        first = max(first, 64 * first_needed_block(at, first / 64, q0 / 64, N, own, band.cbase, lane));
+        first = max(first, 64 * first_needed_block(at, band.ch, first / 64, q0 / 64, (min(N, q0 + 32 * QW) - 1) / 64, N, band.cbase, sl, lane));
         band.from(__builtin_amdgcn_readfirstlane(first), q0, w);
     }
     // rows past N get an exponent of -big, i.e. p = 0
@@ -215,8 +214,7 @@ __device__ __forceinline__ void dkv_split(const BwdBf16& a, int block) {
             const size_t rows = (size_t)(bh0 + g) * N;
             const float* ch = c + rows;
             if (reach_pays(ch[t_hi] - ch[k1], t_hi - k1, kFewBackward)) {
-                const OwnRows own = own_keys(a.reach + rows, k0 / 64, k0 / 64, N, ch[k0], sl);
-                last = max(last, last_needing_block(a.reach + rows, ch, i_min, t_hi / 64, N, own, ch[k0], lane));
+                last = max(last, last_needing_block(a.reach + rows, ch, k0 / 64, i_min, t_hi / 64, N, ch[k0], sl, lane));
             } else {
                 last = t_hi / 64;
             }

@@ -534,7 +534,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) voi
     if (reach.block != 0 && reach_pays(ch[q0] - ch[k_lo], q0 - k_lo, reach.few)) {  // the keys that the gate has erased for all queries stay out
         float q2 = 0.f, k2 = 0.f, own = 0.f;
         const float *qr = Q + ho + (size_t)tc * D + 4 * h, *kr = Kh + (size_t)tc * D + 4 * h;  // (the halves take every other four columns)
-#pragma unroll 4
+#pragma unroll 8
         for (int i = 0; i < D / 8; ++i) {
             const f32x4 q = *reinterpret_cast<const f32x4*>(qr + 8 * i), k = *reinterpret_cast<const f32x4*>(kr + 8 * i);
 #pragma unroll
@@ -709,8 +709,7 @@ __device__ __forceinline__ void dq_f32_mfma(
         int first_key = max(0, q0 - w + 1);
         if (reach != nullptr && reach_pays(ch[q0] - ch[first_key], q0 - first_key, kFewBackward)) {  // the keys that the gate has erased for all queries stay out
             const float* at = reach + (size_t)bh * N;
-            const OwnRows own = own_queries(at, ch, q0 / 64, (min(N, q0 + 32 * NP) - 1) / 64, N, ch[q0], scale * kLog2e);
-            first_key = max(first_key, 64 * first_needed_block(at, first_key / 64, q0 / 64, N, own, ch[q0], lane));
+            first_key = max(first_key, 64 * first_needed_block(at, ch, first_key / 64, q0 / 64, (min(N, q0 + 32 * NP) - 1) / 64, N, ch[q0], scale * kLog2e, lane));
         }
         const int jb_lo = first_key / 32, jb_hi = (min(N, q0 + 32 * NP) - 1) / 32;
         using Mover = F32TileMover<D, 128 * NP>;
@@ -906,8 +905,7 @@ __device__ __forceinline__ void dkv_f32_mfma(
             const float* ch = c + rows;
             const int k1 = min(k0 + 32 * NP, N) - 1, i_min = k1 / 64;
             if (reach != nullptr && t_hi / 64 > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1, kFewBackward)) {
-                const OwnRows own = own_keys(reach + rows, k0 / 64, k1 / 64, N, ch[k0], scale * kLog2e);
-                qb_hi = min(qb_hi, 2 * last_needing_block(reach + rows, ch, i_min, t_hi / 64, N, own, ch[k0], lane) + 1);
+                qb_hi = min(qb_hi, 2 * last_needing_block(reach + rows, ch, k0 / 64, i_min, t_hi / 64, N, ch[k0], scale * kLog2e, lane) + 1);
             }
             return __builtin_amdgcn_readfirstlane(qb_hi) - qb_lo + 1;
         };

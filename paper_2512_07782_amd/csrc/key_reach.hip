@@ -88,7 +88,7 @@ __global__ __launch_bounds__(64) void key_reach_kernel(const T* __restrict__ K, 
 //   taken      B4 H16   N4096 d64  w700                                             61 / 65     61 / 56     59 / 48    58 / 46
 //              B4 H16/4 N8192 d64  w512                                            101 / 106   101 / 89     98 / 70    97 / 62
 //              B1 H32/8 N2048 d128 w1024                                            36 / 40     35 / 29     34 / 24    34 / 23
-//              B2 H16   N4096 d128 w700 fp32                                       278 / 278   279 / 217   277 / 176  282 / 150
+//              B1 H32   N4096 d128 w700 fp32                                       278 / 278   279 / 217   277 / 176  282 / 150
 //   not taken  B4 H16   N4096 d64  w512                                             54 / 57     54 / 55     52 / 47    53 / 44
 //              B1 H32   N2048 d64  w1024                                            25 / 27     24 / 23     24 / 21    24 / 19
 //              B1 H8    N2048 d128 w1024                                            18 / 23     17 / 18     17 / 17    17 / 16
