@@ -50,7 +50,7 @@ constexpr float kTypicalReach = 49.f;
 constexpr int kFewBackward = 128;
 // The whole-tile kernels of bf16 at d = 128 run one workgroup a CU, whose look nothing overlaps: whole bands / shortened, us, B4 H16 N4096 w256, where
 // mu = -1 (0.5) erases 130 (210) keys: 239 / 250 (237 / 234), at d = 64 117 / 115 (115 / 106).
-__device__ constexpr int few_backward(int d) { return d == 128 ? 192 : kFewBackward; }
+__host__ __device__ constexpr int few_backward(int d) { return d == 128 ? 192 : kFewBackward; }
 __device__ __forceinline__ bool reach_pays(float decay, int len, int few) {
     return decay > kTypicalReach && decay * (float)(len - few) > kTypicalReach * (float)len;
 }
@@ -194,7 +194,10 @@ enum : int {
     kReachLast,      // From the whole-tile dK/dV kernel on, in the first block of its 128-key tiles: the last block of queries that needs a key.
     kReachValues
 };
-constexpr int kReachShortest = kFewBackward;  // bands up to this long never pay
+// Bands up to this long are not looked at: only gates of more than 0.25 (fp32 0.37) a key would erase enough of them, and the look costs 2 to 5 %
+// (1 to 3 %) where it is in vain (whole step, us, whole bands / looked at: B2 H12/6 N2653 d64 w302 mu -2 66 / 69; fp32 B6 H13 N257 d128 mu -2
+// 104 / 107, B5 H2 N7686 d128 w289 mu -1 493 / 437).
+constexpr int shortest_reach(int d, size_t size) { return size == 2 ? few_backward(d) + 200 : kFewBackward + 132; }
 // Row of dalpha from which on block i has its values: its first, or for a last block of too few rows the 17th of the one before.
 __device__ __forceinline__ int reach_row(int i, int N) { return kReachRows * i + kReachValues <= N ? kReachRows * i : kReachRows * (i - 1) + 16; }
 
@@ -202,7 +205,7 @@ __device__ __forceinline__ int reach_row(int i, int N) { return kReachRows * i +
 inline float* backward_reach(float* dalpha, const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* c, const float* L,
                              size_t size, int B, int H, int Hkv, int N, int d, int w, float scale) {
     const size_t rows = (size_t)B * H * N, gate = rows * sizeof(float), q = rows * d * size, kv = (size_t)B * Hkv * N * d * size;
-    bool free = scale > 0.f && (w < N ? w : N) > kReachShortest;
+    bool free = scale > 0.f && (w < N ? w : N) > shortest_reach(d, size);
     for (const void* m : {Q, O, dO}) free = free && !overlap(dalpha, gate, m, q);
     for (const void* m : {K, V}) free = free && !overlap(dalpha, gate, m, kv);
     for (const float* v : {c, L}) free = free && !overlap(dalpha, gate, v, gate);

@@ -41,10 +41,37 @@ constexpr float kPosBig = 1.0e30f;
 // 1. D_t = <O_t, dO_t>, and what the dK/dV kernel asks of a block of queries (band_reach.h)
 // ------------------------------------------------------------------------------------------
 // A workgroup takes 64 rows of a head, 16 bytes of each matrix a lane and all of them in flight.  Q is read only where the gate decays
-// enough over the window that keys may be erased for these rows.  KEYS, in front of the split kernels, which hold too few rows to look at the
-// other side for themselves: K and V as well.  reach: dalpha, or nullptr.
+// enough over the window that keys may be erased for these rows.  kDotKeys, in front of the split kernels, which hold too few rows to look at the
+// other side for themselves: K and V as well.  reach: dalpha.
+template <int LPR>
+__device__ __forceinline__ float row_dot(const bf16x8& a, const bf16x8& b) {
+    float x = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x = fmaf((float)a[e], (float)b[e], x);
+    return row_sum<LPR>(x);
+}
+// D alone, where nothing is asked: smaller workgroups over all rows (B8 H60 N1003 d128, us: in the kernel below without its look 44.7, here 42.0).
+template <int D>
+__global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO, float* __restrict__ Dv, long rows) {
+    constexpr int LPR = D / 8, kRows = 256 / LPR, kPasses = D / 64;
+    const int part = threadIdx.x % LPR;
+    const long r0 = (long)blockIdx.x * (kPasses * kRows) + threadIdx.x / LPR;
+    bf16x8 a[kPasses], b[kPasses];
+#pragma unroll
+    for (int p = 0; p < kPasses; ++p) {
+        const size_t at = (size_t)min(r0 + p * kRows, rows - 1) * D + 8 * part;
+        a[p] = *reinterpret_cast<const bf16x8*>(O + at);
+        b[p] = *reinterpret_cast<const bf16x8*>(dO + at);
+    }
+#pragma unroll
+    for (int p = 0; p < kPasses; ++p) {
+        const float dot = row_dot<LPR>(a[p], b[p]);
+        if (part == 0 && r0 + p * kRows < rows) Dv[r0 + p * kRows] = dot;
+    }
+}
+
 template <int D, bool KEYS>
-__global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO,
+__global__ __launch_bounds__(256) void rowdot_reach_bf16_kernel(const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO,
                                                           const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                           const bf16_t* __restrict__ V, const float* __restrict__ c,
                                                           const float* __restrict__ L, float* __restrict__ Dv, float* __restrict__ reach, int N,
@@ -62,20 +89,16 @@ __global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restri
         a[p] = *reinterpret_cast<const bf16x8*>(O + at);
         b[p] = *reinterpret_cast<const bf16x8*>(dO + at);
     }
-    const float c0 = c[head + t0];
-    const int far = max(0, t0 - w + 1), end = (int)min((long)N - 1, (long)t0 + kReachRows - 2 + w);
-    constexpr int few = KEYS ? kFewBackward : few_backward(D);
-    const bool look = reach != nullptr && (reach_pays(c0 - c[head + far], t0 - far, few) || reach_pays(c[head + end] - c0, end - t0, few));
     float dot[kPasses];
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
-        dot[p] = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dot[p] = fmaf((float)a[p][e], (float)b[p][e], dot[p]);
-#pragma unroll
-        for (int d = LPR / 2; d >= 1; d >>= 1) dot[p] += __shfl_xor(dot[p], d, 64);
+        dot[p] = row_dot<LPR>(a[p], b[p]);
         if (part == 0 && r0 + p * kRows < N) Dv[head + r0 + p * kRows] = dot[p];
     }
+    const float c0 = c[head + t0];
+    const int far = max(0, t0 - w + 1), end = (int)min((long)N - 1, (long)t0 + kReachRows - 2 + w);
+    constexpr int few = KEYS ? kFewBackward : few_backward(D);
+    const bool look = reach_pays(c0 - c[head + far], t0 - far, few) || reach_pays(c[head + end] - c0, end - t0, few);
     if (look) {
         const size_t kv = (size_t)kv_head_of(bh, H, G) * N;
         auto norm_of = [&](const bf16_t* x) {
@@ -101,7 +124,7 @@ __global__ __launch_bounds__(256) void rowdot_bf16_kernel(const bf16_t* __restri
         }
         gather_block<KEYS>(&values, mine);
     }
-    if (reach != nullptr && threadIdx.x == 0) write_block(reach + head + reach_row(t0 / kReachRows, N), values, look, KEYS);
+    if (threadIdx.x == 0) write_block(reach + head + reach_row(t0 / kReachRows, N), values, look, KEYS);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -143,16 +166,20 @@ struct KeyFragments {  // already there, a key's row in two lanes
 };
 template <int D>
 struct KeyRows {  // a row in four lanes
-    const bf16_t *K, *V;  // the lane's quarter
-    const float* gate;
+    const bf16_t *K, *V;  // of the head
+    const float* ch;
+    int row0, N, lane;
     bf16x8 k[D / 32], v[D / 32];
     float g;
     __device__ __forceinline__ void request() {
-        g = *gate;
+        GFWA_PIN(lane);  // (addresses that are formed here, not carried through the kernel)
+        const int row = min(row0 + lane / 4, N - 1);
+        const size_t at = (size_t)row * D + D / 4 * (lane % 4);
+        g = ch[row];
 #pragma unroll
         for (int i = 0; i < D / 32; ++i) {
-            k[i] = *reinterpret_cast<const bf16x8*>(K + 8 * i);
-            v[i] = *reinterpret_cast<const bf16x8*>(V + 8 * i);
+            k[i] = *reinterpret_cast<const bf16x8*>(K + at + 8 * i);
+            v[i] = *reinterpret_cast<const bf16x8*>(V + at + 8 * i);
         }
     }
     __device__ __forceinline__ KeyNorms norms() const {
@@ -464,8 +491,6 @@ __global__ __launch_bounds__(2 * kThreads, 1) void bwd_dkv8_bf16_kernel(
     const int key = kw0 + lk;
 
     // K^T and V^T fragments (B operands: column = key, k = head dimension) come from the staged tiles
-    const int norm_key = min(kw0 + 16 * half + lane / 4, N - 1);  // (last_query_tile)
-    const size_t norm_row = head_off + (size_t)norm_key * D + D / 4 * (lane % 4);
     const char* ktile = sm8.kv.a[kg >> 1];
     const char* vtile = sm8.kv.b[kg >> 1];
     const int krow0 = 32 * (kg & 1);
@@ -538,7 +563,7 @@ __global__ __launch_bounds__(2 * kThreads, 1) void bwd_dkv8_bf16_kernel(
         };
         loader.load(Qh, Gh, i_lo, ifull, N, sm.qg.a[0], sm.qg.b[0]);
         load_vec(i_lo);
-        const int i_hi = last_query_tile<D, 8>(KeyRows<D>{K + norm_row, V + norm_row, ch + norm_key}, ch,
+        const int i_hi = last_query_tile<D, 8>(KeyRows<D>{K + head_off, V + head_off, ch, kw0 + 16 * half, N, lane}, ch,
                                                 reach == nullptr ? nullptr : reach + (size_t)bh * N, k0, t_hi, N, cbase, sl, sm.needed, wv, lane);
         store_vec(0);
         __builtin_amdgcn_s_waitcnt(0);
@@ -1182,11 +1207,11 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     char* ds_ws = reinterpret_cast<char*>(ws + 3 * pad) + scan_pad;  // only with `spill`
     BwdBf16 args = {(const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, c, L, Dv,
                     (bf16_t*)dQ, (bf16_t*)dK, (bf16_t*)dV, dc_col, dc_row, nullptr, B, H, Hkv, N, w, scale};
-    auto rowdot = [&](auto keys, float* reach, KernelId as) {
+    auto rowdot_reach = [&](auto keys, float* reach, KernelId as) {
         const int blocks = (N + kReachRows - 1) / kReachRows;
         ProfScope prof(as, s);
-        hipLaunchKernelGGL((rowdot_bf16_kernel<D, decltype(keys)::value>), dim3((unsigned)(B * H) * blocks), dim3(256), 0, s, args.O, args.dO, args.Q,
-                           args.K, args.V, c, L, Dv, reach, N, w, blocks, H, H / Hkv);
+        hipLaunchKernelGGL((rowdot_reach_bf16_kernel<D, decltype(keys)::value>), dim3((unsigned)(B * H) * blocks), dim3(256), 0, s, args.O, args.dO,
+                           args.Q, args.K, args.V, c, L, Dv, reach, N, w, blocks, H, H / Hkv);
     };
     const bool one_launch = bwd_in_one_launch(B * H, B * Hkv, N, D, w);
     // the dS blocks only travel between the kernels of this file: dK/dV is chosen first, dQ by whether there are blocks then
@@ -1202,7 +1227,7 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     if (some_split && !bwd_split_looks(H / Hkv, N, D, w)) reach = nullptr;
     const float* seen = dkv_split ? nullptr : reach;
     if (some_split && reach != nullptr) {
-        rowdot(std::true_type{}, reach, dq_split && !one_launch ? kKernDq : kKernDkv);  // (recorded with the pass that it is for)
+        rowdot_reach(std::true_type{}, reach, dq_split && !one_launch ? kKernDq : kKernDkv);  // (recorded with the pass that it is for)
         args.reach = reach;
     }
     if (one_launch) {
@@ -1212,7 +1237,13 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     if (dq_split) {
         if (hipError_t e = bwd_dq_split_bf16(dq_split, args, D, s)) return e;
     } else if (!some_split || reach == nullptr) {
-        rowdot(std::false_type{}, reach, kKernRowDot);
+        if (reach != nullptr) {
+            rowdot_reach(std::false_type{}, reach, kKernRowDot);
+        } else {
+            constexpr int kRows = 256 / (D / 8) * (D / 64);
+            ProfScope prof(kKernRowDot, s);
+            hipLaunchKernelGGL((rowdot_bf16_kernel<D>), dim3((unsigned)((rows + kRows - 1) / kRows)), dim3(256), 0, s, args.O, args.dO, Dv, (long)rows);
+        }
     }
     if (dkv_split) {
         if (hipError_t e = bwd_dkv_split_bf16(args, D, s)) return e;
