@@ -22,6 +22,7 @@ SHAPES = [
     (1, 6, 3, 5251, 64, 5251, "bf16", 0.5),      # causal, split, the gate fast: most of every band is erased
     (1, 2, 2, 20000, 128, 12000, "bf16", -2.0),  # blocks of 256 keys, more than 64 key tiles of 128 in a window
     (2, 24, 24, 2048, 128, 1024, "bf16", -1.5),
+    (1, 12, 2, 2500, 64, 1500, "bf16", -1.0),    # six query heads to a key/value head: more than the norms' launch takes at once
     (1, 8, 4, 2177, 128, 1600, "f32", -1.0),     # fp32: a last tile of one row
     (1, 8, 8, 4100, 64, 3000, "f32", -0.5),
 ]
@@ -87,8 +88,35 @@ def test_erased_bands(g, oracle, B, H, Hkv, N, d, w, dtype, mu, kind, keep):
     check_grads({k: got[k].reshape(ref[k].shape) for k in ("dQ", "dK", "dV", "dalpha")}, ref, 1e-2 if dtype == "bf16" else 1e-5, kind)
 
 
+@pytest.mark.parametrize("which", ["V", "dO"])
+@pytest.mark.parametrize("B,H,Hkv,N,d,w,dtype,mu", [SHAPES[0], SHAPES[1], SHAPES[2], SHAPES[7], SHAPES[8]])
+def test_far_rows_that_outweigh_their_decay(g, oracle, B, H, Hkv, N, d, w, dtype, mu, which):
+    # one row of 2^58 with small scores: a weight of 2^-58 and less still makes half of an output, so its block must not be left out where
+    # blocks of ordinary rows are (from 2^-48 on)
+    note("outweigh", which, B, H, Hkv, N, d, w, dtype, mu)
+    wl, ins = inputs(B, H, Hkv, N, d, w, dtype, mu)
+    for t in ("Q", "K"):
+        ins[t] = gi.round_to_bf16(ins[t] * np.float32(0.25)) if dtype == "bf16" else ins[t] * np.float32(0.25)
+    at = N // 8 if which == "V" else N - N // 8
+    ins[which][:, :, at] *= np.float32(2.0 ** 58)
+    c32 = oracle.gate_prefix(ins["alpha"]).astype(np.float32)
+    out = step(g, wl, ins, dev(c32, "f32"), True)
+    hs = slice(0, H // Hkv)
+    Q, dO, c = (x[:1, hs] for x in (ins["Q"], ins["dO"], c32))
+    K, V = ins["K"][:1, :1], ins["V"][:1, :1]
+    O_ref, _ = oracle.forward_gqa_from_c(Q, K, V, c, w, wl.scale)
+    if which == "V":
+        got, want = host(out["O"])[:1, hs].reshape(O_ref.shape), O_ref
+    else:
+        got = host(out["dV"])[:1, :1]
+        want = oracle.backward_gqa_from_c(Q, K, V, c, dO, w, wl.scale, O_saved=host(out["O"])[:1, hs])["dV"].reshape(got.shape)
+    # every row against its own size: bf16 probabilities and outputs; the fp32 difference of gates up to 2^7 in an exponent (2^-24 2^7 1.44)
+    err = np.linalg.norm(got - want, axis=-1) / np.linalg.norm(want, axis=-1)
+    assert err.max() <= (1e-2 if dtype == "bf16" else 5e-5), err.max()
+
+
 @pytest.mark.parametrize("which,value", [("V", np.inf), ("K", np.nan), ("dO", np.nan), ("Q", np.inf)])
-@pytest.mark.parametrize("B,H,Hkv,N,d,w,dtype,mu", [SHAPES[0], SHAPES[1], SHAPES[2], SHAPES[6]])
+@pytest.mark.parametrize("B,H,Hkv,N,d,w,dtype,mu", [SHAPES[0], SHAPES[1], SHAPES[2], SHAPES[7]])
 def test_far_rows_that_are_not_finite(g, oracle, B, H, Hkv, N, d, w, dtype, mu, which, value):
     # zero times infinity is NaN: a row that is not finite reaches every row that has it in its window, erased or not
     note("not finite", which, B, H, Hkv, N, d, w, dtype)
