@@ -412,8 +412,13 @@ static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const 
 // filled to 0.58: 99 against 91; H4 N11226 w6064, 0.50: 116 against 156).
 // Sequences shorter than a step's tile are the split kernel's, and there 64 queries are the better than 32 (d = 64, 512 x 4
 // heads of 50: 13.7, 28.0 us).
-// Inside the split kernel: one 32-query block per workgroup while that gives few workgroups (at d = 128 its
-// single-buffered tiles only pay for short bands), 128 queries where the band is long enough to share out: at d = 64 from 2560 on
+// Inside the split kernel: one 32-query block per workgroup while that gives few workgroups, at d = 128, whose tiles are single-buffered, up
+// to two and a half a CU for short bands and one and a half for long ones, which four waves share out better than 64 or 128 queries do
+// (us, 32 / what 64 or 128 queries take: H1 N2100 w1300 15.0 / 20.7, w1800 18.5 / 25.9 and 32.6, H1 N8000 w1300 17.3 / 21.7, H4 N3000 w1800
+// 22.9 / 26.6 and 33.6, causal 33.2 / 39.1 and 46.3; H3 N4096 w1300, at one and a half, 26.7 / 23.9); above, of even heads, 64 before 128 up to
+// two and a quarter (H8 N2100 w1800 27.3 / 33.7, H2 N8000 w4096 53.1 / 63.6; H3 N6000 w1800 38.9 / 36.8, H6 N4096 w1800 39.9 / 36.8).  At
+// d = 64 nearly causal bands from 1500 on take 32 up to three a CU (H8 N3000 22.6 / 30.7, H12 N2100 18.5 / 21.4, H4 N6000 w4096 36.8 / 43.9).
+// 128 queries where the band is long enough to share out: at d = 64 from 2560 on
 // (H15 N4000 causal: 48.5 against 71.7 us with 64; H12 N4000 w2000 38.6 against 31.4), and from 1500 on, near one tile a CU and with
 // uneven bands, for heads that are no multiple of four, above all odd ones: consecutive workgroups are consecutive heads, so that every XCD
 // reads the keys of all of them, half as often with 128 queries (B3 H9 N1855 causal 27.2 against 33.4, B7 H3 N2175 27.1, 36.3, H11 N3968
@@ -429,7 +434,11 @@ static FwdSplit fwd_split_shape(int BH, int N, int d, int w) {
     if (d == 128 && band <= 1024 && band >= (N >= 4096 ? 64 : 128)) filled |= ratio >= 0.85 && tiles <= cus;
     if (d == 128 && band <= 1024 && band >= 128 && N > 192 && fwd_by_length<128, 2>(BH, tiles, N, w)) filled |= ratio >= 0.9 && tiles <= 2 * cus;
     if (N >= 32 * (d == 64 ? kFwdBlocks<64> : kFwdBlocks<128>) && filled) return kFwdSplitNone;
-    if ((long)BH * ((N + 31) / 32) <= 5 * cus / 2 && (d == 64 || band <= 1024)) return kFwdSplitNarrow;
+    const long blocks = (long)BH * ((N + 31) / 32);
+    if (blocks <= 5 * cus / 2 && (d == 64 || band <= 1024)) return kFwdSplitNarrow;
+    if (d == 128 && (band > 1500 ? 5 * blocks <= 8 * cus : 2 * blocks < 3 * cus)) return kFwdSplitNarrow;
+    if (d == 64 && band >= 1500 && 4 * band >= 3L * N && 8 * blocks <= 25 * cus) return kFwdSplitNarrow;
+    if (d == 128 && BH % 2 == 0 && 4 * blocks <= 9 * cus) return kFwdSplitMid;
     const bool uneven = BH % 2 != 0 ? 5L * w >= 2L * N : BH % 4 != 0 && 4L * w >= 3L * N;
     const bool wide = d == 128 || (uneven && ratio >= 0.6 && ratio <= 1.25);
     return band > (wide ? 1500 : 2560) ? kFwdSplitWide : kFwdSplitMid;
