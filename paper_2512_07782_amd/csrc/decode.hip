@@ -21,6 +21,7 @@ namespace gfwa {
 
 constexpr int kDecChunk = 256;  // a chunk is a multiple of this many keys
 constexpr float kDecNegBig = -1.0e30f;
+constexpr size_t kDecOnceBytes = (size_t)24 << 20;
 
 __device__ __forceinline__ void load8(const bf16_t* p, float (&x)[8]) {
     const bf16x8 v = *reinterpret_cast<const bf16x8*>(p);
@@ -42,7 +43,8 @@ __host__ __device__ constexpr int dec_record(int D) { return D + 2; }
 // ONCE: no other workgroup reads them, so bf16 loads are non-temporal.  A cache that holds nothing of the window yet is then read faster (us,
 // three states in turn: B64 H32/8 N16384 d128 w1024 63 -> 57, H32/32 213 -> 174, B16 H32/8 w4096 57 -> 52, B4 H32/8 w1024 12.4 -> 12.4), one that
 // the memory-side cache still holds in full more slowly (the first 52 -> 56): a program reads its other layers in between.  fp32 gains nothing
-// (B16 H32/32 w1024 99 -> 101) and loads as before.
+// (B16 H32/32 w1024 99 -> 101) and loads as before, and so do windows of less than 24 MiB in all, which the L2s may still hold (B26 H2 N1744
+// d128 w992, 26 MB, 9.3 -> 9.0; B4 H8 N13281 d64 w1384, 11 MB, 9.0 -> 10.4).
 template <typename T>
 struct Raw8;
 template <>
@@ -418,6 +420,7 @@ static hipError_t launch_decode(const T* q, const T* Kc, const T* Vc, float* c, 
     if (S > max_splits) S = max_splits;
     const int chunk = ((span + S - 1) / S + kDecChunk - 1) / kDecChunk * kDecChunk;
     S = (span + chunk - 1) / chunk;
+    const bool once = kShort && G == GT && (size_t)B * Hkv * span * D * 2 * sizeof(T) > kDecOnceBytes;
     {
         ProfScope prof(kKernDecode, s);
         auto launch = [&](auto gt, auto nw) {
@@ -426,7 +429,7 @@ static hipError_t launch_decode(const T* q, const T* Kc, const T* Vc, float* c, 
                                    dim3((unsigned)(items * S)), dim3(64 * decltype(nw)::value), 0, s, q, Kc, Vc, c, alpha_t, pos, part,
                                    o, L, H, G, Tlen, w, scale, S, chunk);
             };
-            if (kShort && G == GT) as(std::integral_constant<bool, kShort>{});
+            if (once) as(std::integral_constant<bool, kShort>{});
             else as(std::integral_constant<bool, false>{});
         };
         auto with_heads = [&](auto nw) {

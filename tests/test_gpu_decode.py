@@ -215,10 +215,10 @@ def test_decode_clamps_positions_outside_the_cache(g, oracle):
     assert torch.equal(o1, o2) and torch.equal(L1, L2)
 
 
-@pytest.mark.parametrize("B,Hkv,G,T,d,w", [(1, 2, 4, 700, 128, 300), (2, 1, 2, 1025, 64, 1025), (1, 3, 3, 50, 128, 17), (1, 2, 4, 5000, 64, 4097)])
+@pytest.mark.parametrize("B,Hkv,G,T,d,w", [(1, 2, 4, 700, 128, 300), (2, 1, 2, 1025, 64, 1025), (1, 3, 3, 50, 128, 17), (1, 2, 4, 5000, 64, 4097), (1, 3, 4, 5000, 128, 4200)])
 def test_decode_reads_shared_and_own_rows_alike(g, B, Hkv, G, T, d, w):
-    """Rows that one workgroup alone reads are loaded past the caches, shared ones are not: few heads, so that every
-    workgroup takes a single one in both layouts and the sums are the same bit for bit."""
+    """Rows that one workgroup alone reads are loaded past the caches where the windows are large (the last case), shared ones are not:
+    few heads, so that every workgroup takes a single one in both layouts and the sums are the same bit for bit."""
     gen = torch.Generator(device=DEV).manual_seed(T)
     q, Kc, Vc = (torch.randn(s, generator=gen, device=DEV, dtype=torch.bfloat16)
                  for s in ((B, Hkv * G, d), (B, Hkv, T, d), (B, Hkv, T, d)))
