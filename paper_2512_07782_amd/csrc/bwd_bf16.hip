@@ -45,10 +45,16 @@ constexpr float kPosBig = 1.0e30f;
 // other side for themselves: K and V as well.  reach: dalpha.
 template <int LPR>
 __device__ __forceinline__ float row_dot(const bf16x8& a, const bf16x8& b) {
+    auto moved = [](float v, auto ctrl) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), decltype(ctrl)::value, 0xF, 0xF, true));
+    };
     float x = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) x = fmaf((float)a[e], (float)b[e], x);
-    return row_sum<LPR>(x);
+    if (LPR == 16) x += moved(x, std::integral_constant<int, 0x128>{});  // the lane 8 further on (row_ror),
+    x += moved(moved(x, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{});  // lane ^ 4 (mirrored twice),
+    x += moved(x, std::integral_constant<int, 0x4E>{});  // lane ^ 2,
+    return x + moved(x, std::integral_constant<int, 0xB1>{});  // lane ^ 1
 }
 // D alone, where nothing is asked: smaller workgroups over all rows (B8 H60 N1003 d128, us: in the kernel below without its look 44.7, here 42.0).
 template <int D>
