@@ -22,13 +22,17 @@
 //
 // Measured, us, whole bands / shortened, the pass for the norms included; gates of softplus(N(mu, 1)):
 //                                        mu        -3           -2           -1
-//   forward   B4 H16   N8192 d128 w1024        322 / 327    301 / 266    293 / 201
-//             B1 H32/8 N8192 d128 w4096        378 / 220    372 / 131    373 / 100
-//             B4 H16   N4096 d64  causal       154 / 118    150 /  79    153 /  59
-//   backward  B4 H16   N8192 d128 w1024       1197 /1195   1061 / 835   1043 / 619
-//             B1 H32/8 N8192 d128 w4096       1427 / 670   1399 / 386   1390 / 269
-//             B4 H16/4 N4096 d64  causal       575 / 347    555 / 200    552 / 133
-//   fp32, whole step  B2 H16 N4096 d128 w1024              1430 /1082   1430 / 745
+//   forward   B4 H16   N8192  d128 w1024       301 / 294    291 / 212    286 / 180
+//             B1 H32   N16384 d128 w1024       314 / 300    304 / 217    302 / 185
+//             B1 H32/8 N8192  d128 w4096       361 / 136    354 /  90    350 /  72
+//             B4 H16   N4096  d64  causal      144 /  78    139 /  60    140 /  52
+//             B2 H16   N4096  d128 w1024 fp32  351 / 324    353 / 226    353 / 181
+//   backward  B4 H16   N8192  d128 w1024      1053 / 865   1016 / 613   1008 / 510
+//             B1 H32   N16384 d128 w1024      1084 / 867   1059 / 618   1025 / 517
+//             B1 H32/8 N8192  d128 w4096      1381 / 390   1366 / 257   1354 / 205
+//             B4 H16/4 N4096  d64  causal      547 / 203    537 / 133    531 / 102
+//             B4 H16/4 N4096  d64  w512        158 / 159    157 / 130    152 / 103
+//             B2 H16   N4096  d128 w1024 fp32 1109 / 878   1075 / 561   1043 / 417
 #pragma once
 #include <initializer_list>
 #include <type_traits>

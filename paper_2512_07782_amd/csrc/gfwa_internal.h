@@ -38,6 +38,7 @@ double query_tile_fill(int BH, int N, int w, long slots);  // how full rounds of
 struct KeyReach {
     int block, few;
 };
+bool key_reach_looks(int B, int H, int Hkv, int N, int d, int w, bool bf16);  // whether it would
 hipError_t key_reach(KeyReach& reach, int tile, bool bf16, const void* Q, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv,
                      int N, int d, int w, float scale, hipStream_t s);
 enum FwdSplit { kFwdSplitNone = 0, kFwdSplitNarrow, kFwdSplitMid, kFwdSplitWide };  // 32, 64, 128 queries per workgroup

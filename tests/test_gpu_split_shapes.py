@@ -12,7 +12,9 @@ g = par.g
 
 # 32, 64, 128 queries to a workgroup at d = 128 (32-query blocks: one and a half and two and a quarter to a CU of 256, odd heads), then d = 64
 @pytest.mark.parametrize("B,H,N,d,w", [(1, 1, 2101, 128, 1801), (1, 3, 4065, 128, 1025), (1, 2, 6550, 128, 1700), (1, 2, 8000, 128, 1600),
-                                       (1, 3, 6001, 128, 1501), (1, 8, 3000, 64, 2400), (1, 8, 3001, 64, 2200)])
+                                       (1, 3, 6001, 128, 1501), (1, 6, 5990, 128, 1300), (1, 12, 2099, 128, 1800),
+                                       (1, 12, 2900, 128, 2900), (1, 12, 3010, 128, 3010), (1, 12, 3010, 64, 3010),
+                                       (1, 8, 3000, 64, 2400), (1, 8, 3001, 64, 2200)])
 def test_forward_of_long_bands(g, oracle, B, H, N, d, w):
     note("long bands", B, H, N, d, w)
     wl = gi.custom("long", B, H, N, d, w, alpha_mu=-6.0, index=23)
