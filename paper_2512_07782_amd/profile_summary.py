@@ -40,7 +40,7 @@ LIB = {
     "segment_sum_kernel<false, 0>": "scan_segment_sum",
     "scan_rows_kernel<false, 0>": "gate_prefix_scan",
     "fwd_bf16_kernel<128>": "forward",
-    "rowdot_bf16_kernel<128>": "bwd_rowdot",
+    "rowdot_bf16_kernel<128>": "bwd_rowdot", "rowdot_reach_bf16_kernel": "bwd_rowdot", "rowdot_reach_f32_kernel": "bwd_rowdot",
     "bwd_dkv8_bf16_kernel<128, true>": "bwd_dkv",
     "bwd_dq_spill_bf16_kernel<128>": "bwd_dq",
     "segment_sum_kernel<true, 1>": "gate_grad_segment_sum",
@@ -74,7 +74,23 @@ def lib_name(kernel: str):
     return None
 
 
+def readable(name: str) -> str:
+    """A mangled name (the profiler leaves those with bf16 among their types as they are) of a kernel template as name<arguments>."""
+    m = re.match(r"_ZN4gfwa(\d+)", name)
+    if not m:
+        return name
+    base, rest = name[m.end():m.end() + int(m.group(1))], name[m.end() + int(m.group(1)):]
+    args = []
+    if rest.startswith("I"):
+        rest = rest[1:]
+        while (a := re.match(r"Li(\d+)E|Lb([01])E|(DF16b)|(f)", rest)) is not None:
+            args.append(a.group(1) or (a.group(2) and ("false", "true")[int(a.group(2))]) or ("bf16" if a.group(3) else "float"))
+            rest = rest[a.end():]
+    return f"gfwa::{base}<{', '.join(args)}>" if args else f"gfwa::{base}"
+
+
 def short(name: str) -> str:
+    name = readable(name)
     m = re.search(r"gfwa::(\w+<[^>]*>)", name)
     if m:
         return m.group(1)

@@ -63,3 +63,10 @@ def test_kernel_trace_and_sq_counters(tmp_path):
     assert [float(x) for x in busy[-3:]] == [0.4, 0.4, 0.4]          # 16 * 25 / 1000
     valu = [l for l in text.splitlines() if l.strip().startswith("of which VALU")][0].split()
     assert [float(x) for x in valu[-3:]] == [4.0, 4.0, 4.0]          # (125 - 25) / 25
+
+
+def test_names_that_the_profiler_leaves_mangled():
+    name = "_ZN4gfwa20bwd_dkv8_bf16_kernelILi128ELb0EEEvPKDF16bS2_S2_PKfS4_PDF16bS5_PfS6_Pciifii"
+    assert ps.short(name) == "bwd_dkv8_bf16_kernel<128, false>" and ps.lib_name(ps.short(name)) == "bwd_dkv"
+    assert ps.short("_ZN4gfwa16key_reach_kernelILi64EDF16bEEvPKT0_S3_PKfPS1_iiii") == "key_reach_kernel<64, bf16>"
+    assert ps.short(K["fwd"]) == "fwd_bf16_kernel<128>"
