@@ -127,7 +127,7 @@ __global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __re
                                                                  const float* __restrict__ b,
                                                                  float* __restrict__ out, int N, float eps,
                                                                  const double* __restrict__ partial,
-                                                                 int seg_len, int P) {
+                                                                 int seg_len, int P, bool by_runs) {
     constexpr int RUNS = kScanRuns / WAVES;
     __shared__ double wave_tot[2][WAVES];
     const int seg = (int)(blockIdx.x % P);
@@ -150,7 +150,9 @@ __global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __re
         double acc = 0.0;
         for (int q = lane; q < seg; q += 64) acc += pr[q];
         carry = wave_sum(acc);
-    } else if (seg > 0) {  // of its elements, fp32 over four, fp64 across (as segment_sum_kernel)
+    } else if (seg > 0) {
+        // of its elements: fp32 over four and fp64 across, as segment_sum_kernel, or (by_runs) fp32 over runs and fp64 across, as a whole row
+        // in one workgroup, so that either call's prefix does not depend on the way it is formed
         double acc = 0.0;
         constexpr int U = 4 / RUNS > 1 ? 4 / RUNS : 1;  // chunks in flight
         for (int base = 0; base < begin; base += U * kScanChunk) {
@@ -165,10 +167,11 @@ __global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __re
                 for (int r = 0; r < RUNS; ++r) {
                     float v[4];
                     q[u][r].values(v, eps, run_start<WAVES>(base + u * kScanChunk, wv, r, lane), begin);
-                    acc += (double)((v[0] + v[1]) + (v[2] + v[3]));
+                    if (by_runs) acc += (double)lane_value(wave_scan(((v[0] + v[1]) + v[2]) + v[3]), 63);
+                    else acc += (double)((v[0] + v[1]) + (v[2] + v[3]));
                 }
         }
-        acc = wave_sum(acc);
+        if (!by_runs) acc = wave_sum(acc);
         if (lane == 0) wave_tot[1][wv] = acc;
         __syncthreads();
 #pragma unroll
@@ -278,6 +281,8 @@ static bool scan_four_waves(bool activation, bool segment, long workgroups, int 
 //   plain       4.5 / 8.1 / 4.1   5.4 / 8.0 / 4.3  9.3 / 8.1 / 6.1  17.1 / 8.1 / 9.9   5.0 / 8.4 / 4.3   5.9 / 8.4 / 4.6   7.9 / 8.5 / 5.8  10.0 / 8.6 /  8.2
 //   activation  5.8 / 8.1 / 5.7   7.2 / 8.1 / 6.2 12.7 / 8.1 / 9.6  23.7 / 8.2 / 15.9  6.3 / 8.4 / 6.2   7.7 / 8.5 / 6.8  10.5 / 8.6 / 9.6  13.5 / 8.8 / 14.9
 // (96 rows of 16384, 384 segments: 6.5 / 8.9 / 6.8, 8.3 / 10.5 / 13.4.)
+// (With the sums by runs, which the prefix without a workspace keeps: 1 row of 65536 14.0, 32 rows of 16384 5.2, 8 of 32768 7.9; 17.2, 6.8, 10.2 with the
+// activation; 17.4, 5.8, 9.5 and 24.0, 7.6, 12.9 in one workgroup a row.)
 static bool scan_rows_alone(bool activation, int rows, int N) {
     const int P = (N + kScanChunk - 1) / kScanChunk;
     return P >= 3 && P <= 16 && (activation ? 4 : 3) * (long)rows * P <= 3L * device_cu_count();
@@ -288,7 +293,7 @@ static bool scan_in_two_launches(bool activation, int rows, int N) {
 }
 template <bool REVERSE, int MODE>
 static void launch_scan(const float* a, const float* b, float* out, int rows, int N, float eps, const double* partial, int seg_len,
-                        int P, hipStream_t s) {
+                        int P, bool by_runs, hipStream_t s) {
     if (partial == nullptr) {
         // (out over an input: the segments behind still need what the ones in front overwrite)
         const size_t bytes = (size_t)rows * N * sizeof(float);
@@ -298,9 +303,9 @@ static void launch_scan(const float* a, const float* b, float* out, int rows, in
     }
     const unsigned wgs = (unsigned)(rows * P);
     if (scan_four_waves(MODE == kScanGate, P > 1, wgs, seg_len))
-        hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 4>), dim3(wgs), dim3(256), 0, s, a, b, out, N, eps, partial, seg_len, P);
+        hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 4>), dim3(wgs), dim3(256), 0, s, a, b, out, N, eps, partial, seg_len, P, by_runs);
     else
-        hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 16>), dim3(wgs), dim3(1024), 0, s, a, b, out, N, eps, partial, seg_len, P);
+        hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 16>), dim3(wgs), dim3(1024), 0, s, a, b, out, N, eps, partial, seg_len, P, by_runs);
 }
 template <bool REVERSE, int MODE>
 static void launch_segment_sum(const float* a, const float* b, double* partial, int rows, int N, float eps, int seg_len, int P, hipStream_t s) {
@@ -313,14 +318,14 @@ static void launch_segment_sum(const float* a, const float* b, double* partial, 
 
 hipError_t gate_prefix(const float* alpha, float* c, int rows, int N, hipStream_t s) {
     ProfScope prof(kKernGatePrefix, s);
-    launch_scan<false, kScanPlain>(alpha, nullptr, c, rows, N, 0.f, nullptr, 0, 1, s);
+    launch_scan<false, kScanPlain>(alpha, nullptr, c, rows, N, 0.f, nullptr, 0, 1, true, s);
     return hipGetLastError();
 }
 
 hipError_t gate_activation_prefix(const float* hpre, const float* beta, float eps, float* c, int rows, int N,
                                   hipStream_t s) {
     ProfScope prof(kKernGateActPrefix, s);
-    launch_scan<false, kScanGate>(hpre, beta, c, rows, N, eps, nullptr, 0, 1, s);
+    launch_scan<false, kScanGate>(hpre, beta, c, rows, N, eps, nullptr, 0, 1, true, s);
     return hipGetLastError();
 }
 
@@ -341,8 +346,12 @@ size_t gate_scan_workspace_bytes(int rows, int N) {
 
 hipError_t gate_prefix_stp(const float* in, const float* beta, float eps, float* c, double* partial, int rows,
                            int N, hipStream_t s) {
-    if (!scan_in_two_launches(beta != nullptr, rows, N))
-        return beta != nullptr ? gate_activation_prefix(in, beta, eps, c, rows, N, s) : gate_prefix(in, c, rows, N, s);
+    if (!scan_in_two_launches(beta != nullptr, rows, N)) {
+        ProfScope prof(beta != nullptr ? kKernGateActPrefix : kKernGatePrefix, s);
+        if (beta != nullptr) launch_scan<false, kScanGate>(in, beta, c, rows, N, eps, nullptr, 0, 1, false, s);
+        else launch_scan<false, kScanPlain>(in, nullptr, c, rows, N, 0.f, nullptr, 0, 1, false, s);
+        return hipGetLastError();
+    }
     int seg_len = 0;
     const int P = scan_segments(rows, N, &seg_len);
     {
@@ -352,8 +361,8 @@ hipError_t gate_prefix_stp(const float* in, const float* beta, float eps, float*
     }
     {
         ProfScope prof(kKernScanPropagate, s);
-        if (beta != nullptr) launch_scan<false, kScanGate>(in, beta, c, rows, N, eps, partial, seg_len, P, s);
-        else launch_scan<false, kScanPlain>(in, beta, c, rows, N, eps, partial, seg_len, P, s);
+        if (beta != nullptr) launch_scan<false, kScanGate>(in, beta, c, rows, N, eps, partial, seg_len, P, false, s);
+        else launch_scan<false, kScanPlain>(in, beta, c, rows, N, eps, partial, seg_len, P, false, s);
     }
     return hipGetLastError();
 }
@@ -427,11 +436,11 @@ hipError_t gate_grad_scan(const float* dc_col, const float* dc_row, float* dalph
             launch_segment_sum<true, kScanDiff>(dc_col, dc_row, partial, rows, N, 0.f, seg_len, P, s);
         }
         ProfScope prof(kKernGateGrad, s);
-        launch_scan<true, kScanDiff>(dc_col, dc_row, dalpha, rows, N, 0.f, partial, seg_len, P, s);
+        launch_scan<true, kScanDiff>(dc_col, dc_row, dalpha, rows, N, 0.f, partial, seg_len, P, false, s);
         return hipGetLastError();
     }
     ProfScope prof(kKernGateGrad, s);
-    launch_scan<true, kScanDiff>(dc_col, dc_row, dalpha, rows, N, 0.f, nullptr, 0, 1, s);
+    launch_scan<true, kScanDiff>(dc_col, dc_row, dalpha, rows, N, 0.f, nullptr, 0, 1, false, s);
     return hipGetLastError();
 }
 
