@@ -423,14 +423,9 @@ static hipError_t launch_fwd(const void* Q, const void* K, const void* V, const 
 // uneven bands, for heads that are no multiple of four, above all odd ones: consecutive workgroups are consecutive heads, so that every XCD
 // reads the keys of all of them, half as often with 128 queries (B3 H9 N1855 causal 27.2 against 33.4, B7 H3 N2175 27.1, 36.3, H11 N3968
 // w2459 35.4, 46.6; B2 H16/4 N1806 30.0, 25.6; B2 H18/9 N1517 24.8, 21.9; H6/3 N7231 w2373 52.4, 40.7; H7 N6799 w1618 45.3, 37.2).
-// Where the gate is looked at (key_reach) and there are many tiles, the whole-tile kernel (64 queries at d = 64) before 128 split queries: what
-// gates of the usual kind leave of a long band is short.  us, this / 128 queries, gates softplus(N(mu, 1)) of mu = -2, -3 and -6, which erases
-// nothing: H6 N6000 d128 w2500 31 / 39, 36 / 45, 58 / 53; H12 N6000 d128 w4096 44 / 60, 57 / 72, 124 / 121; H20 N3000 d128 causal 36 / 45, 47 / 56,
-// 66 / 63; H12 N4096 d64 causal 23 / 30, 29 / 37, 45 / 44.  Where it is not, 64 of even heads before 128 at d = 128 (H12 N2100 w1800 28.9 / 33.9).
-// Bands of 1024 to 1500 in sequences of three and more of them go whole from two and three quarters a CU on (H6 N6000 w1300 30 / 35 split, whole
-// bands 39 / 56; H3 N8000 26 / 28, 32 / 42; H16 N2100 30 / 26).
-static FwdSplit fwd_split_shape(int B, int H, int Hkv, int N, int d, int w) {
-    const int BH = B * H;
+// Bands of 1024 to 1500 in sequences of three and more of them go whole from two and three quarters a CU on (H6 N6000 w1300 37 / 56 split, H3 N8000
+// 30 / 40; H16 N2100 30 / 27, H8 N4096 30 / 31).
+static FwdSplit fwd_split_shape(int BH, int N, int d, int w) {
     const long cus = device_cu_count(), band = w < N ? w : N;
     long longest;
     const double ratio = query_tile_steps(BH, N, w, longest) / ((double)cus * (double)longest);
@@ -449,10 +444,7 @@ static FwdSplit fwd_split_shape(int B, int H, int Hkv, int N, int d, int w) {
     if (d == 128 && band > 1024 && band <= 1500 && N >= 3 * band && 4 * blocks >= 11 * cus) return kFwdSplitNone;
     const bool uneven = BH % 2 != 0 ? 5L * w >= 2L * N : BH % 4 != 0 && 4L * w >= 3L * N;
     const bool wide = d == 128 || (uneven && ratio >= 0.6 && ratio <= 1.25);
-    if (band <= (wide ? 1500 : 2560)) return kFwdSplitMid;
-    if (!key_reach_looks(B, H, Hkv, N, d, w, true)) return d == 128 && BH % 2 == 0 ? kFwdSplitMid : kFwdSplitWide;
-    if (3 * blocks < 13 * cus) return kFwdSplitWide;
-    return d == 128 ? kFwdSplitNone : kFwdSplitMid;
+    return band > (wide ? 1500 : 2560) ? kFwdSplitWide : kFwdSplitMid;
 }
 
 hipError_t forward_bf16(const void* Q, const void* K, const void* V, const float* c, void* O, float* L,
@@ -467,7 +459,7 @@ hipError_t forward_bf16(const void* Q, const void* K, const void* V, const float
         return forward_bf16(from(Q, rows), from(K, keys), from(V, keys), c + rows, (char*)O + rows * d * sizeof(bf16_t), L + rows,
                             kv > 1 ? kv - kv0 : 1, kv > 1 ? G : G - g0, 1, N, d, w, scale, s);
     }
-    if (const FwdSplit shape = fwd_split_shape(B, H, Hkv, N, d, w))
+    if (const FwdSplit shape = fwd_split_shape(B * H, N, d, w))
         return forward_split_bf16(shape, Q, K, V, c, O, L, B, H, Hkv, N, d, w, scale, s);
     if (d == 64) return launch_fwd<64>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);
     return launch_fwd<128>(Q, K, V, c, O, L, B, H, Hkv, N, w, scale, s);

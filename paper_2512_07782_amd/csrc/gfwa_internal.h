@@ -32,18 +32,17 @@ hipError_t forward_bf16(const void* Q, const void* K, const void* V, const float
                         int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
 double query_tile_fill(int BH, int N, int w, long slots);  // how full rounds of `slots` 128-query tiles are, 0 .. 1
 // The same for few or uneven query tiles, the band of a tile split over groups of waves (fwd_split_bf16.hip).
+enum FwdSplit { kFwdSplitNone = 0, kFwdSplitNarrow, kFwdSplitMid, kFwdSplitWide };  // 32, 64, 128 queries per workgroup
+hipError_t forward_split_bf16(FwdSplit shape, const void* Q, const void* K, const void* V, const float* c, void* O,
+                              float* L, int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
 // Values of the key blocks in front of the forward's query tiles (band_reach.h), in O.
 // key_reach: launches the pass for tiles of `tile` queries if it pays, and says by what blocks (0: it does not) and how many keys have to be
 // erased for reading their norms to pay.
 struct KeyReach {
     int block, few;
 };
-bool key_reach_looks(int B, int H, int Hkv, int N, int d, int w, bool bf16);  // whether it would
 hipError_t key_reach(KeyReach& reach, int tile, bool bf16, const void* Q, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv,
                      int N, int d, int w, float scale, hipStream_t s);
-enum FwdSplit { kFwdSplitNone = 0, kFwdSplitNarrow, kFwdSplitMid, kFwdSplitWide };  // 32, 64, 128 queries per workgroup
-hipError_t forward_split_bf16(FwdSplit shape, const void* Q, const void* K, const void* V, const float* c, void* O,
-                              float* L, int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
 hipError_t forward_f32(const float* Q, const float* K, const float* V, const float* c, float* O,
                        float* L, int B, int H, int Hkv, int N, int d, int w, float scale, hipStream_t s);
 

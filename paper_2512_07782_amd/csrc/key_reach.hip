@@ -107,8 +107,6 @@ static KeyReach reach_of(int B, int H, int Hkv, int N, int d, int w, bool bf16) 
     return {(int)block, (int)few};
 }
 
-bool key_reach_looks(int B, int H, int Hkv, int N, int d, int w, bool bf16) { return reach_of(B, H, Hkv, N, d, w, bf16).block != 0; }
-
 template <int D, typename T>
 static void launch(KeyReach reach, int tile, const void* K, const void* V, const float* c, void* O, int B, int H, int Hkv, int N, int w, hipStream_t s) {
     const int blocks = (N + reach.block - 1) / reach.block;
