@@ -1,13 +1,16 @@
 // How far the band of a tile reaches before the gate has erased it.
 //
 // The gate's decay grows along the band and soon outweighs what a score can add, which the norms bound: scale |q.k| <= scale |q| |k|.
-// A key whose score then lies below the reference of a row by more than the binary orders that an fp32 sum resolves has no part in it:
-//   kErased = 127  exp2 returns zero for every argument below -126 (the smallest normal number; measured over -120 .. -151), so the
-//                  probability is exactly zero and every product it enters is zero, whatever the values are
-//   kFaint = 48    and one more for every doubling by which the values that the weight would multiply outweigh those of rows close by
-//                  (outweighs): the weights left out add up to less than 2^-36 of the row's (4096 keys) in these terms, so a sum misses
-//                  less than 2^-36 of the values it is made of, 2^-12 of a rounding of fp32.
-// (softplus(N(-2, 1)) decays by 190 over 1024 keys, unit-variance rows of d = 128 have |q| |k| / sqrt(d) of 11 to 15: the far 750 keys are
+// A key whose score then lies more than 127 binary orders (kErased: 126, the smallest normal fp32 number, and one for the roundings of scores
+// and references) below the reference of a row has no part in it:
+//   backward  p = exp2(x - L) is exactly zero: exp2 returns zero for every argument below -126 (measured over -120 .. -151), and then every
+//             product it enters is zero.  No bit of a gradient changes.
+//   forward   the row's reference is at least the score of its own key.  Where the whole band is measured against it (whole-tile kernels of bf16)
+//             p is exactly zero again.  The split and the fp32 kernels form partial sums against references of their own first, in which far
+//             keys weigh more, and scale them afterwards; so the line moves on by the doublings of the largest value row there, and
+//             every product left out is below the smallest normal number by itself.
+// Nothing less will do: a weight of 2^-50 is all that a row has where the values close by are zero or their loss is masked.
+// (softplus(N(-2, 1)) decays by 190 over 1024 keys, unit-variance rows of d = 128 have |q| |k| / sqrt(d) of 11 to 15: the far 450 keys are
 // left out.)
 //
 // So a pass over the rows in front of the kernels takes the largest norm of every block of them, and a workgroup shortens its band, in front
@@ -20,19 +23,20 @@
 // The blocks' values travel in the rows of an output that is not written yet (O in front of the forward, dalpha in front of the
 // backward), so that no call needs more memory for them.
 //
-// Measured, us, whole bands / shortened, the pass for the norms included; gates of softplus(N(mu, 1)):
-//                                        mu        -3           -2           -1
-//   forward   B4 H16   N8192  d128 w1024       301 / 294    291 / 212    286 / 180
-//             B1 H32   N16384 d128 w1024       314 / 300    304 / 217    302 / 185
-//             B1 H32/8 N8192  d128 w4096       361 / 136    354 /  90    350 /  72
-//             B4 H16   N4096  d64  causal      144 /  78    139 /  60    140 /  52
-//             B2 H16   N4096  d128 w1024 fp32  351 / 324    353 / 226    353 / 181
-//   backward  B4 H16   N8192  d128 w1024      1053 / 865   1016 / 613   1008 / 510
-//             B1 H32   N16384 d128 w1024      1084 / 867   1059 / 618   1025 / 517
-//             B1 H32/8 N8192  d128 w4096      1381 / 390   1366 / 257   1354 / 205
-//             B4 H16/4 N4096  d64  causal      547 / 203    537 / 133    531 / 102
-//             B4 H16/4 N4096  d64  w512        158 / 159    157 / 130    152 / 103
-//             B2 H16   N4096  d128 w1024 fp32 1109 / 878   1075 / 561   1043 / 417
+// Measured, us, whole bands / shortened, the pass for the norms included; gates of softplus(N(mu, 1)), of which mu = -6 erases nothing:
+//                                        mu        -6            -3           -2           -1
+//   forward   B4 H16   N8192  d128 w1024       296 / 301     295 / 297    284 / 257    280 / 195
+//             B1 H32   N16384 d128 w1024       308 / 311     307 / 312    300 / 267    293 / 201
+//             B1 H32/8 N8192  d128 w4096       392 / 395     365 / 205    358 / 120    355 /  87
+//             B4 H16   N4096  d64  causal      154 / 157     146 / 113    142 /  75    140 /  57
+//             B1 H8    N5003  d128 w3000        52 /  55      52 /  56     52 /  46     53 /  39
+//             B2 H16   N4096  d128 w1024 fp32  345 / 348     345 / 348    348 / 298    347 / 210
+//   backward  B4 H16   N8192  d128 w1024       954 / 961     956 / 961    935 / 733    919 / 531
+//             B1 H32   N16384 d128 w1024       971 / 981     974 / 978    942 / 749    931 / 548
+//             B1 H32/8 N8192  d128 w4096      1320 / 1333   1268 / 590   1233 / 331   1230 / 229
+//             B4 H16/4 N4096  d64  causal      576 / 579     560 / 336    545 / 189    542 / 128
+//             B1 H8    N5003  d128 w3000       161 / 163     160 / 127    158 /  90    158 /  67
+//             B2 H16   N4096  d128 w1024 fp32 1122 / 1135   1129 / 1126  1084 / 789   1055 / 521
 #pragma once
 #include <initializer_list>
 #include <type_traits>
@@ -42,19 +46,13 @@
 
 namespace gfwa {
 
-// Base-2 exponents below which a weight counts for nothing, with 1 for the roundings of scores and references.
-constexpr float kErased = 127.f, kFaint = 49.f;
-// Doublings by which rows of squared norm `far` outweigh rows of `near` (at least 0; NaN or infinite: no line but kErased holds).
-__device__ __forceinline__ float outweighs(float far, float near) { return far <= near ? 0.f : 0.5f * (fast_log2(far) - fast_log2(near)); }
-// Whether it can pay to read norms: `decay` over the `len` rows that see a block (that it sees).  Scores of unit-variance rows add about
-// 15 to the 34 of kFaint (in units of the gate); `few` rows fewer have to be worth the reading: of one matrix of three in front of the backward,
+constexpr float kErased = 127.f;
+// Whether it can pay to read norms: `decay` over the `len` rows that see a block (that it sees).  Scores and values of unit-variance rows add about
+// 22 to the 88 of kErased (in units of the gate); `few` rows fewer have to be worth the reading: of one matrix of three in front of the backward,
 // of two in a launch of their own in front of the forward (key_reach.hip).  (Two products compared, so that two kernels which ask the same
 // always agree: there is nothing the compiler could fuse in one of them.)
-constexpr float kTypicalReach = 49.f;
-constexpr int kFewBackward = 128;
-// The whole-tile kernels of bf16 at d = 128 run one workgroup a CU, whose look nothing overlaps: whole bands / shortened, us, B4 H16 N4096 w256, where
-// mu = -1 (0.5) erases 130 (210) keys: 239 / 250 (237 / 234), at d = 64 117 / 115 (115 / 106).
-__host__ __device__ constexpr int few_backward(int d) { return d == 128 ? 192 : kFewBackward; }
+constexpr float kTypicalReach = 110.f;
+constexpr int kFewBackward = 192;
 __device__ __forceinline__ bool reach_pays(float decay, int len, int few) {
     return decay > kTypicalReach && decay * (float)(len - few) > kTypicalReach * (float)len;
 }
@@ -113,12 +111,8 @@ __device__ __forceinline__ int norm_bits(float n2) { return __float_as_int(n2) &
 // What a wave (or workgroup) knows of its own rows: the largest squared norm, times (scale log2 e)^2 and a thousandth for the
 // roundings of norms and products.
 __device__ __forceinline__ float reach2_of(int norm, float sl) { return __int_as_float(norm) * (sl * sl * 1.004f); }
-// room: what a score would have to exceed, in base-2 exponents, for a weight of 2^-kErased; heavier: doublings by which the values of the
-// block outweigh others (fminf: kErased for NaN)
-__device__ __forceinline__ bool is_erased(float n2, float reach2, float room, float heavier) {
-    room += kErased - fminf(kFaint + heavier, kErased);
-    return room > 0.f && n2 * reach2 < room * room;
-}
+// room: what a score would have to exceed, in base-2 exponents, for a weight of 2^-kErased
+__device__ __forceinline__ bool is_erased(float n2, float reach2, float room) { return room > 0.f && n2 * reach2 < room * room; }
 
 // ---- keys in front of a query tile (forward).  A tile of queries from q0 finds in its own rows of O, as entry e, what there is to know of the
 // block of `block` keys that is e + 1 blocks before the one that holds q0 (key_reach.hip): the largest squared norms of its key and of its
@@ -145,11 +139,11 @@ __device__ __forceinline__ KeyBlock key_block(const T* first, int rows, int lane
     return {there ? kb.norms : pack_norms(kInfBits, kInfBits), kb.c};
 }
 // First key that the 32 queries of a wave need.  reach2 and `lowest` of the wave (lowest: the lowest exponent, relative to gate cbase,
-// that a weight of a row is measured against, less kErased).  Values close by are those of entry 0.
+// that a weight of a row is measured against, less kErased).
 __device__ __forceinline__ int first_needed_key(const KeyBlock& kb, int q0, int k_lo, int block, float reach2, float lowest, float cbase, int lane) {
-    const int hi = q0 / block - 1, n = hi - k_lo / block + 1;  // (n <= 64, reach_of_forward sees to that)
-    const float near_v2 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(kb.v2())));
-    const bool kept = lane < n && !is_erased(kb.k2(), reach2, lowest - (kb.c - cbase) * kLog2e, outweighs(kb.v2(), near_v2));
+    const int hi = q0 / block - 1, n = hi - k_lo / block + 1;  // (n <= 64, reach_of sees to that)
+    const float doublings = fmaxf(0.f, 0.5f * fast_log2(kb.v2()));
+    const bool kept = lane < n && !is_erased(kb.k2(), reach2, lowest - (kb.c - cbase) * kLog2e - doublings);
     const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
     const int farthest = mask ? 63 - __builtin_clzll(mask) : -1;
     return max(k_lo, (hi - farthest) * block);
@@ -189,78 +183,59 @@ __device__ __forceinline__ int forward_reach(const bf16x8 (&q)[D / 16], const bf
 constexpr int kReachRows = 64;
 enum : int {
     kReachNorm,      // largest squared norm of its query rows (infinite: the block is kept), ..
-    kReachEdge,      // .. lowest (c - c of the first row) + L,
-    kReachG, kReachD,       // .. largest squared norm of dO and square of D,
-    kReachOneK, kReachOneV,  // .. squared norms of its first key and value row: what such rows weigh here;
+    kReachEdge,      // .. lowest (c - c of the first row) + L;
     kReachKeyNorm,   // and, for passes that cannot look at their keys by themselves (split kernels, fp32), the largest squared norm of its
-    kReachKeyHigh,   // .. key rows, their highest gate
-    kReachValue,     // .. and the largest squared norm of its value rows.
+    kReachKeyHigh,   // .. key rows (infinite where a value row is not finite), their highest gate.
     kReachLast,      // From the whole-tile dK/dV kernel on, in the first block of its 128-key tiles: the last block of queries that needs a key.
     kReachValues
 };
-// Bands up to this long are not looked at: only gates of more than 0.25 (fp32 0.37) a key would erase enough of them, and the look costs 2 to 5 %
-// (1 to 3 %) where it is in vain (whole step, us, whole bands / looked at: B2 H12/6 N2653 d64 w302 mu -2 66 / 69; fp32 B6 H13 N257 d128 mu -2
-// 104 / 107, B5 H2 N7686 d128 w289 mu -1 493 / 437).
-constexpr int shortest_reach(int d, size_t size) { return size == 2 ? few_backward(d) + 200 : kFewBackward + 132; }
-// Row of dalpha from which on block i has its values: its first, or for a last block of too few rows the 17th of the one before.
-__device__ __forceinline__ int reach_row(int i, int N) { return kReachRows * i + kReachValues <= N ? kReachRows * i : kReachRows * (i - 1) + 16; }
+// Bands up to this long are not looked at: only gates of more than 0.27 (fp32 0.4) a key would erase enough of them.  Backward, us, whole bands /
+// looked at, mu -6, -2, -1: B4 H16/4 N4096 d64 w512 161 / 163, 160 / 162, 155 / 130; H16 d128 w512 300 / 302, 298 / 302, 297 / 260; H16 d64 w700
+// 199 / 202, 196 / 200 (with 128 for kFewBackward), 193 / 135; fp32 H16 d64 w512 743 / 749, 739 / 745, 709 / 549.
+constexpr int shortest_reach(size_t size) { return kFewBackward + (size == 2 ? 412 : 278); }
+// Row of dalpha from which on block i has its values: its first, or for a last block of too few rows the ninth of the one before.
+__device__ __forceinline__ int reach_row(int i, int N) { return kReachRows * i + kReachValues <= N ? kReachRows * i : kReachRows * (i - 1) + 8; }
 
 // dalpha, if the passes of a backward may leave rows out and may use it as scratch, else nullptr.
 inline float* backward_reach(float* dalpha, const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* c, const float* L,
                              size_t size, int B, int H, int Hkv, int N, int d, int w, float scale) {
     const size_t rows = (size_t)B * H * N, gate = rows * sizeof(float), q = rows * d * size, kv = (size_t)B * Hkv * N * d * size;
-    bool free = scale > 0.f && (w < N ? w : N) > shortest_reach(d, size);
+    bool free = scale > 0.f && (w < N ? w : N) > shortest_reach(size);
     for (const void* m : {Q, O, dO}) free = free && !overlap(dalpha, gate, m, q);
     for (const void* m : {K, V}) free = free && !overlap(dalpha, gate, m, kv);
     for (const float* v : {c, L}) free = free && !overlap(dalpha, gate, v, gate);
     return free ? dalpha : nullptr;
 }
 
-// What the own rows of a tile are: (scale log2 e |row|)^2 of the largest, their edge relative to gate cbase in base-2 exponents (the lowest of
-// queries, the highest of keys), and what rows weigh here.
+// What the own rows of a tile are: (scale log2 e |row|)^2 of the largest, and their edge relative to gate cbase in base-2 exponents (the lowest of
+// queries, the highest of keys).
 struct OwnRows {
     float reach2, edge;
-    float q2, g2, d2;  // (of a key tile: those of the queries at the diagonal)
-    float k2, v2;      // (of a key tile: its own, 0 where the dQ pass looks by itself)
 };
 // Blocks i0 and i1 (the same, or next to each other) of queries.
 __device__ __forceinline__ OwnRows own_queries(const float* at, const float* ch, int i0, int i1, int N, float cbase, float sl) {
     const float *r0 = at + reach_row(i0, N), *r1 = at + reach_row(i1, N);
     const int norm = max(norm_bits(r0[kReachNorm]), norm_bits(r1[kReachNorm]));
     const int edge = min(lowest_order((ch[64 * i0] - cbase) + r0[kReachEdge]), lowest_order((ch[64 * i1] - cbase) + r1[kReachEdge]));
-    OwnRows own = {};
-    own.k2 = fmaxf(r0[kReachOneK], r1[kReachOneK]);
-    own.v2 = fmaxf(r0[kReachOneV], r1[kReachOneV]);
-    own.reach2 = reach2_of(norm, sl);
-    own.edge = from_order(edge) * kLog2e;
-    return own;
+    return {reach2_of(norm, sl), from_order(edge) * kLog2e};
 }
-// Blocks i0 and i1 of keys, and of queries at their diagonal.
+// Blocks i0 and i1 of keys.
 __device__ __forceinline__ OwnRows own_keys(const float* at, int i0, int i1, int N, float cbase, float sl) {
     const float *r0 = at + reach_row(i0, N), *r1 = at + reach_row(i1, N);
     const int norm = max(norm_bits(r0[kReachKeyNorm]), norm_bits(r1[kReachKeyNorm]));
     const int edge = max(highest_order(r0[kReachKeyHigh] - cbase), highest_order(r1[kReachKeyHigh] - cbase));
-    OwnRows own = {};
-    own.reach2 = reach2_of(norm, sl);
-    own.edge = from_order(edge) * kLog2e;
-    own.q2 = fmaxf(r0[kReachNorm], r1[kReachNorm]);
-    own.g2 = fmaxf(r0[kReachG], r1[kReachG]);
-    own.d2 = fmaxf(r0[kReachD], r1[kReachD]);
-    return own;
+    return {reach2_of(norm, sl), from_order(edge) * kLog2e};
 }
 // What block i of queries has to say to a key tile.
 struct QueryBlock {
-    float norm, edge, g, d, one_k, one_v, c;
+    float norm, edge, c;
 };
 __device__ __forceinline__ QueryBlock query_block(const float* at, const float* ch, int i, int N) {
     const float* r = at + reach_row(i, N);
-    return {r[kReachNorm], r[kReachEdge], r[kReachG], r[kReachD], r[kReachOneK], r[kReachOneV], ch[64 * i]};
+    return {r[kReachNorm], r[kReachEdge], ch[64 * i]};
 }
 __device__ __forceinline__ bool needs_keys(const QueryBlock& b, const OwnRows& own, float cbase) {
-    // dO in dV, dS of dO and D times Q in dK; and in these queries' dQ dS of V times K
-    const float here = fmaxf(outweighs(b.g, own.g2), outweighs(b.d, own.d2)) + outweighs(b.norm, own.q2);
-    const float there = outweighs(own.v2, b.one_v) + outweighs(own.k2, b.one_k);
-    return !is_erased(b.norm, own.reach2, ((b.c - cbase) + b.edge) * kLog2e - own.edge - kErased, fmaxf(here, there));
+    return !is_erased(b.norm, own.reach2, ((b.c - cbase) + b.edge) * kLog2e - own.edge - kErased);
 }
 // Last block of queries from i_hi down to i_min + 1 that needs one of the keys, else i_min.  at: of the head; first: block i_hi - lane, if
 // there is one.
@@ -276,19 +251,18 @@ __device__ __forceinline__ int last_needing_block(const float* at, const float* 
 }
 // What block i of keys has to say to a query tile.
 struct KeyValues {
-    float norm, high, value;
+    float norm, high;
 };
 __device__ __forceinline__ KeyValues key_values(const float* at, int i, int N) {
     const float* r = at + reach_row(i, N);
-    return {r[kReachKeyNorm], r[kReachKeyHigh], r[kReachValue]};
+    return {r[kReachKeyNorm], r[kReachKeyHigh]};
 }
 // First block of keys from i_lo on that is needed, i_max if none before it is.  first: block i_lo + lane, if there is one.
 __device__ __forceinline__ int first_needed_block(const float* at, int i_lo, int i_max, int N, const OwnRows& own, float cbase, int lane, KeyValues first) {
     for (int base = i_lo; base < i_max; base += 64) {
         const int i = base + lane;
         if (base != i_lo) first = key_values(at, min(i, i_max), N);
-        const float heavier = outweighs(first.norm, own.k2) + outweighs(first.value, own.v2);
-        const bool kept = i < i_max && !is_erased(first.norm, own.reach2, own.edge - kErased - (first.high - cbase) * kLog2e, heavier);
+        const bool kept = i < i_max && !is_erased(first.norm, own.reach2, own.edge - kErased - (first.high - cbase) * kLog2e);
         const unsigned long long mask = __builtin_amdgcn_ballot_w64(kept);
         if (mask) return base + __builtin_ctzll(mask);
     }
@@ -307,36 +281,29 @@ __device__ __forceinline__ int last_needing_block(const float* at, const float* 
 }
 // What a row-dot workgroup has gathered of a block, `row` its place (one thread).  looked: whether it has; else the block is kept.
 struct BlockValues {
-    int norm, edge, g, d, one_k, one_v, key_norm, high, value;
+    int norm, edge, key_norm, high;
 };
+constexpr BlockValues kNoRows = {0, 0x7fffffff, 0, (int)0x80000000};
 __device__ __forceinline__ void write_block(float* row, const BlockValues& b, bool looked, bool keys) {
     row[kReachNorm] = looked ? __int_as_float(b.norm) : INFINITY;
     row[kReachEdge] = looked ? from_order(b.edge) : 0.f;
-    row[kReachG] = looked ? __int_as_float(b.g) : 0.f;
-    row[kReachD] = looked ? __int_as_float(b.d) : 0.f;
-    row[kReachOneK] = looked ? __int_as_float(b.one_k) : 0.f;
-    row[kReachOneV] = looked ? __int_as_float(b.one_v) : 0.f;
     if (!keys) return;
     row[kReachKeyNorm] = looked ? __int_as_float(b.key_norm) : INFINITY;
     row[kReachKeyHigh] = looked ? from_order(b.high) : 0.f;
-    row[kReachValue] = looked ? __int_as_float(b.value) : 0.f;
 }
 // Over the workgroup, from all waves' lanes; at: of LDS.
 template <bool KEYS>
 __device__ __forceinline__ void gather_block(BlockValues* at, BlockValues b) {
-    if (threadIdx.x == 0) *at = {0, 0x7fffffff, 0, 0, b.one_k, b.one_v, 0, (int)0x80000000, 0};
-    b.norm = lanes_max(b.norm), b.edge = lanes_min(b.edge), b.g = lanes_max(b.g), b.d = lanes_max(b.d);
-    if (KEYS) b.key_norm = lanes_max(b.key_norm), b.high = lanes_max(b.high), b.value = lanes_max(b.value);
+    if (threadIdx.x == 0) *at = kNoRows;
+    b.norm = lanes_max(b.norm), b.edge = lanes_min(b.edge);
+    if (KEYS) b.key_norm = lanes_max(b.key_norm), b.high = lanes_max(b.high);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {
         atomicMax(&at->norm, b.norm);
         atomicMin(&at->edge, b.edge);
-        atomicMax(&at->g, b.g);
-        atomicMax(&at->d, b.d);
         if (KEYS) {
             atomicMax(&at->key_norm, b.key_norm);
             atomicMax(&at->high, b.high);
-            atomicMax(&at->value, b.value);
         }
     }
     __syncthreads();

@@ -41,7 +41,7 @@ constexpr float kPosBig = 1.0e30f;
 // 1. D_t = <O_t, dO_t>, and what the dK/dV kernel asks of a block of queries (band_reach.h)
 // ------------------------------------------------------------------------------------------
 // A workgroup takes 64 rows of a head, 16 bytes of each matrix a lane and all of them in flight.  Q is read only where the gate decays
-// enough over the window that keys may be erased for these rows.  kDotKeys, in front of the split kernels, which hold too few rows to look at the
+// enough over the window that keys may be erased for these rows.  KEYS, in front of the split kernels, which hold too few rows to look at the
 // other side for themselves: K and V as well.  reach: dalpha.
 template <int LPR>
 __device__ __forceinline__ float row_dot(const bf16x8& a, const bf16x8& b) {
@@ -103,15 +103,14 @@ __global__ __launch_bounds__(256) void rowdot_reach_bf16_kernel(const bf16_t* __
     }
     const float c0 = c[head + t0];
     const int far = max(0, t0 - w + 1), end = (int)min((long)N - 1, (long)t0 + kReachRows - 2 + w);
-    constexpr int few = KEYS ? kFewBackward : few_backward(D);
-    const bool look = reach_pays(c0 - c[head + far], t0 - far, few) || reach_pays(c[head + end] - c0, end - t0, few);
+    const bool look = reach_pays(c0 - c[head + far], t0 - far, kFewBackward) || reach_pays(c[head + end] - c0, end - t0, kFewBackward);
     if (look) {
         const size_t kv = (size_t)kv_head_of(bh, H, G) * N;
         auto norm_of = [&](const bf16_t* x) {
             const bf16x8 v = *reinterpret_cast<const bf16x8*>(x + 8 * part);
             return row_sum<LPR>(dot8(v, v, 0.f));
         };
-        BlockValues mine = {0, 0x7fffffff, 0, 0, norm_bits(norm_of(K + (kv + t0) * D)), norm_bits(norm_of(V + (kv + t0) * D)), 0, (int)0x80000000, 0};
+        BlockValues mine = kNoRows;
 #pragma unroll
         for (int p = 0; p < kPasses; ++p) {
             const int r = min(r0 + p * kRows, N - 1);
@@ -119,13 +118,10 @@ __global__ __launch_bounds__(256) void rowdot_reach_bf16_kernel(const bf16_t* __
             // (D is not finite if a value of dO is not)
             mine.norm = max(mine.norm, finite(dot[p]) ? norm_bits(norm_of(Q + row * D)) : kInfBits);
             mine.edge = min(mine.edge, lowest_order((c[row] - c0) + L[row]));
-            mine.g = max(mine.g, norm_bits(row_sum<LPR>(dot8(b[p], b[p], 0.f))));
-            mine.d = max(mine.d, norm_bits(dot[p] * dot[p]));
             if (KEYS) {
                 const float v2 = norm_of(V + (kv + r) * D);
                 mine.key_norm = max(mine.key_norm, finite(v2) ? norm_bits(norm_of(K + (kv + r) * D)) : kInfBits);
                 mine.high = max(mine.high, highest_order(c[row]));
-                mine.value = max(mine.value, norm_bits(v2));
             }
         }
         gather_block<KEYS>(&values, mine);
@@ -146,11 +142,10 @@ struct DkvSmem {
 
 // The last query tile (of 64) that a workgroup's 128 keys are streamed against: that of t_hi, or where the gate has erased all of them
 // before.  at: of the head (nullptr: t_hi's), needed: over_waves, keys: the wave's (or 16 of the 32 that two waves have in common).
-// Norms and gates of keys: the largest squared norm (infinite where a value row is not finite: its dP is not either), that of a value row, the
-// highest gate.
+// Norms and gates of keys: the largest squared norm (infinite where a value row is not finite: its dP is not either), the highest gate.
 struct KeyNorms {
     int norm;
-    float v2, high;
+    float high;
 };
 template <int D>
 struct KeyFragments {  // already there, a key's row in two lanes
@@ -167,7 +162,7 @@ struct KeyFragments {  // already there, a key's row in two lanes
         }
         v2 = xhalf_sum(v2);
         k2 = xhalf_sum(k2);
-        return {lanes_max(finite(v2) ? norm_bits(k2) : kInfBits), __int_as_float(lanes_max(norm_bits(v2))), g};
+        return {lanes_max(finite(v2) ? norm_bits(k2) : kInfBits), g};
     }
 };
 template <int D>
@@ -197,7 +192,7 @@ struct KeyRows {  // a row in four lanes
         }
         v2 = row_sum<4>(v2);
         k2 = row_sum<4>(k2);
-        return {lanes_max(finite(v2) ? norm_bits(k2) : kInfBits), __int_as_float(lanes_max(norm_bits(v2))), g};
+        return {lanes_max(finite(v2) ? norm_bits(k2) : kInfBits), g};
     }
 };
 template <int D, int WAVES, typename Keys>
@@ -206,23 +201,15 @@ __device__ __forceinline__ int last_query_tile(Keys keys, const float* ch, float
     const int i_hi = t_hi / kTileRows, k1 = min(k0 + 128, N) - 1, i_min = k1 / kTileRows;
     int last = i_hi;
     if (at == nullptr) return last;
-    if (i_hi > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1, few_backward(D))) {
+    if (i_hi > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1, kFewBackward)) {
         // All that the answer takes is requested at once, behind the first tiles: four trips to memory one behind the other in front of the first
         // product otherwise.  (Backward, us, one by one / at once: B4 H16 N8192 d128 w1024 mu -2 643 / 609, mu -1 542 / 508, H16/4 N4096 277 / 259.
         // In front of the branch, too, they would be for nothing where it is not taken: w256 mu -3 494 / 522.)
         keys.request();
-        const QueryBlock block = query_block(at, ch, max(i_hi - lane, i_min), N), here = query_block(at, ch, i_min, N),
-                         front = query_block(at, ch, k0 / kReachRows, N);
+        const QueryBlock block = query_block(at, ch, max(i_hi - lane, i_min), N);
         asm volatile("" ::: "memory");
         const KeyNorms n = keys.norms();
-        OwnRows own = {};
-        own.reach2 = reach2_of(n.norm, sl);
-        own.edge = from_order(lanes_max(highest_order(n.high - cbase))) * kLog2e;
-        own.k2 = __int_as_float(n.norm);
-        own.v2 = n.v2;
-        own.q2 = fmaxf(front.norm, here.norm);
-        own.g2 = fmaxf(front.g, here.g);
-        own.d2 = fmaxf(front.d, here.d);
+        const OwnRows own = {reach2_of(n.norm, sl), from_order(lanes_max(highest_order(n.high - cbase))) * kLog2e};
         const int needing = last_needing_block(at, ch, i_min, i_hi, N, own, cbase, lane, block);
         last = over_waves<WAVES, false>(needing, needed, wv, lane);
     }
@@ -1189,14 +1176,19 @@ static bool bwd_in_one_launch(int BH, int BHkv, int N, int d, int w) {
     return blocks <= 2 * cus && (G > 1 || chain <= 40 || 4 * blocks <= 7 * cus);
 }
 
-// Whether the split kernels look at the norms, which a row-dot launch of 4 us then takes for them: for bands that all but the slowest gates
-// erase in part.  Whole step, us, without / with, gates of mu = -6 (nothing erased), -3, -2:
-//   H1 N2000 d64 causal    36 /  38    35 /  39    35 /  33      H8 N2000 d128 causal   120 / 125   120 / 122   120 /  91
-//   H4 N8192 d64 w4096    192 / 198   189 / 106   189 /  73      H1 N16384 d128 w4096   246 / 251   247 / 138   246 /  96
-// Backward alone, gates of mu = -3, -2, -1:
-//   H8 N2048 d128 w1024    57 /  58    57 /  45    57 /  39      H8/2 N2048 d64 w1024    36 /  38    36 /  30    36 /  26
-//   H8 N2048 d128 w700     46 /  59    46 /  46    46 /  41      H8 N2048 d64 w1024      36 /  39    35 /  34    35 /  33  (these do not take it)
-static bool bwd_split_looks(int G, int N, int d, int w) { return (w < N ? w : N) >= (d == 128 || G > 1 ? 1000 : 1500); }
+// Whether the split kernels look at the norms, which a row-dot launch of 3 to 4 us then takes for them: where the keys beyond the first 500 that
+// can be left out take sixteen times as long, at the 450 TFLOP/s of these kernels, so that gates which erase nothing lose 3 % at most.
+// Backward, us, whole bands / looked at, gates of softplus(N(mu, 1)):            mu    -6          -3          -2          -1
+//   taken      H4   N8192  d64  w4096                                               144 / 148   142 / 74    142 / 47    142 / 39
+//              H1   N16384 d128 w4096                                               180 / 184   180 / 93    180 / 61    180 / 49
+//   not taken  H8   N2000  d128 causal                                               85 / 89     85 / 86     85 / 54     85 / 44
+//              H4   N4096  d128 w1500                                                75 / 79     74 / 79     74 / 55     74 / 43
+//              H8/2 N2048  d64  w1024                                                35 / 38     35 / 38     35 / 34     35 / 27
+//              H1   N2000  d64  causal                                               21 / 24     21 / 24     21 / 19     21 / 17
+static bool bwd_split_looks(int BH, int N, int d, int w) {
+    const double band = w < N ? w : N, mean = band - band * band / (2.0 * N);
+    return 10.0 * BH * N * d * (mean - kFewBackward - 500) > 450e6 * 64;
+}
 
 template <int D>
 static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO,
@@ -1230,7 +1222,7 @@ static hipError_t launch_bwd(const void* Q, const void* K, const void* V, const 
     // whole-tile dQ kernels.)
     const bool some_split = dkv_split || dq_split;
     float* reach = backward_reach(dalpha, Q, K, V, O, dO, c, L, sizeof(bf16_t), B, H, Hkv, N, D, w, scale);
-    if (some_split && !bwd_split_looks(H / Hkv, N, D, w)) reach = nullptr;
+    if (some_split && !bwd_split_looks(B * H, N, D, w)) reach = nullptr;
     const float* seen = dkv_split ? nullptr : reach;
     if (some_split && reach != nullptr) {
         rowdot_reach(std::true_type{}, reach, dq_split && !one_launch ? kKernDq : kKernDkv);  // (recorded with the pass that it is for)

@@ -1140,14 +1140,13 @@ __global__ __launch_bounds__(256) void rowdot_reach_f32_kernel(const float* __re
     const size_t head = (size_t)bh * N, kv = (size_t)kv_head_of(bh, H, G) * N;
     const int r0 = t0 + threadIdx.x / kLanes, col = 4 * (lane % kLanes);
     auto row_of = [&](int p) { return min(r0 + p * kRows, N - 1); };
-    float d[kPasses], g2[kPasses];
+    float d[kPasses];
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
         Step o, go;
         o.x[0] = *reinterpret_cast<const f32x4*>(O + (head + row_of(p)) * D + col);
         go.x[0] = *reinterpret_cast<const f32x4*>(dO + (head + row_of(p)) * D + col);
         d[p] = o.dot(go.x[0], 0);
-        g2[p] = go.dot(go.x[0], 0);
         if (r0 + p * kRows < N && lane % kLanes == 0) Dv[head + row_of(p)] = d[p];
     }
     const float* ch = c + head;
@@ -1159,18 +1158,15 @@ __global__ __launch_bounds__(256) void rowdot_reach_f32_kernel(const float* __re
             x.x[0] = *reinterpret_cast<const f32x4*>(row + col);
             return x.dot(x.x[0], 0);
         };
-        BlockValues mine = {0, 0x7fffffff, 0, 0, norm_bits(norm_of(K + (kv + t0) * D)), norm_bits(norm_of(V + (kv + t0) * D)), 0, (int)0x80000000, 0};
+        BlockValues mine = kNoRows;
 #pragma unroll
         for (int p = 0; p < kPasses; ++p) {
             const int row = row_of(p);
             const float v2 = norm_of(V + (kv + row) * D);
             mine.norm = max(mine.norm, finite(d[p]) ? norm_bits(norm_of(Q + (head + row) * D)) : kInfBits);
             mine.edge = min(mine.edge, lowest_order((ch[row] - ch[t0]) + L[head + row]));
-            mine.g = max(mine.g, norm_bits(g2[p]));
-            mine.d = max(mine.d, norm_bits(d[p] * d[p]));
             mine.key_norm = max(mine.key_norm, finite(v2) ? norm_bits(norm_of(K + (kv + row) * D)) : kInfBits);
             mine.high = max(mine.high, highest_order(ch[row]));
-            mine.value = max(mine.value, norm_bits(v2));
         }
         gather_block<true>(&values, mine);
     }

@@ -81,27 +81,27 @@ __global__ __launch_bounds__(64) void key_reach_kernel(const T* __restrict__ K, 
 
 // Whether a forward looks at the reach of its keys, by what blocks, and what a tile has to save.
 // A tile's band has to lose 100 keys that tiles and blocks do not divide (steps of 32 or 64 keys, 64-key blocks, the tile's own queries), and
-// as many as the forward streams while the pass reads K and V (few); for the launch and its trips to memory one behind the other, 7 us, the
-// problem has to pay as well.  A launch in which no tile asks costs 2 to 3 us, so there is one only where a gate of softplus(N(-2, 1)), 0.19 a key,
-// would save 6 us, and where one of softplus(N(-3, 1)), 0.077, pays too or the forward is of 45 us and more.
+// as many as the forward streams while the pass reads K and V (few).  A launch in which no tile asks costs 2 to 3 us: there is one where the keys
+// beyond these and the first 500, which only gates above 0.2 a key erase, take sixteen times as long, so that slow gates lose 4 % at most.
 // (Times at the rates of large problems, with fewer than two tiles a CU accordingly less, at least half.)
-// Whole bands / with the launch, us, gates of softplus(N(mu, 1)):                mu    -3          -2          -1         0.5
-//   taken      B4 H16   N4096 d64  w700                                             61 / 65     61 / 56     59 / 48    58 / 46
-//              B4 H16/4 N8192 d64  w512                                            101 / 106   101 / 89     98 / 70    97 / 62
-//              B1 H32   N4096 d128 w1024                                            75 / 78     74 / 59     71 / 51    70 / 48
-//              B1 H32   N4096 d128 w700 fp32                                       278 / 278   279 / 217   277 / 176  282 / 150
-//   not taken  B1 H32/8 N2048 d128 w1024                                            36 / 40     35 / 29     34 / 24    34 / 23
-//              B4 H16   N4096 d64  w512                                             54 / 57     54 / 55     52 / 47    53 / 44
-//              B1 H32   N2048 d64  w1024                                            25 / 27     24 / 23     24 / 21    24 / 19
-//              B1 H8    N2048 d128 w1024                                            18 / 23     17 / 18     17 / 17    17 / 16
+// Whole bands / with the launch, us, gates of softplus(N(mu, 1)):                mu    -6          -3          -2          -1
+//   taken      B1 H8    N5003  d128 w3000                                           52 / 55     52 / 56     52 / 46     53 / 39
+//              B1 H12   N6000  d128 w4096                                          117 / 119   113 / 82    114 / 69    114 / 58
+//              B1 H4    N16384 d128 w4096                                          139 / 142   134 / 76    135 / 49    136 / 38
+//              B2 H16   N4096  d128 w1024 fp32                                     344 / 347   345 / 347   348 / 301   349 / 210
+//   not taken  B4 H16   N4096  d64  w1024                                           79 / 82     79 / 82     76 / 72     75 / 56
+//              B1 H32   N4096  d128 w1024                                           76 / 78     75 / 78     73 / 73     72 / 57
+//              B1 H20   N3000  d128 causal                                          61 / 63     60 / 65     59 / 50     58 / 43
+//              B1 H12   N4096  d64  causal                                          41 / 43     41 / 44     41 / 33     41 / 28
+//              B4 H16/4 N8192  d64  w512                                            99 / 102    99 / 102    98 / 100    93 / 84
+//              B1 H32   N4096  d128 w700 fp32                                      263 / 266   262 / 266   263 / 272   265 / 210
 static KeyReach reach_of(int B, int H, int Hkv, int N, int d, int w, bool bf16) {
     const double band = w < N ? w : N, mean = band - band * band / (2.0 * N), rows = (double)B * H * N;
     const double tiles = rows / (128 * 512), fill = tiles < 0.5 ? 0.5 : tiles < 1 ? tiles : 1;
     const double rate = bf16 ? d == 128 ? 900e6 : 700e6 : 150e6;  // FLOP/us
     const double per_key = 4 * rows * d / rate / fill;            // us for a key of the band
-    const double few = 100 + 2.0 * B * Hkv * N * d * (bf16 ? 2 : 4) / 6.2e6 / per_key, pays = per_key * (mean - few) - 7;
-    if (pays - per_key * (49 / 0.19) < 6) return {0, 0};
-    if (pays - per_key * (49 / 0.077) < 0 && per_key * mean < 45) return {0, 0};
+    const double few = 100 + 2.0 * B * Hkv * N * d * (bf16 ? 2 : 4) / 6.2e6 / per_key;
+    if (per_key * (mean - few - 500) < 40) return {0, 0};
     long block = 64;
     while (((long)band + block) / block + 1 > 64) block *= 2;  // (an entry for each lane of a wave)
     return {(int)block, (int)few};
