@@ -121,17 +121,15 @@ template <int WAVES>
 __device__ __forceinline__ int run_start(int base, int wv, int r, int lane) { return base + (wv * (kScanRuns / WAVES) + r) * 256 + 4 * lane; }
 
 // A workgroup takes segment blockIdx.x % P of row blockIdx.x / P, seg_len logical positions long, and starts from the sum of the
-// row's earlier segments: from `partial` (scan-then-propagate), or, where that is nullptr, from the row itself (scan_rows_alone).
-template <bool REVERSE, int MODE, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __restrict__ a,
-                                                                 const float* __restrict__ b,
-                                                                 float* __restrict__ out, int N, float eps,
-                                                                 const double* __restrict__ partial,
-                                                                 int seg_len, int P, bool by_runs) {
+// row's earlier segments: from `partial` (scan-then-propagate), or, ALONE, from the row itself (scan_rows_alone).
+template <bool REVERSE, int MODE, int WAVES, bool ALONE>
+__device__ __forceinline__ void scan_rows(const float* __restrict__ a, const float* __restrict__ b, float* __restrict__ out, int N, float eps,
+                                          const double* __restrict__ partial, int seg_len, int P, bool by_runs) {
     constexpr int RUNS = kScanRuns / WAVES;
     __shared__ double wave_tot[2][WAVES];
-    const int seg = (int)(blockIdx.x % P);
-    const size_t row = (size_t)(blockIdx.x / P) * N;
+    // (a row that is one workgroup's does not wait for the divisions, 0.1 us: B2 H8/2 N515 d64 step 35.1 / 35.0)
+    const int seg = P > 1 ? (int)(blockIdx.x % P) : 0;
+    const size_t row = (size_t)(P > 1 ? blockIdx.x / P : blockIdx.x) * N;
     const int begin = seg * seg_len, end = min(N, begin + seg_len);
     const float* ar = a + row;
     const float* br = MODE != kScanPlain ? b + row : nullptr;
@@ -145,14 +143,15 @@ __global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __re
     };
     load(begin);
     double carry = 0.0;
-    if (partial != nullptr && seg > 0) {  // sum of the earlier segments of this row, fp64, in every wave by itself
+    if (!ALONE && partial != nullptr && seg > 0) {  // sum of the earlier segments of this row, fp64, in every wave by itself
         const double* pr = partial + (size_t)(blockIdx.x / P) * P;
         double acc = 0.0;
         for (int q = lane; q < seg; q += 64) acc += pr[q];
         carry = wave_sum(acc);
-    } else if (seg > 0) {
+    }
+    if (ALONE && seg > 0) {
         // of its elements: fp32 over four and fp64 across, as segment_sum_kernel, or (by_runs) fp32 over runs and fp64 across, as a whole row
-        // in one workgroup, so that either call's prefix does not depend on the way it is formed
+        // in one workgroup: the prefix of a call without a workspace does not depend on the way it is formed
         double acc = 0.0;
         constexpr int U = 4 / RUNS > 1 ? 4 / RUNS : 1;  // chunks in flight
         for (int base = 0; base < begin; base += U * kScanChunk) {
@@ -220,6 +219,19 @@ __global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __re
             }
         }
     }
+}
+
+template <bool REVERSE, int MODE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void scan_rows_kernel(const float* __restrict__ a, const float* __restrict__ b, float* __restrict__ out, int N,
+                                                                 float eps, const double* __restrict__ partial, int seg_len, int P) {
+    scan_rows<REVERSE, MODE, WAVES, false>(a, b, out, N, eps, partial, seg_len, P, false);
+}
+// (A kernel of its own: the loads in flight for the row in front take 23 registers, with which one workgroup of 16 waves is left of two on a CU.
+// With the activation, us, one kernel for both / two: 1000 rows of 16384 34.4 / 31.6, 1024 of 12000 28.0 / 24.9, 300 of 65536 51.8 / 47.4.)
+template <bool REVERSE, int MODE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void scan_rows_alone_kernel(const float* __restrict__ a, const float* __restrict__ b, float* __restrict__ out,
+                                                                       int N, float eps, int P, bool by_runs) {
+    scan_rows<REVERSE, MODE, WAVES, true>(a, b, out, N, eps, nullptr, kScanChunk, P, by_runs);
 }
 
 // Phase 1 of scan-then-propagate (App. "Preprocessing via Scan-Then-Propagate"): the sum of every
@@ -297,15 +309,21 @@ static void launch_scan(const float* a, const float* b, float* out, int rows, in
     if (partial == nullptr) {
         // (out over an input: the segments behind still need what the ones in front overwrite)
         const size_t bytes = (size_t)rows * N * sizeof(float);
-        const bool alone = scan_rows_alone(MODE == kScanGate, rows, N) && !overlap(out, bytes, a, bytes) && !(b != nullptr && overlap(out, bytes, b, bytes));
-        seg_len = alone ? kScanChunk : N;
-        P = alone ? (N + kScanChunk - 1) / kScanChunk : 1;
+        if (scan_rows_alone(MODE == kScanGate, rows, N) && !overlap(out, bytes, a, bytes) && !(b != nullptr && overlap(out, bytes, b, bytes))) {
+            constexpr int kWaves = MODE == kScanGate ? 16 : 4;  // (scan_four_waves of one chunk and few workgroups)
+            P = (N + kScanChunk - 1) / kScanChunk;
+            hipLaunchKernelGGL((scan_rows_alone_kernel<REVERSE, MODE, kWaves>), dim3((unsigned)(rows * P)), dim3(64 * kWaves), 0, s, a, b, out, N, eps, P,
+                               by_runs);
+            return;
+        }
+        seg_len = N;
+        P = 1;
     }
     const unsigned wgs = (unsigned)(rows * P);
     if (scan_four_waves(MODE == kScanGate, P > 1, wgs, seg_len))
-        hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 4>), dim3(wgs), dim3(256), 0, s, a, b, out, N, eps, partial, seg_len, P, by_runs);
+        hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 4>), dim3(wgs), dim3(256), 0, s, a, b, out, N, eps, partial, seg_len, P);
     else
-        hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 16>), dim3(wgs), dim3(1024), 0, s, a, b, out, N, eps, partial, seg_len, P, by_runs);
+        hipLaunchKernelGGL((scan_rows_kernel<REVERSE, MODE, 16>), dim3(wgs), dim3(1024), 0, s, a, b, out, N, eps, partial, seg_len, P);
 }
 template <bool REVERSE, int MODE>
 static void launch_segment_sum(const float* a, const float* b, double* partial, int rows, int N, float eps, int seg_len, int P, hipStream_t s) {

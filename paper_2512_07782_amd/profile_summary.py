@@ -38,13 +38,13 @@ import sys
 # demangled kernel name (template arguments kept) -> the name bench.py and the library's profile use
 LIB = {
     "segment_sum_kernel<false, 0>": "scan_segment_sum",
-    "scan_rows_kernel<false, 0>": "gate_prefix_scan",
+    "scan_rows_kernel<false, 0>": "gate_prefix_scan", "scan_rows_alone_kernel<false, 0>": "gate_prefix_scan",
     "fwd_bf16_kernel<128>": "forward",
     "rowdot_bf16_kernel<128>": "bwd_rowdot", "rowdot_reach_bf16_kernel": "bwd_rowdot", "rowdot_reach_f32_kernel": "bwd_rowdot",
     "bwd_dkv8_bf16_kernel<128, true>": "bwd_dkv",
     "bwd_dq_spill_bf16_kernel<128>": "bwd_dq",
     "segment_sum_kernel<true, 1>": "gate_grad_segment_sum",
-    "scan_rows_kernel<true, 1>": "gate_grad_scan",
+    "scan_rows_kernel<true, 1>": "gate_grad_scan", "scan_rows_alone_kernel<true, 1>": "gate_grad_scan",
     # the other head dimension and the backward with its minimum workspace
     "fwd_bf16_kernel<64>": "forward",
     "rowdot_bf16_kernel<64>": "bwd_rowdot",
@@ -136,7 +136,7 @@ def kernel_trace(kt_dir: str, log: str, bench_args: str = "--no-cpu-baseline --p
         "kernel_stats.csv (all launches of the run: the warm-up steps and the first steps after the calibration loops,",
         "slower while the clocks settle, are in rocprofv3's average), next to the average bench.py measured with HIP",
         "events around the launches of its breakdown pass in the same run.",
-        "scan_rows_kernel<reverse, input> / segment_sum_kernel<reverse, input>: input 0 = one tensor, 1 = difference of two",
+        "scan_rows[_alone]_kernel<reverse, input> / segment_sum_kernel<reverse, input>: input 0 = one tensor, 1 = difference of two",
         "tensors.  probe_* are the calibration loops (matrix cores with constant / pseudo-random operands / attention mix, copy).",
         "",
         f"{'kernel':36s} {'calls':>5s} {'avg us':>9s} {'min us':>9s} {'max us':>9s} {'% time':>7s} {'bench.py avg us':>16s}",

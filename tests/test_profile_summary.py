@@ -70,3 +70,4 @@ def test_names_that_the_profiler_leaves_mangled():
     assert ps.short(name) == "bwd_dkv8_bf16_kernel<128, false>" and ps.lib_name(ps.short(name)) == "bwd_dkv"
     assert ps.short("_ZN4gfwa16key_reach_kernelILi64EDF16bEEvPKT0_S3_PKfPS1_iiii") == "key_reach_kernel<64, bf16>"
     assert ps.short(K["fwd"]) == "fwd_bf16_kernel<128>"
+    assert [ps.lib_name(f"scan_rows_alone_kernel<{a}, 4>") for a in ("false, 0", "true, 1")] == ["gate_prefix_scan", "gate_grad_scan"]
