@@ -20,8 +20,9 @@ namespace gfwa {
 
 constexpr float kPosBig = 1.0e30f;
 
-// ---- D_t = <O_t, dO_t>, dQ, row sums of dS.  Workgroup `block` of the pass.
-template <int D, int NW, int QW, int KB, int RING>
+// ---- D_t = <O_t, dO_t>, dQ, row sums of dS.  Workgroup `block` of the pass.  LOOK, here and below: a.reach is there.  (Short problems never have it, and a
+// look that is compiled in costs them: step B2 H8/2 N515 d64 w512 35.2 / 35.0 us.)
+template <int D, int NW, int QW, int KB, int RING, bool LOOK>
 __device__ __forceinline__ void dq_split(const BwdBf16& a, int num_qtiles, int block) {
     using Band = SplitBand<D, NW, QW, KB, RING>;
     constexpr int KC = D / 16, DB = D / 32, KW = Band::KW;
@@ -60,7 +61,7 @@ __device__ __forceinline__ void dq_split(const BwdBf16& a, int num_qtiles, int b
     const float dt = xhalf_sum(dsum);
     if (band.kg == 0 && h == 0 && t < N) Dv[(size_t)bh * N + t] = dt;
     int first = max(0, q0 - w + 1);
-    if (a.reach != nullptr && reach_pays(band.cbase - band.ch[first], q0 - first, kFewBackward)) {  // the keys that the gate has erased for all queries stay out
+    if (LOOK && reach_pays(band.cbase - band.ch[first], q0 - first, kFewBackward)) {  // the keys that the gate has erased for all queries stay out
         const float* at = a.reach + (size_t)bh * N;
         first = max(first, 64 * first_needed_block(at, band.ch, first / 64, q0 / 64, (min(N, q0 + 32 * QW) - 1) / 64, N, band.cbase, sl, lane));
         band.from(__builtin_amdgcn_readfirstlane(first), q0, w);
@@ -163,9 +164,9 @@ __device__ __forceinline__ void dq_split(const BwdBf16& a, int num_qtiles, int b
         dQ + head_off + (size_t)q0 * D, N - q0);
 }
 
-template <int D, int NW, int QW, int KB, int RING>
+template <int D, int NW, int QW, int KB, int RING, bool LOOK>
 __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void bwd_dq_split_bf16_kernel(BwdBf16 a, int num_qtiles) {
-    dq_split<D, NW, QW, KB, RING>(a, num_qtiles, (int)blockIdx.x);
+    dq_split<D, NW, QW, KB, RING, LOOK>(a, num_qtiles, (int)blockIdx.x);
 }
 
 // ---- dK, dV (summed over the query heads of a group), column sums of dS per query head.  OWN_D: D_t is formed here too, from
@@ -185,7 +186,7 @@ struct DkvSplitSmem {
     float col[NW][kDkvSplitMaxGroup][32];
 };
 
-template <int D, int NW, bool OWN_D>
+template <int D, int NW, bool OWN_D, bool LOOK>
 __device__ __forceinline__ void dkv_split(const BwdBf16& a, int block) {
     constexpr int KC = D / 16, DB = D / 32;
     extern __shared__ __align__(256) char smem_raw[];
@@ -207,7 +208,7 @@ __device__ __forceinline__ void dkv_split(const BwdBf16& a, int block) {
     // 32-query blocks that see one of the keys, of every query head of the group in turn; wave wv takes every NW-th
     const int qb_lo = k0 >> 5, t_hi = (int)min((long)N - 1, (long)k0 + 31 + w - 1);
     int nblk = (t_hi >> 5) - qb_lo + 1;
-    if (a.reach != nullptr) {  // up to the last that one of the heads needs: the gate has erased the keys for those behind it
+    if constexpr (LOOK) {  // up to the last that one of the heads needs: the gate has erased the keys for those behind it
         const int k1 = min(k0 + 32, N) - 1, i_min = k1 / 64;
         int last = i_min;
         for (int g = 0; g < G && last < t_hi / 64; ++g) {
@@ -391,31 +392,34 @@ __device__ __forceinline__ void dkv_split(const BwdBf16& a, int block) {
     }
 }
 
-template <int D, int NW>
+template <int D, int NW, bool LOOK>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void bwd_dkv_split_bf16_kernel(BwdBf16 a) {
-    dkv_split<D, NW, false>(a, (int)blockIdx.x);
+    dkv_split<D, NW, false, LOOK>(a, (int)blockIdx.x);
 }
 
 // Both passes in one launch, for problems of few workgroups: one after the other each leaves most of the chip idle and pays for its own
 // launch.  The first dkv_blocks workgroups, the longer chains, are the dK/dV pass.  Every workgroup asks for the LDS of the larger half, about
 // 140 KB, so one is resident on a CU, and a second round starts behind the shortest of the first.
-template <int D, int NW>
+template <int D, int NW, bool LOOK>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 2 : 1) void bwd_both_split_bf16_kernel(BwdBf16 a, int dkv_blocks, int num_qtiles) {
-    if ((int)blockIdx.x < dkv_blocks) dkv_split<D, NW, true>(a, (int)blockIdx.x);
-    else dq_split<D, NW, 2, 1, 2>(a, num_qtiles, (int)blockIdx.x - dkv_blocks);
+    if ((int)blockIdx.x < dkv_blocks) dkv_split<D, NW, true, LOOK>(a, (int)blockIdx.x);
+    else dq_split<D, NW, 2, 1, 2, LOOK>(a, num_qtiles, (int)blockIdx.x - dkv_blocks);
 }
 
-template <int D, int NW, int QW, int KB, int RING>
-static hipError_t launch_dq_split(const BwdBf16& a, hipStream_t s) {
+template <int D, int NW, int QW, int KB, int RING, bool LOOK>
+static hipError_t launch_dq_split_as(const BwdBf16& a, hipStream_t s) {
     using Smem = SplitBandSmem<D, NW, QW, KB, RING>;
+    constexpr auto kernel = bwd_dq_split_bf16_kernel<D, NW, QW, KB, RING, LOOK>;
     static DeviceOnce lds_allowed;
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dq_split_bf16_kernel<D, NW, QW, KB, RING>),
-                                         sizeof(Smem), lds_allowed))
-        return e;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), sizeof(Smem), lds_allowed)) return e;
     const int nq = (a.N + 32 * QW - 1) / (32 * QW), BH = a.B * a.H;
     ProfScope prof(kKernDq, s);
-    hipLaunchKernelGGL((bwd_dq_split_bf16_kernel<D, NW, QW, KB, RING>), dim3((unsigned)BH * nq), dim3(64 * NW), sizeof(Smem), s, a, nq);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)BH * nq), dim3(64 * NW), sizeof(Smem), s, a, nq);
     return hipGetLastError();
+}
+template <int D, int NW, int QW, int KB, int RING>
+static hipError_t launch_dq_split(const BwdBf16& a, hipStream_t s) {
+    return a.reach != nullptr ? launch_dq_split_as<D, NW, QW, KB, RING, true>(a, s) : launch_dq_split_as<D, NW, QW, KB, RING, false>(a, s);
 }
 
 hipError_t bwd_dq_split_bf16(FwdSplit shape, const BwdBf16& a, int d, hipStream_t s) {
@@ -427,37 +431,39 @@ hipError_t bwd_dq_split_bf16(FwdSplit shape, const BwdBf16& a, int d, hipStream_
     return launch_dq_split<64, 4, 1, 1, 2>(a, s);
 }
 
-template <int D, int NW>
+template <int D, int NW, bool LOOK>
 static hipError_t launch_dkv_split(const BwdBf16& a, hipStream_t s) {
     using Smem = DkvSplitSmem<D, NW>;
+    constexpr auto kernel = bwd_dkv_split_bf16_kernel<D, NW, LOOK>;
     static DeviceOnce lds_allowed;
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_dkv_split_bf16_kernel<D, NW>), sizeof(Smem), lds_allowed))
-        return e;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), sizeof(Smem), lds_allowed)) return e;
     ProfScope prof(kKernDkv, s);
-    hipLaunchKernelGGL((bwd_dkv_split_bf16_kernel<D, NW>), dim3((unsigned)(a.B * a.Hkv) * ((a.N + 31) / 32)), dim3(64 * NW),
-                       sizeof(Smem), s, a);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(a.B * a.Hkv) * ((a.N + 31) / 32)), dim3(64 * NW), sizeof(Smem), s, a);
     return hipGetLastError();
 }
 
 hipError_t bwd_dkv_split_bf16(const BwdBf16& a, int d, hipStream_t s) {
-    return d == 128 ? launch_dkv_split<128, 4>(a, s) : launch_dkv_split<64, 8>(a, s);
+    if (a.reach != nullptr) return d == 128 ? launch_dkv_split<128, 4, true>(a, s) : launch_dkv_split<64, 8, true>(a, s);
+    return d == 128 ? launch_dkv_split<128, 4, false>(a, s) : launch_dkv_split<64, 8, false>(a, s);
 }
 
-template <int D, int NW>
+template <int D, int NW, bool LOOK>
 static hipError_t launch_both_split(const BwdBf16& a, hipStream_t s) {
     using DkvSmem = DkvSplitSmem<D, NW>;
     using DqSmem = SplitBandSmem<D, NW, 2, 1, 2>;
     constexpr size_t lds = sizeof(DkvSmem) > sizeof(DqSmem) ? sizeof(DkvSmem) : sizeof(DqSmem);
+    constexpr auto kernel = bwd_both_split_bf16_kernel<D, NW, LOOK>;
     static DeviceOnce lds_allowed;
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_both_split_bf16_kernel<D, NW>), lds, lds_allowed)) return e;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, lds_allowed)) return e;
     const int nq = (a.N + 63) / 64, nk = a.B * a.Hkv * ((a.N + 31) / 32);
     ProfScope prof(kKernDkv, s);
-    hipLaunchKernelGGL((bwd_both_split_bf16_kernel<D, NW>), dim3((unsigned)(nk + a.B * a.H * nq)), dim3(64 * NW), lds, s, a, nk, nq);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(nk + a.B * a.H * nq)), dim3(64 * NW), lds, s, a, nk, nq);
     return hipGetLastError();
 }
 
 hipError_t bwd_both_split_bf16(const BwdBf16& a, int d, hipStream_t s) {
-    return d == 128 ? launch_both_split<128, 4>(a, s) : launch_both_split<64, 8>(a, s);
+    if (a.reach != nullptr) return d == 128 ? launch_both_split<128, 4, true>(a, s) : launch_both_split<64, 8, true>(a, s);
+    return d == 128 ? launch_both_split<128, 4, false>(a, s) : launch_both_split<64, 8, false>(a, s);
 }
 
 }  // namespace gfwa

@@ -27,7 +27,9 @@
 
 namespace gfwa {
 
-template <int D, int NW, int QW, int KB, int RING>
+// LOOK: whether reach is there.  (Short problems never have it, and a look that is compiled in costs them: B1 H32/8 N700 d128 w1024, with the gate's
+// scan, 19.2 / 19.1 us.)
+template <int D, int NW, int QW, int KB, int RING, bool LOOK>
 __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_split_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const float* __restrict__ c, bf16_t* __restrict__ O, float* __restrict__ L, int N, int w, float scale_log2,
@@ -56,7 +58,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_split
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) GFWA_PIN(qf[kc]);
     const int k_lo = max(0, q0 - w + 1);
-    if (reach.block != 0 && reach_pays(band.cbase - band.ch[k_lo], q0 - k_lo, reach.few))  // what the gate has erased for all queries stays out
+    if (LOOK && reach_pays(band.cbase - band.ch[k_lo], q0 - k_lo, reach.few))  // what the gate has erased for all queries stays out
         band.from(forward_reach<D, NW>(qf, K + kv_off + (size_t)tc * D + 8 * h, key_block<D>(O + head_off + (size_t)q0 * D, min(32 * QW, N - q0), lane), cq,
                                        q0, k_lo, reach.block, band.cbase, sl, sm.needed, band.wv, lane),
                   q0, w);
@@ -177,18 +179,19 @@ template <int D, int NW, int QW, int KB, int RING>
 static hipError_t launch_split(const void* Q, const void* K, const void* V, const float* c, void* O, float* L, int B,
                                int H, int Hkv, int N, int w, float scale, hipStream_t s) {
     using Smem = SplitBandSmem<D, NW, QW, KB, RING>;
-    static DeviceOnce lds_allowed;
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&fwd_split_bf16_kernel<D, NW, QW, KB, RING>), sizeof(Smem),
-                                         lds_allowed))
-        return e;
     const int nq = (N + 32 * QW - 1) / (32 * QW);
     ProfScope prof(kKernForward, s);
     KeyReach reach;
     if (hipError_t e = key_reach(reach, 32 * QW, true, Q, K, V, c, O, B, H, Hkv, N, D, w, scale, s)) return e;
-    hipLaunchKernelGGL((fwd_split_bf16_kernel<D, NW, QW, KB, RING>), dim3((unsigned)(B * H) * nq), dim3((64 * NW)), sizeof(Smem),
-                       s, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, c, (bf16_t*)O, L, N, w, scale * kLog2e, nq,
-                       B * H, H, H / Hkv, reach);
-    return hipGetLastError();
+    auto with = [&](auto look) -> hipError_t {
+        constexpr auto kernel = fwd_split_bf16_kernel<D, NW, QW, KB, RING, decltype(look)::value>;
+        static DeviceOnce lds_allowed;
+        if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), sizeof(Smem), lds_allowed)) return e;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(B * H) * nq), dim3((64 * NW)), sizeof(Smem), s, (const bf16_t*)Q, (const bf16_t*)K,
+                           (const bf16_t*)V, c, (bf16_t*)O, L, N, w, scale * kLog2e, nq, B * H, H, H / Hkv, reach);
+        return hipGetLastError();
+    };
+    return reach.block != 0 ? with(std::true_type{}) : with(std::false_type{});
 }
 
 hipError_t forward_split_bf16(FwdSplit shape, const void* Q, const void* K, const void* V, const float* c, void* O,
