@@ -198,13 +198,16 @@ struct KeyRows {  // a row in four lanes
 template <int D, int WAVES, typename Keys>
 __device__ __forceinline__ int last_query_tile(Keys keys, const float* ch, float* at, int k0, int t_hi, int N, float cbase, float sl, int* needed,
                                                int wv, int lane) {
+    if (at == nullptr) return t_hi / kTileRows;
+    // (all of it formed here, not carried through the tile loops of a group's heads in registers that these need)
+    GFWA_PIN(lane);
+    asm volatile("" : "+s"(k0), "+s"(t_hi), "+s"(N));
     const int i_hi = t_hi / kTileRows, k1 = min(k0 + 128, N) - 1, i_min = k1 / kTileRows;
     int last = i_hi;
-    if (at == nullptr) return last;
     if (i_hi > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1, kFewBackward)) {
         // All that the answer takes is requested at once, behind the first tiles: four trips to memory one behind the other in front of the first
-        // product otherwise.  (Backward, us, one by one / at once: B4 H16 N8192 d128 w1024 mu -2 643 / 609, mu -1 542 / 508, H16/4 N4096 277 / 259.
-        // In front of the branch, too, they would be for nothing where it is not taken: w256 mu -3 494 / 522.)
+        // product otherwise, 5 to 7 % of a shortened backward.  (In front of the branch, too, they would be for nothing where it is not taken: 5 % of
+        // one with whole short bands.)
         keys.request();
         const QueryBlock block = query_block(at, ch, max(i_hi - lane, i_min), N);
         asm volatile("" ::: "memory");
