@@ -287,8 +287,7 @@ static bool scan_four_waves(bool activation, bool segment, long workgroups, int 
 }
 // Few rows of three chunks or more go in segments of one chunk that each add up the row before them by themselves: one launch, no scratch,
 // the row read (P + 1) / 2 times out of the L2.  Up to a workgroup a CU, with the activation, which is formed again as often, three on four, and
-// 16 segments.  Scan-then-propagate, a launch more, pays against one workgroup a row from 7 chunks on (5 with the activation), against
-// this from 9 (5).  us, one workgroup a row / scan-then-propagate / this:
+// 16 segments.  us, one workgroup a row / scan-then-propagate / this:
 //               1 row of 12000    16384            32768            65536             32 rows of 12000   16384            24576            32768
 //   plain       4.5 / 8.1 / 4.1   5.4 / 8.0 / 4.3  9.3 / 8.1 / 6.1  17.1 / 8.1 / 9.9   5.0 / 8.4 / 4.3   5.9 / 8.4 / 4.6   7.9 / 8.5 / 5.8  10.0 / 8.6 /  8.2
 //   activation  5.8 / 8.1 / 5.7   7.2 / 8.1 / 6.2 12.7 / 8.1 / 9.6  23.7 / 8.2 / 15.9  6.3 / 8.4 / 6.2   7.7 / 8.5 / 6.8  10.5 / 8.6 / 9.6  13.5 / 8.8 / 14.9
@@ -299,17 +298,23 @@ static bool scan_rows_alone(bool activation, int rows, int N) {
     const int P = (N + kScanChunk - 1) / kScanChunk;
     return P >= 3 && P <= 16 && (activation ? 4 : 3) * (long)rows * P <= 3L * device_cu_count();
 }
-static bool scan_in_two_launches(bool activation, int rows, int N) {
+// Whether scan-then-propagate, and the gate gradient of few rows, which sum up the chunks in front of a segment by fours in fp64, take this instead of
+// their two launches: up to 8 chunks, 4 with the activation.  (One workgroup a row is faster than two launches up to 6 chunks, too, but sums
+// chunks up by runs in fp32, the coarser: against fp64, d(alpha) of B4 H16 N8192 d128 w1024 2.0e-6 by fours, 2.3e-6 by runs.)
+static bool scan_in_one_launch(bool activation, int rows, int N) {
     const int P = (N + kScanChunk - 1) / kScanChunk;
-    return P > (activation ? 4 : scan_rows_alone(false, rows, N) ? 8 : 6);
+    return P == 1 || (P <= (activation ? 4 : 8) && scan_rows_alone(activation, rows, N));
+}
+// (out over an input: the segments behind still need what the ones in front overwrite)
+static bool scan_in_place(const float* a, const float* b, const float* out, int rows, int N) {
+    const size_t bytes = (size_t)rows * N * sizeof(float);
+    return overlap(out, bytes, a, bytes) || (b != nullptr && overlap(out, bytes, b, bytes));
 }
 template <bool REVERSE, int MODE>
 static void launch_scan(const float* a, const float* b, float* out, int rows, int N, float eps, const double* partial, int seg_len,
                         int P, bool by_runs, hipStream_t s) {
     if (partial == nullptr) {
-        // (out over an input: the segments behind still need what the ones in front overwrite)
-        const size_t bytes = (size_t)rows * N * sizeof(float);
-        if (scan_rows_alone(MODE == kScanGate, rows, N) && !overlap(out, bytes, a, bytes) && !(b != nullptr && overlap(out, bytes, b, bytes))) {
+        if (scan_rows_alone(MODE == kScanGate, rows, N) && !scan_in_place(a, b, out, rows, N)) {
             constexpr int kWaves = MODE == kScanGate ? 16 : 4;  // (scan_four_waves of one chunk and few workgroups)
             P = (N + kScanChunk - 1) / kScanChunk;
             hipLaunchKernelGGL((scan_rows_alone_kernel<REVERSE, MODE, kWaves>), dim3((unsigned)(rows * P)), dim3(64 * kWaves), 0, s, a, b, out, N, eps, P,
@@ -364,7 +369,7 @@ size_t gate_scan_workspace_bytes(int rows, int N) {
 
 hipError_t gate_prefix_stp(const float* in, const float* beta, float eps, float* c, double* partial, int rows,
                            int N, hipStream_t s) {
-    if (!scan_in_two_launches(beta != nullptr, rows, N)) {
+    if (scan_in_one_launch(beta != nullptr, rows, N) && (N <= kScanChunk || !scan_in_place(in, beta, c, rows, N))) {
         ProfScope prof(beta != nullptr ? kKernGateActPrefix : kKernGatePrefix, s);
         if (beta != nullptr) launch_scan<false, kScanGate>(in, beta, c, rows, N, eps, nullptr, 0, 1, false, s);
         else launch_scan<false, kScanPlain>(in, nullptr, c, rows, N, 0.f, nullptr, 0, 1, false, s);
@@ -441,7 +446,7 @@ hipError_t gate_activation_backward(const float* hpre, const float* beta, float 
 // Few long rows leave most of the chip idle with one workgroup per row: then the rows are cut into segments
 // (scan-then-propagate, as gate_prefix_stp does for the forward prefix), which needs `partial`.
 bool gate_grad_scan_wants_segments(int rows, int N) {
-    return rows < device_cu_count() && scan_in_two_launches(false, rows, N);
+    return rows < device_cu_count() && N >= 2 * kScanChunk && !scan_in_one_launch(false, rows, N);
 }
 
 hipError_t gate_grad_scan(const float* dc_col, const float* dc_row, float* dalpha, double* partial, int rows, int N,

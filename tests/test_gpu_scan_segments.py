@@ -50,3 +50,16 @@ def test_prefix_over_its_input(g, act):
     over = x.clone()
     got = call(over, over)
     assert (got - want).abs().max() <= 4e-7 * want.max()
+
+
+@pytest.mark.parametrize("rows,N", [(64, 8192), (100, 20000), (32, 16384), (300, 12288)])
+def test_chunks_in_front_are_summed_up_by_fours(g, rows, N):
+    # scan-then-propagate starts a chunk of 4096 from the sum of those in front, fp32 over four elements and fp64 across, however many launches it
+    # takes: its first element is that sum plus one, rounded once (1000 rows of which a workgroup takes two chunks may do otherwise)
+    note("sums by fours", rows, N)
+    alpha = torch.nn.functional.softplus(torch.randn((1, rows, N), generator=torch.Generator(device=par.DEV).manual_seed(5), device=par.DEV) - 1)
+    c = g.gfwa_gate_prefix_stp(alpha)
+    a = alpha[0].cpu()
+    fours = a[:, :4096].reshape(rows, -1, 4)
+    front = ((fours[..., 0] + fours[..., 1]) + (fours[..., 2] + fours[..., 3])).double().sum(-1)
+    assert torch.equal(c[0, :, 4096].cpu(), (front + a[:, 4096].double()).float())
