@@ -421,7 +421,7 @@ def main() -> int:
     f_fwd = wl.flops_fwd_nominal()
     f_bwd = wl.flops_bwd_nominal() if wl.backward else 0.0
     bhn = B * H * N
-    # algorithmic work per launch of each kernel
+    # algorithmic work per launch of each kernel: every product of the window and every input once, whatever the gate has erased (kernel_work below)
     algo = {
         "gate_prefix_scan": ("hbm", 8.0 * bhn),
         "forward": ("mfma", f_fwd),
@@ -489,6 +489,13 @@ def main() -> int:
                         "serves as run-in: the part needs about 25 steps to settle after a change of load; kernels.*: "
                         "the library's event pair around every launch in that pass (a few microseconds of overhead "
                         "each, visible on the ~10 us scans)")
+    span = (c[..., min(w, N) - 1:] - c[..., :N - min(w, N) + 1]).float()   # what the gate takes off a score over a whole window
+    detail["gate_decay_over_window"] = {"mean": round(span.mean().item(), 1), "max": round(span.max().item(), 1)}
+    detail["kernel_work"] = ("kernels.* and roofline, achieved and frac: nominal, every product of the window counted and every input and "
+                             "output once.  Blocks of keys that the gate has brought below 2^-127 (a decay of 88 and what scores add, about 15 to "
+                             "20 here) are not computed, so these are rates of the hardware only where gate_decay_over_window stays below that; the "
+                             "forward's record includes the launch that takes the norms of the keys, and where the gate decays enough to ask for "
+                             "them the row dots read Q as well (split kernels and fp32: K and V, too)")
     if power is not None:
         detail["power"] = power
     if achievable and bf:   # the probes are bf16 loops

@@ -79,7 +79,9 @@ int gfwa_gate_activation_prefix(const float *hpre, const float *beta, float eps,
  * The same prefix by scan-then-propagate (paper App. "Preprocessing via Scan-Then-Propagate"): every row
  * is cut into segments, one launch sums the segments (recomputing the activation), a second one scans
  * each segment starting from the fp64 sum of the segments before it.  It reads the inputs twice and is
- * meant for few, very long rows, where one workgroup per row leaves the chip idle.
+ * meant for few, very long rows, where one workgroup per row leaves the chip idle.  Rows of up to 4096, and few
+ * rows of up to 32768 (16384 with the activation) on which every segment can sum up those before it by itself,
+ * take one launch, which leaves the workspace alone and forms the sums alike.
  * in: [B,H,N] fp32 - alpha when beta is NULL (eps ignored), else the pre-activation h with beta [B,H,N]
  * as in gfwa_gate_activation_prefix.  c: [B,H,N] fp32 out.  workspace: device scratch of at least
  * gfwa_gate_scan_workspace_bytes(B, H, N) bytes, 8-byte aligned, contents undefined before and after.
@@ -107,7 +109,11 @@ int gfwa_gate_activation_backward(const float *hpre, const float *beta, float ep
  *   O_t  = sum_i softmax_i(S_ti) v_i
  *   L_t  = log sum_i exp(S_ti)                  (natural log; what Alg. 2 returns as m + log l)
  *
- * The N x N matrix is never formed; key tiles wholly outside the band are skipped.
+ * The N x N matrix is never formed; key tiles wholly outside the band are skipped, and so are those at its
+ * far end whose weights are shown to lie below 2^-127 of their rows' (less than any normal fp32 number), where
+ * the gate's decay outweighs what scores can add: results are those of the whole band, but the time of
+ * forward and backward depends on the gate.  While they run, rows of O (dalpha in gfwa_backward) hold
+ * intermediate values, unless they lie over an input.
  * `scale` multiplies q.k only (1/sqrt(d) in the paper's workloads), never the bias.
  * Q,K,V: [B,H,N,d] of dtype `dt`;  c: [B,H,N] fp32 (from gfwa_gate_prefix);
  * O: [B,H,N,d] of dtype `dt`, out;  L: [B,H,N] fp32, out.   d in {64, 128}.
@@ -219,8 +225,11 @@ int gfwa_version(void);
  * 0 gate prefix scan, 1 forward, 2 backward row-dot (D), 3 backward dK/dV, 4 backward dQ,
  * 5 gate-gradient reverse scan, 6 gate activation + prefix scan, 7 gate activation backward,
  * 8 decoding step (per-chunk partials), 9 decoding step (merge of the chunks), 10 and 11 the two
- * launches of gfwa_gate_prefix_stp (segment sums, scan of the segments), 12 the segment sums of the
+ * launches of gfwa_gate_prefix_stp (segment sums, scan of the segments; one launch is id 0, with the activation
+ * id 6), 12 the segment sums of the
  * gate-gradient scan when the backward cuts few long rows into segments (its scan is then id 5).
+ * A launch that takes the norms of the keys in front of the forward is part of id 1; in front of the split
+ * kernels of small bf16 backwards the one that takes them is part of the pass behind it, id 4 or 3.
  * Where both passes of the backward go in one launch (fp32, and small bf16 problems) id 3 is that launch and
  * id 4 stays empty; the row dots of small fp32 problems, and of small bf16 ones, are part of the same record.
  * gfwa_profile_kernel_name gives the same as text.
