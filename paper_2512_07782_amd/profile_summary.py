@@ -48,10 +48,9 @@ LIB = {
     # the other head dimension and the backward with its minimum workspace
     "fwd_bf16_kernel<64>": "forward",
     "rowdot_bf16_kernel<64>": "bwd_rowdot",
-    "bwd_dkv_bf16_kernel<64>": "bwd_dkv",
-    "bwd_dq_bf16_kernel<64>": "bwd_dq",
+    "bwd_dkv_bf16_kernel": "bwd_dkv",
+    "bwd_dq_bf16_kernel": "bwd_dq",
     "bwd_dkv8_bf16_kernel<128, false>": "bwd_dkv",
-    "bwd_dq_bf16_kernel<128>": "bwd_dq",
     "fwd_two_blocks_bf16_kernel": "forward",  # d = 128, few workgroups on a CU
     # few or uneven tiles
     "fwd_split_bf16_kernel": "forward", "bwd_dkv_split_bf16_kernel": "bwd_dkv", "bwd_dq_split_bf16_kernel": "bwd_dq",
