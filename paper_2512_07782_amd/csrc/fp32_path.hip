@@ -512,7 +512,9 @@ __device__ __forceinline__ int f32_fwd_tile(int block, int heads, int tiles, int
     return by_length && (D == 64 || !short_band) ? tiles - 1 - tile : tile;
 }
 
-template <int D, int NW, int S>
+// LOOK, here and in the backward: reach is there.  (A look that is compiled in costs problems that never take it up to 2 %: B5 H7 N9536 d64 w58
+// backward 304 / 299 us.)
+template <int D, int NW, int S, bool LOOK>
 __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) void fwd_f32_mfma_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ c, float* __restrict__ O, float* __restrict__ L, int N, int w, float scale,
@@ -531,7 +533,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 && NW == 4 && S == 2 ? 1 : 2) voi
 
     const int k_lo = max(0, q0 - w + 1), jb_hi = (min(N, q0 + BQ) - 1) / 32;
     int first_key = k_lo;
-    if (reach.block != 0 && reach_pays(ch[q0] - ch[k_lo], q0 - k_lo, reach.few)) {  // the keys that the gate has erased for all queries stay out
+    if (LOOK && reach_pays(ch[q0] - ch[k_lo], q0 - k_lo, reach.few)) {  // the keys that the gate has erased for all queries stay out
         float q2 = 0.f, k2 = 0.f, own = 0.f;
         const float *qr = Q + ho + (size_t)tc * D + 4 * h, *kr = Kh + (size_t)tc * D + 4 * h;  // (the halves take every other four columns)
 #pragma unroll 8
@@ -686,7 +688,7 @@ __device__ __forceinline__ int next3(int i) { return i == 2 ? 0 : i + 1; }
 
 // dQ and the row sums of dS (Alg. 3, query loop): the forward's layout.  S^T = K Q^T (wave 0 of a pair) and
 // dP^T = V dO^T (wave 1), then both take half of the block's keys: dS^T = P^T (dP^T - D), dQ^T += K^T dS^T.
-template <int D, int NP>
+template <int D, int NP, bool LOOK>
 __device__ __forceinline__ void dq_f32_mfma(
     int block, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO,
     const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dQ,
@@ -707,7 +709,7 @@ __device__ __forceinline__ void dq_f32_mfma(
         const float *Kh = K + kvo, *Vh = V + kvo, *ch = c + (size_t)bh * N;
 
         int first_key = max(0, q0 - w + 1);
-        if (reach != nullptr && reach_pays(ch[q0] - ch[first_key], q0 - first_key, kFewBackward)) {  // the keys that the gate has erased for all queries stay out
+        if (LOOK && reach_pays(ch[q0] - ch[first_key], q0 - first_key, kFewBackward)) {  // the keys that the gate has erased for all queries stay out
             const float* at = reach + (size_t)bh * N;
             first_key = max(first_key, 64 * first_needed_block(at, ch, first_key / 64, q0 / 64, (min(N, q0 + 32 * NP) - 1) / 64, N, ch[q0], scale * kLog2e, lane));
         }
@@ -874,7 +876,7 @@ __device__ __forceinline__ void dq_f32_mfma(
 // dK, dV (summed over the G query heads of a group) and, per query head, the column sums of dS (Alg. 3, key loop): a
 // workgroup owns 32 NP keys, a pair of waves 32 of them, a lane one key.  S = Q K^T (wave 0) and dP = dO V^T (wave 1) with
 // 32-query tiles of Q and dO from LDS, then dV^T += dO^T P (wave 0) and, a block later, dK^T += Q^T dS (wave 1).
-template <int D, int NP>
+template <int D, int NP, bool LOOK>
 __device__ __forceinline__ void dkv_f32_mfma(
     int block, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO,
     const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dK,
@@ -904,7 +906,7 @@ __device__ __forceinline__ void dkv_f32_mfma(
             const size_t rows = (size_t)(bh0 + g) * N;
             const float* ch = c + rows;
             const int k1 = min(k0 + 32 * NP, N) - 1, i_min = k1 / 64;
-            if (reach != nullptr && t_hi / 64 > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1, kFewBackward)) {
+            if (LOOK && t_hi / 64 > i_min && reach_pays(ch[t_hi] - ch[k1], t_hi - k1, kFewBackward)) {
                 qb_hi = min(qb_hi, 2 * last_needing_block(reach + rows, ch, k0 / 64, i_min, t_hi / 64, N, ch[k0], scale * kLog2e, lane) + 1);
             }
             return __builtin_amdgcn_readfirstlane(qb_hi) - qb_lo + 1;
@@ -1098,15 +1100,15 @@ __device__ __forceinline__ void dkv_f32_mfma(
 // B2 H8/2 N515 d64 181 / 150, B2 H16 N1000 d128 causal 236 / 176, B2 H16 N4096 d128 w1024 1108 / 1065.
 // Both passes deal out their tiles by length, whatever the shape: over 1557 shapes 1.00 to 1.02 of the time of the best order in every
 // class of them, one head after another 1.0 to 1.19 (B1 H2 N10498 d128 w1236 326 -> 308).
-template <int D, int NP>
+template <int D, int NP, bool LOOK>
 __global__ __launch_bounds__(128 * NP, NP == 4 ? 1 : 2) void bwd_f32_mfma_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, const float* __restrict__ dO,
     const float* __restrict__ c, const float* __restrict__ L, const float* __restrict__ Dv, float* __restrict__ dQ, float* __restrict__ dK,
     float* __restrict__ dV, float* __restrict__ dc_col, float* __restrict__ dc_row, const float* __restrict__ reach, int N, int w, float scale,
     int tiles_per_head, int dkv_tiles, int dq_tiles, int H, int G) {
     const int b = (int)blockIdx.x;
-    if (b < dkv_tiles) dkv_f32_mfma<D, NP>(b, Q, K, V, dO, c, L, Dv, dK, dV, dc_col, reach, N, w, scale, tiles_per_head, dkv_tiles, H, G);
-    else dq_f32_mfma<D, NP>(b - dkv_tiles, Q, K, V, dO, c, L, Dv, dQ, dc_row, reach, N, w, scale, tiles_per_head, dq_tiles, H, G);
+    if (b < dkv_tiles) dkv_f32_mfma<D, NP, LOOK>(b, Q, K, V, dO, c, L, Dv, dK, dV, dc_col, reach, N, w, scale, tiles_per_head, dkv_tiles, H, G);
+    else dq_f32_mfma<D, NP, LOOK>(b - dkv_tiles, Q, K, V, dO, c, L, Dv, dQ, dc_row, reach, N, w, scale, tiles_per_head, dq_tiles, H, G);
 }
 
 // ---- D_t = <O_t, dO_t>
@@ -1128,7 +1130,7 @@ __global__ __launch_bounds__(256) void rowdot_f32_kernel(const float* __restrict
 // edge of the queries and the highest gate of the keys, where the gate decays enough that they are asked for.  A value row or a D that
 // is not finite keeps its block.  reach: dalpha.
 template <int D>
-__global__ __launch_bounds__(256) void rowdot_reach_f32_kernel(const float* __restrict__ O, const float* __restrict__ dO,
+__global__ __launch_bounds__(256, 4) void rowdot_reach_f32_kernel(const float* __restrict__ O, const float* __restrict__ dO,
                                                                const float* __restrict__ Q, const float* __restrict__ K,
                                                                const float* __restrict__ V, const float* __restrict__ c,
                                                                const float* __restrict__ L, float* __restrict__ Dv, float* __restrict__ reach,
@@ -1140,18 +1142,22 @@ __global__ __launch_bounds__(256) void rowdot_reach_f32_kernel(const float* __re
     const size_t head = (size_t)bh * N, kv = (size_t)kv_head_of(bh, H, G) * N;
     const int r0 = t0 + threadIdx.x / kLanes, col = 4 * (lane % kLanes);
     auto row_of = [&](int p) { return min(r0 + p * kRows, N - 1); };
+    const float* ch = c + head;
+    const int far = max(0, t0 - w + 1), end = (int)min((long)N - 1, (long)t0 + kReachRows - 2 + w);
+    // (all of them requested before the first is used: a workgroup alone on its CU waits for them one after another otherwise, 13 us)
+    Step o[kPasses], go[kPasses];
+#pragma unroll
+    for (int p = 0; p < kPasses; ++p) {
+        o[p].x[0] = *reinterpret_cast<const f32x4*>(O + (head + row_of(p)) * D + col);
+        go[p].x[0] = *reinterpret_cast<const f32x4*>(dO + (head + row_of(p)) * D + col);
+    }
+    const bool look = reach_pays(ch[t0] - ch[far], t0 - far, kFewBackward) || reach_pays(ch[end] - ch[t0], end - t0, kFewBackward);
     float d[kPasses];
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
-        Step o, go;
-        o.x[0] = *reinterpret_cast<const f32x4*>(O + (head + row_of(p)) * D + col);
-        go.x[0] = *reinterpret_cast<const f32x4*>(dO + (head + row_of(p)) * D + col);
-        d[p] = o.dot(go.x[0], 0);
+        d[p] = o[p].dot(go[p].x[0], 0);
         if (r0 + p * kRows < N && lane % kLanes == 0) Dv[head + row_of(p)] = d[p];
     }
-    const float* ch = c + head;
-    const int far = max(0, t0 - w + 1), end = (int)min((long)N - 1, (long)t0 + kReachRows - 2 + w);
-    const bool look = reach_pays(ch[t0] - ch[far], t0 - far, kFewBackward) || reach_pays(ch[end] - ch[t0], end - t0, kFewBackward);
     if (look) {
         auto norm_of = [&](const float* row) {
             Step x;
@@ -1226,15 +1232,21 @@ static bool f32_use_mfma(bool backward, int B, int H, int Hkv, int N, int d, int
 template <int D, int NW, int S>
 static hipError_t launch_fwd_f32_mfma(const float* Q, const float* K, const float* V, const float* c, float* O, float* L, int B,
                                       int H, int Hkv, int N, int w, float scale, hipStream_t s) {
-    static DeviceOnce lds_allowed;
     constexpr size_t lds = sizeof(F32FwdSmem<D, S>);
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&fwd_f32_mfma_kernel<D, NW, S>), lds, lds_allowed)) return e;
     const int nq = (N + 32 * NW - 1) / (32 * NW), total = B * H * nq;
-    KeyReach reach;
-    if (hipError_t e = key_reach(reach, 32 * NW, false, Q, K, V, c, O, B, H, Hkv, N, D, w, scale, s)) return e;
-    hipLaunchKernelGGL((fwd_f32_mfma_kernel<D, NW, S>), dim3(total), dim3(64 * NW), lds, s, Q, K, V, c, O, L, N, w, scale, nq, total,
-                       H, H / Hkv, reach);
-    return hipGetLastError();
+    KeyReach reach = {0, 0};
+    if constexpr (S == 2)  // (short sequences and bands never look)
+        if (hipError_t e = key_reach(reach, 32 * NW, false, Q, K, V, c, O, B, H, Hkv, N, D, w, scale, s)) return e;
+    auto with = [&](auto look) -> hipError_t {
+        constexpr auto kernel = fwd_f32_mfma_kernel<D, NW, S, decltype(look)::value>;
+        static DeviceOnce lds_allowed;
+        if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, lds_allowed)) return e;
+        hipLaunchKernelGGL(kernel, dim3(total), dim3(64 * NW), lds, s, Q, K, V, c, O, L, N, w, scale, nq, total, H, H / Hkv, reach);
+        return hipGetLastError();
+    };
+    if constexpr (S == 2)
+        if (reach.block != 0) return with(std::true_type{});
+    return with(std::false_type{});
 }
 
 template <int D, int LOADS>
@@ -1320,11 +1332,9 @@ template <int D, int NP>
 static hipError_t launch_bwd_f32_mfma(const float* Q, const float* K, const float* V, const float* O, const float* dO, const float* c,
                                       const float* L, float* Dv, float* dQ, float* dK, float* dV, float* dc_col, float* dc_row, float* reach,
                                       int B, int H, int Hkv, int N, int w, float scale, hipStream_t s) {
-    static DeviceOnce lds_allowed;
     constexpr size_t lds = sizeof(F32BwdSmem<D, NP>);
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&bwd_f32_mfma_kernel<D, NP>), lds, lds_allowed)) return e;
     const int nt = (N + 32 * NP - 1) / (32 * NP);
-    reach = backward_reach(reach, Q, K, V, O, dO, c, L, sizeof(float), B, H, Hkv, N, D, w, scale);
+    reach = NP == 4 ? backward_reach(reach, Q, K, V, O, dO, c, L, sizeof(float), B, H, Hkv, N, D, w, scale) : nullptr;  // (64-row tiles are for short bands)
     {
         ProfScope prof(kKernRowDot, s);
         const int blocks = (N + kReachRows - 1) / kReachRows;
@@ -1333,12 +1343,20 @@ static hipError_t launch_bwd_f32_mfma(const float* Q, const float* K, const floa
             hipLaunchKernelGGL((rowdot_reach_f32_kernel<D>), dim3((unsigned)(B * H) * blocks), dim3(256), 0, s, O, dO, Q, K, V, c, L, Dv, reach, N, w,
                                blocks, H, H / Hkv);
     }
-    ProfScope prof(kKernDkv, s);
-    launch_passes((long)B * Hkv * nt, (long)B * H * nt, 128 * NP, [&](int dkv_tiles, int blocks) {
-        hipLaunchKernelGGL((bwd_f32_mfma_kernel<D, NP>), dim3(blocks), dim3(128 * NP), lds, s, Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row,
-                           reach, N, w, scale, nt, dkv_tiles, blocks - dkv_tiles, H, H / Hkv);
-    });
-    return hipGetLastError();
+    auto with = [&](auto look) -> hipError_t {
+        constexpr auto kernel = bwd_f32_mfma_kernel<D, NP, decltype(look)::value>;
+        static DeviceOnce lds_allowed;
+        if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds, lds_allowed)) return e;
+        ProfScope prof(kKernDkv, s);
+        launch_passes((long)B * Hkv * nt, (long)B * H * nt, 128 * NP, [&](int dkv_tiles, int blocks) {
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(128 * NP), lds, s, Q, K, V, dO, c, L, Dv, dQ, dK, dV, dc_col, dc_row, reach, N, w, scale, nt,
+                               dkv_tiles, blocks - dkv_tiles, H, H / Hkv);
+        });
+        return hipGetLastError();
+    };
+    if constexpr (NP == 4)
+        if (reach != nullptr) return with(std::true_type{});
+    return with(std::false_type{});
 }
 
 template <int D>
