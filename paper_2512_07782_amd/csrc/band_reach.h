@@ -189,10 +189,10 @@ enum : int {
     kReachLast,      // From the whole-tile dK/dV kernel on, in the first block of its 128-key tiles: the last block of queries that needs a key.
     kReachValues
 };
-// Bands up to this long are not looked at: only gates of more than 0.27 (fp32 0.4) a key would erase enough of them.  Backward, us, whole bands /
-// looked at, mu -6, -2, -1: B4 H16/4 N4096 d64 w512 161 / 163, 160 / 162, 155 / 130; H16 d128 w512 300 / 302, 298 / 302, 297 / 260; H16 d64 w700
-// 199 / 202, 196 / 200 (with 128 for kFewBackward), 193 / 135; fp32 H16 d64 w512 743 / 749, 739 / 745, 709 / 549.
-constexpr int shortest_reach(size_t size) { return kFewBackward + (size == 2 ? 412 : 278); }
+// Bands of up to this many keys, on average over the queries, are not looked at: of shorter ones only gates above 0.27 a key would erase enough, and a
+// look in vain costs 1 to 2 % of the backward.  us, whole bands / looked at, mu -6, -2, -1: B4 H16/4 N4096 d64 w512 161 / 163, 160 / 162, 155 / 130;
+// H16 d128 w512 300 / 302, 298 / 302, 297 / 260; H16 d64 w700 199 / 202, 196 / 196, 193 / 134 (that one is looked at).
+constexpr double kShortestMean = 600;
 // Row of dalpha from which on block i has its values: its first, or for a last block of too few rows the ninth of the one before.
 __device__ __forceinline__ int reach_row(int i, int N) { return kReachRows * i + kReachValues <= N ? kReachRows * i : kReachRows * (i - 1) + 8; }
 
@@ -200,7 +200,8 @@ __device__ __forceinline__ int reach_row(int i, int N) { return kReachRows * i +
 inline float* backward_reach(float* dalpha, const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* c, const float* L,
                              size_t size, int B, int H, int Hkv, int N, int d, int w, float scale) {
     const size_t rows = (size_t)B * H * N, gate = rows * sizeof(float), q = rows * d * size, kv = (size_t)B * Hkv * N * d * size;
-    bool free = scale > 0.f && (w < N ? w : N) > shortest_reach(size);
+    const double band = w < N ? w : N;
+    bool free = scale > 0.f && band - band * band / (2.0 * N) > kShortestMean;
     for (const void* m : {Q, O, dO}) free = free && !overlap(dalpha, gate, m, q);
     for (const void* m : {K, V}) free = free && !overlap(dalpha, gate, m, kv);
     for (const float* v : {c, L}) free = free && !overlap(dalpha, gate, v, gate);
