@@ -489,8 +489,9 @@ def main() -> int:
                         "serves as run-in: the part needs about 25 steps to settle after a change of load; kernels.*: "
                         "the library's event pair around every launch in that pass (a few microseconds of overhead "
                         "each, visible on the ~10 us scans)")
-    span = (c[..., min(w, N) - 1:] - c[..., :N - min(w, N) + 1]).float()   # what the gate takes off a score over a whole window
-    detail["gate_decay_over_window"] = {"mean": round(span.mean().item(), 1), "max": round(span.max().item(), 1)}
+    if not args.no_cpu_baseline:   # (profiler runs take the reading of a result for the calibration copy)
+        span = c[..., min(w, N) - 1:] - c[..., :N - min(w, N) + 1]   # what the gate takes off a score over a whole window
+        detail["gate_decay_over_window"] = {"mean": round(span.mean().item(), 1), "max": round(span.max().item(), 1)}
     detail["kernel_work"] = ("kernels.* and roofline, achieved and frac: nominal, every product of the window counted and every input and "
                              "output once.  Blocks of keys that the gate has brought below 2^-127 (a decay of 88 and what scores add, about 15 to "
                              "20 here) are not computed, so these are rates of the hardware only where gate_decay_over_window stays below that; the "
