@@ -4,7 +4,9 @@
 // A key whose score then lies more than 127 binary orders (kErased: 126, the smallest normal fp32 number, and one for the roundings of scores
 // and references) below the reference of a row has no part in it:
 //   backward  p = exp2(x - L) is exactly zero: exp2 returns zero for every argument below -126 (measured over -120 .. -151), and then every
-//             product it enters is zero.  No bit of a gradient changes.
+//             product it enters is zero.  No bit of a gradient changes.  (The split dK/dV kernels add up the column sums of a band's last block
+//             rounded otherwise, so that a shorter band may move d(alpha) by such roundings, 5e-7 of its largest value, and deal the blocks that
+//             are left of grouped heads out to their waves anew, another order of additions.)
 //   forward   the row's reference is at least the score of its own key.  Where the whole band is measured against it (whole-tile kernels of bf16)
 //             p is exactly zero again.  The split and the fp32 kernels form partial sums against references of their own first, in which far
 //             keys weigh more, and scale them afterwards; so the line moves on by the doublings of the largest value row there, and

@@ -215,9 +215,12 @@ def test_far_rows_that_are_not_finite(g, oracle, B, H, Hkv, N, d, w, dtype, mu, 
         assert bad("dK", earlier) and (which == "Q" or bad("dV", earlier))
 
 
-@pytest.mark.parametrize("B,H,N,d,w,dtype", [(3, 6, 6001, 128, 3500, "bf16"), (1, 4, 6146, 128, 4001, "bf16"), (4, 8, 4097, 64, 3000, "bf16"), (1, 8, 2177, 128, 1600, "f32")])
+@pytest.mark.parametrize("B,H,N,d,w,dtype", [(3, 6, 6001, 128, 3500, "bf16"), (1, 4, 6146, 128, 4001, "bf16"), (4, 8, 4097, 64, 3000, "bf16"), (1, 1, 12801, 128, 8000, "bf16"),
+                                             (1, 2, 12000, 64, 12000, "bf16"), (1, 1, 10990, 64, 10990, "bf16"), (1, 8, 2177, 128, 1600, "f32"),
+                                             (1, 8, 4100, 64, 3000, "f32"), (2, 16, 2305, 128, 1500, "f32")])
 def test_outputs_over_inputs(g, oracle, B, H, N, d, w, dtype):
-    # outputs serve as scratch in front of the kernels, unless they lie over an input that is still read
+    # outputs serve as scratch in front of the kernels, unless they lie over an input that is still read: then the bands stay whole, and the
+    # results are the same bit for bit
     note("outputs over inputs", B, H, N, d, w, dtype)
     wl, ins = inputs(B, H, H, N, d, w, dtype, -1.0)
     c = g.gfwa_gate_prefix(dev(ins["alpha"], "f32"))
@@ -230,6 +233,10 @@ def test_outputs_over_inputs(g, oracle, B, H, N, d, w, dtype):
         x = {"c": c.clone(), "L": L.clone()}
         grads = g.gfwa_backward(t["Q"], t["K"], t["V"], O, t["dO"], x["c"], x["L"], w, wl.scale, dalpha=x[name])
         for k, got in zip(("dQ", "dK", "dV", "dalpha"), grads):
-            # the column sums of the last block of a band may be contracted differently, half an ulp each (2^-24 of 16 here), and
-            # dalpha adds up thousands of them: a random walk of 1e-4 at most, of values up to 15
-            assert rel_inf(host(got), host(want[k])) <= (2e-5 if k == "dalpha" else 1e-6), (name, k)
+            # What is left out is exactly zero in the backward.  (The split dK/dV kernels, here those with d = 64 and one or two heads, round the
+            # products of a band's last block before they add them to the column sums, the other blocks' together with the sum: half an ulp
+            # each, 2^-24 of 16 here, of which dalpha adds up thousands: a random walk of 1e-4 at most, of values up to 15.)
+            if k == "dalpha" and d == 64 and H < 4:
+                assert rel_inf(host(got), host(want[k])) <= 2e-5, (name, k)
+            else:
+                assert torch.equal(got, want[k]), (name, k, rel_inf(host(got), host(want[k])))
